@@ -27,6 +27,9 @@
 #include "conv_dgrad_bf16x6.hpp"
 #include "conv_wgrad_bf16x6.hpp"
 #include "conv_wgrad_s1_bf16x6.hpp"
+#include "conv_band.hpp"
+#include "conv_bytes.hpp"
+#include "conv_band_f32.hpp"
 
 using namespace ga3c;
 
@@ -36,7 +39,6 @@ typedef ConvSpec<float, 16, 20, 20, 32, 4, 2> SpecS2;     // small net, conv2
 typedef ConvSpec<uint8_t, 4, 84, 84, 32, 8, 4> SpecL1;    // large net, conv1
 typedef ConvSpec<float, 32, 20, 20, 64, 4, 2> SpecL2;     // large net, conv2
 typedef ConvSpec<float, 64, 9, 9, 64, 3, 1> SpecL3;       // large net, conv3
-typedef ConvSpec<float, 32, 20, 20, 32, 4, 2> SpecP2;     // the paper's larger-network family (Sec. 5), stride-4 member, conv2
 // 16-byte vectors of a small-net fragment buffer: the filters of conv1 / conv2 for the fused forward kernel, then
 // those of conv2 for its input-gradient kernel
 constexpr int CFRAG_FWD_VECS = 3 * C12_FRAG_SET, CFRAG_VECS = CFRAG_FWD_VECS + ConvDgradBf16Geom<SpecS2>::FRAG_VECS;
@@ -143,6 +145,11 @@ struct ga3c_ctx {
     // larger net: the filters of conv2 and conv3 of each parameter copy as ready-made fragments for the forward and the
     // input-gradient kernels (LFRAG_* give the parts); rebuilt by whoever writes the copy
     u32x4 *lfrag[2];
+    // layers on the any-size kernels of conv_band.hpp and conv_bytes.hpp: which ones, where their fragments sit in the
+    // buffer of each parameter copy (in vectors), and the buffers (nullptr where no layer needs one)
+    bool band[GA3C_MAX_CONV];
+    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_dgrad[GA3C_MAX_CONV], bfrag_vecs;
+    u32x4 *bfrag[2];
     int *ticket;                  // predict_small_kernel's per-frame counters, zero between launches
     Work pred, train;
     // training only
@@ -1492,7 +1499,33 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s) {
         ga3c::launch(large_filter_fragments_kernel, dim3(LFRAG_B3), dim3(256), 0, s, w2, w3, c->lfrag[i]);
         HIP_TRY(hipGetLastError());
     }
+    if (c->bfrag[i]) {
+        FragJobs jobs;
+        jobs.n = 0;
+        int blocks = 0;
+        auto add = [&](int l, int kind, u32x4 *dst, int n) {
+            jobs.job[jobs.n++] = FragJob{c->theta2[i] + c->off[2 * l], dst, kind, c->geom[l].C, c->geom[l].OC, c->geom[l].KS, n, blocks};
+            blocks += cdiv(n, 256);
+        };
+        for (int l = 0; l < c->nconv; ++l) {
+            if (!c->band[l]) continue;
+            const ConvGeom &g = c->geom[l];
+            add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
+            if (l > 0) add(l, FRAG_DGRAD_S2, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
+        }
+        ga3c::launch(band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
+        HIP_TRY(hipGetLastError());
+    }
     return GA3C_OK;
+}
+
+// Layers that the any-size kernels take: the byte layer with 8x8 filters over four planes of width 84, and 4x4 stride-2
+// layers on 32 channels; layers with kernels of their own shape keep those.
+bool on_band_kernels(const ConvGeom &g, int l) {
+    if (g.OC != 32 && !(l == 0 && g.OC == 16) && !(l > 0 && g.OC == 64)) return false;
+    if (l == 0) return g.C == 4 && g.KS == 8 && bytes_ok(g.H, g.W, g.S) && !spec_matches<SpecS1>(g, true) && !spec_matches<SpecL1>(g, true);
+    if (g.C != 32 || g.KS != 4 || g.S != 2 || spec_matches<SpecL2>(g, false)) return false;
+    return g.OC == 32 ? band_ok<32, 32>(g.H, g.W) : band_ok<32, 64>(g.H, g.W);
 }
 
 // Forward pass of `B` frames into `w`; heads outputs to the optional pointers.
@@ -1573,6 +1606,23 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
                 continue;
             }
         }
+        // Updates at fp32 accuracy run these layers on the fp32 instruction, in the any-shape kernels' order of sums
+        // (conv_band_f32.hpp says why); predictions take the bf16 terms, which are faster (128 frames of the stride-3
+        // member: conv1 11 against 22 us, conv2 13 against 17, conv3 10 against 14).
+        if (c->fast && c->band[l] && is_aligned16(xin) && is_aligned16(wl)) {
+            const u32x4 *wf = c->bfrag[which] + c->bfrag_fwd[l];
+            const bool f32 = !c->rb && keep_zv;
+            if (l == 0) {
+                if (f32 && g.OC == 16) HIP_TRY(launch_conv_bytes_f32_fwd<16>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
+                else if (f32) HIP_TRY(launch_conv_bytes_f32_fwd<32>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
+                else if (g.OC == 16) HIP_TRY(launch_conv_bytes_fwd<16>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
+                else HIP_TRY(launch_conv_bytes_fwd<32>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
+            } else if (f32 && g.OC == 32) HIP_TRY((launch_conv_band_f32_fwd<32, 32>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s)));
+            else if (f32) HIP_TRY((launch_conv_band_f32_fwd<32, 64>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s)));
+            else if (g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+            else HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+            continue;
+        }
         if (l == 0) {
             ConvFwdP<uint8_t> p; p.rb = c->rb;
             p.M = g.OC; p.N = B * g.OHW; p.K = g.K; p.g = g;
@@ -1647,7 +1697,9 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
         for (int l = 0; l < c->nconv; ++l) {
             const ConvGeom &g = c->geom[l];
             pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kc);
-            add((size_t)std::max(nz, std::min(B, 512)) * g.OC * (g.K + 1));      // generic or frame-resident kernel
+            nz = std::max(nz, std::min(B, 512));                                 // generic or frame-resident kernel
+            if (c->band[l]) nz = std::max(nz, BAND_CUS);                         // a frame may be several items
+            add((size_t)nz * g.OC * (g.K + 1));
         }
         int nz2;
         pick_split(cdiv(c->F, 64) * cdiv(c->flat + 1, 64), B, nz, kc);
@@ -1787,6 +1839,18 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
             if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
         }
     }
+    for (int l = 0; l < c->nconv; ++l) {
+        const ConvGeom &g = c->geom[l];
+        c->band[l] = on_band_kernels(g, l);
+        if (!c->band[l]) continue;
+        c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8;
+        if (l > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8; }
+    }
+    if (c->bfrag_vecs)
+        for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
+            guard(dmalloc((void **)&c->bfrag[i], sizeof(u32x4) * c->bfrag_vecs));
+            if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
+        }
     if (rc == GA3C_OK) guard(alloc_work(c->pred, c, max_predict_batch));
     if (rc == GA3C_OK) guard(alloc_work(c->train, c, max_train_frames));
     if (rc == GA3C_OK && max_train_frames > 0) {
@@ -1836,6 +1900,7 @@ extern "C" int ga3c_destroy(ga3c_ctx *c) {
     }
     (void)hipFree(c->g); (void)hipFree(c->grad);
     (void)hipFree(c->cfrag[0]); (void)hipFree(c->cfrag[1]); (void)hipFree(c->ticket); (void)hipFree(c->lfrag[0]); (void)hipFree(c->lfrag[1]);
+    (void)hipFree(c->bfrag[0]); (void)hipFree(c->bfrag[1]);
     free_work(c->pred); free_work(c->train);
     (void)hipFree(c->dh); (void)hipFree(c->dzv); (void)hipFree(c->R);
     (void)hipFree(c->partials); (void)hipFree(c->colpart); (void)hipFree(c->scale); (void)hipFree(c->stats);
@@ -2092,7 +2157,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                                      : spec_matches<SpecS2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 6 : 3)
                                      : spec_matches<SpecL2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 7 : 4)
                                      : spec_matches<SpecL3>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 8 : 5)
-                                     : (spec_matches<SpecP2>(g, l == 0) && is_aligned16(c->dact[l])) ? 9 : 0;
+                                     : c->band[l] ? 10 : 0;
             if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 3) nz = conv_wgrad_frame_blocks<SpecS2>(B);
@@ -2101,7 +2166,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
             else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
             else if (kind == 7) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
             else if (kind == 8) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
-            else if (kind == 9) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
+            else if (kind == 10)
+                nz = l == 0 ? (g.OC == 16 ? conv_bytes_wgrad_blocks<16>(B, g.H, g.S, c->rb) : conv_bytes_wgrad_blocks<32>(B, g.H, g.S, c->rb))
+                            : g.OC == 32 ? conv_band_wgrad_blocks<32, 32>(B, g.H, g.W, c->rb) : conv_band_wgrad_blocks<32, 64>(B, g.H, g.W, c->rb);
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
@@ -2122,8 +2189,12 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                 HIP_TRY((launch_conv_wgrad_bf16x6<SpecL2, 32>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb)));
             } else if (kind == 8) {
                 HIP_TRY(launch_conv_wgrad_s1_bf16x6<SpecL3>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 9) {
-                HIP_TRY(launch_conv_wgrad_bf16x6<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
+            } else if (kind == 10 && l == 0) {
+                if (g.OC == 16) HIP_TRY(launch_conv_bytes_wgrad<16>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s, c->rb));
+                else HIP_TRY(launch_conv_bytes_wgrad<32>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s, c->rb));
+            } else if (kind == 10) {
+                if (g.OC == 32) HIP_TRY((launch_conv_band_wgrad<32, 32>((const float *)xin, c->dact[l], part, B, g.H, g.W, s, c->rb)));
+                else HIP_TRY((launch_conv_band_wgrad<32, 64>((const float *)xin, c->dact[l], part, B, g.H, g.W, s, c->rb)));
             } else if (l == 0) {
                 ConvWgradP<uint8_t> p; p.rb = c->rb;
                 p.M = g.OC; p.N = g.K + 1; p.K = B * g.OHW; p.kchunk = kchunk; p.g = g;
@@ -2152,8 +2223,10 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                                                      c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr));
             continue;
         }
-        if (c->fast && spec_matches<SpecP2>(g, false) && is_aligned16(th + c->off[2 * l])) {
-            HIP_TRY(launch_conv_dgrad_bf16x6<SpecP2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb));
+        if (c->fast && c->band[l]) {
+            const u32x4 *wf = c->bfrag[cur] + c->bfrag_dgrad[l];
+            if (g.OC == 32) HIP_TRY((launch_conv_band_dgrad<32, 32>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb)));
+            else HIP_TRY((launch_conv_band_dgrad<32, 64>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb)));
             continue;
         }
         if (c->fast && spec_matches<SpecL3>(g, false)) {
@@ -2196,7 +2269,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
     ga3c::launch((rmsprop_kernel<0, 1>), dim3(rb), dim3(256), 0, s, th, c->theta2[cur ^ 1], c->g, c->grad, c->P, (const float *)nullptr,
                        1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[cur ^ 1], (unsigned)c->off[0], (unsigned)c->off[2], c->rb, ca);
     HIP_TRY(hipGetLastError());
-    if (c->lfrag[cur ^ 1]) TRY(refresh_derived(c, cur ^ 1, s));      // the larger net's fragments follow the new parameters
+    if (c->lfrag[cur ^ 1] || c->bfrag[cur ^ 1]) TRY(refresh_derived(c, cur ^ 1, s));      // the larger net's fragments follow the new parameters
     TRY(mark_ready(c, cur ^ 1, s));
     c->cur = cur ^ 1;        // calls enqueued from now on see the new parameters
     return GA3C_OK;

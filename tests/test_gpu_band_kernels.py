@@ -1,0 +1,76 @@
+"""The any-size kernels of the paper's larger-network family (csrc/conv_band.hpp, conv_bytes.hpp, conv_band_f32.hpp)
+at the sizes where their bands can go wrong, layer by layer against the fp64 oracle, and bit for bit against the
+any-shape kernels where the two form the same sums."""
+import numpy as np
+import pytest
+
+import ga3c_synth as synth
+import test_gpu_parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    import paper_1611_06256_amd as g
+    assert torch.cuda.is_available()
+    return g
+
+
+def frames_of(seed, n, h):
+    return synth.rectangle_frames(seed, n, h=h)
+
+
+# conv1 -> conv2 -> conv3 maps: odd and even, one row or column, one band and several, a last band that is short
+SHAPES = [
+    dict(in_h=60, conv=((32, 8, 2), (32, 4, 2), (64, 4, 2))),      # 27x39 -> 12x18 -> 5x8
+    dict(in_h=32, conv=((32, 8, 3), (64, 4, 2))),                  # 9x26 -> 3x12
+    dict(in_h=50, conv=((16, 8, 1), (32, 3, 2), (32, 4, 2))),      # 43x77, 16 filters; 21x38 (general) -> 9x18
+    dict(in_h=84, conv=((32, 8, 5), (32, 4, 2))),                  # 16x16 -> 7x7
+    dict(in_h=36, conv=((32, 8, 9), (64, 4, 2))),                  # 4x9 -> 1x3
+]
+
+
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_band_shapes(G, shape, math):
+    desc = G.NetDesc(in_c=4, in_w=84, fc_units=32, n_actions=5, math=math, **shape)
+    P.check_predict(G, desc, 3, 9100, frames=frames_of(9101, 3, desc.in_h))
+    P.run_train(G, desc, 2, 3, 9110, dict(clip_norm=40.0), frames=frames_of(9111, 6, desc.in_h).reshape(2, 3, 4, desc.in_h, 84))
+
+
+@pytest.mark.parametrize("math", [0, 1])
+def test_several_frames_per_item(G, math):
+    # maps so small and a batch so large that an item holds several frames, the last item fewer
+    desc = G.NetDesc(in_c=4, in_h=40, in_w=84, conv=((32, 8, 8), (32, 4, 2)), fc_units=16, n_actions=4, math=math)
+    N, T = 421, 5
+    fr = np.tile(frames_of(9201, 131, 40), (17, 1, 1, 1))[:N * T]
+    P.run_train(G, desc, N, T, 9200, dict(clip_norm=40.0), frames=fr.reshape(N, T, 4, 40, 84))
+    P.check_predict(G, desc, 1100, 9210, frames=fr[:1100])
+
+
+@pytest.mark.parametrize("shape,n", [(SHAPES[0], 7), (SHAPES[2], 3), (SHAPES[3], 300),
+                                     (dict(in_h=84, conv=((32, 8, 1), (32, 4, 2), (64, 4, 2))), 5)])
+def test_training_activations_are_the_any_shape_kernels_bits(G, shape, n):
+    import torch
+    desc = G.NetDesc(in_c=4, in_w=84, fc_units=16, n_actions=4, **shape)
+    fr = torch.from_numpy(np.tile(frames_of(9301, min(n, 20), desc.in_h), (n // min(n, 20), 1, 1, 1))).cuda()
+    n = int(fr.shape[0])
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9302, n, 1, 4).items()}
+    acts = []
+    for generic in (True, False):
+        net = G.Ga3c(desc, n, n)
+        net.params_init(9303)
+        net.use_generic_kernels(generic)
+        print(f"train n={n} generic={generic}", flush=True)
+        net.train_step(fr.view(n, 1, *fr.shape[1:]), tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.0))
+        c, h, w, got = 4, desc.in_h, 84, []
+        for l, (oc, k, s) in enumerate(desc.conv):
+            c, h, w = oc, (h - k) // s + 1, (w - k) // s + 1
+            got.append(net.train_debug_get(4 + l, torch.empty(n * c * h * w, device="cuda")))
+        torch.cuda.synchronize()
+        acts.append(got)
+        net.close()
+    for l, (a, b) in enumerate(zip(*acts)):
+        assert float(a.abs().max()) > 0 and torch.equal(a, b), f"layer {l}"
