@@ -50,8 +50,8 @@ struct BandGeom {
 };
 
 // LDS pixel pitch in bytes for C channels.
-template <int C, bool ONE>
-constexpr int band_pitch() { return (ONE ? 2 : 6) * C + 16; }
+template <int C>
+constexpr int band_pitch() { return 6 * C + 16; }
 
 // ---------------------------------------------------------------- fragments --
 
@@ -106,15 +106,13 @@ __device__ __forceinline__ void band_load8(const float *base, uint32_t off, int 
 #pragma unroll
     for (int c = 0; c < 8; ++c) r[c] = *(const float *)((const char *)(base + (size_t)c * plane) + off);
 }
-template <int C, bool ONE>
+template <int C>
 __device__ __forceinline__ void band_store8(unsigned char *dst, const float (&r)[8]) {
     u32x4 h, m, l;
     split3x8(r, h, m, l);
     *(u32x4 *)dst = h;
-    if (!ONE) {
-        *(u32x4 *)(dst + 2 * C) = m;
-        *(u32x4 *)(dst + 4 * C) = l;
-    }
+    *(u32x4 *)(dst + 2 * C) = m;
+    *(u32x4 *)(dst + 4 * C) = l;
 }
 // Floats left in a tensor of `total` behind `base`, less the eight planes a unit reads: the largest offset a unit may use.
 __device__ __forceinline__ uint32_t band_limit(size_t total, size_t base, int plane) {
@@ -128,12 +126,12 @@ __device__ __forceinline__ uint32_t band_limit(size_t total, size_t base, int pl
 // filter.  Wavefront w keeps the fragments of filter tile w % (OC / 16) in registers (192 of them: one wavefront per
 // SIMD) and takes every (64 / OC)-th pixel tile, up to four at a time; the operands of the next k-block are read while
 // the current one is multiplied.
-template <int C, int OC, bool ONE>
+template <int C, int OC>
 __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__restrict__ x, const u32x4 *__restrict__ wfrag,
                                                                const float *__restrict__ bias, float *__restrict__ y,
                                                                int nframes, const BandGeom b) {
-    constexpr int KS = 4, S = 2, KB = KS * KS * C / 32, OT = OC / 16, PG = 4 / OT, NTERM = ONE ? 1 : 3;
-    constexpr int PIT = band_pitch<C, ONE>(), MAXU = BAND_MAXU;
+    constexpr int KS = 4, S = 2, KB = KS * KS * C / 32, OT = OC / 16, PG = 4 / OT, NTERM = 3;
+    constexpr int PIT = band_pitch<C>(), MAXU = BAND_MAXU;
     static_assert(C == 32 && (OC == 32 || OC == 64), "32 channels in, 32 or 64 filters");
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
 
@@ -181,7 +179,7 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
         __syncthreads();                                     // the last item's planes have been read
 #pragma unroll
         for (int i = 0; i < MAXU; ++i)
-            if (dst[i] >= 0) band_store8<C, ONE>(band_smem + dst[i], pre[i]);
+            if (dst[i] >= 0) band_store8<C>(band_smem + dst[i], pre[i]);
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
         __builtin_amdgcn_sched_barrier(0);
@@ -216,13 +214,12 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
             for (int kb = 0; kb < KB; ++kb) {
                 if (kb + 1 < KB) read(kb + 1, xv[(kb + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int NPROD = ONE ? 1 : 6;
                 constexpr int PX[6] = {2, 1, 0, 1, 0, 0}, PW[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
 #pragma unroll
-                for (int q = 0; q < NPROD; ++q)
+                for (int q = 0; q < 6; ++q)
 #pragma unroll
                     for (int n = 0; n < N; ++n)
-                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[kb & 1][n][ONE ? 0 : PX[q]].v, wq[kb][ONE ? 0 : PW[q]].v,
+                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[kb & 1][n][PX[q]].v, wq[kb][PW[q]].v,
                                                                          acc[n], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -267,12 +264,12 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
 template <int OC>
 constexpr int band_dgrad_maxu() { return OC == 64 ? 8 : BAND_MAXU; }       // 64 filters: 192 registers hold fragments
 
-template <int C, int OC, bool ONE>
+template <int C, int OC>
 __global__ __launch_bounds__(256, 1) void conv_band_dgrad_kernel(const float *__restrict__ dy, const u32x4 *__restrict__ wfrag,
                                                                  const float *__restrict__ xin, float *__restrict__ dx,
                                                                  int nframes, const BandGeom b) {
-    constexpr int OCB = OC / 32, KB = 4 * OCB, CT = C / 16, PG = 2 / CT, NTERM = ONE ? 1 : 3;
-    constexpr int PIT = band_pitch<OC, ONE>(), MAXU = band_dgrad_maxu<OC>();
+    constexpr int OCB = OC / 32, KB = 4 * OCB, CT = C / 16, PG = 2 / CT, NTERM = 3;
+    constexpr int PIT = band_pitch<OC>(), MAXU = band_dgrad_maxu<OC>();
     static_assert((C == 16 || C == 32) && (OC == 32 || OC == 64), "16 or 32 channels, 32 or 64 filters");
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
 
@@ -332,7 +329,7 @@ __global__ __launch_bounds__(256, 1) void conv_band_dgrad_kernel(const float *__
 #pragma unroll
                     for (int c = 0; c < 8; ++c) pre[i][c] = 0.f;
                 }
-                band_store8<OC, ONE>(band_smem + dst[i], pre[i]);
+                band_store8<OC>(band_smem + dst[i], pre[i]);
             }
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
@@ -378,16 +375,15 @@ __global__ __launch_bounds__(256, 1) void conv_band_dgrad_kernel(const float *__
             for (int kb = 0; kb < KB; ++kb) {
                 if (kb + 1 < KB) read(kb + 1, dv[(kb + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int NPROD = ONE ? 1 : 6;
                 constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
 #pragma unroll
-                for (int q = 0; q < NPROD; ++q)
+                for (int q = 0; q < 6; ++q)
 #pragma unroll
                     for (int n = 0; n < N; ++n)
 #pragma unroll
                         for (int rx = 0; rx < 2; ++rx)
-                            acc[n][rx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wq[rx][kb][ONE ? 0 : PA[q]].v,
-                                                                                 dv[kb & 1][n][ONE ? 0 : PB[q]].v, acc[n][rx], 0, 0, 0);
+                            acc[n][rx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wq[rx][kb][PA[q]].v,
+                                                                                 dv[kb & 1][n][PB[q]].v, acc[n][rx], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -432,12 +428,12 @@ struct ConvBandWgradGeom {
     static constexpr int OUT_BYTES = OC * OTP * 4;
 };
 
-template <int C, int OC, bool ONE>
+template <int C, int OC>
 __global__ __launch_bounds__(256, 1) void conv_band_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy,
                                                                  float *__restrict__ part, int nframes, const BandGeom b) {
     typedef ConvBandWgradGeom<C, OC> G;
-    constexpr int KS = 4, S = 2, CT = C / 16, OT = OC / 16, NTERM = ONE ? 1 : 3;
-    constexpr int XPIT = band_pitch<C, ONE>(), DPIT = band_pitch<OC, ONE>(), MAXX = BAND_MAXU, MAXD = OC / 8;
+    constexpr int KS = 4, S = 2, CT = C / 16, OT = OC / 16, NTERM = 3;
+    constexpr int XPIT = band_pitch<C>(), DPIT = band_pitch<OC>(), MAXX = BAND_MAXU, MAXD = OC / 8;
     static_assert(C % 16 == 0 && OC % 16 == 0, "channels and filters in groups of 16");
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
 
@@ -504,7 +500,7 @@ __global__ __launch_bounds__(256, 1) void conv_band_wgrad_kernel(const float *__
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < MAXX; ++i)
-            if (xdst[i] >= 0) band_store8<C, ONE>(xsm + xdst[i], xpre[i]);
+            if (xdst[i] >= 0) band_store8<C>(xsm + xdst[i], xpre[i]);
 #pragma unroll
         for (int i = 0; i < MAXD; ++i)
             if (ddst[i] >= 0) {
@@ -512,7 +508,7 @@ __global__ __launch_bounds__(256, 1) void conv_band_wgrad_kernel(const float *__
 #pragma unroll
                     for (int c = 0; c < 8; ++c) dpre[i][c] = 0.f;
                 }
-                band_store8<OC, ONE>(dsm + ddst[i], dpre[i]);
+                band_store8<OC>(dsm + ddst[i], dpre[i]);
             }
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
@@ -551,13 +547,12 @@ __global__ __launch_bounds__(256, 1) void conv_band_wgrad_kernel(const float *__
             for (int q = 0; q < 4 * CT; ++q) {
                 if (q + 1 < 4 * CT) read(q + 1, xv[(q + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int NPROD = ONE ? 1 : 6;
                 constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
 #pragma unroll
-                for (int e = 0; e < NPROD; ++e)
+                for (int e = 0; e < 6; ++e)
 #pragma unroll
                     for (int m = 0; m < OT; ++m)
-                        acc[q / CT][q % CT][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[m][ONE ? 0 : PA[e]].v, xv[q & 1][ONE ? 0 : PB[e]].v,
+                        acc[q / CT][q % CT][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[m][PA[e]].v, xv[q & 1][PB[e]].v,
                                                                                          acc[q / CT][q % CT][m], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -624,24 +619,24 @@ inline BandGeom band_geom(int H, int W) {
 }
 inline int band_in_px(const BandGeom &b, int F, int R) { return F * ((R - 1) * 2 + 4) * 2 * ((b.W + 1) / 2); }
 
-template <int C, bool ONE>
+template <int C>
 inline bool band_fwd_geom(BandGeom &b, int nframes) {
-    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return band_in_px(b, F, R) * band_pitch<C, ONE>(); },
+    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return band_in_px(b, F, R) * band_pitch<C>(); },
                       [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); });
 }
-template <int OC, bool ONE>
+template <int OC>
 inline bool band_dgrad_geom(BandGeom &b, int nframes) {
     const int GW = (b.W + 1) / 2;
-    return band_split(b, nframes, (b.H + 1) / 2, GW, [&](int F, int R) { return F * (R + 1) * (GW + 1) * band_pitch<OC, ONE>(); },
+    return band_split(b, nframes, (b.H + 1) / 2, GW, [&](int F, int R) { return F * (R + 1) * (GW + 1) * band_pitch<OC>(); },
                       [&](int F, int R) { return F * (R + 1) * b.OW * (OC / 8); }, band_dgrad_maxu<OC>());
 }
 // dY takes one staging unit per thread and eight filters of up to 256 pixels
-template <int C, int OC, bool ONE>
+template <int C, int OC>
 inline bool band_wgrad_geom(BandGeom &b, int nframes) {
     return band_split(b, nframes, b.OH, b.OW,
                       [&](int F, int R) {
                           const int px = (F * R * b.OW + 31) / 32 * 32;
-                          return px > 256 ? 2 * BAND_LDS : band_in_px(b, F, R) * band_pitch<C, ONE>() + px * band_pitch<OC, ONE>();
+                          return px > 256 ? 2 * BAND_LDS : band_in_px(b, F, R) * band_pitch<C>() + px * band_pitch<OC>();
                       },
                       [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); });
 }
@@ -659,69 +654,53 @@ inline hipError_t band_allow_lds(K kernel, bool &done) {
 template <int C, int OC>
 inline bool band_ok(int H, int W) {
     BandGeom b = band_geom(H, W), c = b, d = b;
-    return H >= 4 && W >= 4 && band_fwd_geom<C, false>(b, 1) && band_dgrad_geom<OC, false>(c, 1) && band_wgrad_geom<C, OC, false>(d, 1);
+    return H >= 4 && W >= 4 && band_fwd_geom<C>(b, 1) && band_dgrad_geom<OC>(c, 1) && band_wgrad_geom<C, OC>(d, 1);
 }
 
-template <int C, int OC, bool ONE>
-inline hipError_t launch_conv_band_fwd1(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
+template <int C, int OC>
+inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
     BandGeom b = band_geom(H, W);
-    if (!band_fwd_geom<C, ONE>(b, n)) return hipErrorInvalidValue;
+    if (!band_fwd_geom<C>(b, n)) return hipErrorInvalidValue;
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_fwd_kernel<C, OC, ONE>, attr);
+    const hipError_t e = band_allow_lds(conv_band_fwd_kernel<C, OC>, attr);
     if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_fwd_kernel<C, OC, ONE>), dim3(band_blocks(b)), dim3(256), band_in_px(b, b.F, b.R) * band_pitch<C, ONE>(), s, x, wfrag,
+    ga3c::launch((conv_band_fwd_kernel<C, OC>), dim3(band_blocks(b)), dim3(256), band_in_px(b, b.F, b.R) * band_pitch<C>(), s, x, wfrag,
                  bias, y, n, b);
     return hipGetLastError();
 }
-// x [n][C][H][W] -> y [n][OC][OH][OW]; wfrag: FRAG_CONV fragments of the filters.
-template <int C, int OC>
-inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s, int rb) {
-    if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_fwd1<C, OC, true>(x, wfrag, bias, y, n, H, W, s) : launch_conv_band_fwd1<C, OC, false>(x, wfrag, bias, y, n, H, W, s);
-}
 
-template <int C, int OC, bool ONE>
-inline hipError_t launch_conv_band_dgrad1(const float *dy, const u32x4 *wfrag, const float *xin, float *dx, int n, int H, int W, hipStream_t s) {
-    BandGeom b = band_geom(H, W);
-    if (!band_dgrad_geom<OC, ONE>(b, n)) return hipErrorInvalidValue;
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_dgrad_kernel<C, OC, ONE>, attr);
-    if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_dgrad_kernel<C, OC, ONE>), dim3(band_blocks(b)), dim3(256),
-                 b.F * (b.R + 1) * (b.cols + 1) * band_pitch<OC, ONE>(), s, dy, wfrag, xin, dx, n, b);
-    return hipGetLastError();
-}
-// dy [n][OC][OH][OW], xin [n][C][H][W] (the layer's input: its ReLU mask) -> dx [n][C][H][W]; wfrag: FRAG_DGRAD_S2.
 template <int C, int OC>
-inline hipError_t launch_conv_band_dgrad(const float *dy, const u32x4 *wfrag, const float *xin, float *dx, int n, int H, int W, hipStream_t s, int rb) {
+inline hipError_t launch_conv_band_dgrad(const float *dy, const u32x4 *wfrag, const float *xin, float *dx, int n, int H, int W, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_dgrad1<C, OC, true>(dy, wfrag, xin, dx, n, H, W, s)
-              : launch_conv_band_dgrad1<C, OC, false>(dy, wfrag, xin, dx, n, H, W, s);
+    BandGeom b = band_geom(H, W);
+    if (!band_dgrad_geom<OC>(b, n)) return hipErrorInvalidValue;
+    static bool attr = false;
+    const hipError_t e = band_allow_lds(conv_band_dgrad_kernel<C, OC>, attr);
+    if (e != hipSuccess) return e;
+    ga3c::launch((conv_band_dgrad_kernel<C, OC>), dim3(band_blocks(b)), dim3(256),
+                 b.F * (b.R + 1) * (b.cols + 1) * band_pitch<OC>(), s, dy, wfrag, xin, dx, n, b);
+    return hipGetLastError();
 }
 
 // Blocks of the weight gradient (= partial gradients it leaves).
 template <int C, int OC>
-inline int conv_band_wgrad_blocks(int n, int H, int W, int rb) {
+inline int conv_band_wgrad_blocks(int n, int H, int W) {
     BandGeom b = band_geom(H, W);
-    if (!(rb ? band_wgrad_geom<C, OC, true>(b, n) : band_wgrad_geom<C, OC, false>(b, n))) return 0;
-    return band_blocks(b);
-}
-template <int C, int OC, bool ONE>
-inline hipError_t launch_conv_band_wgrad1(const float *x, const float *dy, float *part, int n, int H, int W, hipStream_t s) {
-    BandGeom b = band_geom(H, W);
-    if (!band_wgrad_geom<C, OC, ONE>(b, n)) return hipErrorInvalidValue;
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_wgrad_kernel<C, OC, ONE>, attr);
-    if (e != hipSuccess) return e;
-    const int px = (b.F * b.R * b.OW + 31) / 32 * 32;
-    const int lds = std::max(band_in_px(b, b.F, b.R) * band_pitch<C, ONE>() + px * band_pitch<OC, ONE>(), ConvBandWgradGeom<C, OC>::OUT_BYTES);
-    ga3c::launch((conv_band_wgrad_kernel<C, OC, ONE>), dim3(band_blocks(b)), dim3(256), lds, s, x, dy, part, n, b);
-    return hipGetLastError();
+    return band_wgrad_geom<C, OC>(b, n) ? band_blocks(b) : 0;
 }
 template <int C, int OC>
-inline hipError_t launch_conv_band_wgrad(const float *x, const float *dy, float *part, int n, int H, int W, hipStream_t s, int rb) {
+inline hipError_t launch_conv_band_wgrad(const float *x, const float *dy, float *part, int n, int H, int W, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_wgrad1<C, OC, true>(x, dy, part, n, H, W, s) : launch_conv_band_wgrad1<C, OC, false>(x, dy, part, n, H, W, s);
+    BandGeom b = band_geom(H, W);
+    if (!band_wgrad_geom<C, OC>(b, n)) return hipErrorInvalidValue;
+    static bool attr = false;
+    const hipError_t e = band_allow_lds(conv_band_wgrad_kernel<C, OC>, attr);
+    if (e != hipSuccess) return e;
+    const int px = (b.F * b.R * b.OW + 31) / 32 * 32;
+    const int lds = std::max(band_in_px(b, b.F, b.R) * band_pitch<C>() + px * band_pitch<OC>(), ConvBandWgradGeom<C, OC>::OUT_BYTES);
+    ga3c::launch((conv_band_wgrad_kernel<C, OC>), dim3(band_blocks(b)), dim3(256), lds, s, x, dy, part, n, b);
+    return hipGetLastError();
 }
 
 }  // namespace ga3c

@@ -31,7 +31,8 @@ constexpr int BAND_F32_LDS = 80 * 1024;           // two blocks per compute unit
 constexpr int BAND_F32_MAXK = 3;                  // values of a channel in flight per thread
 
 // 4x4, stride 2, 32 channels; a block takes the pixel tiles of its item four wavefronts apart, all filters.
-template <int C, int OC>
+// RB: both operands rounded to bfloat16.
+template <int C, int OC, bool RB>
 __global__ __launch_bounds__(256, 2) void conv_band_f32_fwd_kernel(const float *__restrict__ x, const float *__restrict__ w,
                                                                    const float *__restrict__ bias, float *__restrict__ y, int nframes,
                                                                    const BandGeom b) {
@@ -78,7 +79,7 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_fwd_kernel(const float *
         for (int k = 0; k < MAXK; ++k)
             if (tid + 256 * k < plane) {
 #pragma unroll
-                for (int c = 0; c < C; ++c) xs[c * plane + tid + 256 * k] = pre[c][k];
+                for (int c = 0; c < C; ++c) xs[c * plane + tid + 256 * k] = RB ? bf16_rne(pre[c][k]) : pre[c][k];
             }
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
@@ -104,7 +105,10 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_fwd_kernel(const float *
             float4 wv[2][OT];
             auto read_w = [&](int c, float4 (&d)[OT]) {
 #pragma unroll
-                for (int m = 0; m < OT; ++m) d[m] = *(const float4 *)(wl + (size_t)m * 16 * K + 16 * c);
+                for (int m = 0; m < OT; ++m) {
+                    d[m] = *(const float4 *)(wl + (size_t)m * 16 * K + 16 * c);
+                    if (RB) d[m] = bf16_rne(d[m]);
+                }
             };
             float xv[2][N][4];
             auto read_x = [&](int c, float (&d)[N][4]) {
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_fwd_kernel(const float *
 
 // The byte layer: 8x8 filters over four planes of width 84.  A wavefront keeps all filters in registers (64 x OC / 16) and
 // takes every fourth pixel tile; a lane's four bytes of a filter row come out of the two dwords they lie in.
-template <int OC>
+template <int OC, bool RB>
 __global__ __launch_bounds__(256, 2) void conv_bytes_f32_fwd_kernel(const uint8_t *__restrict__ x, const float *__restrict__ w,
                                                                     const float *__restrict__ bias, float *__restrict__ y, int nframes,
                                                                     float scale, const BytesGeom b) {
@@ -202,7 +206,10 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_f32_fwd_kernel(const uint8_
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int m = 0; m < OT; ++m) wq[kb][m] = *(const float4 *)(w + (size_t)(m * 16 + l16) * 256 + 16 * kb + 4 * g);
+        for (int m = 0; m < OT; ++m) {
+            wq[kb][m] = *(const float4 *)(w + (size_t)(m * 16 + l16) * 256 + 16 * kb + 4 * g);
+            if (RB) wq[kb][m] = bf16_rne(wq[kb][m]);
+        }
     float bv[OT];
 #pragma unroll
     for (int m = 0; m < OT; ++m) bv[m] = bias[m * 16 + l16];
@@ -302,31 +309,40 @@ inline bool band_f32_geom(BandGeom &b, int nframes) {
                       [&](int F, int R) { return px(F, R) <= 256 * BAND_F32_MAXK ? 0 : 1 << 30; }, BAND_MAXU, 2 * BAND_CUS);
 }
 
-// x [n][32][H][W] -> y [n][OC][OH][OW]; w [OC][32][4][4], 16-byte aligned.
-template <int C, int OC>
-inline hipError_t launch_conv_band_f32_fwd(const float *x, const float *w, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
+template <int C, int OC, bool RB>
+inline hipError_t launch_conv_band_f32_fwd1(const float *x, const float *w, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
     BandGeom b = band_geom(H, W);
     if (!band_f32_geom<C>(b, n)) return hipErrorInvalidValue;
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_f32_fwd_kernel<C, OC>, attr);
+    const hipError_t e = band_allow_lds(conv_band_f32_fwd_kernel<C, OC, RB>, attr);
     if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_f32_fwd_kernel<C, OC>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), b.F * ((b.R - 1) * 2 + 4) * b.W * C * 4, s, x, w,
-                 bias, y, n, b);
+    ga3c::launch((conv_band_f32_fwd_kernel<C, OC, RB>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256),
+                 b.F * ((b.R - 1) * 2 + 4) * b.W * C * 4, s, x, w, bias, y, n, b);
     return hipGetLastError();
 }
-
-// x [n][4][H][84] bytes -> y [n][OC][OH][OW]; w [OC][4][8][8], 16-byte aligned.
-template <int OC>
-inline hipError_t launch_conv_bytes_f32_fwd(const uint8_t *x, const float *w, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
+// x [n][32][H][W] -> y [n][OC][OH][OW]; w [OC][32][4][4], 16-byte aligned.
+template <int C, int OC>
+inline hipError_t launch_conv_band_f32_fwd(const float *x, const float *w, const float *bias, float *y, int n, int H, int W, hipStream_t s, int rb) {
     if (n <= 0) return hipSuccess;
+    return rb ? launch_conv_band_f32_fwd1<C, OC, true>(x, w, bias, y, n, H, W, s) : launch_conv_band_f32_fwd1<C, OC, false>(x, w, bias, y, n, H, W, s);
+}
+
+template <int OC, bool RB>
+inline hipError_t launch_conv_bytes_f32_fwd1(const uint8_t *x, const float *w, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
     const BytesGeom b = bytes_fwd_geom(H, S, n);
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_bytes_f32_fwd_kernel<OC>, attr);
+    const hipError_t e = band_allow_lds(conv_bytes_f32_fwd_kernel<OC, RB>, attr);
     if (e != hipSuccess) return e;
     const int RI = (b.R - 1) * b.S + 8;
-    ga3c::launch((conv_bytes_f32_fwd_kernel<OC>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), RI * BYTES_W * 4 + 16, s, x, w, bias, y, n, scale, b);
+    ga3c::launch((conv_bytes_f32_fwd_kernel<OC, RB>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), RI * BYTES_W * 4 + 16, s, x, w, bias, y, n, scale, b);
     return hipGetLastError();
+}
+// x [n][4][H][84] bytes -> y [n][OC][OH][OW]; w [OC][4][8][8], 16-byte aligned.
+template <int OC>
+inline hipError_t launch_conv_bytes_f32_fwd(const uint8_t *x, const float *w, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s,
+                                            int rb) {
+    if (n <= 0) return hipSuccess;
+    return rb ? launch_conv_bytes_f32_fwd1<OC, true>(x, w, bias, y, n, H, S, scale, s) : launch_conv_bytes_f32_fwd1<OC, false>(x, w, bias, y, n, H, S, scale, s);
 }
 
 }  // namespace ga3c

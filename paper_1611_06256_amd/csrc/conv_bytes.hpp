@@ -50,11 +50,11 @@ __device__ __forceinline__ void bytes_store4(unsigned char *dst, const uint32_t 
 // y[oc][i][j] = max(0, scale * sum W[oc][c][u][v] x[c][S i + u][S j + v] + b[oc]).  Wavefront w keeps the fragments of
 // filter tile w % (OC / 16) in registers (96 of them) and takes every (64 / OC)-th pixel tile, four at a time; two blocks
 // share a compute unit.
-template <int OC, bool ONE>
+template <int OC>
 __global__ __launch_bounds__(256, 2) void conv_bytes_fwd_kernel(const uint8_t *__restrict__ x, const u32x4 *__restrict__ wfrag,
                                                                 const float *__restrict__ bias, float *__restrict__ y, int nframes,
                                                                 float scale, const BytesGeom b) {
-    constexpr int OT = OC / 16, PG = 4 / OT, NTERM = ONE ? 1 : 3, KB = 8, MAXU = 7;
+    constexpr int OT = OC / 16, PG = 4 / OT, NTERM = 3, KB = 8, MAXU = 7;
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -159,11 +159,11 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_fwd_kernel(const uint8_t *_
 // [OC] x [256] result (OC / 16 x 16 tiles), and the wavefronts' sums are added through LDS at the end, in a fixed
 // order.  part: [gridDim.x][OC][257].
 constexpr int BYTES_WG_WAVES = 8, BYTES_WG_PX = 512;
-template <int OC, bool ONE>
+template <int OC>
 __global__ __launch_bounds__(64 * BYTES_WG_WAVES, 2) void conv_bytes_wgrad_kernel(const uint8_t *__restrict__ x, const float *__restrict__ dy,
                                                                                float *__restrict__ part, int nframes, float scale,
                                                                                const BytesGeom b) {
-    constexpr int OT = OC / 16, NTERM = ONE ? 1 : 3, NTHR = 64 * BYTES_WG_WAVES, DPIT = band_pitch<OC, ONE>();
+    constexpr int OT = OC / 16, NTERM = 3, NTHR = 64 * BYTES_WG_WAVES, DPIT = band_pitch<OC>();
     constexpr int MAXX = 4, MAXD = BYTES_WG_PX * (OC / 8) / NTHR, K1 = 257;
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(64 * BYTES_WG_WAVES, 2) void conv_bytes_wgrad_kerne
 #pragma unroll
                     for (int c = 0; c < 8; ++c) dpre[i][c] = 0.f;
                 }
-                band_store8<OC, ONE>(dsm + ddst[i], dpre[i]);
+                band_store8<OC>(dsm + ddst[i], dpre[i]);
             }
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
@@ -347,17 +347,17 @@ inline BytesGeom bytes_fwd_geom(int H, int S, int n) {
     bytes_split(b, n, r, 2 * BAND_CUS);
     return b;
 }
-template <int OC, bool ONE>
+template <int OC>
 inline int bytes_wgrad_lds(const BytesGeom &b, int R) {
-    return ((R - 1) * b.S + 8) * BYTES_ROW + (R * b.OW + 31) / 32 * 32 * band_pitch<OC, ONE>();
+    return ((R - 1) * b.S + 8) * BYTES_ROW + (R * b.OW + 31) / 32 * 32 * band_pitch<OC>();
 }
 template <int OC>
 constexpr int bytes_wgrad_out_lds() { return (BYTES_WG_WAVES / 2) * 17 * (OC / 16) * 4 * 64 * 4; }
-template <int OC, bool ONE>
+template <int OC>
 inline BytesGeom bytes_wgrad_geom(int H, int S, int n) {
     BytesGeom b = bytes_geom(H, S);
     int r = 1;
-    while (r < b.OH && (r + 1) * b.OW <= BYTES_WG_PX && bytes_wgrad_lds<OC, ONE>(b, r + 1) <= BAND_LDS - 2048 &&
+    while (r < b.OH && (r + 1) * b.OW <= BYTES_WG_PX && bytes_wgrad_lds<OC>(b, r + 1) <= BAND_LDS - 2048 &&
            (r * S + 8) * BYTES_Q <= 4 * 64 * BYTES_WG_WAVES) ++r;
     bytes_split(b, n, r, BAND_CUS);
     return b;
@@ -367,42 +367,32 @@ inline bool bytes_ok(int H, int W, int S) {
     return W == BYTES_W && H >= 8 && S >= 1 && (BYTES_W - 8) / S + 1 <= 128;
 }
 
-template <int OC, bool ONE>
-inline hipError_t launch_conv_bytes_fwd1(const uint8_t *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
+template <int OC>
+inline hipError_t launch_conv_bytes_fwd(const uint8_t *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
     const BytesGeom b = bytes_fwd_geom(H, S, n);
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_bytes_fwd_kernel<OC, ONE>, attr);
+    const hipError_t e = band_allow_lds(conv_bytes_fwd_kernel<OC>, attr);
     if (e != hipSuccess) return e;
     const int RI = (b.R - 1) * S + 8, units = (RI * BYTES_Q + 255) / 256 * 256;
-    ga3c::launch((conv_bytes_fwd_kernel<OC, ONE>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), units * 32, s, x, wfrag, bias, y, n, scale, b);
+    ga3c::launch((conv_bytes_fwd_kernel<OC>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), units * 32, s, x, wfrag, bias, y, n, scale, b);
     return hipGetLastError();
-}
-// x [n][4][H][84] bytes -> y [n][OC][OH][OW]; wfrag: FRAG_BYTES8 fragments of the filters.
-template <int OC>
-inline hipError_t launch_conv_bytes_fwd(const uint8_t *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int S, float scale,
-                                        hipStream_t s, int rb) {
-    if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_bytes_fwd1<OC, true>(x, wfrag, bias, y, n, H, S, scale, s) : launch_conv_bytes_fwd1<OC, false>(x, wfrag, bias, y, n, H, S, scale, s);
 }
 
 template <int OC>
-inline int conv_bytes_wgrad_blocks(int n, int H, int S, int rb) {
-    return std::min((rb ? bytes_wgrad_geom<OC, true>(H, S, n) : bytes_wgrad_geom<OC, false>(H, S, n)).items, BAND_CUS);
-}
-template <int OC, bool ONE>
-inline hipError_t launch_conv_bytes_wgrad1(const uint8_t *x, const float *dy, float *part, int n, int H, int S, float scale, hipStream_t s) {
-    const BytesGeom b = bytes_wgrad_geom<OC, ONE>(H, S, n);
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_bytes_wgrad_kernel<OC, ONE>, attr);
-    if (e != hipSuccess) return e;
-    const int lds = std::max(bytes_wgrad_lds<OC, ONE>(b, b.R), bytes_wgrad_out_lds<OC>());
-    ga3c::launch((conv_bytes_wgrad_kernel<OC, ONE>), dim3(std::min(b.items, BAND_CUS)), dim3(64 * BYTES_WG_WAVES), lds, s, x, dy, part, n, scale, b);
-    return hipGetLastError();
+inline int conv_bytes_wgrad_blocks(int n, int H, int S) {
+    return std::min(bytes_wgrad_geom<OC>(H, S, n).items, BAND_CUS);
 }
 template <int OC>
-inline hipError_t launch_conv_bytes_wgrad(const uint8_t *x, const float *dy, float *part, int n, int H, int S, float scale, hipStream_t s, int rb) {
+inline hipError_t launch_conv_bytes_wgrad(const uint8_t *x, const float *dy, float *part, int n, int H, int S, float scale, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_bytes_wgrad1<OC, true>(x, dy, part, n, H, S, scale, s) : launch_conv_bytes_wgrad1<OC, false>(x, dy, part, n, H, S, scale, s);
+    const BytesGeom b = bytes_wgrad_geom<OC>(H, S, n);
+    static bool attr = false;
+    const hipError_t e = band_allow_lds(conv_bytes_wgrad_kernel<OC>, attr);
+    if (e != hipSuccess) return e;
+    const int lds = std::max(bytes_wgrad_lds<OC>(b, b.R), bytes_wgrad_out_lds<OC>());
+    ga3c::launch((conv_bytes_wgrad_kernel<OC>), dim3(std::min(b.items, BAND_CUS)), dim3(64 * BYTES_WG_WAVES), lds, s, x, dy, part, n, scale, b);
+    return hipGetLastError();
 }
 
 }  // namespace ga3c

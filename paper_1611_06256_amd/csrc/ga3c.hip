@@ -39,6 +39,7 @@ typedef ConvSpec<float, 16, 20, 20, 32, 4, 2> SpecS2;     // small net, conv2
 typedef ConvSpec<uint8_t, 4, 84, 84, 32, 8, 4> SpecL1;    // large net, conv1
 typedef ConvSpec<float, 32, 20, 20, 64, 4, 2> SpecL2;     // large net, conv2
 typedef ConvSpec<float, 64, 9, 9, 64, 3, 1> SpecL3;       // large net, conv3
+typedef ConvSpec<float, 32, 20, 20, 32, 4, 2> SpecP2;     // the paper's larger-network family (Sec. 5), stride-4 member, conv2
 // 16-byte vectors of a small-net fragment buffer: the filters of conv1 / conv2 for the fused forward kernel, then
 // those of conv2 for its input-gradient kernel
 constexpr int CFRAG_FWD_VECS = 3 * C12_FRAG_SET, CFRAG_VECS = CFRAG_FWD_VECS + ConvDgradBf16Geom<SpecS2>::FRAG_VECS;
@@ -1606,21 +1607,21 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
                 continue;
             }
         }
-        // Updates at fp32 accuracy run these layers on the fp32 instruction, in the any-shape kernels' order of sums
-        // (conv_band_f32.hpp says why); predictions take the bf16 terms, which are faster (128 frames of the stride-3
+        // Updates run these layers on the fp32 instruction, in the any-shape kernels' order of sums (conv_band_f32.hpp
+        // says why), and so does the reduced-precision variant; predictions at fp32 accuracy take the bf16 terms, which are faster (128 frames of the stride-3
         // member: conv1 11 against 22 us, conv2 13 against 17, conv3 10 against 14).
         if (c->fast && c->band[l] && is_aligned16(xin) && is_aligned16(wl)) {
             const u32x4 *wf = c->bfrag[which] + c->bfrag_fwd[l];
-            const bool f32 = !c->rb && keep_zv;
+            const bool f32 = c->rb || keep_zv;
             if (l == 0) {
-                if (f32 && g.OC == 16) HIP_TRY(launch_conv_bytes_f32_fwd<16>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
-                else if (f32) HIP_TRY(launch_conv_bytes_f32_fwd<32>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
-                else if (g.OC == 16) HIP_TRY(launch_conv_bytes_fwd<16>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
-                else HIP_TRY(launch_conv_bytes_fwd<32>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
-            } else if (f32 && g.OC == 32) HIP_TRY((launch_conv_band_f32_fwd<32, 32>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s)));
-            else if (f32) HIP_TRY((launch_conv_band_f32_fwd<32, 64>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s)));
-            else if (g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s, c->rb)));
-            else HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+                if (f32 && g.OC == 16) HIP_TRY(launch_conv_bytes_f32_fwd<16>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
+                else if (f32) HIP_TRY(launch_conv_bytes_f32_fwd<32>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
+                else if (g.OC == 16) HIP_TRY(launch_conv_bytes_fwd<16>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
+                else HIP_TRY(launch_conv_bytes_fwd<32>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
+            } else if (f32 && g.OC == 32) HIP_TRY((launch_conv_band_f32_fwd<32, 32>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+            else if (f32) HIP_TRY((launch_conv_band_f32_fwd<32, 64>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+            else if (g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
+            else HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
             continue;
         }
         if (l == 0) {
@@ -1843,6 +1844,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         const ConvGeom &g = c->geom[l];
         c->band[l] = on_band_kernels(g, l);
         if (!c->band[l]) continue;
+        if (c->rb) continue;                         // runs on the parameters themselves
         c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8;
         if (l > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8; }
     }
@@ -2157,7 +2159,8 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                                      : spec_matches<SpecS2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 6 : 3)
                                      : spec_matches<SpecL2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 7 : 4)
                                      : spec_matches<SpecL3>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 8 : 5)
-                                     : c->band[l] ? 10 : 0;
+                                     : (spec_matches<SpecP2>(g, l == 0) && is_aligned16(c->dact[l])) ? 9
+                                     : c->band[l] && !c->rb ? 10 : 0;
             if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 3) nz = conv_wgrad_frame_blocks<SpecS2>(B);
@@ -2166,9 +2169,10 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
             else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
             else if (kind == 7) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
             else if (kind == 8) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
+            else if (kind == 9) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
             else if (kind == 10)
-                nz = l == 0 ? (g.OC == 16 ? conv_bytes_wgrad_blocks<16>(B, g.H, g.S, c->rb) : conv_bytes_wgrad_blocks<32>(B, g.H, g.S, c->rb))
-                            : g.OC == 32 ? conv_band_wgrad_blocks<32, 32>(B, g.H, g.W, c->rb) : conv_band_wgrad_blocks<32, 64>(B, g.H, g.W, c->rb);
+                nz = l == 0 ? (g.OC == 16 ? conv_bytes_wgrad_blocks<16>(B, g.H, g.S) : conv_bytes_wgrad_blocks<32>(B, g.H, g.S))
+                            : g.OC == 32 ? conv_band_wgrad_blocks<32, 32>(B, g.H, g.W) : conv_band_wgrad_blocks<32, 64>(B, g.H, g.W);
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
@@ -2189,12 +2193,14 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                 HIP_TRY((launch_conv_wgrad_bf16x6<SpecL2, 32>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb)));
             } else if (kind == 8) {
                 HIP_TRY(launch_conv_wgrad_s1_bf16x6<SpecL3>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
+            } else if (kind == 9) {
+                HIP_TRY(launch_conv_wgrad_bf16x6<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 10 && l == 0) {
-                if (g.OC == 16) HIP_TRY(launch_conv_bytes_wgrad<16>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s, c->rb));
-                else HIP_TRY(launch_conv_bytes_wgrad<32>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s, c->rb));
+                if (g.OC == 16) HIP_TRY(launch_conv_bytes_wgrad<16>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s));
+                else HIP_TRY(launch_conv_bytes_wgrad<32>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s));
             } else if (kind == 10) {
-                if (g.OC == 32) HIP_TRY((launch_conv_band_wgrad<32, 32>((const float *)xin, c->dact[l], part, B, g.H, g.W, s, c->rb)));
-                else HIP_TRY((launch_conv_band_wgrad<32, 64>((const float *)xin, c->dact[l], part, B, g.H, g.W, s, c->rb)));
+                if (g.OC == 32) HIP_TRY((launch_conv_band_wgrad<32, 32>((const float *)xin, c->dact[l], part, B, g.H, g.W, s)));
+                else HIP_TRY((launch_conv_band_wgrad<32, 64>((const float *)xin, c->dact[l], part, B, g.H, g.W, s)));
             } else if (l == 0) {
                 ConvWgradP<uint8_t> p; p.rb = c->rb;
                 p.M = g.OC; p.N = g.K + 1; p.K = B * g.OHW; p.kchunk = kchunk; p.g = g;
@@ -2223,10 +2229,15 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                                                      c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr));
             continue;
         }
-        if (c->fast && c->band[l]) {
+        if (c->fast && spec_matches<SpecP2>(g, false) && is_aligned16(th + c->off[2 * l])) {
+            HIP_TRY(launch_conv_dgrad_bf16x6<SpecP2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb));
+            continue;
+        }
+        if (c->fast && c->band[l] && !c->rb) {      // the reduced-precision variant keeps the any-shape kernels' sums
+
             const u32x4 *wf = c->bfrag[cur] + c->bfrag_dgrad[l];
-            if (g.OC == 32) HIP_TRY((launch_conv_band_dgrad<32, 32>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb)));
-            else HIP_TRY((launch_conv_band_dgrad<32, 64>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb)));
+            if (g.OC == 32) HIP_TRY((launch_conv_band_dgrad<32, 32>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s)));
+            else HIP_TRY((launch_conv_band_dgrad<32, 64>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s)));
             continue;
         }
         if (c->fast && spec_matches<SpecL3>(g, false)) {
