@@ -37,7 +37,6 @@ constexpr int BAND_MAXU = 13;                 // staging units (8 channels of a 
 
 typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 // Where the items of a launch lie.  "Rows" are output rows for the forward pass and the weight gradient, rows of the
 // stride-phase grid (ceil(H / 2)) for the input gradient.
@@ -56,7 +55,7 @@ constexpr int band_pitch() { return 6 * C + 16; }
 // ---------------------------------------------------------------- fragments --
 
 // One tensor's fragments: n threads write three vectors (the terms) each, at dst[(i / 64 * 3 + term) * 64 + i % 64].
-enum { FRAG_CONV = 0, FRAG_DGRAD_S2 = 1, FRAG_BYTES8 = 2 };
+enum { FRAG_CONV = 0, FRAG_BYTES8 = 1 };
 struct FragJob {
     const float *w;          // [OC][C][KS][KS]
     u32x4 *dst;
@@ -81,13 +80,6 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
         const int kb = blk % kbs, ot = blk / kbs, tap = kb / cgs, c0 = (kb % cgs) * 32 + 8 * g;
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = j.w[((size_t)(ot * 16 + l16) * j.C + c0 + e) * j.KS * j.KS + tap];
-    } else if (j.kind == FRAG_DGRAD_S2) {    // [channel tile][ry][rx][(a, e, 32 filters)]: row = channel, k = filter
-        const int ocbs = j.OC / 32, kbs = 4 * ocbs;
-        const int kb = blk % kbs; blk /= kbs;
-        const int rx = blk % 2, ry = (blk / 2) % 2, ct = blk / 4;
-        const int tap = kb / ocbs, u = ry + 2 * (tap / 2), v = rx + 2 * (tap % 2), oc0 = (kb % ocbs) * 32 + 8 * g;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) f[e] = j.w[((size_t)(oc0 + e) * j.C + ct * 16 + l16) * 16 + u * 4 + v];
     } else {                                 // byte layer, 4 planes, 8x8: [filter tile][u]: row = filter, k = (v, plane)
         const int u = blk % 8, ot = blk / 8;
 #pragma unroll
@@ -255,338 +247,6 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
     }
 }
 
-// ----------------------------------------------------------- input gradient --
-// dX[c][y][x] = [xin[c][y][x] > 0] * sum_{oc,a,e} dY[oc][iy - a][ix - e] W[oc][c][ry + 2a][rx + 2e],  y = 2 iy + ry,
-// x = 2 ix + rx: on the grid of stride phases a dense 2x2 convolution of the zero-padded dY per phase (ry, rx).
-// Wavefront = (ry, channel tile), and for 16 channels half of the pixel tiles; it computes both column phases from
-// one fetch of dY, so that a lane holds pixels 2 ix and 2 ix + 1 of four channels and a row leaves as consecutive
-// 8-byte stores (and the mask arrives as such loads) without a detour through LDS.
-template <int OC>
-constexpr int band_dgrad_maxu() { return OC == 64 ? 8 : BAND_MAXU; }       // 64 filters: 192 registers hold fragments
-
-template <int C, int OC>
-__global__ __launch_bounds__(256, 1) void conv_band_dgrad_kernel(const float *__restrict__ dy, const u32x4 *__restrict__ wfrag,
-                                                                 const float *__restrict__ xin, float *__restrict__ dx,
-                                                                 int nframes, const BandGeom b) {
-    constexpr int OCB = OC / 32, KB = 4 * OCB, CT = C / 16, PG = 2 / CT, NTERM = 3;
-    constexpr int PIT = band_pitch<OC>(), MAXU = band_dgrad_maxu<OC>();
-    static_assert((C == 16 || C == 32) && (OC == 32 || OC == 64), "16 or 32 channels, 32 or 64 filters");
-    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, g = lane >> 4;
-    const int ry = wave & 1, ct = (wave >> 1) % CT, pg = (wave >> 1) / CT;
-    const int HW = b.H * b.W, NPIX = b.OH * b.OW, GW = b.cols, PW = GW + 1, RL = b.R + 1;      // dY rows in LDS per frame
-    const int npx = b.F * RL * b.OW, NU = npx * (OC / 8);
-    const size_t total = (size_t)nframes * OC * NPIX;
-
-    for (int e = tid; e < b.F * RL * PW * PIT / 16; e += 256) ((u32x4 *)band_smem)[e] = u32x4{0u, 0u, 0u, 0u};   // columns outside dY
-
-    uint32_t src[MAXU];
-    int dst[MAXU], urow[MAXU];
-#pragma unroll
-    for (int i = 0; i < MAXU; ++i) {
-        const int u = min(tid + 256 * i, NU - 1);
-        const int og = u / npx, px = u % npx, row = px / b.OW, xc = px % b.OW, f = row / RL, r = row % RL;
-        src[i] = (uint32_t)((f * OC + og * 8) * NPIX + xc);
-        urow[i] = r - 1;
-        dst[i] = tid + 256 * i < NU ? (row * PW + xc + 1) * PIT + 16 * og : -1;
-    }
-    float pre[MAXU][8];
-    auto fetch = [&](int item) {
-        const int f0 = (item / b.nb) * b.F, g0 = (item % b.nb) * b.R;
-        const size_t base = (size_t)f0 * OC * NPIX;
-        const uint32_t lim = band_limit(total, base, NPIX);
-#pragma unroll
-        for (int i = 0; i < MAXU; ++i)
-            if (256 * i < NU) {
-                const int yr = min(max(g0 + urow[i], 0), b.OH - 1);
-                band_load8(dy + base, 4u * min(src[i] + (uint32_t)(yr * b.OW), lim), NPIX, pre[i]);
-            }
-    };
-    int item = blockIdx.x;
-    fetch(min(item, b.items - 1));
-
-    Bf16x8Bits wq[2][KB][NTERM];
-    {
-        const u32x4 *ws = wfrag + (size_t)((ct * 2 + ry) * 2 * KB) * 3 * 64 + lane;
-#pragma unroll
-        for (int rx = 0; rx < 2; ++rx)
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t) wq[rx][kb][t].u = ws[((rx * KB + kb) * 3 + t) * 64];
-    }
-
-    for (; item < b.items; item += gridDim.x) {
-        const int f0 = (item / b.nb) * b.F, g0 = (item % b.nb) * b.R;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MAXU; ++i)
-            if (dst[i] >= 0) {
-                if ((unsigned)(g0 + urow[i]) >= (unsigned)b.OH) {       // a row above or below dY
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) pre[i][c] = 0.f;
-                }
-                band_store8<OC>(band_smem + dst[i], pre[i]);
-            }
-        __syncthreads();
-        fetch(min(item + (int)gridDim.x, b.items - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        const int cnt = b.F * b.R * GW, ntile = (cnt + 15) / 16;
-        auto pass = [&](auto nc, int t0) {
-            constexpr int N = decltype(nc)::value;
-            int base[N];
-            size_t out[N];
-            bool in[N], two[N];
-            f32x2_dw mk[N][4];
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                uint32_t p = (uint32_t)((t0 + n * PG) * 16 + l16), f, rem, i, j;
-                in[n] = (int)p < cnt;
-                if (!in[n]) p = 0;
-                b.dFR.divmod(p, f, rem);
-                b.dC.divmod(rem, i, j);
-                base[n] = (((int)f * RL + (int)i + 1) * PW + (int)j + 1) * PIT + 16 * g;
-                const int yr = 2 * (g0 + (int)i) + ry;
-                in[n] = in[n] && yr < b.H && f0 + (int)f < nframes;
-                two[n] = 2 * (int)j + 1 < b.W;
-                out[n] = ((size_t)(f0 + (int)f) * C + ct * 16 + 4 * g) * HW + yr * b.W + 2 * (int)j;
-                if (!in[n]) out[n] = 0;
-                // the last column of an odd map is the second of the pair in front of it
-#pragma unroll
-                for (int r = 0; r < 4; ++r) mk[n][r] = *(const f32x2_dw *)(xin + out[n] + (size_t)r * HW - (in[n] && !two[n] ? 1 : 0));
-            }
-            floatx4 acc[N][2];
-#pragma unroll
-            for (int n = 0; n < N; ++n) acc[n][0] = acc[n][1] = floatx4{0.f, 0.f, 0.f, 0.f};
-            Bf16x8Bits dv[2][N][NTERM];
-            auto read = [&](int kb, Bf16x8Bits (&d)[N][NTERM]) {
-                const int tap = kb / OCB, koff = -((tap / 2) * PW + tap % 2) * PIT + (kb % OCB) * 64;
-#pragma unroll
-                for (int n = 0; n < N; ++n)
-#pragma unroll
-                    for (int t = 0; t < NTERM; ++t) d[n][t].u = *(const u32x4 *)(band_smem + base[n] + koff + t * 2 * OC);
-            };
-            read(0, dv[0]);
-            __builtin_amdgcn_sched_barrier(0);               // the mask loads above are on their way
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                if (kb + 1 < KB) read(kb + 1, dv[(kb + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
-#pragma unroll
-                for (int q = 0; q < 6; ++q)
-#pragma unroll
-                    for (int n = 0; n < N; ++n)
-#pragma unroll
-                        for (int rx = 0; rx < 2; ++rx)
-                            acc[n][rx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wq[rx][kb][PA[q]].v,
-                                                                                 dv[kb & 1][n][PB[q]].v, acc[n][rx], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int n = 0; n < N; ++n)
-                if (in[n]) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float *o = dx + out[n] + (size_t)r * HW;
-                        if (two[n])
-                            *(f32x2_dw *)o = f32x2_dw{mk[n][r].x > 0.f ? acc[n][0][r] : 0.f, mk[n][r].y > 0.f ? acc[n][1][r] : 0.f};
-                        else o[0] = mk[n][r].y > 0.f ? acc[n][0][r] : 0.f;
-                    }
-                }
-        };
-        int t = pg, left = (ntile - pg + PG - 1) / PG;
-        for (; left >= 4; left -= 4, t += 4 * PG) pass(std::integral_constant<int, 4>{}, t);
-        if (left == 3) pass(std::integral_constant<int, 3>{}, t);
-        else if (left == 2) pass(std::integral_constant<int, 2>{}, t);
-        else if (left == 1) pass(std::integral_constant<int, 1>{}, t);
-    }
-}
-
-// ---------------------------------------------------------- weight gradient --
-// dW[oc][c][u][v] = sum over frames and output pixels of dY[oc][i][j] x[c][2i + u][2j + v];  db[oc] = sum of dY[oc].
-// The contraction runs over pixels, 32 per product, but LDS holds channels together: the operands come through the
-// transposing LDS read, in which 16 lanes name the places of four pixels (8 bytes = 4 channels each) and every lane
-// receives one channel of the four.  Pixels can be anywhere, so no tap needs a shifted copy and no row any padding.
-// Wavefront u takes the four taps of filter row u, all filters and all channels, and keeps their sums for all items of
-// its block; the bias gradient is one more product, dY times ones.  A block leaves one partial gradient
-// part[blockIdx.x][OC][16 C + 1] (the last column is the bias gradient), added up in block order by a second kernel.
-__device__ __forceinline__ u32x4 band_tr8(const unsigned char *p0, const unsigned char *p1) {
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    union { s16x4 s[2]; u32x4 u; } o;
-    o.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p0);
-    o.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p1);
-    return o.u;
-}
-
-template <int C, int OC>
-struct ConvBandWgradGeom {
-    static constexpr int K1 = 16 * C + 1, OTP = 16 * C + 4;       // OTP: floats per filter row of the block's result in LDS
-    static constexpr int OUT_BYTES = OC * OTP * 4;
-};
-
-template <int C, int OC>
-__global__ __launch_bounds__(256, 1) void conv_band_wgrad_kernel(const float *__restrict__ x, const float *__restrict__ dy,
-                                                                 float *__restrict__ part, int nframes, const BandGeom b) {
-    typedef ConvBandWgradGeom<C, OC> G;
-    constexpr int KS = 4, S = 2, CT = C / 16, OT = OC / 16, NTERM = 3;
-    constexpr int XPIT = band_pitch<C>(), DPIT = band_pitch<OC>(), MAXX = BAND_MAXU, MAXD = OC / 8;
-    static_assert(C % 16 == 0 && OC % 16 == 0, "channels and filters in groups of 16");
-    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, g = lane >> 4;
-    const int HW = b.H * b.W, NPIX = b.OH * b.OW;
-    const int RI = (b.R - 1) * S + KS, WH = (b.W + 1) / 2, WP = 2 * WH;
-    const int npx = b.F * RI * b.W, NX = npx * (C / 8);
-    const int fr = b.R * b.OW, cnt = b.F * fr, nkb = (cnt + 31) / 32, ND = cnt * (OC / 8);
-    unsigned char *xsm = band_smem, *dsm = band_smem + (size_t)b.F * RI * WP * XPIT;
-    const size_t xtotal = (size_t)nframes * C * HW, dtotal = (size_t)nframes * OC * NPIX;
-
-    // everything starts finite, and dY stays zero behind the last pixel: those products add nothing
-    for (int e = tid; e < (int)((dsm - xsm) + nkb * 32 * DPIT) / 16; e += 256) ((u32x4 *)xsm)[e] = u32x4{0u, 0u, 0u, 0u};
-
-    uint32_t xsrc[MAXX], dsrc[MAXD];
-    int xdst[MAXX], ddst[MAXD], drem[MAXD];
-#pragma unroll
-    for (int i = 0; i < MAXX; ++i) {
-        const int u = min(tid + 256 * i, NX - 1);
-        const int cg = u / npx, px = u % npx, row = px / b.W, xc = px % b.W, f = row / RI, r = row % RI;
-        xsrc[i] = (uint32_t)((f * C + cg * 8) * HW + r * b.W + xc);
-        xdst[i] = tid + 256 * i < NX ? (row * WP + (xc & 1) * WH + (xc >> 1)) * XPIT + 16 * cg : -1;
-    }
-#pragma unroll
-    for (int i = 0; i < MAXD; ++i) {
-        const int u = min(tid + 256 * i, ND - 1);
-        const int og = u / cnt, p = u % cnt, f = p / fr, rem = p % fr;
-        dsrc[i] = (uint32_t)((f * OC + og * 8) * NPIX + rem);
-        drem[i] = f * (1 << 20) + rem;
-        ddst[i] = tid + 256 * i < ND ? p * DPIT + 16 * og : -1;
-    }
-    float xpre[MAXX][8], dpre[MAXD][8];
-    auto fetch = [&](int item) {
-        const int f0 = (item / b.nb) * b.F, i0 = (item % b.nb) * b.R;
-        const size_t xb = (size_t)f0 * C * HW + (size_t)i0 * S * b.W, db = (size_t)f0 * OC * NPIX + (size_t)i0 * b.OW;
-        const uint32_t xl = band_limit(xtotal, xb, HW), dl = band_limit(dtotal, db, NPIX);
-#pragma unroll
-        for (int i = 0; i < MAXX; ++i)
-            if (256 * i < NX) band_load8(x + xb, 4u * min(xsrc[i], xl), HW, xpre[i]);
-#pragma unroll
-        for (int i = 0; i < MAXD; ++i)
-            if (256 * i < ND) band_load8(dy + db, 4u * min(dsrc[i], dl), NPIX, dpre[i]);
-    };
-    int item = blockIdx.x;
-    fetch(min(item, b.items - 1));
-
-    floatx4 acc[4][CT][OT], bacc[OT];
-#pragma unroll
-    for (int m = 0; m < OT; ++m) {
-        bacc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int c = 0; c < CT; ++c) acc[v][c][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    Bf16x8Bits ones;
-    ones.u = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-
-    for (; item < b.items; item += gridDim.x) {
-        const int f0 = (item / b.nb) * b.F, i0 = (item % b.nb) * b.R;
-        const int vpix = min(b.R, b.OH - i0) * b.OW, vfr = min(b.F, nframes - f0);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MAXX; ++i)
-            if (xdst[i] >= 0) band_store8<C>(xsm + xdst[i], xpre[i]);
-#pragma unroll
-        for (int i = 0; i < MAXD; ++i)
-            if (ddst[i] >= 0) {
-                if ((drem[i] & ((1 << 20) - 1)) >= vpix || (drem[i] >> 20) >= vfr) {      // a row or frame that does not exist
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) dpre[i][c] = 0.f;
-                }
-                band_store8<OC>(dsm + ddst[i], dpre[i]);
-            }
-        __syncthreads();
-        fetch(min(item + (int)gridDim.x, b.items - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        for (int kb = 0; kb < nkb; ++kb) {
-            // my pixel of each half: k = 16 h + 4 g + (l16 / 4), and my four channels of the tile: 4 (l16 % 4) ..
-            const unsigned char *xp[2], *dp[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t p = (uint32_t)(32 * kb + 16 * h + 4 * g + (l16 >> 2)), f, rem, i, j;
-                dp[h] = dsm + p * DPIT + 8 * (l16 & 3);
-                if ((int)p >= cnt) p = 0;
-                b.dFR.divmod(p, f, rem);
-                b.dC.divmod(rem, i, j);
-                xp[h] = xsm + (((int)f * RI + (int)i * S + wave) * WP + (int)j) * XPIT + 8 * (l16 & 3);
-            }
-            Bf16x8Bits d[OT][NTERM];
-#pragma unroll
-            for (int m = 0; m < OT; ++m)
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t) d[m][t].u = band_tr8(dp[0] + m * 32 + t * 2 * OC, dp[1] + m * 32 + t * 2 * OC);
-            Bf16x8Bits xv[2][NTERM];
-            auto read = [&](int q, Bf16x8Bits (&o)[NTERM]) {
-                const int v = q / CT, c = q % CT, off = ((v & 1) * WH + (v >> 1)) * XPIT + c * 32;
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t) o[t].u = band_tr8(xp[0] + off + t * 2 * C, xp[1] + off + t * 2 * C);
-            };
-            read(0, xv[0]);
-            if ((kb & 3) == wave) {
-#pragma unroll
-                for (int t = NTERM - 1; t >= 0; --t)
-#pragma unroll
-                    for (int m = 0; m < OT; ++m) bacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[m][t].v, ones.v, bacc[m], 0, 0, 0);
-            }
-#pragma unroll
-            for (int q = 0; q < 4 * CT; ++q) {
-                if (q + 1 < 4 * CT) read(q + 1, xv[(q + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
-#pragma unroll
-                for (int e = 0; e < 6; ++e)
-#pragma unroll
-                    for (int m = 0; m < OT; ++m)
-                        acc[q / CT][q % CT][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[m][PA[e]].v, xv[q & 1][PB[e]].v,
-                                                                                         acc[q / CT][q % CT][m], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-    // lane (l16, g), register r of acc[v][c][m]: filter 16 m + 4 g + r, channel 16 c + l16, tap (wave, v); put together
-    // in LDS, so that it leaves in rows
-    __syncthreads();
-    float *ot = (float *)band_smem;
-    __shared__ float bsh[4][OC];
-    if (l16 == 0) {
-#pragma unroll
-        for (int m = 0; m < OT; ++m)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) bsh[wave][m * 16 + 4 * g + r] = bacc[m][r];
-    }
-#pragma unroll
-    for (int c = 0; c < CT; ++c)
-#pragma unroll
-        for (int m = 0; m < OT; ++m)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                *(float4 *)(ot + (m * 16 + 4 * g + r) * G::OTP + (c * 16 + l16) * 16 + wave * 4) =
-                    float4{acc[0][c][m][r], acc[1][c][m][r], acc[2][c][m][r], acc[3][c][m][r]};
-    __syncthreads();
-    float *pb = part + (size_t)blockIdx.x * OC * G::K1;
-    for (int e = tid; e < OC * C * 4; e += 256) {
-        const int oc = e / (C * 4), kq = e % (C * 4);
-        const float4 v = *(const float4 *)(ot + oc * G::OTP + 4 * kq);
-        *(f32x4_dw *)(pb + (size_t)oc * G::K1 + 4 * kq) = f32x4_dw{v.x, v.y, v.z, v.w};
-    }
-    if (tid < OC) pb[(size_t)tid * G::K1 + 16 * C] = (bsh[0][tid] + bsh[1][tid]) + (bsh[2][tid] + bsh[3][tid]);
-}
-
 // ------------------------------------------------------------------- launch --
 
 // The most rows per item for which `bytes(F, R)` fits a compute unit's LDS and `units(F, R)` the staging registers,
@@ -624,22 +284,6 @@ inline bool band_fwd_geom(BandGeom &b, int nframes) {
     return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return band_in_px(b, F, R) * band_pitch<C>(); },
                       [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); });
 }
-template <int OC>
-inline bool band_dgrad_geom(BandGeom &b, int nframes) {
-    const int GW = (b.W + 1) / 2;
-    return band_split(b, nframes, (b.H + 1) / 2, GW, [&](int F, int R) { return F * (R + 1) * (GW + 1) * band_pitch<OC>(); },
-                      [&](int F, int R) { return F * (R + 1) * b.OW * (OC / 8); }, band_dgrad_maxu<OC>());
-}
-// dY takes one staging unit per thread and eight filters of up to 256 pixels
-template <int C, int OC>
-inline bool band_wgrad_geom(BandGeom &b, int nframes) {
-    return band_split(b, nframes, b.OH, b.OW,
-                      [&](int F, int R) {
-                          const int px = (F * R * b.OW + 31) / 32 * 32;
-                          return px > 256 ? 2 * BAND_LDS : band_in_px(b, F, R) * band_pitch<C>() + px * band_pitch<OC>();
-                      },
-                      [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); });
-}
 inline int band_blocks(const BandGeom &b) { return b.items < BAND_CUS ? b.items : BAND_CUS; }
 
 template <class K>
@@ -650,11 +294,11 @@ inline hipError_t band_allow_lds(K kernel, bool &done) {
     return e;
 }
 
-// Whether maps of H x W can be run at all (every kernel's smallest item fits).
-template <int C, int OC>
+// Whether maps of H x W can be run at all (the smallest item fits).
+template <int C>
 inline bool band_ok(int H, int W) {
-    BandGeom b = band_geom(H, W), c = b, d = b;
-    return H >= 4 && W >= 4 && band_fwd_geom<C>(b, 1) && band_dgrad_geom<OC>(c, 1) && band_wgrad_geom<C, OC>(d, 1);
+    BandGeom b = band_geom(H, W);
+    return H >= 4 && W >= 4 && band_fwd_geom<C>(b, 1);
 }
 
 template <int C, int OC>
@@ -667,39 +311,6 @@ inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const
     if (e != hipSuccess) return e;
     ga3c::launch((conv_band_fwd_kernel<C, OC>), dim3(band_blocks(b)), dim3(256), band_in_px(b, b.F, b.R) * band_pitch<C>(), s, x, wfrag,
                  bias, y, n, b);
-    return hipGetLastError();
-}
-
-template <int C, int OC>
-inline hipError_t launch_conv_band_dgrad(const float *dy, const u32x4 *wfrag, const float *xin, float *dx, int n, int H, int W, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    BandGeom b = band_geom(H, W);
-    if (!band_dgrad_geom<OC>(b, n)) return hipErrorInvalidValue;
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_dgrad_kernel<C, OC>, attr);
-    if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_dgrad_kernel<C, OC>), dim3(band_blocks(b)), dim3(256),
-                 b.F * (b.R + 1) * (b.cols + 1) * band_pitch<OC>(), s, dy, wfrag, xin, dx, n, b);
-    return hipGetLastError();
-}
-
-// Blocks of the weight gradient (= partial gradients it leaves).
-template <int C, int OC>
-inline int conv_band_wgrad_blocks(int n, int H, int W) {
-    BandGeom b = band_geom(H, W);
-    return band_wgrad_geom<C, OC>(b, n) ? band_blocks(b) : 0;
-}
-template <int C, int OC>
-inline hipError_t launch_conv_band_wgrad(const float *x, const float *dy, float *part, int n, int H, int W, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    BandGeom b = band_geom(H, W);
-    if (!band_wgrad_geom<C, OC>(b, n)) return hipErrorInvalidValue;
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_wgrad_kernel<C, OC>, attr);
-    if (e != hipSuccess) return e;
-    const int px = (b.F * b.R * b.OW + 31) / 32 * 32;
-    const int lds = std::max(band_in_px(b, b.F, b.R) * band_pitch<C>() + px * band_pitch<OC>(), ConvBandWgradGeom<C, OC>::OUT_BYTES);
-    ga3c::launch((conv_band_wgrad_kernel<C, OC>), dim3(band_blocks(b)), dim3(256), lds, s, x, dy, part, n, b);
     return hipGetLastError();
 }
 

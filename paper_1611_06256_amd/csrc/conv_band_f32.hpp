@@ -302,6 +302,332 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_f32_fwd_kernel(const uint8_
     }
 }
 
+// ----------------------------------------------------------- input gradient --
+// dX[c][y][x] = [xin[c][y][x] > 0] * sum_{oc,a,e} dY[oc][iy - a][ix - e] W[oc][c][ry + 2a][rx + 2e],  y = 2 iy + ry,
+// x = 2 ix + rx, with k in the order (oc, a, e): a group of 16 is four filters, the four products of a group are the four
+// (a, e).  The zero-padded dY sits in LDS as it is in memory; the four phases (ry, rx) of 16 channels share one fetch of
+// it, and a lane's 16 taps of (filter, channel) are 64 contiguous bytes of the weights.  Wavefront = (channel tile, half
+// of the pixel tiles), two pixel tiles at a time.
+// Bound by the instruction (28.7 GFLOP of conv2 at 640 frames of 77x77: 200 us at 144 TFLOP/s).
+template <int OC>
+constexpr int band_f32_dgrad_maxk() { return 64 / OC; }      // values of a filter's plane in flight per thread
+
+template <int OC, bool RB>
+__global__ __launch_bounds__(256, 2) void conv_band_f32_dgrad_kernel(const float *__restrict__ dy, const float *__restrict__ w,
+                                                                     const float *__restrict__ xin, float *__restrict__ dx,
+                                                                     int nframes, int pitch, const BandGeom b) {
+    constexpr int C = 32, MAXK = band_f32_dgrad_maxk<OC>(), KB = OC / 4;
+    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
+    float *ys = (float *)band_smem;                   // [oc][frame][row][PW], `pitch` floats per filter
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const int ct = wave & 1, pg = wave >> 1;
+    const int HW = b.H * b.W, NPIX = b.OH * b.OW, GW = b.cols, PW = GW + 1, RL = b.R + 1;
+    const int chunk = RL * b.OW, plane = b.F * chunk;
+
+    for (int e = tid; e < OC * pitch; e += 256) ys[e] = 0.f;      // columns outside dY stay zero
+
+    int src[MAXK], dst[MAXK], urow[MAXK];
+#pragma unroll
+    for (int k = 0; k < MAXK; ++k) {
+        const int e = min(tid + 256 * k, plane - 1), f = e / chunk, r = e % chunk / b.OW, xc = e % b.OW;
+        src[k] = f * OC * NPIX + xc;
+        urow[k] = r - 1;
+        dst[k] = (f * RL + r) * PW + xc + 1;
+    }
+    const size_t total = (size_t)nframes * OC * NPIX;
+    float pre[OC][MAXK];
+    auto fetch = [&](int item) {
+        const int f0 = (item / b.nb) * b.F, g0 = (item % b.nb) * b.R;
+        const size_t base = (size_t)f0 * OC * NPIX;
+        const size_t left = total - base - (size_t)(OC - 1) * NPIX - 1;
+        const uint32_t lim = left > 0x3fffffff ? 0x3fffffffu : (uint32_t)left;
+#pragma unroll
+        for (int k = 0; k < MAXK; ++k)
+            if (256 * k < plane) {
+                const int yr = min(max(g0 + urow[k], 0), b.OH - 1);
+                const uint32_t off = 4u * min((uint32_t)(src[k] + yr * b.OW), lim);
+#pragma unroll
+                for (int c = 0; c < OC; ++c) pre[c][k] = *(const float *)((const char *)(dy + base + (size_t)c * NPIX) + off);
+            }
+    };
+    int item = blockIdx.x;
+    fetch(min(item, b.items - 1));
+    const float *wl = w + ((size_t)g * C + ct * 16 + l16) * 16;      // my taps of filter g
+
+    for (; item < b.items; item += gridDim.x) {
+        const int f0 = (item / b.nb) * b.F, g0 = (item % b.nb) * b.R;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < MAXK; ++k)
+            if (tid + 256 * k < plane) {
+                const bool in = (unsigned)(g0 + urow[k]) < (unsigned)b.OH;      // else a row above or below dY
+#pragma unroll
+                for (int c = 0; c < OC; ++c) ys[c * pitch + dst[k]] = in ? (RB ? bf16_rne(pre[c][k]) : pre[c][k]) : 0.f;
+            }
+        __syncthreads();
+        fetch(min(item + (int)gridDim.x, b.items - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        const int cnt = b.F * b.R * GW, ntile = (cnt + 15) / 16;
+        auto pass = [&](auto nc, int t0) {
+            constexpr int N = decltype(nc)::value;
+            const float *base[N];
+            size_t out[N];
+            bool in[N][2], two[N];
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                uint32_t p = (uint32_t)((t0 + 2 * n) * 16 + l16), f, rem, i, j;
+                bool ok = (int)p < cnt;
+                if (!ok) p = 0;
+                b.dFR.divmod(p, f, rem);
+                b.dC.divmod(rem, i, j);
+                base[n] = ys + g * pitch + ((int)f * RL + (int)i + 1) * PW + (int)j + 1;
+                const int yr = 2 * (g0 + (int)i);
+                ok = ok && f0 + (int)f < nframes;
+                in[n][0] = ok && yr < b.H;
+                in[n][1] = ok && yr + 1 < b.H;
+                two[n] = 2 * (int)j + 1 < b.W;
+                out[n] = in[n][0] ? ((size_t)(f0 + (int)f) * C + ct * 16 + 4 * g) * HW + yr * b.W + 2 * (int)j : 0;
+            }
+            floatx4 acc[N][2][2];
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc[n][q >> 1][q & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
+            float4 wv[2][4];
+            auto read_w = [&](int kb, float4 (&d)[4]) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    d[u] = ((const float4 *)(wl + (size_t)kb * 4 * C * 16))[u];
+                    if (RB) d[u] = bf16_rne(d[u]);
+                }
+            };
+            float yv[2][N][4];
+            auto read_y = [&](int kb, float (&d)[N][4]) {
+#pragma unroll
+                for (int n = 0; n < N; ++n)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) d[n][t] = base[n][kb * 4 * pitch - (t >> 1) * PW - (t & 1)];
+            };
+            read_w(0, wv[0]);
+            read_y(0, yv[0]);
+#pragma unroll 2
+            for (int kb = 0; kb < KB; ++kb) {
+                const int kn = min(kb + 1, KB - 1);
+                read_w(kn, wv[(kb + 1) & 1]);
+                read_y(kn, yv[(kb + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int ry = 0; ry < 2; ++ry) {
+                        const float4 q = wv[kb & 1][ry + 2 * (t >> 1)];
+#pragma unroll
+                        for (int rx = 0; rx < 2; ++rx) {
+                            const float we = t & 1 ? (rx ? q.w : q.z) : (rx ? q.y : q.x);
+#pragma unroll
+                            for (int n = 0; n < N; ++n)
+                                acc[n][ry][rx] = __builtin_amdgcn_mfma_f32_16x16x4f32(we, yv[kb & 1][n][t], acc[n][ry][rx], 0, 0, 0);
+                        }
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int n = 0; n < N; ++n) {
+                f32x2_dw mk[2][4];
+                // the last column of an odd map is the second of the pair in front of it
+#pragma unroll
+                for (int ry = 0; ry < 2; ++ry)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        mk[ry][r] = *(const f32x2_dw *)(xin + out[n] + (in[n][ry] ? ry * b.W : 0) + (size_t)r * HW - (in[n][0] && !two[n] ? 1 : 0));
+#pragma unroll
+                for (int ry = 0; ry < 2; ++ry)
+                    if (in[n][ry]) {
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            float *o = dx + out[n] + ry * b.W + (size_t)r * HW;
+                            const f32x2_dw m = mk[ry][r];
+                            if (two[n]) *(f32x2_dw *)o = f32x2_dw{m.x > 0.f ? acc[n][ry][0][r] : 0.f, m.y > 0.f ? acc[n][ry][1][r] : 0.f};
+                            else o[0] = m.y > 0.f ? acc[n][ry][0][r] : 0.f;
+                        }
+                    }
+            }
+        };
+        int t = pg, left = (ntile - pg + 1) / 2;
+        for (; left >= 2; left -= 2, t += 4) pass(std::integral_constant<int, 2>{}, t);
+        if (left == 1) pass(std::integral_constant<int, 1>{}, t);
+    }
+}
+
+// ---------------------------------------------------------- weight gradient --
+// dW[oc][k] = scale * sum over the pixels P of all frames of dY[P][oc] x[P][tap k], db[oc] = sum of dY[P][oc], in the chunks of
+// pixels (blockIdx.x) and the order of problems.hpp's ConvWgradP: part[chunk][OC][K + 1].  TIn bytes: 8x8 filters over four
+// planes, any stride; floats: 4x4, stride 2, 32 channels.
+//
+// A chunk is one long chain of sums, so the parallelism left is chunks x columns: a wavefront keeps one tile of 16 taps (a
+// channel of the 4x4 filters, two rows of an 8x8 plane) of all filters; the tile of column K multiplies by one.  The chunk
+// goes by in steps of F32_WG_KT pixels, whose dY lies in LDS as [filter][pixel] and whose input rows as they are in memory:
+// the rows that a frame's windows touch, numbered on from frame to frame (S (OH - 1) + KS to a frame), are contiguous for any
+// run of pixels, also across frames, and a table gives each pixel's place in them.
+// Bound by the instruction and by whole wavefronts per SIMD: 62 GFLOP of conv1 at 640 frames of 84x84 with stride 1 are 2907
+// tiles of 161 us on 1024 SIMDs.
+// The next step's values go from memory straight to the other half of the LDS buffers (no registers hold them).
+constexpr int F32_WG_KT = 64;
+struct F32WgradGeom {
+    int C, H, W, S, OH, OW;
+    int K, kchunk;           // pixels in all, pixels per chunk
+    int rows;                // input rows of a step in LDS, at most
+    int RF;                  // rows per frame in the numbering above
+    int stage;               // bytes of one half of the LDS buffers
+    FastDiv dNPIX, dOW, dRF;
+    float scale;
+};
+template <class TIn> constexpr int f32_wgrad_waves() { return sizeof(TIn) == 1 ? 6 : 8; }
+template <class TIn> constexpr int f32_wgrad_maxx() { return sizeof(TIn) == 1 ? 8 : 13; }      // dwords of input per thread and step
+
+// One dword per lane from `src` to lds + 4 * lane; lds is the same for the whole wavefront.
+__device__ __forceinline__ void load_dword_to_lds(const void *src, void *lds) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t *)src, (__attribute__((address_space(3))) uint32_t *)lds, 4, 0, 0);
+}
+
+template <class TIn, int OC, bool RB>
+__global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 : 4) void conv_f32_wgrad_kernel(
+    const TIn *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, const F32WgradGeom b) {
+    constexpr bool BYTE = sizeof(TIn) == 1;
+    constexpr int OT = OC / 16, KT = F32_WG_KT, AP = KT + 4, NW = f32_wgrad_waves<TIn>(), NT = 64 * NW, MAXX = f32_wgrad_maxx<TIn>();
+    constexpr int NG = KT / 16, ESZ = (int)sizeof(TIn);
+    static_assert(KT == 64, "a lane stages one pixel");
+    // each half: dY [OC][AP] floats, [KT] byte offsets of the pixels' windows, the input [channel][rows][W]
+    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
+    constexpr int OTAB = OC * AP * 4, XS = OTAB + KT * 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const int NPIX = b.OH * b.OW, HW = b.H * b.W, ncol = BYTE ? 16 : b.C;
+    const int q = (int)blockIdx.y * NW + wave;
+    // the channels this block's tiles need, in dwords
+    const int c0 = BYTE ? 0 : (int)blockIdx.y * NW, nch = BYTE ? 4 : max(0, min(NW, b.C - c0));
+    const int UW = b.W * ESZ / 4, NU = nch * b.rows * UW, bytes_per_ch = b.rows * b.W * ESZ;
+    const int kbeg = (int)blockIdx.x * b.kchunk, kend = min(b.K, kbeg + b.kchunk);
+    const int last_row = (int)b.dNPIX.div((uint32_t)(b.K - 1)) * b.RF + b.RF - 1;
+
+    uint32_t xoff[MAXX];
+    int xrow[MAXX];
+#pragma unroll
+    for (int i = 0; i < MAXX; ++i) {
+        const int u = max(0, min(tid + NT * i, NU - 1)), c = u / (b.rows * UW), rem = u % (b.rows * UW);
+        xrow[i] = rem / UW;
+        xoff[i] = (uint32_t)((c0 + c) * HW * ESZ + 4 * (rem % UW));
+    }
+    auto fetch = [&](int k0, unsigned char *half) {
+        uint32_t f0, p0, i0, j0;
+        b.dNPIX.divmod((uint32_t)k0, f0, p0);
+        b.dOW.divmod(p0, i0, j0);
+        const int row0 = (int)f0 * b.RF + (int)i0 * b.S;
+#pragma unroll
+        for (int i = 0; i < MAXX; ++i)
+            if (64 * wave + NT * i < NU) {
+                uint32_t f, r;
+                b.dRF.divmod((uint32_t)min(row0 + xrow[i], last_row), f, r);
+                load_dword_to_lds((const char *)x + (size_t)f * b.C * HW * ESZ + xoff[i] + r * (uint32_t)(b.W * ESZ),
+                                  half + XS + (64 * wave + NT * i) * 4);
+            }
+        uint32_t f, p, i, j;
+        b.dNPIX.divmod((uint32_t)min(k0 + lane, b.K - 1), f, p);
+        const float *src = dy + (size_t)f * OC * NPIX + p;
+#pragma unroll
+        for (int m = 0; m < OC; m += NW)
+            if (OC % NW == 0 || m + wave < OC) load_dword_to_lds(src + (size_t)(m + wave) * NPIX, half + (m + wave) * AP * 4);
+        b.dOW.divmod(p, i, j);
+        if (wave == 0) ((int *)(half + OTAB))[lane] = k0 + lane < kend ? (((int)f * b.RF + (int)i * b.S - row0) * b.W + (int)j * b.S) * ESZ : 0;
+    };
+    fetch(kbeg, band_smem);
+
+    floatx4 acc[OT];
+#pragma unroll
+    for (int m = 0; m < OT; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // my tap's place behind a window's first value
+    const int xl = BYTE ? (q / 4) * bytes_per_ch + (2 * (q % 4) + (l16 >> 3)) * b.W + (l16 & 7)
+                        : (q - c0) * bytes_per_ch + ((l16 >> 2) * b.W + (l16 & 3)) * 4;
+    int at = 0;
+    for (int k0 = kbeg; k0 < kend; k0 += KT, at ^= 1) {
+        unsigned char *half = band_smem + at * b.stage;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // my loads for this step have arrived in LDS
+        __syncthreads();                                      // everybody's have, and the other half has been read
+        if (k0 + KT < kend) fetch(k0 + KT, band_smem + (at ^ 1) * b.stage);
+        else if (k0 + KT > kend) {                            // no pixels behind the chunk's last
+            for (int oc = wave; oc < OC; oc += NW)
+                if (k0 + lane >= kend) ((float *)half)[oc * AP + lane] = 0.f;
+            __syncthreads();
+        }
+        const float *al = (const float *)half + l16 * AP + 4 * g;
+        auto read_a = [&](int grp, float4 (&d)[OT]) {
+#pragma unroll
+            for (int m = 0; m < OT; ++m) {
+                d[m] = *(const float4 *)(al + m * 16 * AP + 16 * grp);
+                if (RB) d[m] = bf16_rne(d[m]);
+            }
+        };
+        if (q < ncol) {
+            const int4 *ol = (const int4 *)(half + OTAB) + g;
+            const unsigned char *xb = half + XS + xl;
+            auto read_x = [&](const int4 o, float (&d)[4]) {
+                if (BYTE) { d[0] = (float)xb[o.x]; d[1] = (float)xb[o.y]; d[2] = (float)xb[o.z]; d[3] = (float)xb[o.w]; }
+                else {
+                    d[0] = *(const float *)(xb + o.x); d[1] = *(const float *)(xb + o.y); d[2] = *(const float *)(xb + o.z); d[3] = *(const float *)(xb + o.w);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        if (RB) d[t] = bf16_rne(d[t]);
+                }
+            };
+            int4 o[NG];
+#pragma unroll
+            for (int grp = 0; grp < NG; ++grp) o[grp] = ol[4 * grp];
+            float xv[2][4];
+            float4 av[2][OT];
+            read_x(o[0], xv[0]);
+            read_a(0, av[0]);
+#pragma unroll
+            for (int grp = 0; grp < NG; ++grp) {
+                if (grp + 1 < NG) {
+                    read_x(o[grp + 1], xv[(grp + 1) & 1]);
+                    read_a(grp + 1, av[(grp + 1) & 1]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int m = 0; m < OT; ++m) {
+                        const float4 a = av[grp & 1][m];
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(t == 0 ? a.x : t == 1 ? a.y : t == 2 ? a.z : a.w, xv[grp & 1][t], acc[m], 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else if (q == ncol) {
+#pragma unroll
+            for (int grp = 0; grp < NG; ++grp) {
+                float4 a[OT];
+                read_a(grp, a);
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int m = 0; m < OT; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(t == 0 ? a[m].x : t == 1 ? a[m].y : t == 2 ? a[m].z : a[m].w, 1.f, acc[m], 0, 0, 0);
+            }
+        }
+    }
+    const int K1 = 16 * ncol + 1;
+    float *pb = part + (size_t)blockIdx.x * OC * K1;
+    if (q < ncol || (q == ncol && l16 == 0)) {
+#pragma unroll
+        for (int m = 0; m < OT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pb[(size_t)(m * 16 + 4 * g + r) * K1 + 16 * q + l16] = q < ncol ? acc[m][r] * b.scale : acc[m][r];
+    }
+}
+
 template <int C>
 inline bool band_f32_geom(BandGeom &b, int nframes) {
     auto px = [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W; };
@@ -343,6 +669,94 @@ inline hipError_t launch_conv_bytes_f32_fwd(const uint8_t *x, const float *w, co
                                             int rb) {
     if (n <= 0) return hipSuccess;
     return rb ? launch_conv_bytes_f32_fwd1<OC, true>(x, w, bias, y, n, H, S, scale, s) : launch_conv_bytes_f32_fwd1<OC, false>(x, w, bias, y, n, H, S, scale, s);
+}
+
+template <int OC>
+inline int band_f32_dgrad_pitch(const BandGeom &b) {      // floats per filter: the four filters of a group on different banks
+    const int n = b.F * (b.R + 1) * (b.cols + 1);
+    return (n + 47) / 64 * 64 + 16;
+}
+template <int OC>
+inline bool band_f32_dgrad_geom(BandGeom &b, int nframes) {
+    const int GW = (b.W + 1) / 2;
+    return band_split(b, nframes, (b.H + 1) / 2, GW,
+                      [&](int F, int R) { return (F * (R + 1) * (GW + 1) + 63) * OC * 4 <= BAND_F32_LDS ? 0 : 2 * BAND_LDS; },
+                      [&](int F, int R) { return F * (R + 1) * b.OW <= 256 * band_f32_dgrad_maxk<OC>() ? 0 : 1 << 30; }, BAND_MAXU,
+                      2 * BAND_CUS);
+}
+template <int OC, bool RB>
+inline hipError_t launch_conv_band_f32_dgrad1(const float *dy, const float *w, const float *xin, float *dx, int n, int H, int W, hipStream_t s) {
+    BandGeom b = band_geom(H, W);
+    if (!band_f32_dgrad_geom<OC>(b, n)) return hipErrorInvalidValue;
+    static bool attr = false;
+    const hipError_t e = band_allow_lds(conv_band_f32_dgrad_kernel<OC, RB>, attr);
+    if (e != hipSuccess) return e;
+    const int pitch = band_f32_dgrad_pitch<OC>(b);
+    ga3c::launch((conv_band_f32_dgrad_kernel<OC, RB>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), OC * pitch * 4, s, dy, w, xin, dx, n,
+                 pitch, b);
+    return hipGetLastError();
+}
+// dy [n][OC][OH][OW] -> dx [n][32][H][W], masked by xin > 0; w [OC][32][4][4], 16-byte aligned.
+template <int OC>
+inline hipError_t launch_conv_band_f32_dgrad(const float *dy, const float *w, const float *xin, float *dx, int n, int H, int W, hipStream_t s, int rb) {
+    if (n <= 0) return hipSuccess;
+    return rb ? launch_conv_band_f32_dgrad1<OC, true>(dy, w, xin, dx, n, H, W, s) : launch_conv_band_f32_dgrad1<OC, false>(dy, w, xin, dx, n, H, W, s);
+}
+
+// Whether the forward pass and the input gradient can run maps of H x W.
+template <int C>
+inline bool band_f32_ok(int H, int W) {
+    BandGeom b = band_geom(H, W), c = b, d = b;
+    return band_f32_geom<C>(b, 1) && band_f32_dgrad_geom<32>(c, 1) && band_f32_dgrad_geom<64>(d, 1);
+}
+
+// b.rows: rows of input that a step of F32_WG_KT pixels can touch; it covers up to R output rows and d frame boundaries.
+template <class TIn>
+inline F32WgradGeom f32_wgrad_geom(int C, int H, int W, int S, int n, int kchunk, float scale) {
+    constexpr int KS = sizeof(TIn) == 1 ? 8 : 4;
+    F32WgradGeom b{};
+    b.C = C; b.H = H; b.W = W; b.S = S; b.OH = (H - KS) / S + 1; b.OW = (W - KS) / S + 1;
+    b.K = n * b.OH * b.OW; b.kchunk = kchunk; b.scale = scale;
+    b.RF = S * (b.OH - 1) + KS;
+    const int R = (F32_WG_KT - 2) / b.OW + 2, d = (R - 2) / b.OH + 1;
+    b.rows = S * (R - 1) + KS + d * std::max(0, KS - S);
+    b.dNPIX = FastDiv((uint32_t)(b.OH * b.OW)); b.dOW = FastDiv((uint32_t)b.OW); b.dRF = FastDiv((uint32_t)b.RF);
+    return b;
+}
+template <class TIn>
+inline int f32_wgrad_stage(const F32WgradGeom &b, int OC) {      // the input's part rounded up to whole wavefronts
+    const int x = (sizeof(TIn) == 1 ? 4 : f32_wgrad_waves<TIn>()) * b.rows * b.W * (int)sizeof(TIn);
+    return (OC * (F32_WG_KT + 4) + F32_WG_KT) * 4 + (x + 255) / 256 * 256;
+}
+// Whether a step fits the threads and half of a compute unit's LDS.
+template <class TIn>
+inline bool f32_wgrad_ok(int C, int H, int W, int S, int OC) {
+    const F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, 1, F32_WG_KT, 1.f);
+    const int nch = sizeof(TIn) == 1 ? 4 : f32_wgrad_waves<TIn>();
+    return nch * b.rows * (W * (int)sizeof(TIn) / 4) <= 64 * f32_wgrad_waves<TIn>() * f32_wgrad_maxx<TIn>() &&
+           2 * f32_wgrad_stage<TIn>(b, OC) <= BAND_F32_LDS;
+}
+// part [nz][OC][K + 1], nz chunks of kchunk pixels (a multiple of 16).
+template <class TIn, int OC>
+inline hipError_t launch_conv_f32_wgrad(const TIn *x, const float *dy, float *part, int n, int C, int H, int W, int S, int nz, int kchunk, float scale,
+                                        hipStream_t s, int rb) {
+    if (n <= 0) return hipSuccess;
+    F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, n, kchunk, scale);
+    b.stage = f32_wgrad_stage<TIn>(b, OC);
+    constexpr int NW = f32_wgrad_waves<TIn>();
+    const dim3 grid(nz, ((sizeof(TIn) == 1 ? 16 : C) + 1 + NW - 1) / NW), block(64 * NW);
+    const int lds = 2 * b.stage;
+    static bool attr0 = false, attr1 = false;
+    if (rb) {
+        const hipError_t e = band_allow_lds(conv_f32_wgrad_kernel<TIn, OC, true>, attr1);
+        if (e != hipSuccess) return e;
+        ga3c::launch((conv_f32_wgrad_kernel<TIn, OC, true>), grid, block, lds, s, x, dy, part, b);
+    } else {
+        const hipError_t e = band_allow_lds(conv_f32_wgrad_kernel<TIn, OC, false>, attr0);
+        if (e != hipSuccess) return e;
+        ga3c::launch((conv_f32_wgrad_kernel<TIn, OC, false>), grid, block, lds, s, x, dy, part, b);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace ga3c

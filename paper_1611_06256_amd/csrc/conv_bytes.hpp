@@ -154,178 +154,6 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_fwd_kernel(const uint8_t *_
     }
 }
 
-// dW[oc][c][u][v] = scale * sum over frames and output pixels of dY[oc][i][j] x[c][S i + u][S j + v]; db[oc] = sum of
-// dY[oc].  The pixels of an item are divided among the wavefronts in groups of 32; a wavefront keeps the whole
-// [OC] x [256] result (OC / 16 x 16 tiles), and the wavefronts' sums are added through LDS at the end, in a fixed
-// order.  part: [gridDim.x][OC][257].
-constexpr int BYTES_WG_WAVES = 8, BYTES_WG_PX = 512;
-template <int OC>
-__global__ __launch_bounds__(64 * BYTES_WG_WAVES, 2) void conv_bytes_wgrad_kernel(const uint8_t *__restrict__ x, const float *__restrict__ dy,
-                                                                               float *__restrict__ part, int nframes, float scale,
-                                                                               const BytesGeom b) {
-    constexpr int OT = OC / 16, NTERM = 3, NTHR = 64 * BYTES_WG_WAVES, DPIT = band_pitch<OC>();
-    constexpr int MAXX = 4, MAXD = BYTES_WG_PX * (OC / 8) / NTHR, K1 = 257;
-    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, g = lane >> 4;
-    const int RI = (b.R - 1) * b.S + 8, NX = RI * BYTES_Q, PLANE = b.H * BYTES_W, NPIX = b.OH * b.OW;
-    const int full = b.R * b.OW, nkb = (full + 31) / 32, ND = full * (OC / 8);
-    unsigned char *xsm = band_smem, *dsm = band_smem + (size_t)RI * BYTES_ROW;
-
-    for (int e = tid; e < nkb * 32 * DPIT / 16; e += NTHR) ((u32x4 *)dsm)[e] = u32x4{0u, 0u, 0u, 0u};      // behind the last pixel
-
-    uint32_t xpre[MAXX][4];
-    float dpre[MAXD][8];
-    uint32_t dsrc[MAXD];
-    int drem[MAXD], ddst[MAXD];
-#pragma unroll
-    for (int i = 0; i < MAXD; ++i) {
-        const int u = min(tid + NTHR * i, ND - 1);
-        const int og = u / full, p = u % full;
-        dsrc[i] = (uint32_t)(og * 8 * NPIX + p);
-        drem[i] = p;
-        ddst[i] = tid + NTHR * i < ND ? p * DPIT + 16 * og : -1;
-    }
-    const size_t dtotal = (size_t)nframes * OC * NPIX;
-    auto fetch = [&](int item) {
-        const int f = item / b.nb, i0 = (item % b.nb) * b.R, r0 = i0 * b.S;
-        const uint8_t *src = x + (size_t)f * 4 * PLANE + (size_t)r0 * BYTES_W;
-        const int last = (b.H - r0) * BYTES_Q - 1;
-#pragma unroll
-        for (int i = 0; i < MAXX; ++i)
-            if (NTHR * i < NX) {
-                const uint32_t off = 4u * (uint32_t)min(min(tid + NTHR * i, NX - 1), last);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) xpre[i][c] = *(const uint32_t *)(src + (size_t)c * PLANE + off);
-            }
-        const size_t db = (size_t)f * OC * NPIX + (size_t)i0 * b.OW;
-        const uint32_t dl = band_limit(dtotal, db, NPIX);
-#pragma unroll
-        for (int i = 0; i < MAXD; ++i)
-            if (NTHR * i < ND) band_load8(dy + db, 4u * min(dsrc[i], dl), NPIX, dpre[i]);
-    };
-    int item = blockIdx.x;
-    fetch(min(item, b.items - 1));
-
-    floatx4 acc[16][OT], bacc[OT];
-#pragma unroll
-    for (int m = 0; m < OT; ++m) {
-        bacc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[q][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
-    Bf16x8Bits ones;
-    ones.u = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
-
-    for (; item < b.items; item += gridDim.x) {
-        const int i0 = (item % b.nb) * b.R, cnt = min(b.R, b.OH - i0) * b.OW;
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MAXX; ++i)
-            if (tid + NTHR * i < NX) bytes_store4(xsm + (size_t)(tid + NTHR * i) * 32, xpre[i]);
-#pragma unroll
-        for (int i = 0; i < MAXD; ++i)
-            if (ddst[i] >= 0) {
-                if (drem[i] >= cnt) {
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) dpre[i][c] = 0.f;
-                }
-                band_store8<OC>(dsm + ddst[i], dpre[i]);
-            }
-        __syncthreads();
-        fetch(min(item + (int)gridDim.x, b.items - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        for (int kb = wave; kb < nkb; kb += BYTES_WG_WAVES) {
-            const unsigned char *xp[2], *dp[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t p = (uint32_t)(32 * kb + 16 * h + 4 * g + (l16 >> 2)), i, j;
-                dp[h] = dsm + p * DPIT + 8 * (l16 & 3);
-                if ((int)p >= full) p = 0;
-                b.dC.divmod(p, i, j);
-                xp[h] = xsm + ((int)i * b.S * BYTES_W + (int)j * b.S + (l16 & 3)) * 8;
-            }
-            Bf16x8Bits d[OT][NTERM];
-#pragma unroll
-            for (int m = 0; m < OT; ++m)
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t) d[m][t].u = band_tr8(dp[0] + m * 32 + t * 2 * OC, dp[1] + m * 32 + t * 2 * OC);
-#pragma unroll
-            for (int t = NTERM - 1; t >= 0; --t)
-#pragma unroll
-                for (int m = 0; m < OT; ++m) bacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[m][t].v, ones.v, bacc[m], 0, 0, 0);
-            // column tile q: filter row q / 2, columns 4 (q % 2) .. + 3, four planes; two tiles at a time
-            Bf16x8Bits xv[2][2];
-            auto read = [&](int q, Bf16x8Bits &o) {
-                const int off = (q / 2) * BYTES_ROW + (q % 2) * 32;
-                o.u = band_tr8(xp[0] + off, xp[1] + off);
-            };
-            read(0, xv[0][0]); read(1, xv[0][1]);
-#pragma unroll
-            for (int q = 0; q < 16; q += 2) {
-                if (q + 2 < 16) { read(q + 2, xv[(q / 2 + 1) & 1][0]); read(q + 3, xv[(q / 2 + 1) & 1][1]); }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = NTERM - 1; t >= 0; --t)
-#pragma unroll
-                    for (int w = 0; w < 2; ++w)
-#pragma unroll
-                        for (int m = 0; m < OT; ++m)
-                            acc[q + w][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[m][t].v, xv[(q / 2) & 1][w].v, acc[q + w][m], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    }
-    // add up the wavefronts' sums: the upper half hands its sums to the lower half until one is left
-    float *xch = (float *)band_smem;
-    constexpr int PER = (16 + 1) * OT * 4 * 64;           // floats of one wavefront
-#pragma unroll
-    for (int half = BYTES_WG_WAVES / 2; half >= 1; half /= 2) {
-        __syncthreads();
-        if (wave >= half && wave < 2 * half) {
-            float *o = xch + (size_t)(wave - half) * PER + lane;
-#pragma unroll
-            for (int m = 0; m < OT; ++m)
-#pragma unroll
-                for (int q = 0; q < 17; ++q)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) o[((m * 17 + q) * 4 + r) * 64] = q < 16 ? acc[q < 16 ? q : 0][m][r] : bacc[m][r];
-        }
-        __syncthreads();
-        if (wave < half) {
-            const float *o = xch + (size_t)wave * PER + lane;
-#pragma unroll
-            for (int m = 0; m < OT; ++m)
-#pragma unroll
-                for (int q = 0; q < 17; ++q)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float v = o[((m * 17 + q) * 4 + r) * 64];
-                        if (q < 16) acc[q < 16 ? q : 0][m][r] += v; else bacc[m][r] += v;
-                    }
-        }
-    }
-    // lane (l16, g), register r of acc[q][m]: filter 16 m + 4 g + r, plane l16 % 4, tap (q / 2, 4 (q % 2) + l16 / 4)
-    __syncthreads();
-    float *ot = (float *)band_smem;
-    constexpr int OTP = 260;
-    if (wave == 0) {
-#pragma unroll
-        for (int m = 0; m < OT; ++m)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float *row = ot + (m * 16 + 4 * g + r) * OTP;
-#pragma unroll
-                for (int q = 0; q < 16; ++q) row[(l16 & 3) * 64 + (q / 2) * 8 + 4 * (q % 2) + (l16 >> 2)] = acc[q][m][r] * scale;
-                if (l16 == 0) row[256] = bacc[m][r];
-            }
-    }
-    __syncthreads();
-    float *pb = part + (size_t)blockIdx.x * OC * K1;
-    for (int e = tid; e < OC * K1; e += NTHR) pb[e] = ot[(e / K1) * OTP + e % K1];
-}
-
 inline BytesGeom bytes_geom(int H, int S) {
     BytesGeom b{};
     b.H = H; b.S = S; b.OH = (H - 8) / S + 1; b.OW = (BYTES_W - 8) / S + 1;
@@ -347,21 +175,6 @@ inline BytesGeom bytes_fwd_geom(int H, int S, int n) {
     bytes_split(b, n, r, 2 * BAND_CUS);
     return b;
 }
-template <int OC>
-inline int bytes_wgrad_lds(const BytesGeom &b, int R) {
-    return ((R - 1) * b.S + 8) * BYTES_ROW + (R * b.OW + 31) / 32 * 32 * band_pitch<OC>();
-}
-template <int OC>
-constexpr int bytes_wgrad_out_lds() { return (BYTES_WG_WAVES / 2) * 17 * (OC / 16) * 4 * 64 * 4; }
-template <int OC>
-inline BytesGeom bytes_wgrad_geom(int H, int S, int n) {
-    BytesGeom b = bytes_geom(H, S);
-    int r = 1;
-    while (r < b.OH && (r + 1) * b.OW <= BYTES_WG_PX && bytes_wgrad_lds<OC>(b, r + 1) <= BAND_LDS - 2048 &&
-           (r * S + 8) * BYTES_Q <= 4 * 64 * BYTES_WG_WAVES) ++r;
-    bytes_split(b, n, r, BAND_CUS);
-    return b;
-}
 // Frames of H rows of 84 pixels, any stride.  A row of the map must fit the weight gradient's item.
 inline bool bytes_ok(int H, int W, int S) {
     return W == BYTES_W && H >= 8 && S >= 1 && (BYTES_W - 8) / S + 1 <= 128;
@@ -376,22 +189,6 @@ inline hipError_t launch_conv_bytes_fwd(const uint8_t *x, const u32x4 *wfrag, co
     if (e != hipSuccess) return e;
     const int RI = (b.R - 1) * S + 8, units = (RI * BYTES_Q + 255) / 256 * 256;
     ga3c::launch((conv_bytes_fwd_kernel<OC>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), units * 32, s, x, wfrag, bias, y, n, scale, b);
-    return hipGetLastError();
-}
-
-template <int OC>
-inline int conv_bytes_wgrad_blocks(int n, int H, int S) {
-    return std::min(bytes_wgrad_geom<OC>(H, S, n).items, BAND_CUS);
-}
-template <int OC>
-inline hipError_t launch_conv_bytes_wgrad(const uint8_t *x, const float *dy, float *part, int n, int H, int S, float scale, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const BytesGeom b = bytes_wgrad_geom<OC>(H, S, n);
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_bytes_wgrad_kernel<OC>, attr);
-    if (e != hipSuccess) return e;
-    const int lds = std::max(bytes_wgrad_lds<OC>(b, b.R), bytes_wgrad_out_lds<OC>());
-    ga3c::launch((conv_bytes_wgrad_kernel<OC>), dim3(std::min(b.items, BAND_CUS)), dim3(64 * BYTES_WG_WAVES), lds, s, x, dy, part, n, scale, b);
     return hipGetLastError();
 }
 

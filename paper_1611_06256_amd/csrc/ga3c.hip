@@ -149,7 +149,7 @@ struct ga3c_ctx {
     // layers on the any-size kernels of conv_band.hpp and conv_bytes.hpp: which ones, where their fragments sit in the
     // buffer of each parameter copy (in vectors), and the buffers (nullptr where no layer needs one)
     bool band[GA3C_MAX_CONV];
-    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_dgrad[GA3C_MAX_CONV], bfrag_vecs;
+    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_vecs;
     u32x4 *bfrag[2];
     int *ticket;                  // predict_small_kernel's per-frame counters, zero between launches
     Work pred, train;
@@ -1512,7 +1512,6 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s) {
             if (!c->band[l]) continue;
             const ConvGeom &g = c->geom[l];
             add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
-            if (l > 0) add(l, FRAG_DGRAD_S2, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
         }
         ga3c::launch(band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
         HIP_TRY(hipGetLastError());
@@ -1526,7 +1525,7 @@ bool on_band_kernels(const ConvGeom &g, int l) {
     if (g.OC != 32 && !(l == 0 && g.OC == 16) && !(l > 0 && g.OC == 64)) return false;
     if (l == 0) return g.C == 4 && g.KS == 8 && bytes_ok(g.H, g.W, g.S) && !spec_matches<SpecS1>(g, true) && !spec_matches<SpecL1>(g, true);
     if (g.C != 32 || g.KS != 4 || g.S != 2 || spec_matches<SpecL2>(g, false)) return false;
-    return g.OC == 32 ? band_ok<32, 32>(g.H, g.W) : band_ok<32, 64>(g.H, g.W);
+    return band_ok<32>(g.H, g.W) && band_f32_ok<32>(g.H, g.W);
 }
 
 // Forward pass of `B` frames into `w`; heads outputs to the optional pointers.
@@ -1699,7 +1698,6 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
             const ConvGeom &g = c->geom[l];
             pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kc);
             nz = std::max(nz, std::min(B, 512));                                 // generic or frame-resident kernel
-            if (c->band[l]) nz = std::max(nz, BAND_CUS);                         // a frame may be several items
             add((size_t)nz * g.OC * (g.K + 1));
         }
         int nz2;
@@ -1846,7 +1844,6 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         if (!c->band[l]) continue;
         if (c->rb) continue;                         // runs on the parameters themselves
         c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8;
-        if (l > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8; }
     }
     if (c->bfrag_vecs)
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
@@ -2160,7 +2157,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
                                      : spec_matches<SpecL2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 7 : 4)
                                      : spec_matches<SpecL3>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 8 : 5)
                                      : (spec_matches<SpecP2>(g, l == 0) && is_aligned16(c->dact[l])) ? 9
-                                     : c->band[l] && !c->rb ? 10 : 0;
+                                     : c->band[l] && (l == 0 ? f32_wgrad_ok<uint8_t>(g.C, g.H, g.W, g.S, g.OC) : f32_wgrad_ok<float>(g.C, g.H, g.W, g.S, g.OC)) ? 10 : 0;
             if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 3) nz = conv_wgrad_frame_blocks<SpecS2>(B);
@@ -2170,9 +2167,6 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
             else if (kind == 7) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
             else if (kind == 8) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
             else if (kind == 9) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
-            else if (kind == 10)
-                nz = l == 0 ? (g.OC == 16 ? conv_bytes_wgrad_blocks<16>(B, g.H, g.S) : conv_bytes_wgrad_blocks<32>(B, g.H, g.S))
-                            : g.OC == 32 ? conv_band_wgrad_blocks<32, 32>(B, g.H, g.W) : conv_band_wgrad_blocks<32, 64>(B, g.H, g.W);
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
@@ -2196,11 +2190,11 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
             } else if (kind == 9) {
                 HIP_TRY(launch_conv_wgrad_bf16x6<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 10 && l == 0) {
-                if (g.OC == 16) HIP_TRY(launch_conv_bytes_wgrad<16>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s));
-                else HIP_TRY(launch_conv_bytes_wgrad<32>(frames, c->dact[l], part, B, g.H, g.S, 1.f / 255.f, s));
+                if (g.OC == 16) HIP_TRY((launch_conv_f32_wgrad<uint8_t, 16>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
+                else HIP_TRY((launch_conv_f32_wgrad<uint8_t, 32>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
             } else if (kind == 10) {
-                if (g.OC == 32) HIP_TRY((launch_conv_band_wgrad<32, 32>((const float *)xin, c->dact[l], part, B, g.H, g.W, s)));
-                else HIP_TRY((launch_conv_band_wgrad<32, 64>((const float *)xin, c->dact[l], part, B, g.H, g.W, s)));
+                if (g.OC == 32) HIP_TRY((launch_conv_f32_wgrad<float, 32>((const float *)xin, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f, s, c->rb)));
+                else HIP_TRY((launch_conv_f32_wgrad<float, 64>((const float *)xin, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f, s, c->rb)));
             } else if (l == 0) {
                 ConvWgradP<uint8_t> p; p.rb = c->rb;
                 p.M = g.OC; p.N = g.K + 1; p.K = B * g.OHW; p.kchunk = kchunk; p.g = g;
@@ -2233,11 +2227,10 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
             HIP_TRY(launch_conv_dgrad_bf16x6<SpecP2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb));
             continue;
         }
-        if (c->fast && c->band[l] && !c->rb) {      // the reduced-precision variant keeps the any-shape kernels' sums
-
-            const u32x4 *wf = c->bfrag[cur] + c->bfrag_dgrad[l];
-            if (g.OC == 32) HIP_TRY((launch_conv_band_dgrad<32, 32>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s)));
-            else HIP_TRY((launch_conv_band_dgrad<32, 64>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s)));
+        if (c->fast && c->band[l] && is_aligned16(th + c->off[2 * l])) {
+            const float *wl = th + c->off[2 * l];
+            if (g.OC == 32) HIP_TRY(launch_conv_band_f32_dgrad<32>(c->dact[l], wl, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
+            else HIP_TRY(launch_conv_band_f32_dgrad<64>(c->dact[l], wl, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
             continue;
         }
         if (c->fast && spec_matches<SpecL3>(g, false)) {
