@@ -467,90 +467,114 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_dgrad_kernel(const float
 // planes, any stride; floats: 4x4, stride 2, 32 channels.
 //
 // A chunk is one long chain of sums, so the parallelism left is chunks x columns: a wavefront keeps one tile of 16 taps (a
-// channel of the 4x4 filters, two rows of an 8x8 plane) of all filters; the tile of column K multiplies by one.  The chunk
-// goes by in steps of F32_WG_KT pixels, whose dY lies in LDS as [filter][pixel] and whose input rows as they are in memory:
+// channel of the 4x4 filters, two rows of an 8x8 plane) of all filters.  The instruction adds its four products one after
+// the other, so the column of the bias gradient, whose products are dY itself, is formed with plain additions in that order,
+// by one wavefront of a chunk on the side (a wavefront of its own would end last: one chain of dependent instructions).
+// The chunk goes by in steps of KT pixels, whose dY lies in LDS as [filter][pixel] and whose input rows as they are in memory:
 // the rows that a frame's windows touch, numbered on from frame to frame (S (OH - 1) + KS to a frame), are contiguous for any
-// run of pixels, also across frames, and a table gives each pixel's place in them.
-// Bound by the instruction and by whole wavefronts per SIMD: 62 GFLOP of conv1 at 640 frames of 84x84 with stride 1 are 2907
-// tiles of 161 us on 1024 SIMDs.
-// The next step's values go from memory straight to the other half of the LDS buffers (no registers hold them).
-constexpr int F32_WG_KT = 64;
+// run of pixels, also across frames, and a table gives each pixel's place in them.  The next step's values go from memory
+// straight to the other half of the LDS buffers (no registers hold them).
+// Bound by the instruction next to the address and byte-conversion instructions (8 per 8 products of 32 cycles), and by whole
+// wavefronts per SIMD: conv1 at 640 frames of 84x84, stride 1, is 2736 tiles of 161 us on 1024 SIMDs (483 us; 785 measured,
+// 4 ms for the gather kernel).
+template <class TIn> constexpr int f32_wgrad_kt() { return sizeof(TIn) == 1 ? 128 : 64; }
 struct F32WgradGeom {
-    int C, H, W, S, OH, OW;
-    int K, kchunk;           // pixels in all, pixels per chunk
+    int nframes, C, H, W, S, OH, OW;
+    int K, kchunk, nz;       // pixels in all, pixels per chunk, chunks
+    int ny;                  // blocks per chunk
     int rows;                // input rows of a step in LDS, at most
-    int RF;                  // rows per frame in the numbering above
+    int RF, d;               // rows per frame in the numbering above; frame boundaries in a step, at most
     int stage;               // bytes of one half of the LDS buffers
     FastDiv dNPIX, dOW, dRF;
     float scale;
 };
-template <class TIn> constexpr int f32_wgrad_waves() { return sizeof(TIn) == 1 ? 6 : 8; }
-template <class TIn> constexpr int f32_wgrad_maxx() { return sizeof(TIn) == 1 ? 8 : 13; }      // dwords of input per thread and step
+template <class TIn> constexpr int f32_wgrad_waves() { return sizeof(TIn) == 1 ? 4 : 8; }
+template <class TIn> constexpr int f32_wgrad_maxx() { return 13; }      // dwords of input per thread and step
 
-// One dword per lane from `src` to lds + 4 * lane; lds is the same for the whole wavefront.
-__device__ __forceinline__ void load_dword_to_lds(const void *src, void *lds) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t *)src, (__attribute__((address_space(3))) uint32_t *)lds, 4, 0, 0);
+// One dword per lane from base + off (bytes) to lds + 4 * lane; base and lds are the same for the whole wavefront.  The caller
+// waits for vmcnt itself: the compiler, which would wait for every such load in front of the next LDS read, does not see it.
+__device__ __forceinline__ void load_dword_to_lds(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
 }
 
 template <class TIn, int OC, bool RB>
 __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 : 4) void conv_f32_wgrad_kernel(
     const TIn *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, const F32WgradGeom b) {
     constexpr bool BYTE = sizeof(TIn) == 1;
-    constexpr int OT = OC / 16, KT = F32_WG_KT, AP = KT + 4, NW = f32_wgrad_waves<TIn>(), NT = 64 * NW, MAXX = f32_wgrad_maxx<TIn>();
+    constexpr int OT = OC / 16, KS = BYTE ? 8 : 4, KT = f32_wgrad_kt<TIn>(), AP = KT + 4, NW = f32_wgrad_waves<TIn>(), NT = 64 * NW, MAXX = f32_wgrad_maxx<TIn>();
     constexpr int NG = KT / 16, ESZ = (int)sizeof(TIn);
-    static_assert(KT == 64, "a lane stages one pixel");
-    // each half: dY [OC][AP] floats, [KT] byte offsets of the pixels' windows, the input [channel][rows][W]
+    // each half: dY [OC][AP] floats, [KT] byte offsets of the pixels' windows, the input [row][channel][W]
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
     constexpr int OTAB = OC * AP * 4, XS = OTAB + KT * 4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int NPIX = b.OH * b.OW, HW = b.H * b.W, ncol = BYTE ? 16 : b.C;
-    const int q = (int)blockIdx.y * NW + wave;
+    // an XCD takes every eighth chunk, the blocks of a chunk next to each other: its dY then comes from the L2
+    const int local = (int)blockIdx.x / 8, by = local % b.ny, z = local / b.ny * 8 + (int)blockIdx.x % 8;
+    if (z >= b.nz) return;
+    const int q = by * NW + wave;
     // the channels this block's tiles need, in dwords
-    const int c0 = BYTE ? 0 : (int)blockIdx.y * NW, nch = BYTE ? 4 : max(0, min(NW, b.C - c0));
-    const int UW = b.W * ESZ / 4, NU = nch * b.rows * UW, bytes_per_ch = b.rows * b.W * ESZ;
-    const int kbeg = (int)blockIdx.x * b.kchunk, kend = min(b.K, kbeg + b.kchunk);
-    const int last_row = (int)b.dNPIX.div((uint32_t)(b.K - 1)) * b.RF + b.RF - 1;
+    const int c0 = BYTE ? 0 : by * NW, nch = BYTE ? 4 : NW;
+    const int UW = b.W * ESZ / 4, UR = nch * UW, NU = b.rows * UR, ROW = nch * b.W * ESZ;      // dwords of a row of a channel and of all; bytes
+    const int kbeg = z * b.kchunk, kend = min(b.K, kbeg + b.kchunk);
 
     uint32_t xoff[MAXX];
     int xrow[MAXX];
 #pragma unroll
     for (int i = 0; i < MAXX; ++i) {
-        const int u = max(0, min(tid + NT * i, NU - 1)), c = u / (b.rows * UW), rem = u % (b.rows * UW);
-        xrow[i] = rem / UW;
-        xoff[i] = (uint32_t)((c0 + c) * HW * ESZ + 4 * (rem % UW));
+        const int u = min(tid + NT * i, NU - 1), rem = u % UR;
+        xrow[i] = u / UR;
+        xoff[i] = (uint32_t)((c0 * HW + rem / UW * HW + xrow[i] * b.W) * ESZ + 4 * (rem % UW));
     }
+    const uint32_t jump = (uint32_t)((b.C * b.H - b.RF) * b.W * ESZ);         // over the rows between two frames' channels
+    const size_t xbytes = (size_t)b.nframes * b.C * HW * ESZ;
     auto fetch = [&](int k0, unsigned char *half) {
-        uint32_t f0, p0, i0, j0;
+        const uint32_t lds = lds_address(half);
+        uint32_t f0, p0, f1, p1;
         b.dNPIX.divmod((uint32_t)k0, f0, p0);
-        b.dOW.divmod(p0, i0, j0);
-        const int row0 = (int)f0 * b.RF + (int)i0 * b.S;
+        b.dNPIX.divmod((uint32_t)min(k0 + KT, kend) - 1, f1, p1);
+        const int r0 = (int)b.dOW.div(p0) * b.S;
+        const int rows = (int)(f1 - f0) * b.RF + (int)b.dOW.div(p1) * b.S + KS - r0;      // that this step's windows touch
+        const int nu = rows * UR;
+        const size_t xb = (size_t)f0 * b.C * HW * ESZ + (size_t)r0 * b.W * ESZ;
+        const uint32_t lim = xbytes - xb > 0x7fffffff ? 0x7fffffffu : (uint32_t)(xbytes - xb) - 4u;
 #pragma unroll
         for (int i = 0; i < MAXX; ++i)
-            if (64 * wave + NT * i < NU) {
-                uint32_t f, r;
-                b.dRF.divmod((uint32_t)min(row0 + xrow[i], last_row), f, r);
-                load_dword_to_lds((const char *)x + (size_t)f * b.C * HW * ESZ + xoff[i] + r * (uint32_t)(b.W * ESZ),
-                                  half + XS + (64 * wave + NT * i) * 4);
+            if (64 * wave + NT * i < nu) {
+                uint32_t off = xoff[i] + (xrow[i] >= b.RF - r0 ? jump : 0u);
+                if (b.d > 1)
+                    for (int q = 2; q <= b.d; ++q) off += xrow[i] >= q * b.RF - r0 ? jump : 0u;
+                load_dword_to_lds((const char *)x + xb, min(off, lim), lds + XS + (64 * wave + NT * i) * 4);
             }
-        uint32_t f, p, i, j;
-        b.dNPIX.divmod((uint32_t)min(k0 + lane, b.K - 1), f, p);
-        const float *src = dy + (size_t)f * OC * NPIX + p;
+        const float *src = dy + (size_t)f0 * OC * NPIX;
 #pragma unroll
-        for (int m = 0; m < OC; m += NW)
-            if (OC % NW == 0 || m + wave < OC) load_dword_to_lds(src + (size_t)(m + wave) * NPIX, half + (m + wave) * AP * 4);
-        b.dOW.divmod(p, i, j);
-        if (wave == 0) ((int *)(half + OTAB))[lane] = k0 + lane < kend ? (((int)f * b.RF + (int)i * b.S - row0) * b.W + (int)j * b.S) * ESZ : 0;
+        for (int h = 0; h < KT; h += 64) {
+            const int k = k0 + h + lane;
+            uint32_t f, p, i, j;
+            b.dNPIX.divmod((uint32_t)min(k, b.K - 1), f, p);
+            const uint32_t off = 4u * ((f - f0) * (uint32_t)(OC * NPIX) + p);
+#pragma unroll
+            for (int m = 0; m < OC; m += NW)
+                if (OC % NW == 0 || m + wave < OC) load_dword_to_lds(src + (size_t)(m + wave) * NPIX, off, lds + ((m + wave) * AP + h) * 4);
+            if (wave == 0) {
+                b.dOW.divmod(p, i, j);
+                ((int *)(half + OTAB))[h + lane] = k < kend ? ((int)(f - f0) * b.RF + (int)i * b.S - r0) * ROW + (int)j * b.S * ESZ : 0;
+            }
+        }
     };
     fetch(kbeg, band_smem);
 
     floatx4 acc[OT];
+    float bsum = 0.f;
 #pragma unroll
     for (int m = 0; m < OT; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
     // my tap's place behind a window's first value
-    const int xl = BYTE ? (q / 4) * bytes_per_ch + (2 * (q % 4) + (l16 >> 3)) * b.W + (l16 & 7)
-                        : (q - c0) * bytes_per_ch + ((l16 >> 2) * b.W + (l16 & 3)) * 4;
+    const int xl = BYTE ? (2 * (q % 4) + (l16 >> 3)) * ROW + (q / 4) * b.W + (l16 & 7)
+                        : (l16 >> 2) * ROW + ((q - c0) * b.W + (l16 & 3)) * 4;
     int at = 0;
     for (int k0 = kbeg; k0 < kend; k0 += KT, at ^= 1) {
         unsigned char *half = band_smem + at * b.stage;
@@ -559,7 +583,8 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
         if (k0 + KT < kend) fetch(k0 + KT, band_smem + (at ^ 1) * b.stage);
         else if (k0 + KT > kend) {                            // no pixels behind the chunk's last
             for (int oc = wave; oc < OC; oc += NW)
-                if (k0 + lane >= kend) ((float *)half)[oc * AP + lane] = 0.f;
+                for (int kk = lane; kk < KT; kk += 64)
+                    if (k0 + kk >= kend) ((float *)half)[oc * AP + kk] = 0.f;
             __syncthreads();
         }
         const float *al = (const float *)half + l16 * AP + 4 * g;
@@ -570,62 +595,65 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
                 if (RB) d[m] = bf16_rne(d[m]);
             }
         };
-        if (q < ncol) {
-            const int4 *ol = (const int4 *)(half + OTAB) + g;
-            const unsigned char *xb = half + XS + xl;
-            auto read_x = [&](const int4 o, float (&d)[4]) {
-                if (BYTE) { d[0] = (float)xb[o.x]; d[1] = (float)xb[o.y]; d[2] = (float)xb[o.z]; d[3] = (float)xb[o.w]; }
-                else {
-                    d[0] = *(const float *)(xb + o.x); d[1] = *(const float *)(xb + o.y); d[2] = *(const float *)(xb + o.z); d[3] = *(const float *)(xb + o.w);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        if (RB) d[t] = bf16_rne(d[t]);
-                }
-            };
-            int4 o[NG];
-#pragma unroll
-            for (int grp = 0; grp < NG; ++grp) o[grp] = ol[4 * grp];
-            float xv[2][4];
-            float4 av[2][OT];
-            read_x(o[0], xv[0]);
-            read_a(0, av[0]);
-#pragma unroll
-            for (int grp = 0; grp < NG; ++grp) {
-                if (grp + 1 < NG) {
-                    read_x(o[grp + 1], xv[(grp + 1) & 1]);
-                    read_a(grp + 1, av[(grp + 1) & 1]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int m = 0; m < OT; ++m) {
-                        const float4 a = av[grp & 1][m];
-                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(t == 0 ? a.x : t == 1 ? a.y : t == 2 ? a.z : a.w, xv[grp & 1][t], acc[m], 0, 0, 0);
-                    }
-                __builtin_amdgcn_sched_barrier(0);
+        const int4 *ol = (const int4 *)(half + OTAB) + g;
+        const unsigned char *xb = half + XS + xl;
+        uint32_t xr[2][4];
+        auto read_x = [&](const int4 o, uint32_t (&d)[4]) {
+            if (BYTE) { d[0] = xb[o.x]; d[1] = xb[o.y]; d[2] = xb[o.z]; d[3] = xb[o.w]; }
+            else {
+                d[0] = *(const uint32_t *)(xb + o.x); d[1] = *(const uint32_t *)(xb + o.y);
+                d[2] = *(const uint32_t *)(xb + o.z); d[3] = *(const uint32_t *)(xb + o.w);
             }
-        } else if (q == ncol) {
+        };
+        int4 o = ol[0];
+        float4 av[2][OT];
+        read_x(o, xr[0]);
+        read_a(0, av[0]);
+        o = ol[4];
+#pragma unroll
+        for (int grp = 0; grp < NG; ++grp) {
+            if (grp + 1 < NG) {
+                read_x(o, xr[(grp + 1) & 1]);
+                read_a(grp + 1, av[(grp + 1) & 1]);
+                if (grp + 2 < NG) o = ol[4 * (grp + 2)];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t v = xr[grp & 1][t];
+                const float xv = BYTE ? (float)v : RB ? bf16_rne(__uint_as_float(v)) : __uint_as_float(v);
+#pragma unroll
+                for (int m = 0; m < OT; ++m) {
+                    const float4 a = av[grp & 1][m];
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(t == 0 ? a.x : t == 1 ? a.y : t == 2 ? a.z : a.w, xv, acc[m], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (by == 0 && wave == (z & (NW - 1))) {      // the bias gradient, a filter per lane: the sums the instruction would form
+            const float *bl = (const float *)half + min(lane, OC - 1) * AP;
 #pragma unroll
             for (int grp = 0; grp < NG; ++grp) {
-                float4 a[OT];
-                read_a(grp, a);
+                float v[16];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float4 d = *(const float4 *)(bl + 16 * grp + 4 * e);
+                    v[4 * e] = d.x; v[4 * e + 1] = d.y; v[4 * e + 2] = d.z; v[4 * e + 3] = d.w;
+                }
 #pragma unroll
                 for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int m = 0; m < OT; ++m)
-                        acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(t == 0 ? a[m].x : t == 1 ? a[m].y : t == 2 ? a[m].z : a[m].w, 1.f, acc[m], 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) bsum += RB ? bf16_rne(v[4 * e + t]) : v[4 * e + t];
             }
         }
     }
     const int K1 = 16 * ncol + 1;
-    float *pb = part + (size_t)blockIdx.x * OC * K1;
-    if (q < ncol || (q == ncol && l16 == 0)) {
+    float *pb = part + (size_t)z * OC * K1;
 #pragma unroll
-        for (int m = 0; m < OT; ++m)
+    for (int m = 0; m < OT; ++m)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) pb[(size_t)(m * 16 + 4 * g + r) * K1 + 16 * q + l16] = q < ncol ? acc[m][r] * b.scale : acc[m][r];
-    }
+        for (int r = 0; r < 4; ++r) pb[(size_t)(m * 16 + 4 * g + r) * K1 + 16 * q + l16] = acc[m][r] * b.scale;
+    if (by == 0 && wave == (z & (NW - 1)) && lane < OC) pb[(size_t)lane * K1 + K1 - 1] = bsum;
 }
 
 template <int C>
@@ -710,28 +738,29 @@ inline bool band_f32_ok(int H, int W) {
     return band_f32_geom<C>(b, 1) && band_f32_dgrad_geom<32>(c, 1) && band_f32_dgrad_geom<64>(d, 1);
 }
 
-// b.rows: rows of input that a step of F32_WG_KT pixels can touch; it covers up to R output rows and d frame boundaries.
+// b.rows: rows of input that a step can touch; it covers up to R output rows and d frame boundaries.
 template <class TIn>
 inline F32WgradGeom f32_wgrad_geom(int C, int H, int W, int S, int n, int kchunk, float scale) {
     constexpr int KS = sizeof(TIn) == 1 ? 8 : 4;
     F32WgradGeom b{};
-    b.C = C; b.H = H; b.W = W; b.S = S; b.OH = (H - KS) / S + 1; b.OW = (W - KS) / S + 1;
+    b.nframes = n; b.C = C; b.H = H; b.W = W; b.S = S; b.OH = (H - KS) / S + 1; b.OW = (W - KS) / S + 1;
     b.K = n * b.OH * b.OW; b.kchunk = kchunk; b.scale = scale;
     b.RF = S * (b.OH - 1) + KS;
-    const int R = (F32_WG_KT - 2) / b.OW + 2, d = (R - 2) / b.OH + 1;
-    b.rows = S * (R - 1) + KS + d * std::max(0, KS - S);
+    const int R = (f32_wgrad_kt<TIn>() - 2) / b.OW + 2;
+    b.d = (R - 2) / b.OH + 1;
+    b.rows = S * (R - 1) + KS + b.d * std::max(0, KS - S);
     b.dNPIX = FastDiv((uint32_t)(b.OH * b.OW)); b.dOW = FastDiv((uint32_t)b.OW); b.dRF = FastDiv((uint32_t)b.RF);
     return b;
 }
 template <class TIn>
 inline int f32_wgrad_stage(const F32WgradGeom &b, int OC) {      // the input's part rounded up to whole wavefronts
     const int x = (sizeof(TIn) == 1 ? 4 : f32_wgrad_waves<TIn>()) * b.rows * b.W * (int)sizeof(TIn);
-    return (OC * (F32_WG_KT + 4) + F32_WG_KT) * 4 + (x + 255) / 256 * 256;
+    return (OC * (f32_wgrad_kt<TIn>() + 4) + f32_wgrad_kt<TIn>()) * 4 + (x + 255) / 256 * 256;
 }
 // Whether a step fits the threads and half of a compute unit's LDS.
 template <class TIn>
 inline bool f32_wgrad_ok(int C, int H, int W, int S, int OC) {
-    const F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, 1, F32_WG_KT, 1.f);
+    const F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, 1, f32_wgrad_kt<TIn>(), 1.f);
     const int nch = sizeof(TIn) == 1 ? 4 : f32_wgrad_waves<TIn>();
     return nch * b.rows * (W * (int)sizeof(TIn) / 4) <= 64 * f32_wgrad_waves<TIn>() * f32_wgrad_maxx<TIn>() &&
            2 * f32_wgrad_stage<TIn>(b, OC) <= BAND_F32_LDS;
@@ -744,7 +773,8 @@ inline hipError_t launch_conv_f32_wgrad(const TIn *x, const float *dy, float *pa
     F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, n, kchunk, scale);
     b.stage = f32_wgrad_stage<TIn>(b, OC);
     constexpr int NW = f32_wgrad_waves<TIn>();
-    const dim3 grid(nz, ((sizeof(TIn) == 1 ? 16 : C) + 1 + NW - 1) / NW), block(64 * NW);
+    b.nz = nz; b.ny = (sizeof(TIn) == 1 ? 16 : C) / NW;
+    const dim3 grid((nz + 7) / 8 * 8 * b.ny), block(64 * NW);
     const int lds = 2 * b.stage;
     static bool attr0 = false, attr1 = false;
     if (rb) {
