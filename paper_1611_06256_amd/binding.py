@@ -12,6 +12,8 @@ import os
 from dataclasses import dataclass
 from typing import Dict, Optional, Sequence, Tuple
 
+import numpy as np
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 MAX_CONV = 4
 
@@ -43,6 +45,10 @@ class _SchedConfig(C.Structure):
 
 class Prediction(C.Structure):
     _fields_ = [("agent", C.c_int32), ("action", C.c_int32), ("value", C.c_float), ("policy_version", C.c_int32)]
+
+
+# a Prediction as numpy sees it
+_RESULT = np.dtype([("agent", "<i4"), ("action", "<i4"), ("value", "<f4"), ("policy_version", "<i4")])
 
 
 class SchedStats(C.Structure):
@@ -158,7 +164,7 @@ def load_library() -> C.CDLL:
     lib.ga3c_sched_submit_predict_many.argtypes = [vp, i32, vp, vp, vp]
     lib.ga3c_sched_submit_trajectory_many.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp]
     lib.ga3c_sched_tick.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
-    lib.ga3c_sched_poll.argtypes = [vp, C.POINTER(Prediction), i32]
+    lib.ga3c_sched_poll.argtypes = [vp, vp, i32]
     lib.ga3c_sched_drain.argtypes = [vp]
     lib.ga3c_sched_get_stats.argtypes = [vp, C.POINTER(SchedStats)]
     lib.ga3c_sched_last_error.restype = C.c_char_p
@@ -399,6 +405,7 @@ class Scheduler:
                            train_cap_lo, train_cap_hi, train_cap_step, seed, hp.c(), adjust_margin)
         self._s = C.c_void_p()
         self.t_max = t_max
+        self._results, self._results_at = np.empty(0, dtype=_RESULT), None      # poll_arrays' buffer and its address
         _scheck(self._lib.ga3c_sched_create(net._ctx, C.byref(cfg), C.byref(self._s)), "ga3c_sched_create")
 
     def close(self):
@@ -419,7 +426,6 @@ class Scheduler:
 
     def submit_trajectory(self, agent: int, frames, actions, rewards, dones, bootstrap: float) -> None:
         """frames: GPU u8 [t_max,C,H,W]; actions i32 / rewards f32 / dones u8: numpy arrays of t_max entries."""
-        import numpy as np
         import torch
         a = np.ascontiguousarray(actions, dtype=np.int32); r = np.ascontiguousarray(rewards, dtype=np.float32)
         d = np.ascontiguousarray(dones, dtype=np.uint8)
@@ -433,7 +439,6 @@ class Scheduler:
     def submit_segment(self, agent: int, frames, actions, rewards, dones, bootstrap: float, policy_version: int = -1) -> None:
         """frames: GPU u8 [len,C,H,W] with 1 <= len <= t_max; actions / rewards / dones: numpy arrays of len entries;
         policy_version: the one that came with the prediction of the first action (-1 = not given)."""
-        import numpy as np
         import torch
         a = np.ascontiguousarray(actions, dtype=np.int32); r = np.ascontiguousarray(rewards, dtype=np.float32)
         d = np.ascontiguousarray(dones, dtype=np.uint8)
@@ -446,7 +451,6 @@ class Scheduler:
 
     def submit_predict_many(self, agents, frame_ptrs, uniforms) -> None:
         """agents i32 [n], frame_ptrs u64 [n] (device addresses), uniforms f32 [n]: numpy arrays."""
-        import numpy as np
         a = np.ascontiguousarray(agents, dtype=np.int32); p = np.ascontiguousarray(frame_ptrs, dtype=np.uint64)
         u = np.ascontiguousarray(uniforms, dtype=np.float32)
         _scheck(self._lib.ga3c_sched_submit_predict_many(self._s, a.size, a.ctypes.data_as(C.c_void_p),
@@ -454,7 +458,6 @@ class Scheduler:
                 "ga3c_sched_submit_predict_many")
 
     def submit_trajectory_many(self, agents, frame_ptrs, actions, rewards, dones, bootstrap) -> None:
-        import numpy as np
         a = np.ascontiguousarray(agents, dtype=np.int32); p = np.ascontiguousarray(frame_ptrs, dtype=np.uint64)
         ac = np.ascontiguousarray(actions, dtype=np.int32); r = np.ascontiguousarray(rewards, dtype=np.float32)
         d = np.ascontiguousarray(dones, dtype=np.uint8); bo = np.ascontiguousarray(bootstrap, dtype=np.float32)
@@ -468,7 +471,6 @@ class Scheduler:
     def submit_segment_many(self, agents, frame_ptrs, lens, actions, rewards, dones, bootstrap, policy_versions=None) -> None:
         """n segments at once: lens i32 [n]; actions / rewards / dones [n, t_max] (row i: the first lens[i] entries
         count); frame_ptrs u64 [n] (device addresses); policy_versions i64 [n] or None."""
-        import numpy as np
         a = np.ascontiguousarray(agents, dtype=np.int32); p = np.ascontiguousarray(frame_ptrs, dtype=np.uint64)
         ln = np.ascontiguousarray(lens, dtype=np.int32)
         ac = np.ascontiguousarray(actions, dtype=np.int32); r = np.ascontiguousarray(rewards, dtype=np.float32)
@@ -485,11 +487,11 @@ class Scheduler:
 
     def poll_arrays(self, cap: int = 4096, with_version: bool = False):
         """Finished predictions as numpy arrays (agents, actions, values[, policy versions])."""
-        import numpy as np
-        buf = (Prediction * cap)()
-        n = _scheck(self._lib.ga3c_sched_poll(self._s, buf, cap), "ga3c_sched_poll")
-        rec = np.frombuffer(buf, dtype=np.dtype([("agent", "<i4"), ("action", "<i4"), ("value", "<f4"),
-                                                 ("policy_version", "<i4")]), count=n)
+        if self._results.size < cap:
+            self._results = np.empty(cap, dtype=_RESULT)
+            self._results_at = self._results.ctypes.data
+        n = _scheck(self._lib.ga3c_sched_poll(self._s, self._results_at, cap), "ga3c_sched_poll")
+        rec = self._results[:n]
         out = (rec["agent"].copy(), rec["action"].copy(), rec["value"].copy())
         return out + (rec["policy_version"].copy(),) if with_version else out
 

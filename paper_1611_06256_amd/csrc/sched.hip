@@ -17,7 +17,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <deque>
 #include <new>
 #include <vector>
 
@@ -36,12 +35,54 @@ namespace {
                          hipGetErrorString(e_));                                                     \
     } while (0)
 
-// Copies whole frames by pointer: dst[i] = *src[i], frame_vecs 16-byte vectors each.
-__global__ __launch_bounds__(256) void gather_frames_kernel(const uint4 *const *__restrict__ src, uint4 *__restrict__ dst,
-                                                            int frame_vecs) {
-    const uint4 *s = src[blockIdx.y];
-    uint4 *d = dst + (size_t)blockIdx.y * frame_vecs;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < frame_vecs; i += gridDim.x * 256) d[i] = s[i];
+// A batch's frames and scalars are fetched by the kernel itself from what the host has written into pinned memory: one
+// launch where a copy command per list (each a few microseconds of its own on the stream) went before it.  Reads of host
+// memory are not cached, so a frame's block asks for its pointer once and keeps all of a thread's vectors in flight.
+// (256 requests and 256 trained segments per round of the closed loop: 24 copy commands fewer per update.)
+constexpr int GATHER_VPT = 8;        // 16-byte vectors of a frame in flight per thread
+
+__device__ __forceinline__ void copy_frame(const uint4 *__restrict__ s, uint4 *__restrict__ d, int frame_vecs) {
+    for (int i0 = threadIdx.x; i0 < frame_vecs; i0 += 256 * GATHER_VPT) {
+        uint4 v[GATHER_VPT];
+#pragma unroll
+        for (int j = 0; j < GATHER_VPT; ++j) v[j] = s[min(i0 + 256 * j, frame_vecs - 1)];
+#pragma unroll
+        for (int j = 0; j < GATHER_VPT; ++j)
+            if (i0 + 256 * j < frame_vecs) d[i0 + 256 * j] = v[j];
+    }
+}
+
+// Block i: frame i of a prediction batch and its uniform number.  *_h are host memory.
+__global__ __launch_bounds__(256) void gather_requests_kernel(const uint4 *const *__restrict__ src_h, const float *__restrict__ unif_h,
+                                                              uint4 *__restrict__ frames, float *__restrict__ unif, int frame_vecs) {
+    const int i = blockIdx.x;
+    if (threadIdx.x == 0) unif[i] = unif_h[i];
+    copy_frame(src_h[i], frames + (size_t)i * frame_vecs, frame_vecs);
+}
+
+// Block i: experience i of a training batch; the first n_segments blocks also fetch a segment's bootstrap value and start.
+struct GatherTrain {
+    const uint4 *const *src_h;
+    const int32_t *act_h, *seg_h;
+    const float *rew_h, *boot_h;
+    const uint8_t *done_h;
+    uint4 *frames;
+    int32_t *act, *seg;
+    float *rew, *boot;
+    uint8_t *done;
+    int frame_vecs, n_segments;
+};
+__global__ __launch_bounds__(256) void gather_experiences_kernel(const GatherTrain a) {
+    const int i = blockIdx.x, t = threadIdx.x;
+    if (t == 0) a.act[i] = a.act_h[i];
+    if (t == 64) a.rew[i] = a.rew_h[i];
+    if (t == 128) a.done[i] = a.done_h[i];
+    if (t == 192 && i < a.n_segments) {
+        a.boot[i] = a.boot_h[i];
+        a.seg[i] = a.seg_h[i];
+        if (i == 0) a.seg[a.n_segments] = a.seg_h[a.n_segments];
+    }
+    copy_frame(a.src_h[i], a.frames + (size_t)i * a.frame_vecs, a.frame_vecs);
 }
 
 }  // namespace
@@ -55,24 +96,39 @@ constexpr int RING = 4;    // batches in flight per stream
 struct PredReq { int agent; const uint8_t *frame; float uniform; };
 struct Traj {
     int agent;
-    int len;                 // experiences in the segment, 1 .. t_max
+    int len;                 // experiences in the segment, 1 .. t_max; their actions, rewards and dones lie in the queue's flat lists
     int64_t version;         // updates issued before the policy that chose its first action was read; -1 = not given
     const uint8_t *frames;
-    std::vector<int32_t> actions;
-    std::vector<float> rewards;
-    std::vector<uint8_t> dones;
     float bootstrap;
+};
+
+// First in, first out, in one piece of memory: takes and gives runs of elements without an allocation for each.
+template <class T>
+struct FlatQueue {
+    std::vector<T> v;
+    size_t head = 0;
+    size_t size() const { return v.size() - head; }
+    bool empty() const { return head == v.size(); }
+    const T *data() const { return v.data() + head; }
+    const T &operator[](size_t i) const { return v[head + i]; }
+    void push(const T *p, size_t n) { v.insert(v.end(), p, p + n); }
+    void push(const T &x) { v.push_back(x); }
+    void pop(size_t n) {
+        head += n;
+        if (head == v.size()) { v.clear(); head = 0; }
+        else if (head > 4096 && head > v.size() / 2) { v.erase(v.begin(), v.begin() + head); head = 0; }
+    }
 };
 
 struct PredSlot {
     hipEvent_t done = nullptr;
     bool busy = false;
     int n = 0;
-    const uint4 **ptrs_h = nullptr, **ptrs_d = nullptr;   // pinned host / device pointer lists
+    const uint4 **ptrs_h = nullptr;                       // *_h: pinned host memory, which the kernels read and write
     float *unif_h = nullptr, *unif_d = nullptr;
     uint8_t *frames_d = nullptr;
-    int32_t *act_d = nullptr, *act_h = nullptr;
-    float *val_d = nullptr, *val_h = nullptr;
+    int32_t *act_h = nullptr;
+    float *val_h = nullptr;
     std::vector<int> agents;
     int64_t version = 0;     // updates issued before this batch
 };
@@ -81,7 +137,7 @@ struct TrainSlot {
     hipEvent_t done = nullptr;
     bool busy = false;
     int n_agents = 0;
-    const uint4 **ptrs_h = nullptr, **ptrs_d = nullptr;
+    const uint4 **ptrs_h = nullptr;
     uint8_t *frames_d = nullptr;
     int32_t *act_h = nullptr, *act_d = nullptr;
     float *rew_h = nullptr, *rew_d = nullptr;
@@ -100,13 +156,16 @@ struct ga3c_sched {
     size_t frame_bytes;
     int predict_cap, train_cap;
     hipStream_t sp, st;
-    std::deque<PredReq> pq;
-    std::deque<Traj> tq;
+    FlatQueue<PredReq> pq;
+    FlatQueue<Traj> tq;
+    FlatQueue<int32_t> tq_act;       // of the experiences waiting in tq, segment after segment
+    FlatQueue<float> tq_rew;
+    FlatQueue<uint8_t> tq_done;
     int64_t tq_frames;       // experiences waiting in tq
     PredSlot ps[RING];
     TrainSlot ts[RING];
     int ps_next, ts_next;
-    std::deque<ga3c_prediction> ready;
+    FlatQueue<ga3c_prediction> ready;
     ga3c_tuner *tuner;
     ga3c_sched_stats stats;
     int64_t window_ticks, window_frames;
@@ -132,14 +191,13 @@ int alloc_slots(ga3c_sched *s) {
     for (int i = 0; i < RING; ++i) {
         PredSlot &p = s->ps[i];
         SHIP(hipEventCreateWithFlags(&p.done, hipEventDisableTiming));
-        STRY(pinned(&p.ptrs_h, s->max_pred)); STRY(device(&p.ptrs_d, s->max_pred));
+        STRY(pinned(&p.ptrs_h, s->max_pred));
         STRY(pinned(&p.unif_h, s->max_pred)); STRY(device(&p.unif_d, s->max_pred));
         STRY(device(&p.frames_d, (size_t)s->max_pred * s->frame_bytes));
-        STRY(device(&p.act_d, s->max_pred)); STRY(pinned(&p.act_h, s->max_pred));
-        STRY(device(&p.val_d, s->max_pred)); STRY(pinned(&p.val_h, s->max_pred));
+        STRY(pinned(&p.act_h, s->max_pred)); STRY(pinned(&p.val_h, s->max_pred));
         TrainSlot &t = s->ts[i];
         SHIP(hipEventCreateWithFlags(&t.done, hipEventDisableTiming));
-        STRY(pinned(&t.ptrs_h, maxN)); STRY(device(&t.ptrs_d, maxN));
+        STRY(pinned(&t.ptrs_h, maxN));
         STRY(device(&t.frames_d, (size_t)s->max_train * s->frame_bytes));
         STRY(pinned(&t.act_h, s->max_train)); STRY(device(&t.act_d, s->max_train));
         STRY(pinned(&t.rew_h, s->max_train)); STRY(device(&t.rew_d, s->max_train));
@@ -162,7 +220,7 @@ int harvest(ga3c_sched *s, bool wait) {
             if (q != hipSuccess) return sfail(GA3C_EHIP, "hipEventQuery: %s", hipGetErrorString(q));
         }
         for (int i = 0; i < p.n; ++i)
-            s->ready.push_back(ga3c_prediction{p.agents[i], p.act_h[i], p.val_h[i], (int32_t)p.version});
+            s->ready.push(ga3c_prediction{p.agents[i], p.act_h[i], p.val_h[i], (int32_t)p.version});
         p.busy = false;
     }
     for (int k = 0; k < RING; ++k) {
@@ -199,18 +257,13 @@ int issue_predict(ga3c_sched *s, int *count) {
         const PredReq &r = s->pq[i];
         p.agents[i] = r.agent; p.ptrs_h[i] = (const uint4 *)r.frame; p.unif_h[i] = r.uniform;
     }
-    SHIP(hipMemcpyAsync(p.ptrs_d, p.ptrs_h, sizeof(void *) * n, hipMemcpyHostToDevice, s->sp));
-    SHIP(hipMemcpyAsync(p.unif_d, p.unif_h, sizeof(float) * n, hipMemcpyHostToDevice, s->sp));
-    const int vecs = (int)(s->frame_bytes / 16);
-    hipLaunchKernelGGL(gather_frames_kernel, dim3(std::min(8, (vecs + 255) / 256), n), dim3(256), 0, s->sp, p.ptrs_d,
-                       (uint4 *)p.frames_d, vecs);
+    hipLaunchKernelGGL(gather_requests_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, p.unif_h, (uint4 *)p.frames_d, p.unif_d,
+                       (int)(s->frame_bytes / 16));
     SHIP(hipGetLastError());
-    if (ga3c_predict(s->ctx, p.frames_d, n, p.unif_d, nullptr, p.val_d, nullptr, p.act_d, s->sp) != GA3C_OK)
+    if (ga3c_predict(s->ctx, p.frames_d, n, p.unif_d, nullptr, p.val_h, nullptr, p.act_h, s->sp) != GA3C_OK)
         return sfail(GA3C_EHIP, "ga3c_predict: %s", ga3c_last_error());
-    SHIP(hipMemcpyAsync(p.act_h, p.act_d, sizeof(int32_t) * n, hipMemcpyDeviceToHost, s->sp));
-    SHIP(hipMemcpyAsync(p.val_h, p.val_d, sizeof(float) * n, hipMemcpyDeviceToHost, s->sp));
     SHIP(hipEventRecord(p.done, s->sp));
-    s->pq.erase(s->pq.begin(), s->pq.begin() + n);
+    s->pq.pop(n);
     p.busy = true; p.n = n;
     p.version = s->stats.train_batches;      // the call above reads the parameters that this many updates produced
     s->ps_next = (s->ps_next + 1) % RING;
@@ -240,24 +293,18 @@ int issue_train(ga3c_sched *s, int *count) {
         const Traj &tr = s->tq[n];
         const int L = tr.len;
         for (int k = 0; k < L; ++k) t.ptrs_h[B + k] = (const uint4 *)(tr.frames + (size_t)k * s->frame_bytes);
-        memcpy(t.act_h + B, tr.actions.data(), sizeof(int32_t) * L);
-        memcpy(t.rew_h + B, tr.rewards.data(), sizeof(float) * L);
-        memcpy(t.done_h + B, tr.dones.data(), L);
         t.boot_h[n] = tr.bootstrap;
         t.seg_h[n] = B;
         if (L != T) equal = false;
         B += L; n += 1;
     }
     t.seg_h[n] = B;
-    SHIP(hipMemcpyAsync(t.ptrs_d, t.ptrs_h, sizeof(void *) * B, hipMemcpyHostToDevice, s->st));
-    SHIP(hipMemcpyAsync(t.act_d, t.act_h, sizeof(int32_t) * B, hipMemcpyHostToDevice, s->st));
-    SHIP(hipMemcpyAsync(t.rew_d, t.rew_h, sizeof(float) * B, hipMemcpyHostToDevice, s->st));
-    SHIP(hipMemcpyAsync(t.done_d, t.done_h, B, hipMemcpyHostToDevice, s->st));
-    SHIP(hipMemcpyAsync(t.boot_d, t.boot_h, sizeof(float) * n, hipMemcpyHostToDevice, s->st));
-    if (!equal) SHIP(hipMemcpyAsync(t.seg_d, t.seg_h, sizeof(int32_t) * (n + 1), hipMemcpyHostToDevice, s->st));
-    const int vecs = (int)(s->frame_bytes / 16);
-    hipLaunchKernelGGL(gather_frames_kernel, dim3(std::min(8, (vecs + 255) / 256), B), dim3(256), 0, s->st, t.ptrs_d,
-                       (uint4 *)t.frames_d, vecs);
+    memcpy(t.act_h, s->tq_act.data(), sizeof(int32_t) * B);
+    memcpy(t.rew_h, s->tq_rew.data(), sizeof(float) * B);
+    memcpy(t.done_h, s->tq_done.data(), B);
+    const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, (uint4 *)t.frames_d, t.act_d, t.seg_d, t.rew_d, t.boot_d,
+                         t.done_d, (int)(s->frame_bytes / 16), n};
+    hipLaunchKernelGGL(gather_experiences_kernel, dim3(B), dim3(256), 0, s->st, ga);
     SHIP(hipGetLastError());
     const int rc = equal ? ga3c_train_step(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp,
                                            nullptr, s->st)
@@ -276,7 +323,7 @@ int issue_train(ga3c_sched *s, int *count) {
         }
         s->tq_frames -= tr.len;
     }
-    s->tq.erase(s->tq.begin(), s->tq.begin() + n);
+    s->tq.pop(n); s->tq_act.pop(B); s->tq_rew.pop(B); s->tq_done.pop(B);
     t.busy = true; t.n_agents = n;
     s->ts_next = (s->ts_next + 1) % RING;
     s->stats.trained_frames += (int64_t)B; s->stats.train_batches += 1;
@@ -339,12 +386,11 @@ extern "C" int ga3c_sched_destroy(ga3c_sched *s) {
     for (int i = 0; i < RING; ++i) {
         PredSlot &p = s->ps[i];
         if (p.done) (void)hipEventDestroy(p.done);
-        (void)hipHostFree(p.ptrs_h); (void)hipFree(p.ptrs_d); (void)hipHostFree(p.unif_h); (void)hipFree(p.unif_d);
-        (void)hipFree(p.frames_d); (void)hipFree(p.act_d); (void)hipHostFree(p.act_h); (void)hipFree(p.val_d);
-        (void)hipHostFree(p.val_h);
+        (void)hipHostFree(p.ptrs_h); (void)hipHostFree(p.unif_h); (void)hipFree(p.unif_d); (void)hipFree(p.frames_d);
+        (void)hipHostFree(p.act_h); (void)hipHostFree(p.val_h);
         TrainSlot &t = s->ts[i];
         if (t.done) (void)hipEventDestroy(t.done);
-        (void)hipHostFree(t.ptrs_h); (void)hipFree(t.ptrs_d); (void)hipFree(t.frames_d);
+        (void)hipHostFree(t.ptrs_h); (void)hipFree(t.frames_d);
         (void)hipHostFree(t.act_h); (void)hipFree(t.act_d); (void)hipHostFree(t.rew_h); (void)hipFree(t.rew_d);
         (void)hipHostFree(t.done_h); (void)hipFree(t.done_d); (void)hipHostFree(t.boot_h); (void)hipFree(t.boot_d);
         (void)hipHostFree(t.seg_h); (void)hipFree(t.seg_d);
@@ -359,7 +405,7 @@ extern "C" int ga3c_sched_destroy(ga3c_sched *s) {
 extern "C" int ga3c_sched_submit_predict(ga3c_sched *s, int agent, const uint8_t *frame_dev, float uniform) {
     if (!s || !frame_dev) return sfail(GA3C_EINVAL, "ga3c_sched_submit_predict: null argument");
     if (((uintptr_t)frame_dev) & 15) return sfail(GA3C_EINVAL, "ga3c_sched_submit_predict: frame must be 16-byte aligned");
-    s->pq.push_back(PredReq{agent, frame_dev, uniform});
+    s->pq.push(PredReq{agent, frame_dev, uniform});
     return GA3C_OK;
 }
 
@@ -378,10 +424,10 @@ extern "C" int ga3c_sched_submit_segment(ga3c_sched *s, int agent, const uint8_t
     Traj tr;
     tr.agent = agent; tr.len = len; tr.version = policy_version < 0 ? -1 : policy_version;
     tr.frames = frames_dev; tr.bootstrap = bootstrap;
-    tr.actions.assign(actions, actions + len);
-    tr.rewards.assign(rewards, rewards + len);
-    tr.dones.assign(dones, dones + len);
-    s->tq.push_back(std::move(tr));
+    s->tq_act.push(actions, len);
+    s->tq_rew.push(rewards, len);
+    s->tq_done.push(dones, len);
+    s->tq.push(tr);
     s->tq_frames += len;
     return GA3C_OK;
 }
@@ -399,7 +445,7 @@ extern "C" int ga3c_sched_submit_predict_many(ga3c_sched *s, int n, const int32_
     for (int i = 0; i < n; ++i)
         if (!frames_dev[i] || (((uintptr_t)frames_dev[i]) & 15))
             return sfail(GA3C_EINVAL, "ga3c_sched_submit_predict_many: frame %d is null or not 16-byte aligned", i);
-    for (int i = 0; i < n; ++i) s->pq.push_back(PredReq{agents[i], frames_dev[i], uniforms[i]});
+    for (int i = 0; i < n; ++i) s->pq.push(PredReq{agents[i], frames_dev[i], uniforms[i]});
     return GA3C_OK;
 }
 
@@ -468,11 +514,9 @@ extern "C" int ga3c_sched_tick(ga3c_sched *s, int *predicted, int *trained) {
 extern "C" int ga3c_sched_poll(ga3c_sched *s, ga3c_prediction *out, int cap) {
     if (!s || (!out && cap > 0) || cap < 0) return sfail(GA3C_EINVAL, "ga3c_sched_poll: bad argument");
     STRY(harvest(s, false));
-    int n = 0;
-    while (n < cap && !s->ready.empty()) {
-        out[n++] = s->ready.front();
-        s->ready.pop_front();
-    }
+    const int n = (int)std::min<size_t>(s->ready.size(), (size_t)cap);
+    if (n > 0) memcpy(out, s->ready.data(), sizeof(ga3c_prediction) * n);
+    s->ready.pop(n);
     return n;
 }
 
