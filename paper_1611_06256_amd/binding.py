@@ -432,8 +432,8 @@ class Scheduler:
         if a.size != self.t_max or r.size != self.t_max or d.size != self.t_max:
             raise Ga3cError("trajectory arrays must have t_max entries")
         _scheck(self._lib.ga3c_sched_submit_trajectory(self._s, agent, _ptr(frames, torch.uint8, "frames"),
-                                                       a.ctypes.data_as(C.c_void_p), r.ctypes.data_as(C.c_void_p),
-                                                       d.ctypes.data_as(C.c_void_p), bootstrap),
+                                                       a.ctypes.data, r.ctypes.data,
+                                                       d.ctypes.data, bootstrap),
                 "ga3c_sched_submit_trajectory")
 
     def submit_segment(self, agent: int, frames, actions, rewards, dones, bootstrap: float, policy_version: int = -1) -> None:
@@ -445,16 +445,16 @@ class Scheduler:
         if r.size != a.size or d.size != a.size or int(frames.shape[0]) != a.size:
             raise Ga3cError("segment arrays and frames must have the same number of entries")
         _scheck(self._lib.ga3c_sched_submit_segment(self._s, agent, _ptr(frames, torch.uint8, "frames"), a.size,
-                                                    a.ctypes.data_as(C.c_void_p), r.ctypes.data_as(C.c_void_p),
-                                                    d.ctypes.data_as(C.c_void_p), bootstrap, policy_version),
+                                                    a.ctypes.data, r.ctypes.data,
+                                                    d.ctypes.data, bootstrap, policy_version),
                 "ga3c_sched_submit_segment")
 
     def submit_predict_many(self, agents, frame_ptrs, uniforms) -> None:
         """agents i32 [n], frame_ptrs u64 [n] (device addresses), uniforms f32 [n]: numpy arrays."""
         a = np.ascontiguousarray(agents, dtype=np.int32); p = np.ascontiguousarray(frame_ptrs, dtype=np.uint64)
         u = np.ascontiguousarray(uniforms, dtype=np.float32)
-        _scheck(self._lib.ga3c_sched_submit_predict_many(self._s, a.size, a.ctypes.data_as(C.c_void_p),
-                                                         p.ctypes.data_as(C.c_void_p), u.ctypes.data_as(C.c_void_p)),
+        _scheck(self._lib.ga3c_sched_submit_predict_many(self._s, a.size, a.ctypes.data,
+                                                         p.ctypes.data, u.ctypes.data),
                 "ga3c_sched_submit_predict_many")
 
     def submit_trajectory_many(self, agents, frame_ptrs, actions, rewards, dones, bootstrap) -> None:
@@ -464,9 +464,9 @@ class Scheduler:
         if ac.size != a.size * self.t_max or r.size != ac.size or d.size != ac.size or bo.size != a.size:
             raise Ga3cError("trajectory arrays must be [n, t_max] and [n]")
         _scheck(self._lib.ga3c_sched_submit_trajectory_many(
-            self._s, a.size, a.ctypes.data_as(C.c_void_p), p.ctypes.data_as(C.c_void_p),
-            ac.ctypes.data_as(C.c_void_p), r.ctypes.data_as(C.c_void_p), d.ctypes.data_as(C.c_void_p),
-            bo.ctypes.data_as(C.c_void_p)), "ga3c_sched_submit_trajectory_many")
+            self._s, a.size, a.ctypes.data, p.ctypes.data,
+            ac.ctypes.data, r.ctypes.data, d.ctypes.data,
+            bo.ctypes.data), "ga3c_sched_submit_trajectory_many")
 
     def submit_segment_many(self, agents, frame_ptrs, lens, actions, rewards, dones, bootstrap, policy_versions=None) -> None:
         """n segments at once: lens i32 [n]; actions / rewards / dones [n, t_max] (row i: the first lens[i] entries
@@ -480,9 +480,9 @@ class Scheduler:
                 ln.size != a.size or p.size != a.size or (pv is not None and pv.size != a.size):
             raise Ga3cError("segment arrays must be [n, t_max] and [n]")
         _scheck(self._lib.ga3c_sched_submit_segment_many(
-            self._s, a.size, a.ctypes.data_as(C.c_void_p), p.ctypes.data_as(C.c_void_p), ln.ctypes.data_as(C.c_void_p),
-            ac.ctypes.data_as(C.c_void_p), r.ctypes.data_as(C.c_void_p), d.ctypes.data_as(C.c_void_p),
-            bo.ctypes.data_as(C.c_void_p), None if pv is None else pv.ctypes.data_as(C.c_void_p)),
+            self._s, a.size, a.ctypes.data, p.ctypes.data, ln.ctypes.data,
+            ac.ctypes.data, r.ctypes.data, d.ctypes.data,
+            bo.ctypes.data, None if pv is None else pv.ctypes.data),
             "ga3c_sched_submit_segment_many")
 
     def poll_arrays(self, cap: int = 4096, with_version: bool = False):

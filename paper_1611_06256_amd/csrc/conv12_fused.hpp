@@ -112,7 +112,7 @@ inline hipError_t launch_conv12_filter_fragments(const float *w1, const float *w
     return hipGetLastError();
 }
 
-// x: [n][4][84][84] bytes; frag: the three fragment sets; b1 [16], b2 [32];
+// x: [n][4][84][84] bytes, or table: where each frame lies (FramePointer); frag: the three fragment sets; b1 [16], b2 [32];
 // y1: [n][16][400] or nullptr; y2: [n][32][81].  Frames blockIdx.x, + gridDim.x, ...
 // ONE: the reduced-precision variant (operands rounded to bfloat16): only the first
 // term of every operand exists, so one MFMA per tap block replaces three / six and
@@ -126,8 +126,9 @@ inline hipError_t launch_conv12_filter_fragments(const float *w1, const float *w
 // reading it.  idle(it) is called by the layer-1 wavefronts in the iterations in which they have no frame left to
 // work on (while layer 2 runs), idle2() by the layer-2 wavefronts in the first iteration, when there is no layer-1
 // output yet.
-template <bool ONE, bool KEEP, bool TO_LDS, class Idle, class Idle2>
-__device__ __forceinline__ void conv12_fused_block(const uint8_t *__restrict__ x, const u32x4 *__restrict__ frag,
+template <bool ONE, bool KEEP, bool TO_LDS, bool TABLE, class Idle, class Idle2>
+__device__ __forceinline__ void conv12_fused_block(const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table,
+                                                   const u32x4 *__restrict__ frag,
                                                    const float *__restrict__ b1, const float *__restrict__ b2,
                                                    float *__restrict__ y1, float *__restrict__ y2, int first, int stride,
                                                    int nframes, float scale, unsigned char *c12_smem, Idle idle, Idle2 idle2) {
@@ -151,10 +152,13 @@ __device__ __forceinline__ void conv12_fused_block(const uint8_t *__restrict__ x
     int vidx[VPT];
 #pragma unroll
     for (int i = 0; i < VPT; ++i) vidx[i] = min(rt + 256 * i, NV - 1);
+    FramePointer<TABLE> next;
     if (layer1) {
-        const u32x4 *src = (const u32x4 *)(x + (size_t)first * CHW1);
+        next.ask(x, table, first, CHW1);
+        const u32x4 *src = (const u32x4 *)next.get();
 #pragma unroll
         for (int i = 0; i < VPT; ++i) pre[i] = src[vidx[i]];
+        if (TABLE && !TO_LDS) next.ask(x, table, min(first + stride, nframes - 1), CHW1);
     }
 
     // My filter fragments, split into three bf16 terms ahead of time (conv12_filter_fragments_kernel).  Every block
@@ -234,10 +238,12 @@ __device__ __forceinline__ void conv12_fused_block(const uint8_t *__restrict__ x
         if (layer1) {
             if (it < n) {
                 const int f = first + it * grid;
-                {
-                    const u32x4 *src = (const u32x4 *)(x + (size_t)min(f + grid, nframes - 1) * CHW1);
+                if (!TO_LDS) {
+                    if (!TABLE) next.ask(x, table, min(f + grid, nframes - 1), CHW1);
+                    const u32x4 *src = (const u32x4 *)next.get();
 #pragma unroll
                     for (int i = 0; i < VPT; ++i) pre[i] = src[vidx[i]];
+                    if (TABLE) next.ask(x, table, min(f + 2 * grid, nframes - 1), CHW1);
                 }
                 __bf16 *yp = ys + (it & 1) * 3 * C12_Y1;
                 float *yb = KEEP ? y1 + (size_t)f * 16 * NPIX1 : nullptr;
@@ -387,27 +393,30 @@ __device__ __forceinline__ void conv12_fused_block(const uint8_t *__restrict__ x
     }
 }
 
-template <bool ONE, bool KEEP>
+template <bool ONE, bool KEEP, bool TABLE>
 __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t *__restrict__ x,
+                                                                  const uint8_t *const *__restrict__ table,
                                                                   const u32x4 *__restrict__ frag,
                                                                   const float *__restrict__ b1,
                                                                   const float *__restrict__ b2, float *__restrict__ y1,
                                                                   float *__restrict__ y2, int nframes, float scale,
                                                                   int rb) {
     extern __shared__ __attribute__((aligned(16))) unsigned char c12_smem[];
-    conv12_fused_block<ONE, KEEP, false>(x, frag, b1, b2, y1, y2, (int)blockIdx.x, (int)gridDim.x, nframes, scale,
+    conv12_fused_block<ONE, KEEP, false, TABLE>(x, table, frag, b1, b2, y1, y2, (int)blockIdx.x, (int)gridDim.x, nframes, scale,
                                          c12_smem, [](int) {}, []() {});
 }
 
 inline int conv12_fused_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
 
-inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const u32x4 *frag, const float *b1, const float *b2, float *y1,
+inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2, float *y1,
                                           float *y2, int nframes, float scale, hipStream_t s, int rb) {
     if (nframes <= 0) return hipSuccess;
     static bool attr_set = false;     // the kernels need more LDS than the default limit
     if (!attr_set) {
-        const void *ks[4] = {(const void *)conv12_fused_fwd_kernel<false, false>, (const void *)conv12_fused_fwd_kernel<false, true>,
-                             (const void *)conv12_fused_fwd_kernel<true, false>, (const void *)conv12_fused_fwd_kernel<true, true>};
+        const void *ks[8] = {(const void *)conv12_fused_fwd_kernel<false, false, false>, (const void *)conv12_fused_fwd_kernel<false, true, false>,
+                             (const void *)conv12_fused_fwd_kernel<true, false, false>, (const void *)conv12_fused_fwd_kernel<true, true, false>,
+                             (const void *)conv12_fused_fwd_kernel<false, false, true>, (const void *)conv12_fused_fwd_kernel<false, true, true>,
+                             (const void *)conv12_fused_fwd_kernel<true, false, true>, (const void *)conv12_fused_fwd_kernel<true, true, true>};
         for (const void *k : ks) {
             const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C12_LDS_BYTES);
             if (e != hipSuccess) return e;
@@ -416,8 +425,12 @@ inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const u32x4 *frag, c
     }
     const dim3 grid(conv12_fused_blocks(nframes)), block(512);
 #define GA3C_C12_LAUNCH(ONE_, KEEP_)                                                                                          \
-    ga3c::launch((conv12_fused_fwd_kernel<ONE_, KEEP_>), grid, block, C12_LDS_BYTES, s, x, frag, b1, b2, y1, y2, nframes, \
-                       scale, rb)
+    do {                                                                                                                      \
+        if (table) ga3c::launch((conv12_fused_fwd_kernel<ONE_, KEEP_, true>), grid, block, C12_LDS_BYTES, s, x, table, frag,  \
+                                b1, b2, y1, y2, nframes, scale, rb);                                                         \
+        else ga3c::launch((conv12_fused_fwd_kernel<ONE_, KEEP_, false>), grid, block, C12_LDS_BYTES, s, x, table, frag, b1,   \
+                          b2, y1, y2, nframes, scale, rb);                                                                   \
+    } while (0)
     if (rb) { if (y1) GA3C_C12_LAUNCH(true, true); else GA3C_C12_LAUNCH(true, false); }
     else { if (y1) GA3C_C12_LAUNCH(false, true); else GA3C_C12_LAUNCH(false, false); }
 #undef GA3C_C12_LAUNCH

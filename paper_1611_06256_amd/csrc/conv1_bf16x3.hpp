@@ -68,6 +68,22 @@ __device__ __forceinline__ void split3_pair(float x, float y, uint32_t &hi, uint
     lo = pack_bf16_rne(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xffff0000u));
 }
 
+// Where frame f lies.  TABLE: wherever the table's entry points (x is not used).  The table is host memory that no cache keeps,
+// and an entry takes about two microseconds to arrive: one lane asks for it, and kernels that walk over frames ask early.
+template <bool TABLE>
+struct FramePointer {
+    const uint8_t *at;
+    __device__ __forceinline__ void ask(const uint8_t *x, const uint8_t *const *table, int f, int bytes) {
+        if (!TABLE) at = x + (size_t)f * bytes;
+        else if ((threadIdx.x & 63) == 0) at = __builtin_nontemporal_load(table + f);
+    }
+    __device__ __forceinline__ const uint8_t *get() const {
+        if (!TABLE) return at;
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)at), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uintptr_t)at >> 32));
+        return (const uint8_t *)(((uintptr_t)hi << 32) | lo);
+    }
+};
+
 // 16 bytes -> 16 bf16 (two 16-byte vectors)
 __device__ __forceinline__ void bytes_to_bf16(const u32x4 b, u32x4 &lo8, u32x4 &hi8) {
     Bf16x8Bits o[2];
@@ -88,8 +104,9 @@ __device__ __forceinline__ void bytes_to_bf16(const u32x4 b, u32x4 &lo8, u32x4 &
 // frame sits in LDS as bf16 [4][84][84]; a lane (pixel p, group g) reads the 8
 // taps of filter row u = 4*(kb%2) + g of channel kb/2 in one go, which is the
 // k = 8g..8g+7 share of a 16x16x32 MFMA.  The split filters stay in registers.
-template <int OC>
+template <int OC, bool TABLE>
 __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t *__restrict__ x,
+                                                                  const uint8_t *const *__restrict__ table,
                                                                   const float *__restrict__ w,
                                                                   const float *__restrict__ bias, float *__restrict__ y,
                                                                   int nframes, float scale, int rb) {
@@ -141,10 +158,14 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
     u32x4 pre[VPT];
     int f = blockIdx.x;
     {
-        const u32x4 *src = (const u32x4 *)(x + (size_t)min(f, nframes - 1) * CHW);
+        FramePointer<TABLE> first;
+        first.ask(x, table, min(f, nframes - 1), CHW);
+        const u32x4 *src = (const u32x4 *)first.get();
 #pragma unroll
         for (int i = 0; i < VPT; ++i) pre[i] = src[vidx[i]];
     }
+    FramePointer<TABLE> next;
+    if (TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
     for (; f < nframes; f += gridDim.x) {
         __syncthreads();
 #pragma unroll
@@ -156,9 +177,11 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
         }
         __syncthreads();
         {
-            const u32x4 *src = (const u32x4 *)(x + (size_t)min(f + (int)gridDim.x, nframes - 1) * CHW);
+            if (!TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
+            const u32x4 *src = (const u32x4 *)next.get();
 #pragma unroll
             for (int i = 0; i < VPT; ++i) pre[i] = src[vidx[i]];
+            if (TABLE) next.ask(x, table, min(f + 2 * (int)gridDim.x, nframes - 1), CHW);
         }
         floatx4 acc[TPW];
 #pragma unroll
@@ -197,11 +220,12 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
 }
 
 template <int OC>
-inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const float *w, const float *bias, float *y, int nframes,
+inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const uint8_t *const *table, const float *w, const float *bias, float *y, int nframes,
                                           float scale, hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
     const int grid = nframes < 512 ? nframes : 512;
-    ga3c::launch((conv1_bf16x3_fwd_kernel<OC>), dim3(grid), dim3(256), 0, s, x, w, bias, y, nframes, scale, rb);
+    if (table) ga3c::launch((conv1_bf16x3_fwd_kernel<OC, true>), dim3(grid), dim3(256), 0, s, x, table, w, bias, y, nframes, scale, rb);
+    else ga3c::launch((conv1_bf16x3_fwd_kernel<OC, false>), dim3(grid), dim3(256), 0, s, x, table, w, bias, y, nframes, scale, rb);
     return hipGetLastError();
 }
 
@@ -219,8 +243,9 @@ inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const float *w, cons
 // Rows of 20 pixels are padded to 24 = 3 blocks of 8 with zero dY.
 // part: [gridDim.x][OCT][257]; the last column is the bias gradient.  A layer
 // with OCT = 32 filters is done in two slices of 16 (blockIdx.y).
-template <int OCT, int NPART>
+template <int OCT, int NPART, bool TABLE>
 __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const uint8_t *__restrict__ x,
+                                                                 const uint8_t *const *__restrict__ table,
                                                                  const float *__restrict__ dy,
                                                                  float *__restrict__ part, int nframes, float scale,
                                                                  int rb) {
@@ -278,8 +303,8 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
     typedef uint32_t u32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
     u32x4 xpre[IPT];
     float4 dpre[DPT];
-    auto fetch = [&](int ff) {
-        const uint32_t *xs = (const uint32_t *)(x + (size_t)ff * CHW);
+    auto fetch = [&](const uint8_t *at, int ff) {
+        const uint32_t *xs = (const uint32_t *)at;
 #pragma unroll
         for (int i = 0; i < IPT; ++i) xpre[i] = *(const u32x4_dword_aligned *)(xs + xsrc[i]);
         const float4 *ds = (const float4 *)(dy + ((size_t)ff * OCT + oc0) * NPIX);
@@ -287,7 +312,10 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
         for (int i = 0; i < DPT; ++i) dpre[i] = ds[dsrc[i]];
     };
     int f = blockIdx.x;
-    fetch(min(f, nframes - 1));
+    FramePointer<TABLE> next;
+    next.ask(x, table, min(f, nframes - 1), CHW);
+    fetch(next.get(), min(f, nframes - 1));
+    if (TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
     const int ch = wave & 3, prt = wave >> 2;        // wavefronts w, w + 4, ... share channel w and divide the pixel blocks
     const __bf16 *xq = xp + (ch * 16 + l16) * XPLANE;                // my plane
     for (; f < nframes; f += gridDim.x) {
@@ -321,7 +349,9 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
             }
         }
         __syncthreads();
-        fetch(min(f + (int)gridDim.x, nframes - 1));
+        if (!TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
+        fetch(next.get(), min(f + (int)gridDim.x, nframes - 1));
+        if (TABLE) next.ask(x, table, min(f + 2 * (int)gridDim.x, nframes - 1), CHW);
         if (tid < 256) {   // bias: 16 lanes share a filter, 100 partial sums each
             const int oc = tid / 16, pt = tid % 16;
             float sum = 0.f;
@@ -408,11 +438,12 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
 inline int conv1_bf16x3_wgrad_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
 
 template <int OCT = 16, int NPART = 4>
-inline hipError_t launch_conv1_bf16x3_wgrad(const uint8_t *x, const float *dy, float *part, int nframes, float scale,
+inline hipError_t launch_conv1_bf16x3_wgrad(const uint8_t *x, const uint8_t *const *table, const float *dy, float *part, int nframes, float scale,
                                             hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
-    ga3c::launch((conv1_bf16x3_wgrad_kernel<OCT, NPART>), dim3(conv1_bf16x3_wgrad_blocks(nframes), OCT / 16),
-                       dim3(256 * NPART), 0, s, x, dy, part, nframes, scale, rb);
+    const dim3 grid(conv1_bf16x3_wgrad_blocks(nframes), OCT / 16), block(256 * NPART);
+    if (table) ga3c::launch((conv1_bf16x3_wgrad_kernel<OCT, NPART, true>), grid, block, 0, s, x, table, dy, part, nframes, scale, rb);
+    else ga3c::launch((conv1_bf16x3_wgrad_kernel<OCT, NPART, false>), grid, block, 0, s, x, table, dy, part, nframes, scale, rb);
     return hipGetLastError();
 }
 

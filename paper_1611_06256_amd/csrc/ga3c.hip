@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/ga3c.h"
+#include "frame_table.hpp"
 #include "problems.hpp"
 #include "conv_frame.hpp"
 #include "dense_gemm.hpp"
@@ -347,7 +348,6 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
     // thread tid < nout finishes output a of frame fb
     const int ofb = min(tid / (A + 1), nf - 1), oa = tid % (A + 1);
     const float obias = oa < A ? bp[oa] : bv[0];
-    const float ou = (actions && tid < nout) ? uniforms[b0 + ofb] : 0.f;
     // padding columns of the LDS rows stay zero
     for (int e = tid; e < 4 * (F4 - F); e += NT) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
     if (!WSTAGED)
@@ -411,6 +411,8 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
         }
     }
     __syncthreads();
+    // asked for after everything that the products need, and needed last: it may be in host memory
+    const float ou = (actions && tid < nout) ? uniforms[b0 + ofb] : 0.f;
     // Dot products from LDS, 16 bytes per read, without cross-lane traffic:
     // thread (frame, output, part of k) adds its share; KP shares make one output (three where the block has
     // threads for them, fewer when there are many actions).
@@ -512,9 +514,9 @@ constexpr size_t SP_HEADS_MAX = sizeof(__bf16) * (C12_XS + 2 * 3 * C12_Y1) - SP_
 constexpr int SP_ROWS = 2;                                 // fc outputs per wavefront
 constexpr int SP_WJ = (SP_FLAT / 4 + 63) / 64;             // 16-byte vectors of one fc row per lane
 
-template <bool ONE, int SLICES>
+template <bool ONE, int SLICES, bool TABLE>
 __global__ __launch_bounds__(512, 1) void predict_small_kernel(
-    const uint8_t *__restrict__ x, const u32x4 *__restrict__ frag, const float *__restrict__ b1,
+    const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table, const u32x4 *__restrict__ frag, const float *__restrict__ b1,
     const float *__restrict__ b2, const float *__restrict__ Wfc, const float *__restrict__ fcb, float *__restrict__ h,
     int *__restrict__ ticket, int A, const float *__restrict__ Wp, const float *__restrict__ bp,
     const float *__restrict__ Wv, const float *__restrict__ bv, float *logits, float *values, float *probs,
@@ -568,7 +570,7 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
         if (hw_early) heads_store_weights<256>((float *)(sp_smem + SP_HEADS_OFF), hw, tid - 256, SP_FC, A, rb);
         else heads_stage_weights<256>((float *)(sp_smem + SP_HEADS_OFF), tid - 256, SP_FC, A, Wp, Wv, rb);
     };
-    conv12_fused_block<ONE, false, true>(x, frag, b1, b2, nullptr, nullptr, frame, 1 << 24, frame + 1, scale, sp_smem,
+    conv12_fused_block<ONE, false, true, TABLE>(x, table, frag, b1, b2, nullptr, nullptr, frame, 1 << 24, frame + 1, scale, sp_smem,
                                          fetch_rows, store_heads_weights);
     if (ALL_WAVES_FC && wave >= 4) { load_rows(0, 0); pin_rows(0); }
     __syncthreads();
@@ -1528,8 +1530,9 @@ bool on_band_kernels(const ConvGeom &g, int l) {
     return band_ok<32>(g.H, g.W) && band_f32_ok<32>(g.H, g.W);
 }
 
-// Forward pass of `B` frames into `w`; heads outputs to the optional pointers.
-int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool keep_zv, float *logits, float *values,
+// Forward pass of `B` frames into `w`; heads outputs to the optional pointers.  table (frames is nullptr then): the frames lie
+// where its entries point; only where takes_frame_table says so.
+int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_t *const *table, int B, bool keep_zv, float *logits, float *values,
             float *probs, const float *uniforms, int32_t *actions, hipStream_t s, bool with_heads = true) {
     const float *th = c->theta2[which];
     const int nb = 2 * c->nconv;
@@ -1540,11 +1543,12 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
         // a handful of frames: one launch for the whole network
         static bool attr_set = false;
         if (!attr_set) {
-            const void *ks[8] = {(const void *)predict_small_kernel<false, 32>, (const void *)predict_small_kernel<true, 32>,
-                                 (const void *)predict_small_kernel<false, 16>, (const void *)predict_small_kernel<true, 16>,
-                                 (const void *)predict_small_kernel<false, 8>, (const void *)predict_small_kernel<true, 8>,
-                                 (const void *)predict_small_kernel<false, 4>, (const void *)predict_small_kernel<true, 4>};
-            for (const void *k : ks) HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C12_LDS_BYTES));
+#define GA3C_SP_ALLOW(ONE_, SL_)                                                                                               \
+    for (const void *k : {(const void *)predict_small_kernel<ONE_, SL_, false>, (const void *)predict_small_kernel<ONE_, SL_, true>}) \
+        HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C12_LDS_BYTES))
+            GA3C_SP_ALLOW(false, 32); GA3C_SP_ALLOW(false, 16); GA3C_SP_ALLOW(false, 8); GA3C_SP_ALLOW(false, 4);
+            GA3C_SP_ALLOW(true, 32); GA3C_SP_ALLOW(true, 16); GA3C_SP_ALLOW(true, 8); GA3C_SP_ALLOW(true, 4);
+#undef GA3C_SP_ALLOW
             attr_set = true;
         }
         const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1];
@@ -1552,8 +1556,9 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
               (double)B * g0.CHW + 4.0 * c->flat * c->F);
         const int slices = B <= 8 ? 32 : B <= 16 ? 16 : B <= 32 ? 8 : 4;
         const dim3 grid(B * slices), block(512);
-#define GA3C_SP_LAUNCH(ONE_, SL_)                                                                                              \
-    ga3c::launch((predict_small_kernel<ONE_, SL_>), grid, block, C12_LDS_BYTES, s, frames, c->cfrag[which],             \
+#define GA3C_SP_LAUNCH(ONE_, SL_) do { if (table) GA3C_SP_LAUNCH1(ONE_, SL_, true); else GA3C_SP_LAUNCH1(ONE_, SL_, false); } while (0)
+#define GA3C_SP_LAUNCH1(ONE_, SL_, TABLE_)                                                                                     \
+    ga3c::launch((predict_small_kernel<ONE_, SL_, TABLE_>), grid, block, C12_LDS_BYTES, s, frames, table, c->cfrag[which],             \
                        th + c->off[1], th + c->off[3], th + c->off[nb], th + c->off[nb + 1], w.h, c->ticket, c->A,            \
                        th + c->off[nb + 2], th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5], logits, values,    \
                        probs, uniforms, actions, 1.f / 255.f, c->rb)
@@ -1565,6 +1570,7 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
         if (c->rb) GA3C_SP_PICK(true); else GA3C_SP_PICK(false);
 #undef GA3C_SP_PICK
 #undef GA3C_SP_LAUNCH
+#undef GA3C_SP_LAUNCH1
         HIP_TRY(hipGetLastError());
         return GA3C_OK;
     }
@@ -1573,7 +1579,7 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
         const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1];
         STAGE("conv12_fwd", 2.0 * B * (g0.OHW * g0.OC * g0.K + g1.OHW * g1.OC * g1.K),
               (double)B * (g0.CHW + (keep_zv ? 4.0 * g0.OC * g0.OHW : 0.0) + 4.0 * g1.OC * g1.OHW));
-        HIP_TRY(launch_conv12_fused_fwd(frames, c->cfrag[which], th + c->off[1], th + c->off[3],
+        HIP_TRY(launch_conv12_fused_fwd(frames, table, c->cfrag[which], th + c->off[1], th + c->off[3],
                                         keep_zv ? w.act[0] : nullptr, w.act[1], B, 1.f / 255.f, s, c->rb));
         first = 2;
     }
@@ -1584,11 +1590,11 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, int B, bool 
         const void *xin = l == 0 ? (const void *)frames : (const void *)w.act[l - 1];
         if (c->fast && is_aligned16(wl) && is_aligned16(xin)) {
             if (spec_matches<SpecS1>(g, l == 0)) {
-                HIP_TRY(launch_conv1_bf16x3_fwd<16>((const uint8_t *)xin, wl, bl, w.act[l], B, 1.f / 255.f, s, c->rb));
+                HIP_TRY(launch_conv1_bf16x3_fwd<16>((const uint8_t *)xin, table, wl, bl, w.act[l], B, 1.f / 255.f, s, c->rb));
                 continue;
             }
             if (spec_matches<SpecL1>(g, l == 0)) {
-                HIP_TRY(launch_conv1_bf16x3_fwd<32>((const uint8_t *)xin, wl, bl, w.act[l], B, 1.f / 255.f, s, c->rb));
+                HIP_TRY(launch_conv1_bf16x3_fwd<32>((const uint8_t *)xin, table, wl, bl, w.act[l], B, 1.f / 255.f, s, c->rb));
                 continue;
             }
             if (spec_matches<SpecS2>(g, l == 0)) {
@@ -1976,25 +1982,30 @@ extern "C" int ga3c_params_set(ga3c_ctx *c, int which, const float *src, size_t 
     return GA3C_OK;
 }
 
-extern "C" int ga3c_predict(ga3c_ctx *c, const uint8_t *frames, int B, const float *uniforms, float *logits,
-                            float *values, float *probs, int32_t *actions, void *stream) {
+static int predict_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *const *table, int B, const float *uniforms, float *logits,
+                        float *values, float *probs, int32_t *actions, void *stream) {
     if (!c) return fail(GA3C_EINVAL, "ga3c_predict: null context");
     if (B < 0 || B > c->max_pred) return fail(GA3C_EINVAL, "ga3c_predict: B = %d outside [0, %d]", B, c->max_pred);
     if (B == 0) return GA3C_OK;
-    if (!frames) return fail(GA3C_EINVAL, "ga3c_predict: null frames");
+    if (!frames && !table) return fail(GA3C_EINVAL, "ga3c_predict: null frames");
     if (actions && !uniforms) return fail(GA3C_EINVAL, "ga3c_predict: actions requested without uniforms");
     hipStream_t s = (hipStream_t)stream;
     const int cur = c->cur;
     TRY(wait_ready(c, cur, s));
-    const int rc = forward(c, cur, c->pred, frames, B, false, logits, values, probs, uniforms, actions, s);
+    const int rc = forward(c, cur, c->pred, frames, table, B, false, logits, values, probs, uniforms, actions, s);
     if (rc != GA3C_OK) return rc;
     TRY(mark_readers(c, cur, s));
     return GA3C_OK;
 }
 
+extern "C" int ga3c_predict(ga3c_ctx *c, const uint8_t *frames, int B, const float *uniforms, float *logits,
+                            float *values, float *probs, int32_t *actions, void *stream) {
+    return predict_impl(c, frames, nullptr, B, uniforms, logits, values, probs, actions, stream);
+}
+
 // One update on B frames.  seg_start == nullptr: N segments of T frames each
 // (B = N*T); otherwise N segments of unequal length, T = 1.
-static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *actions, const float *rewards,
+static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *const *table, const int32_t *actions, const float *rewards,
                            const uint8_t *dones, const float *bootstrap, const int32_t *seg_start, int N, int T, int B,
                            const ga3c_hparams *hp, ga3c_train_stats *stats, void *stream) {
     hipStream_t s = (hipStream_t)stream;
@@ -2008,7 +2019,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
     // One kernel finishes the fc layer, runs the heads, the loss and the heads' backward pass, if its LDS fits.
     const size_t ht_lds = sizeof(float) * (size_t)heads_train_lds_floats(F, A);
     const bool fused_heads = c->fast && ht_lds <= HEADS_TRAIN_MAX_LDS && HD_FRAMES * (A + 1) <= 256;      // a thread per (frame, output)
-    int rc = forward(c, cur, w, frames, B, true, nullptr, nullptr, nullptr, nullptr, nullptr, s, !fused_heads);
+    int rc = forward(c, cur, w, frames, table, B, true, nullptr, nullptr, nullptr, nullptr, nullptr, s, !fused_heads);
     if (rc != GA3C_OK) return rc;
 
     const int nloss = fused_heads ? cdiv(B, HD_FRAMES) : cdiv(B, LOSS_THREADS);
@@ -2172,9 +2183,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const int32_t *ac
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
             STAGE(CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * ((l == 0 ? 1.0 : 4.0) * g.CHW + 4.0 * g.OC * g.OHW));
             if (kind == 1) {
-                HIP_TRY(launch_conv1_bf16x3_wgrad((const uint8_t *)xin, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
+                HIP_TRY(launch_conv1_bf16x3_wgrad((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
             } else if (kind == 2) {
-                HIP_TRY(launch_conv1_bf16x3_wgrad<32>((const uint8_t *)xin, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
+                HIP_TRY(launch_conv1_bf16x3_wgrad<32>((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
             } else if (kind == 3) {
                 HIP_TRY((launch_conv_wgrad_frame<SpecS2, 1, 8>)((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 4) {
@@ -2288,7 +2299,7 @@ extern "C" int ga3c_train_step(ga3c_ctx *c, const uint8_t *frames, const int32_t
     if (BL > c->max_train) return fail(GA3C_EINVAL, "ga3c_train_step: N*T = %lld above capacity %d", BL, c->max_train);
     if (BL == 0) return GA3C_OK;
     if (!frames || !actions || !rewards || !dones || !hp) return fail(GA3C_EINVAL, "ga3c_train_step: null argument");
-    return train_step_impl(c, frames, actions, rewards, dones, bootstrap, nullptr, N, T, (int)BL, hp, stats, stream);
+    return train_step_impl(c, frames, nullptr, actions, rewards, dones, bootstrap, nullptr, N, T, (int)BL, hp, stats, stream);
 }
 
 extern "C" int ga3c_train_step_ragged(ga3c_ctx *c, const uint8_t *frames, const int32_t *actions, const float *rewards,
@@ -2302,7 +2313,21 @@ extern "C" int ga3c_train_step_ragged(ga3c_ctx *c, const uint8_t *frames, const 
     if (N == 0) return fail(GA3C_EINVAL, "ga3c_train_step_ragged: frames without a segment");
     if (!frames || !actions || !rewards || !dones || !seg_start || !hp)
         return fail(GA3C_EINVAL, "ga3c_train_step_ragged: null argument");
-    return train_step_impl(c, frames, actions, rewards, dones, bootstrap, seg_start, N, 1, n_frames, hp, stats, stream);
+    return train_step_impl(c, frames, nullptr, actions, rewards, dones, bootstrap, seg_start, N, 1, n_frames, hp, stats, stream);
+}
+
+// What the scheduler calls (frame_table.hpp).
+bool ga3c::takes_frame_table(const ga3c_ctx *c) {
+    const ConvGeom &g = c->geom[0];
+    return c->fast && is_aligned16(c->theta2[0] + c->off[0]) && (spec_matches<SpecS1>(g, true) || spec_matches<SpecL1>(g, true));
+}
+int ga3c::predict_from_table(ga3c_ctx *c, const uint8_t *const *table, int B, const float *uniforms, float *values, int32_t *actions, hipStream_t s) {
+    return predict_impl(c, nullptr, table, B, uniforms, nullptr, values, nullptr, actions, s);
+}
+int ga3c::train_from_table(ga3c_ctx *c, const uint8_t *const *table, const int32_t *actions, const float *rewards, const uint8_t *dones,
+                           const float *bootstrap, const int32_t *seg_start, int N, int T, int B, const ga3c_hparams *hp, hipStream_t s) {
+    if (B < 1 || B > c->max_train) return fail(GA3C_EINVAL, "ga3c_train_step: %d frames outside 1..%d", B, c->max_train);
+    return train_step_impl(c, nullptr, table, actions, rewards, dones, bootstrap, seg_start, N, T, B, hp, nullptr, s);
 }
 
 extern "C" int ga3c_train_debug_get(ga3c_ctx *c, int which, float *dst, size_t n, void *stream) {
@@ -2481,5 +2506,5 @@ extern "C" int ga3c_predict_static(int n_actions, int math, const float *theta, 
     hipStream_t s = (hipStream_t)stream;
     // the filters as split MFMA fragments, from the caller's parameters (a context does this when they change)
     TRY(refresh_derived(&c, 0, s));
-    return forward(&c, 0, c.pred, frames, B, false, logits, values, probs, uniforms, actions, s);
+    return forward(&c, 0, c.pred, frames, nullptr, B, false, logits, values, probs, uniforms, actions, s);
 }

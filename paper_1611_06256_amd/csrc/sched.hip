@@ -21,6 +21,7 @@
 #include <vector>
 
 #include "../../include/ga3c.h"
+#include "frame_table.hpp"
 #include "sched_error.hpp"
 
 using ga3c::sfail;
@@ -35,10 +36,11 @@ namespace {
                          hipGetErrorString(e_));                                                     \
     } while (0)
 
-// A batch's frames and scalars are fetched by the kernel itself from what the host has written into pinned memory: one
-// launch where a copy command per list (each a few microseconds of its own on the stream) went before it.  Reads of host
-// memory are not cached, so a frame's block asks for its pointer once and keeps all of a thread's vectors in flight.
-// (256 requests and 256 trained segments per round of the closed loop: 24 copy commands fewer per update.)
+// A batch goes to the GPU as a table of frame pointers and lists of scalars that the host has written into pinned memory:
+// where the network's first layer takes frames from a table (frame_table.hpp) its kernels read all of that themselves, other
+// networks get their frames put together by a kernel first.  No copy commands either way (a few microseconds of the stream
+// each; a round of 256 agents had 24 of them).  Reads of host memory are not cached, so a frame's block asks for its pointer
+// once and keeps all of a thread's vectors in flight.
 constexpr int GATHER_VPT = 8;        // 16-byte vectors of a frame in flight per thread
 
 __device__ __forceinline__ void copy_frame(const uint4 *__restrict__ s, uint4 *__restrict__ d, int frame_vecs) {
@@ -52,15 +54,13 @@ __device__ __forceinline__ void copy_frame(const uint4 *__restrict__ s, uint4 *_
     }
 }
 
-// Block i: frame i of a prediction batch and its uniform number.  *_h are host memory.
-__global__ __launch_bounds__(256) void gather_requests_kernel(const uint4 *const *__restrict__ src_h, const float *__restrict__ unif_h,
-                                                              uint4 *__restrict__ frames, float *__restrict__ unif, int frame_vecs) {
-    const int i = blockIdx.x;
-    if (threadIdx.x == 0) unif[i] = unif_h[i];
-    copy_frame(src_h[i], frames + (size_t)i * frame_vecs, frame_vecs);
+// Block i: frame i of a prediction batch.
+__global__ __launch_bounds__(256) void gather_frames_kernel(const uint4 *const *__restrict__ src_h, uint4 *__restrict__ frames, int frame_vecs) {
+    copy_frame(src_h[blockIdx.x], frames + (size_t)blockIdx.x * frame_vecs, frame_vecs);
 }
 
-// Block i: experience i of a training batch; the first n_segments blocks also fetch a segment's bootstrap value and start.
+// Block i: experience i of a training batch (frames == nullptr: without its frame); the first n_segments blocks also fetch a
+// segment's bootstrap value and start.  *_h: host memory.
 struct GatherTrain {
     const uint4 *const *src_h;
     const int32_t *act_h, *seg_h;
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void gather_experiences_kernel(const GatherTra
         a.seg[i] = a.seg_h[i];
         if (i == 0) a.seg[a.n_segments] = a.seg_h[a.n_segments];
     }
-    copy_frame(a.src_h[i], a.frames + (size_t)i * a.frame_vecs, a.frame_vecs);
+    if (a.frames) copy_frame(a.src_h[i], a.frames + (size_t)i * a.frame_vecs, a.frame_vecs);
 }
 
 }  // namespace
@@ -125,8 +125,8 @@ struct PredSlot {
     bool busy = false;
     int n = 0;
     const uint4 **ptrs_h = nullptr;                       // *_h: pinned host memory, which the kernels read and write
-    float *unif_h = nullptr, *unif_d = nullptr;
-    uint8_t *frames_d = nullptr;
+    float *unif_h = nullptr;
+    uint8_t *frames_d = nullptr;                          // the batch's frames, for networks that do not take a table
     int32_t *act_h = nullptr;
     float *val_h = nullptr;
     std::vector<int> agents;
@@ -192,13 +192,11 @@ int alloc_slots(ga3c_sched *s) {
         PredSlot &p = s->ps[i];
         SHIP(hipEventCreateWithFlags(&p.done, hipEventDisableTiming));
         STRY(pinned(&p.ptrs_h, s->max_pred));
-        STRY(pinned(&p.unif_h, s->max_pred)); STRY(device(&p.unif_d, s->max_pred));
-        STRY(device(&p.frames_d, (size_t)s->max_pred * s->frame_bytes));
+        STRY(pinned(&p.unif_h, s->max_pred));
         STRY(pinned(&p.act_h, s->max_pred)); STRY(pinned(&p.val_h, s->max_pred));
         TrainSlot &t = s->ts[i];
         SHIP(hipEventCreateWithFlags(&t.done, hipEventDisableTiming));
         STRY(pinned(&t.ptrs_h, maxN));
-        STRY(device(&t.frames_d, (size_t)s->max_train * s->frame_bytes));
         STRY(pinned(&t.act_h, s->max_train)); STRY(device(&t.act_d, s->max_train));
         STRY(pinned(&t.rew_h, s->max_train)); STRY(device(&t.rew_d, s->max_train));
         STRY(pinned(&t.done_h, s->max_train)); STRY(device(&t.done_d, s->max_train));
@@ -257,11 +255,16 @@ int issue_predict(ga3c_sched *s, int *count) {
         const PredReq &r = s->pq[i];
         p.agents[i] = r.agent; p.ptrs_h[i] = (const uint4 *)r.frame; p.unif_h[i] = r.uniform;
     }
-    hipLaunchKernelGGL(gather_requests_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, p.unif_h, (uint4 *)p.frames_d, p.unif_d,
-                       (int)(s->frame_bytes / 16));
-    SHIP(hipGetLastError());
-    if (ga3c_predict(s->ctx, p.frames_d, n, p.unif_d, nullptr, p.val_h, nullptr, p.act_h, s->sp) != GA3C_OK)
-        return sfail(GA3C_EHIP, "ga3c_predict: %s", ga3c_last_error());
+    int rc;
+    if (ga3c::takes_frame_table(s->ctx))
+        rc = ga3c::predict_from_table(s->ctx, (const uint8_t *const *)p.ptrs_h, n, p.unif_h, p.val_h, p.act_h, s->sp);
+    else {
+        if (!p.frames_d) STRY(device(&p.frames_d, (size_t)s->max_pred * s->frame_bytes));      // made when first needed
+        hipLaunchKernelGGL(gather_frames_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, (uint4 *)p.frames_d, (int)(s->frame_bytes / 16));
+        SHIP(hipGetLastError());
+        rc = ga3c_predict(s->ctx, p.frames_d, n, p.unif_h, nullptr, p.val_h, nullptr, p.act_h, s->sp);
+    }
+    if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_predict: %s", ga3c_last_error());
     SHIP(hipEventRecord(p.done, s->sp));
     s->pq.pop(n);
     p.busy = true; p.n = n;
@@ -302,14 +305,21 @@ int issue_train(ga3c_sched *s, int *count) {
     memcpy(t.act_h, s->tq_act.data(), sizeof(int32_t) * B);
     memcpy(t.rew_h, s->tq_rew.data(), sizeof(float) * B);
     memcpy(t.done_h, s->tq_done.data(), B);
-    const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, (uint4 *)t.frames_d, t.act_d, t.seg_d, t.rew_d, t.boot_d,
-                         t.done_d, (int)(s->frame_bytes / 16), n};
-    hipLaunchKernelGGL(gather_experiences_kernel, dim3(B), dim3(256), 0, s->st, ga);
-    SHIP(hipGetLastError());
-    const int rc = equal ? ga3c_train_step(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp,
-                                           nullptr, s->st)
-                         : ga3c_train_step_ragged(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.seg_d, t.boot_d, n, B,
-                                                  &s->cfg.hp, nullptr, s->st);
+    const bool table = ga3c::takes_frame_table(s->ctx);
+    int rc;
+    if (table && equal) {        // every list is read where the host wrote it
+        rc = ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_h, t.rew_h, t.done_h, t.boot_h, nullptr, n, T, B, &s->cfg.hp, s->st);
+    } else {
+        if (!table && !t.frames_d) STRY(device(&t.frames_d, (size_t)s->max_train * s->frame_bytes));
+        const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, table ? nullptr : (uint4 *)t.frames_d, t.act_d, t.seg_d,
+                             t.rew_d, t.boot_d, t.done_d, (int)(s->frame_bytes / 16), n};
+        hipLaunchKernelGGL(gather_experiences_kernel, dim3(B), dim3(256), 0, s->st, ga);
+        SHIP(hipGetLastError());
+        rc = table   ? ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_d, t.rew_d, t.done_d, t.boot_d, t.seg_d, n, 1, B,
+                                              &s->cfg.hp, s->st)
+             : equal ? ga3c_train_step(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp, nullptr, s->st)
+                     : ga3c_train_step_ragged(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.seg_d, t.boot_d, n, B, &s->cfg.hp, nullptr, s->st);
+    }
     if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_train_step: %s", ga3c_last_error());
     SHIP(hipEventRecord(t.done, s->st));
     const int64_t now = s->stats.train_batches;       // updates issued before this one = the version it starts from
@@ -386,7 +396,7 @@ extern "C" int ga3c_sched_destroy(ga3c_sched *s) {
     for (int i = 0; i < RING; ++i) {
         PredSlot &p = s->ps[i];
         if (p.done) (void)hipEventDestroy(p.done);
-        (void)hipHostFree(p.ptrs_h); (void)hipHostFree(p.unif_h); (void)hipFree(p.unif_d); (void)hipFree(p.frames_d);
+        (void)hipHostFree(p.ptrs_h); (void)hipHostFree(p.unif_h); (void)hipFree(p.frames_d);
         (void)hipHostFree(p.act_h); (void)hipHostFree(p.val_h);
         TrainSlot &t = s->ts[i];
         if (t.done) (void)hipEventDestroy(t.done);
