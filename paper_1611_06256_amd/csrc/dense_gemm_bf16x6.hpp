@@ -79,7 +79,7 @@ __device__ __forceinline__ void fetch_tile(const float *__restrict__ X, long ld,
 
 // Split what fetch_tile brought and store it as S[term][k-group][row].
 template <bool ROWMAJOR, int ROWS, int ITEMS, int NT, bool ONE = false>
-__device__ __forceinline__ void stash_tile(u32x4 (&S)[3][4][ROWS + 1], int tid, const float (&r)[ITEMS][8], int rb) {
+__device__ __forceinline__ void stash_tile(u32x4 (*S)[4][ROWS + 1], int tid, const float (&r)[ITEMS][8], int rb) {
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         const int e = tid + it * NT;
@@ -94,18 +94,22 @@ __device__ __forceinline__ void stash_tile(u32x4 (&S)[3][4][ROWS + 1], int tid, 
     }
 }
 
-// ONE: the reduced-precision variant (operands rounded to bfloat16): one term per operand, one MFMA per tile pair.
-template <int TM, int TN, int WM, int WN, bool A_ROWMAJOR, bool B_ROWMAJOR, int EPI, bool ONE>
-__global__ __launch_bounds__(WM *WN * 64, 2) void dense_gemm_bf16x6_kernel(const DenseGemmArgs p) {
+// LDS of one block, in 16-byte units: [term][k-group of 8][row] of both operands, one spare unit per line.
+template <int BM, int BN>
+constexpr int dense_lds_units() { return 3 * 4 * (BM + 1 + BN + 1); }
+
+// One block's work (block id bid of the product's own grid).  ONE: the reduced-precision variant (operands rounded to
+// bfloat16): one term per operand, one MFMA per tile pair.  PF: k-steps in flight from memory.
+template <int TM, int TN, int WM, int WN, bool A_ROWMAJOR, bool B_ROWMAJOR, int EPI, bool ONE, int PF>
+__device__ __forceinline__ void dense_gemm_block(const DenseGemmArgs &p, const int bid, u32x4 *smem) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, BK = 32, NT = WM * WN * 64;
     constexpr bool SWAP = EPI == DG_MASK;            // the input gradient: output and mask are read and written in rows
-    // LDS: [term][k-group of 8][row] in 16-byte units, one spare unit per line
-    __shared__ u32x4 As[3][4][BM + 1];
-    __shared__ u32x4 Bs[3][4][BN + 1];
+    u32x4(*As)[4][BM + 1] = (u32x4(*)[4][BM + 1])smem;
+    u32x4(*Bs)[4][BN + 1] = (u32x4(*)[4][BN + 1])(smem + 3 * 4 * (BM + 1));
     constexpr int A_ITEMS = BM * 4 / NT, B_ITEMS = BN * 4 / NT;      // (row, k-group) items per thread
     static_assert(BM * 4 % NT == 0 && BN * 4 % NT == 0 && A_ITEMS >= 1 && B_ITEMS >= 1, "tile does not fit the block");
 
-    const int xcd = blockIdx.x % DG_XCDS, local = blockIdx.x / DG_XCDS;
+    const int xcd = bid % DG_XCDS, local = bid / DG_XCDS;
     int tm, tn, z;
     if (p.split == DG_SPLIT_Z) {
         const int tiles = p.ntm * p.ntn;
@@ -134,24 +138,29 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void dense_gemm_bf16x6_kernel(const
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    float ra[A_ITEMS][8], rb[B_ITEMS][8];
-    if (kbeg < kend) {
-        fetch_tile<A_ROWMAJOR, BM, A_ITEMS, NT>(p.A, p.lda, m0, p.M, p.K, kbeg, kend, tid, ra);
-        fetch_tile<B_ROWMAJOR, BN, B_ITEMS, NT>(p.B, p.ldb, n0, p.N, p.K, kbeg, kend, tid, rb);
-    }
-    for (int k0 = kbeg; k0 < kend; k0 += BK) {
-        __syncthreads();
-        stash_tile<A_ROWMAJOR, BM, A_ITEMS, NT, ONE>(As, tid, ra, p.rb);
-        stash_tile<B_ROWMAJOR, BN, B_ITEMS, NT, ONE>(Bs, tid, rb, p.rb);
-        __syncthreads();
-        if (k0 + 2 * BK <= kend) {          // a whole group of 32 comes next: nothing to zero
-            constexpr bool PS = A_ROWMAJOR && B_ROWMAJOR;
-            fetch_tile<A_ROWMAJOR, BM, A_ITEMS, NT, false, PS>(p.A, p.lda, m0, p.M, p.K, k0 + BK, kend, tid, ra);
-            fetch_tile<B_ROWMAJOR, BN, B_ITEMS, NT, false, PS>(p.B, p.ldb, n0, p.N, p.K, k0 + BK, kend, tid, rb);
-        } else if (k0 + BK < kend) {
-            fetch_tile<A_ROWMAJOR, BM, A_ITEMS, NT>(p.A, p.lda, m0, p.M, p.K, k0 + BK, kend, tid, ra);
-            fetch_tile<B_ROWMAJOR, BN, B_ITEMS, NT>(p.B, p.ldb, n0, p.N, p.K, k0 + BK, kend, tid, rb);
+    float ra[PF][A_ITEMS][8], rb[PF][B_ITEMS][8];
+    auto fetch = [&](int k0, int set) {
+        constexpr bool PS = A_ROWMAJOR && B_ROWMAJOR;
+        if (k0 + BK <= kend) {              // a whole group of 32: nothing to zero
+            fetch_tile<A_ROWMAJOR, BM, A_ITEMS, NT, false, PS>(p.A, p.lda, m0, p.M, p.K, k0, kend, tid, ra[set]);
+            fetch_tile<B_ROWMAJOR, BN, B_ITEMS, NT, false, PS>(p.B, p.ldb, n0, p.N, p.K, k0, kend, tid, rb[set]);
+        } else if (k0 < kend) {
+            fetch_tile<A_ROWMAJOR, BM, A_ITEMS, NT>(p.A, p.lda, m0, p.M, p.K, k0, kend, tid, ra[set]);
+            fetch_tile<B_ROWMAJOR, BN, B_ITEMS, NT>(p.B, p.ldb, n0, p.N, p.K, k0, kend, tid, rb[set]);
         }
+    };
+#pragma unroll
+    for (int i = 0; i < PF; ++i) fetch(kbeg + i * BK, i);
+    for (int kb0 = kbeg; kb0 < kend; kb0 += PF * BK)
+#pragma unroll
+    for (int st = 0; st < PF; ++st) {
+        const int k0 = kb0 + st * BK;
+        if (PF > 1 && k0 >= kend) break;
+        __syncthreads();
+        stash_tile<A_ROWMAJOR, BM, A_ITEMS, NT, ONE>(As, tid, ra[st], p.rb);
+        stash_tile<B_ROWMAJOR, BN, B_ITEMS, NT, ONE>(Bs, tid, rb[st], p.rb);
+        __syncthreads();
+        fetch(k0 + PF * BK, st);
         Bf16x8Bits a[TM][3], b[TN][3];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -231,21 +240,47 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void dense_gemm_bf16x6_kernel(const
         }
 }
 
-template <int TM, int TN, int WM, int WN, bool A_ROWMAJOR, bool B_ROWMAJOR, int EPI>
-inline hipError_t launch_dense_gemm_bf16x6(DenseGemmArgs p, int split, hipStream_t s) {
-    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
-    if (p.M <= 0 || p.N <= 0) return hipSuccess;
+template <int TM, int TN, int WM, int WN, bool A_ROWMAJOR, bool B_ROWMAJOR, int EPI, bool ONE, int PF>
+__global__ __launch_bounds__(WM *WN * 64, 2) void dense_gemm_bf16x6_kernel(const DenseGemmArgs p) {
+    __shared__ u32x4 smem[dense_lds_units<16 * TM * WM, 16 * TN * WN>()];
+    dense_gemm_block<TM, TN, WM, WN, A_ROWMAJOR, B_ROWMAJOR, EPI, ONE, PF>(p, blockIdx.x, smem);
+}
+
+// Tiles of a product and the blocks of its grid.
+inline int dense_place(DenseGemmArgs &p, int BM, int BN, int split) {
     p.ntm = (p.M + BM - 1) / BM;
     p.ntn = (p.N + BN - 1) / BN;
     p.split = split;
     if (split == DG_SPLIT_Z) p.per_xcd = ((p.nz + DG_XCDS - 1) / DG_XCDS) * p.ntm * p.ntn;
     else p.per_xcd = ((p.ntn + DG_XCDS - 1) / DG_XCDS) * p.ntm * p.nz;
-    if (p.rb)
-        ga3c::launch((dense_gemm_bf16x6_kernel<TM, TN, WM, WN, A_ROWMAJOR, B_ROWMAJOR, EPI, true>),
-                           dim3(DG_XCDS * p.per_xcd), dim3(WM * WN * 64), 0, s, p);
-    else
-        ga3c::launch((dense_gemm_bf16x6_kernel<TM, TN, WM, WN, A_ROWMAJOR, B_ROWMAJOR, EPI, false>),
-                           dim3(DG_XCDS * p.per_xcd), dim3(WM * WN * 64), 0, s, p);
+    return DG_XCDS * p.per_xcd;
+}
+
+template <int TM, int TN, int WM, int WN, bool A_ROWMAJOR, bool B_ROWMAJOR, int EPI, int PF = 1>
+inline hipError_t launch_dense_gemm_bf16x6(DenseGemmArgs p, int split, hipStream_t s) {
+    if (p.M <= 0 || p.N <= 0) return hipSuccess;
+    const dim3 grid(dense_place(p, 16 * TM * WM, 16 * TN * WN, split)), block(WM * WN * 64);
+    if (p.rb) ga3c::launch((dense_gemm_bf16x6_kernel<TM, TN, WM, WN, A_ROWMAJOR, B_ROWMAJOR, EPI, true, PF>), grid, block, 0, s, p);
+    else ga3c::launch((dense_gemm_bf16x6_kernel<TM, TN, WM, WN, A_ROWMAJOR, B_ROWMAJOR, EPI, false, PF>), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+// The fc layer's two gradients in one launch: they share their inputs and neither needs the other.  The input gradient's
+// blocks come first (the next kernel waits for them), the weight gradient's fill the compute units that those leave idle: all
+// of them at small batches, the last round of blocks at large ones.  TMD: the input gradient's tile is 32 TMD x 64.
+template <int TMD, bool ONE, int PF>
+__global__ __launch_bounds__(256, 2) void dense_fc_grads_kernel(const DenseGemmArgs dx, const DenseGemmArgs dw) {
+    __shared__ u32x4 smem[dense_lds_units<32 * (TMD > 2 ? TMD : 2), 64>()];
+    const int nx = DG_XCDS * dx.per_xcd;
+    if ((int)blockIdx.x < nx) dense_gemm_block<TMD, 2, 2, 2, false, true, DG_MASK, ONE, PF>(dx, blockIdx.x, smem);
+    else dense_gemm_block<2, 2, 2, 2, true, true, DG_PARTIAL, ONE, 1>(dw, (int)blockIdx.x - nx, smem);
+}
+
+template <int TMD, int PF>
+inline hipError_t launch_dense_fc_grads(DenseGemmArgs dx, DenseGemmArgs dw, hipStream_t s) {
+    const int nx = dense_place(dx, 32 * TMD, 64, DG_SPLIT_N), nw = dense_place(dw, 64, 64, DG_SPLIT_Z);
+    if (dx.rb) ga3c::launch((dense_fc_grads_kernel<TMD, true, PF>), dim3(nx + nw), dim3(256), 0, s, dx, dw);
+    else ga3c::launch((dense_fc_grads_kernel<TMD, false, PF>), dim3(nx + nw), dim3(256), 0, s, dx, dw);
     return hipGetLastError();
 }
 

@@ -108,7 +108,7 @@ struct Work {            // activations of one call; predict and train own one e
 namespace {
 // Optional per-stage timing: the execution times of the kernels of each stage (an event pair per launch).
 struct ProfStage { const char *name; long calls; double ms, flop, bytes; };
-struct ProfRec { int stage; hipEvent_t a, b; };
+struct ProfRec { int stage, stage2; hipEvent_t a, b; };      // stage2 >= 0: the launch does the work of two stages
 struct Profiler {
     bool on = false;
     std::vector<ProfStage> stages;
@@ -1376,19 +1376,27 @@ int mark_readers(ga3c_ctx *c, int i, hipStream_t s) {
 #define TRY(expr) do { int rc_ = (expr); if (rc_ != GA3C_OK) return rc_; } while (0)
 
 // While one of these is alive and profiling is on, every kernel launched by this host thread carries an event pair
-// of its own (launch.hpp), booked to the stage: the stage's time is the sum of its kernels' execution times.  Costs
-// one branch when profiling is off.
+// of its own (launch.hpp), booked to the stage: the stage's time is the sum of its kernels' execution times.  A launch
+// that does the work of two stages counts for both, its time in the proportion of their operations.  Costs one branch
+// when profiling is off.
 struct ProfScope final : ga3c::LaunchTimer {
-    Profiler *p; int sid;
-    ProfScope(ga3c_ctx *c, hipStream_t, const char *name, double flop, double bytes) : p(c->prof), sid(-1) {
+    Profiler *p; int sid, sid2;
+    ProfScope(ga3c_ctx *c, hipStream_t, const char *name, double flop, double bytes, const char *name2 = nullptr, double flop2 = 0, double bytes2 = 0)
+        : p(c->prof), sid(-1), sid2(-1) {
         if (!p || !p->on) { p = nullptr; return; }
-        for (size_t i = 0; i < p->stages.size(); ++i) if (!strcmp(p->stages[i].name, name)) { sid = (int)i; break; }
-        if (sid < 0) { p->stages.push_back({name, 0, 0.0, 0.0, 0.0}); sid = (int)p->stages.size() - 1; }
-        p->stages[sid].calls += 1; p->stages[sid].flop += flop; p->stages[sid].bytes += bytes;
+        sid = book(name, flop, bytes);
+        if (name2) sid2 = book(name2, flop2, bytes2);
         ga3c::launch_timer = this;
     }
+    int book(const char *name, double flop, double bytes) {
+        size_t i = 0;
+        while (i < p->stages.size() && strcmp(p->stages[i].name, name)) ++i;
+        if (i == p->stages.size()) p->stages.push_back({name, 0, 0.0, 0.0, 0.0});
+        p->stages[i].calls += 1; p->stages[i].flop += flop; p->stages[i].bytes += bytes;
+        return (int)i;
+    }
     bool next_events(hipEvent_t *start, hipEvent_t *stop) override {
-        ProfRec r; r.stage = sid; r.a = r.b = nullptr;
+        ProfRec r; r.stage = sid; r.stage2 = sid2; r.a = r.b = nullptr;
         for (hipEvent_t *e : {&r.a, &r.b}) {
             if (!p->pool.empty()) { *e = p->pool.back(); p->pool.pop_back(); }
             else if (hipEventCreate(e) != hipSuccess) { *e = nullptr; }
@@ -1406,6 +1414,7 @@ struct ProfScope final : ga3c::LaunchTimer {
     ProfScope &operator=(const ProfScope &) = delete;
 };
 #define STAGE(name, flop, bytes) ProfScope prof_scope_(c, s, name, (double)(flop), (double)(bytes))
+#define STAGE2(name, flop, bytes, name2, flop2, bytes2) ProfScope prof_scope_(c, s, name, (double)(flop), (double)(bytes), name2, (double)(flop2), (double)(bytes2))
 
 const char *const CONV_FWD[GA3C_MAX_CONV] = {"conv1_fwd", "conv2_fwd", "conv3_fwd", "conv4_fwd"};
 const char *const CONV_WGRAD[GA3C_MAX_CONV] = {"conv1_wgrad", "conv2_wgrad", "conv3_wgrad", "conv4_wgrad"};
@@ -2118,10 +2127,14 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         p.A = c->dh; p.lda = F; p.B = xfc; p.ldb = c->flat;
         p.C = region((size_t)nz * p.M * p.N); p.ldc = 0; p.aux = nullptr;
         if (!p.C) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc wgrad)");
-        {
-            STAGE("fc_wgrad", 2.0 * B * F * c->flat, 0);
-            HIP_TRY((launch_dense_gemm_bf16x6<2, 2, 2, 2, true, true, DG_PARTIAL>(p, DG_SPLIT_Z, s)));
-        }
+        // fc input gradient, masked by the ReLU of the last conv layer
+        DenseGemmArgs q{}; q.rb = c->rb;
+        q.M = B; q.N = c->flat; q.K = F; q.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK; q.nz = 1;
+        q.A = c->dh; q.lda = F; q.B = wfc; q.ldb = c->flat;
+        q.C = c->dact[c->nconv - 1]; q.ldc = c->flat; q.aux = xfc;
+        STAGE2("fc_wgrad", 2.0 * B * F * c->flat, 0, "fc_dgrad", 2.0 * B * F * c->flat, 0);
+        if (B <= 640) HIP_TRY((launch_dense_fc_grads<2, 2>(q, p, s)));
+        else HIP_TRY((launch_dense_fc_grads<4, 1>(q, p, s)));
         add_seg(p.C, nz, p.M, p.N, 0, p.M, c->grad + c->off[nb], nullptr, 0);
         add_seg(c->colpart, cdiv(B, HD_FRAMES), 1, F, 0, 1, c->grad + c->off[nb + 1], nullptr, 0);
     } else {   // general shapes: one more column of ones yields the bias gradient
@@ -2139,22 +2152,14 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         }
         add_seg(p.C, nz, p.M, p.N, 0, p.M, c->grad + c->off[nb], c->grad + c->off[nb + 1], 1);
     }
-    {   // fc input gradient, masked by the ReLU of the last conv layer
+    if (!fc_dense) {   // fc input gradient, masked by the ReLU of the last conv layer
         STAGE("fc_dgrad", 2.0 * B * F * c->flat, 0);
-        if (fc_dense) {
-            DenseGemmArgs p{}; p.rb = c->rb;
-            p.M = B; p.N = c->flat; p.K = F; p.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK; p.nz = 1;
-            p.A = c->dh; p.lda = F; p.B = wfc; p.ldb = c->flat;
-            p.C = c->dact[c->nconv - 1]; p.ldc = c->flat; p.aux = xfc;
-            HIP_TRY((launch_dense_gemm_bf16x6<4, 2, 2, 2, false, true, DG_MASK>(p, DG_SPLIT_N, s)));
-        } else {
-            GemmP<EPI_MASK, false> p; p.rb = c->rb;
-            p.M = B; p.N = c->flat; p.K = F; p.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK;
-            p.A = c->dh; p.sAm = F; p.sAk = 1;
-            p.B = wfc; p.sBn = 1; p.sBk = c->flat;
-            p.C = c->dact[c->nconv - 1]; p.ldc = c->flat; p.aux = xfc;
-            HIP_TRY((launch_gemm<2, 2, 2, 2, false, true>(p, 1, s)));
-        }
+        GemmP<EPI_MASK, false> p; p.rb = c->rb;
+        p.M = B; p.N = c->flat; p.K = F; p.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK;
+        p.A = c->dh; p.sAm = F; p.sAk = 1;
+        p.B = wfc; p.sBn = 1; p.sBk = c->flat;
+        p.C = c->dact[c->nconv - 1]; p.ldc = c->flat; p.aux = xfc;
+        HIP_TRY((launch_gemm<2, 2, 2, 2, false, true>(p, 1, s)));
     }
     for (int l = c->nconv - 1; l >= 0; --l) {
         const ConvGeom &g = c->geom[l];
@@ -2393,7 +2398,11 @@ extern "C" int ga3c_profile_read(ga3c_ctx *c, char *buf, size_t cap) {
         HIP_TRY(hipEventSynchronize(r.b));
         float ms = 0.f;
         HIP_TRY(hipEventElapsedTime(&ms, r.a, r.b));
-        p->stages[r.stage].ms += ms;
+        const double f1 = p->stages[r.stage].flop / p->stages[r.stage].calls;
+        const double f2 = r.stage2 >= 0 ? p->stages[r.stage2].flop / p->stages[r.stage2].calls : 0.0;
+        const double share = r.stage2 >= 0 && f1 + f2 > 0 ? f1 / (f1 + f2) : 1.0;
+        p->stages[r.stage].ms += share * ms;
+        if (r.stage2 >= 0) p->stages[r.stage2].ms += (1.0 - share) * ms;
         p->pool.push_back(r.a); p->pool.push_back(r.b);
     }
     p->recs.clear();
