@@ -231,13 +231,20 @@ __device__ __forceinline__ void copy_to_lds(float *dst, const float *__restrict_
 __host__ __device__ inline int heads_f4(int F) { return (F + 3) / 4 * 4; }
 __host__ __device__ inline int heads_lds_floats(int F, int A) { return 4 * heads_f4(F) + (A + 1) * (heads_f4(F) + 4 + 12); }
 
+// The columns F .. WP - 1 (at most seven) of `rows` rows of the heads' weights in LDS.
+template <int NT>
+__device__ __forceinline__ void heads_zero_padding(float *wsh, const int t, int F, int WP, int rows) {
+    for (int r = t >> 3; r < rows; r += NT / 8)
+        if ((t & 7) < WP - F) wsh[r * WP + F + (t & 7)] = 0.f;
+}
+
 // Both weight matrices into the block's LDS in the layout heads_fwd_body reads, by threads t = 0 .. NT-1.
 template <int NT>
 __device__ __forceinline__ void heads_stage_weights(float *hs, const int t, int F, int A, const float *__restrict__ Wp,
                                                     const float *__restrict__ Wv, int rb) {
     const int F4 = heads_f4(F), WP = F4 + 4;
     float *wsh = hs + 4 * F4;
-    for (int e = t; e < (A + 1) * (WP - F); e += NT) wsh[(e / (WP - F)) * WP + F + e % (WP - F)] = 0.f;
+    heads_zero_padding<NT>(wsh, t, F, WP, A + 1);
     const int nw = (A + 1) * F;
     for (int e0 = 0; e0 < nw; e0 += 24 * NT) {
         float wv[24];
@@ -269,7 +276,7 @@ template <int NT>
 __device__ __forceinline__ void heads_store_weights(float *hs, const float (&wv)[24], const int t, int F, int A, int rb) {
     const int F4 = heads_f4(F), WP = F4 + 4;
     float *wsh = hs + 4 * F4;
-    for (int e = t; e < (A + 1) * (WP - F); e += NT) wsh[(e / (WP - F)) * WP + F + e % (WP - F)] = 0.f;
+    heads_zero_padding<NT>(wsh, t, F, WP, A + 1);
     const int nw = (A + 1) * F;
 #pragma unroll
     for (int j = 0; j < 24; ++j) {
@@ -282,52 +289,80 @@ __device__ __forceinline__ void heads_store_weights(float *hs, const float (&wv)
 // hundred cycles issuing each one, whatever its width): the split-k partial sums of the fc layer for NF frames are
 // added up in chunk order, bias and ReLU follow, the result goes to h and (rounded if rb) to hs [NF][F4]; the heads'
 // weights go to wsh [A+1][WP] (the value head's row with 4-byte loads: it follows the policy biases in the parameter
-// vector and is not aligned).  Needs F % 4 == 0 and 16-byte aligned pointers (heads_vec4_ok).  Every load of a round
-// is issued before the first one is used.
+// vector and is not aligned).  Needs F % 4 == 0 and 16-byte aligned pointers (heads_vec4_ok).
+// What it takes is rounds of latency, so the weights, the biases and the partial sums of IP outputs per thread, CH chunks
+// each, are all requested before the first of them is used: one round where the chunks fit CH and the outputs IP (training
+// on 40 frames, 40 chunks: the block's loads 7.5 us when every output and every eight chunks were a round of their own).
 __device__ __forceinline__ bool heads_vec4_ok(int F, const void *ws, const void *fcb, const void *h, const void *Wp) {
     return F % 4 == 0 && (((uintptr_t)ws | (uintptr_t)fcb | (uintptr_t)h | (uintptr_t)Wp) & 15) == 0;
 }
-template <int NT, int NF, int CH>
+template <int NT, int NF, int CH, int IP>
 __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int tid, const int b0, const int nf,
                                                 const float *__restrict__ ws, int nz, const float *__restrict__ fcb,
                                                 float *__restrict__ h, int B, int F, int F4, int WP, int A,
-                                                const float *__restrict__ Wp, const float *__restrict__ Wv, int rb) {
-    const int FQ = F >> 2, nwq = A * FQ;
+                                                const float *__restrict__ Wp, const float *__restrict__ Wv, int rb, const FastDiv dFQ) {
+    constexpr int WQ = 8, WVQ = 2;
+    const int FQ = F >> 2, nwq = A * FQ, nit = NF * FQ;
     const size_t stride4 = (size_t)B * FQ;
-    for (int q0 = 0; q0 < nwq || q0 == 0; q0 += 8 * NT) {
-        float4 wv4[8];
+    float4 wv4[WQ];
+    float wv[WVQ];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) wv4[j] = ((const float4 *)Wp)[min(q0 + j * NT + tid, nwq - 1)];
-        if (q0 == 0) {
-            for (int k = tid; k < F; k += NT) wsh[A * WP + k] = rb ? bf16_rne(Wv[k]) : Wv[k];
-            for (int it = tid; it < NF * FQ; it += NT) {
-                const int fb = it / FQ, oq = it % FQ;
-                const float4 bias = ((const float4 *)fcb)[oq];
-                const float4 *src = (const float4 *)(ws + (size_t)(b0 + min(fb, nf - 1)) * F) + oq;
-                float4 acc = float4{0.f, 0.f, 0.f, 0.f};
-                for (int z = 0; z < nz; z += CH) {
-                    float4 v[CH];
+    for (int j = 0; j < WQ; ++j) wv4[j] = ((const float4 *)Wp)[min(j * NT + tid, nwq - 1)];
 #pragma unroll
-                    for (int i = 0; i < CH; ++i) v[i] = src[(size_t)min(z + i, nz - 1) * stride4];
+    for (int j = 0; j < WVQ; ++j) wv[j] = Wv[min(j * NT + tid, F - 1)];
+    for (int it0 = tid; it0 < nit; it0 += IP * NT) {
+        // output it of the block is vector b0 * FQ + it of a chunk's sums
+        const float4 *src = (const float4 *)ws + (size_t)b0 * FQ;
+        float4 bias[IP], acc[IP];
+        uint32_t off[IP];
 #pragma unroll
-                    for (int i = 0; i < CH; ++i) {
-                        const bool in = z + i < nz;
-                        acc.x += in ? v[i].x : 0.f; acc.y += in ? v[i].y : 0.f;
-                        acc.z += in ? v[i].z : 0.f; acc.w += in ? v[i].w : 0.f;
-                    }
+        for (int p = 0; p < IP; ++p) {
+            off[p] = (uint32_t)min(it0 + p * NT, nf * FQ - 1);
+            uint32_t fb, oq;
+            dFQ.divmod(off[p], fb, oq);
+            bias[p] = ((const float4 *)fcb)[oq];
+            acc[p] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int z = 0; z < nz; z += CH) {
+            float4 v[IP][CH];
+#pragma unroll
+            for (int p = 0; p < IP; ++p)
+#pragma unroll
+                for (int i = 0; i < CH; ++i) v[p][i] = (src + (size_t)min(z + i, nz - 1) * stride4)[off[p]];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < IP; ++p)
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    const bool in = z + i < nz;
+                    acc[p].x += in ? v[p][i].x : 0.f; acc[p].y += in ? v[p][i].y : 0.f;
+                    acc[p].z += in ? v[p][i].z : 0.f; acc[p].w += in ? v[p][i].w : 0.f;
                 }
-                float4 r = float4{acc.x + bias.x, acc.y + bias.y, acc.z + bias.z, acc.w + bias.w};
-                r.x = r.x > 0.f ? r.x : 0.f; r.y = r.y > 0.f ? r.y : 0.f; r.z = r.z > 0.f ? r.z : 0.f; r.w = r.w > 0.f ? r.w : 0.f;
-                if (fb < nf) *(float4 *)(h + (size_t)(b0 + fb) * F + 4 * oq) = r;
-                *(float4 *)(hs + fb * F4 + 4 * oq) = rb ? bf16_rne(r) : r;
-            }
         }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int q = q0 + j * NT + tid;
-            if (q < nwq) *(float4 *)(wsh + (q / FQ) * WP + 4 * (q % FQ)) = rb ? bf16_rne(wv4[j]) : wv4[j];
+        for (int p = 0; p < IP; ++p) {
+            const int it = it0 + p * NT;
+            if (it >= nit) break;
+            float4 r = float4{acc[p].x + bias[p].x, acc[p].y + bias[p].y, acc[p].z + bias[p].z, acc[p].w + bias[p].w};
+            r.x = r.x > 0.f ? r.x : 0.f; r.y = r.y > 0.f ? r.y : 0.f; r.z = r.z > 0.f ? r.z : 0.f; r.w = r.w > 0.f ? r.w : 0.f;
+            if (it < nf * FQ) ((float4 *)h + (size_t)b0 * FQ)[it] = r;
+            ((float4 *)hs)[it] = rb ? bf16_rne(r) : r;            // F4 == F here
         }
     }
+    for (int q0 = 0;; q0 += WQ * NT) {
+#pragma unroll
+        for (int j = 0; j < WQ; ++j) {
+            const int q = q0 + j * NT + tid;
+            if (q < nwq) *(float4 *)(wsh + 4 * q + (WP - F) * (int)dFQ.div((uint32_t)q)) = rb ? bf16_rne(wv4[j]) : wv4[j];
+        }
+        if (q0 + WQ * NT >= nwq) break;
+#pragma unroll
+        for (int j = 0; j < WQ; ++j) wv4[j] = ((const float4 *)Wp)[min(q0 + (WQ + j) * NT + tid, nwq - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < WVQ; ++j)
+        if (j * NT + tid < F) wsh[A * WP + j * NT + tid] = rb ? bf16_rne(wv[j]) : wv[j];
+    for (int k = WVQ * NT + tid; k < F; k += NT) wsh[A * WP + k] = rb ? bf16_rne(Wv[k]) : Wv[k];
 }
 
 // The body, for a block of NT threads (all of them must call it) that works on frames b0 .. min(b0 + 4, B) - 1;
@@ -339,22 +374,28 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
                                                const float *__restrict__ Wp, const float *__restrict__ bp,
                                                const float *__restrict__ Wv, const float *__restrict__ bv, float *zv,
                                                float *logits, float *values, float *probs, const float *uniforms,
-                                               int32_t *actions, int rb) {
-    // rb: the products of the heads take h and the weights rounded to bfloat16 (h itself is stored as computed)
+                                               int32_t *actions, int rb, const FastDiv dFQ, const FastDiv dA1) {
+    // dFQ, dA1: divisions by F / 4 and A + 1 (a division by a run-time number costs tens of instructions, and these kernels are
+    // short).  rb: the products of the heads take h and the weights rounded to bfloat16 (h itself is stored as computed)
     const int F4 = heads_f4(F), WP = F4 + 4;                        // hs: [4][F4], weights [A+1][F4+4], partial dots
     float *wsh = hs + 4 * F4;
     const int nf = min(4, B - b0);
     const int nout = nf * (A + 1);
     // thread tid < nout finishes output a of frame fb
-    const int ofb = min(tid / (A + 1), nf - 1), oa = tid % (A + 1);
+    uint32_t tq, tr;
+    dA1.divmod((uint32_t)tid, tq, tr);
+    const int ofb = min((int)tq, nf - 1), oa = (int)tr;
     const float obias = oa < A ? bp[oa] : bv[0];
     // padding columns of the LDS rows stay zero
     for (int e = tid; e < 4 * (F4 - F); e += NT) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
     if (!WSTAGED)
-        for (int e = tid; e < (A + 1) * (WP - F); e += NT) wsh[(e / (WP - F)) * WP + F + e % (WP - F)] = 0.f;
+        heads_zero_padding<NT>(wsh, tid, F, WP, A + 1);
     const int nw = (A + 1) * F;                 // Wp [A][F] and Wv [F] are adjacent in LDS, not in global memory
     const bool vec4 = !WSTAGED && ws && heads_vec4_ok(F, ws, fcb, h, Wp);
-    if (vec4) heads_load_vec4<NT, 4, 16>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb);
+    if (vec4) {
+        if (nz <= 8) heads_load_vec4<NT, 4, 8, 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+        else heads_load_vec4<NT, 4, 16, 1>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+    }
     for (int e0 = 0; !vec4 && ((!WSTAGED && e0 < nw) || e0 == 0); e0 += 24 * NT) {
         float wv[24];
         if (!WSTAGED) {
@@ -417,12 +458,12 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
     // thread (frame, output, part of k) adds its share; KP shares make one output (three where the block has
     // threads for them, fewer when there are many actions).
     float *zs = wsh + (A + 1) * WP;                  // [4][A+1][3] partial dots, then [4][A+1] values
-    const int KP = max(1, min(3, 256 / (4 * (A + 1))));      // the first 256 threads finish the outputs
+    const int KP = max(1, min(3, (int)dA1.div(64)));      // the first 256 threads finish the outputs
     if (tid < KP * nout) {
-        const int kp = tid / nout, r = tid % nout;
-        const int fb = r / (A + 1), a = r % (A + 1);
+        // thread tid: output a of frame fb, part kp, in this order of significance: tid = (kp nf + fb) (A + 1) + a
+        const int a = oa, kp = nf == 4 ? (int)(tq >> 2) : (int)tq / nf, fb = (int)tq - kp * nf;
         const int nk = F4 / 4;
-        const int klo = (nk * kp) / KP, khi = (nk * (kp + 1)) / KP;
+        const int klo = KP == 3 ? (nk * kp) / 3 : (nk * kp) / KP, khi = KP == 3 ? (nk * (kp + 1)) / 3 : (nk * (kp + 1)) / KP;
         const float4 *hb = (const float4 *)(hs + fb * F4), *wr = (const float4 *)(wsh + a * WP);
         float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
 #pragma unroll 4
@@ -488,10 +529,10 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict_
                                                         const float *__restrict__ bp, const float *__restrict__ Wv,
                                                         const float *__restrict__ bv, float *zv, float *logits,
                                                         float *values, float *probs, const float *uniforms,
-                                                        int32_t *actions, int rb) {
+                                                        int32_t *actions, int rb, const FastDiv dFQ, const FastDiv dA1) {
     extern __shared__ __attribute__((aligned(16))) float heads_smem[];
     heads_fwd_body<256, false, false>(heads_smem, threadIdx.x, blockIdx.x * 4, ws, nz, fcb, h, B, F, A, Wp, bp, Wv, bv, zv, logits,
-                               values, probs, uniforms, actions, rb);
+                               values, probs, uniforms, actions, rb, dFQ, dA1);
 }
 
 // The whole forward pass of the small network (Sec. 3.2) for a handful of frames in ONE launch, for the latency of a
@@ -516,7 +557,7 @@ constexpr int SP_WJ = (SP_FLAT / 4 + 63) / 64;             // 16-byte vectors of
 
 template <bool ONE, int SLICES, bool TABLE>
 __global__ __launch_bounds__(512, 1) void predict_small_kernel(
-    const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table, const u32x4 *__restrict__ frag, const float *__restrict__ b1,
+    const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table, const FastDiv dA1, const u32x4 *__restrict__ frag, const float *__restrict__ b1,
     const float *__restrict__ b2, const float *__restrict__ Wfc, const float *__restrict__ fcb, float *__restrict__ h,
     int *__restrict__ ticket, int A, const float *__restrict__ Wp, const float *__restrict__ bp,
     const float *__restrict__ Wv, const float *__restrict__ bv, float *logits, float *values, float *probs,
@@ -639,7 +680,7 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
     __syncthreads();
     if (!last) return;
     heads_fwd_body<512, true, true>((float *)(sp_smem + SP_HEADS_OFF), tid, frame, nullptr, 0, fcb, h, frame + 1, SP_FC, A, Wp, bp, Wv, bv, nullptr,
-                              logits, values, probs, uniforms, actions, rb);
+                              logits, values, probs, uniforms, actions, rb, dA1 /* not used */, dA1);
 }
 
 // n-step return (text after Eq. 1) of frame i when the segments have unequal
@@ -836,10 +877,11 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     const int32_t *__restrict__ actions, const float *__restrict__ rewards, const uint8_t *__restrict__ dones,
     const float *__restrict__ bootstrap, const int32_t *__restrict__ seg_start, int N, int T, float gamma, float beta,
     float cv, float eps, float *__restrict__ h, float *__restrict__ zv, float *__restrict__ R, float *__restrict__ dzv,
-    float *__restrict__ dh, float *__restrict__ colpart, float *__restrict__ wpart, float *__restrict__ losspart, int rb) {
+    float *__restrict__ dh, float *__restrict__ colpart, float *__restrict__ wpart, float *__restrict__ losspart, int rb,
+    const FastDiv dFQ, const FastDiv dA1, const FastDiv dKP, const FastDiv dT) {
     extern __shared__ __attribute__((aligned(16))) float sm[];
     constexpr int NF = HD_FRAMES;
-    const int F4 = heads_f4(F), WP = F4 + 4, A1 = A + 1, KP = heads_train_kparts(F, A);
+    const int F4 = heads_f4(F), WP = F4 + 4, A1 = A + 1, KP = (int)dKP.d;
     const int ZR = heads_f4(A1);             // row pitch of the per-(frame, output) arrays: rows start on 16 bytes
     float *hs = sm;                          // [NF][F4]   fc output of my frames (rounded if rb)
     float *wsh = hs + NF * F4;               // [A1][WP]   head weights (rounded if rb)
@@ -856,22 +898,27 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     const int nf = min(NF, B - b0);
 
     // ---- everything from global memory is requested first
-    const int n0 = b0 / T, n1 = (b0 + nf - 1) / T;          // agents of my frames
+    const int n0 = (int)dT.div((uint32_t)b0), n1 = (int)dT.div((uint32_t)(b0 + nf - 1));      // agents of my frames
     const int nrw = (n1 - n0 + 1) * T;
     const bool rw_lds = !seg_start && nrw <= 256;      // segments of unequal length read their rewards from global memory
     float my_rw = 0.f, my_dn = 0.f;
     if (rw_lds && tid < nrw) { my_rw = rewards[(size_t)n0 * T + tid]; my_dn = dones[(size_t)n0 * T + tid] ? 0.f : 1.f; }
-    const int ofb = min(tid / A1, nf - 1), oa = tid % A1;   // thread tid < nf*A1 owns output oa of frame ofb
+    uint32_t tq, tr;
+    dA1.divmod((uint32_t)tid, tq, tr);
+    const int ofb = min((int)tq, nf - 1), oa = (int)tr;     // thread tid < nf*A1 owns output oa of frame ofb
     const bool mine = tid < nf * A1;
     const int ob = b0 + ofb;
     const float obias = oa < A ? bp[oa] : bv[0];
     const int oact = actions[ob];
-    const float oboot = bootstrap && !seg_start ? bootstrap[ob / T] : 0.f;
+    const float oboot = bootstrap && !seg_start ? bootstrap[dT.div((uint32_t)ob)] : 0.f;
     for (int e = tid; e < NF * (F4 - F); e += 256) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
-    for (int e = tid; e < A1 * (WP - F); e += 256) wsh[(e / (WP - F)) * WP + F + e % (WP - F)] = 0.f;
+    heads_zero_padding<256>(wsh, tid, F, WP, A1);
     const int nw = A1 * F;
     const bool vec4 = heads_vec4_ok(F, ws, fcb, h, Wp);
-    if (vec4) heads_load_vec4<256, NF, 8>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb);
+    if (vec4) {
+        if (nz <= 8) heads_load_vec4<256, NF, 8, 4>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+        else heads_load_vec4<256, NF, 16, 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+    }
     for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * 256) {
         float wv[24];
 #pragma unroll
@@ -919,10 +966,10 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
 
     // ---- heads: thread (action a, part kp of k) for all frames, then the parts are added in order
     {
-        const int a = tid % A1, kp = tid / A1;
+        const int a = oa, kp = (int)tq;
         if (kp < KP) {
             const int nk = F4 / 4;
-            const int klo = (nk * kp) / KP, khi = (nk * (kp + 1)) / KP;
+            const int klo = (int)dKP.div((uint32_t)(nk * kp)), khi = (int)dKP.div((uint32_t)(nk * (kp + 1)));
             const float4 *wr = (const float4 *)(wsh + a * WP);
             float s[NF];
 #pragma unroll
@@ -951,7 +998,7 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     // ---- n-step return of my frame (threads with oa == A: one per frame)
     float Rt = 0.f;
     if (mine && oa == A) {
-        const int n = ob / T, t = ob % T;
+        const int n = (int)dT.div((uint32_t)ob), t = ob - n * T;
         float next = oboot;
         if (seg_start) {
             next = ragged_return(rewards, dones, seg_start, bootstrap, N, B, ob, gamma);
@@ -1035,7 +1082,7 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
         dzv[(size_t)ob * A1 + oa] = dzo;
     }
     // the gradients go to zt[output][frame] (zero for frames the block does not have) for the backward pass
-    if (tid < NF * A1) zt[oa * NF + tid / A1] = mine ? (rb ? bf16_rne(dzo) : dzo) : 0.f;
+    if (tid < NF * A1) zt[oa * NF + (int)tq] = mine ? (rb ? bf16_rne(dzo) : dzo) : 0.f;
     // loss sums of the block, frames in order (threads oa == A hold them)
     if (mine && oa == A) { rw[ofb] = s_pl; rw[NF + ofb] = s_vl; rw[2 * NF + ofb] = s_en; }
     __syncthreads();
@@ -1351,6 +1398,13 @@ __global__ __launch_bounds__(256) void fill_kernel(float *__restrict__ dst, size
     if (i < n) dst[i] = v;
 }
 
+// dst = src, n floats; n4 of the 16-byte vectors first (0 where the two are not aligned alike).
+__global__ __launch_bounds__(256) void copy_kernel(float *__restrict__ dst, const float *__restrict__ src, size_t n, size_t n4) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, stride = (size_t)gridDim.x * 256;
+    for (size_t k = i; k < n4; k += stride) ((float4 *)dst)[k] = ((const float4 *)src)[k];
+    for (size_t k = 4 * n4 + i; k < n; k += stride) dst[k] = src[k];
+}
+
 // ------------------------------------------------------------ host helpers --
 
 // Event fences between the calls of a context.  A wait is skipped when the
@@ -1567,7 +1621,7 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         const dim3 grid(B * slices), block(512);
 #define GA3C_SP_LAUNCH(ONE_, SL_) do { if (table) GA3C_SP_LAUNCH1(ONE_, SL_, true); else GA3C_SP_LAUNCH1(ONE_, SL_, false); } while (0)
 #define GA3C_SP_LAUNCH1(ONE_, SL_, TABLE_)                                                                                     \
-    ga3c::launch((predict_small_kernel<ONE_, SL_, TABLE_>), grid, block, C12_LDS_BYTES, s, frames, table, c->cfrag[which],             \
+    ga3c::launch((predict_small_kernel<ONE_, SL_, TABLE_>), grid, block, C12_LDS_BYTES, s, frames, table, FastDiv(c->A + 1), c->cfrag[which],             \
                        th + c->off[1], th + c->off[3], th + c->off[nb], th + c->off[nb + 1], w.h, c->ticket, c->A,            \
                        th + c->off[nb + 2], th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5], logits, values,    \
                        probs, uniforms, actions, 1.f / 255.f, c->rb)
@@ -1689,7 +1743,7 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     ga3c::launch(heads_fwd_kernel, dim3(cdiv(B, 4)), dim3(256), hf_lds, s, fc_ws, fc_nz,
                        th + c->off[nb + 1], w.h, B, c->F, c->A, th + c->off[nb + 2],
                        th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5],
-                       keep_zv ? w.zv : nullptr, logits, values, probs, uniforms, actions, c->rb);
+                       keep_zv ? w.zv : nullptr, logits, values, probs, uniforms, actions, c->rb, FastDiv(std::max(1, c->F / 4)), FastDiv(c->A + 1));
     HIP_TRY(hipGetLastError());
     return GA3C_OK;
 }
@@ -1972,7 +2026,9 @@ extern "C" int ga3c_params_get(ga3c_ctx *c, int which, float *dst, size_t n, voi
     float *src = select_buffer(c, which);
     if (!src || n != c->P) return fail(GA3C_EINVAL, "ga3c_params_get: which must be 0..2 and n the parameter count");
     TRY(wait_ready(c, c->cur, (hipStream_t)stream));
-    HIP_TRY(hipMemcpyAsync(dst, src, sizeof(float) * n, hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    const size_t n4 = is_aligned16(dst) && is_aligned16(src) ? n / 4 : 0;
+    ga3c::launch(copy_kernel, dim3(std::min(blocks_for(n4 ? n4 : n), 4096u)), dim3(256), 0, (hipStream_t)stream, dst, (const float *)src, n, n4);
+    HIP_TRY(hipGetLastError());
     return GA3C_OK;
 }
 
@@ -2080,7 +2136,8 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         STAGE("heads_train", 6.0 * B * (A + 1) * F, 4.0 * (w.fc_nz + 1) * B * F);
         ga3c::launch(heads_train_kernel, dim3(nblk), dim3(256), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
                            th + c->off[nb + 3], Wv, th + c->off[nb + 5], actions, rewards, dones, bootstrap, seg_start, N, T, hp->gamma, hp->beta,
-                           hp->value_coef, hp->log_eps, w.h, w.zv, c->R, c->dzv, c->dh, c->colpart, part, losspart, c->rb);
+                           hp->value_coef, hp->log_eps, w.h, w.zv, c->R, c->dzv, c->dh, c->colpart, part, losspart, c->rb,
+                           FastDiv(std::max(1, F / 4)), FastDiv(A + 1), FastDiv(heads_train_kparts(F, A)), FastDiv(T));
         HIP_TRY(hipGetLastError());
         add_seg(part, nblk, A + 1, F + 1, 0, A, c->grad + c->off[nb + 2], c->grad + c->off[nb + 3], 1);
         add_seg(part, nblk, A + 1, F + 1, A, 1, c->grad + c->off[nb + 4], c->grad + c->off[nb + 5], 1);
