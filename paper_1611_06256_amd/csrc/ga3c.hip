@@ -289,12 +289,16 @@ __device__ __forceinline__ void heads_store_weights(float *hs, const float (&wv)
 // hundred cycles issuing each one, whatever its width): the split-k partial sums of the fc layer for NF frames are
 // added up in chunk order, bias and ReLU follow, the result goes to h and (rounded if rb) to hs [NF][F4]; the heads'
 // weights go to wsh [A+1][WP] (the value head's row with 4-byte loads: it follows the policy biases in the parameter
-// vector and is not aligned).  Needs F % 4 == 0 and 16-byte aligned pointers (heads_vec4_ok).
+// vector and is not aligned).  Needs F % 4 == 0 and 16-byte aligned pointers (heads_loads).
 // What it takes is rounds of latency, so the weights, the biases and the partial sums of IP outputs per thread, CH chunks
 // each, are all requested before the first of them is used: one round where the chunks fit CH and the outputs IP (training
 // on 40 frames, 40 chunks: the block's loads 7.5 us when every output and every eight chunks were a round of their own).
-__device__ __forceinline__ bool heads_vec4_ok(int F, const void *ws, const void *fcb, const void *h, const void *Wp) {
-    return F % 4 == 0 && (((uintptr_t)ws | (uintptr_t)fcb | (uintptr_t)h | (uintptr_t)Wp) & 15) == 0;
+// A block runs these kernels' code once and fetches it from memory as it goes, so each way to load is a kernel of its own
+// (LOADS) instead of a branch.
+enum { LOADS_SCALAR = 0, LOADS_VEC8 = 1, LOADS_VEC16 = 2 };      // any shape; 16-byte vectors, 8 or 16 chunks at a time
+inline int heads_loads(int F, int nz, const void *ws, const void *fcb, const void *h, const void *Wp) {
+    if (F % 4 != 0 || !ws || (((uintptr_t)ws | (uintptr_t)fcb | (uintptr_t)h | (uintptr_t)Wp) & 15) != 0) return LOADS_SCALAR;
+    return nz <= 8 ? LOADS_VEC8 : LOADS_VEC16;
 }
 template <int NT, int NF, int CH, int IP>
 __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int tid, const int b0, const int nf,
@@ -368,7 +372,7 @@ __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int
 // The body, for a block of NT threads (all of them must call it) that works on frames b0 .. min(b0 + 4, B) - 1;
 // hs is the block's LDS.  COHERENT: h was written by other blocks of the same launch, so it is read past the
 // caches that are not kept coherent within a launch.  WSTAGED: heads_stage_weights has already run on hs.
-template <int NT, bool COHERENT, bool WSTAGED>
+template <int NT, bool COHERENT, bool WSTAGED, int LOADS>
 __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const int b0, const float *__restrict__ ws, int nz,
                                                const float *__restrict__ fcb, float *__restrict__ h, int B, int F, int A,
                                                const float *__restrict__ Wp, const float *__restrict__ bp,
@@ -391,11 +395,9 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
     if (!WSTAGED)
         heads_zero_padding<NT>(wsh, tid, F, WP, A + 1);
     const int nw = (A + 1) * F;                 // Wp [A][F] and Wv [F] are adjacent in LDS, not in global memory
-    const bool vec4 = !WSTAGED && ws && heads_vec4_ok(F, ws, fcb, h, Wp);
-    if (vec4) {
-        if (nz <= 8) heads_load_vec4<NT, 4, 8, 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
-        else heads_load_vec4<NT, 4, 16, 1>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
-    }
+    constexpr bool vec4 = LOADS != LOADS_SCALAR;
+    static_assert(!vec4 || !WSTAGED, "the vector loads bring the weights too");
+    if (vec4) heads_load_vec4<NT, 4, LOADS == LOADS_VEC8 ? 8 : 16, LOADS == LOADS_VEC8 ? 2 : 1>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
     for (int e0 = 0; !vec4 && ((!WSTAGED && e0 < nw) || e0 == 0); e0 += 24 * NT) {
         float wv[24];
         if (!WSTAGED) {
@@ -523,6 +525,7 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
     }
 }
 
+template <int LOADS>
 __global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict__ ws, int nz,
                                                         const float *__restrict__ fcb, float *__restrict__ h, int B,
                                                         int F, int A, const float *__restrict__ Wp,
@@ -531,7 +534,7 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict_
                                                         float *values, float *probs, const float *uniforms,
                                                         int32_t *actions, int rb, const FastDiv dFQ, const FastDiv dA1) {
     extern __shared__ __attribute__((aligned(16))) float heads_smem[];
-    heads_fwd_body<256, false, false>(heads_smem, threadIdx.x, blockIdx.x * 4, ws, nz, fcb, h, B, F, A, Wp, bp, Wv, bv, zv, logits,
+    heads_fwd_body<256, false, false, LOADS>(heads_smem, threadIdx.x, blockIdx.x * 4, ws, nz, fcb, h, B, F, A, Wp, bp, Wv, bv, zv, logits,
                                values, probs, uniforms, actions, rb, dFQ, dA1);
 }
 
@@ -679,7 +682,7 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
     }
     __syncthreads();
     if (!last) return;
-    heads_fwd_body<512, true, true>((float *)(sp_smem + SP_HEADS_OFF), tid, frame, nullptr, 0, fcb, h, frame + 1, SP_FC, A, Wp, bp, Wv, bv, nullptr,
+    heads_fwd_body<512, true, true, LOADS_SCALAR>((float *)(sp_smem + SP_HEADS_OFF), tid, frame, nullptr, 0, fcb, h, frame + 1, SP_FC, A, Wp, bp, Wv, bv, nullptr,
                               logits, values, probs, uniforms, actions, rb, dA1 /* not used */, dA1);
 }
 
@@ -871,6 +874,7 @@ __host__ __device__ inline int heads_train_lds_floats(int F, int A) {
            3 * HD_FRAMES * heads_f4(A + 1) + HD_FRAMES * (A + 1) * heads_train_kparts(F, A) + 512;
 }
 
+template <int LOADS>
 __global__ __launch_bounds__(256) void heads_train_kernel(
     const float *__restrict__ ws, int nz, const float *__restrict__ fcb, int B, int F, int A,
     const float *__restrict__ Wp, const float *__restrict__ bp, const float *__restrict__ Wv, const float *__restrict__ bv,
@@ -901,8 +905,9 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     const int n0 = (int)dT.div((uint32_t)b0), n1 = (int)dT.div((uint32_t)(b0 + nf - 1));      // agents of my frames
     const int nrw = (n1 - n0 + 1) * T;
     const bool rw_lds = !seg_start && nrw <= 256;      // segments of unequal length read their rewards from global memory
-    float my_rw = 0.f, my_dn = 0.f;
-    if (rw_lds && tid < nrw) { my_rw = rewards[(size_t)n0 * T + tid]; my_dn = dones[(size_t)n0 * T + tid] ? 0.f : 1.f; }
+    const size_t at_rw = rw_lds ? (size_t)n0 * T + min(tid, nrw - 1) : 0;
+    const float my_rw = rewards[at_rw];
+    const uint32_t my_done = dones[at_rw];
     uint32_t tq, tr;
     dA1.divmod((uint32_t)tid, tq, tr);
     const int ofb = min((int)tq, nf - 1), oa = (int)tr;     // thread tid < nf*A1 owns output oa of frame ofb
@@ -914,11 +919,8 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     for (int e = tid; e < NF * (F4 - F); e += 256) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
     heads_zero_padding<256>(wsh, tid, F, WP, A1);
     const int nw = A1 * F;
-    const bool vec4 = heads_vec4_ok(F, ws, fcb, h, Wp);
-    if (vec4) {
-        if (nz <= 8) heads_load_vec4<256, NF, 8, 4>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
-        else heads_load_vec4<256, NF, 16, 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
-    }
+    constexpr bool vec4 = LOADS != LOADS_SCALAR;
+    if (vec4) heads_load_vec4<256, NF, LOADS == LOADS_VEC8 ? 8 : 16, LOADS == LOADS_VEC8 ? 4 : 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
     for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * 256) {
         float wv[24];
 #pragma unroll
@@ -961,7 +963,7 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
             if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
         }
     }
-    if (rw_lds && tid < nrw) { rw[tid] = my_rw; dn[tid] = my_dn; }
+    if (rw_lds && tid < nrw) { rw[tid] = my_rw; dn[tid] = my_done ? 0.f : 1.f; }
     __syncthreads();
 
     // ---- heads: thread (action a, part kp of k) for all frames, then the parts are added in order
@@ -1737,10 +1739,13 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     w.fc_ws = fc_ws; w.fc_nz = fc_nz;
     if (!with_heads) return GA3C_OK;          // the caller finishes the fc layer and the heads itself
     const size_t hf_lds = sizeof(float) * heads_lds_floats(c->F, c->A);
-    static size_t hf_lds_set = 0;
-    HIP_TRY(allow_dynamic_lds((const void *)heads_fwd_kernel, hf_lds, hf_lds_set));
+    typedef decltype(&heads_fwd_kernel<LOADS_SCALAR>) HeadsFwd;
+    static const HeadsFwd hf_kernels[3] = {heads_fwd_kernel<LOADS_SCALAR>, heads_fwd_kernel<LOADS_VEC8>, heads_fwd_kernel<LOADS_VEC16>};
+    static size_t hf_lds_set[3] = {0, 0, 0};
+    const int hf = heads_loads(c->F, fc_nz, fc_ws, th + c->off[nb + 1], w.h, th + c->off[nb + 2]);
+    HIP_TRY(allow_dynamic_lds((const void *)hf_kernels[hf], hf_lds, hf_lds_set[hf]));
     STAGE("heads_fwd", 2.0 * B * c->F * (c->A + 1), 4.0 * (fc_nz + 1) * B * c->F);
-    ga3c::launch(heads_fwd_kernel, dim3(cdiv(B, 4)), dim3(256), hf_lds, s, fc_ws, fc_nz,
+    ga3c::launch(hf_kernels[hf], dim3(cdiv(B, 4)), dim3(256), hf_lds, s, fc_ws, fc_nz,
                        th + c->off[nb + 1], w.h, B, c->F, c->A, th + c->off[nb + 2],
                        th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5],
                        keep_zv ? w.zv : nullptr, logits, values, probs, uniforms, actions, c->rb, FastDiv(std::max(1, c->F / 4)), FastDiv(c->A + 1));
@@ -2131,10 +2136,13 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         const int nblk = cdiv(B, HD_FRAMES);
         float *part = region((size_t)nblk * (A + 1) * (F + 1));
         if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (heads)");
-        static size_t ht_lds_set = 0;
-        HIP_TRY(allow_dynamic_lds((const void *)heads_train_kernel, ht_lds, ht_lds_set));
+        typedef decltype(&heads_train_kernel<LOADS_SCALAR>) HeadsTrain;
+        static const HeadsTrain ht_kernels[3] = {heads_train_kernel<LOADS_SCALAR>, heads_train_kernel<LOADS_VEC8>, heads_train_kernel<LOADS_VEC16>};
+        static size_t ht_lds_set[3] = {0, 0, 0};
+        const int ht = heads_loads(F, w.fc_nz, w.fc_ws, th + c->off[nb + 1], w.h, Wp);
+        HIP_TRY(allow_dynamic_lds((const void *)ht_kernels[ht], ht_lds, ht_lds_set[ht]));
         STAGE("heads_train", 6.0 * B * (A + 1) * F, 4.0 * (w.fc_nz + 1) * B * F);
-        ga3c::launch(heads_train_kernel, dim3(nblk), dim3(256), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
+        ga3c::launch(ht_kernels[ht], dim3(nblk), dim3(256), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
                            th + c->off[nb + 3], Wv, th + c->off[nb + 5], actions, rewards, dones, bootstrap, seg_start, N, T, hp->gamma, hp->beta,
                            hp->value_coef, hp->log_eps, w.h, w.zv, c->R, c->dzv, c->dh, c->colpart, part, losspart, c->rb,
                            FastDiv(std::max(1, F / 4)), FastDiv(A + 1), FastDiv(heads_train_kparts(F, A)), FastDiv(T));
