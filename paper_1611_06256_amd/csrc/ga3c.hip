@@ -215,6 +215,17 @@ __device__ __forceinline__ void copy_to_lds(float *dst, const float *__restrict_
     }
 }
 
+// A division by a constant as a FastDiv, for code that takes either.
+template <uint32_t D>
+struct FastDivConst {
+    static __device__ __forceinline__ FastDiv get() {
+        static_assert((D & (D - 1)) == 0, "a power of two");
+        FastDiv f = {};
+        f.d = D; f.mul = 1; f.shift = 31 - __builtin_clz(D);
+        return f;
+    }
+};
+
 // Policy and value heads (Sec. 3.2: softmax policy output, linear value
 // output), then softmax and inverse-CDF sampling; optionally preceded by the
 // last step of a split-k fully connected layer.  A block takes 4 frames.
@@ -236,53 +247,6 @@ template <int NT>
 __device__ __forceinline__ void heads_zero_padding(float *wsh, const int t, int F, int WP, int rows) {
     for (int r = t >> 3; r < rows; r += NT / 8)
         if ((t & 7) < WP - F) wsh[r * WP + F + (t & 7)] = 0.f;
-}
-
-// Both weight matrices into the block's LDS in the layout heads_fwd_body reads, by threads t = 0 .. NT-1.
-template <int NT>
-__device__ __forceinline__ void heads_stage_weights(float *hs, const int t, int F, int A, const float *__restrict__ Wp,
-                                                    const float *__restrict__ Wv, int rb) {
-    const int F4 = heads_f4(F), WP = F4 + 4;
-    float *wsh = hs + 4 * F4;
-    heads_zero_padding<NT>(wsh, t, F, WP, A + 1);
-    const int nw = (A + 1) * F;
-    for (int e0 = 0; e0 < nw; e0 += 24 * NT) {
-        float wv[24];
-#pragma unroll
-        for (int j = 0; j < 24; ++j) {
-            const int e = min(e0 + j * NT + t, nw - 1);
-            wv[j] = e < A * F ? Wp[e] : Wv[e - A * F];
-        }
-#pragma unroll
-        for (int j = 0; j < 24; ++j) {
-            const int e = e0 + j * NT + t;
-            if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
-        }
-    }
-}
-
-// The same in two steps for at most 24 * NT weights: the loads first, the stores whenever the caller has time.
-template <int NT>
-__device__ __forceinline__ void heads_load_weights(float (&wv)[24], const int t, int F, int A, const float *__restrict__ Wp,
-                                                   const float *__restrict__ Wv) {
-    const int nw = (A + 1) * F;
-#pragma unroll
-    for (int j = 0; j < 24; ++j) {
-        const int e = min(j * NT + t, nw - 1);
-        wv[j] = e < A * F ? Wp[e] : Wv[e - A * F];
-    }
-}
-template <int NT>
-__device__ __forceinline__ void heads_store_weights(float *hs, const float (&wv)[24], const int t, int F, int A, int rb) {
-    const int F4 = heads_f4(F), WP = F4 + 4;
-    float *wsh = hs + 4 * F4;
-    heads_zero_padding<NT>(wsh, t, F, WP, A + 1);
-    const int nw = (A + 1) * F;
-#pragma unroll
-    for (int j = 0; j < 24; ++j) {
-        const int e = j * NT + t;
-        if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
-    }
 }
 
 // The loads of a heads block as 16-byte vectors (a quarter of the load instructions: a wavefront spends about a
@@ -369,16 +333,16 @@ __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int
     for (int k = WVQ * NT + tid; k < F; k += NT) wsh[A * WP + k] = rb ? bf16_rne(Wv[k]) : Wv[k];
 }
 
-// The body, for a block of NT threads (all of them must call it) that works on frames b0 .. min(b0 + 4, B) - 1;
-// hs is the block's LDS.  COHERENT: h was written by other blocks of the same launch, so it is read past the
-// caches that are not kept coherent within a launch.  WSTAGED: heads_stage_weights has already run on hs.
-template <int NT, bool COHERENT, bool WSTAGED, int LOADS>
-__device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const int b0, const float *__restrict__ ws, int nz,
-                                               const float *__restrict__ fcb, float *__restrict__ h, int B, int F, int A,
-                                               const float *__restrict__ Wp, const float *__restrict__ bp,
-                                               const float *__restrict__ Wv, const float *__restrict__ bv, float *zv,
-                                               float *logits, float *values, float *probs, const float *uniforms,
-                                               int32_t *actions, int rb, const FastDiv dFQ, const FastDiv dA1) {
+template <int LOADS>
+__global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict__ ws, int nz, const float *__restrict__ fcb,
+                                                        float *__restrict__ h, int B, int F, int A,
+                                                        const float *__restrict__ Wp, const float *__restrict__ bp,
+                                                        const float *__restrict__ Wv, const float *__restrict__ bv, float *zv,
+                                                        float *logits, float *values, float *probs, const float *uniforms,
+                                                        int32_t *actions, int rb, const FastDiv dFQ, const FastDiv dA1) {
+    extern __shared__ __attribute__((aligned(16))) float hs[];
+    constexpr int NT = 256;
+    const int tid = threadIdx.x, b0 = blockIdx.x * 4;
     // dFQ, dA1: divisions by F / 4 and A + 1 (a division by a run-time number costs tens of instructions, and these kernels are
     // short).  rb: the products of the heads take h and the weights rounded to bfloat16 (h itself is stored as computed)
     const int F4 = heads_f4(F), WP = F4 + 4;                        // hs: [4][F4], weights [A+1][F4+4], partial dots
@@ -392,20 +356,16 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
     const float obias = oa < A ? bp[oa] : bv[0];
     // padding columns of the LDS rows stay zero
     for (int e = tid; e < 4 * (F4 - F); e += NT) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
-    if (!WSTAGED)
-        heads_zero_padding<NT>(wsh, tid, F, WP, A + 1);
+    heads_zero_padding<NT>(wsh, tid, F, WP, A + 1);
     const int nw = (A + 1) * F;                 // Wp [A][F] and Wv [F] are adjacent in LDS, not in global memory
     constexpr bool vec4 = LOADS != LOADS_SCALAR;
-    static_assert(!vec4 || !WSTAGED, "the vector loads bring the weights too");
     if (vec4) heads_load_vec4<NT, 4, LOADS == LOADS_VEC8 ? 8 : 16, LOADS == LOADS_VEC8 ? 2 : 1>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
-    for (int e0 = 0; !vec4 && ((!WSTAGED && e0 < nw) || e0 == 0); e0 += 24 * NT) {
+    for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * NT) {
         float wv[24];
-        if (!WSTAGED) {
 #pragma unroll
-            for (int j = 0; j < 24; ++j) {
-                const int e = min(e0 + j * NT + tid, nw - 1);
-                wv[j] = e < A * F ? Wp[e] : Wv[e - A * F];
-            }
+        for (int j = 0; j < 24; ++j) {
+            const int e = min(e0 + j * NT + tid, nw - 1);
+            wv[j] = e < A * F ? Wp[e] : Wv[e - A * F];
         }
         if (e0 == 0) {
             for (int o = tid; o < F; o += NT) {
@@ -438,19 +398,17 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
 #pragma unroll
                     for (int fb = 0; fb < 4; ++fb) {
                         const float *src = h + (size_t)(b0 + min(fb, nf - 1)) * F + o;
-                        v[fb] = COHERENT ? __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *src;
+                        v[fb] = *src;
                     }
 #pragma unroll
                     for (int fb = 0; fb < 4; ++fb) hs[fb * F4 + o] = rb ? bf16_rne(v[fb]) : v[fb];
                 }
             }
         }
-        if (!WSTAGED) {
 #pragma unroll
-            for (int j = 0; j < 24; ++j) {
-                const int e = e0 + j * NT + tid;
-                if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
-            }
+        for (int j = 0; j < 24; ++j) {
+            const int e = e0 + j * NT + tid;
+            if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
         }
     }
     __syncthreads();
@@ -525,165 +483,454 @@ __device__ __forceinline__ void heads_fwd_body(float *hs, const int tid, const i
     }
 }
 
-template <int LOADS>
-__global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict__ ws, int nz,
-                                                        const float *__restrict__ fcb, float *__restrict__ h, int B,
-                                                        int F, int A, const float *__restrict__ Wp,
-                                                        const float *__restrict__ bp, const float *__restrict__ Wv,
-                                                        const float *__restrict__ bv, float *zv, float *logits,
-                                                        float *values, float *probs, const float *uniforms,
-                                                        int32_t *actions, int rb, const FastDiv dFQ, const FastDiv dA1) {
-    extern __shared__ __attribute__((aligned(16))) float heads_smem[];
-    heads_fwd_body<256, false, false, LOADS>(heads_smem, threadIdx.x, blockIdx.x * 4, ws, nz, fcb, h, B, F, A, Wp, bp, Wv, bv, zv, logits,
-                               values, probs, uniforms, actions, rb, dFQ, dA1);
+// The end of a prediction, by one wavefront: lane a < A holds logit a of frame b, lane A the value.  Softmax and the draw stay
+// in registers; the sums run left to right in fp32 exactly as a single thread would form them, so the sampled action is a
+// pure function of the probabilities written out.
+__device__ __forceinline__ void heads_finish_frame(const int lane, const float z, const int A, const int b, const float u, float *logits,
+                                                   float *values, float *probs, int32_t *actions) {
+    const bool pol = lane < A;
+    if (pol && logits) logits[(size_t)b * A + lane] = z;
+    if (lane == A && values) values[b] = z;
+    if (!probs && !actions) return;
+    const float zmax = wave_max(pol ? z : -3.4e38f);
+    const float e = pol ? expf(z - zmax) : 0.f;
+    float S = 0.f;
+    for (int j = 0; j < A; ++j) S += lane_f32(e, j);
+    const float pr = e / S;
+    if (pol && probs) probs[(size_t)b * A + lane] = pr;
+    if (!actions) return;
+    // the first action whose running sum exceeds u; the last one if none does
+    float c = 0.f;
+    int act = A - 1;
+    for (int j = A - 1, k = 0; k <= j; ++k) {
+        c += lane_f32(pr, k);
+        if (c > u) { act = k; break; }
+    }
+    if (lane == 0) actions[b] = act;
 }
 
-// The whole forward pass of the small network (Sec. 3.2) for a handful of frames in ONE launch, for the latency of a
-// small prediction batch (the paper's Sec. 5.2 finds the per-call overhead, not the arithmetic, dominant there).
-// SLICES blocks work on each frame (32 for up to 8 frames, 16 for up to 16, 8 for up to 32, 4 for up to 64: at most one
-// block per compute unit either way):
-// every one of them runs both convolution layers of the frame (the same work SLICES times: the chip is otherwise
-// idle), keeps the result in LDS and computes its own 256 / SLICES outputs of the fully connected layer, two per
-// wavefront: the idle layer-1 wavefronts fetch their weight rows while layer 2 runs; with 16 slices the layer-2
-// wavefronts take two rows each as well and fetch them when they are done.  The block that finishes a frame's fc
-// outputs last (a ticket counter per frame; nobody waits for anybody) runs the heads, the softmax and the draw for
-// that frame.  h [B][256]; ticket [B][SP_TICKET_PITCH], zero before the launch and zero
-// again after it.
-constexpr int SP_FC = 256, SP_FLAT = 2592, SP_MAX_FRAMES = 64;
-constexpr int SP_TICKET_PITCH = 32;                        // ints between two frames' counters: a cache line each
-// LDS of the heads: the 4 KB of fc outputs end where the layer-2 output ends, the weights follow in the part of the
-// second layer-1 buffer that a single frame never touches, so that they can be staged while the convolutions run.
-constexpr size_t SP_HEADS_OFF = C12_Y2S_OFF + sizeof(float) * (SP_FLAT - 4 * SP_FC);
-constexpr size_t SP_HEADS_MAX = sizeof(__bf16) * (C12_XS + 2 * 3 * C12_Y1) - SP_HEADS_OFF;
-constexpr int SP_ROWS = 2;                                 // fc outputs per wavefront
-constexpr int SP_WJ = (SP_FLAT / 4 + 63) / 64;             // 16-byte vectors of one fc row per lane
+// The heads' weights [A + 1][WP] in LDS, columns F .. WP - 1 not used; by NT threads, at most WQ vectors per thread in flight.
+// Needs F % 4 == 0 and a 16-byte aligned policy matrix.  fetch and store are apart so that other loads can go out in between.
+template <int NT, int WQ>
+struct HeadWeights {
+    float4 w[WQ];
+    float v[2];
+    __device__ __forceinline__ void fetch(int t, int q0, int F, int A, const float *__restrict__ Wp, const float *__restrict__ Wv) {
+        const int nwq = A * (F >> 2);
+#pragma unroll
+        for (int j = 0; j < WQ; ++j) w[j] = ((const float4 *)Wp)[min(q0 + j * NT + t, nwq - 1)];
+        if (q0 == 0) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) v[j] = Wv[min(j * NT + t, F - 1)];
+        }
+    }
+    __device__ __forceinline__ void store(float *wsh, int t, int F, int WP, int A, const float *__restrict__ Wp, const float *__restrict__ Wv, int rb,
+                                          const FastDiv dFQ) {
+        const int nwq = A * (F >> 2);
+        for (int q0 = 0;; q0 += WQ * NT) {
+#pragma unroll
+            for (int j = 0; j < WQ; ++j) {
+                const int q = q0 + j * NT + t;
+                if (q < nwq) *(float4 *)(wsh + 4 * q + (WP - F) * (int)dFQ.div((uint32_t)q)) = rb ? bf16_rne(w[j]) : w[j];
+            }
+            if (q0 == 0) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    if (j * NT + t < F) wsh[A * WP + j * NT + t] = rb ? bf16_rne(v[j]) : v[j];
+                for (int k = 2 * NT + t; k < F; k += NT) wsh[A * WP + k] = rb ? bf16_rne(Wv[k]) : Wv[k];
+            }
+            if (q0 + WQ * NT >= nwq) break;
+            fetch(t, q0 + WQ * NT, F, A, Wp, Wv);
+        }
+    }
+};
 
-template <bool ONE, int SLICES, bool TABLE>
+// Heads of a prediction after the split-k fc layer of F = 256 NJ units: wavefront w of a block takes frame 4 blockIdx.x + w and
+// keeps everything of it in registers (its fc outputs, then its logits); only the weights, which the block's four frames share,
+// go through LDS, behind the one barrier.  CH chunks of partial sums in flight per lane.
+// Latency: loads and arithmetic of 1024 frames 6.8 us, 7.9 us with a barrier between the steps (heads_fwd_kernel).
+template <int NJ, int CH>
+__global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restrict__ ws, int nz, const float *__restrict__ fcb, int B, int A,
+                                                            const float *__restrict__ Wp, const float *__restrict__ bp,
+                                                            const float *__restrict__ Wv, const float *__restrict__ bv, float *logits,
+                                                            float *values, float *probs, const float *uniforms, int32_t *actions, int rb) {
+    constexpr int F = 256 * NJ, FQ = F / 4, WP = F + 4;
+    extern __shared__ __attribute__((aligned(16))) float heads_smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int b = blockIdx.x * 4 + wave;
+    HeadWeights<256, 5> hw;
+    hw.fetch(tid, 0, F, A, Wp, Wv);
+    const float obias = lane < A ? bp[lane] : bv[0];
+    float4 bias[NJ], acc[NJ];
+    const float4 *src = (const float4 *)ws + (size_t)min(b, B - 1) * FQ;
+    const size_t stride4 = (size_t)B * FQ;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        bias[j] = ((const float4 *)fcb)[64 * j + lane];
+        acc[j] = float4{0.f, 0.f, 0.f, 0.f};
+    }
+    for (int z = 0; z < nz; z += CH) {
+        float4 v[CH][NJ];
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) v[i][j] = (src + (size_t)min(z + i, nz - 1) * stride4)[64 * j + lane];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const bool in = z + i < nz;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                acc[j].x += in ? v[i][j].x : 0.f; acc[j].y += in ? v[i][j].y : 0.f;
+                acc[j].z += in ? v[i][j].z : 0.f; acc[j].w += in ? v[i][j].w : 0.f;
+            }
+        }
+    }
+    hw.store(heads_smem, tid, F, WP, A, Wp, Wv, rb, FastDivConst<FQ>::get());
+    // asked for last and needed last: it may be in host memory
+    const float u = actions && uniforms ? uniforms[min(b, B - 1)] : 0.f;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        acc[j] = float4{acc[j].x + bias[j].x, acc[j].y + bias[j].y, acc[j].z + bias[j].z, acc[j].w + bias[j].w};
+        acc[j].x = acc[j].x > 0.f ? acc[j].x : 0.f; acc[j].y = acc[j].y > 0.f ? acc[j].y : 0.f;
+        acc[j].z = acc[j].z > 0.f ? acc[j].z : 0.f; acc[j].w = acc[j].w > 0.f ? acc[j].w : 0.f;
+        if (rb) acc[j] = bf16_rne(acc[j]);
+    }
+    __syncthreads();
+    if (b >= B) return;
+    float z = 0.f;
+#pragma unroll 4
+    for (int a = 0; a <= A; ++a) {
+        float d = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const float4 w = *(const float4 *)(heads_smem + a * WP + 256 * j + 4 * lane);
+            d += (acc[j].x * w.x + acc[j].y * w.y) + (acc[j].z * w.z + acc[j].w * w.w);
+        }
+        d = wave_sum(d);
+        z = lane == a ? d : z;
+    }
+    heads_finish_frame(lane, z + obias, A, b, u, logits, values, probs, actions);
+}
+
+// The whole forward pass of the small network (Sec. 3.2) for up to SP_MAX_FRAMES frames in ONE launch, for the latency of a
+// small prediction batch (the paper's Sec. 5.2 finds the per-call overhead, not the arithmetic, dominant there).
+//
+// A block takes FB frames, three of the nine output rows of layer 2 (`rg`; they need 36 of the frame's 84 rows and 8 of
+// layer 1's 20) and 256 / NS outputs of the fully connected layer, for which it forms the sums over its rows.  Wavefronts 0..3
+// run layer 1 from LDS (as in conv12_fused.hpp), then wavefronts 4..7 layer 2, and all eight the fc sums, two outputs per
+// wavefront and pass, whose weights are on their way while the convolutions run.  The block that finishes a frame group last
+// (a ticket per group; nobody waits for anybody) adds the three row groups up and runs the heads, the softmax and the draw.
+// Blocks in order of (row group, slice): an XCD reads few parts of the fc weights.
+// Latency: nothing is large.  One frame 15.8 -> @1@ us a call, 37 frames 23.9 -> @37@ us against a kernel whose blocks each ran
+// both layers of a whole frame.
+constexpr int SP_FC = 256, SP_FLAT = 2592, SP_MAX_FRAMES = 64;
+constexpr int SP_TICKET_PITCH = 32;                        // ints between two groups' counters: a cache line each
+constexpr int SP_ROWS1 = 8, SP_PIX1 = SP_ROWS1 * 20, SP_PIX2 = 27, SP_XROWS = 36;      // of a row group: layer 1, layer 2, input
+constexpr int SP_XVEC = 4 * SP_XROWS * 84 / 16;            // 16-byte vectors of a frame's part
+constexpr int SP_Y1 = 16 * SP_PIX1;                        // elements of one plane of its layer-1 output
+constexpr int SP_Y2 = 32 * 28;                             // floats of its layer-2 output: 27 pixels and a zero per filter
+constexpr int SP_WP = SP_FC + 4;
+template <int FB>
+struct SpLds {
+    static constexpr int XS = 0, FR = XS + FB * SP_XVEC * 32, Y1 = FR + 3 * 8 * 64 * 16, EX = Y1 + FB * 3 * SP_Y1 * 2, Y2 = EX + FB * 4096,
+                         ZS = Y2 + FB * SP_Y2 * 4, WS = ZS + FB * 256;
+    static size_t bytes(int A) { return WS + sizeof(float) * (A + 1) * SP_WP; }
+};
+
+template <bool ONE, int FB, bool TABLE>
 __global__ __launch_bounds__(512, 1) void predict_small_kernel(
-    const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table, const FastDiv dA1, const u32x4 *__restrict__ frag, const float *__restrict__ b1,
-    const float *__restrict__ b2, const float *__restrict__ Wfc, const float *__restrict__ fcb, float *__restrict__ h,
-    int *__restrict__ ticket, int A, const float *__restrict__ Wp, const float *__restrict__ bp,
-    const float *__restrict__ Wv, const float *__restrict__ bv, float *logits, float *values, float *probs,
-    const float *uniforms, int32_t *actions, float scale, int rb) {
+    const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table, const u32x4 *__restrict__ frag, const float *__restrict__ b1,
+    const float *__restrict__ b2, const float *__restrict__ Wfc, const float *__restrict__ fcb, float *__restrict__ part,
+    int *__restrict__ ticket, int B, int NS, int A, const float *__restrict__ Wp, const float *__restrict__ bp,
+    const float *__restrict__ Wv, const float *__restrict__ bv, float *logits, float *values, float *probs, const float *uniforms,
+    int32_t *actions, float scale, int rb) {
+    typedef SpLds<FB> L;
+    constexpr int NTERM = ONE ? 1 : 3, CHW1 = 4 * 84 * 84, FPT = NTERM * 2;
+    constexpr int XPT = (FB * SP_XVEC + 255) / 256, T1 = (FB * 10 + 3) / 4;      // vectors of input, layer-1 tiles per wavefront
     extern __shared__ __attribute__((aligned(16))) unsigned char sp_smem[];
     __shared__ int last;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // fc rows of a block: 256 / SLICES.  32 slices: the four layer-1 wavefronts take two rows each; 16 or fewer
-    // slices: all eight wavefronts take two rows per pass, in 1, 2 or 4 passes.
-    constexpr bool ALL_WAVES_FC = SLICES <= 16;
-    constexpr int PASSES = ALL_WAVES_FC ? SP_FC / (SLICES * 8 * SP_ROWS) : 1;
-    static_assert(SLICES * 4 * SP_ROWS == SP_FC || SLICES * 8 * SP_ROWS * PASSES == SP_FC, "two fc outputs per wavefront and pass");
-    const int frame = blockIdx.x / SLICES, slice = blockIdx.x % SLICES;
-    // first fc output of my wavefront in pass p
-    auto row0 = [&](int p) { return slice * (SP_FC / SLICES) + (p * (ALL_WAVES_FC ? 8 : 4) + wave) * SP_ROWS; };
+    const int rt = tid & 255, rw = wave & 3, l16 = lane & 15, g = lane >> 4;
+    const int groups = (B + FB - 1) / FB, per = (int)gridDim.x / 8, at = (int)blockIdx.x % 8 * per + (int)blockIdx.x / 8;
+    if (at >= 3 * NS * groups) return;
+    const int combo = at / groups, fg = at % groups, rg = combo / NS, o0 = combo % NS * (SP_FC / NS), f0 = fg * FB;
+    const int passes = SP_FC / NS / 16;
+    __bf16 *xs = (__bf16 *)(sp_smem + L::XS), *y1 = (__bf16 *)(sp_smem + L::Y1);
+    float *ex = (float *)(sp_smem + L::EX), *y2 = (float *)(sp_smem + L::Y2), *zs = (float *)(sp_smem + L::ZS), *wsh = (float *)(sp_smem + L::WS);
 
-    // the layer-2 wavefronts ask for the heads' weights now (with their filters, before the first barrier waits for
-    // both) and put them into LDS while layer 1 runs
-    float hw[24];
-    const bool hw_early = (A + 1) * SP_FC <= 24 * 256;
-    if (wave >= 4 && hw_early) heads_load_weights<256>(hw, tid - 256, SP_FC, A, Wp, Wv);
-    float4 wreg[PASSES > 1 ? 2 : 1][SP_ROWS][SP_WJ];
-    float fbias[PASSES > 1 ? 2 : 1][SP_ROWS];
-    auto load_rows = [&](int set, int p) {
-        const int o0 = row0(p);
+    // ---- everything that can be asked for now
+    u32x4 xpre[XPT], fpre[FPT];
+    HeadWeights<256, 5> hw;
+    if (wave < 4) {
 #pragma unroll
-        for (int r = 0; r < SP_ROWS; ++r) fbias[set][r] = fcb[min(o0 + r, SP_FC - 1)];
+        for (int f = 0; f < FB; ++f) {
+            FramePointer<TABLE> fp;
+            fp.ask(x, table, min(f0 + f, B - 1), CHW1);
+            const u32x4 *src = (const u32x4 *)fp.get() + rg * (24 * 84 / 16);
 #pragma unroll
-        for (int r = 0; r < SP_ROWS; ++r)
-#pragma unroll
-            for (int j = 0; j < SP_WJ; ++j)          // rows are 16-byte aligned: the tensor starts on one and a row is 2592 floats
-                wreg[set][r][j] = ((const float4 *)(Wfc + (size_t)min(o0 + r, SP_FC - 1) * SP_FLAT))[min(lane + 64 * j, SP_FLAT / 4 - 1)];
-    };
-    // the loads happen where this is called, and not where the compiler finds their first use
-    auto pin_rows = [&](int set) {
-#pragma unroll
-        for (int r = 0; r < SP_ROWS; ++r)
-#pragma unroll
-            for (int j = 0; j < SP_WJ; ++j)
-                asm volatile("" : "+v"(wreg[set][r][j].x), "+v"(wreg[set][r][j].y), "+v"(wreg[set][r][j].z), "+v"(wreg[set][r][j].w));
-#pragma unroll
-        for (int r = 0; r < SP_ROWS; ++r) asm volatile("" : "+v"(fbias[set][r]));
-    };
-    auto fetch_rows = [&](int it) {      // the idle layer-1 wavefronts, while layer 2 runs
-        if (it != 1) return;
-        load_rows(0, 0);
-        pin_rows(0);
-    };
-    auto store_heads_weights = [&]() {
-        if (hw_early) heads_store_weights<256>((float *)(sp_smem + SP_HEADS_OFF), hw, tid - 256, SP_FC, A, rb);
-        else heads_stage_weights<256>((float *)(sp_smem + SP_HEADS_OFF), tid - 256, SP_FC, A, Wp, Wv, rb);
-    };
-    conv12_fused_block<ONE, false, true, TABLE>(x, table, frag, b1, b2, nullptr, nullptr, frame, 1 << 24, frame + 1, scale, sp_smem,
-                                         fetch_rows, store_heads_weights);
-    if (ALL_WAVES_FC && wave >= 4) { load_rows(0, 0); pin_rows(0); }
-    __syncthreads();
-    if (ALL_WAVES_FC || wave < 4) {
-        const float *y2s = (const float *)(sp_smem + C12_Y2S_OFF);
-        float4 yreg[PASSES > 1 ? SP_WJ : 1];     // several passes: the layer-2 output is read from LDS once
-        if (PASSES > 1) {
-#pragma unroll
-            for (int j = 0; j < SP_WJ; ++j) {
-                yreg[j] = ((const float4 *)y2s)[min(lane + 64 * j, SP_FLAT / 4 - 1)];
-                if (rb) yreg[j] = bf16_rne(yreg[j]);
+            for (int i = 0; i < XPT / FB; ++i) {
+                const int v = min(rt + 256 * i, SP_XVEC - 1);
+                xpre[f * (XPT / FB) + i] = src[v / 189 * 441 + v % 189];            // plane by plane: 36 rows are 189 vectors of 441
             }
         }
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-            const int set = p & 1;
-            if (p + 1 < PASSES) load_rows(set ^ 1, p + 1);      // the next pass's rows travel while this pass adds up
-            const int o0 = row0(p);
+        for (int i = 0; i < FPT; ++i) fpre[i] = frag[rt + 256 * i];
+    } else {
+        hw.fetch(rt, 0, SP_FC, A, Wp, Wv);
+        for (int e = rt; e < FB * 32; e += 256) y2[e * 28 + 27] = 0.f;
+    }
+    // my lane's vectors of an fc row: vector v is four pixels of filter v / 7, at an address that is a multiple of 4 bytes only; the
+    // seventh of a filter has one value too many
+    typedef float f32x4_dw4 __attribute__((ext_vector_type(4), aligned(4)));
+    int voff[4];
+    bool odd[4];
 #pragma unroll
-            for (int r = 0; r < SP_ROWS; ++r) {
-                float sum = 0.f;
+    for (int j = 0; j < 4; ++j) {
+        const int v = min(lane + 64 * j, 223);
+        voff[j] = v / 7 * 81 + 27 * rg + 4 * (v % 7);
+        odd[j] = v % 7 == 6;
+    }
+    float4 wreg[2][2][4];
+    auto load_rows = [&](int set, int p) {
 #pragma unroll
-                for (int j = 0; j < SP_WJ; ++j) {
-                    const int k4 = lane + 64 * j;
-                    float4 y, w = wreg[set][r][j];
-                    if (PASSES > 1) y = yreg[j];
-                    else {
-                        y = ((const float4 *)y2s)[min(k4, SP_FLAT / 4 - 1)];
-                        if (rb) y = bf16_rne(y);
-                    }
-                    if (rb) w = bf16_rne(w);
-                    const float d = (y.x * w.x + y.y * w.y) + (y.z * w.z + y.w * w.w);
-                    sum += k4 < SP_FLAT / 4 ? d : 0.f;
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4_dw4 t = *(const f32x4_dw4 *)(Wfc + (size_t)(o0 + (p * 8 + wave) * 2 + r) * SP_FLAT + voff[j]);
+                wreg[set][r][j] = float4{t[0], t[1], t[2], t[3]};
+            }
+        asm volatile("" ::: "memory");      // the loads go out here, and not where the compiler finds their first use
+    };
+    if (wave < 4) {
+#pragma unroll
+        for (int f = 0; f < FB; ++f)
+#pragma unroll
+            for (int i = 0; i < XPT / FB; ++i) {
+                u32x4 a, b;
+                bytes_to_bf16(xpre[f * (XPT / FB) + i], a, b);
+                const int v = rt + 256 * i;
+                if (v < SP_XVEC) {
+                    u32x4 *dst = (u32x4 *)(xs + (size_t)(f * SP_XVEC + v) * 16);
+                    dst[0] = a; dst[1] = b;
                 }
+            }
 #pragma unroll
-                for (int m = 32; m >= 1; m >>= 1) sum += __shfl_xor(sum, m, 64);
-                if (lane == 0) {
-                    const float v = sum + fbias[set][r];
-                    // written through to where every compute unit sees it (a device-wide fence instead would write
-                    // back and invalidate the whole L2 of this block's XCD, once per block)
-                    __hip_atomic_store(h + (size_t)frame * SP_FC + o0 + r, v > 0.f ? v : 0.f, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < FPT; ++i) ((u32x4 *)(sp_smem + L::FR))[rt + 256 * i] = fpre[i];
+    }
+    __syncthreads();
+    const int pg = rw >> 1, kh = rw & 1;                           // layer 2: pixel tiles pg, pg + 2, ..; taps 128 kh ..
+    bf16x8 wq[NTERM][8];
+    {
+        const u32x4 *src = wave < 4 ? (const u32x4 *)(sp_smem + L::FR) + lane : frag + (size_t)(1 + kh) * C12_FRAG_SET + lane;
+#pragma unroll
+        for (int t = 0; t < NTERM; ++t)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                Bf16x8Bits v;
+                v.u = src[(t * 8 + j) * 64];
+                wq[t][j] = v.v;
+            }
+    }
+    // ---- layer 1: pixels are the rows of the products, filters the columns
+    if (wave < 4) {
+        const float bias = b1[l16];
+        int base[T1];
+        floatx4 acc[T1];
+#pragma unroll
+        for (int j = 0; j < T1; ++j) {
+            const int t = min(rw + 4 * j, FB * 10 - 1), f = t / 10, p = t % 10 * 16 + l16;
+            base[j] = f * SP_XVEC * 16 + (p / 20 * 4 + g) * 84 + p % 20 * 4;
+            acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int kb = 0; kb < 8; ++kb) {
+            bf16x8 xv[T1];
+#pragma unroll
+            for (int j = 0; j < T1; ++j) {
+                const __bf16 *src = xs + base[j] + (kb / 2) * (SP_XROWS * 84) + 4 * (kb % 2) * 84;      // 8-byte aligned
+                const uint2 lo = *(const uint2 *)src, hi = *(const uint2 *)(src + 4);
+                Bf16x8Bits v;
+                v.u = u32x4{lo.x, lo.y, hi.x, hi.y};
+                xv[j] = v.v;
+            }
+#pragma unroll
+            for (int t = NTERM - 1; t >= 0; --t)
+#pragma unroll
+                for (int j = 0; j < T1; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[j], wq[t][kb], acc[j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int j = 0; j < T1; ++j) {
+            const int t = rw + 4 * j;
+            if (t >= FB * 10) continue;
+            const int f = t / 10, p = t % 10 * 16 + 4 * g, row = p / 20, col = p % 20;            // four pixels of one row
+            __bf16 *yp = y1 + (size_t)f * 3 * SP_Y1 + l16 * SP_PIX1 + (row >> 1) * 40 + (col >> 1) * 4 + (row & 1) * 2;
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = acc[j][r] * scale + bias;
+                v[r] = v[r] > 0.f ? v[r] : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint32_t hi, mid, lo;
+                split3_pair(v[2 * q], v[2 * q + 1], hi, mid, lo);
+                *(uint32_t *)(yp + 4 * q) = hi;
+                if (!ONE) {
+                    *(uint32_t *)(yp + SP_Y1 + 4 * q) = mid;
+                    *(uint32_t *)(yp + 2 * SP_Y1 + 4 * q) = lo;
                 }
+            }
+        }
+    } else hw.store(wsh, rt, SP_FC, SP_WP, A, Wp, Wv, rb, FastDivConst<SP_FC / 4>::get());
+    __syncthreads();
+    // ---- layer 2: filters are the rows; a wavefront takes half of the taps, its partner the other half
+    load_rows(0, 0);
+    floatx4 keep[FB];
+    if (wave >= 4) {
+        floatx4 acc[FB][2];
+        int off[FB];
+#pragma unroll
+        for (int i = 0; i < FB; ++i) {
+            const int p = min((pg + 2 * i) * 16 + l16, FB * SP_PIX2 - 1), f = p / SP_PIX2, q = p % SP_PIX2;
+            off[i] = f * 3 * SP_Y1 + (g / 2) * SP_PIX1 + (q / 9 + g % 2) * 40 + q % 9 * 4 + 8 * kh * SP_PIX1;
+            acc[i][0] = acc[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int kbl = 0; kbl < 4; ++kbl) {
+            Bf16x8Bits xv[FB][3];
+#pragma unroll
+            for (int i = 0; i < FB; ++i)
+#pragma unroll
+                for (int t = 0; t < NTERM; ++t) {
+                    const uint2 *q = (const uint2 *)(y1 + t * SP_Y1 + off[i] + 2 * kbl * SP_PIX1);      // 8-byte aligned
+                    const uint2 lo = q[0], hi = q[1];
+                    xv[i][t].u = u32x4{lo.x, lo.y, hi.x, hi.y};
+                }
+            // the six largest term products, smallest first
+            constexpr int WT[6] = {2, 1, 0, 1, 0, 0}, XT[6] = {0, 1, 2, 0, 1, 0};
+#pragma unroll
+            for (int q = ONE ? 5 : 0; q < 6; ++q)
+#pragma unroll
+                for (int i = 0; i < FB; ++i)
+#pragma unroll
+                    for (int o = 0; o < 2; ++o)
+                        acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wq[WT[q]][2 * kbl + o], xv[i][XT[q]].v, acc[i][o], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < FB; ++i) {
+            keep[i] = kh ? acc[i][1] : acc[i][0];
+            *(floatx4 *)(ex + ((rw * FB + i) * 64 + lane) * 4) = kh ? acc[i][0] : acc[i][1];      // my partner finishes that filter tile
+        }
+    }
+    __syncthreads();
+    if (wave >= 4) {
+#pragma unroll
+        for (int i = 0; i < FB; ++i) {
+            const int p = (pg + 2 * i) * 16 + l16, f = p / SP_PIX2, q = p % SP_PIX2;
+            const floatx4 other = *(const floatx4 *)(ex + (((rw ^ 1) * FB + i) * 64 + lane) * 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float v = keep[i][r] + other[r] + b2[kh * 16 + 4 * g + r];
+                if (p < FB * SP_PIX2) y2[f * SP_Y2 + (kh * 16 + 4 * g + r) * 28 + q] = v > 0.f ? v : 0.f;
             }
         }
     }
-    // Hand-off to whichever block finishes the frame last.  Order of events that makes its reads of h safe:
-    //  1. every wavefront waits until the memory system has acknowledged its own stores of h (they are device-scope
-    //     atomic stores, which the hardware writes through to the level all compute units share, and a store leaves
-    //     the wavefront's count of outstanding memory operations only when that write is acknowledged);
-    //  2. the barrier: all of the block's stores of h are therefore acknowledged before thread 0 goes on;
+    __syncthreads();
+    // ---- my outputs of the fully connected layer, over my rows
+    float4 yv[FB][4];
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            yv[f][j] = ((const float4 *)(y2 + f * SP_Y2))[min(lane + 64 * j, 223)];
+            if (rb) yv[f][j] = bf16_rne(yv[f][j]);
+            if (lane + 64 * j > 223) yv[f][j] = float4{0.f, 0.f, 0.f, 0.f};
+        }
+    float res = 0.f;                                               // lane (2 p + r) FB + f: output r of pass p, frame f
+    auto fc_pass = [&](int set, int p) {
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            float d[FB];
+#pragma unroll
+            for (int f = 0; f < FB; ++f) d[f] = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float4 w = wreg[set][r][j];
+                if (rb) w = bf16_rne(w);
+                if (odd[j]) w.w = 0.f;
+#pragma unroll
+                for (int f = 0; f < FB; ++f) d[f] += (yv[f][j].x * w.x + yv[f][j].y * w.y) + (yv[f][j].z * w.z + yv[f][j].w * w.w);
+            }
+#pragma unroll
+            for (int f = 0; f < FB; ++f) {
+                const float t = wave_sum(d[f]);
+                res = lane == (2 * p + r) * FB + f ? t : res;
+            }
+        }
+    };
+    for (int p = 0; p < passes; p += 2) {                          // the next pass's rows travel while this pass adds up
+        if (p + 1 < passes) load_rows(1, p + 1);
+        fc_pass(0, p);
+        if (p + 2 < passes) load_rows(0, p + 2);
+        if (p + 1 < passes) fc_pass(1, p + 1);
+    }
+    if (lane < 2 * passes * FB) {
+        const int pr = lane / FB, f = lane % FB;
+        // written through to where every compute unit sees it (a device-wide fence instead would write back and invalidate
+        // the whole L2 of this block's XCD, once per block)
+        if (f0 + f < B)
+            __hip_atomic_store(part + ((size_t)(f0 + f) * 3 + rg) * SP_FC + o0 + (pr / 2 * 8 + wave) * 2 + pr % 2, res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // Hand-off to whichever block finishes the group last.  Order of events that makes its reads of `part` safe:
+    //  1. every wavefront waits until the memory system has acknowledged its own stores (they are device-scope atomic
+    //     stores, which the hardware writes through to the level all compute units share, and a store leaves the
+    //     wavefront's count of outstanding memory operations only when that write is acknowledged);
+    //  2. the barrier: all of the block's stores are therefore acknowledged before thread 0 goes on;
     //  3. thread 0 draws the ticket with a device-scope read-modify-write and waits for its result;
-    //  4. the block that draws the last ticket knows that steps 1-3 of every other block are complete, and reads h
-    //     with device-scope atomic loads issued after its ticket returned: they are served from the shared level.
+    //  4. the block that draws the last ticket knows that steps 1-3 of every other block are complete, and reads the
+    //     sums with device-scope atomic loads issued after its ticket returned: they are served from the shared level.
     // No fence is used: a device-scope release or acquire fence writes back / invalidates the whole L2 of the XCD,
     // which costs more than the three kernels this one replaces when a training step shares the chip.
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
-        int *mine = ticket + frame * SP_TICKET_PITCH;
+        int *mine = ticket + fg * SP_TICKET_PITCH;
         const int t = __hip_atomic_fetch_add(mine, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = t == SLICES - 1;
+        last = t == 3 * NS - 1;
         // for the next launch (stream order puts it after this kernel's end, which completes the store)
         if (last) __hip_atomic_store(mine, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (!last) return;
-    heads_fwd_body<512, true, true, LOADS_SCALAR>((float *)(sp_smem + SP_HEADS_OFF), tid, frame, nullptr, 0, fcb, h, frame + 1, SP_FC, A, Wp, bp, Wv, bv, nullptr,
-                              logits, values, probs, uniforms, actions, rb, dA1 /* not used */, dA1);
+    // ---- heads: 8 / FB wavefronts share a frame's outputs, then one finishes it
+    const int hf = wave % FB, b = f0 + hf;
+    float4 h;
+    {
+        float q[3][4];
+        const float *src = part + (size_t)min(b, B - 1) * 3 * SP_FC + 4 * lane;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[r][e] = __hip_atomic_load(src + r * SP_FC + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float4 bias = ((const float4 *)fcb)[lane];
+        h = float4{((q[0][0] + q[1][0]) + q[2][0]) + bias.x, ((q[0][1] + q[1][1]) + q[2][1]) + bias.y,
+                   ((q[0][2] + q[1][2]) + q[2][2]) + bias.z, ((q[0][3] + q[1][3]) + q[2][3]) + bias.w};
+        h.x = h.x > 0.f ? h.x : 0.f; h.y = h.y > 0.f ? h.y : 0.f; h.z = h.z > 0.f ? h.z : 0.f; h.w = h.w > 0.f ? h.w : 0.f;
+        if (rb) h = bf16_rne(h);
+    }
+    const float obias = lane < A ? bp[lane] : bv[0];
+    const float u = actions && uniforms ? uniforms[min(b, B - 1)] : 0.f;
+#pragma unroll 2
+    for (int a = wave / FB; a <= A; a += 8 / FB) {
+        const float4 w = *(const float4 *)(wsh + a * SP_WP + 4 * lane);
+        const float d = wave_sum((h.x * w.x + h.y * w.y) + (h.z * w.z + h.w * w.w));
+        if (lane == 0) zs[hf * 64 + a] = d;
+    }
+    __syncthreads();
+    if (wave < FB && b < B) heads_finish_frame(lane, zs[hf * 64 + lane] + obias, A, b, u, logits, values, probs, actions);
 }
 
 // n-step return (text after Eq. 1) of frame i when the segments have unequal
@@ -1602,40 +1849,28 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     const float *th = c->theta2[which];
     const int nb = 2 * c->nconv;
     int first = 0;
-    if (c->fast && c->small_predict && c->ticket && c->cfrag[which] && is_aligned16(frames) && !keep_zv && with_heads &&
-        B <= SP_MAX_FRAMES && c->nconv == 2 && c->F == SP_FC && c->flat == SP_FLAT && c->off[nb] % 4 == 0 &&
-        sizeof(float) * heads_lds_floats(c->F, c->A) <= SP_HEADS_MAX) {
-        // a handful of frames: one launch for the whole network
-        static bool attr_set = false;
-        if (!attr_set) {
-#define GA3C_SP_ALLOW(ONE_, SL_)                                                                                               \
-    for (const void *k : {(const void *)predict_small_kernel<ONE_, SL_, false>, (const void *)predict_small_kernel<ONE_, SL_, true>}) \
-        HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C12_LDS_BYTES))
-            GA3C_SP_ALLOW(false, 32); GA3C_SP_ALLOW(false, 16); GA3C_SP_ALLOW(false, 8); GA3C_SP_ALLOW(false, 4);
-            GA3C_SP_ALLOW(true, 32); GA3C_SP_ALLOW(true, 16); GA3C_SP_ALLOW(true, 8); GA3C_SP_ALLOW(true, 4);
-#undef GA3C_SP_ALLOW
-            attr_set = true;
-        }
+    if (c->fast && c->small_predict && c->ticket && c->cfrag[which] && is_aligned16(frames) && !keep_zv && with_heads && B <= SP_MAX_FRAMES &&
+        c->nconv == 2 && c->F == SP_FC && c->flat == SP_FLAT && is_aligned16(th + c->off[nb + 1]) && is_aligned16(th + c->off[nb + 2])) {
+        // a handful of frames: one launch for the whole network, in about as many blocks as there are compute units
+        const bool two = B > 21 && SpLds<2>::bytes(c->A) <= HEADS_FWD_MAX_LDS;
+        const int NS = two ? (B <= 42 ? 4 : 2) : B <= 5 ? 16 : B <= 10 ? 8 : B <= 21 ? 4 : B <= 42 ? 2 : 1;
+        const int groups = two ? (B + 1) / 2 : B;
+        if ((size_t)B * 3 * SP_FC > w.ws_floats) return fail(GA3C_EINVAL, "internal: workspace too small (small predictions)");
         const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1];
         STAGE("predict_small", 2.0 * B * (g0.OHW * g0.OC * g0.K + g1.OHW * g1.OC * g1.K + (double)c->flat * c->F + c->F * (c->A + 1)),
               (double)B * g0.CHW + 4.0 * c->flat * c->F);
-        const int slices = B <= 8 ? 32 : B <= 16 ? 16 : B <= 32 ? 8 : 4;
-        const dim3 grid(B * slices), block(512);
-#define GA3C_SP_LAUNCH(ONE_, SL_) do { if (table) GA3C_SP_LAUNCH1(ONE_, SL_, true); else GA3C_SP_LAUNCH1(ONE_, SL_, false); } while (0)
-#define GA3C_SP_LAUNCH1(ONE_, SL_, TABLE_)                                                                                     \
-    ga3c::launch((predict_small_kernel<ONE_, SL_, TABLE_>), grid, block, C12_LDS_BYTES, s, frames, table, FastDiv(c->A + 1), c->cfrag[which],             \
-                       th + c->off[1], th + c->off[3], th + c->off[nb], th + c->off[nb + 1], w.h, c->ticket, c->A,            \
-                       th + c->off[nb + 2], th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5], logits, values,    \
-                       probs, uniforms, actions, 1.f / 255.f, c->rb)
-#define GA3C_SP_PICK(ONE_)                                                                                                     \
-    do {                                                                                                                       \
-        if (slices == 32) GA3C_SP_LAUNCH(ONE_, 32); else if (slices == 16) GA3C_SP_LAUNCH(ONE_, 16);                           \
-        else if (slices == 8) GA3C_SP_LAUNCH(ONE_, 8); else GA3C_SP_LAUNCH(ONE_, 4);                                           \
-    } while (0)
-        if (c->rb) GA3C_SP_PICK(true); else GA3C_SP_PICK(false);
-#undef GA3C_SP_PICK
-#undef GA3C_SP_LAUNCH
-#undef GA3C_SP_LAUNCH1
+        typedef decltype(&predict_small_kernel<false, 1, false>) PredictSmall;
+        static const PredictSmall kernels[8] = {predict_small_kernel<false, 1, false>, predict_small_kernel<false, 1, true>,
+                                                predict_small_kernel<false, 2, false>, predict_small_kernel<false, 2, true>,
+                                                predict_small_kernel<true, 1, false>,  predict_small_kernel<true, 1, true>,
+                                                predict_small_kernel<true, 2, false>,  predict_small_kernel<true, 2, true>};
+        static size_t lds_set[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        const int k = (c->rb ? 4 : 0) + (two ? 2 : 0) + (table ? 1 : 0);
+        const size_t lds = two ? SpLds<2>::bytes(c->A) : SpLds<1>::bytes(c->A);
+        HIP_TRY(allow_dynamic_lds((const void *)kernels[k], lds, lds_set[k]));
+        ga3c::launch(kernels[k], dim3((3 * NS * groups + 7) / 8 * 8), dim3(512), lds, s, frames, table, c->cfrag[which], th + c->off[1],
+                     th + c->off[3], th + c->off[nb], th + c->off[nb + 1], w.ws, c->ticket, B, NS, c->A, th + c->off[nb + 2], th + c->off[nb + 3],
+                     th + c->off[nb + 4], th + c->off[nb + 5], logits, values, probs, uniforms, actions, 1.f / 255.f, c->rb);
         HIP_TRY(hipGetLastError());
         return GA3C_OK;
     }
@@ -1738,11 +1973,26 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     }
     w.fc_ws = fc_ws; w.fc_nz = fc_nz;
     if (!with_heads) return GA3C_OK;          // the caller finishes the fc layer and the heads itself
+    const int hf = heads_loads(c->F, fc_nz, fc_ws, th + c->off[nb + 1], w.h, th + c->off[nb + 2]);
+    const int nj = c->F % 256 == 0 ? c->F / 256 : 0;
+    if (c->fast && !keep_zv && hf != LOADS_SCALAR && (nj == 1 || nj == 2 || nj == 4)) {
+        typedef decltype(&heads_predict_kernel<1, 8>) HeadsPredict;
+        static const HeadsPredict hp_kernels[6] = {heads_predict_kernel<1, 8>, heads_predict_kernel<1, 20>, heads_predict_kernel<2, 8>,
+                                                   heads_predict_kernel<2, 16>, heads_predict_kernel<4, 8>, heads_predict_kernel<4, 8>};
+        static size_t hp_lds_set[6] = {0, 0, 0, 0, 0, 0};
+        const int k = (nj == 1 ? 0 : nj == 2 ? 2 : 4) + (hf == LOADS_VEC16 ? 1 : 0);
+        const size_t lds = sizeof(float) * (c->A + 1) * (c->F + 4);
+        HIP_TRY(allow_dynamic_lds((const void *)hp_kernels[k], lds, hp_lds_set[k]));
+        STAGE("heads_fwd", 2.0 * B * c->F * (c->A + 1), 4.0 * fc_nz * B * c->F);
+        ga3c::launch(hp_kernels[k], dim3(cdiv(B, 4)), dim3(256), lds, s, fc_ws, fc_nz, th + c->off[nb + 1], B, c->A, th + c->off[nb + 2],
+                     th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5], logits, values, probs, uniforms, actions, c->rb);
+        HIP_TRY(hipGetLastError());
+        return GA3C_OK;
+    }
     const size_t hf_lds = sizeof(float) * heads_lds_floats(c->F, c->A);
     typedef decltype(&heads_fwd_kernel<LOADS_SCALAR>) HeadsFwd;
     static const HeadsFwd hf_kernels[3] = {heads_fwd_kernel<LOADS_SCALAR>, heads_fwd_kernel<LOADS_VEC8>, heads_fwd_kernel<LOADS_VEC16>};
     static size_t hf_lds_set[3] = {0, 0, 0};
-    const int hf = heads_loads(c->F, fc_nz, fc_ws, th + c->off[nb + 1], w.h, th + c->off[nb + 2]);
     HIP_TRY(allow_dynamic_lds((const void *)hf_kernels[hf], hf_lds, hf_lds_set[hf]));
     STAGE("heads_fwd", 2.0 * B * c->F * (c->A + 1), 4.0 * (fc_nz + 1) * B * c->F);
     ga3c::launch(hf_kernels[hf], dim3(cdiv(B, 4)), dim3(256), hf_lds, s, fc_ws, fc_nz,

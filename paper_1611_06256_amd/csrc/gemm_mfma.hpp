@@ -33,7 +33,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // n / d for 0 <= n < 2^31 by multiply-high and shift (d >= 1 fixed on the host).
 struct FastDiv {
     uint32_t d, mul, shift;
-    FastDiv() : d(1), mul(1), shift(0) {}
+    __host__ __device__ FastDiv() : d(1), mul(1), shift(0) {}
     explicit FastDiv(uint32_t dd) : d(dd) {
         shift = 0;
         while ((1ull << shift) < dd) ++shift;
