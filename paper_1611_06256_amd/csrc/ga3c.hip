@@ -197,6 +197,28 @@ __device__ __forceinline__ float wave_max(float v) {
     return fmaxf(fmaxf(lane_f32(v, 0), lane_f32(v, 16)), fmaxf(lane_f32(v, 32), lane_f32(v, 48)));
 }
 
+// Sums over a row's 16 lanes of two or four values at once: lane l of every row ends up with its row's sum of value l % N.
+// (Pairs of values trade halves first, so N values cost little more than one.)
+__device__ __forceinline__ float row_sums(const float (&v)[2], const int lane) {
+    const bool odd = lane & 1;
+    float t = (odd ? v[1] : v[0]) + dpp_f32<0xB1>(odd ? v[0] : v[1]);      // quad_perm [1,0,3,2]
+    t += dpp_f32<0x4E>(t);      // quad_perm [2,3,0,1]
+    t += dpp_f32<0x124>(t);     // row_ror:4
+    return t + dpp_f32<0x128>(t);
+}
+__device__ __forceinline__ float row_sums(const float (&v)[4], const int lane) {
+    const bool odd = lane & 1, up = lane & 2;
+    const float a = (odd ? v[1] : v[0]) + dpp_f32<0xB1>(odd ? v[0] : v[1]), b = (odd ? v[3] : v[2]) + dpp_f32<0xB1>(odd ? v[2] : v[3]);
+    float t = (up ? b : a) + dpp_f32<0x4E>(up ? a : b);
+    t += dpp_f32<0x124>(t);
+    return t + dpp_f32<0x128>(t);
+}
+// The sum over the four rows of what lanes 16 r + l hold, in each of them.
+__device__ __forceinline__ float across_rows(float v) {
+    v += __shfl_xor(v, 16, 64);
+    return v + __shfl_xor(v, 32, 64);
+}
+
 // Global memory answers in roughly half a microsecond, so short kernels are
 // bound by the number of dependent load rounds, not by bytes.  These helpers
 // issue a batch of independent loads (indices past the end are clamped, the
@@ -484,8 +506,8 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict_
 }
 
 // The end of a prediction, by one wavefront: lane a < A holds logit a of frame b, lane A the value.  Softmax and the draw stay
-// in registers; the sums run left to right in fp32 exactly as a single thread would form them, so the sampled action is a
-// pure function of the probabilities written out.
+// in registers; the running sums of the draw go left to right in fp32 exactly as a single thread would form them, so the
+// sampled action is a pure function of the probabilities written out.
 __device__ __forceinline__ void heads_finish_frame(const int lane, const float z, const int A, const int b, const float u, float *logits,
                                                    float *values, float *probs, int32_t *actions) {
     const bool pol = lane < A;
@@ -494,18 +516,20 @@ __device__ __forceinline__ void heads_finish_frame(const int lane, const float z
     if (!probs && !actions) return;
     const float zmax = wave_max(pol ? z : -3.4e38f);
     const float e = pol ? expf(z - zmax) : 0.f;
-    float S = 0.f;
-    for (int j = 0; j < A; ++j) S += lane_f32(e, j);
-    const float pr = e / S;
+    const float pr = e / wave_sum(e);
     if (pol && probs) probs[(size_t)b * A + lane] = pr;
     if (!actions) return;
-    // the first action whose running sum exceeds u; the last one if none does
+    // the first action whose running sum exceeds u, the last one if none does: the running sums never fall
     float c = 0.f;
-    int act = A - 1;
-    for (int j = A - 1, k = 0; k <= j; ++k) {
-        c += lane_f32(pr, k);
-        if (c > u) { act = k; break; }
+    int act = 0;
+    for (int j0 = 0; j0 < A; j0 += 8) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            c += lane_f32(pr, min(j0 + j, 63));            // zero from action A on
+            act += c > u ? 0 : 1;
+        }
     }
+    act = min(act, A - 1);
     if (lane == 0) actions[b] = act;
 }
 
@@ -599,17 +623,27 @@ __global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restr
     }
     __syncthreads();
     if (b >= B) return;
+    // sixteen outputs at a time: output a of them lands in lane a % 16 of every row, and row a / 16 keeps it
     float z = 0.f;
-#pragma unroll 4
-    for (int a = 0; a <= A; ++a) {
-        float d = 0.f;
+    for (int a0 = 0; a0 <= A; a0 += 16) {
+        float s16 = 0.f;
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const float4 w = *(const float4 *)(heads_smem + a * WP + 256 * j + 4 * lane);
-            d += (acc[j].x * w.x + acc[j].y * w.y) + (acc[j].z * w.z + acc[j].w * w.w);
+        for (int q = 0; q < 4; ++q) {
+            float d[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                d[i] = 0.f;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const float4 w = *(const float4 *)(heads_smem + min(a0 + 4 * q + i, A) * WP + 256 * j + 4 * lane);
+                    d[i] += (acc[j].x * w.x + acc[j].y * w.y) + (acc[j].z * w.z + acc[j].w * w.w);
+                }
+            }
+            const float t = row_sums(d, lane);
+            s16 = (lane >> 2 & 3) == q ? t : s16;
         }
-        d = wave_sum(d);
-        z = lane == a ? d : z;
+        s16 = across_rows(s16);
+        z = lane >> 4 == a0 >> 4 ? s16 : z;
     }
     heads_finish_frame(lane, z + obias, A, b, u, logits, values, probs, actions);
 }
@@ -619,8 +653,8 @@ __global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restr
 //
 // A block takes FB frames, three of the nine output rows of layer 2 (`rg`; they need 36 of the frame's 84 rows and 8 of
 // layer 1's 20) and 256 / NS outputs of the fully connected layer, for which it forms the sums over its rows.  Wavefronts 0..3
-// run layer 1 from LDS (as in conv12_fused.hpp), then wavefronts 4..7 layer 2, and all eight the fc sums, two outputs per
-// wavefront and pass, whose weights are on their way while the convolutions run.  The block that finishes a frame group last
+// run layer 1 from LDS (as in conv12_fused.hpp), then all eight layer 2, a quarter of its taps and half of the pixel tiles each,
+// and the fc sums, two outputs per wavefront and pass, whose weights are on their way while layer 2 runs.  The block that finishes a frame group last
 // (a ticket per group; nobody waits for anybody) adds the three row groups up and runs the heads, the softmax and the draw.
 // Blocks in order of (row group, slice): an XCD reads few parts of the fc weights.
 // Latency: nothing is large.  One frame 15.8 -> @1@ us a call, 37 frames 23.9 -> @37@ us against a kernel whose blocks each ran
@@ -634,8 +668,8 @@ constexpr int SP_Y2 = 32 * 28;                             // floats of its laye
 constexpr int SP_WP = SP_FC + 4;
 template <int FB>
 struct SpLds {
-    static constexpr int XS = 0, FR = XS + FB * SP_XVEC * 32, Y1 = FR + 3 * 8 * 64 * 16, EX = Y1 + FB * 3 * SP_Y1 * 2, Y2 = EX + FB * 4096,
-                         ZS = Y2 + FB * SP_Y2 * 4, WS = ZS + FB * 256;
+    static constexpr int XS = 0, FR = XS + FB * SP_XVEC * 32, EX = FR,      // layer 1's filters, later layer 2's partial sums
+                         Y1 = FR + (FB == 1 ? 3 * 8 * 64 * 16 : FB * 16384), Y2 = Y1 + FB * 3 * SP_Y1 * 2, ZS = Y2 + FB * SP_Y2 * 4, WS = ZS + FB * 256;
     static size_t bytes(int A) { return WS + sizeof(float) * (A + 1) * SP_WP; }
 };
 
@@ -721,10 +755,21 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
         for (int i = 0; i < FPT; ++i) ((u32x4 *)(sp_smem + L::FR))[rt + 256 * i] = fpre[i];
     }
     __syncthreads();
-    const int pg = rw >> 1, kh = rw & 1;                           // layer 2: pixel tiles pg, pg + 2, ..; taps 128 kh ..
-    bf16x8 wq[NTERM][8];
+    const int pg = wave >> 2;                                      // layer 2: pixel tiles pg, pg + 2, ..; taps 64 rw ..
+    bf16x8 wq[NTERM][8], w2[NTERM][4];                             // w2: slot 2 kb + filter tile
     {
-        const u32x4 *src = wave < 4 ? (const u32x4 *)(sp_smem + L::FR) + lane : frag + (size_t)(1 + kh) * C12_FRAG_SET + lane;
+        const u32x4 *src = frag + (size_t)(1 + (rw >> 1)) * C12_FRAG_SET + (rw & 1) * 4 * 64 + lane;
+#pragma unroll
+        for (int t = 0; t < NTERM; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                Bf16x8Bits v;
+                v.u = src[(t * 8 + j) * 64];
+                w2[t][j] = v.v;
+            }
+    }
+    if (wave < 4) {
+        const u32x4 *src = (const u32x4 *)(sp_smem + L::FR) + lane;
 #pragma unroll
         for (int t = 0; t < NTERM; ++t)
 #pragma unroll
@@ -786,29 +831,27 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
         }
     } else hw.store(wsh, rt, SP_FC, SP_WP, A, Wp, Wv, rb, FastDivConst<SP_FC / 4>::get());
     __syncthreads();
-    // ---- layer 2: filters are the rows; a wavefront takes half of the taps, its partner the other half
+    // ---- layer 2: filters are the rows
     load_rows(0, 0);
-    floatx4 keep[FB];
-    if (wave >= 4) {
+    {
         floatx4 acc[FB][2];
-        int off[FB];
+        Bf16x8Bits xv[2][FB][NTERM];
 #pragma unroll
         for (int i = 0; i < FB; ++i) {
             const int p = min((pg + 2 * i) * 16 + l16, FB * SP_PIX2 - 1), f = p / SP_PIX2, q = p % SP_PIX2;
-            off[i] = f * 3 * SP_Y1 + (g / 2) * SP_PIX1 + (q / 9 + g % 2) * 40 + q % 9 * 4 + 8 * kh * SP_PIX1;
+            const __bf16 *src = y1 + f * 3 * SP_Y1 + (g / 2 + 4 * rw) * SP_PIX1 + (q / 9 + g % 2) * 40 + q % 9 * 4;
             acc[i][0] = acc[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
-        }
 #pragma unroll
-        for (int kbl = 0; kbl < 4; ++kbl) {
-            Bf16x8Bits xv[FB][3];
-#pragma unroll
-            for (int i = 0; i < FB; ++i)
+            for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                 for (int t = 0; t < NTERM; ++t) {
-                    const uint2 *q = (const uint2 *)(y1 + t * SP_Y1 + off[i] + 2 * kbl * SP_PIX1);      // 8-byte aligned
-                    const uint2 lo = q[0], hi = q[1];
-                    xv[i][t].u = u32x4{lo.x, lo.y, hi.x, hi.y};
+                    const uint2 *q2 = (const uint2 *)(src + t * SP_Y1 + 2 * kb * SP_PIX1);      // 8-byte aligned
+                    const uint2 lo = q2[0], hi = q2[1];
+                    xv[kb][i][t].u = u32x4{lo.x, lo.y, hi.x, hi.y};
                 }
+        }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
             // the six largest term products, smallest first
             constexpr int WT[6] = {2, 1, 0, 1, 0, 0}, XT[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
@@ -817,24 +860,24 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
                 for (int i = 0; i < FB; ++i)
 #pragma unroll
                     for (int o = 0; o < 2; ++o)
-                        acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wq[WT[q]][2 * kbl + o], xv[i][XT[q]].v, acc[i][o], 0, 0, 0);
+                        acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[WT[q]][2 * kb + o], xv[kb][i][XT[q]].v, acc[i][o], 0, 0, 0);
         }
 #pragma unroll
-        for (int i = 0; i < FB; ++i) {
-            keep[i] = kh ? acc[i][1] : acc[i][0];
-            *(floatx4 *)(ex + ((rw * FB + i) * 64 + lane) * 4) = kh ? acc[i][0] : acc[i][1];      // my partner finishes that filter tile
-        }
+        for (int i = 0; i < FB; ++i)
+#pragma unroll
+            for (int o = 0; o < 2; ++o) *(floatx4 *)(ex + ((rw * 4 * FB + (pg + 2 * i) * 2 + o) * 64 + lane) * 4) = acc[i][o];
     }
     __syncthreads();
-    if (wave >= 4) {
+    for (int e = tid; e < 4 * FB * 64; e += 512) {                 // (pixel tile, filter tile, lane)
+        const int el = e & 63, o = e >> 6 & 1, p = (e >> 7) * 16 + (el & 15), f = p / SP_PIX2, q = p % SP_PIX2, oc = o * 16 + (el >> 4) * 4;
+        floatx4 s[4];
 #pragma unroll
-        for (int i = 0; i < FB; ++i) {
-            const int p = (pg + 2 * i) * 16 + l16, f = p / SP_PIX2, q = p % SP_PIX2;
-            const floatx4 other = *(const floatx4 *)(ex + (((rw ^ 1) * FB + i) * 64 + lane) * 4);
+        for (int k = 0; k < 4; ++k) s[k] = *(const floatx4 *)(ex + (k * 4 * FB * 64 + e) * 4);
+        if (p < FB * SP_PIX2) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float v = keep[i][r] + other[r] + b2[kh * 16 + 4 * g + r];
-                if (p < FB * SP_PIX2) y2[f * SP_Y2 + (kh * 16 + 4 * g + r) * 28 + q] = v > 0.f ? v : 0.f;
+                const float v = ((s[0][r] + s[1][r]) + (s[2][r] + s[3][r])) + b2[oc + r];
+                y2[f * SP_Y2 + (oc + r) * 28 + q] = v > 0.f ? v : 0.f;
             }
         }
     }
@@ -849,27 +892,28 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
             if (rb) yv[f][j] = bf16_rne(yv[f][j]);
             if (lane + 64 * j > 223) yv[f][j] = float4{0.f, 0.f, 0.f, 0.f};
         }
-    float res = 0.f;                                               // lane (2 p + r) FB + f: output r of pass p, frame f
+    // lane 2 FB (p % PG) + 2 f + r of every row, register p / PG: the row's share of output r of pass p, frame f
+    constexpr int PG = 8 / FB;
+    float res[2] = {0.f, 0.f};
     auto fc_pass = [&](int set, int p) {
+        float d[2 * FB];
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            float d[FB];
 #pragma unroll
-            for (int f = 0; f < FB; ++f) d[f] = 0.f;
+            for (int f = 0; f < FB; ++f) d[2 * f + r] = 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 float4 w = wreg[set][r][j];
                 if (rb) w = bf16_rne(w);
                 if (odd[j]) w.w = 0.f;
 #pragma unroll
-                for (int f = 0; f < FB; ++f) d[f] += (yv[f][j].x * w.x + yv[f][j].y * w.y) + (yv[f][j].z * w.z + yv[f][j].w * w.w);
-            }
-#pragma unroll
-            for (int f = 0; f < FB; ++f) {
-                const float t = wave_sum(d[f]);
-                res = lane == (2 * p + r) * FB + f ? t : res;
+                for (int f = 0; f < FB; ++f) d[2 * f + r] += (yv[f][j].x * w.x + yv[f][j].y * w.y) + (yv[f][j].z * w.z + yv[f][j].w * w.w);
             }
         }
+        const float t = row_sums(d, lane);
+        const bool mine = (lane & 15) / (2 * FB) == p % PG;
+        res[0] = mine && p < PG ? t : res[0];
+        res[1] = mine && p >= PG ? t : res[1];
     };
     for (int p = 0; p < passes; p += 2) {                          // the next pass's rows travel while this pass adds up
         if (p + 1 < passes) load_rows(1, p + 1);
@@ -877,12 +921,14 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
         if (p + 2 < passes) load_rows(0, p + 2);
         if (p + 1 < passes) fc_pass(1, p + 1);
     }
-    if (lane < 2 * passes * FB) {
-        const int pr = lane / FB, f = lane % FB;
+    {
+        const float v0 = across_rows(res[0]), v1 = across_rows(res[1]);
+        const int p = (lane & 15) / (2 * FB) + (lane >> 4) * PG, f = (lane & 15) % (2 * FB) / 2, r = lane & 1;
         // written through to where every compute unit sees it (a device-wide fence instead would write back and invalidate
         // the whole L2 of this block's XCD, once per block)
-        if (f0 + f < B)
-            __hip_atomic_store(part + ((size_t)(f0 + f) * 3 + rg) * SP_FC + o0 + (pr / 2 * 8 + wave) * 2 + pr % 2, res, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane < 32 && p < passes && f0 + f < B)
+            __hip_atomic_store(part + ((size_t)(f0 + f) * 3 + rg) * SP_FC + o0 + (p * 8 + wave) * 2 + r, lane < 16 ? v0 : v1, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
     }
     // Hand-off to whichever block finishes the group last.  Order of events that makes its reads of `part` safe:
     //  1. every wavefront waits until the memory system has acknowledged its own stores (they are device-scope atomic
@@ -923,11 +969,15 @@ __global__ __launch_bounds__(512, 1) void predict_small_kernel(
     }
     const float obias = lane < A ? bp[lane] : bv[0];
     const float u = actions && uniforms ? uniforms[min(b, B - 1)] : 0.f;
-#pragma unroll 2
-    for (int a = wave / FB; a <= A; a += 8 / FB) {
-        const float4 w = *(const float4 *)(wsh + a * SP_WP + 4 * lane);
-        const float d = wave_sum((h.x * w.x + h.y * w.y) + (h.z * w.z + h.w * w.w));
-        if (lane == 0) zs[hf * 64 + a] = d;
+    for (int a0 = wave / FB * 4; a0 <= A; a0 += 32 / FB) {         // four outputs at a time
+        float d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float4 w = *(const float4 *)(wsh + min(a0 + i, A) * SP_WP + 4 * lane);
+            d[i] = (h.x * w.x + h.y * w.y) + (h.z * w.z + h.w * w.w);
+        }
+        const float t = across_rows(row_sums(d, lane));
+        if (lane < 4 && a0 + lane <= A) zs[hf * 64 + a0 + lane] = t;
     }
     __syncthreads();
     if (wave < FB && b < B) heads_finish_frame(lane, zs[hf * 64 + lane] + obias, A, b, u, logits, values, probs, actions);
