@@ -1716,15 +1716,16 @@ int fence_wait(hipStream_t s, hipEvent_t ev, bool set, hipStream_t where) {
 }
 int wait_ready(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(s, c->ev_ready[i], c->ready_set[i], c->ready_stream[i]); }
 int wait_readers(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(s, c->ev_readers[i], c->readers_set[i], c->readers_stream[i]); }
-// A call marks its event as set by its last launch (next_stop, launch.hpp) or records it where that launch did not take it.
-int mark(hipEvent_t ev, bool &set, hipStream_t &where, hipStream_t s, bool attached) {
-    if (!attached || ga3c::next_stop) HIP_TRY(hipEventRecord(ev, s));
-    ga3c::next_stop = nullptr;
-    set = true; where = s;
+int mark_ready(ga3c_ctx *c, int i, hipStream_t s) {
+    HIP_TRY(hipEventRecord(c->ev_ready[i], s));
+    c->ready_set[i] = true; c->ready_stream[i] = s;
     return GA3C_OK;
 }
-int mark_ready(ga3c_ctx *c, int i, hipStream_t s, bool attached = false) { return mark(c->ev_ready[i], c->ready_set[i], c->ready_stream[i], s, attached); }
-int mark_readers(ga3c_ctx *c, int i, hipStream_t s, bool attached = false) { return mark(c->ev_readers[i], c->readers_set[i], c->readers_stream[i], s, attached); }
+int mark_readers(ga3c_ctx *c, int i, hipStream_t s) {
+    HIP_TRY(hipEventRecord(c->ev_readers[i], s));
+    c->readers_set[i] = true; c->readers_stream[i] = s;
+    return GA3C_OK;
+}
 #define TRY(expr) do { int rc_ = (expr); if (rc_ != GA3C_OK) return rc_; } while (0)
 
 // While one of these is alive and profiling is on, every kernel launched by this host thread carries an event pair
@@ -1852,8 +1853,7 @@ inline bool spec_matches(const ConvGeom &g, bool byte_input) {
 inline bool is_aligned16(const void *p) { return (((uintptr_t)p) & 15) == 0; }
 
 // Things derived from parameter copy i, rebuilt on s after that copy was written there.
-// `stop`: the event that the last launch completes; needs a context with fragments of the larger net or of the any-size kernels.
-int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, hipEvent_t stop = nullptr) {
+int refresh_derived(ga3c_ctx *c, int i, hipStream_t s) {
     if (c->cfrag[i]) {
         HIP_TRY(launch_conv12_filter_fragments(c->theta2[i] + c->off[0], c->theta2[i] + c->off[2], c->cfrag[i], s, c->rb));
         if (c->cfrag_dgrad)
@@ -1861,7 +1861,6 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, hipEvent_t stop = nullptr
     }
     if (c->lfrag[i]) {
         const float *w2 = c->theta2[i] + c->off[2], *w3 = c->theta2[i] + c->off[4];
-        if (!c->bfrag[i]) ga3c::next_stop = stop;
         ga3c::launch(large_filter_fragments_kernel, dim3(LFRAG_B3), dim3(256), 0, s, w2, w3, c->lfrag[i]);
         HIP_TRY(hipGetLastError());
     }
@@ -1878,7 +1877,6 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, hipEvent_t stop = nullptr
             const ConvGeom &g = c->geom[l];
             add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
         }
-        ga3c::next_stop = stop;
         ga3c::launch(band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
         HIP_TRY(hipGetLastError());
     }
@@ -1895,9 +1893,9 @@ bool on_band_kernels(const ConvGeom &g, int l) {
 }
 
 // Forward pass of `B` frames into `w`; heads outputs to the optional pointers.  table (frames is nullptr then): the frames lie
-// where its entries point; only where takes_frame_table says so.  stop: the event that the last kernel completes.
+// where its entries point; only where takes_frame_table says so.
 int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_t *const *table, int B, bool keep_zv, float *logits, float *values,
-            float *probs, const float *uniforms, int32_t *actions, hipStream_t s, bool with_heads = true, hipEvent_t stop = nullptr) {
+            float *probs, const float *uniforms, int32_t *actions, hipStream_t s, bool with_heads = true) {
     const float *th = c->theta2[which];
     const int nb = 2 * c->nconv;
     int first = 0;
@@ -1920,7 +1918,6 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         const int k = (c->rb ? 4 : 0) + (two ? 2 : 0) + (table ? 1 : 0);
         const size_t lds = two ? SpLds<2>::bytes(c->A) : SpLds<1>::bytes(c->A);
         HIP_TRY(allow_dynamic_lds((const void *)kernels[k], lds, lds_set[k]));
-        ga3c::next_stop = stop;
         ga3c::launch(kernels[k], dim3((3 * NS * groups + 7) / 8 * 8), dim3(512), lds, s, frames, table, c->cfrag[which], th + c->off[1],
                      th + c->off[3], th + c->off[nb], th + c->off[nb + 1], w.ws, c->ticket, B, NS, c->A, th + c->off[nb + 2], th + c->off[nb + 3],
                      th + c->off[nb + 4], th + c->off[nb + 5], logits, values, probs, uniforms, actions, 1.f / 255.f, c->rb);
@@ -2037,7 +2034,6 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         const size_t lds = sizeof(float) * (c->A + 1) * (c->F + 4);
         HIP_TRY(allow_dynamic_lds((const void *)hp_kernels[k], lds, hp_lds_set[k]));
         STAGE("heads_fwd", 2.0 * B * c->F * (c->A + 1), 4.0 * fc_nz * B * c->F);
-        ga3c::next_stop = stop;
         ga3c::launch(hp_kernels[k], dim3(cdiv(B, 4)), dim3(256), lds, s, fc_ws, fc_nz, th + c->off[nb + 1], B, c->A, th + c->off[nb + 2],
                      th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5], logits, values, probs, uniforms, actions, c->rb);
         HIP_TRY(hipGetLastError());
@@ -2049,7 +2045,6 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     static size_t hf_lds_set[3] = {0, 0, 0};
     HIP_TRY(allow_dynamic_lds((const void *)hf_kernels[hf], hf_lds, hf_lds_set[hf]));
     STAGE("heads_fwd", 2.0 * B * c->F * (c->A + 1), 4.0 * (fc_nz + 1) * B * c->F);
-    ga3c::next_stop = stop;
     ga3c::launch(hf_kernels[hf], dim3(cdiv(B, 4)), dim3(256), hf_lds, s, fc_ws, fc_nz,
                        th + c->off[nb + 1], w.h, B, c->F, c->A, th + c->off[nb + 2],
                        th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5],
@@ -2181,13 +2176,11 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         if (e != hipSuccess) { guard(fail(GA3C_EHIP, "hipMemcpy: %s", hipGetErrorString(e))); break; }
         g.koff = c->koff[l];
     }
-    // these events order kernels of one device and nobody inspects them: no fence to the host's memory (1.5 us of each call)
-    constexpr unsigned order_only = hipEventDisableTiming | hipEventDisableSystemFence;
     for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
         guard(dmalloc((void **)&c->theta2[i], sizeof(float) * c->P));
-        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_ready[i], order_only) != hipSuccess)
+        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_ready[i], hipEventDisableTiming) != hipSuccess)
             guard(fail(GA3C_EHIP, "hipEventCreate failed"));
-        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_readers[i], order_only) != hipSuccess)
+        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_readers[i], hipEventDisableTiming) != hipSuccess)
             guard(fail(GA3C_EHIP, "hipEventCreate failed"));
     }
     if (rc == GA3C_OK) guard(dmalloc((void **)&c->g, sizeof(float) * c->P));
@@ -2369,9 +2362,9 @@ static int predict_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *const
     hipStream_t s = (hipStream_t)stream;
     const int cur = c->cur;
     TRY(wait_ready(c, cur, s));
-    const int rc = forward(c, cur, c->pred, frames, table, B, false, logits, values, probs, uniforms, actions, s, true, c->ev_readers[cur]);
-    if (rc != GA3C_OK) { ga3c::next_stop = nullptr; return rc; }
-    TRY(mark_readers(c, cur, s, true));
+    const int rc = forward(c, cur, c->pred, frames, table, B, false, logits, values, probs, uniforms, actions, s);
+    if (rc != GA3C_OK) return rc;
+    TRY(mark_readers(c, cur, s));
     return GA3C_OK;
 }
 
@@ -2658,13 +2651,11 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     RmsClip ca;
     ca.normpart = c->partials; ca.nnorm = red_blocks; ca.losspart = losspart; ca.nloss = nloss; ca.clip = hp->clip_norm;
     ca.scale_out = c->scale; ca.own = c->stats; ca.user = stats;
-    const bool derived = c->lfrag[cur ^ 1] || c->bfrag[cur ^ 1];      // the fragments follow the new parameters, in a launch of their own
-    if (!derived) ga3c::next_stop = c->ev_ready[cur ^ 1];
     ga3c::launch((rmsprop_kernel<0, 1>), dim3(rb), dim3(256), 0, s, th, c->theta2[cur ^ 1], c->g, c->grad, c->P, (const float *)nullptr,
                        1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[cur ^ 1], (unsigned)c->off[0], (unsigned)c->off[2], c->rb, ca);
     HIP_TRY(hipGetLastError());
-    if (derived) TRY(refresh_derived(c, cur ^ 1, s, c->ev_ready[cur ^ 1]));
-    TRY(mark_ready(c, cur ^ 1, s, true));
+    if (c->lfrag[cur ^ 1] || c->bfrag[cur ^ 1]) TRY(refresh_derived(c, cur ^ 1, s));      // the larger net's fragments follow the new parameters
+    TRY(mark_ready(c, cur ^ 1, s));
     c->cur = cur ^ 1;        // calls enqueued from now on see the new parameters
     return GA3C_OK;
 }

@@ -24,11 +24,6 @@ protected:
 // the open stage timer of this host thread, if any
 inline thread_local LaunchTimer *launch_timer = nullptr;
 
-// An event that the next launch of this host thread shall complete.  It then is the dispatch's own completion signal; an
-// event recorded behind the launch is one more packet for the queue, 1.5 to 3 us of the stream's time.  Untouched by a timed
-// launch (which has events of its own): whoever set it records it then.
-inline thread_local hipEvent_t next_stop = nullptr;
-
 namespace detail {
 template <typename... KArgs, size_t... I>
 inline hipError_t launch_timed(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, hipEvent_t a,
@@ -46,12 +41,6 @@ inline void launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, 
     if (launch_timer && launch_timer->next_events(&a, &b)) {
         std::tuple<KArgs...> held{static_cast<KArgs>(args)...};
         (void)detail::launch_timed(kernel, grid, block, lds, s, a, b, held, std::index_sequence_for<KArgs...>{});
-        return;
-    }
-    if (next_stop) {
-        std::tuple<KArgs...> held{static_cast<KArgs>(args)...};
-        (void)detail::launch_timed(kernel, grid, block, lds, s, nullptr, next_stop, held, std::index_sequence_for<KArgs...>{});
-        next_stop = nullptr;
         return;
     }
     hipLaunchKernelGGL(kernel, grid, block, lds, s, static_cast<KArgs>(args)...);
