@@ -139,6 +139,8 @@ struct ga3c_ctx {
     hipEvent_t ev_ready[2], ev_readers[2];
     hipStream_t ready_stream[2], readers_stream[2];   // where each event was last recorded
     bool ready_set[2], readers_set[2];
+    bool entered, several_streams;                    // whether a call came yet, and on more than one stream
+    hipStream_t first_stream;
     float *g, *grad;
     // small net: conv1/conv2 filters of each parameter copy as split MFMA fragments (nullptr for other nets), forward
     // kernel's first, then (at CFRAG_FWD_VECS) the input-gradient kernel's; refreshed by whoever writes the copy
@@ -657,7 +659,7 @@ __global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restr
 // and the fc sums, two outputs per wavefront and pass, whose weights are on their way while layer 2 runs.  The block that finishes a frame group last
 // (a ticket per group; nobody waits for anybody) adds the three row groups up and runs the heads, the softmax and the draw.
 // Blocks in order of (row group, slice): an XCD reads few parts of the fc weights.
-// Latency: nothing is large.  One frame 15.8 -> @1@ us a call, 37 frames 23.9 -> @37@ us against a kernel whose blocks each ran
+// Latency: nothing is large.  One frame 15.8 -> 9.6 us a call, 37 frames 23.9 -> 15.8 us against a kernel whose blocks each ran
 // both layers of a whole frame.
 constexpr int SP_FC = 256, SP_FLAT = 2592, SP_MAX_FRAMES = 64;
 constexpr int SP_TICKET_PITCH = 32;                        // ints between two groups' counters: a cache line each
@@ -1706,26 +1708,42 @@ __global__ __launch_bounds__(256) void copy_kernel(float *__restrict__ dst, cons
 
 // ------------------------------------------------------------ host helpers --
 
-// Event fences between the calls of a context.  A wait is skipped when the
-// event was last recorded on the same stream (stream order already holds) or
-// never recorded.
-int fence_wait(hipStream_t s, hipEvent_t ev, bool set, hipStream_t where) {
-    if (!set || where == s) return GA3C_OK;
+// Event fences between the calls of a context.  As long as all calls come on one stream, the stream's order is all that
+// is needed and no event is recorded (a record behind a prediction costs 1.5 to 3 us of the stream's time, a fifth of a
+// prediction of one frame).  The first call on another stream records what the calls so far have left on the first one, and
+// from then on every call records its own.  A wait is skipped when the event was last recorded on the same stream or never.
+int enter(ga3c_ctx *c, hipStream_t s) {
+    if (c->several_streams) return GA3C_OK;
+    if (!c->entered) { c->entered = true; c->first_stream = s; return GA3C_OK; }
+    if (s == c->first_stream) return GA3C_OK;
+    c->several_streams = true;
+    for (int i = 0; i < 2; ++i) {
+        hipError_t e = hipSuccess;
+        if (c->ready_set[i]) e = hipEventRecord(c->ev_ready[i], c->first_stream);
+        if (e == hipSuccess && c->readers_set[i]) e = hipEventRecord(c->ev_readers[i], c->first_stream);
+        if (e != hipSuccess) {                  // the first stream is gone: whatever it still had to do is over after this
+            (void)hipGetLastError();
+            HIP_TRY(hipDeviceSynchronize());
+            c->ready_set[0] = c->ready_set[1] = c->readers_set[0] = c->readers_set[1] = false;
+            return GA3C_OK;
+        }
+    }
+    return GA3C_OK;
+}
+int fence_wait(const ga3c_ctx *c, hipStream_t s, hipEvent_t ev, bool set, hipStream_t where) {
+    if (!c->several_streams || !set || where == s) return GA3C_OK;
     HIP_TRY(hipStreamWaitEvent(s, ev, 0));
     return GA3C_OK;
 }
-int wait_ready(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(s, c->ev_ready[i], c->ready_set[i], c->ready_stream[i]); }
-int wait_readers(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(s, c->ev_readers[i], c->readers_set[i], c->readers_stream[i]); }
-int mark_ready(ga3c_ctx *c, int i, hipStream_t s) {
-    HIP_TRY(hipEventRecord(c->ev_ready[i], s));
-    c->ready_set[i] = true; c->ready_stream[i] = s;
+int wait_ready(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(c, s, c->ev_ready[i], c->ready_set[i], c->ready_stream[i]); }
+int wait_readers(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(c, s, c->ev_readers[i], c->readers_set[i], c->readers_stream[i]); }
+int mark(const ga3c_ctx *c, hipEvent_t ev, bool &set, hipStream_t &where, hipStream_t s) {
+    if (c->several_streams) HIP_TRY(hipEventRecord(ev, s));
+    set = true; where = s;
     return GA3C_OK;
 }
-int mark_readers(ga3c_ctx *c, int i, hipStream_t s) {
-    HIP_TRY(hipEventRecord(c->ev_readers[i], s));
-    c->readers_set[i] = true; c->readers_stream[i] = s;
-    return GA3C_OK;
-}
+int mark_ready(ga3c_ctx *c, int i, hipStream_t s) { return mark(c, c->ev_ready[i], c->ready_set[i], c->ready_stream[i], s); }
+int mark_readers(ga3c_ctx *c, int i, hipStream_t s) { return mark(c, c->ev_readers[i], c->readers_set[i], c->readers_stream[i], s); }
 #define TRY(expr) do { int rc_ = (expr); if (rc_ != GA3C_OK) return rc_; } while (0)
 
 // While one of these is alive and profiling is on, every kernel launched by this host thread carries an event pair
@@ -2176,11 +2194,13 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         if (e != hipSuccess) { guard(fail(GA3C_EHIP, "hipMemcpy: %s", hipGetErrorString(e))); break; }
         g.koff = c->koff[l];
     }
+    // these events order kernels of one device and nobody inspects them: no fence to the host's memory (1 us of each call)
+    constexpr unsigned order_only = hipEventDisableTiming | hipEventDisableSystemFence;
     for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
         guard(dmalloc((void **)&c->theta2[i], sizeof(float) * c->P));
-        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_ready[i], hipEventDisableTiming) != hipSuccess)
+        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_ready[i], order_only) != hipSuccess)
             guard(fail(GA3C_EHIP, "hipEventCreate failed"));
-        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_readers[i], hipEventDisableTiming) != hipSuccess)
+        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_readers[i], order_only) != hipSuccess)
             guard(fail(GA3C_EHIP, "hipEventCreate failed"));
     }
     if (rc == GA3C_OK) guard(dmalloc((void **)&c->g, sizeof(float) * c->P));
@@ -2299,6 +2319,7 @@ extern "C" int ga3c_params_init(ga3c_ctx *c, uint64_t seed, void *stream) {
     hipStream_t s = (hipStream_t)stream;
     float *theta = c->theta2[c->cur];
     // wait for whoever wrote or still reads this copy
+    TRY(enter(c, s));
     TRY(wait_ready(c, c->cur, s));
     TRY(wait_readers(c, c->cur, s));
     ga3c::launch(fill_kernel, dim3(blocks_for(c->P)), dim3(256), 0, s, theta, c->P, 0.f);
@@ -2330,6 +2351,7 @@ extern "C" int ga3c_params_get(ga3c_ctx *c, int which, float *dst, size_t n, voi
     if (!c || !dst) return fail(GA3C_EINVAL, "ga3c_params_get: null argument");
     float *src = select_buffer(c, which);
     if (!src || n != c->P) return fail(GA3C_EINVAL, "ga3c_params_get: which must be 0..2 and n the parameter count");
+    TRY(enter(c, (hipStream_t)stream));
     TRY(wait_ready(c, c->cur, (hipStream_t)stream));
     const size_t n4 = is_aligned16(dst) && is_aligned16(src) ? n / 4 : 0;
     ga3c::launch(copy_kernel, dim3(std::min(blocks_for(n4 ? n4 : n), 4096u)), dim3(256), 0, (hipStream_t)stream, dst, (const float *)src, n, n4);
@@ -2342,6 +2364,7 @@ extern "C" int ga3c_params_set(ga3c_ctx *c, int which, const float *src, size_t 
     if ((which != 0 && which != 1) || n != c->P)
         return fail(GA3C_EINVAL, "ga3c_params_set: which must be 0 or 1 and n the parameter count");
     hipStream_t s = (hipStream_t)stream;
+    TRY(enter(c, s));
     TRY(wait_ready(c, c->cur, s));
     TRY(wait_readers(c, c->cur, s));
     HIP_TRY(hipMemcpyAsync(select_buffer(c, which), src, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
@@ -2361,6 +2384,7 @@ static int predict_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *const
     if (actions && !uniforms) return fail(GA3C_EINVAL, "ga3c_predict: actions requested without uniforms");
     hipStream_t s = (hipStream_t)stream;
     const int cur = c->cur;
+    TRY(enter(c, s));
     TRY(wait_ready(c, cur, s));
     const int rc = forward(c, cur, c->pred, frames, table, B, false, logits, values, probs, uniforms, actions, s);
     if (rc != GA3C_OK) return rc;
@@ -2385,6 +2409,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
 
     const int cur = c->cur;
     const float *th = c->theta2[cur];
+    TRY(enter(c, s));
     TRY(wait_ready(c, cur, s));
     // One kernel finishes the fc layer, runs the heads, the loss and the heads' backward pass, if its LDS fits.
     const size_t ht_lds = sizeof(float) * (size_t)heads_train_lds_floats(F, A);
