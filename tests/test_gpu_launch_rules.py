@@ -1,0 +1,82 @@
+"""The batch sizes at which a launch rule of the prediction and update paths changes its kernel or its split of the work,
+and the order of calls that come on more than one stream."""
+import numpy as np
+import pytest
+
+import ga3c_synth as synth
+import test_gpu_parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def G():
+    import torch
+    import paper_1611_06256_amd as g
+    assert torch.cuda.is_available()
+    return g
+
+
+@pytest.mark.parametrize("A,batches", [(18, (1, 2, 5, 6, 10, 11, 21, 22, 42, 43, 64, 65)), (63, (4, 9, 20, 41, 64))])
+def test_small_net_predictions_across_the_splits_of_a_frame(G, A, batches):
+    # up to 64 frames one launch; the slices of the fc layer per frame and the frames per block change with the batch,
+    # and many actions leave no room in LDS for two frames
+    for B in batches:
+        P.check_predict(G, G.SMALL_NET(A), B, 7000 + B)
+
+
+@pytest.mark.parametrize("F,B", [(256, 3), (256, 66), (512, 1), (512, 5), (512, 130), (1024, 2), (1024, 65)])
+def test_heads_after_few_and_many_partial_sums(G, F, B):
+    desc = G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=18)
+    P.check_predict(G, desc, B, 7100 + B)
+
+
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("N", [128, 129])
+def test_fc_gradients_where_the_tile_changes(G, N, math):
+    desc = G.SMALL_NET(6)
+    desc.math = math
+    P.run_train(G, desc, N, 5, 7200 + N, dict(clip_norm=40.0), frames=synth.rectangle_frames(7201, N * 5).reshape(N, 5, 4, 84, 84))
+
+
+def test_parameters_read_out_to_any_place(G):
+    import torch
+    net, _, theta = P.make(G, G.NetDesc(**P.ODD), 1, 0, 7300)
+    for off in range(5):
+        buf = torch.full((net.n_params + 9,), 7.0, device="cuda")
+        net.params_get(0, out=buf[off:off + net.n_params])
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy()
+        np.testing.assert_array_equal(got[off:off + net.n_params], theta)
+        assert (got[:off] == 7).all() and (got[off + net.n_params:] == 7).all()
+    net.close()
+
+
+def test_calls_that_move_to_a_second_stream_wait_for_the_first(G):
+    # one stream alone records no event; the first call elsewhere has to wait for everything before it all the same
+    import torch
+    N, T, A = 128, 5, 18
+    desc = G.SMALL_NET(A)
+    frames = torch.from_numpy(synth.rectangle_frames(7401, N * T).reshape(N, T, 4, 84, 84)).cuda()
+    first = frames[:, 0].contiguous()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(7402, N, T, A).items()}
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = []
+    for several in (False, True):
+        net = G.Ga3c(desc, N, N * T)
+        a, b = streams if several else streams[:1] * 2
+        out = torch.empty(N, A, device="cuda")
+        torch.cuda.synchronize()
+        print("several streams" if several else "one stream", flush=True)
+        net.params_init(7403, stream=a)
+        for _ in range(3):
+            net.predict(first, logits=out, stream=a)
+            net.train_step(frames, tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.01), stream=a)
+        net.predict(first, logits=out, stream=b)
+        net.train_step(frames, tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.01), stream=b)
+        net.predict(first, logits=out, stream=a)
+        torch.cuda.synchronize()
+        got.append((out.cpu().numpy(), net.params_get(0).cpu().numpy()))
+        net.close()
+    for x, y in zip(*got):
+        np.testing.assert_array_equal(x, y)
