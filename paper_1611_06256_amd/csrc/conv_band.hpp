@@ -1,10 +1,9 @@
 // The 4x4, stride-2 convolution layer with 16 or 32 input channels and 32 or 64
 // filters on maps of any size (the paper's larger-network family, Sec. 5, whose
-// maps are 9 to 77 pixels wide): forward, input gradient and weight gradient on
-// the bf16 matrix cores at fp32 accuracy.
+// maps are 9 to 77 pixels wide): forward pass of predictions on the bf16 matrix
+// cores at fp32 accuracy (updates keep one order of sums: conv_band_f32.hpp).
 //
-// Common to the three kernels.  A work item is a band of output rows of one
-// frame, as many as a compute unit's LDS holds, or several whole small frames
+// A work item is a band of output rows of one frame, as many as a compute unit's LDS holds, or several whole small frames
 // (BandGeom, chosen on the host); a block walks over items and the next item
 // travels from memory while the current one is multiplied.  Operands are split
 // into three bf16 terms (x = hi + mid + lo exactly) while they are staged, and a
@@ -38,8 +37,8 @@ constexpr int BAND_MAXU = 13;                 // staging units (8 channels of a 
 typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
 
-// Where the items of a launch lie.  "Rows" are output rows for the forward pass and the weight gradient, rows of the
-// stride-phase grid (ceil(H / 2)) for the input gradient.
+// Where the items of a launch lie.  "Rows" are output rows for the forward pass, rows of the stride-phase grid
+// (ceil(H / 2)) for the input gradient (conv_band_f32.hpp).
 struct BandGeom {
     int H, W, OH, OW;
     int F, R;                // an item: R rows of each of F consecutive frames (F > 1 only with all rows)

@@ -463,7 +463,7 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_dgrad_kernel(const float
 
 // ---------------------------------------------------------- weight gradient --
 // dW[oc][k] = scale * sum over the pixels P of all frames of dY[P][oc] x[P][tap k], db[oc] = sum of dY[P][oc], in the chunks of
-// pixels (blockIdx.x) and the order of problems.hpp's ConvWgradP: part[chunk][OC][K + 1].  TIn bytes: 8x8 filters over four
+// pixels and the order of problems.hpp's ConvWgradP: part[chunk][OC][K + 1].  TIn bytes: 8x8 filters over four
 // planes, any stride; floats: 4x4, stride 2, 32 channels.
 //
 // A chunk is one long chain of sums, so the parallelism left is chunks x columns: a wavefront keeps one tile of 16 taps (a

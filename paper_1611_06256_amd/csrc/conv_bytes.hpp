@@ -1,6 +1,6 @@
 // First convolution layer (8x8 filters over four planes of bytes, any stride;
-// the paper's larger-network family, Sec. 5, uses 4, 3, 2 and 1): forward and
-// weight gradient on the bf16 matrix cores at fp32 accuracy.
+// the paper's larger-network family, Sec. 5, uses 4, 3, 2 and 1): forward
+// pass of predictions on the bf16 matrix cores at fp32 accuracy.
 //
 // A byte is exact in bf16 and an fp32 weight or gradient is the exact sum of
 // three bf16 terms, so a product is three bf16 products that are exact in the
@@ -10,9 +10,6 @@
 // pixel.  The contraction index of the forward pass is ordered (u, v, plane):
 // one k-block of 32 is one filter row, and the 8 values of a lane are two
 // neighbouring pixels, 16 bytes at an 8-byte aligned place whatever the stride.
-// The weight gradient reads both operands with the transposing LDS read
-// (conv_band.hpp): 16 columns of a product are four neighbouring pixels times
-// four planes, at any place, so no stride needs re-laid planes or shifts.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -175,7 +172,7 @@ inline BytesGeom bytes_fwd_geom(int H, int S, int n) {
     bytes_split(b, n, r, 2 * BAND_CUS);
     return b;
 }
-// Frames of H rows of 84 pixels, any stride.  A row of the map must fit the weight gradient's item.
+// Frames of H rows of 84 pixels, any stride.  A row of the map must fit an item.
 inline bool bytes_ok(int H, int W, int S) {
     return W == BYTES_W && H >= 8 && S >= 1 && (BYTES_W - 8) / S + 1 <= 128;
 }

@@ -2019,7 +2019,11 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         STAGE("fc_fwd", 2.0 * B * c->F * c->flat, 0);
         int nz, kchunk;
         if (c->fast && dense_operand_ok(x, c->flat, c->flat) && dense_operand_ok(wfc, c->flat, c->flat)) {
-            pick_split_xcd(cdiv(B, 64) * cdiv(c->F, 64), c->flat, nz, kchunk);
+            // Up to 16 tiles a prediction fills the chip with one block per compute unit: the second one would double the
+            // partial sums that the heads add up one after the other (larger net, 16 to 128 frames: 3 % of the call).  With
+            // more tiles two blocks hide each other's loads (256 frames: 54.5 us, 56.5 with one).  Updates keep one order of sums.
+            const int tiles = cdiv(B, 64) * cdiv(c->F, 64);
+            pick_split_xcd(tiles, c->flat, nz, kchunk, !keep_zv && tiles <= 16 ? 256 : 512);
             DenseGemmArgs p{}; p.rb = c->rb;
             p.M = B; p.N = c->F; p.K = c->flat; p.kchunk = kchunk; p.nz = nz;
             p.A = x; p.lda = c->flat; p.B = wfc; p.ldb = c->flat;
