@@ -68,6 +68,19 @@ __device__ __forceinline__ void split3_pair(float x, float y, uint32_t &hi, uint
     lo = pack_bf16_rne(rx - __uint_as_float(mid << 16), ry - __uint_as_float(mid & 0xffff0000u));
 }
 
+// One dword per lane from base + off (bytes) to lds + 4 * lane; base and lds are the same for the whole wavefront.  The caller
+// waits for vmcnt itself: the compiler, which would wait for every such load in front of the next LDS read, does not see it.
+__device__ __forceinline__ void load_dword_to_lds(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+// The same with 16 bytes per lane, to lds + 16 * lane.
+__device__ __forceinline__ void load_vec_to_lds(const void *base, uint32_t off, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_address(const void *p) {
+    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
+}
+
 // Where frame f lies.  TABLE: wherever the table's entry points (x is not used).  The table is host memory that no cache keeps,
 // and an entry takes about two microseconds to arrive: one lane asks for it, and kernels that walk over frames ask early.
 template <bool TABLE>

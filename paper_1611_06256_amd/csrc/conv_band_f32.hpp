@@ -491,15 +491,6 @@ struct F32WgradGeom {
 template <class TIn> constexpr int f32_wgrad_waves() { return sizeof(TIn) == 1 ? 4 : 8; }
 template <class TIn> constexpr int f32_wgrad_maxx() { return 13; }      // dwords of input per thread and step
 
-// One dword per lane from base + off (bytes) to lds + 4 * lane; base and lds are the same for the whole wavefront.  The caller
-// waits for vmcnt itself: the compiler, which would wait for every such load in front of the next LDS read, does not see it.
-__device__ __forceinline__ void load_dword_to_lds(const void *base, uint32_t off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
-}
-__device__ __forceinline__ uint32_t lds_address(const void *p) {
-    return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p;
-}
-
 template <class TIn, int OC, bool RB>
 __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 : 4) void conv_f32_wgrad_kernel(
     const TIn *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, const F32WgradGeom b) {

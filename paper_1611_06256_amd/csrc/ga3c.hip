@@ -22,6 +22,7 @@
 #include "dense_gemm.hpp"
 #include "conv1_bf16x3.hpp"
 #include "dense_gemm_bf16x6.hpp"
+#include "fc_forward.hpp"
 #include "conv2_bf16x6.hpp"
 #include "conv12_fused.hpp"
 #include "conv_fwd_bf16x6.hpp"
@@ -154,6 +155,8 @@ struct ga3c_ctx {
     bool band[GA3C_MAX_CONV];
     size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_vecs;
     u32x4 *bfrag[2];
+    ga3c::FcPlanes fcw[2];        // fc weights of each parameter copy as operands of the forward product (w == nullptr: none); kept
+                                  // current by whoever writes the copy
     int *ticket;                  // predict_small_kernel's per-frame counters, zero between launches
     Work pred, train;
     // training only
@@ -1583,9 +1586,11 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, flo
                                                       const float *__restrict__ grad, size_t n,
                                                       const float *__restrict__ scale_dev, float scale_host, float lr,
                                                       float alpha, float eps, u32x4 *__restrict__ frag, unsigned w1_off,
-                                                      unsigned w2_off, int frag_rb, const RmsClip clipargs) {
+                                                      unsigned w2_off, int frag_rb, const ga3c::FcPlanes fcw,
+                                                      const RmsClip clipargs) {
     // frag (optional): split MFMA fragments of the small net's conv filters, kept current with theta_out;
-    // w1_off / w2_off: where the two filter tensors start in the flat buffer (multiples of 4)
+    // w1_off / w2_off: where the two filter tensors start in the flat buffer (multiples of 4).  fcw (optional): the fc weights
+    // as operands of the forward product, likewise
     float s = scale_dev ? scale_dev[0] : scale_host;
     if (clipargs.normpart) {
         __shared__ float sh[4][4];
@@ -1654,6 +1659,10 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, flo
                     conv_dgrad_store_fragment4<SpecS2>(frag + CFRAG_FWD_VECS, (int)r2, t[j]);
                 }
             }
+            if (fcw.w) {
+                const unsigned r = (unsigned)(i + 256 * j) - fcw.first;
+                if (r < fcw.n) ga3c::fc_planes_store4(fcw, r, t[j]);
+            }
         }
     }
     for (size_t i = ntile * (256 * VPT) + (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
@@ -1667,6 +1676,10 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, flo
                 conv12_store_fragment4(frag, 1, (int)r2, t, frag_rb);
                 conv_dgrad_store_fragment4<SpecS2>(frag + CFRAG_FWD_VECS, (int)r2, t);
             }
+        }
+        if (fcw.w) {
+            const unsigned r = (unsigned)i - fcw.first;
+            if (r < fcw.n) ga3c::fc_planes_store4(fcw, r, t);
         }
     }
     for (size_t k = n4 * 4 + (size_t)blockIdx.x * 256 + threadIdx.x; k < n; k += stride) {
@@ -1870,8 +1883,13 @@ inline bool spec_matches(const ConvGeom &g, bool byte_input) {
 }
 inline bool is_aligned16(const void *p) { return (((uintptr_t)p) & 15) == 0; }
 
-// Things derived from parameter copy i, rebuilt on s after that copy was written there.
-int refresh_derived(ga3c_ctx *c, int i, hipStream_t s) {
+// Things derived from parameter copy i, rebuilt on s after that copy was written there.  fc: the fc weights' too (an update
+// writes those itself).
+int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true) {
+    if (fc && c->fcw[i].w) {
+        ga3c::launch(fc_planes_kernel, dim3(blocks_for(c->fcw[i].n)), dim3(256), 0, s, (const float4 *)c->theta2[i], c->fcw[i]);
+        HIP_TRY(hipGetLastError());
+    }
     if (c->cfrag[i]) {
         HIP_TRY(launch_conv12_filter_fragments(c->theta2[i] + c->off[0], c->theta2[i] + c->off[2], c->cfrag[i], s, c->rb));
         if (c->cfrag_dgrad)
@@ -2024,12 +2042,19 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
             // more tiles two blocks hide each other's loads (256 frames: 54.5 us, 56.5 with one).  Updates keep one order of sums.
             const int tiles = cdiv(B, 64) * cdiv(c->F, 64);
             pick_split_xcd(tiles, c->flat, nz, kchunk, !keep_zv && tiles <= 16 ? 256 : 512);
-            DenseGemmArgs p{}; p.rb = c->rb;
-            p.M = B; p.N = c->F; p.K = c->flat; p.kchunk = kchunk; p.nz = nz;
-            p.A = x; p.lda = c->flat; p.B = wfc; p.ldb = c->flat;
-            p.C = w.ws; p.ldc = c->F; p.aux = nullptr;
             if ((size_t)nz * B * c->F > w.ws_floats) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc)");
-            HIP_TRY((launch_dense_gemm_bf16x6<2, 2, 2, 2, false, false, DG_PARTIAL>(p, DG_SPLIT_Z, s)));
+            if (c->fcw[which].w && fc_forward_batch_ok(x, B, c->flat)) {
+                FcForwardArgs p;
+                p.M = B; p.N = c->F; p.K = c->flat; p.kchunk = kchunk; p.nz = nz;
+                p.x = x; p.w = c->fcw[which].w; p.part = w.ws;
+                HIP_TRY(launch_fc_forward(p, c->rb, s));
+            } else {
+                DenseGemmArgs p{}; p.rb = c->rb;
+                p.M = B; p.N = c->F; p.K = c->flat; p.kchunk = kchunk; p.nz = nz;
+                p.A = x; p.lda = c->flat; p.B = wfc; p.ldb = c->flat;
+                p.C = w.ws; p.ldc = c->F; p.aux = nullptr;
+                HIP_TRY((launch_dense_gemm_bf16x6<2, 2, 2, 2, false, false, DG_PARTIAL>(p, DG_SPLIT_Z, s)));
+            }
             fc_ws = w.ws; fc_nz = nz;
         } else {
             pick_split(cdiv(B, 64) * cdiv(c->F, 64), c->flat, nz, kchunk);
@@ -2248,6 +2273,24 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
             guard(dmalloc((void **)&c->bfrag[i], sizeof(u32x4) * c->bfrag_vecs));
             if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
         }
+    // a small net whose calls all fit one launch has no use for them
+    if (rc == GA3C_OK && fc_forward_ok(c->flat, c->F) && c->off[2 * c->nconv] % 4 == 0 && c->P < (size_t)1 << 31 &&
+        !(c->ticket && max_train_frames == 0 && max_predict_batch <= SP_MAX_FRAMES)) {
+        const int terms = c->rb ? 1 : 3;
+        const size_t bytes = (size_t)c->flat * c->F * 2 * terms;
+        unsigned char *w = nullptr;
+        guard(dmalloc((void **)&w, 2 * bytes));
+        if (rc == GA3C_OK) {
+            for (int i = 0; i < 2; ++i) {
+                FcPlanes &f = c->fcw[i];
+                f.w = (u32x4 *)(w + i * bytes);
+                f.first = (unsigned)(c->off[2 * c->nconv] / 4); f.n = (unsigned)((size_t)c->flat * c->F / 4);
+                f.kblocks = c->flat / 32; f.terms = terms; f.row = FastDiv(c->flat / 4);
+            }
+            const hipError_t e = hipMemset(w, 0, 2 * bytes);         // of parameters that are zero
+            if (e != hipSuccess) guard(fail(GA3C_EHIP, "hipMemset: %s", hipGetErrorString(e)));
+        }
+    }
     if (rc == GA3C_OK) guard(alloc_work(c->pred, c, max_predict_batch));
     if (rc == GA3C_OK) guard(alloc_work(c->train, c, max_train_frames));
     if (rc == GA3C_OK && max_train_frames > 0) {
@@ -2297,7 +2340,7 @@ extern "C" int ga3c_destroy(ga3c_ctx *c) {
     }
     (void)hipFree(c->g); (void)hipFree(c->grad);
     (void)hipFree(c->cfrag[0]); (void)hipFree(c->cfrag[1]); (void)hipFree(c->ticket); (void)hipFree(c->lfrag[0]); (void)hipFree(c->lfrag[1]);
-    (void)hipFree(c->bfrag[0]); (void)hipFree(c->bfrag[1]);
+    (void)hipFree(c->bfrag[0]); (void)hipFree(c->bfrag[1]); (void)hipFree(c->fcw[0].w);      // both copies' in one piece
     free_work(c->pred); free_work(c->train);
     (void)hipFree(c->dh); (void)hipFree(c->dzv); (void)hipFree(c->R);
     (void)hipFree(c->partials); (void)hipFree(c->colpart); (void)hipFree(c->scale); (void)hipFree(c->stats);
@@ -2681,9 +2724,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     ca.normpart = c->partials; ca.nnorm = red_blocks; ca.losspart = losspart; ca.nloss = nloss; ca.clip = hp->clip_norm;
     ca.scale_out = c->scale; ca.own = c->stats; ca.user = stats;
     ga3c::launch((rmsprop_kernel<0, 1>), dim3(rb), dim3(256), 0, s, th, c->theta2[cur ^ 1], c->g, c->grad, c->P, (const float *)nullptr,
-                       1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[cur ^ 1], (unsigned)c->off[0], (unsigned)c->off[2], c->rb, ca);
+                       1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[cur ^ 1], (unsigned)c->off[0], (unsigned)c->off[2], c->rb, c->fcw[cur ^ 1], ca);
     HIP_TRY(hipGetLastError());
-    if (c->lfrag[cur ^ 1] || c->bfrag[cur ^ 1]) TRY(refresh_derived(c, cur ^ 1, s));      // the larger net's fragments follow the new parameters
+    if (c->lfrag[cur ^ 1] || c->bfrag[cur ^ 1]) TRY(refresh_derived(c, cur ^ 1, s, false));      // the larger net's fragments follow the new parameters
     TRY(mark_ready(c, cur ^ 1, s));
     c->cur = cur ^ 1;        // calls enqueued from now on see the new parameters
     return GA3C_OK;
@@ -2772,7 +2815,7 @@ extern "C" int ga3c_rmsprop_flat(float *theta, float *g, const float *grad, size
     memset(&none, 0, sizeof(none));
 #define GA3C_RMS_LAUNCH(V)                                                                                               \
     ga3c::launch((rmsprop_kernel<V, 4>), dim3(rb), dim3(256), 0, (hipStream_t)stream, theta, theta, g, grad, n,         \
-                       (const float *)nullptr, scale, lr, rms_decay, rms_eps, (u32x4 *)nullptr, 0u, 0u, 0, none)
+                       (const float *)nullptr, scale, lr, rms_decay, rms_eps, (u32x4 *)nullptr, 0u, 0u, 0, FcPlanes(), none)
     if (stream_past_caches) GA3C_RMS_LAUNCH(3); else GA3C_RMS_LAUNCH(0);
 #undef GA3C_RMS_LAUNCH
     HIP_TRY(hipGetLastError());
