@@ -11,7 +11,7 @@
 // [16 channels] x [4 OC] x [pixels of the phase].  The four phases are
 // interleaved in an LDS copy of the output frame, which is then masked and
 // stored with full-width writes.  A block computes 16 input channels,
-// 16 blockIdx.y .. (gridDim.y = C / 16), of frames blockIdx.x, + gridDim.x, ...
+// 16 by .. (C / 16 slices), of frames bx, + nbx, ...
 //
 // Both operands are split into
 // three bf16 terms (x = hi + mid + lo exactly) and a product is evaluated as the
@@ -105,9 +105,9 @@ inline hipError_t launch_conv_dgrad_filter_fragments(const float *w, u32x4 *wfra
 
 // ONE: operands rounded to bfloat16 (the reduced-precision variant): one term, one product.
 template <class SP, bool ONE>
-__global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *__restrict__ dy, const float *__restrict__ w,
-                                                                   const float *__restrict__ xin, float *__restrict__ dx,
-                                                                   int nframes, const u32x4 *__restrict__ wfrag) {
+__device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict__ dy, const float *__restrict__ w,
+                                                        const float *__restrict__ xin, float *__restrict__ dx, int nframes,
+                                                        const u32x4 *__restrict__ wfrag, const int bx, const int by, const int nbx) {
     typedef ConvDgradBf16Geom<SP> G;
     static_assert(SP::KS == 4 && SP::S == 2, "kernel must be 4x4 with stride 2");
     static_assert(SP::C % 16 == 0 && SP::OC % 32 == 0, "16 input channels per block, filters in groups of 32");
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int ry = wave / S, rx = wave % S;
-    const int c0 = blockIdx.y * CS;
+    const int c0 = by * CS;
 
     for (int e = tid; e < NTERM * PLANE / 16; e += 256) ((u32x4 *)dp)[e] = u32x4{0u, 0u, 0u, 0u};     // zero border
 
@@ -162,12 +162,12 @@ __global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *
 #pragma unroll
             for (int j = 0; j < 4; ++j) dpre[i][j] = dsrc[dsrc_off[i] + j * SP::NPIX];
     };
-    int f = blockIdx.x;
+    int f = bx;
     fetch_dy(min(f, nframes - 1));       // on its way while the filters arrive
     // sub-filter fragments of my phase: row = channel l16, k = (tap, filter 8g..8g+7 of the block's 32)
     Bf16x8Bits af[KB][NTERM];
     if (wfrag) {
-        const u32x4 *src = wfrag + (size_t)((blockIdx.y * 4 + wave) * KB) * 3 * 64 + lane;
+        const u32x4 *src = wfrag + (size_t)((by * 4 + wave) * KB) * 3 * 64 + lane;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *
         }
     }
     CONV_DGRAD_STAMP(1);
-    for (; f < nframes; f += gridDim.x) {
+    for (; f < nframes; f += nbx) {
         __syncthreads();                      // the border is zero; the last frame's dY and outs have been read
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *
                 for (int x = 0; x < NTERM; ++x) *(uint2 *)(dp + x * PLANE + dlds[i]) = o3[x];
             }
         __syncthreads();
-        fetch_dy(min(f + (int)gridDim.x, nframes - 1));
+        fetch_dy(min(f + nbx, nframes - 1));
         float4 mask[XPT];
         {
             const float4 *msrc = (const float4 *)(xin + (size_t)f * SP::CHW + (size_t)c0 * (SP::H * SP::W));
@@ -275,6 +275,12 @@ __global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *
         }
     }
     CONV_DGRAD_STAMP(2);
+}
+template <class SP, bool ONE>
+__global__ __launch_bounds__(256, 2) void conv_dgrad_bf16x6_kernel(const float *__restrict__ dy, const float *__restrict__ w,
+                                                                   const float *__restrict__ xin, float *__restrict__ dx,
+                                                                   int nframes, const u32x4 *__restrict__ wfrag) {
+    conv_dgrad_bf16x6_block<SP, ONE>(dy, w, xin, dx, nframes, wfrag, blockIdx.x, blockIdx.y, gridDim.x);
 }
 
 // `blocks`: how many blocks the chip holds at once (two per CU), shared out over the channel slices.

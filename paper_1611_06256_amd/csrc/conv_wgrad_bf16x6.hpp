@@ -24,11 +24,11 @@
 // nine term products (dense_gemm_bf16x6.hpp): 6 x 16 cycles per 32 pixels
 // instead of 8 x 32 on the fp32 instruction.
 //
-// A block takes 16 input channels, 16 blockIdx.y .. (gridDim.y = C / 16), and
-// OCB filters, OCB blockIdx.z .. (all of them, or 32 where two blocks then fit
+// A block takes 16 input channels, 16 by .. (C / 16 slices), and
+// OCB filters, OCB bz .. (all of them, or 32 where two blocks then fit
 // a compute unit's LDS), of
-// frames blockIdx.x, + gridDim.x, .. and writes its part of one partial gradient,
-// part[blockIdx.x][OC][K + 1] (K = 16 C; the last column is the bias gradient,
+// frames bx, + nbx, .. and writes its part of one partial gradient,
+// part[bx][OC][K + 1] (K = 16 C; the last column is the bias gradient,
 // written by the blocks of channel slice 0), which a second kernel adds up in
 // block order: no atomics, the result does not depend on timing.
 #pragma once
@@ -41,7 +41,7 @@
 
 namespace ga3c {
 
-// OCB: filters per block (a multiple of 16; blockIdx.z takes the slices of OCB filters)
+// OCB: filters per block (a multiple of 16; bz takes the slices of OCB filters)
 template <class SP, int OCB = SP::OC>
 struct ConvWgradBf16Geom {
     static constexpr int CS = 16;
@@ -63,10 +63,8 @@ struct ConvWgradBf16Geom {
 
 // ONE: operands rounded to bfloat16 (the reduced-precision variant): one term, one product.
 template <class SP, bool ONE, int OCB = SP::OC>
-__global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void conv_wgrad_bf16x6_kernel(const float *__restrict__ x,
-                                                                                              const float *__restrict__ dy,
-                                                                                              float *__restrict__ part,
-                                                                                              int nframes, float scale) {
+__device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part,
+                                                        int nframes, float scale, const int bx, const int by, const int bz, const int nbx) {
     typedef ConvWgradBf16Geom<SP, OCB> G;
     static_assert(SP::OC % OCB == 0 && OCB % 16 == 0, "whole slices of filters");
     static_assert(SP::KS == 4 && SP::S == 2, "kernel must be 4x4 with stride 2");
@@ -89,7 +87,7 @@ __global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void con
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
     const int ry = wave / 2, rx = wave % 2;
-    const int c0 = blockIdx.y * CS, oc0 = blockIdx.z * OCB;
+    const int c0 = by * CS, oc0 = bz * OCB;
 
     for (int e = tid; e < NTERM * (DTERM + PTERM) / 8; e += 256) ((u32x4 *)smem)[e] = u32x4{0u, 0u, 0u, 0u};   // padding stays zero
 
@@ -132,9 +130,9 @@ __global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void con
 #pragma unroll
         for (int i = 0; i < DPT; ++i) dpre[i] = ds[min(tid + 256 * i, NDV - 1)];
     };
-    int f = blockIdx.x;
+    int f = bx;
     fetch(min(f, nframes - 1));
-    for (; f < nframes; f += gridDim.x) {
+    for (; f < nframes; f += nbx) {
         __syncthreads();                      // the last frame's operands have been read
 #pragma unroll
         for (int i = 0; i < XPT; ++i)
@@ -164,7 +162,7 @@ __global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void con
                 }
             }
         __syncthreads();
-        fetch(min(f + (int)gridDim.x, nframes - 1));
+        fetch(min(f + nbx, nframes - 1));
         // the loads above go out before the products start (the compiler would otherwise sink them below the MFMAs)
         __builtin_amdgcn_sched_barrier(0);
         constexpr int NPROD = ONE ? 1 : 6;
@@ -203,7 +201,7 @@ __global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void con
                                                __builtin_amdgcn_alignbit(dw[o + 3], dw[o + 2], 16), __builtin_amdgcn_alignbit(dw[o + 4], dw[o + 3], 16)};
                 }
             }
-            if (blockIdx.y == 0 && kb % 4 == wave) {      // bias: the terms add up to dY exactly, smallest first
+            if (by == 0 && kb % 4 == wave) {      // bias: the terms add up to dY exactly, smallest first
 #pragma unroll
                 for (int t = NTERM - 1; t >= 0; --t)
 #pragma unroll
@@ -244,14 +242,21 @@ __global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void con
     }
     __syncthreads();
     typedef float f32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
-    float *pb = part + ((size_t)blockIdx.x * SP::OC + oc0) * K1 + c0 * 16;
+    float *pb = part + ((size_t)bx * SP::OC + oc0) * K1 + c0 * 16;
     for (int it = tid; it < OCB * CS * 4; it += 256) {
         const int oc = it / (CS * 4), kq = it % (CS * 4);
         const float4 v = *(const float4 *)(ot + oc * OTP + 4 * kq);
         *(f32x4_dword_aligned *)(pb + (size_t)oc * K1 + 4 * kq) = f32x4_dword_aligned{v.x * scale, v.y * scale, v.z * scale, v.w * scale};
     }
-    if (blockIdx.y == 0 && tid < OCB)
-        part[((size_t)blockIdx.x * SP::OC + oc0 + tid) * K1 + SP::K] = (bsh[0][tid] + bsh[1][tid]) + (bsh[2][tid] + bsh[3][tid]);
+    if (by == 0 && tid < OCB)
+        part[((size_t)bx * SP::OC + oc0 + tid) * K1 + SP::K] = (bsh[0][tid] + bsh[1][tid]) + (bsh[2][tid] + bsh[3][tid]);
+}
+template <class SP, bool ONE, int OCB = SP::OC>
+__global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void conv_wgrad_bf16x6_kernel(const float *__restrict__ x,
+                                                                                              const float *__restrict__ dy,
+                                                                                              float *__restrict__ part,
+                                                                                              int nframes, float scale) {
+    conv_wgrad_bf16x6_block<SP, ONE, OCB>(x, dy, part, nframes, scale, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
 }
 
 // One partial dW per block: fewer blocks where a partial is large.

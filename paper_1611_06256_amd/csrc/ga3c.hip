@@ -27,6 +27,7 @@
 #include "conv12_fused.hpp"
 #include "conv_fwd_bf16x6.hpp"
 #include "conv_dgrad_bf16x6.hpp"
+#include "conv_grads_bf16x6.hpp"
 #include "conv_wgrad_bf16x6.hpp"
 #include "conv_wgrad_s1_bf16x6.hpp"
 #include "conv_band.hpp"
@@ -2623,6 +2624,24 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
+            // The 4x4 stride-2 layers' two gradients share a launch.  The small net's has a quarter of the products, and above 640
+            // frames (a bit more than one per block that the chip holds) it gains or loses 1 % with how the frames divide.
+            if ((kind == 6 || kind == 7 || kind == 9) && (kind != 6 || B <= 640) && is_aligned16(th + c->off[2 * l])) {
+                STAGE2(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W),
+                       CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * (4.0 * g.CHW + 4.0 * g.OC * g.OHW));
+                const float *x = (const float *)xin, *dy = c->dact[l], *wl = th + c->off[2 * l];
+                // the fragments of the copy being trained on, when the context keeps them
+                if (kind == 6)
+                    HIP_TRY(launch_conv_grads_bf16x6<SpecS2>(x, dy, wl, c->cfrag[cur] && c->cfrag_dgrad ? c->cfrag[cur] + CFRAG_FWD_VECS : nullptr,
+                                                             c->dact[l - 1], part, B, s, c->rb));
+                else if (kind == 7)
+                    HIP_TRY((launch_conv_grads_bf16x6<SpecL2, 32>(x, dy, wl, c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr,
+                                                                  c->dact[l - 1], part, B, s, c->rb)));
+                else
+                    HIP_TRY(launch_conv_grads_bf16x6<SpecP2>(x, dy, wl, nullptr, c->dact[l - 1], part, B, s, c->rb));
+                add_seg(part, nz, g.OC, g.K + 1, 0, g.OC, c->grad + c->off[2 * l], c->grad + c->off[2 * l + 1], 1);
+                continue;
+            }
             STAGE(CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * ((l == 0 ? 1.0 : 4.0) * g.CHW + 4.0 * g.OC * g.OHW));
             if (kind == 1) {
                 HIP_TRY(launch_conv1_bf16x3_wgrad((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
