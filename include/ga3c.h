@@ -19,10 +19,14 @@
  *     calls must be stream-ordered among themselves, and so must
  *     ga3c_train_step calls (each kind owns one set of workspaces), but the
  *     two kinds may run on two different streams: the context keeps two
- *     copies of the parameters, an update writes the copy that is not being
- *     read and publishes it, and HIP events order that against the
- *     predictions (a prediction sees the parameters of the last update that
- *     was ENQUEUED before it, never a half-written set).
+ *     copies of the parameters, a writer (an update, ga3c_params_init,
+ *     ga3c_params_set) writes the copy that no prediction reads and publishes
+ *     it, and HIP events order that against the predictions (a prediction sees
+ *     the parameters of the last writer that was ENQUEUED before it, never a
+ *     half-written set).  A ga3c_params_get is complete before the parameters
+ *     it copies change; when the updates move to another stream, order them
+ *     behind the copies on the one they leave.  A stream may be destroyed once
+ *     the work on it is over: no stream is used after the call it was given to.
  *   - One HOST thread at a time drives a context: the calls keep host-side
  *     state without locks (which parameter copy is published, where each event
  *     was last recorded, the profiler's lists).  The paper's predictor and

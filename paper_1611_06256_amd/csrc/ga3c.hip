@@ -119,6 +119,17 @@ struct Profiler {
 };
 }  // namespace
 
+namespace {
+// An event and where it was last recorded (the handle is only ever compared).
+struct Mark {
+    hipEvent_t ev;
+    hipStream_t where;
+    bool set;
+};
+// Predictions of a parameter copy since it was written: none, some that no event stands behind yet, all behind an event.
+enum Reads { READS_NONE, READS_OPEN, READS_MARKED };
+}  // namespace
+
 struct ga3c_ctx {
     Profiler *prof;
     bool fast;                    // use the fixed-geometry kernels where they apply
@@ -132,17 +143,14 @@ struct ga3c_ctx {
     int noff;
     size_t P;
     int max_pred, max_train;
-    // Two copies of the parameters.  theta2[cur] is the published snapshot that
-    // predictions and the forward/backward of an update read; RMSProp writes the
-    // other copy and publishes it.  ev_ready[i]: copy i has been written;
-    // ev_readers[i]: the last prediction that read copy i has finished.
+    // Two copies of the parameters.  theta2[cur] is the published one, which every call reads; a writer (an update,
+    // params_init, params_set) writes the other one, or in place (copy_to_write), and publishes it.
     float *theta2[2];
     int cur;
-    hipEvent_t ev_ready[2], ev_readers[2];
-    hipStream_t ready_stream[2], readers_stream[2];   // where each event was last recorded
-    bool ready_set[2], readers_set[2];
-    bool entered, several_streams;                    // whether a call came yet, and on more than one stream
-    hipStream_t first_stream;
+    Reads reads[2];               // of copy i by predictions
+    Mark ready[2];                // copy i has been written
+    Mark turned;                  // all predictions of the copy that is not published are over (READS_MARKED)
+    Mark copied[2];               // all params_get of copy i are over
     float *g, *grad;
     // small net: conv1/conv2 filters of each parameter copy as split MFMA fragments (nullptr for other nets), forward
     // kernel's first, then (at CFRAG_FWD_VECS) the input-gradient kernel's; refreshed by whoever writes the copy
@@ -1722,42 +1730,61 @@ __global__ __launch_bounds__(256) void copy_kernel(float *__restrict__ dst, cons
 
 // ------------------------------------------------------------ host helpers --
 
-// Event fences between the calls of a context.  As long as all calls come on one stream, the stream's order is all that
-// is needed and no event is recorded (a record behind a prediction costs 1.5 to 3 us of the stream's time, a fifth of a
-// prediction of one frame).  The first call on another stream records what the calls so far have left on the first one, and
-// from then on every call records its own.  A wait is skipped when the event was last recorded on the same stream or never.
-int enter(ga3c_ctx *c, hipStream_t s) {
-    if (c->several_streams) return GA3C_OK;
-    if (!c->entered) { c->entered = true; c->first_stream = s; return GA3C_OK; }
-    if (s == c->first_stream) return GA3C_OK;
-    c->several_streams = true;
-    for (int i = 0; i < 2; ++i) {
-        hipError_t e = hipSuccess;
-        if (c->ready_set[i]) e = hipEventRecord(c->ev_ready[i], c->first_stream);
-        if (e == hipSuccess && c->readers_set[i]) e = hipEventRecord(c->ev_readers[i], c->first_stream);
-        if (e != hipSuccess) {                  // the first stream is gone: whatever it still had to do is over after this
-            (void)hipGetLastError();
-            HIP_TRY(hipDeviceSynchronize());
-            c->ready_set[0] = c->ready_set[1] = c->readers_set[0] = c->readers_set[1] = false;
-            return GA3C_OK;
-        }
+// Order between calls of one context on different streams.
+//   - A writer of the parameters leaves an event when it is done (ready); every call that reads them waits for it.
+//   - Predictions leave no event of their own (behind a prediction it costs 1.5 to 3 us of the stream's time, a fifth of a
+//     prediction of one frame).  The first one that reads a newly published copy records one event before its work, if the other
+//     copy has been read: calls of this kind are in order among themselves, so all predictions of the other copy are over then
+//     (turned).
+//   - A writer takes the other copy, behind that event.  If the other copy has been read and no prediction has come since, there
+//     is no event, but nothing reads the published copy either, and that is written in place.
+// Events are recorded only on the stream that the running call was given: a handle kept from an earlier call may by then be a
+// stream that is gone, or another one.  A wait is skipped when the event was last recorded on the same stream (stream order
+// already holds) or never.
+int wait_mark(const Mark &m, hipStream_t s) {
+    if (!m.set || m.where == s) return GA3C_OK;
+    HIP_TRY(hipStreamWaitEvent(s, m.ev, 0));
+    return GA3C_OK;
+}
+int set_mark(Mark &m, hipStream_t s, const ga3c::StopEvent *stop = nullptr) {
+    if (!stop || !stop->attached) HIP_TRY(hipEventRecord(m.ev, s));
+    m.set = true; m.where = s;
+    return GA3C_OK;
+}
+// The mark's event for a call's last launch to complete; a stream that is being captured gets it as a node of its own instead.
+ga3c::StopEvent stop_for(const Mark &m, hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    ga3c::StopEvent stop;
+    if (e == hipSuccess && st == hipStreamCaptureStatusNone) stop.ev = m.ev;
+    return stop;
+}
+int wait_ready(ga3c_ctx *c, hipStream_t s) { return wait_mark(c->ready[c->cur], s); }
+// A prediction on s is about to read the published copy.
+int begin_prediction(ga3c_ctx *c, hipStream_t s) {
+    if (c->reads[c->cur ^ 1] == READS_OPEN) {
+        const int rc = set_mark(c->turned, s);
+        if (rc != GA3C_OK) return rc;
+        c->reads[c->cur ^ 1] = READS_MARKED;
     }
+    c->reads[c->cur] = READS_OPEN;
     return GA3C_OK;
 }
-int fence_wait(const ga3c_ctx *c, hipStream_t s, hipEvent_t ev, bool set, hipStream_t where) {
-    if (!c->several_streams || !set || where == s) return GA3C_OK;
-    HIP_TRY(hipStreamWaitEvent(s, ev, 0));
+// The copy that the next writer writes; what has to be over before it does; its publication.
+int copy_to_write(const ga3c_ctx *c) { return c->reads[c->cur ^ 1] == READS_OPEN ? c->cur : c->cur ^ 1; }
+int wait_writable(ga3c_ctx *c, hipStream_t s) {
+    const int to = copy_to_write(c);
+    const int rc = c->reads[to] == READS_MARKED ? wait_mark(c->turned, s) : GA3C_OK;
+    return rc == GA3C_OK ? wait_mark(c->copied[to], s) : rc;
+}
+int publish(ga3c_ctx *c, hipStream_t s, const ga3c::StopEvent *stop = nullptr) {
+    const int to = copy_to_write(c), rc = set_mark(c->ready[to], s, stop);
+    if (rc != GA3C_OK) return rc;
+    c->reads[to] = READS_NONE; c->copied[to].set = false;
+    c->cur = to;                 // calls enqueued from now on see the new parameters
     return GA3C_OK;
 }
-int wait_ready(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(c, s, c->ev_ready[i], c->ready_set[i], c->ready_stream[i]); }
-int wait_readers(ga3c_ctx *c, int i, hipStream_t s) { return fence_wait(c, s, c->ev_readers[i], c->readers_set[i], c->readers_stream[i]); }
-int mark(const ga3c_ctx *c, hipEvent_t ev, bool &set, hipStream_t &where, hipStream_t s) {
-    if (c->several_streams) HIP_TRY(hipEventRecord(ev, s));
-    set = true; where = s;
-    return GA3C_OK;
-}
-int mark_ready(ga3c_ctx *c, int i, hipStream_t s) { return mark(c, c->ev_ready[i], c->ready_set[i], c->ready_stream[i], s); }
-int mark_readers(ga3c_ctx *c, int i, hipStream_t s) { return mark(c, c->ev_readers[i], c->readers_set[i], c->readers_stream[i], s); }
 #define TRY(expr) do { int rc_ = (expr); if (rc_ != GA3C_OK) return rc_; } while (0)
 
 // While one of these is alive and profiling is on, every kernel launched by this host thread carries an event pair
@@ -2228,10 +2255,9 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     constexpr unsigned order_only = hipEventDisableTiming | hipEventDisableSystemFence;
     for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
         guard(dmalloc((void **)&c->theta2[i], sizeof(float) * c->P));
-        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_ready[i], order_only) != hipSuccess)
-            guard(fail(GA3C_EHIP, "hipEventCreate failed"));
-        if (rc == GA3C_OK && hipEventCreateWithFlags(&c->ev_readers[i], order_only) != hipSuccess)
-            guard(fail(GA3C_EHIP, "hipEventCreate failed"));
+        for (Mark *m : {&c->ready[i], &c->copied[i], &c->turned})
+            if (rc == GA3C_OK && !m->ev && hipEventCreateWithFlags(&m->ev, order_only) != hipSuccess)
+                guard(fail(GA3C_EHIP, "hipEventCreate failed"));
     }
     if (rc == GA3C_OK) guard(dmalloc((void **)&c->g, sizeof(float) * c->P));
     if (rc == GA3C_OK) guard(dmalloc((void **)&c->grad, sizeof(float) * c->P));
@@ -2334,11 +2360,9 @@ extern "C" int ga3c_destroy(ga3c_ctx *c) {
     if (!c) return GA3C_OK;
     (void)hipDeviceSynchronize();
     for (int l = 0; l < GA3C_MAX_CONV; ++l) { (void)hipFree(c->koff[l]); (void)hipFree(c->dact[l]); }
-    for (int i = 0; i < 2; ++i) {
-        (void)hipFree(c->theta2[i]);
-        if (c->ev_ready[i]) (void)hipEventDestroy(c->ev_ready[i]);
-        if (c->ev_readers[i]) (void)hipEventDestroy(c->ev_readers[i]);
-    }
+    for (Mark *m : {&c->ready[0], &c->ready[1], &c->turned, &c->copied[0], &c->copied[1]})
+        if (m->ev) (void)hipEventDestroy(m->ev);
+    (void)hipFree(c->theta2[0]); (void)hipFree(c->theta2[1]);
     (void)hipFree(c->g); (void)hipFree(c->grad);
     (void)hipFree(c->cfrag[0]); (void)hipFree(c->cfrag[1]); (void)hipFree(c->ticket); (void)hipFree(c->lfrag[0]); (void)hipFree(c->lfrag[1]);
     (void)hipFree(c->bfrag[0]); (void)hipFree(c->bfrag[1]); (void)hipFree(c->fcw[0].w);      // both copies' in one piece
@@ -2365,11 +2389,10 @@ extern "C" int ga3c_params_offsets(const ga3c_ctx *c, int64_t *off, int cap) {
 extern "C" int ga3c_params_init(ga3c_ctx *c, uint64_t seed, void *stream) {
     if (!c) return fail(GA3C_EINVAL, "ga3c_params_init: null context");
     hipStream_t s = (hipStream_t)stream;
-    float *theta = c->theta2[c->cur];
-    // wait for whoever wrote or still reads this copy
-    TRY(enter(c, s));
-    TRY(wait_ready(c, c->cur, s));
-    TRY(wait_readers(c, c->cur, s));
+    const int to = copy_to_write(c);
+    float *theta = c->theta2[to];
+    TRY(wait_ready(c, s));
+    TRY(wait_writable(c, s));
     ga3c::launch(fill_kernel, dim3(blocks_for(c->P)), dim3(256), 0, s, theta, c->P, 0.f);
     ga3c::launch(fill_kernel, dim3(blocks_for(c->P)), dim3(256), 0, s, c->g, c->P, 0.f);
     HIP_TRY(hipGetLastError());
@@ -2386,9 +2409,8 @@ extern "C" int ga3c_params_init(ga3c_ctx *c, uint64_t seed, void *stream) {
                            (size_t)t[i].off, t[i].n, sqrtf(2.f / (float)t[i].fan_in), seed);
         HIP_TRY(hipGetLastError());
     }
-    TRY(refresh_derived(c, c->cur, s));
-    TRY(mark_ready(c, c->cur, s));
-    return GA3C_OK;
+    TRY(refresh_derived(c, to, s));
+    return publish(c, s);
 }
 
 static float *select_buffer(ga3c_ctx *c, int which) {
@@ -2399,12 +2421,21 @@ extern "C" int ga3c_params_get(ga3c_ctx *c, int which, float *dst, size_t n, voi
     if (!c || !dst) return fail(GA3C_EINVAL, "ga3c_params_get: null argument");
     float *src = select_buffer(c, which);
     if (!src || n != c->P) return fail(GA3C_EINVAL, "ga3c_params_get: which must be 0..2 and n the parameter count");
-    TRY(enter(c, (hipStream_t)stream));
-    TRY(wait_ready(c, c->cur, (hipStream_t)stream));
+    hipStream_t s = (hipStream_t)stream;
+    TRY(wait_ready(c, s));
+    // the writer that the copying has to come before: on the last writer's stream, unless that one writes in place (the event
+    // costs the stream 2 us)
+    Mark &done = c->copied[c->cur];
+    const bool marked = which == 0 && (copy_to_write(c) == c->cur || c->ready[c->cur].where != s);
+    ga3c::StopEvent stop;
+    if (marked) {
+        TRY(wait_mark(done, s));      // the event then stands for the earlier copies too
+        stop = stop_for(done, s);
+    }
     const size_t n4 = is_aligned16(dst) && is_aligned16(src) ? n / 4 : 0;
-    ga3c::launch(copy_kernel, dim3(std::min(blocks_for(n4 ? n4 : n), 4096u)), dim3(256), 0, (hipStream_t)stream, dst, (const float *)src, n, n4);
+    ga3c::launch_stop(&stop, copy_kernel, dim3(std::min(blocks_for(n4 ? n4 : n), 4096u)), dim3(256), 0, s, dst, (const float *)src, n, n4);
     HIP_TRY(hipGetLastError());
-    return GA3C_OK;
+    return marked ? set_mark(done, s, &stop) : GA3C_OK;
 }
 
 extern "C" int ga3c_params_set(ga3c_ctx *c, int which, const float *src, size_t n, void *stream) {
@@ -2412,15 +2443,13 @@ extern "C" int ga3c_params_set(ga3c_ctx *c, int which, const float *src, size_t 
     if ((which != 0 && which != 1) || n != c->P)
         return fail(GA3C_EINVAL, "ga3c_params_set: which must be 0 or 1 and n the parameter count");
     hipStream_t s = (hipStream_t)stream;
-    TRY(enter(c, s));
-    TRY(wait_ready(c, c->cur, s));
-    TRY(wait_readers(c, c->cur, s));
-    HIP_TRY(hipMemcpyAsync(select_buffer(c, which), src, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
-    if (which == 0) {
-        TRY(refresh_derived(c, c->cur, s));
-        TRY(mark_ready(c, c->cur, s));
-    }
-    return GA3C_OK;
+    TRY(wait_ready(c, s));
+    if (which == 0) TRY(wait_writable(c, s));
+    const int to = copy_to_write(c);
+    HIP_TRY(hipMemcpyAsync(which == 0 ? c->theta2[to] : c->g, src, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+    if (which != 0) return GA3C_OK;
+    TRY(refresh_derived(c, to, s));
+    return publish(c, s);
 }
 
 static int predict_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *const *table, int B, const float *uniforms, float *logits,
@@ -2431,13 +2460,9 @@ static int predict_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *const
     if (!frames && !table) return fail(GA3C_EINVAL, "ga3c_predict: null frames");
     if (actions && !uniforms) return fail(GA3C_EINVAL, "ga3c_predict: actions requested without uniforms");
     hipStream_t s = (hipStream_t)stream;
-    const int cur = c->cur;
-    TRY(enter(c, s));
-    TRY(wait_ready(c, cur, s));
-    const int rc = forward(c, cur, c->pred, frames, table, B, false, logits, values, probs, uniforms, actions, s);
-    if (rc != GA3C_OK) return rc;
-    TRY(mark_readers(c, cur, s));
-    return GA3C_OK;
+    TRY(wait_ready(c, s));
+    TRY(begin_prediction(c, s));
+    return forward(c, c->cur, c->pred, frames, table, B, false, logits, values, probs, uniforms, actions, s);
 }
 
 extern "C" int ga3c_predict(ga3c_ctx *c, const uint8_t *frames, int B, const float *uniforms, float *logits,
@@ -2457,8 +2482,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
 
     const int cur = c->cur;
     const float *th = c->theta2[cur];
-    TRY(enter(c, s));
-    TRY(wait_ready(c, cur, s));
+    TRY(wait_ready(c, s));
     // One kernel finishes the fc layer, runs the heads, the loss and the heads' backward pass, if its LDS fits.
     const size_t ht_lds = sizeof(float) * (size_t)heads_train_lds_floats(F, A);
     const bool fused_heads = c->fast && ht_lds <= HEADS_TRAIN_MAX_LDS && HD_FRAMES * (A + 1) <= 256;      // a thread per (frame, output)
@@ -2737,18 +2761,19 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     STAGE("rmsprop", 8.0 * c->P, 20.0 * c->P);
     // one float4 per thread at these sizes; the clip factor and the statistics are formed in the kernel's prologue
     const unsigned rb = std::min<unsigned>(blocks_for(c->P / 4 + 1), 2048u);
-    // the copy about to be overwritten may still be read by predictions issued before the last update
-    TRY(wait_readers(c, cur ^ 1, s));
+    const int to = copy_to_write(c);
+    TRY(wait_writable(c, s));
     RmsClip ca;
     ca.normpart = c->partials; ca.nnorm = red_blocks; ca.losspart = losspart; ca.nloss = nloss; ca.clip = hp->clip_norm;
     ca.scale_out = c->scale; ca.own = c->stats; ca.user = stats;
-    ga3c::launch((rmsprop_kernel<0, 1>), dim3(rb), dim3(256), 0, s, th, c->theta2[cur ^ 1], c->g, c->grad, c->P, (const float *)nullptr,
-                       1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[cur ^ 1], (unsigned)c->off[0], (unsigned)c->off[2], c->rb, c->fcw[cur ^ 1], ca);
+    const bool fragments = c->lfrag[to] || c->bfrag[to];      // they follow the new parameters, in launches of their own
+    ga3c::StopEvent stop = stop_for(c->ready[to], s);
+    ga3c::launch_stop(fragments ? nullptr : &stop, (rmsprop_kernel<0, 1>), dim3(rb), dim3(256), 0, s, th, c->theta2[to], c->g, c->grad, c->P,
+                      (const float *)nullptr, 1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[to], (unsigned)c->off[0], (unsigned)c->off[2], c->rb,
+                      c->fcw[to], ca);
     HIP_TRY(hipGetLastError());
-    if (c->lfrag[cur ^ 1] || c->bfrag[cur ^ 1]) TRY(refresh_derived(c, cur ^ 1, s, false));      // the larger net's fragments follow the new parameters
-    TRY(mark_ready(c, cur ^ 1, s));
-    c->cur = cur ^ 1;        // calls enqueued from now on see the new parameters
-    return GA3C_OK;
+    if (fragments) TRY(refresh_derived(c, to, s, false));
+    return publish(c, s, &stop);
 }
 
 extern "C" int ga3c_train_step(ga3c_ctx *c, const uint8_t *frames, const int32_t *actions, const float *rewards,

@@ -26,24 +26,38 @@ inline thread_local LaunchTimer *launch_timer = nullptr;
 
 namespace detail {
 template <typename... KArgs, size_t... I>
-inline hipError_t launch_timed(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, hipEvent_t a,
+inline hipError_t launch_events(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, hipEvent_t a,
                                hipEvent_t b, std::tuple<KArgs...> &args, std::index_sequence<I...>) {
     void *ptrs[sizeof...(KArgs) > 0 ? sizeof...(KArgs) : 1] = {(void *)&std::get<I>(args)...};
     return hipExtLaunchKernel((const void *)kernel, grid, block, ptrs, lds, s, a, b, 0);
 }
 }  // namespace detail
 
+// An event that a launch shall complete, as the dispatch's own completion signal: an event recorded behind the launch is one
+// more packet for the queue (an update of 8 agents: 77.7 us with a recorded event, 76.2 with this one, 74.4 with none).
+// ev == nullptr, or a launch that a stage timer has taken: not attached, and whoever wants the event records it.
+struct StopEvent {
+    hipEvent_t ev = nullptr;
+    bool attached = false;
+};
+
 // kernel<<<grid, block, lds, s>>>(args...); the arguments convert to the kernel's parameter types as in a call.
 template <typename... KArgs, typename... Args>
-inline void launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, Args &&...args) {
+inline void launch_stop(StopEvent *stop, void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, Args &&...args) {
     static_assert(sizeof...(KArgs) == sizeof...(Args), "one argument per kernel parameter");
     hipEvent_t a = nullptr, b = nullptr;
-    if (launch_timer && launch_timer->next_events(&a, &b)) {
+    const bool timed = launch_timer && launch_timer->next_events(&a, &b);
+    if (!timed && stop && stop->ev) { b = stop->ev; stop->attached = true; }
+    if (b) {
         std::tuple<KArgs...> held{static_cast<KArgs>(args)...};
-        (void)detail::launch_timed(kernel, grid, block, lds, s, a, b, held, std::index_sequence_for<KArgs...>{});
+        (void)detail::launch_events(kernel, grid, block, lds, s, a, b, held, std::index_sequence_for<KArgs...>{});
         return;
     }
     hipLaunchKernelGGL(kernel, grid, block, lds, s, static_cast<KArgs>(args)...);
+}
+template <typename... KArgs, typename... Args>
+inline void launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t lds, hipStream_t s, Args &&...args) {
+    launch_stop(nullptr, kernel, grid, block, lds, s, static_cast<Args &&>(args)...);
 }
 
 }  // namespace ga3c

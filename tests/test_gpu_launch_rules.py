@@ -80,3 +80,56 @@ def test_calls_that_move_to_a_second_stream_wait_for_the_first(G):
         net.close()
     for x, y in zip(*got):
         np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("B", [5, 64, 70])
+def test_captured_predictions_replay_as_called(G, B):
+    # a stream under capture gets its fences as nodes of their own (a launch that completes an event cannot be captured)
+    import torch
+    A = 18
+    net = G.Ga3c(G.SMALL_NET(A), B, 0)
+    s = torch.cuda.Stream()
+    frames = torch.from_numpy(synth.rectangle_frames(7501, B)).cuda()
+    got, want = torch.zeros(B, A, device="cuda"), torch.zeros(B, A, device="cuda")
+    net.params_init(7502)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        net.predict(frames, logits=got, stream=s)
+    for _ in range(3):
+        got.zero_()
+        net.predict(frames, logits=want, stream=s)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want.cpu().numpy())
+    assert want.abs().max().item() > 0
+    net.close()
+
+
+@pytest.mark.parametrize("which", ["small", "large", "paper3"])
+def test_updates_in_place_give_the_same_parameters(G, which):
+    # updates without a prediction between them overwrite the published parameters, and what is derived from them; with one
+    # between them they write the other copy
+    import torch
+    N, T, A = 9, 5, 6
+    desc = {"small": G.SMALL_NET(A), "large": G.LARGE_NET(A)}.get(which) or P.paper_family_net(G, 3, A)
+    frames = torch.from_numpy(synth.rectangle_frames(7601, N * T).reshape(N, T, 4, 84, 84)).cuda()
+    first = frames[:, 0].contiguous()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(7602, N, T, A).items()}
+    got = []
+    for predictions in (1, 2, 0):                 # before every update, before every second one, only at the end
+        net = G.Ga3c(desc, N, N * T)
+        net.params_init(7603)
+        out = torch.empty(N, A, device="cuda")
+        for k in range(6):
+            if predictions and k % predictions == 0:
+                net.predict(first, logits=out)
+            net.train_step(frames, tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.01))
+        net.predict(first, logits=out)
+        torch.cuda.synchronize()
+        got.append((out.cpu().numpy(), net.params_get(0).cpu().numpy(), net.params_get(1).cpu().numpy()))
+        net.close()
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            np.testing.assert_array_equal(x, y)
