@@ -126,7 +126,6 @@ struct PredSlot {
     int n = 0;
     const uint4 **ptrs_h = nullptr;                       // *_h: pinned host memory, which the kernels read and write
     float *unif_h = nullptr;
-    uint8_t *frames_d = nullptr;                          // the batch's frames, for networks that do not take a table
     int32_t *act_h = nullptr;
     float *val_h = nullptr;
     std::vector<int> agents;
@@ -138,7 +137,6 @@ struct TrainSlot {
     bool busy = false;
     int n_agents = 0;
     const uint4 **ptrs_h = nullptr;
-    uint8_t *frames_d = nullptr;
     int32_t *act_h = nullptr, *act_d = nullptr;
     float *rew_h = nullptr, *rew_d = nullptr;
     uint8_t *done_h = nullptr, *done_d = nullptr;
@@ -165,6 +163,8 @@ struct ga3c_sched {
     PredSlot ps[RING];
     TrainSlot ts[RING];
     int ps_next, ts_next;
+    uint8_t *pred_frames, *train_frames;      // a batch's frames, where the network does not take them from a table: one of each
+                                              // will do, since the batches of a kind follow each other on their stream
     FlatQueue<ga3c_prediction> ready;
     ga3c_tuner *tuner;
     ga3c_sched_stats stats;
@@ -188,6 +188,9 @@ int device(T **p, size_t n) {
 
 int alloc_slots(ga3c_sched *s) {
     const int maxN = s->max_train;      // a segment has at least one frame
+    // also for a network that takes a table: ga3c_use_generic_kernels may come at any time, and a tick allocates nothing
+    STRY(device(&s->pred_frames, (size_t)s->max_pred * s->frame_bytes));
+    STRY(device(&s->train_frames, (size_t)s->max_train * s->frame_bytes));
     for (int i = 0; i < RING; ++i) {
         PredSlot &p = s->ps[i];
         SHIP(hipEventCreateWithFlags(&p.done, hipEventDisableTiming));
@@ -259,10 +262,9 @@ int issue_predict(ga3c_sched *s, int *count) {
     if (ga3c::takes_frame_table(s->ctx))
         rc = ga3c::predict_from_table(s->ctx, (const uint8_t *const *)p.ptrs_h, n, p.unif_h, p.val_h, p.act_h, s->sp);
     else {
-        if (!p.frames_d) STRY(device(&p.frames_d, (size_t)s->max_pred * s->frame_bytes));      // made when first needed
-        hipLaunchKernelGGL(gather_frames_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, (uint4 *)p.frames_d, (int)(s->frame_bytes / 16));
+        hipLaunchKernelGGL(gather_frames_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, (uint4 *)s->pred_frames, (int)(s->frame_bytes / 16));
         SHIP(hipGetLastError());
-        rc = ga3c_predict(s->ctx, p.frames_d, n, p.unif_h, nullptr, p.val_h, nullptr, p.act_h, s->sp);
+        rc = ga3c_predict(s->ctx, s->pred_frames, n, p.unif_h, nullptr, p.val_h, nullptr, p.act_h, s->sp);
     }
     if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_predict: %s", ga3c_last_error());
     SHIP(hipEventRecord(p.done, s->sp));
@@ -310,15 +312,14 @@ int issue_train(ga3c_sched *s, int *count) {
     if (table && equal) {        // every list is read where the host wrote it
         rc = ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_h, t.rew_h, t.done_h, t.boot_h, nullptr, n, T, B, &s->cfg.hp, s->st);
     } else {
-        if (!table && !t.frames_d) STRY(device(&t.frames_d, (size_t)s->max_train * s->frame_bytes));
-        const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, table ? nullptr : (uint4 *)t.frames_d, t.act_d, t.seg_d,
+        const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, table ? nullptr : (uint4 *)s->train_frames, t.act_d, t.seg_d,
                              t.rew_d, t.boot_d, t.done_d, (int)(s->frame_bytes / 16), n};
         hipLaunchKernelGGL(gather_experiences_kernel, dim3(B), dim3(256), 0, s->st, ga);
         SHIP(hipGetLastError());
         rc = table   ? ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_d, t.rew_d, t.done_d, t.boot_d, t.seg_d, n, 1, B,
                                               &s->cfg.hp, s->st)
-             : equal ? ga3c_train_step(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp, nullptr, s->st)
-                     : ga3c_train_step_ragged(s->ctx, t.frames_d, t.act_d, t.rew_d, t.done_d, t.seg_d, t.boot_d, n, B, &s->cfg.hp, nullptr, s->st);
+             : equal ? ga3c_train_step(s->ctx, s->train_frames, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp, nullptr, s->st)
+                     : ga3c_train_step_ragged(s->ctx, s->train_frames, t.act_d, t.rew_d, t.done_d, t.seg_d, t.boot_d, n, B, &s->cfg.hp, nullptr, s->st);
     }
     if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_train_step: %s", ga3c_last_error());
     SHIP(hipEventRecord(t.done, s->st));
@@ -363,7 +364,7 @@ extern "C" int ga3c_sched_create(ga3c_ctx *ctx, const ga3c_sched_config *cfg, ga
     if (!s) return sfail(GA3C_ENOMEM, "ga3c_sched_create: out of memory");
     s->ctx = ctx; s->cfg = *cfg; s->desc = d; s->max_pred = mp; s->max_train = mt; s->frame_bytes = fb;
     s->predict_cap = cfg->predict_cap; s->train_cap = cfg->train_cap;
-    s->sp = s->st = nullptr; s->ps_next = s->ts_next = 0; s->tuner = nullptr; s->tq_frames = 0;
+    s->sp = s->st = nullptr; s->ps_next = s->ts_next = 0; s->pred_frames = s->train_frames = nullptr; s->tuner = nullptr; s->tq_frames = 0;
     memset(&s->stats, 0, sizeof(s->stats));
     s->stats.predict_cap = s->predict_cap; s->stats.train_cap = s->train_cap;
     s->window_ticks = s->window_frames = 0;
@@ -396,15 +397,16 @@ extern "C" int ga3c_sched_destroy(ga3c_sched *s) {
     for (int i = 0; i < RING; ++i) {
         PredSlot &p = s->ps[i];
         if (p.done) (void)hipEventDestroy(p.done);
-        (void)hipHostFree(p.ptrs_h); (void)hipHostFree(p.unif_h); (void)hipFree(p.frames_d);
+        (void)hipHostFree(p.ptrs_h); (void)hipHostFree(p.unif_h);
         (void)hipHostFree(p.act_h); (void)hipHostFree(p.val_h);
         TrainSlot &t = s->ts[i];
         if (t.done) (void)hipEventDestroy(t.done);
-        (void)hipHostFree(t.ptrs_h); (void)hipFree(t.frames_d);
+        (void)hipHostFree(t.ptrs_h);
         (void)hipHostFree(t.act_h); (void)hipFree(t.act_d); (void)hipHostFree(t.rew_h); (void)hipFree(t.rew_d);
         (void)hipHostFree(t.done_h); (void)hipFree(t.done_d); (void)hipHostFree(t.boot_h); (void)hipFree(t.boot_d);
         (void)hipHostFree(t.seg_h); (void)hipFree(t.seg_d);
     }
+    (void)hipFree(s->pred_frames); (void)hipFree(s->train_frames);
     if (s->sp) (void)hipStreamDestroy(s->sp);
     if (s->st) (void)hipStreamDestroy(s->st);
     ga3c_tuner_destroy(s->tuner);

@@ -302,12 +302,47 @@ static void packets_check() {
     }
 }
 
+// A scheduler's tick only enqueues, from the first one on, whichever way its network takes the frames: nothing is allocated, no
+// stream is waited for, no other stream used than the scheduler's two.
+static void ticks_check() {
+    for (const char *net : {"small", "large", "paper3"})
+        for (bool generic : {false, true}) {
+            Program p(net);
+            p.init(nullptr);
+            const std::map<hipStream_t, Stream> before = streams;
+            ga3c_sched_config cfg;
+            memset(&cfg, 0, sizeof(cfg));
+            cfg.t_max = 5; cfg.predict_cap = 16; cfg.train_min = 10; cfg.train_cap = 40; cfg.hp = p.hp;
+            ga3c_sched *s = nullptr;
+            if (ga3c_sched_create(p.ctx, &cfg, &s) != GA3C_OK) { PROBLEM("sched_create: %s", ga3c_sched_last_error()); return; }
+            given.clear();
+            for (const auto &x : streams) if (!before.count(x.first)) given.insert(x.first);
+            if (generic) ga3c_use_generic_kernels(p.ctx, 1);
+            const int32_t actions[5] = {0, 1, 2, 3, 4};
+            const float rewards[5] = {0, 0, 1, 0, 0};
+            const uint8_t dones[5] = {0, 0, 0, 0, 1};
+            for (int k = 0; k < 12; ++k) {
+                for (int a = 0; a < 20; ++a) {
+                    if (ga3c_sched_submit_predict(s, a, address(a), 0.5f) != GA3C_OK) PROBLEM("submit_predict");
+                    if (ga3c_sched_submit_segment(s, a, address(a), 1 + (a + k) % 5, actions, rewards, dones, 0.f, 0) != GA3C_OK) PROBLEM("submit_segment");
+                }
+                in_call = true;
+                int predicted = 0, trained = 0;
+                if (ga3c_sched_tick(s, &predicted, &trained) != GA3C_OK) PROBLEM("tick: %s", ga3c_sched_last_error());
+                in_call = false;
+                if (predicted < 1 || trained < 1) PROBLEM("a tick of %d predictions and %d trained frames", predicted, trained);
+            }
+            ga3c_sched_destroy(s);
+        }
+}
+
 int main(int argc, char **argv) {
     streams[nullptr] = Stream();
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "streams") streams_check();
     else if (what == "capture") capture_check();
     else if (what == "packets") packets_check();
+    else if (what == "ticks") ticks_check();
     else PROBLEM("no such check");
     printf("%zu launches, %d problems\n", ops.size(), problems);
     return problems ? 1 : 0;

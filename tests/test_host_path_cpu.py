@@ -30,6 +30,7 @@ def model(tmp_path_factory):
     "streams",      # calls on streams that come and go: every read and write of a parameter copy in order, no handle kept
     "capture",      # a stream that is being captured
     "packets",      # what predictions and updates leave in the queues besides their launches
+    "ticks",        # a scheduler's tick allocates nothing and waits for nothing
 ])
 def test_host_path(model, check):
     r = subprocess.run([model, check], capture_output=True, text=True, timeout=120)
