@@ -217,6 +217,77 @@ def test_short_segments_and_policy_lag(G):
     sched.close(); ns.close(); nd.close()
 
 
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("which", ["small", "large", "paper4", "paper3"])
+def test_batches_of_any_size_match_direct_calls(G, which, math):
+    # The frames of a batch lie anywhere: the small and the larger net's first layer takes them from a table of pointers, up to
+    # two turns of the grid ahead (batches of more frames than twice the 512 blocks), for other networks a kernel puts them
+    # together first.  Small batches of the small net go through the one-launch kernels with one and with two frames per block.
+    import torch
+    T, N, A = 5, 210, 6
+    sizes = [1037, 5, 37] if which == "small" else [1037, 9]
+    desc = {"small": G.SMALL_NET(A), "large": G.LARGE_NET(A)}.get(which) or \
+        G.NetDesc(conv=((32, 8, int(which[-1])), (32, 4, 2), (64, 4, 2)), fc_units=256, n_actions=A)
+    desc.math = math
+    ns, nd = [G.Ga3c(desc, max(sizes), N * T) for _ in range(2)]      # behind the scheduler; called directly
+    theta = torch.from_numpy(synth.perturbed_theta(8800, nd.offsets(), nd.n_params)).cuda()
+    for n in (ns, nd):
+        n.params_set(theta, 0)
+    gen = torch.Generator(device="cuda").manual_seed(8801)
+    frames = torch.randint(0, 256, (N, T, 4, 84, 84), dtype=torch.uint8, generator=gen, device="cuda")
+    flat, fb = frames.view(N * T, 4, 84, 84), 4 * 84 * 84
+    rng = np.random.default_rng(8802)
+    hp = G.HParams(lr=1e-3, clip_norm=40.0)
+    sched = G.Scheduler(ns, hp, t_max=T, predict_cap=max(sizes), train_min=1, train_cap=N * T)
+    torch.cuda.synchronize()
+
+    def predictions(n):
+        at = rng.permutation(N * T)[:n]
+        u = rng.random(n, dtype=np.float32)
+        sched.submit_predict_many(np.arange(n, dtype=np.int32), np.uint64(flat.data_ptr()) + at.astype(np.uint64) * np.uint64(fb), u)
+        print(f"{which} math={math} predict {n}", flush=True)
+        assert sched.tick() == (n, 0)
+        sched.drain()
+        who, act, val = sched.poll_arrays()
+        v, p, a = direct_predict(nd, flat[torch.from_numpy(at).cuda()].contiguous(), u)
+        assert v.std() > 0
+        np.testing.assert_array_equal(val[np.argsort(who)], v)
+        np.testing.assert_array_equal(act[np.argsort(who)], a)
+
+    def update(lens):
+        n = len(lens)
+        order = rng.permutation(N)[:n]                                # whose frames: nothing lies where its place in the batch is
+        tr = synth.trajectories(8803 + n, n, T, A)
+        boot = rng.standard_normal(n).astype(np.float32)
+        start = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        sched.submit_segment_many(np.arange(n, dtype=np.int32), np.uint64(flat.data_ptr()) + order.astype(np.uint64) * np.uint64(T * fb),
+                                  lens, tr["actions"], tr["rewards"], tr["dones"], boot)
+        print(f"{which} math={math} update of {start[-1]} frames", flush=True)
+        assert sched.tick() == (0, start[-1])
+        sched.drain()
+        fr = frames[torch.from_numpy(order).cuda()]
+        dev = {k: torch.from_numpy(v).cuda() for k, v in tr.items()}
+        bt = torch.from_numpy(boot).cuda()
+        if (lens == T).all():
+            nd.train_step(fr.contiguous(), dev["actions"], dev["rewards"], dev["dones"], bt, hp)
+        else:
+            keep = torch.from_numpy(np.arange(T)[None] < lens[:, None]).cuda()
+            nd.train_step_ragged(fr[keep].contiguous(), dev["actions"][keep], dev["rewards"][keep], dev["dones"][keep],
+                                 torch.from_numpy(start).cuda(), bt, hp)
+        torch.cuda.synchronize()
+        for k in (0, 1):
+            np.testing.assert_array_equal(ns.params_get(k).cpu().numpy(), nd.params_get(k).cpu().numpy())
+
+    for n in sizes:
+        predictions(n)
+    update(np.full(N, T, np.int32))
+    predictions(sizes[0])
+    update(rng.integers(1, T + 1, N).astype(np.int32))
+    update(np.full(3, T, np.int32))
+    predictions(sizes[-1])
+    sched.close(); ns.close(); nd.close()
+
+
 def test_scheduler_host_code_is_clean_under_the_address_and_undefined_behaviour_sanitizers():
     # paper_1611_06256_amd/sched_sanitized (built beforehand by build.py / the entry point's build()) is the whole
     # library with its HOST code under ASan and UBSan plus tests/sched_sanitizer_driver.cpp: a closed loop of agents with
