@@ -1,4 +1,4 @@
-// The 4x4, stride-2 convolution layer with 16 or 32 input channels and 32 or 64
+// The 4x4, stride-2 convolution layer with 32 input channels and 32 or 64
 // filters on maps of any size (the paper's larger-network family, Sec. 5, whose
 // maps are 9 to 77 pixels wide): forward pass of predictions on the bf16 matrix
 // cores at fp32 accuracy (updates keep one order of sums: conv_band_f32.hpp).

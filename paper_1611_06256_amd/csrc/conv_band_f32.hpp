@@ -485,7 +485,7 @@ struct F32WgradGeom {
     int rows;                // input rows of a step in LDS, at most
     int RF, d;               // rows per frame in the numbering above; frame boundaries in a step, at most
     int stage;               // bytes of one half of the LDS buffers
-    FastDiv dNPIX, dOW, dRF;
+    FastDiv dNPIX, dOW;
     float scale;
 };
 template <class TIn> constexpr int f32_wgrad_waves() { return sizeof(TIn) == 1 ? 4 : 8; }
@@ -740,7 +740,7 @@ inline F32WgradGeom f32_wgrad_geom(int C, int H, int W, int S, int n, int kchunk
     const int R = (f32_wgrad_kt<TIn>() - 2) / b.OW + 2;
     b.d = (R - 2) / b.OH + 1;
     b.rows = S * (R - 1) + KS + b.d * std::max(0, KS - S);
-    b.dNPIX = FastDiv((uint32_t)(b.OH * b.OW)); b.dOW = FastDiv((uint32_t)b.OW); b.dRF = FastDiv((uint32_t)b.RF);
+    b.dNPIX = FastDiv((uint32_t)(b.OH * b.OW)); b.dOW = FastDiv((uint32_t)b.OW);
     return b;
 }
 template <class TIn>

@@ -2146,7 +2146,7 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
         for (int l = 0; l < c->nconv; ++l) {
             const ConvGeom &g = c->geom[l];
             pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kc);
-            nz = std::max(nz, std::min(B, 512));                                 // generic or frame-resident kernel
+            nz = std::max(nz, std::min(B, 512));                                 // any-shape kernel, or one partial per block
             add((size_t)nz * g.OC * (g.K + 1));
         }
         int nz2;
@@ -2629,36 +2629,34 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         {
             const void *xin = l == 0 ? (const void *)frames : (const void *)w.act[l - 1];
             const bool ok = c->fast && is_aligned16(xin);
-            const int kind = !ok ? 0 : (spec_matches<SpecS1>(g, l == 0) && is_aligned16(c->dact[l])) ? 1
-                                     : (spec_matches<SpecL1>(g, l == 0) && is_aligned16(c->dact[l])) ? 2
-                                     : spec_matches<SpecS2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 6 : 3)
-                                     : spec_matches<SpecL2>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 7 : 4)
-                                     : spec_matches<SpecL3>(g, l == 0) ? (is_aligned16(c->dact[l]) ? 8 : 5)
-                                     : (spec_matches<SpecP2>(g, l == 0) && is_aligned16(c->dact[l])) ? 9
-                                     : c->band[l] && (l == 0 ? f32_wgrad_ok<uint8_t>(g.C, g.H, g.W, g.S, g.OC) : f32_wgrad_ok<float>(g.C, g.H, g.W, g.S, g.OC)) ? 10 : 0;
+            const int kind = !ok || !is_aligned16(c->dact[l]) ? 0
+                                     : spec_matches<SpecS1>(g, l == 0) ? 1
+                                     : spec_matches<SpecL1>(g, l == 0) ? 2
+                                     : spec_matches<SpecS2>(g, l == 0) ? 3
+                                     : spec_matches<SpecL2>(g, l == 0) ? 4
+                                     : spec_matches<SpecL3>(g, l == 0) ? 5
+                                     : spec_matches<SpecP2>(g, l == 0) ? 6
+                                     : c->band[l] && (l == 0 ? f32_wgrad_ok<uint8_t>(g.C, g.H, g.W, g.S, g.OC) : f32_wgrad_ok<float>(g.C, g.H, g.W, g.S, g.OC)) ? 7 : 0;
             if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
-            else if (kind == 3) nz = conv_wgrad_frame_blocks<SpecS2>(B);
-            else if (kind == 4) nz = conv_wgrad_frame_blocks<SpecL2>(B);
-            else if (kind == 5) nz = conv_wgrad_frame_blocks<SpecL3>(B);
-            else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
-            else if (kind == 7) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
-            else if (kind == 8) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
-            else if (kind == 9) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
+            else if (kind == 3) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
+            else if (kind == 4) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
+            else if (kind == 5) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
+            else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
             // The 4x4 stride-2 layers' two gradients share a launch.  The small net's has a quarter of the products, and above 640
             // frames (a bit more than one per block that the chip holds) it gains or loses 1 % with how the frames divide.
-            if ((kind == 6 || kind == 7 || kind == 9) && (kind != 6 || B <= 640) && is_aligned16(th + c->off[2 * l])) {
+            if ((kind == 3 || kind == 4 || kind == 6) && (kind != 3 || B <= 640) && is_aligned16(th + c->off[2 * l])) {
                 STAGE2(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W),
                        CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * (4.0 * g.CHW + 4.0 * g.OC * g.OHW));
                 const float *x = (const float *)xin, *dy = c->dact[l], *wl = th + c->off[2 * l];
                 // the fragments of the copy being trained on, when the context keeps them
-                if (kind == 6)
+                if (kind == 3)
                     HIP_TRY(launch_conv_grads_bf16x6<SpecS2>(x, dy, wl, c->cfrag[cur] && c->cfrag_dgrad ? c->cfrag[cur] + CFRAG_FWD_VECS : nullptr,
                                                              c->dact[l - 1], part, B, s, c->rb));
-                else if (kind == 7)
+                else if (kind == 4)
                     HIP_TRY((launch_conv_grads_bf16x6<SpecL2, 32>(x, dy, wl, c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr,
                                                                   c->dact[l - 1], part, B, s, c->rb)));
                 else
@@ -2672,23 +2670,17 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             } else if (kind == 2) {
                 HIP_TRY(launch_conv1_bf16x3_wgrad<32>((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
             } else if (kind == 3) {
-                HIP_TRY((launch_conv_wgrad_frame<SpecS2, 1, 8>)((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 4) {
-                HIP_TRY((launch_conv_wgrad_frame<SpecL2, 4, 8>)((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 5) {
-                HIP_TRY((launch_conv_wgrad_frame<SpecL3, 3>)((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 6) {
                 HIP_TRY(launch_conv_wgrad_bf16x6<SpecS2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 7) {
+            } else if (kind == 4) {
                 HIP_TRY((launch_conv_wgrad_bf16x6<SpecL2, 32>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb)));
-            } else if (kind == 8) {
+            } else if (kind == 5) {
                 HIP_TRY(launch_conv_wgrad_s1_bf16x6<SpecL3>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 9) {
+            } else if (kind == 6) {
                 HIP_TRY(launch_conv_wgrad_bf16x6<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 10 && l == 0) {
+            } else if (kind == 7 && l == 0) {
                 if (g.OC == 16) HIP_TRY((launch_conv_f32_wgrad<uint8_t, 16>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
                 else HIP_TRY((launch_conv_f32_wgrad<uint8_t, 32>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
-            } else if (kind == 10) {
+            } else if (kind == 7) {
                 if (g.OC == 32) HIP_TRY((launch_conv_f32_wgrad<float, 32>((const float *)xin, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f, s, c->rb)));
                 else HIP_TRY((launch_conv_f32_wgrad<float, 64>((const float *)xin, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f, s, c->rb)));
             } else if (l == 0) {
@@ -2712,15 +2704,6 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             // the fragments of the copy being trained on, when the context keeps them (it does when conv1 is the small net's too)
             const u32x4 *wfrag = c->cfrag[cur] && c->cfrag_dgrad ? c->cfrag[cur] + CFRAG_FWD_VECS : nullptr;
             HIP_TRY(launch_conv_dgrad_bf16x6<SpecS2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb, wfrag));
-            continue;
-        }
-        if (c->fast && spec_matches<SpecL2>(g, false) && is_aligned16(th + c->off[2 * l])) {
-            HIP_TRY(launch_conv_dgrad_bf16x6<SpecL2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb,
-                                                     c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr));
-            continue;
-        }
-        if (c->fast && spec_matches<SpecP2>(g, false) && is_aligned16(th + c->off[2 * l])) {
-            HIP_TRY(launch_conv_dgrad_bf16x6<SpecP2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb));
             continue;
         }
         if (c->fast && c->band[l] && is_aligned16(th + c->off[2 * l])) {
