@@ -2595,7 +2595,12 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         q.A = c->dh; q.lda = F; q.B = wfc; q.ldb = c->flat;
         q.C = c->dact[c->nconv - 1]; q.ldc = c->flat; q.aux = xfc;
         STAGE2("fc_wgrad", 2.0 * B * F * c->flat, 0, "fc_dgrad", 2.0 * B * F * c->flat, 0);
-        if (B <= 640) HIP_TRY((launch_dense_fc_grads<2, 2>(q, p, s)));
+        // The input gradient's tile is 64x64 as long as there is one tile per compute unit at most, 128x64 above that: fewer tiles
+        // leave units idle, more read their operands twice.  64x64 against 128x64, us of the launch (tiles of 64x64): small net
+        // 160 frames 15.9 / 18.7 (123), 320: 15.0 / 17.9 (205), 480: 19.8 / 19.0 (328), 2560: 63.5 / 57.2; larger net 320: 28.3 /
+        // 30.0 (245), 480: 37.9 / 35.8 (392), 1280: 74.1 / 66.9; stride-4 member 960: 13.1 / 16.9 (135); stride-2 member 320: 20.3
+        // / 19.7 (320); stride-1 member 80: 294 / 286 (578).
+        if (cdiv(B, 64) * cdiv(c->flat, 64) <= 256) HIP_TRY((launch_dense_fc_grads<2, 2>(q, p, s)));
         else HIP_TRY((launch_dense_fc_grads<4, 1>(q, p, s)));
         add_seg(p.C, nz, p.M, p.N, 0, p.M, c->grad + c->off[nb], nullptr, 0);
         add_seg(c->colpart, cdiv(B, HD_FRAMES), 1, F, 0, 1, c->grad + c->off[nb + 1], nullptr, 0);

@@ -32,7 +32,7 @@ def test_heads_after_few_and_many_partial_sums(G, F, B):
 
 
 @pytest.mark.parametrize("math", [0, 1])
-@pytest.mark.parametrize("N", [128, 129])
+@pytest.mark.parametrize("N", [76, 77, 128, 129])      # the input gradient's 41 columns of tiles: 6 rows of them up to 384 frames
 def test_fc_gradients_where_the_tile_changes(G, N, math):
     desc = G.SMALL_NET(6)
     desc.math = math
