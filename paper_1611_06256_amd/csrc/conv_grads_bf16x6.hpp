@@ -2,8 +2,9 @@
 // the same dY and neither needs the other.  The input gradient's blocks come
 // first (the layer below waits for them); the weight gradient's take the compute
 // units those leave idle, all of them at small batches, the end of the launch at
-// large ones.  Updates of the small net: 40 frames 82.2 -> 76.7 us, 640 frames
-// 134.1 -> 131.8; larger net: 5 frames 157.8 -> 149.4, 1280 frames 528 -> 523.
+// large ones.  Two launches against one, us of an update: small net 5 frames 70.8 /
+// 64.9, 40: 75.4 / 69.6, 640: 124.0 / 119.3, 2560: 270.2 / 265.9; larger net 5: 148.1 /
+// 140.6, 640: 344.3 / 333.2, 1280: 505 / 508; stride-4 member 640: 243.1 / 236.9.
 #pragma once
 #include <hip/hip_runtime.h>
 

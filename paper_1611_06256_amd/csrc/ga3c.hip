@@ -2651,9 +2651,8 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
-            // The 4x4 stride-2 layers' two gradients share a launch.  The small net's has a quarter of the products, and above 640
-            // frames (a bit more than one per block that the chip holds) it gains or loses 1 % with how the frames divide.
-            if ((kind == 3 || kind == 4 || kind == 6) && (kind != 3 || B <= 640) && is_aligned16(th + c->off[2 * l])) {
+            // the 4x4 stride-2 layers' two gradients share a launch (conv_grads_bf16x6.hpp)
+            if ((kind == 3 || kind == 4 || kind == 6) && is_aligned16(th + c->off[2 * l])) {
                 STAGE2(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W),
                        CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * (4.0 * g.CHW + 4.0 * g.OC * g.OHW));
                 const float *x = (const float *)xin, *dy = c->dact[l], *wl = th + c->off[2 * l];
@@ -2705,12 +2704,6 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         // input gradient
         // bytes: dY in, the layer's input (for the ReLU mask) in, dX out
         STAGE(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W));
-        if (c->fast && spec_matches<SpecS2>(g, false) && is_aligned16(th + c->off[2 * l])) {
-            // the fragments of the copy being trained on, when the context keeps them (it does when conv1 is the small net's too)
-            const u32x4 *wfrag = c->cfrag[cur] && c->cfrag_dgrad ? c->cfrag[cur] + CFRAG_FWD_VECS : nullptr;
-            HIP_TRY(launch_conv_dgrad_bf16x6<SpecS2>(c->dact[l], th + c->off[2 * l], w.act[l - 1], c->dact[l - 1], B, s, 512, c->rb, wfrag));
-            continue;
-        }
         if (c->fast && c->band[l] && is_aligned16(th + c->off[2 * l])) {
             const float *wl = th + c->off[2 * l];
             if (g.OC == 32) HIP_TRY(launch_conv_band_f32_dgrad<32>(c->dact[l], wl, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
