@@ -1912,8 +1912,8 @@ inline bool spec_matches(const ConvGeom &g, bool byte_input) {
 inline bool is_aligned16(const void *p) { return (((uintptr_t)p) & 15) == 0; }
 
 // Things derived from parameter copy i, rebuilt on s after that copy was written there.  fc: the fc weights' too (an update
-// writes those itself).
-int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true) {
+// writes those itself).  stop: the event for the last launch, if the larger nets' fragments are among them.
+int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::StopEvent *stop = nullptr) {
     if (fc && c->fcw[i].w) {
         ga3c::launch(fc_planes_kernel, dim3(blocks_for(c->fcw[i].n)), dim3(256), 0, s, (const float4 *)c->theta2[i], c->fcw[i]);
         HIP_TRY(hipGetLastError());
@@ -1925,7 +1925,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true) {
     }
     if (c->lfrag[i]) {
         const float *w2 = c->theta2[i] + c->off[2], *w3 = c->theta2[i] + c->off[4];
-        ga3c::launch(large_filter_fragments_kernel, dim3(LFRAG_B3), dim3(256), 0, s, w2, w3, c->lfrag[i]);
+        ga3c::launch_stop(c->bfrag[i] ? nullptr : stop, large_filter_fragments_kernel, dim3(LFRAG_B3), dim3(256), 0, s, w2, w3, c->lfrag[i]);
         HIP_TRY(hipGetLastError());
     }
     if (c->bfrag[i]) {
@@ -1941,7 +1941,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true) {
             const ConvGeom &g = c->geom[l];
             add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
         }
-        ga3c::launch(band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
+        ga3c::launch_stop(stop, band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
         HIP_TRY(hipGetLastError());
     }
     return GA3C_OK;
@@ -2753,7 +2753,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                       (const float *)nullptr, 1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[to], (unsigned)c->off[0], (unsigned)c->off[2], c->rb,
                       c->fcw[to], ca);
     HIP_TRY(hipGetLastError());
-    if (fragments) TRY(refresh_derived(c, to, s, false));
+    if (fragments) TRY(refresh_derived(c, to, s, false, &stop));
     return publish(c, s, &stop);
 }
 

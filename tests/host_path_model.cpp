@@ -288,17 +288,19 @@ static void capture_check() {
 // Predictions leave no event behind, whatever stream they are on: one per publication, before the first of them; an update's event
 // rides on its last launch, and it does not wait for predictions of the parameters that it reads itself.
 static void packets_check() {
-    Program p("small");
-    hipStream_t a = new_stream(), b = new_stream();
-    p.init(a);
-    for (int k = 0; k < 10; ++k) {
-        const int before = records;
-        for (int j = 0; j < 5; ++j) p.predict(b, 1 + 6 * k);
-        if (records != before + (k > 0)) PROBLEM("%d events recorded for five predictions", records - before);
-        const int latest = (int)ops.size() - 1, marked = records;
-        p.train(a, 8);
-        if (records != marked) PROBLEM("an update recorded events behind its launches");
-        if (latest < (int)ops.back().before.size() && ops.back().before[latest]) PROBLEM("an update waits for predictions of the parameters that it reads");
+    for (const char *net : {"small", "large", "paper3"}) {
+        Program p(net);
+        hipStream_t a = new_stream(), b = new_stream();
+        p.init(a);
+        for (int k = 0; k < 10; ++k) {
+            const int before = records;
+            for (int j = 0; j < 5; ++j) p.predict(b, 1 + 6 * k);
+            if (records != before + (k > 0)) PROBLEM("%d events recorded for five predictions", records - before);
+            const int latest = (int)ops.size() - 1, marked = records;
+            p.train(a, 8);
+            if (records != marked) PROBLEM("an update recorded events behind its launches");
+            if (latest < (int)ops.back().before.size() && ops.back().before[latest]) PROBLEM("an update waits for predictions of the parameters that it reads");
+        }
     }
 }
 
