@@ -11,6 +11,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -1796,6 +1797,9 @@ struct ProfScope final : ga3c::LaunchTimer {
     ProfScope(ga3c_ctx *c, hipStream_t, const char *name, double flop, double bytes, const char *name2 = nullptr, double flop2 = 0, double bytes2 = 0)
         : p(c->prof), sid(-1), sid2(-1) {
         if (!p || !p->on) { p = nullptr; return; }
+        try {
+            p->stages.reserve(p->stages.size() + 2);
+        } catch (const std::bad_alloc &) { p = nullptr; return; }      // untimed
         sid = book(name, flop, bytes);
         if (name2) sid2 = book(name2, flop2, bytes2);
         ga3c::launch_timer = this;
@@ -1809,6 +1813,10 @@ struct ProfScope final : ga3c::LaunchTimer {
     }
     bool next_events(hipEvent_t *start, hipEvent_t *stop) override {
         ProfRec r; r.stage = sid; r.stage2 = sid2; r.a = r.b = nullptr;
+        try {       // the record, and its events' way back to the pool
+            if (p->recs.size() == p->recs.capacity()) p->recs.reserve(2 * p->recs.size() + 16);
+            p->pool.reserve(2 * p->recs.capacity() + p->pool.size());
+        } catch (const std::bad_alloc &) { return false; }
         for (hipEvent_t *e : {&r.a, &r.b}) {
             if (!p->pool.empty()) { *e = p->pool.back(); p->pool.pop_back(); }
             else if (hipEventCreate(e) != hipSuccess) { *e = nullptr; }
@@ -2242,12 +2250,13 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     for (int l = 0; l < c->nconv && rc == GA3C_OK; ++l) {
         ConvGeom &g = c->geom[l];
         const int n = (g.K + 3) / 4 * 4;
-        std::vector<int> t(n, 0);
+        std::unique_ptr<int[]> t(new (std::nothrow) int[n]());
+        if (!t) { guard(fail(GA3C_ENOMEM, "ga3c_create: host allocation failed")); break; }
         for (int cc = 0; cc < g.C; ++cc)
             for (int u = 0; u < g.KS; ++u)
                 for (int v = 0; v < g.KS; ++v) t[(cc * g.KS + u) * g.KS + v] = cc * g.H * g.W + u * g.W + v;
         if (!guard(dmalloc((void **)&c->koff[l], sizeof(int) * n))) break;
-        hipError_t e = hipMemcpy(c->koff[l], t.data(), sizeof(int) * n, hipMemcpyHostToDevice);
+        hipError_t e = hipMemcpy(c->koff[l], t.get(), sizeof(int) * n, hipMemcpyHostToDevice);
         if (e != hipSuccess) { guard(fail(GA3C_EHIP, "hipMemcpy: %s", hipGetErrorString(e))); break; }
         g.koff = c->koff[l];
     }

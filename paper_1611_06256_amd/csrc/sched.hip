@@ -111,6 +111,10 @@ struct FlatQueue {
     bool empty() const { return head == v.size(); }
     const T *data() const { return v.data() + head; }
     const T &operator[](size_t i) const { return v[head + i]; }
+    // room for n more, or std::bad_alloc with nothing changed; what is pushed into room throws nothing
+    void room(size_t n) {
+        if (v.capacity() - v.size() < n) v.reserve(std::max(v.size() + n, 2 * v.capacity()));
+    }
     void push(const T *p, size_t n) { v.insert(v.end(), p, p + n); }
     void push(const T &x) { v.push_back(x); }
     void pop(size_t n) {
@@ -184,6 +188,8 @@ int device(T **p, size_t n) {
     SHIP(hipMalloc((void **)p, sizeof(T) * std::max<size_t>(n, 1)));
     return GA3C_OK;
 }
+// A queue that cannot grow is an error code at the C boundary.
+#define NO_MEMORY(what) catch (const std::bad_alloc &) { return sfail(GA3C_ENOMEM, what ": out of memory"); }
 #define STRY(expr) do { int rc_ = (expr); if (rc_ != GA3C_OK) return rc_; } while (0)
 
 int alloc_slots(ga3c_sched *s) {
@@ -197,6 +203,7 @@ int alloc_slots(ga3c_sched *s) {
         STRY(pinned(&p.ptrs_h, s->max_pred));
         STRY(pinned(&p.unif_h, s->max_pred));
         STRY(pinned(&p.act_h, s->max_pred)); STRY(pinned(&p.val_h, s->max_pred));
+        try { p.agents.reserve(s->max_pred); } NO_MEMORY("ga3c_sched_create")
         TrainSlot &t = s->ts[i];
         SHIP(hipEventCreateWithFlags(&t.done, hipEventDisableTiming));
         STRY(pinned(&t.ptrs_h, maxN));
@@ -220,6 +227,7 @@ int harvest(ga3c_sched *s, bool wait) {
             if (q == hipErrorNotReady) continue;
             if (q != hipSuccess) return sfail(GA3C_EHIP, "hipEventQuery: %s", hipGetErrorString(q));
         }
+        try { s->ready.room(p.n); } NO_MEMORY("ga3c_sched: results")
         for (int i = 0; i < p.n; ++i)
             s->ready.push(ga3c_prediction{p.agents[i], p.act_h[i], p.val_h[i], (int32_t)p.version});
         p.busy = false;
@@ -417,6 +425,7 @@ extern "C" int ga3c_sched_destroy(ga3c_sched *s) {
 extern "C" int ga3c_sched_submit_predict(ga3c_sched *s, int agent, const uint8_t *frame_dev, float uniform) {
     if (!s || !frame_dev) return sfail(GA3C_EINVAL, "ga3c_sched_submit_predict: null argument");
     if (((uintptr_t)frame_dev) & 15) return sfail(GA3C_EINVAL, "ga3c_sched_submit_predict: frame must be 16-byte aligned");
+    try { s->pq.room(1); } NO_MEMORY("ga3c_sched_submit_predict")
     s->pq.push(PredReq{agent, frame_dev, uniform});
     return GA3C_OK;
 }
@@ -436,6 +445,7 @@ extern "C" int ga3c_sched_submit_segment(ga3c_sched *s, int agent, const uint8_t
     Traj tr;
     tr.agent = agent; tr.len = len; tr.version = policy_version < 0 ? -1 : policy_version;
     tr.frames = frames_dev; tr.bootstrap = bootstrap;
+    try { s->tq_act.room(len); s->tq_rew.room(len); s->tq_done.room(len); s->tq.room(1); } NO_MEMORY("ga3c_sched_submit_segment")
     s->tq_act.push(actions, len);
     s->tq_rew.push(rewards, len);
     s->tq_done.push(dones, len);
@@ -457,6 +467,7 @@ extern "C" int ga3c_sched_submit_predict_many(ga3c_sched *s, int n, const int32_
     for (int i = 0; i < n; ++i)
         if (!frames_dev[i] || (((uintptr_t)frames_dev[i]) & 15))
             return sfail(GA3C_EINVAL, "ga3c_sched_submit_predict_many: frame %d is null or not 16-byte aligned", i);
+    try { s->pq.room(n); } NO_MEMORY("ga3c_sched_submit_predict_many")
     for (int i = 0; i < n; ++i) s->pq.push(PredReq{agents[i], frames_dev[i], uniforms[i]});
     return GA3C_OK;
 }

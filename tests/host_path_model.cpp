@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <set>
 #include <string>
 #include <vector>
@@ -16,6 +17,15 @@
 
 static int problems = 0;
 #define PROBLEM(...) do { if (++problems <= 20) { printf("problem: " __VA_ARGS__); printf("\n"); } } while (0)
+
+static int memory_left = -1;                          // allocations until one fails; -1: none does
+void *operator new(size_t n) {
+    if (memory_left >= 0 && memory_left-- == 0) throw std::bad_alloc();
+    if (void *p = malloc(n ? n : 1)) return p;
+    abort();
+}
+void operator delete(void *p) noexcept { free(p); }
+void operator delete(void *p, size_t) noexcept { free(p); }
 
 // ------------------------------------------------------------------ the stand-in runtime --
 
@@ -338,6 +348,49 @@ static void ticks_check() {
         }
 }
 
+// Host memory that runs out while requests and segments are handed in is an error code, with nothing or everything queued.
+static void memory_check() {
+    Program p("small");
+    p.init(nullptr);
+    ga3c_sched_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.t_max = 5; cfg.predict_cap = 16; cfg.train_min = 160; cfg.train_cap = 160; cfg.hp = p.hp;
+    ga3c_sched *s = nullptr;
+    if (ga3c_sched_create(p.ctx, &cfg, &s) != GA3C_OK) { PROBLEM("sched_create: %s", ga3c_sched_last_error()); return; }
+    const int32_t actions[5] = {0, 1, 2, 3, 4}, agents[3] = {0, 1, 2};
+    const float rewards[5] = {0, 0, 1, 0, 0}, uniforms[3] = {0.1f, 0.2f, 0.3f};
+    const uint8_t dones[5] = {0, 0, 0, 0, 1}, *frames[3] = {address(0), address(1), address(2)};
+    long requests = 0, segments = 0, refused = 0;
+    for (int k = 0; k < 600; ++k)
+        for (int left = 0; left < 6; ++left) {          // the first, second, ... allocation of the call fails
+            const int what = k % 3;
+            memory_left = left;
+            int rc;
+            try {
+                rc = what == 0   ? ga3c_sched_submit_predict(s, k, address(0), 0.5f)
+                     : what == 1 ? ga3c_sched_submit_predict_many(s, 3, agents, frames, uniforms)
+                                 : ga3c_sched_submit_segment(s, k, address(0), 1 + k % 5, actions, rewards, dones, 0.f, 0);
+            } catch (...) { memory_left = -1; PROBLEM("an exception came out of a call"); return; }
+            memory_left = -1;
+            if (rc == GA3C_OK) { requests += what == 0 ? 1 : what == 1 ? 3 : 0; segments += what == 2; }
+            else if (rc != GA3C_ENOMEM) PROBLEM("code %d for memory that ran out", rc);
+            else ++refused;
+            ga3c_sched_stats st;
+            ga3c_sched_get_stats(s, &st);
+            if (st.predict_queue != requests || st.train_queue != segments) PROBLEM("%ld requests and %ld segments queued, %ld and %ld accepted",
+                                                                                    (long)st.predict_queue, (long)st.train_queue, requests, segments);
+        }
+    if (refused < 10) PROBLEM("memory ran out %ld times only", refused);
+    for (int total = 0, none = 0; none < 3;) {           // what was accepted goes through
+        int predicted = 0, trained = 0;
+        if (ga3c_sched_tick(s, &predicted, &trained) != GA3C_OK) { PROBLEM("tick: %s", ga3c_sched_last_error()); break; }
+        total += predicted;
+        none = predicted || trained ? 0 : none + 1;
+        if (none == 3 && total != requests) PROBLEM("%d of %ld requests went through", total, requests);
+    }
+    ga3c_sched_destroy(s);
+}
+
 int main(int argc, char **argv) {
     streams[nullptr] = Stream();
     const std::string what = argc > 1 ? argv[1] : "";
@@ -345,6 +398,7 @@ int main(int argc, char **argv) {
     else if (what == "capture") capture_check();
     else if (what == "packets") packets_check();
     else if (what == "ticks") ticks_check();
+    else if (what == "memory") memory_check();
     else PROBLEM("no such check");
     printf("%zu launches, %d problems\n", ops.size(), problems);
     return problems ? 1 : 0;
