@@ -40,8 +40,9 @@ Roofline conventions.  FLOP = 2 per multiply-add of a layer's definition
 sum of three bf16 terms, so a layer costs 3 (bytes x fp32) or 6 (fp32 x fp32)
 MFMAs per nominal one ("executed" FLOP); with --math 1 it costs one.  A stage's
 `frac` is algorithmic FLOP/s over the bf16 peak; `executed_frac` counts the
-MFMAs that actually run; both are at most 1.  The one fp32-MFMA kernel left
-(conv weight gradients of layers 2 and 3) is priced against 157.3 TFLOP/s.
+MFMAs that actually run; both are at most 1.  Two stages whose work goes out in
+one launch (a layer's two gradients) are booked its time in the proportion of
+their operations.
 `fp32_equivalent_tflops` is the algorithmic rate again, for comparison with
 an fp32-MFMA implementation; it is not a roofline fraction.
 """
@@ -70,27 +71,22 @@ TIMED_BLOCKS = 10
 # bytes: on the streaming RMSProp kernel over 2^28 parameters (12 B read, 8 B written per parameter) the counters read
 # 0.5000 and 1.0000 of the known bytes, hence the scale factors.  The summary is kept under profiles/.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
-COUNTER_KIB = {   # stage: {frames per launch: (FETCH_SIZE, WRITE_SIZE)}
-    "conv12_fwd": {512: (7553.2, 5184.0), 1024: (14625.2, 10368.1), 2560: (35845.2, 89929.8)},   # 2560: training, keeps y1
-    "fc_fwd": {512: (4153.5, 7168.0), 1024: (6649.5, 8192.0), 2560: (14425.5, 20480.5)},
-    "heads_fwd": {512: (3761.5, 592.0), 1024: (4262.0, 1104.0)},
-    "heads_train": {2560: (10529.0, 11960.4)},
-    "conv1_wgrad": {2560: (67613.1, 4112.0)},
-    "conv2_wgrad": {2560: (45157.9, 16450.1)},
-    "conv2_dgrad": {2560: (45250.0, 64000.0)},
-    "fc_wgrad": {2560: (19915.5, 20736.0)},
-    "fc_dgrad": {2560: (25863.8, 26022.2)},
-    "wgrad_reduce": {2560: (24263.6, 2728.5)},
-    "rmsprop": {2560: (4064.8, 5496.2)},
+COUNTER_KIB = {   # stage: {frames per launch: (FETCH_SIZE, WRITE_SIZE)}; two stages of one launch have no figure of their own
+    "conv12_fwd": {512: (7558.0, 5184.0), 1024: (14630.0, 10370.0), 2560: (35850.0, 89930.0)},   # 2560: training, keeps y1
+    "fc_fwd": {512: (4561.0, 4096.0), 1024: (7152.0, 8192.0), 2560: (14940.0, 20480.0)},
+    "heads_fwd": {512: (2188.0, 80.0), 1024: (4228.0, 80.0)},
+    "heads_train": {2560: (10520.0, 11960.0)},
+    "conv1_wgrad": {2560: (67610.0, 4112.0)},
+    "wgrad_reduce": {2560: (24260.0, 2726.0)},
+    "rmsprop": {2560: (4068.0, 9385.0)},
 }
 
 # HIP kernel behind each stage of the small net's fast path, and the larger net's
-KERNELS = {"conv12_fwd": "conv12_fused_fwd_kernel", "fc_fwd": "dense_gemm_bf16x6_kernel<2,2,2,2,k-major,k-major>",
-           "fc_wgrad": "dense_gemm_bf16x6_kernel<2,2,2,2,row-major,row-major>",
-           "fc_dgrad": "dense_gemm_bf16x6_kernel<4,2,2,2,k-major,row-major,mask>", "heads_fwd": "heads_fwd_kernel",
+KERNELS = {"conv12_fwd": "conv12_fused_fwd_kernel", "fc_fwd": "fc_forward_kernel",
+           "fc_wgrad": "dense_fc_grads_kernel", "fc_dgrad": "dense_fc_grads_kernel", "heads_fwd": "heads_predict_kernel",
            "heads_train": "heads_train_kernel", "conv1_wgrad": "conv1_bf16x3_wgrad_kernel",
-           "conv2_wgrad": "conv_wgrad_bf16x6_kernel", "conv3_wgrad": "conv_wgrad_s1_bf16x6_kernel",
-           "conv2_dgrad": "conv_dgrad_bf16x6_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
+           "conv2_wgrad": "conv_grads_bf16x6_kernel", "conv3_wgrad": "conv_wgrad_s1_bf16x6_kernel",
+           "conv2_dgrad": "conv_grads_bf16x6_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
            "conv1_fwd": "conv1_bf16x3_fwd_kernel", "conv2_fwd": "conv_fwd_bf16x6_kernel", "conv3_fwd": "conv_fwd_bf16x6_kernel",
            "wgrad_reduce": "reduce_all_kernel", "rmsprop": "rmsprop_kernel", "predict_small": "predict_small_kernel"}
 # bf16 MFMAs executed per nominal one with fp32-grade accuracy (operand split into three bf16 terms); "f32" = the
@@ -344,9 +340,9 @@ def main() -> int:
         "ms_per_step": round(sec * 1e3, 4), "spread_ms_per_step": spread([s * 1e3 for s in secs]),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32" if args.math == 0 else "bf16", "data": "synthetic",
         "arithmetic": ("fp32 accuracy with fp32 accumulation: fp32 operands split exactly into three bf16 terms on the bf16 "
-                       "MFMA (bytes are exact in bf16); one weight-gradient kernel on the fp32 MFMA") if args.math == 0 else
+                       "MFMA (bytes are exact in bf16)") if args.math == 0 else
                       "operands of every contraction rounded to bfloat16, exact products, fp32 accumulation, fp32 parameters",
-        "config": {"workload": f"configs[1]+[2]: {args.net} net, 18 actions; per step {T}x predict B={N} "
+        "config": {"workload": f"{args.net} net, 18 actions; per step {T}x predict B={N} "
                                f"and 1 train_step {N} agents x t_max={T} = {N * T} frames, "
                                "clip 40; " + ("predictions and training on two streams" if args.streams == 2 else
                                               "one stream"), "agents": N, "t_max": T, "seed": seed, "streams": args.streams,

@@ -1,14 +1,18 @@
-// Forward pass of the layers of conv_band.hpp and conv_bytes.hpp on the fp32
-// matrix instruction, for maps of any size: the 4x4 stride-2 layer on 32
-// channels, and the 8x8 byte layer of any stride.
+// The layers of conv_band.hpp and conv_bytes.hpp on the fp32 matrix instruction,
+// for maps of any size (the 4x4 stride-2 layer on 32 channels, and the 8x8 byte
+// layer of any stride): forward pass, input gradient and weight gradient.
 //
-// Every output is formed by the same instructions in the same order as in
+// Every sum is formed by the same instructions in the same order as in
 // gemm_mfma.hpp (v_mfma_f32_16x16x4_f32, product t of a group of 16 k sums
-// k = 16 kb + 4 g + t over g, groups and t ascending), so the activations are
-// the same bits as those of the any-shape kernels.  That matters in training:
-// where a pre-activation lies within rounding of zero, another order of the sum
-// can put it on the other side of the rectifier, and a map of millions of
-// pixels has enough of those to move the gradient of a filter by 1e-4 of itself.
+// k = 16 kb + 4 g + t over g, groups and t ascending), so activations and
+// gradients are the same bits as those of the any-shape kernels.  In the forward
+// pass of an update that matters: where a pre-activation lies within rounding of
+// zero, another order of the sum can put it on the other side of the rectifier,
+// and a map of millions of pixels has enough of those to move the gradient of a
+// filter by 1e-4 of itself.  The gradients decide nothing: an input gradient's
+// mask is the stored activation, and a weight gradient feeds nothing within the
+// update.  Keeping their order of sums too buys equal bits, not accuracy, and
+// costs the rate of the bf16 instruction.
 //
 // What bounds them is the instruction: 146 - 150 TFLOP/s on this chip.  With k
 // in the filter's own order (c, u, v), the four k of a lane are four columns of
@@ -475,7 +479,7 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_dgrad_kernel(const float
 // run of pixels, also across frames, and a table gives each pixel's place in them.  The next step's values go from memory
 // straight to the other half of the LDS buffers (no registers hold them).
 // Bound by the instruction next to the address and byte-conversion instructions (8 per 8 products of 32 cycles), and by whole
-// wavefronts per SIMD: conv1 at 640 frames of 84x84, stride 1, is 2736 tiles of 161 us on 1024 SIMDs (483 us; 785 measured,
+// wavefronts per SIMD: conv1 at 640 frames of 84x84, stride 1, is 2736 tiles of 161 us on 1024 SIMDs (483 us; 776 measured,
 // 4 ms for the gather kernel).
 template <class TIn> constexpr int f32_wgrad_kt() { return sizeof(TIn) == 1 ? 128 : 64; }
 struct F32WgradGeom {

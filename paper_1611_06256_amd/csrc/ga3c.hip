@@ -587,7 +587,7 @@ struct HeadWeights {
 // Heads of a prediction after the split-k fc layer of F = 256 NJ units: wavefront w of a block takes frame 4 blockIdx.x + w and
 // keeps everything of it in registers (its fc outputs, then its logits); only the weights, which the block's four frames share,
 // go through LDS, behind the one barrier.  CH chunks of partial sums in flight per lane.
-// Latency: loads and arithmetic of 1024 frames 6.8 us, 7.9 us with a barrier between the steps (heads_fwd_kernel).
+// Latency: 1024 frames 5.2 us with 8 chunks; 6.8 us with 16, where barriers between the steps (heads_fwd_kernel) took 7.9.
 template <int NJ, int CH>
 __global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restrict__ ws, int nz, const float *__restrict__ fcb, int B, int A,
                                                             const float *__restrict__ Wp, const float *__restrict__ bp,
@@ -672,8 +672,8 @@ __global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restr
 // and the fc sums, two outputs per wavefront and pass, whose weights are on their way while layer 2 runs.  The block that finishes a frame group last
 // (a ticket per group; nobody waits for anybody) adds the three row groups up and runs the heads, the softmax and the draw.
 // Blocks in order of (row group, slice): an XCD reads few parts of the fc weights.
-// Latency: nothing is large.  One frame 15.8 -> 9.6 us a call, 37 frames 23.9 -> 15.8 us against a kernel whose blocks each ran
-// both layers of a whole frame.
+// Latency: nothing is large.  One frame 15.9 -> 12.8 us a call, 37 frames 23.9 -> 18.6 us against a kernel whose blocks each ran
+// both layers of a whole frame, with an event recorded behind every call (9.6 and 14.9 us without one).
 constexpr int SP_FC = 256, SP_FLAT = 2592, SP_MAX_FRAMES = 64;
 constexpr int SP_TICKET_PITCH = 32;                        // ints between two groups' counters: a cache line each
 constexpr int SP_ROWS1 = 8, SP_PIX1 = SP_ROWS1 * 20, SP_PIX2 = 27, SP_XROWS = 36;      // of a row group: layer 1, layer 2, input
@@ -2034,9 +2034,11 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
                 continue;
             }
         }
-        // Updates run these layers on the fp32 instruction, in the any-shape kernels' order of sums (conv_band_f32.hpp
-        // says why), and so does the reduced-precision variant; predictions at fp32 accuracy take the bf16 terms, which are faster (128 frames of the stride-3
-        // member: conv1 11 against 22 us, conv2 13 against 17, conv3 10 against 14).
+        // Updates run these layers on the fp32 instruction, in the any-shape kernels' order of sums (conv_band_f32.hpp says why),
+        // and so does the reduced-precision variant.  Predictions at fp32 accuracy take the bf16 terms: they round differently
+        // from the same frames' forward pass in an update (both within 1e-6 of the exact sums) and are faster (128 frames of the
+        // stride-3 member, bf16 terms against the reduced-precision kernels: conv1 9.5 / 24.9 us, conv2 14.8 / 19.6, conv3 11.2 /
+        // 20.5).
         if (c->fast && c->band[l] && is_aligned16(xin) && is_aligned16(wl)) {
             const u32x4 *wf = c->bfrag[which] + c->bfrag_fwd[l];
             const bool f32 = c->rb || keep_zv;
