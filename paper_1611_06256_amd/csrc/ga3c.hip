@@ -2075,11 +2075,11 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         STAGE("fc_fwd", 2.0 * B * c->F * c->flat, 0);
         int nz, kchunk;
         if (c->fast && dense_operand_ok(x, c->flat, c->flat) && dense_operand_ok(wfc, c->flat, c->flat)) {
-            // A prediction's fc product takes about one block per compute unit: a second one would double the partial sums that the
-            // heads add up one after the other.  One block against two, us a call: small net 256 frames 21.0 / 22.8, 384: 27.1 /
-            // 30.2, 768: 33.5 / 36.5, 1024: 37.1 / 37.2; larger net 16: 42.2 / 44.2, 128: 45.8 / 48.1, 192: 48.7 / 53.3, 512: 73.8 /
-            // 73.8; stride-1 member 64: 114 / 117.  Updates keep one order of sums.
-            pick_split_xcd(cdiv(B, 64) * cdiv(c->F, 64), c->flat, nz, kchunk, keep_zv ? 512 : 256);
+            // Up to 16 tiles a prediction fills the chip with one block per compute unit: the second one would double the
+            // partial sums that the heads add up one after the other (larger net, 16 to 128 frames: 3 % of the call).  With
+            // more tiles two blocks hide each other's loads (256 frames: 54.5 us, 56.5 with one).  Updates keep one order of sums.
+            const int tiles = cdiv(B, 64) * cdiv(c->F, 64);
+            pick_split_xcd(tiles, c->flat, nz, kchunk, !keep_zv && tiles <= 16 ? 256 : 512);
             if ((size_t)nz * B * c->F > w.ws_floats) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc)");
             if (c->fcw[which].w && fc_forward_batch_ok(x, B, c->flat)) {
                 FcForwardArgs p;
