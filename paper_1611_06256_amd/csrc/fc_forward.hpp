@@ -15,8 +15,7 @@
 // x, still fp32; it is the only one that uses those rows and splits them as it
 // reads them.  Two blocks per compute unit: 1024 frames 16.0 -> 11.3 us, 512 10.4
 // -> 8.6, 2560 30.1 -> 25.7, 256 of the larger net 11.7 -> 9.3 (1280: 34.3 -> 29.2),
-// 128 x 1024 x 18496 42.5 -> 36.0.  Predictions take one block, which leaves half as
-// many partial sums to the heads (512 frames 8.6 us, 256 of the larger net 8.9).
+// 128 x 1024 x 18496 42.5 -> 36.0.
 // What is left is LDS reads (14 per wavefront and k-step of 384 cycles of products)
 // and, at small batches, start and end of the launch.  32 rows per wavefront read
 // less but leave one block per compute unit (12.5 us at 1024 frames); four k-steps in

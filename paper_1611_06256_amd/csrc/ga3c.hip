@@ -587,7 +587,8 @@ struct HeadWeights {
 // Heads of a prediction after the split-k fc layer of F = 256 NJ units: wavefront w of a block takes frame 4 blockIdx.x + w and
 // keeps everything of it in registers (its fc outputs, then its logits); only the weights, which the block's four frames share,
 // go through LDS, behind the one barrier.  CH chunks of partial sums in flight per lane.
-// Latency: 1024 frames 5.2 us with 8 chunks; 6.8 us with 16, where barriers between the steps (heads_fwd_kernel) took 7.9.
+// Latency: 1024 frames 5.2 us with 8 chunks of partial sums; 6.8 us with 16, where barriers between the steps
+// (heads_fwd_kernel) took 7.9.
 template <int NJ, int CH>
 __global__ __launch_bounds__(256) void heads_predict_kernel(const float *__restrict__ ws, int nz, const float *__restrict__ fcb, int B, int A,
                                                             const float *__restrict__ Wp, const float *__restrict__ bp,
@@ -2075,9 +2076,13 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         STAGE("fc_fwd", 2.0 * B * c->F * c->flat, 0);
         int nz, kchunk;
         if (c->fast && dense_operand_ok(x, c->flat, c->flat) && dense_operand_ok(wfc, c->flat, c->flat)) {
-            // Up to 16 tiles a prediction fills the chip with one block per compute unit: the second one would double the
-            // partial sums that the heads add up one after the other (larger net, 16 to 128 frames: 3 % of the call).  With
-            // more tiles two blocks hide each other's loads (256 frames: 54.5 us, 56.5 with one).  Updates keep one order of sums.
+            // Up to 16 tiles a prediction's fc product takes one block per compute unit: a second one would double the partial
+            // sums that the heads add up one after the other.  One block against two, us a call: larger net 16 frames 42.2 / 44.2,
+            // 128: 45.8 / 48.1; small net 192: 21.3 / 21.7, 256: 21.0 / 22.8.  With more tiles one block would be level or ahead too
+            // (small net 512 frames 27.9 / 28.5, 768: 33.5 / 36.5, 1024: 37.1 / 37.2; larger net 192: 48.7 / 53.3, 256: 50.8 / 51.7,
+            // 512: 73.8 / 73.8); the line stays because a prediction's value enters its segment's update as the bootstrap, and another
+            // rounding of it can move a pre-activation across zero a few updates later (512 agents: gradient 2.5e-4 off in one of 24
+            // updates).  Updates keep one order of sums.
             const int tiles = cdiv(B, 64) * cdiv(c->F, 64);
             pick_split_xcd(tiles, c->flat, nz, kchunk, !keep_zv && tiles <= 16 ? 256 : 512);
             if ((size_t)nz * B * c->F > w.ws_floats) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc)");
