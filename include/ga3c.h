@@ -27,6 +27,9 @@
  *     it copies change; when the updates move to another stream, order them
  *     behind the copies on the one they leave.  A stream may be destroyed once
  *     the work on it is over: no stream is used after the call it was given to.
+ *     A prediction that is captured into a graph keeps reading the copy that was
+ *     published then: capture it anew after a writer, and begin a capture when
+ *     the calls before it are over.
  *   - One HOST thread at a time drives a context: the calls keep host-side
  *     state without locks (which parameter copy is published, where each event
  *     was last recorded, the profiler's lists).  The paper's predictor and
