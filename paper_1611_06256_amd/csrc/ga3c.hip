@@ -24,6 +24,7 @@
 #include "conv1_bf16x3.hpp"
 #include "dense_gemm_bf16x6.hpp"
 #include "fc_forward.hpp"
+#include "fc_grads.hpp"
 #include "conv2_bf16x6.hpp"
 #include "conv12_fused.hpp"
 #include "conv_fwd_bf16x6.hpp"
@@ -167,11 +168,13 @@ struct ga3c_ctx {
     u32x4 *bfrag[2];
     ga3c::FcPlanes fcw[2];        // fc weights of each parameter copy as operands of the forward product (w == nullptr: none); kept
                                   // current by whoever writes the copy
+    bool fold_ok;                 // the fc weight gradient can be written without partial sums (fc_grads.hpp)
     int *ticket;                  // predict_small_kernel's per-frame counters, zero between launches
     Work pred, train;
     // training only
     float *dact[GA3C_MAX_CONV];   // dL/d(pre-activation) of each conv output
     float *dh;                    // dL/d(pre-activation) of the fc output
+    ga3c::FcDhPlanes dhp;         // dh as operands of the fc gradients (w == nullptr: none)
     float *dzv;                   // dL/d(logits, value) [cap][A+1]
     float *R;                     // returns [cap]
     float *partials;              // one squared-norm partial per reduce block, then 3 per loss block
@@ -1195,7 +1198,7 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     const float *__restrict__ bootstrap, const int32_t *__restrict__ seg_start, int N, int T, float gamma, float beta,
     float cv, float eps, float *__restrict__ h, float *__restrict__ zv, float *__restrict__ R, float *__restrict__ dzv,
     float *__restrict__ dh, float *__restrict__ colpart, float *__restrict__ wpart, float *__restrict__ losspart, int rb,
-    const FastDiv dFQ, const FastDiv dA1, const FastDiv dKP, const FastDiv dT) {
+    const FastDiv dFQ, const FastDiv dA1, const FastDiv dKP, const FastDiv dT, const ga3c::FcDhPlanes dhp) {
     extern __shared__ __attribute__((aligned(16))) float sm[];
     constexpr int NF = HD_FRAMES;
     const int F4 = heads_f4(F), WP = F4 + 4, A1 = A + 1, KP = (int)dKP.d;
@@ -1444,6 +1447,9 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
         for (int fb = 0; fb < NF; ++fb) *(float4 *)(red + (ag * NF + fb) * 256 + 4 * kl) = sd[fb];
         __syncthreads();
         const int k = kbase + tid;
+        float v[NF];
+#pragma unroll
+        for (int fb = 0; fb < NF; ++fb) v[fb] = 0.f;
         if (k < F) {
             float col = 0.f;
 #pragma unroll
@@ -1451,11 +1457,20 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
                 if (fb < nf) {
                     const float sum = (red[fb * 256 + tid] + red[(NF + fb) * 256 + tid]) +
                                       (red[(2 * NF + fb) * 256 + tid] + red[(3 * NF + fb) * 256 + tid]);
-                    const float v = hs[fb * F4 + k] > 0.f ? sum : 0.f;
-                    dh[(size_t)(b0 + fb) * F + k] = v;
-                    col += rb ? bf16_rne(v) : v;
+                    v[fb] = hs[fb * F4 + k] > 0.f ? sum : 0.f;
+                    dh[(size_t)(b0 + fb) * F + k] = v[fb];
+                    col += rb ? bf16_rne(v[fb]) : v[fb];
                 }
             colpart[(size_t)blockIdx.x * F + k] = col;
+        }
+        if (dhp.w && k < F) {                         // dh as operands of the fc gradients
+            static_assert(NF == 8, "a block's frames are one group of eight k");
+            const int kbw = (B + 31) / 32;
+            fc_dh_store8(dhp, k, blockIdx.x, kbw, v);
+            if (blockIdx.x + 1 == gridDim.x) {        // nothing behind the last frame
+                const float none[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                for (int b8 = blockIdx.x + 1; b8 < 4 * kbw; ++b8) fc_dh_store8(dhp, k, b8, kbw, none);
+            }
         }
         __syncthreads();                              // red is written again in the next pass
     }
@@ -1468,7 +1483,7 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
 
 // One launch adds up the partial weight gradients of every layer and, on the
 // way, the squares of the results (for the global norm).
-// A segment is a stack of nz partial matrices ws[z][M][N].  Rows [r0, r0+rows)
+// A segment is a stack of nz partial matrices ws[z][M][N] (nz = 1 and ws = gW: the gradient itself).  Rows [r0, r0+rows)
 // go to gW[(m-r0)*(N-1) + n] for n < N-1 and gb[m-r0] for n = N-1 (bias_col),
 // or all N columns to gW[(m-r0)*N + n] (no bias_col).  A block handles 256/zg
 // outputs with zg threads each: thread j adds z = j, j+zg, ... (eight loads in
@@ -1507,7 +1522,9 @@ __global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceArgs a) {
     const size_t i = (((size_t)(lb % 8) * g.per_xcd + lb / 8) * opb + o) * per;
     float4 s = float4{0.f, 0.f, 0.f, 0.f};
     const size_t src = (size_t)g.r0 * g.N + i, stride = (size_t)g.M * g.N;
-    if (g.vec && i + 3 < cnt) {
+    if (g.vec && g.nz == 1 && i + 3 < cnt) {
+        if (zi == 0) s = *(const float4 *)(g.ws + src);
+    } else if (g.vec && i + 3 < cnt) {
         for (int z = zi; z < g.nz; z += 8 * g.zg) {
             float4 v[8];
 #pragma unroll
@@ -1546,9 +1563,11 @@ __global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceArgs a) {
         for (int e = 0; e < ne; ++e) {
             const size_t ie = i + e;
             const int m = (int)(ie / g.N), n = (int)(ie % g.N);
-            if (!g.bias_col) g.gW[ie] = te[e];
-            else if (n < g.N - 1) g.gW[(size_t)m * (g.N - 1) + n] = te[e];
-            else g.gb[m] = te[e];
+            if (g.ws != g.gW) {                         // else the gradient is there already: only its squares are wanted
+                if (!g.bias_col) g.gW[ie] = te[e];
+                else if (n < g.N - 1) g.gW[(size_t)m * (g.N - 1) + n] = te[e];
+                else g.gb[m] = te[e];
+            }
             sq += te[e] * te[e];
         }
     }
@@ -2167,6 +2186,7 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
         int nz2;
         pick_split(cdiv(c->F, 64) * cdiv(c->flat + 1, 64), B, nz, kc);
         pick_split_xcd(cdiv(c->F, 64) * cdiv(c->flat, 64), B, nz2, kc, 256);
+        if (c->fold_ok && fc_grads_fold(c->F, c->flat, 1 << 30, c->dhp.terms)) nz2 = 0;
         add((size_t)std::max(nz, nz2) * c->F * (c->flat + 1));
         pick_split(conv_like_tiles(c->A + 1, c->F + 1), B, nz, kc);
         add((size_t)std::max(nz, cdiv(B, HD_FRAMES)) * (c->A + 1) * (c->F + 1));
@@ -2341,6 +2361,11 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         for (int l = 0; l < c->nconv && rc == GA3C_OK; ++l)
             guard(dmalloc((void **)&c->dact[l], sizeof(float) * B * c->geom[l].OC * c->geom[l].OHW));
         if (rc == GA3C_OK) guard(dmalloc((void **)&c->dh, sizeof(float) * B * c->F));
+        if (c->fcw[0].w) {
+            c->dhp.terms = c->fcw[0].terms;
+            c->fold_ok = is_aligned16(c->grad + c->off[2 * c->nconv]);
+            if (rc == GA3C_OK) guard(dmalloc((void **)&c->dhp.w, fc_dh_planes_bytes(max_train_frames, c->F, c->dhp.terms)));
+        }
         if (rc == GA3C_OK) guard(dmalloc((void **)&c->dzv, sizeof(float) * B * (c->A + 1)));
         if (rc == GA3C_OK) guard(dmalloc((void **)&c->R, sizeof(float) * B));
         c->max_norm_parts = (int)(c->P / 4 + 24 * MAX_REDUCE_SEGS);   // a reduce block covers at least 4 outputs
@@ -2383,7 +2408,7 @@ extern "C" int ga3c_destroy(ga3c_ctx *c) {
     (void)hipFree(c->cfrag[0]); (void)hipFree(c->cfrag[1]); (void)hipFree(c->ticket); (void)hipFree(c->lfrag[0]); (void)hipFree(c->lfrag[1]);
     (void)hipFree(c->bfrag[0]); (void)hipFree(c->bfrag[1]); (void)hipFree(c->fcw[0].w);      // both copies' in one piece
     free_work(c->pred); free_work(c->train);
-    (void)hipFree(c->dh); (void)hipFree(c->dzv); (void)hipFree(c->R);
+    (void)hipFree(c->dhp.w); (void)hipFree(c->dh); (void)hipFree(c->dzv); (void)hipFree(c->R);
     (void)hipFree(c->partials); (void)hipFree(c->colpart); (void)hipFree(c->scale); (void)hipFree(c->stats);
     if (c->prof) {
         for (ProfRec &r : c->prof->recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
@@ -2558,7 +2583,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         ga3c::launch(ht_kernels[ht], dim3(nblk), dim3(256), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
                            th + c->off[nb + 3], Wv, th + c->off[nb + 5], actions, rewards, dones, bootstrap, seg_start, N, T, hp->gamma, hp->beta,
                            hp->value_coef, hp->log_eps, w.h, w.zv, c->R, c->dzv, c->dh, c->colpart, part, losspart, c->rb,
-                           FastDiv(std::max(1, F / 4)), FastDiv(A + 1), FastDiv(heads_train_kparts(F, A)), FastDiv(T));
+                           FastDiv(std::max(1, F / 4)), FastDiv(A + 1), FastDiv(heads_train_kparts(F, A)), FastDiv(T), c->dhp);
         HIP_TRY(hipGetLastError());
         add_seg(part, nblk, A + 1, F + 1, 0, A, c->grad + c->off[nb + 2], c->grad + c->off[nb + 3], 1);
         add_seg(part, nblk, A + 1, F + 1, A, 1, c->grad + c->off[nb + 4], c->grad + c->off[nb + 5], 1);
@@ -2600,25 +2625,38 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                           dense_operand_ok(wfc, c->flat, c->flat);
     if (fc_dense) {   // fc weight gradient: D[o][i] = sum_b dh[b][o] x[b][i]; bias from the column sums of dh
         pick_split_xcd(cdiv(F, 64) * cdiv(c->flat, 64), B, nz, kchunk, 256);
-        DenseGemmArgs p{}; p.rb = c->rb;
-        p.M = F; p.N = c->flat; p.K = B; p.kchunk = kchunk; p.nz = nz;
-        p.A = c->dh; p.lda = F; p.B = xfc; p.ldb = c->flat;
-        p.C = region((size_t)nz * p.M * p.N); p.ldc = 0; p.aux = nullptr;
-        if (!p.C) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc wgrad)");
-        // fc input gradient, masked by the ReLU of the last conv layer
-        DenseGemmArgs q{}; q.rb = c->rb;
-        q.M = B; q.N = c->flat; q.K = F; q.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK; q.nz = 1;
-        q.A = c->dh; q.lda = F; q.B = wfc; q.ldb = c->flat;
-        q.C = c->dact[c->nconv - 1]; q.ldc = c->flat; q.aux = xfc;
+        const bool planes = c->dhp.w && c->fcw[cur].w;
+        // chunks added up by the block itself go straight into the gradient
+        const bool fold = planes && c->fold_ok && fc_grads_fold(F, c->flat, B, c->dhp.terms);
+        float *dw = fold ? c->grad + c->off[nb] : region((size_t)nz * F * c->flat);
+        if (!dw) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc wgrad)");
         STAGE2("fc_wgrad", 2.0 * B * F * c->flat, 0, "fc_dgrad", 2.0 * B * F * c->flat, 0);
-        // The input gradient's tile is 64x64 as long as there is one tile per compute unit at most, 128x64 above that: fewer tiles
-        // leave units idle, more read their operands twice.  64x64 against 128x64, us of the launch (tiles of 64x64): small net
-        // 160 frames 15.9 / 18.7 (123), 320: 15.0 / 17.9 (205), 480: 19.8 / 19.0 (328), 2560: 63.5 / 57.2; larger net 320: 28.3 /
-        // 30.0 (245), 480: 37.9 / 35.8 (392), 1280: 74.1 / 66.9; stride-4 member 960: 13.1 / 16.9 (135); stride-2 member 320: 20.3
-        // / 19.7 (320); stride-1 member 80: 294 / 286 (578).
-        if (cdiv(B, 64) * cdiv(c->flat, 64) <= 256) HIP_TRY((launch_dense_fc_grads<2, 2>(q, p, s)));
-        else HIP_TRY((launch_dense_fc_grads<4, 1>(q, p, s)));
-        add_seg(p.C, nz, p.M, p.N, 0, p.M, c->grad + c->off[nb], nullptr, 0);
+        if (planes) {
+            if (!fused_heads) HIP_TRY(launch_fc_dh_planes(c->dh, c->dhp, B, F, s));
+            FcGradArgs p{};
+            p.B = B; p.F = F; p.flat = c->flat; p.kchunk = kchunk; p.nz = nz;
+            p.dh = c->dhp; p.w = c->fcw[cur].w; p.x = xfc; p.dx = c->dact[c->nconv - 1]; p.dw = dw;
+            HIP_TRY(launch_fc_grads(p, fold, c->rb, s));
+        } else {
+            DenseGemmArgs p{}; p.rb = c->rb;
+            p.M = F; p.N = c->flat; p.K = B; p.kchunk = kchunk; p.nz = nz;
+            p.A = c->dh; p.lda = F; p.B = xfc; p.ldb = c->flat;
+            p.C = dw; p.ldc = 0; p.aux = nullptr;
+            // fc input gradient, masked by the ReLU of the last conv layer
+            DenseGemmArgs q{}; q.rb = c->rb;
+            q.M = B; q.N = c->flat; q.K = F; q.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK; q.nz = 1;
+            q.A = c->dh; q.lda = F; q.B = wfc; q.ldb = c->flat;
+            q.C = c->dact[c->nconv - 1]; q.ldc = c->flat; q.aux = xfc;
+            // What fc_grads.hpp does not take (layers that are not multiples of 32 and 64).  The input gradient's tile is 64x64 as
+            // long as there is one tile per compute unit at most, 128x64 above that: fewer tiles leave units idle, more read their
+            // operands twice.  64x64 against 128x64 on layers of both kernels, us of the launch (tiles of 64x64): small net
+            // 160 frames 15.9 / 18.7 (123), 320: 15.0 / 17.9 (205), 480: 19.8 / 19.0 (328), 2560: 63.5 / 57.2; larger net 320: 28.3 /
+            // 30.0 (245), 480: 37.9 / 35.8 (392), 1280: 74.1 / 66.9; stride-4 member 960: 13.1 / 16.9 (135); stride-2 member 320: 20.3
+            // / 19.7 (320); stride-1 member 80: 294 / 286 (578).
+            if (cdiv(B, 64) * cdiv(c->flat, 64) <= 256) HIP_TRY((launch_dense_fc_grads<2, 2>(q, p, s)));
+            else HIP_TRY((launch_dense_fc_grads<4, 1>(q, p, s)));
+        }
+        add_seg(dw, fold ? 1 : nz, F, c->flat, 0, F, c->grad + c->off[nb], nullptr, 0);
         add_seg(c->colpart, cdiv(B, HD_FRAMES), 1, F, 0, 1, c->grad + c->off[nb + 1], nullptr, 0);
     } else {   // general shapes: one more column of ones yields the bias gradient
         GemmP<EPI_PARTIAL, true> p; p.rb = c->rb;

@@ -39,6 +39,19 @@ def test_fc_gradients_where_the_tile_changes(G, N, math):
     P.run_train(G, desc, N, 5, 7200 + N, dict(clip_norm=40.0), frames=synth.rectangle_frames(7201, N * 5).reshape(N, 5, 4, 84, 84))
 
 
+# (the family's members at fp32 accuracy only: the medians for rounded operands are bounds of the two-layer nets)
+@pytest.mark.parametrize("stride,F,A,N,math", [(0, F, A, N, m) for m in (0, 1) for F, A, N in
+                                               [(256, 6, 1), (256, 6, 31), (256, 6, 32), (256, 6, 65), (256, 18, 1024), (256, 18, 1030), (64, 6, 530), (512, 40, 77)]] +
+                         [(3, 256, 6, 70, 0), (2, 320, 6, 34, 0)])
+def test_fc_gradients_at_the_edges_of_tiles_and_chunks(G, stride, F, A, N, math):
+    # k-steps of 32 frames, tiles of 64 frames, units and columns (2592, 1600 and 4096 columns); chunks in a block or a block each;
+    # heads that split their own gradients and heads that do not (40 actions).  Uniform bytes: frames made of a few drawn ones
+    # repeat one operand's rounding a thousandfold, and the median of the forward outputs, bounded for roundings that are
+    # independent, says nothing about them.
+    conv = ((32, 8, stride), (32, 4, 2), (64, 4, 2)) if stride else ((16, 8, 4), (32, 4, 2))
+    P.run_train(G, G.NetDesc(conv=conv, fc_units=F, n_actions=A, math=math), N, 1, 7250 + N, dict(clip_norm=40.0))
+
+
 def test_parameters_read_out_to_any_place(G):
     import torch
     net, _, theta = P.make(G, G.NetDesc(**P.ODD), 1, 0, 7300)
