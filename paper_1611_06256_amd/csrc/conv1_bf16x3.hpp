@@ -28,6 +28,17 @@ union Bf16x8Bits {
     u32x4 u;
 };
 
+// Pitch, in units of 16 bytes, of the LDS rows (pixels, filters, channels) from which a lane (l16, g) of the matrix instructions
+// reads unit g of row l16.  A 16-byte read takes its lanes in groups of 16: eight of one g and the other eight l16 of its
+// neighbour.  With an odd pitch a row's unit g + 1 falls on the banks of another row's unit g and the read takes twice as long (8
+// against 4.2 cycles); with twice an odd number the two halves of a group fall on the even and the odd units of the 256 bytes that
+// the banks hold.  (Twice an odd number also keeps 8- and 16-byte writes of consecutive rows at 16 cycles a kilobyte, provided
+// that a lane writes whole units; with 8 bytes each they take twice as long as from an odd pitch.)
+constexpr int lds_row_units(int least) {
+    while (least % 4 != 2) ++least;
+    return least;
+}
+
 // Sum step inside a row of 16 lanes (DPP control CTRL).
 template <int CTRL>
 __device__ __forceinline__ float dpp_row_f32(float v) {

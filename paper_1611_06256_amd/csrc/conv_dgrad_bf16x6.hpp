@@ -20,8 +20,10 @@
 // fp32 instruction.  The contraction index is ordered (tap, oc), and dY sits in
 // LDS as [padded pixel][oc] per term, so the 8 consecutive k a lane feeds to an
 // MFMA are 8 consecutive filters of one pixel: one 16-byte LDS read per term.
-// The pixel pitch is 2 OC + 16 bytes, which spreads 16 consecutive pixels over
-// all banks.  The sub-filters of a wavefront's phase stay in registers as split
+// The pixel pitch (lds_row_units) and a padded grid as wide as the phase grid spread
+// 16 pixels of a tile over all banks (both gradients of the layer at 1280 frames of the
+// larger net 104.0 -> 94.8 us, at 2560 of the small one 57.2 -> 54.2, with the rows of
+// the weight gradient's operands at such a pitch too).  The sub-filters of a wavefront's phase stay in registers as split
 // fragments for the whole launch.  A block can take them ready-made (`wfrag`:
 // the register image of every wavefront, which the kernel that updates the
 // parameters keeps current): gathering them from the filter tensor costs 32
@@ -58,10 +60,12 @@ struct ConvDgradBf16Geom {
     static constexpr int CS = 16, S = 2;
     static constexpr int GH = SP::H / S, GW = SP::W / S, GP = GH * GW;
     static constexpr int NT = (GP + 15) / 16;
-    static constexpr int PH = SP::OH + 2, PW = SP::OW + 2;
+    // Padded dY: a column of zeros in front of every row, which is the column behind the row above it; a row of zeros in front
+    // and behind.  So the pixels of the phase grid are consecutive pixels of the padded one.
+    static constexpr int PH = SP::OH + 2, PW = SP::OW + 1, PPIX = PH * PW + 1;
     static constexpr int OCB = SP::OC / 32, KB = 4 * OCB;          // k-blocks of 32: (tap, 32 filters)
-    static constexpr int PIT = 2 * SP::OC + 16;                    // bytes per padded pixel and term
-    static constexpr int PLANE = PH * PW * PIT;
+    static constexpr int PIT = 16 * lds_row_units(SP::OC / 8);     // bytes per padded pixel and term
+    static constexpr int PLANE = PPIX * PIT;
     static constexpr int NX = CS * SP::H * SP::W;
     __host__ __device__ static constexpr int lds_bytes(bool one) { return (one ? 1 : 3) * PLANE + NX * 4; }
     // ready-made filter fragments: [channel slice][wavefront = phase][k-block][term][lane] vectors of 8 bf16
@@ -116,7 +120,7 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
     constexpr int CS = G::CS, S = G::S, GW = G::GW, GP = G::GP, NT = G::NT, PW = G::PW;
     constexpr int OCB = G::OCB, KB = G::KB, PIT = G::PIT, PLANE = G::PLANE, NX = G::NX;
     constexpr int NTERM = ONE ? 1 : 3;
-    constexpr int NITEM = (SP::OC / 4) * SP::NPIX, DPT = (NITEM + 255) / 256;      // items: 4 filters of one pixel
+    constexpr int NITEM = (SP::OC / 8) * SP::NPIX, DPT = (NITEM + 255) / 256;      // items: 8 filters of one pixel
     constexpr int XV = NX / 4, XPT = (XV + 255) / 256;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     unsigned char *dp = smem;                                   // [term][padded pixel][oc] bf16
@@ -147,20 +151,20 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
     for (int i = 0; i < DPT; ++i) {
         const int e = min(tid + 256 * i, NITEM - 1);
         const int ocq = e / SP::NPIX, pix = e % SP::NPIX;
-        dsrc_off[i] = 4 * ocq * SP::NPIX + pix;
-        dlds[i] = ((pix / SP::OW + 1) * PW + pix % SP::OW + 1) * PIT + 8 * ocq;
+        dsrc_off[i] = 8 * ocq * SP::NPIX + pix;
+        dlds[i] = ((pix / SP::OW + 1) * PW + pix % SP::OW + 1) * PIT + 16 * ocq;
     }
     int xidx[XPT];
 #pragma unroll
     for (int i = 0; i < XPT; ++i) xidx[i] = min(tid + 256 * i, XV - 1);
 
-    float dpre[DPT][4];
+    float dpre[DPT][8];
     auto fetch_dy = [&](int f) {
         const float *dsrc = dy + (size_t)f * (SP::OC * SP::NPIX);
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) dpre[i][j] = dsrc[dsrc_off[i] + j * SP::NPIX];
+            for (int j = 0; j < 8; ++j) dpre[i][j] = dsrc[dsrc_off[i] + j * SP::NPIX];
     };
     int f = bx;
     fetch_dy(min(f, nframes - 1));       // on its way while the filters arrive
@@ -196,11 +200,15 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
             if (tid + 256 * i < NITEM) {
-                uint2 o3[3];
-                split3_pair(dpre[i][0], dpre[i][1], o3[0].x, o3[1].x, o3[2].x);
-                split3_pair(dpre[i][2], dpre[i][3], o3[0].y, o3[1].y, o3[2].y);
+                u32x4 o3[3];
 #pragma unroll
-                for (int x = 0; x < NTERM; ++x) *(uint2 *)(dp + x * PLANE + dlds[i]) = o3[x];
+                for (int j = 0; j < 4; ++j) {
+                    uint32_t t[3];
+                    split3_pair(dpre[i][2 * j], dpre[i][2 * j + 1], t[0], t[1], t[2]);
+                    o3[0][j] = t[0]; o3[1][j] = t[1]; o3[2][j] = t[2];
+                }
+#pragma unroll
+                for (int x = 0; x < NTERM; ++x) *(u32x4 *)(dp + x * PLANE + dlds[i]) = o3[x];
             }
         __syncthreads();
         fetch_dy(min(f + nbx, nframes - 1));

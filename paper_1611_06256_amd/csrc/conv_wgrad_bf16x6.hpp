@@ -48,9 +48,9 @@ struct ConvWgradBf16Geom {
     static constexpr int GH = SP::H / 2, GW = SP::W / 2;
     static constexpr int KTOT = SP::OH * GW;                       // k = i * GW + j
     static constexpr int NKB = (KTOT + 31) / 32;                   // groups of 32 k
-    static constexpr int DROW = NKB * 32 + 8;                      // bf16 per filter row of dY (52 dwords: 16 rows hit all banks)
+    static constexpr int DROW = 8 * lds_row_units(NKB * 4);        // bf16 per filter row of dY
     static constexpr int WIN = 24;                                 // elements of a plane row a lane reads per group and term
-    static constexpr int PROW = NKB * 32 + WIN;                    // bf16 per channel row of a phase plane (60 dwords)
+    static constexpr int PROW = 8 * lds_row_units((NKB * 32 - 8 + WIN) / 8);      // bf16 per channel row of a phase plane
     static constexpr int MT = OCB / 16;
     static constexpr int DTERM = OCB * DROW, PTERM = 4 * CS * PROW;         // elements per term
     static constexpr int OTP = CS * 16 + 4;                        // floats per filter row of the block's result in LDS
