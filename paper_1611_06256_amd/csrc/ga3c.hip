@@ -334,17 +334,26 @@ __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int
         for (int z = 0; z < nz; z += CH) {
             float4 v[IP][CH];
 #pragma unroll
-            for (int p = 0; p < IP; ++p)
+            for (int i = 0; i < CH; i += 4)
+                if (z + i < nz) {
 #pragma unroll
-                for (int i = 0; i < CH; ++i) v[p][i] = (src + (size_t)min(z + i, nz - 1) * stride4)[off[p]];
+                    for (int p = 0; p < IP; ++p)
+#pragma unroll
+                        for (int j = i; j < i + 4; ++j) v[p][j] = (src + (size_t)min(z + j, nz - 1) * stride4)[off[p]];
+                }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int p = 0; p < IP; ++p)
+            for (int i = 0; i < CH; i += 4)
+                if (z + i < nz) {
 #pragma unroll
-                for (int i = 0; i < CH; ++i) {
-                    const bool in = z + i < nz;
-                    acc[p].x += in ? v[p][i].x : 0.f; acc[p].y += in ? v[p][i].y : 0.f;
-                    acc[p].z += in ? v[p][i].z : 0.f; acc[p].w += in ? v[p][i].w : 0.f;
+                    for (int j = i; j < i + 4; ++j) {
+                        const bool in = z + j < nz;
+#pragma unroll
+                        for (int p = 0; p < IP; ++p) {
+                            acc[p].x += in ? v[p][j].x : 0.f; acc[p].y += in ? v[p][j].y : 0.f;
+                            acc[p].z += in ? v[p][j].z : 0.f; acc[p].w += in ? v[p][j].w : 0.f;
+                        }
+                    }
                 }
         }
 #pragma unroll
@@ -1175,9 +1184,17 @@ __global__ __launch_bounds__(256) void heads_dgrad_kernel(const float *__restric
 // do not depend on the thread layout; (4) heads backward: dh = [h > 0] dz W,
 // and the block's shares of the heads' weight and bias gradients (wpart
 // [block][A+1][F+1]) and of the fc bias gradient (colpart [block][F]): a
-// thread takes four consecutive k and every fourth output (its wavefront's),
-// so that weights, activations and gradients move as 16-byte vectors; the four
-// partial sums of dh meet in LDS.
+// thread takes VK consecutive k and every fourth output, so that weights,
+// activations and gradients move as vectors; the four partial sums of dh meet in
+// LDS.
+// What it takes is one block's chain of steps (us since its start, 40 frames of 256
+// units, 27 chunks of partial sums: operands in LDS 6.2, dots 7.3, returns and loss
+// 10.5, end 13.5), and in the long ones of them the block's instructions and its
+// requests to memory, each of which occupies a wavefront for a hundred cycles.  So a
+// block has eight wavefronts where the launch leaves compute units idle: 14.9 -> 12.9 us
+// (40 frames), 512 units 26.6 -> 19.5 (40 frames), 21.3 -> 17.8 (1280).  With more than
+// 1024 frames of 256 units four of them with vectors of four are as good (update of
+// 1280 frames 157.6 us against 158.9, 2560: 258.0 / 260.2).
 // Writes h, zv, R, dzv (kept for inspection), dh, colpart, wpart and three loss
 // sums per block.  rb: operands of every product rounded to bfloat16.
 // Dynamic LDS: heads_train_lds_floats(F, A) floats.
@@ -1185,13 +1202,18 @@ __host__ __device__ inline int heads_train_kparts(int F, int A) {
     const int kp = 256 / (A + 1), nk = heads_f4(F) / 4;
     return kp < nk ? kp : nk;
 }
+// Threads of a block, and k per thread in the backward part (a pass over 256 or 512 units); see there for the line.
+struct HeadsTrainShape { int threads, vk; };
+inline HeadsTrainShape heads_train_shape(int F, int B) {
+    return HeadsTrainShape{F > 256 || B <= 1024 ? 512 : 256, F > 256 ? 4 : B <= 1024 ? 2 : 4};
+}
 __host__ __device__ inline int heads_train_lds_floats(int F, int A) {
-    return HD_FRAMES * heads_f4(F) + (A + 1) * (heads_f4(F) + 4) + 4 * HD_FRAMES * 256 + (A + 1) * HD_FRAMES +
+    return HD_FRAMES * heads_f4(F) + (A + 1) * (heads_f4(F) + 4) + HD_FRAMES * (F > 256 ? 2048 : 1024) + (A + 1) * HD_FRAMES +
            3 * HD_FRAMES * heads_f4(A + 1) + HD_FRAMES * (A + 1) * heads_train_kparts(F, A) + 512;
 }
 
-template <int LOADS>
-__global__ __launch_bounds__(256) void heads_train_kernel(
+template <int LOADS, int NT, int VK>
+__global__ __launch_bounds__(NT) void heads_train_kernel(
     const float *__restrict__ ws, int nz, const float *__restrict__ fcb, int B, int F, int A,
     const float *__restrict__ Wp, const float *__restrict__ bp, const float *__restrict__ Wv, const float *__restrict__ bv,
     const int32_t *__restrict__ actions, const float *__restrict__ rewards, const uint8_t *__restrict__ dones,
@@ -1200,13 +1222,13 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     float *__restrict__ dh, float *__restrict__ colpart, float *__restrict__ wpart, float *__restrict__ losspart, int rb,
     const FastDiv dFQ, const FastDiv dA1, const FastDiv dKP, const FastDiv dT, const ga3c::FcDhPlanes dhp) {
     extern __shared__ __attribute__((aligned(16))) float sm[];
-    constexpr int NF = HD_FRAMES;
+    constexpr int NF = HD_FRAMES, KPASS = NT / 4 * VK;      // k of a pass of the backward part
     const int F4 = heads_f4(F), WP = F4 + 4, A1 = A + 1, KP = (int)dKP.d;
     const int ZR = heads_f4(A1);             // row pitch of the per-(frame, output) arrays: rows start on 16 bytes
     float *hs = sm;                          // [NF][F4]   fc output of my frames (rounded if rb)
     float *wsh = hs + NF * F4;               // [A1][WP]   head weights (rounded if rb)
-    float *red = wsh + A1 * WP;              // [4][NF][256] partial sums of dh, one set per wavefront
-    float *zt = red + 4 * NF * 256;          // [A1][NF]   gradients of the head outputs, transposed
+    float *red = wsh + A1 * WP;              // [4][NF][KPASS] partial sums of dh, one set per quarter of the outputs
+    float *zt = red + 4 * NF * KPASS;          // [A1][NF]   gradients of the head outputs, transposed
     float *zs = zt + A1 * NF;                // [NF][ZR]   head outputs, later their gradients
     float *ex = zs + NF * ZR;                // [NF][ZR]   exp / per-action terms
     float *tm = ex + NF * ZR;                // [NF][ZR]   per-action terms
@@ -1232,20 +1254,20 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
     const float obias = oa < A ? bp[oa] : bv[0];
     const int oact = actions[ob];
     const float oboot = bootstrap && !seg_start ? bootstrap[dT.div((uint32_t)ob)] : 0.f;
-    for (int e = tid; e < NF * (F4 - F); e += 256) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
-    heads_zero_padding<256>(wsh, tid, F, WP, A1);
+    for (int e = tid; e < NF * (F4 - F); e += NT) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
+    heads_zero_padding<NT>(wsh, tid, F, WP, A1);
     const int nw = A1 * F;
     constexpr bool vec4 = LOADS != LOADS_SCALAR;
-    if (vec4) heads_load_vec4<256, NF, LOADS == LOADS_VEC8 ? 8 : 16, LOADS == LOADS_VEC8 ? 4 : 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
-    for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * 256) {
+    if (vec4) heads_load_vec4<NT, NF, LOADS == LOADS_VEC8 ? 8 : VK == 2 ? 28 : 20, VK == 2 ? 1 : 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+    for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * NT) {
         float wv[24];
 #pragma unroll
         for (int j = 0; j < 24; ++j) {
-            const int e = min(e0 + j * 256 + tid, nw - 1);
+            const int e = min(e0 + j * NT + tid, nw - 1);
             wv[j] = e < A * F ? Wp[e] : Wv[e - A * F];
         }
         if (e0 == 0) {
-            for (int o = tid; o < F; o += 256) {
+            for (int o = tid; o < F; o += NT) {
                 const float bias = fcb[o];
                 const size_t stride = (size_t)B * F;
                 const float *src = ws + (size_t)b0 * F + o;
@@ -1275,33 +1297,36 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
         }
 #pragma unroll
         for (int j = 0; j < 24; ++j) {
-            const int e = e0 + j * 256 + tid;
+            const int e = e0 + j * NT + tid;
             if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
         }
     }
     if (rw_lds && tid < nrw) { rw[tid] = my_rw; dn[tid] = my_done ? 0.f : 1.f; }
     __syncthreads();
 
-    // ---- heads: thread (action a, part kp of k) for all frames, then the parts are added in order
+    // ---- heads: thread (action a, part kp of k) for the frames of its 256 threads, then the parts are added in order
     {
-        const int a = oa, kp = (int)tq;
+        constexpr int NH = NF * 256 / NT;
+        uint32_t kp_, a_;
+        dA1.divmod((uint32_t)(tid & 255), kp_, a_);
+        const int a = (int)a_, kp = (int)kp_, f0 = NH * (tid >> 8);
         if (kp < KP) {
             const int nk = F4 / 4;
             const int klo = (int)dKP.div((uint32_t)(nk * kp)), khi = (int)dKP.div((uint32_t)(nk * (kp + 1)));
             const float4 *wr = (const float4 *)(wsh + a * WP);
-            float s[NF];
+            float s[NH];
 #pragma unroll
-            for (int fb = 0; fb < NF; ++fb) s[fb] = 0.f;
+            for (int fb = 0; fb < NH; ++fb) s[fb] = 0.f;
             for (int k = klo; k < khi; ++k) {
                 const float4 w = wr[k];
 #pragma unroll
-                for (int fb = 0; fb < NF; ++fb) {
-                    const float4 x = ((const float4 *)(hs + fb * F4))[k];
+                for (int fb = 0; fb < NH; ++fb) {
+                    const float4 x = ((const float4 *)(hs + (f0 + fb) * F4))[k];
                     s[fb] += (x.x * w.x + x.y * w.y) + (x.z * w.z + x.w * w.w);
                 }
             }
 #pragma unroll
-            for (int fb = 0; fb < NF; ++fb) zp[(fb * A1 + a) * KP + kp] = s[fb];
+            for (int fb = 0; fb < NH; ++fb) zp[((f0 + fb) * A1 + a) * KP + kp] = s[fb];
         }
     }
     __syncthreads();
@@ -1410,66 +1435,69 @@ __global__ __launch_bounds__(256) void heads_train_kernel(
         for (int fb = 0; fb < nf; ++fb) sum += src[fb];
         losspart[3 * blockIdx.x + tid] = sum;
     }
-    // ---- heads backward (zt holds dz of my frames).  Wavefront ag takes the outputs ag, ag + 4, ..; lane kl the four
-    // k starting at kbase + 4 kl, 256 k per pass.
-    typedef float f32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
-    const int ag = tid >> 6, kl = tid & 63;
-    for (int kbase = 0; kbase < F; kbase += 256) {
-        const int k4 = kbase + 4 * kl;
-        const bool kin = k4 < F4;
-        float4 hv[NF], sd[NF];
+    // ---- heads backward (zt holds dz of my frames).  A quarter of the block takes the outputs ag, ag + 4, ..; thread kl of it the
+    // VK k starting at kbase + VK kl.
+    typedef float fk __attribute__((ext_vector_type(VK)));
+    typedef float fk_dword_aligned __attribute__((ext_vector_type(VK), aligned(4)));
+    const int ag = tid / (NT / 4), kl = tid % (NT / 4);
+    for (int kbase = 0; kbase < F; kbase += KPASS) {
+        const int kv = kbase + VK * kl;
+        const bool kin = kv < F4;
+        fk hv[NF], sd[NF];
 #pragma unroll
         for (int fb = 0; fb < NF; ++fb) {
-            hv[fb] = kin ? *(const float4 *)(hs + fb * F4 + k4) : float4{0.f, 0.f, 0.f, 0.f};
-            sd[fb] = float4{0.f, 0.f, 0.f, 0.f};
+            hv[fb] = kin ? *(const fk *)(hs + fb * F4 + kv) : (fk)(0.f);
+            sd[fb] = (fk)(0.f);
         }
-        float *wp = wpart + (size_t)blockIdx.x * A1 * (F + 1) + k4;
+        float *wp = wpart + (size_t)blockIdx.x * A1 * (F + 1) + kv;
         for (int a = ag; a < A1; a += 4) {
-            const float4 wv = kin ? *(const float4 *)(wsh + a * WP + k4) : float4{0.f, 0.f, 0.f, 0.f};
+            const fk wv = kin ? *(const fk *)(wsh + a * WP + kv) : (fk)(0.f);
             const float4 d0 = *(const float4 *)(zt + a * NF), d1 = *(const float4 *)(zt + a * NF + 4);
             const float d[NF] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-            float4 gw = float4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int fb = 0; fb < NF; ++fb) {
-                sd[fb].x += d[fb] * wv.x; sd[fb].y += d[fb] * wv.y; sd[fb].z += d[fb] * wv.z; sd[fb].w += d[fb] * wv.w;
-                gw.x += d[fb] * hv[fb].x; gw.y += d[fb] * hv[fb].y; gw.z += d[fb] * hv[fb].z; gw.w += d[fb] * hv[fb].w;
-            }
-            float *dst = wp + (size_t)a * (F + 1);
-            if (k4 + 3 < F) {
-                *(f32x4_dword_aligned *)dst = f32x4_dword_aligned{gw.x, gw.y, gw.z, gw.w};
-            } else {
-                if (k4 < F) dst[0] = gw.x;
-                if (k4 + 1 < F) dst[1] = gw.y;
-                if (k4 + 2 < F) dst[2] = gw.z;
-            }
-        }
-#pragma unroll
-        for (int fb = 0; fb < NF; ++fb) *(float4 *)(red + (ag * NF + fb) * 256 + 4 * kl) = sd[fb];
-        __syncthreads();
-        const int k = kbase + tid;
-        float v[NF];
-#pragma unroll
-        for (int fb = 0; fb < NF; ++fb) v[fb] = 0.f;
-        if (k < F) {
-            float col = 0.f;
+            fk gw = (fk)(0.f);
 #pragma unroll
             for (int fb = 0; fb < NF; ++fb)
+#pragma unroll
+                for (int e = 0; e < VK; ++e) { sd[fb][e] += d[fb] * wv[e]; gw[e] += d[fb] * hv[fb][e]; }
+            float *dst = wp + (size_t)a * (F + 1);
+            if (kv + VK - 1 < F) {
+                *(fk_dword_aligned *)dst = gw;
+            } else {
+#pragma unroll
+                for (int e = 0; e < VK - 1; ++e)
+                    if (kv + e < F) dst[e] = gw[e];
+            }
+        }
+#pragma unroll
+        for (int fb = 0; fb < NF; ++fb) *(fk *)(red + (ag * NF + fb) * KPASS + VK * kl) = sd[fb];
+        __syncthreads();
+        const int kk = tid % KPASS, k = kbase + kk;
+        // where a pass has half as many k as the block threads, one half writes dh and the other what is made of it
+        const bool writes_dh = KPASS >= NT || tid < KPASS, writes_sums = KPASS >= NT || tid >= KPASS;
+        if (k < F) {
+            float v[NF], col = 0.f;
+#pragma unroll
+            for (int fb = 0; fb < NF; ++fb) {
+                v[fb] = 0.f;
                 if (fb < nf) {
-                    const float sum = (red[fb * 256 + tid] + red[(NF + fb) * 256 + tid]) +
-                                      (red[(2 * NF + fb) * 256 + tid] + red[(3 * NF + fb) * 256 + tid]);
+                    const float sum = (red[fb * KPASS + kk] + red[(NF + fb) * KPASS + kk]) +
+                                      (red[(2 * NF + fb) * KPASS + kk] + red[(3 * NF + fb) * KPASS + kk]);
                     v[fb] = hs[fb * F4 + k] > 0.f ? sum : 0.f;
-                    dh[(size_t)(b0 + fb) * F + k] = v[fb];
+                    if (writes_dh) dh[(size_t)(b0 + fb) * F + k] = v[fb];
                     col += rb ? bf16_rne(v[fb]) : v[fb];
                 }
-            colpart[(size_t)blockIdx.x * F + k] = col;
-        }
-        if (dhp.w && k < F) {                         // dh as operands of the fc gradients
-            static_assert(NF == 8, "a block's frames are one group of eight k");
-            const int kbw = (B + 31) / 32;
-            fc_dh_store8(dhp, k, blockIdx.x, kbw, v);
-            if (blockIdx.x + 1 == gridDim.x) {        // nothing behind the last frame
-                const float none[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                for (int b8 = blockIdx.x + 1; b8 < 4 * kbw; ++b8) fc_dh_store8(dhp, k, b8, kbw, none);
+            }
+            if (writes_sums) {
+                colpart[(size_t)blockIdx.x * F + k] = col;
+                if (dhp.w) {                              // dh as operands of the fc gradients
+                    static_assert(NF == 8, "a block's frames are one group of eight k");
+                    const int kbw = (B + 31) / 32;
+                    fc_dh_store8(dhp, k, blockIdx.x, kbw, v);
+                    if (blockIdx.x + 1 == gridDim.x) {    // nothing behind the last frame
+                        const float none[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                        for (int b8 = blockIdx.x + 1; b8 < 4 * kbw; ++b8) fc_dh_store8(dhp, k, b8, kbw, none);
+                    }
+                }
             }
         }
         __syncthreads();                              // red is written again in the next pass
@@ -1920,7 +1948,7 @@ inline int conv_like_tiles(int M, int N) {
 }
 
 // LDS the fused training heads kernel may ask for; larger heads fall back to the separate kernels.
-constexpr size_t HEADS_TRAIN_MAX_LDS = 128 * 1024;
+constexpr size_t HEADS_TRAIN_MAX_LDS = 160 * 1024;
 constexpr size_t HEADS_FWD_MAX_LDS = 160 * 1024;      // all of a compute unit's LDS
 
 // A kernel may take more than 64 KB of dynamic LDS only after its limit has
@@ -2574,13 +2602,17 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         const int nblk = cdiv(B, HD_FRAMES);
         float *part = region((size_t)nblk * (A + 1) * (F + 1));
         if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (heads)");
-        typedef decltype(&heads_train_kernel<LOADS_SCALAR>) HeadsTrain;
-        static const HeadsTrain ht_kernels[3] = {heads_train_kernel<LOADS_SCALAR>, heads_train_kernel<LOADS_VEC8>, heads_train_kernel<LOADS_VEC16>};
-        static size_t ht_lds_set[3] = {0, 0, 0};
-        const int ht = heads_loads(F, w.fc_nz, w.fc_ws, th + c->off[nb + 1], w.h, Wp);
+        typedef decltype(&heads_train_kernel<LOADS_SCALAR, 256, 4>) HeadsTrain;
+        static const HeadsTrain ht_kernels[9] = {
+            heads_train_kernel<LOADS_SCALAR, 256, 4>, heads_train_kernel<LOADS_VEC8, 256, 4>, heads_train_kernel<LOADS_VEC16, 256, 4>,
+            heads_train_kernel<LOADS_SCALAR, 512, 2>, heads_train_kernel<LOADS_VEC8, 512, 2>, heads_train_kernel<LOADS_VEC16, 512, 2>,
+            heads_train_kernel<LOADS_SCALAR, 512, 4>, heads_train_kernel<LOADS_VEC8, 512, 4>, heads_train_kernel<LOADS_VEC16, 512, 4>};
+        static size_t ht_lds_set[9] = {};
+        const HeadsTrainShape shape = heads_train_shape(F, B);
+        const int ht = heads_loads(F, w.fc_nz, w.fc_ws, th + c->off[nb + 1], w.h, Wp) + (shape.threads == 256 ? 0 : shape.vk == 2 ? 3 : 6);
         HIP_TRY(allow_dynamic_lds((const void *)ht_kernels[ht], ht_lds, ht_lds_set[ht]));
         STAGE("heads_train", 6.0 * B * (A + 1) * F, 4.0 * (w.fc_nz + 1) * B * F);
-        ga3c::launch(ht_kernels[ht], dim3(nblk), dim3(256), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
+        ga3c::launch(ht_kernels[ht], dim3(nblk), dim3(shape.threads), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
                            th + c->off[nb + 3], Wv, th + c->off[nb + 5], actions, rewards, dones, bootstrap, seg_start, N, T, hp->gamma, hp->beta,
                            hp->value_coef, hp->log_eps, w.h, w.zv, c->R, c->dzv, c->dh, c->colpart, part, losspart, c->rb,
                            FastDiv(std::max(1, F / 4)), FastDiv(A + 1), FastDiv(heads_train_kparts(F, A)), FastDiv(T), c->dhp);
