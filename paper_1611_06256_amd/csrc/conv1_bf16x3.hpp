@@ -128,12 +128,15 @@ __device__ __forceinline__ void bytes_to_bf16(const u32x4 b, u32x4 &lo8, u32x4 &
 // frame sits in LDS as bf16 [4][84][84]; a lane (pixel p, group g) reads the 8
 // taps of filter row u = 4*(kb%2) + g of channel kb/2 in one go, which is the
 // k = 8g..8g+7 share of a 16x16x32 MFMA.  The split filters stay in registers.
-template <int OC, bool TABLE>
+// ONE: operands rounded to bfloat16 (the reduced-precision variant): one term, one product (1280 frames of 32 filters 27.9 -> 24.2 us
+// against two more terms that were zero).
+template <int OC, bool TABLE, bool ONE>
 __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t *__restrict__ x,
                                                                   const uint8_t *const *__restrict__ table,
                                                                   const float *__restrict__ w,
                                                                   const float *__restrict__ bias, float *__restrict__ y,
-                                                                  int nframes, float scale, int rb) {
+                                                                  int nframes, float scale) {
+    constexpr int NTERM = ONE ? 1 : 3;
     constexpr int C = 4, H = 84, W = 84, S = 4, OW = 20, NPIX = 400, K = 256, CHW = C * H * W;
     constexpr int NV = CHW / 16, VPT = (NV + 255) / 256;           // 16-byte vectors of the byte frame
     constexpr int OT = OC / 16, JOBS = 25 * OT, TPW = (JOBS + 3) / 4;
@@ -149,7 +152,7 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
     const int ot = wave % OT;
 
     // my filter (row l16 of tile ot), split into three bf16 terms, 8 taps per 32-tap block
-    bf16x8 wq[3][8];
+    bf16x8 wq[NTERM][8];
 #pragma unroll
     for (int kb = 0; kb < 8; ++kb) {
         const float *src = w + (size_t)(ot * 16 + l16) * K + (kb / 2) * 64 + (4 * (kb % 2) + g) * 8;
@@ -157,9 +160,10 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
         const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            __bf16 h, m, l;
-            split3(f[e], h, m, l, rb);
-            wq[0][kb][e] = h; wq[1][kb][e] = m; wq[2][kb][e] = l;
+            __bf16 t[3];
+            split3(f[e], t[0], t[1], t[2]);
+#pragma unroll
+            for (int q = 0; q < NTERM; ++q) wq[q][kb][e] = t[q];
         }
     }
     // The MFMAs take the pixels as rows and the filters as columns: a lane ends up with four consecutive pixels
@@ -215,9 +219,8 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
             const uint2 lo = *(const uint2 *)src, hi = *(const uint2 *)(src + 4);
             Bf16x8Bits xv;
             xv.u = u32x4{lo.x, lo.y, hi.x, hi.y};
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv.v, wq[2][kb], acc[i], 0, 0, 0);
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv.v, wq[1][kb], acc[i], 0, 0, 0);
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv.v, wq[0][kb], acc[i], 0, 0, 0);
+#pragma unroll
+            for (int q = NTERM - 1; q >= 0; --q) acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv.v, wq[q][kb], acc[i], 0, 0, 0);
         };
 #pragma unroll
         for (int kb = 0; kb < 8; ++kb)
@@ -248,8 +251,9 @@ inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const uint8_t *const
                                           float scale, hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
     const int grid = nframes < 512 ? nframes : 512;
-    if (table) ga3c::launch((conv1_bf16x3_fwd_kernel<OC, true>), dim3(grid), dim3(256), 0, s, x, table, w, bias, y, nframes, scale, rb);
-    else ga3c::launch((conv1_bf16x3_fwd_kernel<OC, false>), dim3(grid), dim3(256), 0, s, x, table, w, bias, y, nframes, scale, rb);
+    auto go = [&](auto kernel) { ga3c::launch(kernel, dim3(grid), dim3(256), 0, s, x, table, w, bias, y, nframes, scale); };
+    if (table) rb ? go(conv1_bf16x3_fwd_kernel<OC, true, true>) : go(conv1_bf16x3_fwd_kernel<OC, true, false>);
+    else rb ? go(conv1_bf16x3_fwd_kernel<OC, false, true>) : go(conv1_bf16x3_fwd_kernel<OC, false, false>);
     return hipGetLastError();
 }
 
@@ -267,23 +271,31 @@ inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const uint8_t *const
 // Rows of 20 pixels are padded to 24 = 3 blocks of 8 with zero dY.
 // part: [gridDim.x][OCT][257]; the last column is the bias gradient.  A layer
 // with OCT = 32 filters is done in two slices of 16 (blockIdx.y).
-template <int OCT, int NPART, bool TABLE>
+// Matrix and vector instructions (28 % and 36 % of the SIMDs' cycles: bytes to bf16, the split of dY) and the phases of
+// the one block per compute unit bound it; half of the cycles of the LDS were bank conflicts while rows of the planes
+// were 32 pixels and planes and filters at odd pitches: 2560 frames of 16 filters 36.4 -> 34.5 us, 1280 of 32 40.9 ->
+// 38.1; with one term of dY (ONE) instead of two more that were zero 36.6 -> 30.1 and 41.3 -> 32.5.
+template <int OCT, int NPART, bool TABLE, bool ONE>
 __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const uint8_t *__restrict__ x,
                                                                  const uint8_t *const *__restrict__ table,
                                                                  const float *__restrict__ dy,
-                                                                 float *__restrict__ part, int nframes, float scale,
-                                                                 int rb) {
-    // rb: dY enters the products (and the bias sums) rounded to bfloat16
+                                                                 float *__restrict__ part, int nframes, float scale) {
+    // ONE: dY enters the products (and the bias sums) rounded to bfloat16
     constexpr int C = 4, H = 84, W = 84, OC = 16, OH = 20, NPIX = 400, K = 256, CHW = C * H * W;
-    constexpr int XROW = 32, XPLANE = 21 * XROW + 8;       // bf16 elements; plane pitch 20 mod 32 dwords
-    constexpr int DROW = 24, DOC = OH * DROW + 8;          // dY rows padded to 24, filter pitch 20 mod 32 dwords
+    // bf16 elements.  Blocks of 8 pixels are consecutive units of 16 bytes, in the planes as in dY; dY's filters lie at a pitch
+    // of lds_row_units.  A plane (c, u', v') lies 4 u' + {0, 2, 8, 10}[v'] (mod 16) units behind a multiple of 256 bytes: even
+    // places that differ within {0-3, 12-15} and within {4-11}, as lds_row_units wants them, and the four u' that a store
+    // instruction meets are 64 bytes apart.
+    constexpr int XROW = 24, XPLANE = 80 * 8;
+    constexpr int DROW = 24, DOC = 8 * lds_row_units(OH * 3);
+    constexpr int NTERM = ONE ? 1 : 3;
     constexpr int NTHR = 256 * NPART;                      // NPART wavefronts per SIMD, so that one's LDS and
                                                            // conversion work fills another's MFMA waits
     constexpr int NITEM = 336 * 6, IPT = (NITEM + NTHR - 1) / NTHR;    // (frame row, group of 4 dwords)
     constexpr int NDV = OC * NPIX / 4, DPT = (NDV + NTHR - 1) / NTHR;  // float4 of dY per frame
     constexpr int NSTEP = OH * 3 / 4;                      // 60 blocks of 8 pixels, 4 per MFMA
-    __shared__ __attribute__((aligned(16))) __bf16 xp[64 * XPLANE];
-    __shared__ __attribute__((aligned(16))) __bf16 dp[3 * OC * DOC];
+    __shared__ __attribute__((aligned(16))) __bf16 xp[64 * XPLANE + 16 * 8];
+    __shared__ __attribute__((aligned(16))) __bf16 dp[NTERM * OC * DOC];
     __shared__ float bsh[NDV];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -292,13 +304,13 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
     const int oc0 = blockIdx.y * OC;                       // my slice of the filters
     static_assert(OCT % OC == 0, "whole slices of 16 filters");
 
-    for (int e = tid; e < 64 * XPLANE / 2; e += NTHR) ((uint32_t *)xp)[e] = 0u;     // padding stays zero
-    for (int e = tid; e < 3 * OC * DOC / 2; e += NTHR) ((uint32_t *)dp)[e] = 0u;
+    for (int e = tid; e < (64 * XPLANE + 16 * 8) / 2; e += NTHR) ((uint32_t *)xp)[e] = 0u;     // padding stays zero
+    for (int e = tid; e < NTERM * OC * DOC / 2; e += NTHR) ((uint32_t *)dp)[e] = 0u;
 
     // staging descriptors: where my dwords come from and where they go.  A row of 21 dwords is five groups of four
     // and a last group of one; that one is fetched as the last of the row's dwords 17..20, so that every fetch is one
     // 16-byte load (4-byte aligned) that stays inside the frame.
-    int xsrc[IPT], xdst[IPT], xcnt[IPT];
+    int xsrc[IPT], xdst[IPT], xup[IPT], xcnt[IPT];       // xup: where v' = 2 lies, from v' = 0
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
         const int it = min(tid + NTHR * i, NITEM - 1);
@@ -306,7 +318,8 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
         const int c = row / H, r = row % H;
         xsrc[i] = row * (W / 4) + (gq == 5 ? 17 : 4 * gq); // dword index in the frame
         xcnt[i] = (tid + NTHR * i < NITEM) ? (gq == 5 ? 1 : 4) : 0;
-        xdst[i] = ((c * 4 + r % 4) * 4) * XPLANE + (r / 4) * XROW + 4 * gq;   // plane (c, u'=r%4, v'=0)
+        xdst[i] = ((c * 4 + r % 4) * 4) * XPLANE + 4 * (r % 4) * 8 + (r / 4) * XROW + 4 * gq;   // plane (c, u'=r%4, v'=0)
+        xup[i] = 2 * XPLANE + (r % 4 < 2 ? 64 : -64);
     }
     int dsrc[DPT], ddst[DPT];
 #pragma unroll
@@ -341,7 +354,7 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
     fetch(next.get(), min(f, nframes - 1));
     if (TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
     const int ch = wave & 3, prt = wave >> 2;        // wavefronts w, w + 4, ... share channel w and divide the pixel blocks
-    const __bf16 *xq = xp + (ch * 16 + l16) * XPLANE;                // my plane
+    const __bf16 *xq = xp + (ch * 16 + l16) * XPLANE + 8 * ((4 * (l16 >> 2) + (l16 & 1) * 2 + (l16 & 2) * 4) & 15);      // my plane
     for (; f < nframes; f += gridDim.x) {
         __syncthreads();
 #pragma unroll
@@ -354,7 +367,7 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
                     union { __bf16 h[4]; uint2 u; } o;
 #pragma unroll
                     for (int t = 0; t < 4; ++t) o.h[t] = (__bf16)(float)((xv[t] >> (8 * vq)) & 0xff);
-                    *(uint2 *)(xp + xdst[i] + vq * XPLANE) = o.u;
+                    *(uint2 *)(xp + xdst[i] + (vq / 2) * xup[i] + (vq % 2) * (XPLANE + 16)) = o.u;
                 }
             }
         }
@@ -365,10 +378,9 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
                 union { __bf16 h[4]; uint2 u; } o[3];
                 split3_pair(v[0], v[1], o[0].u.x, o[1].u.x, o[2].u.x);
                 split3_pair(v[2], v[3], o[0].u.y, o[1].u.y, o[2].u.y);
-                if (rb) { o[1].u = uint2{0u, 0u}; o[2].u = uint2{0u, 0u}; }
 #pragma unroll
-                for (int term = 0; term < 3; ++term) *(uint2 *)(dp + term * OC * DOC + ddst[i]) = o[term].u;
-                bsh[tid + NTHR * i] = rb ? ((float)o[0].h[0] + (float)o[0].h[1]) + ((float)o[0].h[2] + (float)o[0].h[3])
+                for (int term = 0; term < NTERM; ++term) *(uint2 *)(dp + term * OC * DOC + ddst[i]) = o[term].u;
+                bsh[tid + NTHR * i] = ONE ? ((float)o[0].h[0] + (float)o[0].h[1]) + ((float)o[0].h[2] + (float)o[0].h[3])
                                         : (v[0] + v[1]) + (v[2] + v[3]);
             }
         }
@@ -387,14 +399,14 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
         auto steps = [&](auto first, auto last) {
 #pragma unroll
             for (int st = decltype(first)::value; st < decltype(last)::value; ++st) {
-                const int blk = 4 * st + g, i = blk / 3, jb = blk % 3;
+                const int blk = 4 * st + g;               // row blk / 3 of 24 pixels, block blk % 3 of it
                 Bf16x8Bits d[3];
 #pragma unroll
-                for (int term = 0; term < 3; ++term)
-                    d[term].u = *(const u32x4 *)(dp + term * OC * DOC + l16 * DOC + i * DROW + 8 * jb);
+                for (int term = 0; term < NTERM; ++term)
+                    d[term].u = *(const u32x4 *)(dp + term * OC * DOC + l16 * DOC + 8 * blk);
 #pragma unroll
                 for (int a = 0; a < 2; ++a) {
-                    const __bf16 *src = xq + (i + a) * XROW + 8 * jb;
+                    const __bf16 *src = xq + 8 * blk + a * XROW;
                     const u32x4 c0 = *(const u32x4 *)src;
                     const uint32_t c4 = *(const uint32_t *)(src + 8);
                     Bf16x8Bits x0, x1;
@@ -402,7 +414,7 @@ __global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const u
                     x1.u = u32x4{__builtin_amdgcn_alignbit(c0[1], c0[0], 16), __builtin_amdgcn_alignbit(c0[2], c0[1], 16),
                                  __builtin_amdgcn_alignbit(c0[3], c0[2], 16), __builtin_amdgcn_alignbit(c4, c0[3], 16)};
 #pragma unroll
-                    for (int term = 2; term >= 0; --term) {
+                    for (int term = NTERM - 1; term >= 0; --term) {
                         acc[a][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[term].v, x0.v, acc[a][0], 0, 0, 0);
                         acc[a][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[term].v, x1.v, acc[a][1], 0, 0, 0);
                     }
@@ -466,8 +478,9 @@ inline hipError_t launch_conv1_bf16x3_wgrad(const uint8_t *x, const uint8_t *con
                                             hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
     const dim3 grid(conv1_bf16x3_wgrad_blocks(nframes), OCT / 16), block(256 * NPART);
-    if (table) ga3c::launch((conv1_bf16x3_wgrad_kernel<OCT, NPART, true>), grid, block, 0, s, x, table, dy, part, nframes, scale, rb);
-    else ga3c::launch((conv1_bf16x3_wgrad_kernel<OCT, NPART, false>), grid, block, 0, s, x, table, dy, part, nframes, scale, rb);
+    auto go = [&](auto kernel) { ga3c::launch(kernel, grid, block, 0, s, x, table, dy, part, nframes, scale); };
+    if (table) rb ? go(conv1_bf16x3_wgrad_kernel<OCT, NPART, true, true>) : go(conv1_bf16x3_wgrad_kernel<OCT, NPART, true, false>);
+    else rb ? go(conv1_bf16x3_wgrad_kernel<OCT, NPART, false, true>) : go(conv1_bf16x3_wgrad_kernel<OCT, NPART, false, false>);
     return hipGetLastError();
 }
 
