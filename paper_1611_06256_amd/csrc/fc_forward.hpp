@@ -10,16 +10,17 @@
 // Reading x and W as fp32 and splitting both in every block, that kernel was
 // bound by the latency of one load per k-step and by the splitting: 16 us for
 // 1024 x 256 x 2592 with 3.2 us of products.  Here nothing passes through
-// registers on its way to LDS, so several k-steps can be under way: a wavefront
-// asks for the weights of a quarter of the columns and for its own 16 MT rows of
-// x, still fp32; it is the only one that uses those rows and splits them as it
-// reads them.  Two blocks per compute unit: 1024 frames 16.0 -> 11.3 us, 512 10.4
-// -> 8.6, 2560 30.1 -> 25.7, 256 of the larger net 11.7 -> 9.3 (1280: 34.3 -> 29.2),
-// 128 x 1024 x 18496 42.5 -> 36.0.
+// registers on its way to LDS, so a k-step is under way while the last one is
+// multiplied: a wavefront asks for the weights of a quarter of the columns and for
+// its own 16 MT rows of x, still fp32; it is the only one that uses those rows and
+// splits them as it reads them.  Two steps in LDS leave room for four blocks per
+// compute unit, which hide each other's waits better than two blocks with three
+// steps do: 2560 frames 26.1 -> 23.1 us, 640: 11.6 -> 9.8, larger net 320: 12.7 ->
+// 10.7, 1280: 30.9 -> 28.6 (with three: 1024 frames 16.0 -> 11.3 against the kernel
+// above, 512 10.4 -> 8.6, 2560 30.1 -> 25.7, 256 of the larger net 11.7 -> 9.3).
 // What is left is LDS reads (14 per wavefront and k-step of 384 cycles of products)
 // and, at small batches, start and end of the launch.  32 rows per wavefront read
-// less but leave one block per compute unit (12.5 us at 1024 frames); four k-steps in
-// LDS instead of three gain nothing.
+// less but left one block per compute unit (12.5 us at 1024 frames).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -65,14 +66,14 @@ __global__ __launch_bounds__(256) void fc_planes_kernel(const float4 *__restrict
     if (i < p.n) fc_planes_store4(p, i, theta[p.first + i]);
 }
 
-constexpr int FC_STEPS = 3;                   // k-steps of 32 in LDS (60 KB: two blocks per compute unit)
-template <bool ONE>
-constexpr int fc_forward_lds() { return FC_STEPS * (4 * 2048 + 4 * (ONE ? 1 : 3) * 1024); }
+// NS: k-steps of 32 in LDS (20 KB each).
+template <bool ONE, int NS>
+constexpr int fc_forward_lds() { return NS * (4 * 2048 + 4 * (ONE ? 1 : 3) * 1024); }
 
 // ONE: operands rounded to bfloat16 (one term).
-template <bool ONE>
+template <bool ONE, int NS>
 __global__ __launch_bounds__(256, 2) void fc_forward_kernel(const FcForwardArgs p) {
-    constexpr int NS = FC_STEPS, NTERM = ONE ? 1 : 3, XB = 4 * 2048, WB = 4 * NTERM * 1024, LOADS = 2 + NTERM;
+    constexpr int NTERM = ONE ? 1 : 3, XB = 4 * 2048, WB = 4 * NTERM * 1024, LOADS = 2 + NTERM;
     extern __shared__ __attribute__((aligned(16))) unsigned char fc_smem[];    // [step][x: wavefront, row, k | w: column tile, term, lane]
     // chunk z belongs to XCD z % 8, whose L2 then holds one slice of the weights
     const int local = blockIdx.x / DG_XCDS, zi = p.tiles.div(local), t = local - zi * (int)p.tiles.d;
@@ -153,9 +154,12 @@ inline bool fc_forward_batch_ok(const float *x, int M, int K) { return (uintptr_
 inline hipError_t launch_fc_forward(FcForwardArgs p, int rb, hipStream_t s) {
     const int ntm = (p.M + 63) / 64, ntn = p.N / FC_BN;
     p.tiles = FastDiv(ntm * ntn); p.cols = FastDiv(ntn);
-    const dim3 grid(DG_XCDS * ((p.nz + DG_XCDS - 1) / DG_XCDS) * ntm * ntn);
-    if (rb) ga3c::launch(fc_forward_kernel<true>, grid, dim3(256), fc_forward_lds<true>(), s, p);
-    else ga3c::launch(fc_forward_kernel<false>, grid, dim3(256), fc_forward_lds<false>(), s, p);
+    const unsigned blocks = DG_XCDS * ((p.nz + DG_XCDS - 1) / DG_XCDS) * ntm * ntn;
+    auto go = [&](auto kernel, int lds) { ga3c::launch(kernel, dim3(blocks), dim3(256), lds, s, p); };
+    // a block that has a compute unit to itself waits for memory alone: one step more on its way (prediction of 128 frames of the
+    // stride-3 member 41.9 us against 42.5; with 512 blocks two steps are level or ahead)
+    if (blocks <= 256) rb ? go(fc_forward_kernel<true, 3>, fc_forward_lds<true, 3>()) : go(fc_forward_kernel<false, 3>, fc_forward_lds<false, 3>());
+    else rb ? go(fc_forward_kernel<true, 2>, fc_forward_lds<true, 2>()) : go(fc_forward_kernel<false, 2>, fc_forward_lds<false, 2>());
     return hipGetLastError();
 }
 
