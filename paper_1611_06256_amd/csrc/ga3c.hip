@@ -1511,10 +1511,9 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
 
 // One launch adds up the partial weight gradients of every layer and, on the
 // way, the squares of the results (for the global norm).
-// A segment is a stack of nz partial matrices ws[z][M][N] (nz = 1 and ws = gW: the gradient itself).  Rows [r0, r0+rows)
-// go to gW[(m-r0)*(N-1) + n] for n < N-1 and gb[m-r0] for n = N-1 (bias_col),
-// or all N columns to gW[(m-r0)*N + n] (no bias_col).  A block handles 256/zg
-// outputs with zg threads each: thread j adds z = j, j+zg, ... (eight loads in
+// A segment is a stack of nz partial matrices [rows][N], `stride` floats apart (nz = 1 and in place: the gradient itself).
+// It goes to gW[m*(N-1) + n] for n < N-1 and gb[m] for n = N-1 (bias column), or all N columns to gW[m*N + n].
+// A block handles 256/zg outputs with zg threads each: thread j adds z = j, j+zg, ... (sixteen loads in
 // flight at a time), then the zg sums are added in order of j.  Nothing depends
 // on timing, so the gradient is reproducible bit for bit.
 // Block ids go round-robin over the 8 XCDs; the ids of one XCD take consecutive
@@ -1522,81 +1521,114 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
 // sums also share an L2.  Where the first row of the segment and the planes of the stack start on 16-byte
 // boundaries a thread takes four consecutive outputs and reads its partial sums as 16-byte vectors (a quarter of the
 // load instructions); the sums of an output are formed in the same order either way.
-struct ReduceSeg {
-    const float *ws;
-    float *gW, *gb;
-    int nz, M, N, r0, rows, bias_col, zg, first_block;
-    int per_xcd;         // the segment owns 8 * per_xcd block ids, first_block is a multiple of 8
-    int vec;             // a thread takes four consecutive outputs and reads 16-byte vectors (the stack allows it)
-};
 constexpr int MAX_REDUCE_SEGS = 12;
+struct alignas(64) ReduceSeg {
+    const float *ws;     // first row of the segment in the first matrix
+    float *gW, *gb;
+    size_t stride, cnt;  // cnt = rows * N
+    int nz, N;
+    uint32_t mul;        // FastDiv(N) is {N, mul, shift}
+    int per_xcd;         // the segment owns 8 * per_xcd block ids, the first of them is a multiple of 8
+    uint8_t shift, lzg;  // zg = 1 << lzg
+    bool bias_col, vec, in_place;        // vec: a thread takes four consecutive outputs and reads 16-byte vectors (the stack allows it)
+};
+static_assert(sizeof(ReduceSeg) == 64, "a segment is one line of the arguments");
 struct ReduceArgs {
-    ReduceSeg seg[MAX_REDUCE_SEGS];
-    int nseg;
+    int first[MAX_REDUCE_SEGS];          // first block of a segment; INT32_MAX for those there are not
     float *normpart;     // one partial sum of squares per block
+    ReduceSeg seg[MAX_REDUCE_SEGS];
 };
 
+// What bounds it on small updates is the chain of one block: arguments, loads, LDS, stores.  The arguments come from host
+// memory a line at a time, about a microsecond each, so a block finds its segment in one line (`first`) and reads one more,
+// and the four outputs of a thread are divided by N once: training of the small net on 40 frames 67.0 -> 65.4 us, of the larger
+// net on 1280 466.0 -> 462.2 (against a search from segment to segment, 64-bit divisions per output and eight loads a round).
 __global__ __launch_bounds__(256) void reduce_all_kernel(const ReduceArgs a) {
     __shared__ float4 sh[256];
     __shared__ float wsum[4];
-    int si = 0;
-    while (si + 1 < a.nseg && (int)blockIdx.x >= a.seg[si + 1].first_block) ++si;
+    int si = 0, first = a.first[0];
+#pragma unroll
+    for (int k = 1; k < MAX_REDUCE_SEGS; ++k)
+        if ((int)blockIdx.x >= a.first[k]) { si = k; first = a.first[k]; }
     const ReduceSeg &g = a.seg[si];
-    const int opb = 256 / g.zg;
-    const int o = threadIdx.x % opb, zi = threadIdx.x / opb;
-    const size_t cnt = (size_t)g.rows * g.N;
-    const int lb = blockIdx.x - g.first_block;
+    const int lopb = 8 - g.lzg, zg = 1 << g.lzg, opb = 1 << lopb, N = g.N, nz = g.nz;
+    const int o = threadIdx.x & (opb - 1), zi = threadIdx.x >> lopb;
+    const int lb = blockIdx.x - first;
     const int per = g.vec ? 4 : 1;                      // outputs per thread
-    const size_t i = (((size_t)(lb % 8) * g.per_xcd + lb / 8) * opb + o) * per;
+    const size_t cnt = g.cnt, stride = g.stride;
+    const size_t i = ((size_t)((lb & 7) * g.per_xcd + (lb >> 3)) * opb + o) * per;
     float4 s = float4{0.f, 0.f, 0.f, 0.f};
-    const size_t src = (size_t)g.r0 * g.N + i, stride = (size_t)g.M * g.N;
-    if (g.vec && g.nz == 1 && i + 3 < cnt) {
-        if (zi == 0) s = *(const float4 *)(g.ws + src);
+    const float *src = g.ws + i;
+    if (g.vec && nz == 1 && i + 3 < cnt) {
+        if (zi == 0) s = *(const float4 *)src;
     } else if (g.vec && i + 3 < cnt) {
-        for (int z = zi; z < g.nz; z += 8 * g.zg) {
-            float4 v[8];
+        for (int z0 = 0; z0 < nz; z0 += 16 * zg) {
+            float4 v[16];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = *(const float4 *)(g.ws + (size_t)min(z + j * g.zg, g.nz - 1) * stride + src);
+            for (int q = 0; q < 16; q += 4)
+                if (z0 + q * zg < nz) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool in = z + j * g.zg < g.nz;
-                s.x += in ? v[j].x : 0.f; s.y += in ? v[j].y : 0.f; s.z += in ? v[j].z : 0.f; s.w += in ? v[j].w : 0.f;
-            }
+                    for (int j = q; j < q + 4; ++j) v[j] = *(const float4 *)(src + (size_t)min(z0 + zi + j * zg, nz - 1) * stride);
+                }
+#pragma unroll
+            for (int q = 0; q < 16; q += 4)
+                if (z0 + q * zg < nz) {
+#pragma unroll
+                    for (int j = q; j < q + 4; ++j) {
+                        const bool in = z0 + zi + j * zg < nz;
+                        s.x += in ? v[j].x : 0.f; s.y += in ? v[j].y : 0.f; s.z += in ? v[j].z : 0.f; s.w += in ? v[j].w : 0.f;
+                    }
+                }
         }
     } else if (i < cnt) {                               // one output, or the last, partial group of four
         const int ne = (int)min((size_t)per, cnt - i);
         for (int e = 0; e < ne; ++e) {
             float t = 0.f;
-            for (int z = zi; z < g.nz; z += 8 * g.zg) {
+            for (int z = zi; z < nz; z += 8 * zg) {
                 float v[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) v[j] = g.ws[(size_t)min(z + j * g.zg, g.nz - 1) * stride + src + e];
+                for (int j = 0; j < 8; ++j) v[j] = src[(size_t)min(z + j * zg, nz - 1) * stride + e];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) t += (z + j * g.zg < g.nz) ? v[j] : 0.f;
+                for (int j = 0; j < 8; ++j) t += (z + j * zg < nz) ? v[j] : 0.f;
             }
             if (e == 0) s.x = t; else if (e == 1) s.y = t; else if (e == 2) s.z = t; else s.w = t;
         }
     }
-    sh[threadIdx.x] = s;
-    __syncthreads();
     float sq = 0.f;
+    if (zg > 1) {
+        sh[threadIdx.x] = s;
+        __syncthreads();
+    }
     if (zi == 0 && i < cnt) {
-        float4 t = sh[o];
-        for (int j = 1; j < g.zg; ++j) {
+        for (int j = 1; j < zg; ++j) {
             const float4 u = sh[j * opb + o];
-            t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
+            s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
         }
-        const float te[4] = {t.x, t.y, t.z, t.w};
-        const int ne = (int)min((size_t)per, cnt - i);
-        for (int e = 0; e < ne; ++e) {
-            const size_t ie = i + e;
-            const int m = (int)(ie / g.N), n = (int)(ie % g.N);
-            if (g.ws != g.gW) {                         // else the gradient is there already: only its squares are wanted
-                if (!g.bias_col) g.gW[ie] = te[e];
-                else if (n < g.N - 1) g.gW[(size_t)m * (g.N - 1) + n] = te[e];
-                else g.gb[m] = te[e];
+        const float te[4] = {s.x, s.y, s.z, s.w};       // those behind the last output are zero
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq += te[e] * te[e];
+        if (!g.in_place) {                              // else the gradient is there already: only its squares are wanted
+            typedef float f4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
+            size_t m = 0, n = i;
+            if (g.bias_col) {                           // FastDiv takes 31 bits
+                if (cnt >> 31) m = i / (size_t)N;
+                else m = (__umulhi((uint32_t)i, g.mul) + (uint32_t)i) >> g.shift;
+                n = i - m * N;
             }
-            sq += te[e] * te[e];
+            const int NW = g.bias_col ? N - 1 : N;      // columns of gW
+            float *dst = g.gW + (m * (size_t)(g.bias_col ? NW : 0) + n);
+            if (g.vec && i + 3 < cnt && (!g.bias_col || n + 3 < (size_t)NW)) {
+                *(f4_dword_aligned *)dst = f4_dword_aligned{te[0], te[1], te[2], te[3]};
+            } else {
+                const int ne = (int)min((size_t)per, cnt - i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < ne) {
+                        if (!g.bias_col || n < (size_t)NW) *dst++ = te[e];
+                        else g.gb[m] = te[e];
+                        if (g.bias_col && ++n == (size_t)N) { n = 0; ++m; }
+                    }
+            }
         }
     }
     sq = wave_sum(sq);
@@ -2571,7 +2603,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     int nz, kchunk;
     // Every weight gradient leaves its partial sums in a region of its own; one kernel adds them all up at the end.
     ReduceArgs red;
-    red.nseg = 0; red.normpart = c->partials;
+    std::fill(red.first, red.first + MAX_REDUCE_SEGS, INT32_MAX);
+    red.normpart = c->partials;
+    int nseg = 0;
     // the fused heads kernel still reads the fc partial sums, which sit at the start of the workspace
     size_t ws_used = fused_heads ? ((size_t)w.fc_nz * B * F + 63) / 64 * 64 : 0;
     int red_blocks = 0;
@@ -2583,15 +2617,17 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     };
     bool seg_overflow = false;
     auto add_seg = [&](const float *ws, int nz_, int M, int Ncols, int r0, int rows, float *gW, float *gb, int bias_col) {
-        if (red.nseg >= MAX_REDUCE_SEGS) { seg_overflow = true; return; }
-        ReduceSeg &g = red.seg[red.nseg++];
-        g.ws = ws; g.nz = nz_; g.M = M; g.N = Ncols; g.r0 = r0; g.rows = rows; g.gW = gW; g.gb = gb; g.bias_col = bias_col;
-        int zg = 1;
-        while (zg < 64 && zg * 16 < nz_) zg *= 2;      // at most two rounds of eight loads per thread
-        g.zg = zg; g.first_block = red_blocks;
-        g.vec = ((size_t)r0 * Ncols) % 4 == 0 && ((size_t)M * Ncols) % 4 == 0 && (uintptr_t)ws % 16 == 0;
-        const size_t per_block = (size_t)(256 / zg) * (g.vec ? 4 : 1);
-        const int nblk = (int)(((size_t)rows * Ncols + per_block - 1) / per_block);
+        if (nseg >= MAX_REDUCE_SEGS) { seg_overflow = true; return; }
+        red.first[nseg] = red_blocks;
+        ReduceSeg &g = red.seg[nseg++];
+        g.ws = ws + (size_t)r0 * Ncols; g.gW = gW; g.gb = gb; g.nz = nz_; g.N = Ncols; g.bias_col = bias_col != 0; g.in_place = ws == gW;
+        g.stride = (size_t)M * Ncols; g.cnt = (size_t)rows * Ncols;
+        const FastDiv by_n((uint32_t)Ncols);
+        g.mul = by_n.mul; g.shift = (uint8_t)by_n.shift; g.lzg = 0;
+        while (g.lzg < 6 && (16 << g.lzg) < nz_) ++g.lzg;      // one round of sixteen loads per thread
+        g.vec = ((size_t)r0 * Ncols) % 4 == 0 && g.stride % 4 == 0 && (uintptr_t)ws % 16 == 0;
+        const size_t per_block = (size_t)(256 >> g.lzg) * (g.vec ? 4 : 1);
+        const int nblk = (int)((g.cnt + per_block - 1) / per_block);
         g.per_xcd = (nblk + 7) / 8;
         red_blocks += 8 * g.per_xcd;
         red_bytes += 4.0 * (nz_ + 1) * rows * Ncols;

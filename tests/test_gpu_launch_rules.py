@@ -52,6 +52,13 @@ def test_fc_gradients_at_the_edges_of_tiles_and_chunks(G, stride, F, A, N, math)
     P.run_train(G, G.NetDesc(conv=conv, fc_units=F, n_actions=A, math=math), N, 1, 7250 + N, dict(clip_norm=40.0))
 
 
+@pytest.mark.parametrize("F,A,N", [(256, 3, 1), (256, 3, 17), (64, 7, 33), (256, 4, 129), (64, 3, 136), (256, 11, 264)])
+def test_partial_gradients_added_up_at_the_ends_of_rows_and_rounds(G, F, A, N):
+    # 1 to 264 matrices of partial sums (sixteen to a thread and round); rows of F + 1 = 257 and 65 columns of which groups of four
+    # outputs take the bias with them, segments of 771, 455 and 195 outputs whose last group is not whole, and some without groups
+    P.run_train(G, G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=A), N, 1, 7270 + N, dict(clip_norm=40.0))
+
+
 def test_parameters_read_out_to_any_place(G):
     import torch
     net, _, theta = P.make(G, G.NetDesc(**P.ODD), 1, 0, 7300)
