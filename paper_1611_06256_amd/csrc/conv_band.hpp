@@ -12,7 +12,7 @@
 // [channel], so one staging unit (8 channels of a pixel: eight loads along
 // planes, coalesced over pixels) leaves as one 16-byte store per term, and the 8
 // consecutive channels a lane feeds to an MFMA are one 16-byte read.  The pixel
-// pitch (6 C + 16 bytes) puts 16 consecutive pixels on all banks; with stride 2
+// pitch is 6 C + 16 bytes (one of lds_row_units' was level here); with stride 2
 // the even and the odd columns of an input row are stored apart, so that
 // consecutive output pixels read consecutive LDS pixels.  Filters come as
 // ready-made fragments (band_filter_fragments_kernel, once per parameter copy).
