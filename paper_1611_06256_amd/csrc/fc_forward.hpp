@@ -13,11 +13,9 @@
 // registers on its way to LDS, so a k-step is under way while the last one is
 // multiplied: a wavefront asks for the weights of a quarter of the columns and for
 // its own 16 MT rows of x, still fp32; it is the only one that uses those rows and
-// splits them as it reads them.  Two steps in LDS leave room for four blocks per
-// compute unit, which hide each other's waits better than two blocks with three
-// steps do: 2560 frames 26.1 -> 23.1 us, 640: 11.6 -> 9.8, larger net 320: 12.7 ->
-// 10.7, 1280: 30.9 -> 28.6 (with three: 1024 frames 16.0 -> 11.3 against the kernel
-// above, 512 10.4 -> 8.6, 2560 30.1 -> 25.7, 256 of the larger net 11.7 -> 9.3).
+// splits them as it reads them (three steps in LDS against the kernel above: 1024
+// frames 16.0 -> 11.3 us, 512 10.4 -> 8.6, 2560 30.1 -> 25.7, 256 of the larger net
+// 11.7 -> 9.3).  How many steps are in LDS is chosen per launch: fc_forward_steps.
 // What is left is LDS reads (14 per wavefront and k-step of 384 cycles of products)
 // and, at small batches, start and end of the launch.  32 rows per wavefront read
 // less but left one block per compute unit (12.5 us at 1024 frames).
@@ -66,7 +64,7 @@ __global__ __launch_bounds__(256) void fc_planes_kernel(const float4 *__restrict
     if (i < p.n) fc_planes_store4(p, i, theta[p.first + i]);
 }
 
-// NS: k-steps of 32 in LDS (20 KB each).
+// NS: k-steps of 32 in LDS (20 KB each, with one term 12 KB).
 template <bool ONE, int NS>
 constexpr int fc_forward_lds() { return NS * (4 * 2048 + 4 * (ONE ? 1 : 3) * 1024); }
 
@@ -151,14 +149,36 @@ __global__ __launch_bounds__(256, 2) void fc_forward_kernel(const FcForwardArgs 
 inline bool fc_forward_ok(int K, int N) { return K % 32 == 0 && N % FC_BN == 0; }
 inline bool fc_forward_batch_ok(const float *x, int M, int K) { return (uintptr_t)x % 16 == 0 && (size_t)M * K * 4 < (size_t)1 << 32; }
 
-inline hipError_t launch_fc_forward(FcForwardArgs p, int rb, hipStream_t s) {
+// k-steps in LDS: with three, two are on their way while one is multiplied; with two, more blocks fit a compute unit and hide each
+// other's waits (three terms: four blocks instead of two; one term: six instead of four).  Two steps against three, us of the
+// launch, medians of 30 to 40 calls:
+// Three terms.  Up to 256 blocks a block has a compute unit to itself and waits for memory alone: stride-1 member 32 frames 25.9 /
+// 24.4, stride-2 member 256: 8.1 / 7.8, larger net 128: 7.7 / 7.4.  From two blocks a unit on two steps are ahead: small net 512
+// frames (512 blocks) 9.2 / 10.2, 700: 11.1 / 12.9, larger net 256: 9.7 / 10.6, 10368 columns x 1024 units 256: 32.4 / 34.1, stride-1
+// member 192 (768 blocks): 56.0 / 60.3, update of the small net 640: 10.6 / 12.9, 2560: 24.7 / 27.9, larger net 1280: 29.0 / 31.6 -
+// unless there are two blocks a unit at most and the weights come from HBM because the activations in front of them no longer leave
+// them in the 256 MB of the Infinity Cache: stride-1 member 128 frames (114 + 129 MB) 36.9 / 35.4
+// (medians of eleven runs, 33 - 40 / 30 - 39), 256 (114 + 258): 68.8 / 67.1, with 512 units 200 (57 + 202): 35.5 / 31.1; not yet with
+// 112 frames (114 + 113): 28.8 / 29.8, nor with 20736 columns x 1024 units at 256 (127 + 71): 59.9 / 63.2.
+// One term.  Four blocks fit with three steps already, and three are ahead up to three blocks a unit: small net 256 frames 6.3 / 5.1,
+// 512: 8.0 / 6.7, 1024: 8.8 / 6.7, larger net 128: 6.8 / 5.4, 512: 9.9 / 7.7, stride-1 member 128: 21.0 / 14.9, 256: 49.2 / 30.8,
+// update of the small net 1280 (640 blocks) 9.4 / 8.9.  Above that two are ahead or level: larger net 400 frames (896) 9.6 / 10.1,
+// its update of 1280 (1280) 14.5 / 15.1, small net 2250 (1152) 13.1 / 13.8, 2560: 14.0 / 13.7.
+inline int fc_forward_steps(bool one, unsigned blocks, size_t weight_bytes, size_t pass_bytes) {
+    constexpr unsigned CUS = 256;
+    if (one) return blocks <= 3 * CUS ? 3 : 2;
+    const bool from_hbm = weight_bytes + pass_bytes > (size_t)230 << 20;
+    return blocks <= (from_hbm ? 2 * CUS : CUS) ? 3 : 2;
+}
+
+// pass_bytes: the activations that the forward pass has written in front of this product.
+inline hipError_t launch_fc_forward(FcForwardArgs p, size_t pass_bytes, int rb, hipStream_t s) {
     const int ntm = (p.M + 63) / 64, ntn = p.N / FC_BN;
     p.tiles = FastDiv(ntm * ntn); p.cols = FastDiv(ntn);
     const unsigned blocks = DG_XCDS * ((p.nz + DG_XCDS - 1) / DG_XCDS) * ntm * ntn;
     auto go = [&](auto kernel, int lds) { ga3c::launch(kernel, dim3(blocks), dim3(256), lds, s, p); };
-    // a block that has a compute unit to itself waits for memory alone: one step more on its way (prediction of 128 frames of the
-    // stride-3 member 41.9 us against 42.5; with 512 blocks two steps are level or ahead)
-    if (blocks <= 256) rb ? go(fc_forward_kernel<true, 3>, fc_forward_lds<true, 3>()) : go(fc_forward_kernel<false, 3>, fc_forward_lds<false, 3>());
+    if (fc_forward_steps(rb != 0, blocks, (size_t)p.N * p.K * 2 * (rb ? 1 : 3), pass_bytes) == 3)
+        rb ? go(fc_forward_kernel<true, 3>, fc_forward_lds<true, 3>()) : go(fc_forward_kernel<false, 3>, fc_forward_lds<false, 3>());
     else rb ? go(fc_forward_kernel<true, 2>, fc_forward_lds<true, 2>()) : go(fc_forward_kernel<false, 2>, fc_forward_lds<false, 2>());
     return hipGetLastError();
 }

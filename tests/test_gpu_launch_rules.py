@@ -59,6 +59,32 @@ def test_partial_gradients_added_up_at_the_ends_of_rows_and_rounds(G, F, A, N):
     P.run_train(G, G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=A), N, 1, 7270 + N, dict(clip_norm=40.0))
 
 
+# (frames of a batch, frames of the parts that it is predicted in once more): both are cut into the same chunks of k.  Small net, fp32
+# accuracy: 512 and 256 blocks of the fc product, with two and three k-steps in LDS; rounded: 960 and 512, two and three.  Stride-1
+# member: 512 blocks with three steps (its weights and the activations of 128 frames exceed the Infinity Cache), 512 with two, 256
+# with three; rounded: three.
+@pytest.mark.parametrize("net,math,B,parts", [("small", 0, 512, (256, 256)), ("small", 1, 900, (450, 450)),
+                                              ("paper1", 0, 128, (64, 64)), ("paper1", 0, 128, (100, 28)), ("paper1", 1, 128, (64, 64))])
+def test_fc_product_has_the_same_bits_with_two_and_three_steps_in_lds(G, net, math, B, parts):
+    import torch
+    A = 18
+    desc = G.SMALL_NET(A) if net == "small" else P.paper_family_net(G, 1, A)
+    desc.math = math
+    net = G.Ga3c(desc, B, 0)
+    net.params_init(7801)
+    frames = torch.from_numpy(synth.uniform_frames(7802, (B, 4, 84, 84))).cuda()
+    whole, split = torch.empty(B, A, device="cuda"), torch.empty(B, A, device="cuda")
+    print(f"predict B={B} math={math}", flush=True)
+    net.predict(frames, logits=whole)
+    at = 0
+    for n in parts:
+        net.predict(frames[at:at + n], logits=split[at:at + n])
+        at += n
+    torch.cuda.synchronize()
+    assert float(whole.abs().max()) > 0 and torch.equal(whole, split)
+    net.close()
+
+
 def test_parameters_read_out_to_any_place(G):
     import torch
     net, _, theta = P.make(G, G.NetDesc(**P.ODD), 1, 0, 7300)
