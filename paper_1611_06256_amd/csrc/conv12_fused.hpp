@@ -115,7 +115,8 @@ inline hipError_t launch_conv12_filter_fragments(const float *w1, const float *w
 // only the first plane of the layer-1 output is written and read.
 // KEEP: the layer-1 output is also written to y1 (a template parameter rather than a test of the pointer, so that
 // the stores do not cut the epilogue into a basic block each).
-template <bool ONE, bool KEEP, bool TABLE>
+// EARLY: the next frame is staged between the layer-1 wavefronts' own waits instead of between two barriers of the block.
+template <bool ONE, bool KEEP, bool TABLE, bool EARLY>
 __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t *__restrict__ x,
                                                                   const uint8_t *const *__restrict__ table,
                                                                   const u32x4 *__restrict__ frag,
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
     constexpr int CHW1 = 4 * 84 * 84, W1 = 84, NPIX1 = 400, OW1 = 20;
     constexpr int NV = CHW1 / 16, VPT = 7;                         // 16-byte vectors of a frame, per layer-1 thread
     constexpr int HW2 = 400, NPIX2 = 81, OW2 = 9, OC2 = 32;
-    __shared__ int l1_read;                                        // layer-1 wavefronts that have read their frame, over all frames
+    __shared__ int l1_read;                                        // EARLY: layer-1 wavefronts that have read their frame, over all frames
     __bf16 *xs = (__bf16 *)c12_smem;
     __bf16 *ys = xs + C12_XS;                                      // [2][3][C12_Y1]
     float *exb = (float *)(ys + 2 * 3 * C12_Y1);                   // [2][C12_EX]
@@ -176,11 +177,6 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
 
     const int n = (nframes - first + grid - 1) / grid;             // frames of this block (>= 1)
 
-    // Where a block has more than two frames they are staged between the layer-1 wavefronts' own waits instead of between two
-    // barriers of the block (us of the launch with barriers / early: 1024 frames 21.9 / 20.9, 2560 kept 49.6 / 49.0, rounded 38.5 /
-    // 35.6; a prediction of 512 frames, rounded, took 24.0 early, 23.75 with barriers).
-    const bool early = n > 2;
-
     floatx4 keep[3];                                               // layer 2: my filter tile's sums of the previous frame
 #pragma unroll
     for (int i = 0; i < 3; ++i) keep[i] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -196,7 +192,7 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
         }
     };
     // before the first iteration: the first frame and the layer-1 filter set go to LDS, then everybody takes its filters
-    if (tid == 0) l1_read = 0;
+    if (EARLY && tid == 0) l1_read = 0;
     if (layer1) {
         stage_frame();
 #pragma unroll
@@ -228,8 +224,8 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
     }
     for (int it = 0; it <= n + 1; ++it) {
         if (it > 0) {
-            __syncthreads();          // layer 2 has read the planes that layer 1 writes now; early: layer 1's frame is in xs
-            if (!early) {
+            __syncthreads();          // layer 2 has read the planes that layer 1 writes now; EARLY: layer 1's frame is in xs
+            if (!EARLY) {
                 if (layer1 && it < n) stage_frame();
                 __syncthreads();
             }
@@ -308,9 +304,9 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
                             for (int j = 0; j < 6; ++j)
                                 acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[j], wq[term][kb], acc[j], 0, 0, 0);
                     }
-                    floatx4 odd = floatx4{0.f, 0.f, 0.f, 0.f};
-                    if (rw == 0) {
+                    auto odd_tile = [&]() {
                         const int base24 = tile_base(24);
+                        floatx4 odd = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                         for (int kb = 0; kb < 8; ++kb) {
                             const bf16x8 xv = operand(base24, kb);
@@ -318,17 +314,22 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
                             for (int term = ONE ? 0 : 2; term >= 0; --term)
                                 odd = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv, wq[term][kb], odd, 0, 0, 0);
                         }
+                        return odd;
+                    };
+                    floatx4 odd = floatx4{0.f, 0.f, 0.f, 0.f};
+                    if (EARLY) {
+                        if (rw == 0) odd = odd_tile();
+                        // I have read the frame; what is left to do with it needs no more of it
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        if (lane == 0) __hip_atomic_fetch_add(&l1_read, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
                     }
-                    // I have read the frame; what is left to do with it needs no more of it
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                    if (lane == 0) __hip_atomic_fetch_add(&l1_read, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
                     for (int j = 0; j < 6; ++j) finish(rw + 4 * j, acc[j]);
-                    if (rw == 0) finish(24, odd);
+                    if (rw == 0) finish(24, EARLY ? odd : odd_tile());
                 }
-                // early: the next frame takes its place as soon as the four layer-1 wavefronts have read this one, while layer 2 goes
+                // EARLY: the next frame takes its place as soon as the four layer-1 wavefronts have read this one, while layer 2 goes
                 // on (every one of them arrives here in every such iteration, so the wait ends).
-                if (early && it + 1 < n) {
+                if (EARLY && it + 1 < n) {
                     while (__hip_atomic_load(&l1_read, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < 4 * (it + 1)) __builtin_amdgcn_s_sleep(1);
                     stage_frame();
                 }
@@ -400,32 +401,37 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
 
 inline int conv12_fused_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
 
+// Whether the next frame is staged early (barriers / early, us of the launch, medians of three runs).  At fp32 accuracy where a
+// block has more than two frames: 512 frames 14.95 / 14.98, 600: 18.4 / 17.9, 768: 18.6 / 18.4, 1024: 22.8 / 22.6, update of 1025:
+// 25.7 / 25.1, 2560: 50.1 / 48.8.  (One frame a block has nothing to stage, and the wait and the count of the early variant cost it
+// 0.3 us: 128 frames 8.35 / 8.6, 256: 9.4 / 9.7.)  Rounded operands have a sixth of the products for the wait to hide behind; early
+// gains only where layer 1 is stored too and a block has more than five frames: update of 640 frames 13.7 / 14.4, 1025: 17.3 / 17.8,
+// 1280: 20.5 / 20.5, 1400: 22.4 / 22.3, 1750: 25.3 / 24.7, 2560: 39.2 / 36.2; prediction of 1024: 15.1 / 15.5, 2048: 23.5 / 24.2.
+inline bool conv12_fused_early(int nframes, bool one, bool keep) {
+    if (one && !keep) return false;
+    return nframes > (one ? 5 : 2) * conv12_fused_blocks(nframes);
+}
+
 inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2, float *y1,
                                           float *y2, int nframes, float scale, hipStream_t s, int rb) {
     if (nframes <= 0) return hipSuccess;
+    typedef decltype(&conv12_fused_fwd_kernel<false, false, false, false>) Kernel;
+    static const Kernel kernels[16] = {                    // ONE, KEEP, TABLE, EARLY (which a rounded prediction never takes)
+#define GA3C_C12_PAIR(ONE_, KEEP_, TABLE_) \
+    conv12_fused_fwd_kernel<ONE_, KEEP_, TABLE_, false>, conv12_fused_fwd_kernel<ONE_, KEEP_, TABLE_, !ONE_ || KEEP_>
+        GA3C_C12_PAIR(false, false, false), GA3C_C12_PAIR(false, false, true), GA3C_C12_PAIR(false, true, false), GA3C_C12_PAIR(false, true, true),
+        GA3C_C12_PAIR(true, false, false), GA3C_C12_PAIR(true, false, true), GA3C_C12_PAIR(true, true, false), GA3C_C12_PAIR(true, true, true)};
+#undef GA3C_C12_PAIR
     static bool attr_set = false;     // the kernels need more LDS than the default limit
     if (!attr_set) {
-        const void *ks[8] = {(const void *)conv12_fused_fwd_kernel<false, false, false>, (const void *)conv12_fused_fwd_kernel<false, true, false>,
-                             (const void *)conv12_fused_fwd_kernel<true, false, false>, (const void *)conv12_fused_fwd_kernel<true, true, false>,
-                             (const void *)conv12_fused_fwd_kernel<false, false, true>, (const void *)conv12_fused_fwd_kernel<false, true, true>,
-                             (const void *)conv12_fused_fwd_kernel<true, false, true>, (const void *)conv12_fused_fwd_kernel<true, true, true>};
-        for (const void *k : ks) {
-            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C12_LDS_BYTES);
+        for (const Kernel k : kernels) {
+            const hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)C12_LDS_BYTES);
             if (e != hipSuccess) return e;
         }
         attr_set = true;
     }
-    const dim3 grid(conv12_fused_blocks(nframes)), block(512);
-#define GA3C_C12_LAUNCH(ONE_, KEEP_)                                                                                          \
-    do {                                                                                                                      \
-        if (table) ga3c::launch((conv12_fused_fwd_kernel<ONE_, KEEP_, true>), grid, block, C12_LDS_BYTES, s, x, table, frag,  \
-                                b1, b2, y1, y2, nframes, scale, rb);                                                         \
-        else ga3c::launch((conv12_fused_fwd_kernel<ONE_, KEEP_, false>), grid, block, C12_LDS_BYTES, s, x, table, frag, b1,   \
-                          b2, y1, y2, nframes, scale, rb);                                                                   \
-    } while (0)
-    if (rb) { if (y1) GA3C_C12_LAUNCH(true, true); else GA3C_C12_LAUNCH(true, false); }
-    else { if (y1) GA3C_C12_LAUNCH(false, true); else GA3C_C12_LAUNCH(false, false); }
-#undef GA3C_C12_LAUNCH
+    const Kernel kernel = kernels[8 * (rb != 0) + 4 * (y1 != nullptr) + 2 * (table != nullptr) + (conv12_fused_early(nframes, rb != 0, y1 != nullptr) ? 1 : 0)];
+    ga3c::launch(kernel, dim3(conv12_fused_blocks(nframes)), dim3(512), C12_LDS_BYTES, s, x, table, frag, b1, b2, y1, y2, nframes, scale, rb);
     return hipGetLastError();
 }
 

@@ -60,10 +60,11 @@ def test_partial_gradients_added_up_at_the_ends_of_rows_and_rounds(G, F, A, N):
 
 
 # (frames of a batch, frames of the parts that it is predicted in once more): both are cut into the same chunks of k.  Small net, fp32
-# accuracy: 512 and 256 blocks of the fc product, with two and three k-steps in LDS; rounded: 960 and 512, two and three.  Stride-1
+# accuracy: 512 and 256 blocks of the fc product, with two and three k-steps in LDS; 700 frames besides stage early in the fused
+# convolutions, their parts between barriers; rounded: 960 and 512 blocks, two and three steps.  Stride-1
 # member: 512 blocks with three steps (its weights and the activations of 128 frames exceed the Infinity Cache), 512 with two, 256
 # with three; rounded: three.
-@pytest.mark.parametrize("net,math,B,parts", [("small", 0, 512, (256, 256)), ("small", 1, 900, (450, 450)),
+@pytest.mark.parametrize("net,math,B,parts", [("small", 0, 512, (256, 256)), ("small", 0, 700, (450, 250)), ("small", 1, 900, (450, 450)),
                                               ("paper1", 0, 128, (64, 64)), ("paper1", 0, 128, (100, 28)), ("paper1", 1, 128, (64, 64))])
 def test_fc_product_has_the_same_bits_with_two_and_three_steps_in_lds(G, net, math, B, parts):
     import torch
@@ -82,6 +83,31 @@ def test_fc_product_has_the_same_bits_with_two_and_three_steps_in_lds(G, net, ma
         at += n
     torch.cuda.synchronize()
     assert float(whole.abs().max()) > 0 and torch.equal(whole, split)
+    net.close()
+
+
+# two and three frames a block at fp32 accuracy, five and six with rounded operands: staged between barriers and early
+@pytest.mark.parametrize("math,B", [(0, 512), (0, 520), (1, 1280), (1, 1290)])
+def test_training_convolutions_have_the_same_bits_in_batches_of_any_size(G, math, B):
+    import torch
+    A = 6
+    desc = G.SMALL_NET(A)
+    desc.math = math
+    net = G.Ga3c(desc, B, B)
+    net.params_init(7811)
+    frames = torch.from_numpy(synth.uniform_frames(7812, (B, 1, 4, 84, 84))).cuda()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(7813, B, 1, A).items()}
+
+    def convolutions(at, n):
+        print(f"train {n} frames of {B}, math {math}", flush=True)
+        net.train_step(frames[at:at + n], tr["actions"][at:at + n], tr["rewards"][at:at + n], tr["dones"][at:at + n], None, G.HParams(lr=0.0))
+        return [net.train_debug_get(4 + l, torch.empty(n * k, device="cuda")).clone() for l, k in enumerate((16 * 400, 32 * 81))]
+
+    whole = convolutions(0, B)
+    parts = [convolutions(at, min(256, B - at)) for at in range(0, B, 256)]
+    torch.cuda.synchronize()
+    for l in range(2):
+        assert float(whole[l].abs().max()) > 0 and torch.equal(whole[l], torch.cat([p[l] for p in parts])), f"layer {l + 1}"
     net.close()
 
 
