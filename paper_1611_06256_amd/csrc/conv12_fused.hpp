@@ -108,6 +108,10 @@ inline hipError_t launch_conv12_filter_fragments(const float *w1, const float *w
     return hipGetLastError();
 }
 
+// The next frame of a block is staged between two barriers of the block, or early: between the layer-1 wavefronts' own waits, while
+// layer 2 goes on; or either, as the block's number of frames says (the wait is there in any case).
+enum Conv12Stage { C12_BARRIERS, C12_EARLY, C12_EITHER };
+
 // x: [n][4][84][84] bytes, or table: where each frame lies (FramePointer); frag: the three fragment sets; b1 [16], b2 [32];
 // y1: [n][16][400] or nullptr; y2: [n][32][81].  Frames blockIdx.x, + gridDim.x, ...
 // ONE: the reduced-precision variant (operands rounded to bfloat16): only the first
@@ -115,8 +119,8 @@ inline hipError_t launch_conv12_filter_fragments(const float *w1, const float *w
 // only the first plane of the layer-1 output is written and read.
 // KEEP: the layer-1 output is also written to y1 (a template parameter rather than a test of the pointer, so that
 // the stores do not cut the epilogue into a basic block each).
-// EARLY: the next frame is staged between the layer-1 wavefronts' own waits instead of between two barriers of the block.
-template <bool ONE, bool KEEP, bool TABLE, bool EARLY>
+// STAGE: when the next frame is staged (launch_conv12_fused_fwd has the measurements).
+template <bool ONE, bool KEEP, bool TABLE, int STAGE>
 __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t *__restrict__ x,
                                                                   const uint8_t *const *__restrict__ table,
                                                                   const u32x4 *__restrict__ frag,
@@ -124,12 +128,13 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
                                                                   const float *__restrict__ b2, float *__restrict__ y1,
                                                                   float *__restrict__ y2, int nframes, float scale,
                                                                   int rb) {
+    constexpr bool WAIT = STAGE != C12_BARRIERS;
     extern __shared__ __attribute__((aligned(16))) unsigned char c12_smem[];
     const int first = (int)blockIdx.x, grid = (int)gridDim.x;
     constexpr int CHW1 = 4 * 84 * 84, W1 = 84, NPIX1 = 400, OW1 = 20;
     constexpr int NV = CHW1 / 16, VPT = 7;                         // 16-byte vectors of a frame, per layer-1 thread
     constexpr int HW2 = 400, NPIX2 = 81, OW2 = 9, OC2 = 32;
-    __shared__ int l1_read;                                        // EARLY: layer-1 wavefronts that have read their frame, over all frames
+    __shared__ int l1_read;                                        // WAIT: layer-1 wavefronts that have read their frame, over all frames
     __bf16 *xs = (__bf16 *)c12_smem;
     __bf16 *ys = xs + C12_XS;                                      // [2][3][C12_Y1]
     float *exb = (float *)(ys + 2 * 3 * C12_Y1);                   // [2][C12_EX]
@@ -177,6 +182,8 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
 
     const int n = (nframes - first + grid - 1) / grid;             // frames of this block (>= 1)
 
+    const bool early = STAGE == C12_EITHER ? n > (ONE ? 5 : 2) : WAIT;
+
     floatx4 keep[3];                                               // layer 2: my filter tile's sums of the previous frame
 #pragma unroll
     for (int i = 0; i < 3; ++i) keep[i] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -192,7 +199,7 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
         }
     };
     // before the first iteration: the first frame and the layer-1 filter set go to LDS, then everybody takes its filters
-    if (EARLY && tid == 0) l1_read = 0;
+    if (WAIT && tid == 0) l1_read = 0;
     if (layer1) {
         stage_frame();
 #pragma unroll
@@ -224,8 +231,8 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
     }
     for (int it = 0; it <= n + 1; ++it) {
         if (it > 0) {
-            __syncthreads();          // layer 2 has read the planes that layer 1 writes now; EARLY: layer 1's frame is in xs
-            if (!EARLY) {
+            __syncthreads();          // layer 2 has read the planes that layer 1 writes now; early: layer 1's frame is in xs
+            if (!early) {
                 if (layer1 && it < n) stage_frame();
                 __syncthreads();
             }
@@ -317,7 +324,7 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
                         return odd;
                     };
                     floatx4 odd = floatx4{0.f, 0.f, 0.f, 0.f};
-                    if (EARLY) {
+                    if (WAIT) {
                         if (rw == 0) odd = odd_tile();
                         // I have read the frame; what is left to do with it needs no more of it
                         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -325,11 +332,11 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
                     }
 #pragma unroll
                     for (int j = 0; j < 6; ++j) finish(rw + 4 * j, acc[j]);
-                    if (rw == 0) finish(24, EARLY ? odd : odd_tile());
+                    if (rw == 0) finish(24, WAIT ? odd : odd_tile());
                 }
-                // EARLY: the next frame takes its place as soon as the four layer-1 wavefronts have read this one, while layer 2 goes
+                // early: the next frame takes its place as soon as the four layer-1 wavefronts have read this one, while layer 2 goes
                 // on (every one of them arrives here in every such iteration, so the wait ends).
-                if (EARLY && it + 1 < n) {
+                if (WAIT && early && it + 1 < n) {
                     while (__hip_atomic_load(&l1_read, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < 4 * (it + 1)) __builtin_amdgcn_s_sleep(1);
                     stage_frame();
                 }
@@ -401,27 +408,26 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
 
 inline int conv12_fused_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
 
-// Whether the next frame is staged early (barriers / early, us of the launch, medians of three runs).  At fp32 accuracy where a
-// block has more than two frames: 512 frames 14.95 / 14.98, 600: 18.4 / 17.9, 768: 18.6 / 18.4, 1024: 22.8 / 22.6, update of 1025:
-// 25.7 / 25.1, 2560: 50.1 / 48.8.  (One frame a block has nothing to stage, and the wait and the count of the early variant cost it
-// 0.3 us: 128 frames 8.35 / 8.6, 256: 9.4 / 9.7.)  Rounded operands have a sixth of the products for the wait to hide behind; early
-// gains only where layer 1 is stored too and a block has more than five frames: update of 640 frames 13.7 / 14.4, 1025: 17.3 / 17.8,
-// 1280: 20.5 / 20.5, 1400: 22.4 / 22.3, 1750: 25.3 / 24.7, 2560: 39.2 / 36.2; prediction of 1024: 15.1 / 15.5, 2048: 23.5 / 24.2.
-inline bool conv12_fused_early(int nframes, bool one, bool keep) {
-    if (one && !keep) return false;
-    return nframes > (one ? 5 : 2) * conv12_fused_blocks(nframes);
-}
-
+// When the next frame is staged (barriers / early, us of the launch, medians of three runs).
+// Predictions at fp32 accuracy: early where a block has more than two frames, 512 frames 14.95 / 14.98, 600: 18.4 / 17.9, 768: 18.6 /
+// 18.4, 1024: 22.8 / 22.6.  One frame a block has nothing to stage, and the wait and the count cost it 0.3 us (128 frames 8.35 / 8.6,
+// 256: 9.4 / 9.7), so the two are kernels of their own.  Frames from a table need two registers more than there are to stage early, and
+// a launch with scratch memory starts about a microsecond later; with rounded operands there is a sixth of the products for the wait to
+// hide behind (1024: 15.1 / 15.5, 2048: 23.5 / 24.2): barriers.
+// Updates: early in blocks of three frames and more, with rounded operands of six and more, one kernel for both; 1025 frames 25.7 /
+// 25.1, 2560: 50.1 / 48.8; rounded 640: 14.7 / 14.7, 1025: 18.6 / 19.1, 1280: 20.2 / 20.3, 1750: 25.3 / 24.7, 2560: 39.2 / 36.2.
+// (Kernels of their own took 0.3 us less for 40 frames and 0.8 for 640 rounded ones, but the 50 KB of them moved the other kernels
+// of an update in memory, and updates of 640 to 2560 frames took 1 - 2 % longer in kernels whose code was the same.)
 inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2, float *y1,
                                           float *y2, int nframes, float scale, hipStream_t s, int rb) {
     if (nframes <= 0) return hipSuccess;
-    typedef decltype(&conv12_fused_fwd_kernel<false, false, false, false>) Kernel;
-    static const Kernel kernels[16] = {                    // ONE, KEEP, TABLE, EARLY (which a rounded prediction never takes)
-#define GA3C_C12_PAIR(ONE_, KEEP_, TABLE_) \
-    conv12_fused_fwd_kernel<ONE_, KEEP_, TABLE_, false>, conv12_fused_fwd_kernel<ONE_, KEEP_, TABLE_, !ONE_ || KEEP_>
-        GA3C_C12_PAIR(false, false, false), GA3C_C12_PAIR(false, false, true), GA3C_C12_PAIR(false, true, false), GA3C_C12_PAIR(false, true, true),
-        GA3C_C12_PAIR(true, false, false), GA3C_C12_PAIR(true, false, true), GA3C_C12_PAIR(true, true, false), GA3C_C12_PAIR(true, true, true)};
-#undef GA3C_C12_PAIR
+    typedef decltype(&conv12_fused_fwd_kernel<false, false, false, C12_BARRIERS>) Kernel;
+    static const Kernel kernels[9] = {                     // ONE, KEEP, TABLE; the last: predictions staged early
+        conv12_fused_fwd_kernel<false, false, false, C12_BARRIERS>, conv12_fused_fwd_kernel<false, false, true, C12_BARRIERS>,
+        conv12_fused_fwd_kernel<false, true, false, C12_EITHER>, conv12_fused_fwd_kernel<false, true, true, C12_EITHER>,
+        conv12_fused_fwd_kernel<true, false, false, C12_BARRIERS>, conv12_fused_fwd_kernel<true, false, true, C12_BARRIERS>,
+        conv12_fused_fwd_kernel<true, true, false, C12_EITHER>, conv12_fused_fwd_kernel<true, true, true, C12_EITHER>,
+        conv12_fused_fwd_kernel<false, false, false, C12_EARLY>};
     static bool attr_set = false;     // the kernels need more LDS than the default limit
     if (!attr_set) {
         for (const Kernel k : kernels) {
@@ -430,7 +436,8 @@ inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const uint8_t *const
         }
         attr_set = true;
     }
-    const Kernel kernel = kernels[8 * (rb != 0) + 4 * (y1 != nullptr) + 2 * (table != nullptr) + (conv12_fused_early(nframes, rb != 0, y1 != nullptr) ? 1 : 0)];
+    const bool early = !rb && !y1 && !table && nframes > 2 * conv12_fused_blocks(nframes);
+    const Kernel kernel = kernels[early ? 8 : 4 * (rb != 0) + 2 * (y1 != nullptr) + (table != nullptr)];
     ga3c::launch(kernel, dim3(conv12_fused_blocks(nframes)), dim3(512), C12_LDS_BYTES, s, x, table, frag, b1, b2, y1, y2, nframes, scale, rb);
     return hipGetLastError();
 }

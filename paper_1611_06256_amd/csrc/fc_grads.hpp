@@ -250,7 +250,9 @@ __global__ __launch_bounds__(256, 2) void fc_grads_kernel(const FcGradArgs p) {
 // update, one block against one per chunk: larger net (392 tiles) 320 frames 233 / 239, 1280: 503 / 520, rounded to bfloat16 308 /
 // 324; stride-1 member (4624) 640: 3804 / 4022, stride-2 member (256) 945 / 951, stride-3 member (100) 496.5 / 494.5, stride-4
 // member (36) 239 / 234; small net (164) 640: 113.5 / 116.3, 960: 133.6 / 136.2, 1280: 154.9 / 155.9, 2560: 256.8 / 254.0, rounded
-// 640: 90.0 / 92.2, 1280: 124.4 / 121.9.
+// 640: 90.0 / 92.2, 1280: 124.4 / 121.9.  Other layers between the two lines, 960 to 1020 frames (640 rounded): small net with 320 units
+// (205 tiles) 151 / 158 (100 / 104), larger net with 256 and 192 units (196 and 147) 350 / 358 and 344 / 347 (185 / 192, 183 / 186),
+// stride-3 member with 384 units (150) 686 / 689 (566 / 570), stride-4 member with 1024 (144) 352 / 355 (292 / 296); at 2000 frames level.
 inline bool fc_grads_fold(int F, int flat, int B, int terms) {
     const int tiles = (F + 63) / 64 * ((flat + 63) / 64);
     return tiles >= 256 || (tiles >= 128 && B <= (terms == 1 ? 640 : 1024));

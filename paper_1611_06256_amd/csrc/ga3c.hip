@@ -299,7 +299,8 @@ __device__ __forceinline__ void heads_zero_padding(float *wsh, const int t, int 
 // on 40 frames, 40 chunks: the block's loads 7.5 us when every output and every eight chunks were a round of their own).
 // A block runs these kernels' code once and fetches it from memory as it goes, so each way to load is a kernel of its own
 // (LOADS) instead of a branch.
-enum { LOADS_SCALAR = 0, LOADS_VEC8 = 1, LOADS_VEC16 = 2 };      // any shape; 16-byte vectors, 8 or 16 chunks at a time
+// any shape; 16-byte vectors, of at most 8 chunks and of more (16 at a time; heads_train_kernel takes 28 or 20)
+enum { LOADS_SCALAR = 0, LOADS_VEC8 = 1, LOADS_VEC16 = 2 };
 inline int heads_loads(int F, int nz, const void *ws, const void *fcb, const void *h, const void *Wp) {
     if (F % 4 != 0 || !ws || (((uintptr_t)ws | (uintptr_t)fcb | (uintptr_t)h | (uintptr_t)Wp) & 15) != 0) return LOADS_SCALAR;
     return nz <= 8 ? LOADS_VEC8 : LOADS_VEC16;
@@ -1258,7 +1259,11 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
     heads_zero_padding<NT>(wsh, tid, F, WP, A1);
     const int nw = A1 * F;
     constexpr bool vec4 = LOADS != LOADS_SCALAR;
-    if (vec4) heads_load_vec4<NT, NF, LOADS == LOADS_VEC8 ? 8 : VK == 2 ? 28 : 20, VK == 2 ? 1 : 2>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+    // Outputs per thread and round: a block of 512 threads has one each of up to 256 units, two of 512.  Chunks per round: with one
+    // output as many as the 27 that the small net's updates of at most 320 frames leave, in whole fours; with two outputs 28 would be
+    // 224 registers of the 256 that eight wavefronts leave each, 20 are 160.
+    constexpr int IP = VK == 2 ? 1 : 2, CH = LOADS == LOADS_VEC8 ? 8 : VK == 2 ? 28 : 20;
+    if (vec4) heads_load_vec4<NT, NF, CH, IP>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
     for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * NT) {
         float wv[24];
 #pragma unroll
@@ -2717,9 +2722,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             q.M = B; q.N = c->flat; q.K = F; q.kchunk = (F + GEMM_BK - 1) / GEMM_BK * GEMM_BK; q.nz = 1;
             q.A = c->dh; q.lda = F; q.B = wfc; q.ldb = c->flat;
             q.C = c->dact[c->nconv - 1]; q.ldc = c->flat; q.aux = xfc;
-            // What fc_grads.hpp does not take (layers that are not multiples of 32 and 64).  The input gradient's tile is 64x64 as
-            // long as there is one tile per compute unit at most, 128x64 above that: fewer tiles leave units idle, more read their
-            // operands twice.  64x64 against 128x64 on layers of both kernels, us of the launch (tiles of 64x64): small net
+            // What fc_grads.hpp does not take (units that are not a multiple of 64, columns that are not one of 32).  The input
+            // gradient's tile is 64x64 as long as there is one tile per compute unit at most, 128x64 above that: fewer tiles leave
+            // units idle, more read their operands twice.  64x64 against 128x64 on layers of both kernels, us of the launch (tiles of 64x64): small net
             // 160 frames 15.9 / 18.7 (123), 320: 15.0 / 17.9 (205), 480: 19.8 / 19.0 (328), 2560: 63.5 / 57.2; larger net 320: 28.3 /
             // 30.0 (245), 480: 37.9 / 35.8 (392), 1280: 74.1 / 66.9; stride-4 member 960: 13.1 / 16.9 (135); stride-2 member 320: 20.3
             // / 19.7 (320); stride-1 member 80: 294 / 286 (578).
