@@ -22,7 +22,7 @@
 // MFMA are 8 consecutive filters of one pixel: one 16-byte LDS read per term.
 // The pixel pitch (lds_row_units) and a padded grid as wide as the phase grid spread
 // 16 pixels of a tile over all banks (both gradients of the layer at 1280 frames of the
-// larger net 104.0 -> 94.8 us, at 2560 of the small one 57.2 -> 54.2, with the rows of
+// larger net 104.0 -> 94.8 us, at 2560 of the small one 60.2 -> 57.6, with the rows of
 // the weight gradient's operands at such a pitch too).  The sub-filters of a wavefront's phase stay in registers as split
 // fragments for the whole launch.  A block can take them ready-made (`wfrag`:
 // the register image of every wavefront, which the kernel that updates the

@@ -13,7 +13,7 @@
 // three blocks share a compute unit (48 KB each): MFMA 29 - 43 %, vector instructions 19 - 27 %, no bank conflicts; the rest is
 // waiting at the one barrier of a k-step (two blocks with two steps ahead: 64 instead of 57 us).  Rows of 128 units or frames
 // in blocks of eight wavefronts were level.  us of the launch before and after, and of the reduction behind it where dW needs no
-// partial sums any more: small net 40 frames 14.6 -> 8.0, 640: 20.0 -> 16.0 (10.1 -> 8.3), 2560: 54.8 -> 45.8; larger net 1280:
+// partial sums any more: small net 40 frames 14.6 -> 8.0, 640: 20.0 -> 16.0 (10.1 -> 8.3), 2560: 55.2 -> 47.7; larger net 1280:
 // 67.0 -> 49.8 (34.8 -> 23.5), its operands rounded to bfloat16 38.8 -> 23.4 (36.7 -> 24.7); 640 x 1024 x 18496: 430 -> 250 (125
 // -> 35).
 #pragma once
