@@ -54,7 +54,7 @@ constexpr int band_pitch() { return 6 * C + 16; }
 // ---------------------------------------------------------------- fragments --
 
 // One tensor's fragments: n threads write three vectors (the terms) each, at dst[(i / 64 * 3 + term) * 64 + i % 64].
-enum { FRAG_CONV = 0, FRAG_BYTES8 = 1 };
+enum { FRAG_CONV = 0, FRAG_BYTES8 = 1, FRAG_DGRAD = 2 };
 struct FragJob {
     const float *w;          // [OC][C][KS][KS]
     u32x4 *dst;
@@ -79,6 +79,11 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
         const int kb = blk % kbs, ot = blk / kbs, tap = kb / cgs, c0 = (kb % cgs) * 32 + 8 * g;
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = j.w[((size_t)(ot * 16 + l16) * j.C + c0 + e) * j.KS * j.KS + tap];
+    } else if (j.kind == FRAG_DGRAD) {       // 4x4, stride 2: [channel tile][ry][rx][(a, e, 32 filters)]: row = channel, k = filter
+        const int ogs = j.OC / 32, kb = blk % (4 * ogs), ph = blk / (4 * ogs), tap = kb / ogs, o0 = (kb % ogs) * 32 + 8 * g;
+        const int u = (ph >> 1 & 1) + 2 * (tap >> 1), v = (ph & 1) + 2 * (tap & 1), c = (ph >> 2) * 16 + l16;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = j.w[((size_t)(o0 + e) * j.C + c) * 16 + u * 4 + v];
     } else {                                 // byte layer, 4 planes, 8x8: [filter tile][u]: row = filter, k = (v, plane)
         const int u = blk % 8, ot = blk / 8;
 #pragma unroll

@@ -1,6 +1,7 @@
 // The layers of conv_band.hpp and conv_bytes.hpp on the fp32 matrix instruction,
 // for maps of any size (the 4x4 stride-2 layer on 32 channels, and the 8x8 byte
-// layer of any stride): forward pass, input gradient and weight gradient.
+// layer of any stride): forward pass, and the byte layer's weight gradient for
+// the strides and filter counts that conv_band_grads.hpp does not take.
 //
 // Every sum is formed by the same instructions in the same order as in
 // gemm_mfma.hpp (v_mfma_f32_16x16x4_f32, product t of a group of 16 k sums
@@ -11,8 +12,7 @@
 // and a map of millions of pixels has enough of those to move the gradient of a
 // filter by 1e-4 of itself.  The gradients decide nothing: an input gradient's
 // mask is the stored activation, and a weight gradient feeds nothing within the
-// update.  Keeping their order of sums too buys equal bits, not accuracy, and
-// costs the rate of the bf16 instruction.
+// update (conv_band_grads.hpp has them on the bf16 instruction).
 //
 // What bounds them is the instruction: 146 - 150 TFLOP/s on this chip.  With k
 // in the filter's own order (c, u, v), the four k of a lane are four columns of
@@ -308,172 +308,13 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_f32_fwd_kernel(const uint8_
     }
 }
 
-// ----------------------------------------------------------- input gradient --
-// dX[c][y][x] = [xin[c][y][x] > 0] * sum_{oc,a,e} dY[oc][iy - a][ix - e] W[oc][c][ry + 2a][rx + 2e],  y = 2 iy + ry,
-// x = 2 ix + rx, with k in the order (oc, a, e): a group of 16 is four filters, the four products of a group are the four
-// (a, e).  The zero-padded dY sits in LDS as it is in memory; the four phases (ry, rx) of 16 channels share one fetch of
-// it, and a lane's 16 taps of (filter, channel) are 64 contiguous bytes of the weights.  Wavefront = (channel tile, half
-// of the pixel tiles), two pixel tiles at a time.
-// Bound by the instruction (28.7 GFLOP of conv2 at 640 frames of 77x77: 200 us at 144 TFLOP/s).
-template <int OC>
-constexpr int band_f32_dgrad_maxk() { return 64 / OC; }      // values of a filter's plane in flight per thread
-
-template <int OC, bool RB>
-__global__ __launch_bounds__(256, 2) void conv_band_f32_dgrad_kernel(const float *__restrict__ dy, const float *__restrict__ w,
-                                                                     const float *__restrict__ xin, float *__restrict__ dx,
-                                                                     int nframes, int pitch, const BandGeom b) {
-    constexpr int C = 32, MAXK = band_f32_dgrad_maxk<OC>(), KB = OC / 4;
-    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
-    float *ys = (float *)band_smem;                   // [oc][frame][row][PW], `pitch` floats per filter
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, g = lane >> 4;
-    const int ct = wave & 1, pg = wave >> 1;
-    const int HW = b.H * b.W, NPIX = b.OH * b.OW, GW = b.cols, PW = GW + 1, RL = b.R + 1;
-    const int chunk = RL * b.OW, plane = b.F * chunk;
-
-    for (int e = tid; e < OC * pitch; e += 256) ys[e] = 0.f;      // columns outside dY stay zero
-
-    int src[MAXK], dst[MAXK], urow[MAXK];
-#pragma unroll
-    for (int k = 0; k < MAXK; ++k) {
-        const int e = min(tid + 256 * k, plane - 1), f = e / chunk, r = e % chunk / b.OW, xc = e % b.OW;
-        src[k] = f * OC * NPIX + xc;
-        urow[k] = r - 1;
-        dst[k] = (f * RL + r) * PW + xc + 1;
-    }
-    const size_t total = (size_t)nframes * OC * NPIX;
-    float pre[OC][MAXK];
-    auto fetch = [&](int item) {
-        const int f0 = (item / b.nb) * b.F, g0 = (item % b.nb) * b.R;
-        const size_t base = (size_t)f0 * OC * NPIX;
-        const size_t left = total - base - (size_t)(OC - 1) * NPIX - 1;
-        const uint32_t lim = left > 0x3fffffff ? 0x3fffffffu : (uint32_t)left;
-#pragma unroll
-        for (int k = 0; k < MAXK; ++k)
-            if (256 * k < plane) {
-                const int yr = min(max(g0 + urow[k], 0), b.OH - 1);
-                const uint32_t off = 4u * min((uint32_t)(src[k] + yr * b.OW), lim);
-#pragma unroll
-                for (int c = 0; c < OC; ++c) pre[c][k] = *(const float *)((const char *)(dy + base + (size_t)c * NPIX) + off);
-            }
-    };
-    int item = blockIdx.x;
-    fetch(min(item, b.items - 1));
-    const float *wl = w + ((size_t)g * C + ct * 16 + l16) * 16;      // my taps of filter g
-
-    for (; item < b.items; item += gridDim.x) {
-        const int f0 = (item / b.nb) * b.F, g0 = (item % b.nb) * b.R;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < MAXK; ++k)
-            if (tid + 256 * k < plane) {
-                const bool in = (unsigned)(g0 + urow[k]) < (unsigned)b.OH;      // else a row above or below dY
-#pragma unroll
-                for (int c = 0; c < OC; ++c) ys[c * pitch + dst[k]] = in ? (RB ? bf16_rne(pre[c][k]) : pre[c][k]) : 0.f;
-            }
-        __syncthreads();
-        fetch(min(item + (int)gridDim.x, b.items - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        const int cnt = b.F * b.R * GW, ntile = (cnt + 15) / 16;
-        auto pass = [&](auto nc, int t0) {
-            constexpr int N = decltype(nc)::value;
-            const float *base[N];
-            size_t out[N];
-            bool in[N][2], two[N];
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                uint32_t p = (uint32_t)((t0 + 2 * n) * 16 + l16), f, rem, i, j;
-                bool ok = (int)p < cnt;
-                if (!ok) p = 0;
-                b.dFR.divmod(p, f, rem);
-                b.dC.divmod(rem, i, j);
-                base[n] = ys + g * pitch + ((int)f * RL + (int)i + 1) * PW + (int)j + 1;
-                const int yr = 2 * (g0 + (int)i);
-                ok = ok && f0 + (int)f < nframes;
-                in[n][0] = ok && yr < b.H;
-                in[n][1] = ok && yr + 1 < b.H;
-                two[n] = 2 * (int)j + 1 < b.W;
-                out[n] = in[n][0] ? ((size_t)(f0 + (int)f) * C + ct * 16 + 4 * g) * HW + yr * b.W + 2 * (int)j : 0;
-            }
-            floatx4 acc[N][2][2];
-#pragma unroll
-            for (int n = 0; n < N; ++n)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) acc[n][q >> 1][q & 1] = floatx4{0.f, 0.f, 0.f, 0.f};
-            float4 wv[2][4];
-            auto read_w = [&](int kb, float4 (&d)[4]) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    d[u] = ((const float4 *)(wl + (size_t)kb * 4 * C * 16))[u];
-                    if (RB) d[u] = bf16_rne(d[u]);
-                }
-            };
-            float yv[2][N][4];
-            auto read_y = [&](int kb, float (&d)[N][4]) {
-#pragma unroll
-                for (int n = 0; n < N; ++n)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) d[n][t] = base[n][kb * 4 * pitch - (t >> 1) * PW - (t & 1)];
-            };
-            read_w(0, wv[0]);
-            read_y(0, yv[0]);
-#pragma unroll 2
-            for (int kb = 0; kb < KB; ++kb) {
-                const int kn = min(kb + 1, KB - 1);
-                read_w(kn, wv[(kb + 1) & 1]);
-                read_y(kn, yv[(kb + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int ry = 0; ry < 2; ++ry) {
-                        const float4 q = wv[kb & 1][ry + 2 * (t >> 1)];
-#pragma unroll
-                        for (int rx = 0; rx < 2; ++rx) {
-                            const float we = t & 1 ? (rx ? q.w : q.z) : (rx ? q.y : q.x);
-#pragma unroll
-                            for (int n = 0; n < N; ++n)
-                                acc[n][ry][rx] = __builtin_amdgcn_mfma_f32_16x16x4f32(we, yv[kb & 1][n][t], acc[n][ry][rx], 0, 0, 0);
-                        }
-                    }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                f32x2_dw mk[2][4];
-                // the last column of an odd map is the second of the pair in front of it
-#pragma unroll
-                for (int ry = 0; ry < 2; ++ry)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        mk[ry][r] = *(const f32x2_dw *)(xin + out[n] + (in[n][ry] ? ry * b.W : 0) + (size_t)r * HW - (in[n][0] && !two[n] ? 1 : 0));
-#pragma unroll
-                for (int ry = 0; ry < 2; ++ry)
-                    if (in[n][ry]) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            float *o = dx + out[n] + ry * b.W + (size_t)r * HW;
-                            const f32x2_dw m = mk[ry][r];
-                            if (two[n]) *(f32x2_dw *)o = f32x2_dw{m.x > 0.f ? acc[n][ry][0][r] : 0.f, m.y > 0.f ? acc[n][ry][1][r] : 0.f};
-                            else o[0] = m.y > 0.f ? acc[n][ry][0][r] : 0.f;
-                        }
-                    }
-            }
-        };
-        int t = pg, left = (ntile - pg + 1) / 2;
-        for (; left >= 2; left -= 2, t += 4) pass(std::integral_constant<int, 2>{}, t);
-        if (left == 1) pass(std::integral_constant<int, 1>{}, t);
-    }
-}
-
 // ---------------------------------------------------------- weight gradient --
 // dW[oc][k] = scale * sum over the pixels P of all frames of dY[P][oc] x[P][tap k], db[oc] = sum of dY[P][oc], in the chunks of
-// pixels and the order of problems.hpp's ConvWgradP: part[chunk][OC][K + 1].  TIn bytes: 8x8 filters over four
-// planes, any stride; floats: 4x4, stride 2, 32 channels.
+// pixels and the order of problems.hpp's ConvWgradP: part[chunk][OC][K + 1].  8x8 filters over four planes of bytes, any
+// stride.
 //
-// A chunk is one long chain of sums, so the parallelism left is chunks x columns: a wavefront keeps one tile of 16 taps (a
-// channel of the 4x4 filters, two rows of an 8x8 plane) of all filters.  The instruction adds its four products one after
+// A chunk is one long chain of sums, so the parallelism left is chunks x columns: a wavefront keeps one tile of 16 taps (two
+// rows of a plane's 8x8) of all filters.  The instruction adds its four products one after
 // the other, so the column of the bias gradient, whose products are dY itself, is formed with plain additions in that order,
 // by one wavefront of a chunk on the side (a wavefront of its own would end last: one chain of dependent instructions).
 // The chunk goes by in steps of KT pixels, whose dY lies in LDS as [filter][pixel] and whose input rows as they are in memory:
@@ -481,9 +322,9 @@ __global__ __launch_bounds__(256, 2) void conv_band_f32_dgrad_kernel(const float
 // run of pixels, also across frames, and a table gives each pixel's place in them.  The next step's values go from memory
 // straight to the other half of the LDS buffers (no registers hold them).
 // Bound by the instruction next to the address and byte-conversion instructions (8 per 8 products of 32 cycles), and by whole
-// wavefronts per SIMD: conv1 at 640 frames of 84x84, stride 1, is 2736 tiles of 161 us on 1024 SIMDs (483 us; 776 measured,
-// 4 ms for the gather kernel).
-template <class TIn> constexpr int f32_wgrad_kt() { return sizeof(TIn) == 1 ? 128 : 64; }
+// wavefronts per SIMD.
+constexpr int F32_WGRAD_KT = 128, F32_WGRAD_WAVES = 4;
+constexpr int F32_WGRAD_MAXX = 13;                // dwords of input per thread and step
 struct F32WgradGeom {
     int nframes, C, H, W, S, OH, OW;
     int K, kchunk, nz;       // pixels in all, pixels per chunk, chunks
@@ -494,29 +335,24 @@ struct F32WgradGeom {
     FastDiv dNPIX, dOW;
     float scale;
 };
-template <class TIn> constexpr int f32_wgrad_waves() { return sizeof(TIn) == 1 ? 4 : 8; }
-template <class TIn> constexpr int f32_wgrad_maxx() { return 13; }      // dwords of input per thread and step
 
-template <class TIn, int OC, bool RB>
-__global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 : 4) void conv_f32_wgrad_kernel(
-    const TIn *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part, const F32WgradGeom b) {
-    constexpr bool BYTE = sizeof(TIn) == 1;
-    constexpr int OT = OC / 16, KS = BYTE ? 8 : 4, KT = f32_wgrad_kt<TIn>(), AP = KT + 4, NW = f32_wgrad_waves<TIn>(), NT = 64 * NW, MAXX = f32_wgrad_maxx<TIn>();
-    constexpr int NG = KT / 16, ESZ = (int)sizeof(TIn);
+template <int OC, bool RB>
+__global__ __launch_bounds__(64 * F32_WGRAD_WAVES, 5) void conv_f32_wgrad_kernel(const uint8_t *__restrict__ x, const float *__restrict__ dy,
+                                                                                 float *__restrict__ part, const F32WgradGeom b) {
+    constexpr int OT = OC / 16, KS = 8, KT = F32_WGRAD_KT, AP = KT + 4, NW = F32_WGRAD_WAVES, NT = 64 * NW, MAXX = F32_WGRAD_MAXX;
+    constexpr int NG = KT / 16;
     // each half: dY [OC][AP] floats, [KT] byte offsets of the pixels' windows, the input [row][channel][W]
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
     constexpr int OTAB = OC * AP * 4, XS = OTAB + KT * 4;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    const int NPIX = b.OH * b.OW, HW = b.H * b.W, ncol = BYTE ? 16 : b.C;
+    const int NPIX = b.OH * b.OW, HW = b.H * b.W;
     // an XCD takes every eighth chunk, the blocks of a chunk next to each other: its dY then comes from the L2
     const int local = (int)blockIdx.x / 8, by = local % b.ny, z = local / b.ny * 8 + (int)blockIdx.x % 8;
     if (z >= b.nz) return;
     const int q = by * NW + wave;
-    // the channels this block's tiles need, in dwords
-    const int c0 = BYTE ? 0 : by * NW, nch = BYTE ? 4 : NW;
-    const int UW = b.W * ESZ / 4, UR = nch * UW, NU = b.rows * UR, ROW = nch * b.W * ESZ;      // dwords of a row of a channel and of all; bytes
+    const int UW = b.W / 4, UR = 4 * UW, NU = b.rows * UR, ROW = 4 * b.W;      // dwords of a row of a plane and of all; bytes
     const int kbeg = z * b.kchunk, kend = min(b.K, kbeg + b.kchunk);
 
     uint32_t xoff[MAXX];
@@ -525,10 +361,10 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
     for (int i = 0; i < MAXX; ++i) {
         const int u = min(tid + NT * i, NU - 1), rem = u % UR;
         xrow[i] = u / UR;
-        xoff[i] = (uint32_t)((c0 * HW + rem / UW * HW + xrow[i] * b.W) * ESZ + 4 * (rem % UW));
+        xoff[i] = (uint32_t)(rem / UW * HW + xrow[i] * b.W + 4 * (rem % UW));
     }
-    const uint32_t jump = (uint32_t)((b.C * b.H - b.RF) * b.W * ESZ);         // over the rows between two frames' channels
-    const size_t xbytes = (size_t)b.nframes * b.C * HW * ESZ;
+    const uint32_t jump = (uint32_t)((b.C * b.H - b.RF) * b.W);         // over the rows between two frames' channels
+    const size_t xbytes = (size_t)b.nframes * b.C * HW;
     auto fetch = [&](int k0, unsigned char *half) {
         const uint32_t lds = lds_address(half);
         uint32_t f0, p0, f1, p1;
@@ -537,7 +373,7 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
         const int r0 = (int)b.dOW.div(p0) * b.S;
         const int rows = (int)(f1 - f0) * b.RF + (int)b.dOW.div(p1) * b.S + KS - r0;      // that this step's windows touch
         const int nu = rows * UR;
-        const size_t xb = (size_t)f0 * b.C * HW * ESZ + (size_t)r0 * b.W * ESZ;
+        const size_t xb = (size_t)f0 * b.C * HW + (size_t)r0 * b.W;
         const uint32_t lim = xbytes - xb > 0x7fffffff ? 0x7fffffffu : (uint32_t)(xbytes - xb) - 4u;
 #pragma unroll
         for (int i = 0; i < MAXX; ++i)
@@ -559,7 +395,7 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
                 if (OC % NW == 0 || m + wave < OC) load_dword_to_lds(src + (size_t)(m + wave) * NPIX, off, lds + ((m + wave) * AP + h) * 4);
             if (wave == 0) {
                 b.dOW.divmod(p, i, j);
-                ((int *)(half + OTAB))[h + lane] = k < kend ? ((int)(f - f0) * b.RF + (int)i * b.S - r0) * ROW + (int)j * b.S * ESZ : 0;
+                ((int *)(half + OTAB))[h + lane] = k < kend ? ((int)(f - f0) * b.RF + (int)i * b.S - r0) * ROW + (int)j * b.S : 0;
             }
         }
     };
@@ -570,8 +406,7 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
 #pragma unroll
     for (int m = 0; m < OT; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
     // my tap's place behind a window's first value
-    const int xl = BYTE ? (2 * (q % 4) + (l16 >> 3)) * ROW + (q / 4) * b.W + (l16 & 7)
-                        : (l16 >> 2) * ROW + ((q - c0) * b.W + (l16 & 3)) * 4;
+    const int xl = (2 * (q % 4) + (l16 >> 3)) * ROW + (q / 4) * b.W + (l16 & 7);
     int at = 0;
     for (int k0 = kbeg; k0 < kend; k0 += KT, at ^= 1) {
         unsigned char *half = band_smem + at * b.stage;
@@ -595,13 +430,7 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
         const int4 *ol = (const int4 *)(half + OTAB) + g;
         const unsigned char *xb = half + XS + xl;
         uint32_t xr[2][4];
-        auto read_x = [&](const int4 o, uint32_t (&d)[4]) {
-            if (BYTE) { d[0] = xb[o.x]; d[1] = xb[o.y]; d[2] = xb[o.z]; d[3] = xb[o.w]; }
-            else {
-                d[0] = *(const uint32_t *)(xb + o.x); d[1] = *(const uint32_t *)(xb + o.y);
-                d[2] = *(const uint32_t *)(xb + o.z); d[3] = *(const uint32_t *)(xb + o.w);
-            }
-        };
+        auto read_x = [&](const int4 o, uint32_t (&d)[4]) { d[0] = xb[o.x]; d[1] = xb[o.y]; d[2] = xb[o.z]; d[3] = xb[o.w]; };
         int4 o = ol[0];
         float4 av[2][OT];
         read_x(o, xr[0]);
@@ -617,8 +446,7 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                const uint32_t v = xr[grp & 1][t];
-                const float xv = BYTE ? (float)v : RB ? bf16_rne(__uint_as_float(v)) : __uint_as_float(v);
+                const float xv = (float)xr[grp & 1][t];
 #pragma unroll
                 for (int m = 0; m < OT; ++m) {
                     const float4 a = av[grp & 1][m];
@@ -644,7 +472,7 @@ __global__ __launch_bounds__(64 * f32_wgrad_waves<TIn>(), sizeof(TIn) == 1 ? 5 :
             }
         }
     }
-    const int K1 = 16 * ncol + 1;
+    constexpr int K1 = 257;
     float *pb = part + (size_t)z * OC * K1;
 #pragma unroll
     for (int m = 0; m < OT; ++m)
@@ -696,92 +524,53 @@ inline hipError_t launch_conv_bytes_f32_fwd(const uint8_t *x, const float *w, co
     return rb ? launch_conv_bytes_f32_fwd1<OC, true>(x, w, bias, y, n, H, S, scale, s) : launch_conv_bytes_f32_fwd1<OC, false>(x, w, bias, y, n, H, S, scale, s);
 }
 
-template <int OC>
-inline int band_f32_dgrad_pitch(const BandGeom &b) {      // floats per filter: the four filters of a group on different banks
-    const int n = b.F * (b.R + 1) * (b.cols + 1);
-    return (n + 47) / 64 * 64 + 16;
-}
-template <int OC>
-inline bool band_f32_dgrad_geom(BandGeom &b, int nframes) {
-    const int GW = (b.W + 1) / 2;
-    return band_split(b, nframes, (b.H + 1) / 2, GW,
-                      [&](int F, int R) { return (F * (R + 1) * (GW + 1) + 63) * OC * 4 <= BAND_F32_LDS ? 0 : 2 * BAND_LDS; },
-                      [&](int F, int R) { return F * (R + 1) * b.OW <= 256 * band_f32_dgrad_maxk<OC>() ? 0 : 1 << 30; }, BAND_MAXU,
-                      2 * BAND_CUS);
-}
-template <int OC, bool RB>
-inline hipError_t launch_conv_band_f32_dgrad1(const float *dy, const float *w, const float *xin, float *dx, int n, int H, int W, hipStream_t s) {
-    BandGeom b = band_geom(H, W);
-    if (!band_f32_dgrad_geom<OC>(b, n)) return hipErrorInvalidValue;
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_f32_dgrad_kernel<OC, RB>, attr);
-    if (e != hipSuccess) return e;
-    const int pitch = band_f32_dgrad_pitch<OC>(b);
-    ga3c::launch((conv_band_f32_dgrad_kernel<OC, RB>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), OC * pitch * 4, s, dy, w, xin, dx, n,
-                 pitch, b);
-    return hipGetLastError();
-}
-// dy [n][OC][OH][OW] -> dx [n][32][H][W], masked by xin > 0; w [OC][32][4][4], 16-byte aligned.
-template <int OC>
-inline hipError_t launch_conv_band_f32_dgrad(const float *dy, const float *w, const float *xin, float *dx, int n, int H, int W, hipStream_t s, int rb) {
-    if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_f32_dgrad1<OC, true>(dy, w, xin, dx, n, H, W, s) : launch_conv_band_f32_dgrad1<OC, false>(dy, w, xin, dx, n, H, W, s);
-}
-
-// Whether the forward pass and the input gradient can run maps of H x W.
+// Whether the forward pass can run maps of H x W.
 template <int C>
 inline bool band_f32_ok(int H, int W) {
-    BandGeom b = band_geom(H, W), c = b, d = b;
-    return band_f32_geom<C>(b, 1) && band_f32_dgrad_geom<32>(c, 1) && band_f32_dgrad_geom<64>(d, 1);
+    BandGeom b = band_geom(H, W);
+    return band_f32_geom<C>(b, 1);
 }
 
 // b.rows: rows of input that a step can touch; it covers up to R output rows and d frame boundaries.
-template <class TIn>
 inline F32WgradGeom f32_wgrad_geom(int C, int H, int W, int S, int n, int kchunk, float scale) {
-    constexpr int KS = sizeof(TIn) == 1 ? 8 : 4;
+    constexpr int KS = 8;
     F32WgradGeom b{};
     b.nframes = n; b.C = C; b.H = H; b.W = W; b.S = S; b.OH = (H - KS) / S + 1; b.OW = (W - KS) / S + 1;
     b.K = n * b.OH * b.OW; b.kchunk = kchunk; b.scale = scale;
     b.RF = S * (b.OH - 1) + KS;
-    const int R = (f32_wgrad_kt<TIn>() - 2) / b.OW + 2;
+    const int R = (F32_WGRAD_KT - 2) / b.OW + 2;
     b.d = (R - 2) / b.OH + 1;
     b.rows = S * (R - 1) + KS + b.d * std::max(0, KS - S);
     b.dNPIX = FastDiv((uint32_t)(b.OH * b.OW)); b.dOW = FastDiv((uint32_t)b.OW);
     return b;
 }
-template <class TIn>
 inline int f32_wgrad_stage(const F32WgradGeom &b, int OC) {      // the input's part rounded up to whole wavefronts
-    const int x = (sizeof(TIn) == 1 ? 4 : f32_wgrad_waves<TIn>()) * b.rows * b.W * (int)sizeof(TIn);
-    return (OC * (f32_wgrad_kt<TIn>() + 4) + f32_wgrad_kt<TIn>()) * 4 + (x + 255) / 256 * 256;
+    return (OC * (F32_WGRAD_KT + 4) + F32_WGRAD_KT) * 4 + (4 * b.rows * b.W + 255) / 256 * 256;
 }
 // Whether a step fits the threads and half of a compute unit's LDS.
-template <class TIn>
 inline bool f32_wgrad_ok(int C, int H, int W, int S, int OC) {
-    const F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, 1, f32_wgrad_kt<TIn>(), 1.f);
-    const int nch = sizeof(TIn) == 1 ? 4 : f32_wgrad_waves<TIn>();
-    return nch * b.rows * (W * (int)sizeof(TIn) / 4) <= 64 * f32_wgrad_waves<TIn>() * f32_wgrad_maxx<TIn>() &&
-           2 * f32_wgrad_stage<TIn>(b, OC) <= BAND_F32_LDS;
+    const F32WgradGeom b = f32_wgrad_geom(C, H, W, S, 1, F32_WGRAD_KT, 1.f);
+    return b.rows * W <= 64 * F32_WGRAD_WAVES * F32_WGRAD_MAXX && 2 * f32_wgrad_stage(b, OC) <= BAND_F32_LDS;
 }
 // part [nz][OC][K + 1], nz chunks of kchunk pixels (a multiple of 16).
-template <class TIn, int OC>
-inline hipError_t launch_conv_f32_wgrad(const TIn *x, const float *dy, float *part, int n, int C, int H, int W, int S, int nz, int kchunk, float scale,
+template <int OC>
+inline hipError_t launch_conv_f32_wgrad(const uint8_t *x, const float *dy, float *part, int n, int C, int H, int W, int S, int nz, int kchunk, float scale,
                                         hipStream_t s, int rb) {
     if (n <= 0) return hipSuccess;
-    F32WgradGeom b = f32_wgrad_geom<TIn>(C, H, W, S, n, kchunk, scale);
-    b.stage = f32_wgrad_stage<TIn>(b, OC);
-    constexpr int NW = f32_wgrad_waves<TIn>();
-    b.nz = nz; b.ny = (sizeof(TIn) == 1 ? 16 : C) / NW;
-    const dim3 grid((nz + 7) / 8 * 8 * b.ny), block(64 * NW);
+    F32WgradGeom b = f32_wgrad_geom(C, H, W, S, n, kchunk, scale);
+    b.stage = f32_wgrad_stage(b, OC);
+    b.nz = nz; b.ny = 16 / F32_WGRAD_WAVES;
+    const dim3 grid((nz + 7) / 8 * 8 * b.ny), block(64 * F32_WGRAD_WAVES);
     const int lds = 2 * b.stage;
     static bool attr0 = false, attr1 = false;
     if (rb) {
-        const hipError_t e = band_allow_lds(conv_f32_wgrad_kernel<TIn, OC, true>, attr1);
+        const hipError_t e = band_allow_lds(conv_f32_wgrad_kernel<OC, true>, attr1);
         if (e != hipSuccess) return e;
-        ga3c::launch((conv_f32_wgrad_kernel<TIn, OC, true>), grid, block, lds, s, x, dy, part, b);
+        ga3c::launch((conv_f32_wgrad_kernel<OC, true>), grid, block, lds, s, x, dy, part, b);
     } else {
-        const hipError_t e = band_allow_lds(conv_f32_wgrad_kernel<TIn, OC, false>, attr0);
+        const hipError_t e = band_allow_lds(conv_f32_wgrad_kernel<OC, false>, attr0);
         if (e != hipSuccess) return e;
-        ga3c::launch((conv_f32_wgrad_kernel<TIn, OC, false>), grid, block, lds, s, x, dy, part, b);
+        ga3c::launch((conv_f32_wgrad_kernel<OC, false>), grid, block, lds, s, x, dy, part, b);
     }
     return hipGetLastError();
 }

@@ -35,6 +35,7 @@
 #include "conv_band.hpp"
 #include "conv_bytes.hpp"
 #include "conv_band_f32.hpp"
+#include "conv_band_grads.hpp"
 
 using namespace ga3c;
 
@@ -164,7 +165,7 @@ struct ga3c_ctx {
     // layers on the any-size kernels of conv_band.hpp and conv_bytes.hpp: which ones, where their fragments sit in the
     // buffer of each parameter copy (in vectors), and the buffers (nullptr where no layer needs one)
     bool band[GA3C_MAX_CONV];
-    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_vecs;
+    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_dgrad[GA3C_MAX_CONV], bfrag_vecs;
     u32x4 *bfrag[2];
     ga3c::FcPlanes fcw[2];        // fc weights of each parameter copy as operands of the forward product (w == nullptr: none); kept
                                   // current by whoever writes the copy
@@ -1957,7 +1958,7 @@ int alloc_work(Work &w, const ga3c_ctx *c, int cap) {
     w.cap = cap;
     if (cap <= 0) return GA3C_OK;
     for (int l = 0; l < c->nconv; ++l)
-        HIP_TRY(hipMalloc(&w.act[l], sizeof(float) * (size_t)cap * c->geom[l].OC * c->geom[l].OHW));
+        HIP_TRY(hipMalloc(&w.act[l], sizeof(float) * ((size_t)cap * c->geom[l].OC * c->geom[l].OHW + BAND_SLACK)));
     HIP_TRY(hipMalloc(&w.h, sizeof(float) * (size_t)cap * c->F));
     HIP_TRY(hipMalloc(&w.zv, sizeof(float) * (size_t)cap * (c->A + 1)));
     return GA3C_OK;
@@ -2032,7 +2033,8 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
         for (int l = 0; l < c->nconv; ++l) {
             if (!c->band[l]) continue;
             const ConvGeom &g = c->geom[l];
-            add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
+            if (!c->rb) add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
+            if (l > 0 && c->max_train > 0) add(l, FRAG_DGRAD, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
         }
         ga3c::launch_stop(stop, band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
         HIP_TRY(hipGetLastError());
@@ -2046,7 +2048,7 @@ bool on_band_kernels(const ConvGeom &g, int l) {
     if (g.OC != 32 && !(l == 0 && g.OC == 16) && !(l > 0 && g.OC == 64)) return false;
     if (l == 0) return g.C == 4 && g.KS == 8 && bytes_ok(g.H, g.W, g.S) && !spec_matches<SpecS1>(g, true) && !spec_matches<SpecL1>(g, true);
     if (g.C != 32 || g.KS != 4 || g.S != 2 || spec_matches<SpecL2>(g, false)) return false;
-    return band_ok<32>(g.H, g.W) && band_f32_ok<32>(g.H, g.W);
+    return band_ok<32>(g.H, g.W) && band_f32_ok<32>(g.H, g.W) && band_grads_ok(g.H, g.W);
 }
 
 // Forward pass of `B` frames into `w`; heads outputs to the optional pointers.  table (frames is nullptr then): the frames lie
@@ -2247,7 +2249,7 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
         for (int l = 0; l < c->nconv; ++l) {
             const ConvGeom &g = c->geom[l];
             pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kc);
-            nz = std::max(nz, std::min(B, 512));                                 // any-shape kernel, or one partial per block
+            nz = std::max(nz, c->band[l] ? 512 : std::min(B, 512));              // any-shape kernel, or one partial per block
             add((size_t)nz * g.OC * (g.K + 1));
         }
         int nz2;
@@ -2395,8 +2397,9 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         const ConvGeom &g = c->geom[l];
         c->band[l] = on_band_kernels(g, l);
         if (!c->band[l]) continue;
-        if (c->rb) continue;                         // runs on the parameters themselves
-        c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)3 * g.OC * g.K / 8;
+        const size_t vecs = (size_t)3 * g.OC * g.K / 8;
+        if (!c->rb) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }      // reduced precision runs forward on the parameters themselves
+        if (l > 0 && max_train_frames > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
     }
     if (c->bfrag_vecs)
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
@@ -2426,7 +2429,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     if (rc == GA3C_OK && max_train_frames > 0) {
         const size_t B = (size_t)max_train_frames;
         for (int l = 0; l < c->nconv && rc == GA3C_OK; ++l)
-            guard(dmalloc((void **)&c->dact[l], sizeof(float) * B * c->geom[l].OC * c->geom[l].OHW));
+            guard(dmalloc((void **)&c->dact[l], sizeof(float) * (B * c->geom[l].OC * c->geom[l].OHW + BAND_SLACK)));
         if (rc == GA3C_OK) guard(dmalloc((void **)&c->dh, sizeof(float) * B * c->F));
         if (c->fcw[0].w) {
             c->dhp.terms = c->fcw[0].terms;
@@ -2770,13 +2773,16 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                                      : spec_matches<SpecL2>(g, l == 0) ? 4
                                      : spec_matches<SpecL3>(g, l == 0) ? 5
                                      : spec_matches<SpecP2>(g, l == 0) ? 6
-                                     : c->band[l] && (l == 0 ? f32_wgrad_ok<uint8_t>(g.C, g.H, g.W, g.S, g.OC) : f32_wgrad_ok<float>(g.C, g.H, g.W, g.S, g.OC)) ? 7 : 0;
+                                     : c->band[l] && (l > 0 || bytes_wgrad_ok(g.S, g.OC)) ? 8
+                                     : c->band[l] && f32_wgrad_ok(g.C, g.H, g.W, g.S, g.OC) ? 7 : 0;
             if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 3) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
             else if (kind == 4) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
             else if (kind == 5) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
             else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
+            else if (kind == 8) nz = l == 0 ? bytes_wgrad_parts(B, g.H, g.S, c->rb)
+                                   : g.OC == 32 ? band_wgrad_parts<32>(B, g.H, g.W, c->rb) : band_wgrad_parts<64>(B, g.H, g.W, c->rb);
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
@@ -2810,12 +2816,16 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                 HIP_TRY(launch_conv_wgrad_s1_bf16x6<SpecL3>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 6) {
                 HIP_TRY(launch_conv_wgrad_bf16x6<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
-            } else if (kind == 7 && l == 0) {
-                if (g.OC == 16) HIP_TRY((launch_conv_f32_wgrad<uint8_t, 16>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
-                else HIP_TRY((launch_conv_f32_wgrad<uint8_t, 32>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
             } else if (kind == 7) {
-                if (g.OC == 32) HIP_TRY((launch_conv_f32_wgrad<float, 32>((const float *)xin, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f, s, c->rb)));
-                else HIP_TRY((launch_conv_f32_wgrad<float, 64>((const float *)xin, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f, s, c->rb)));
+                if (g.OC == 16) HIP_TRY((launch_conv_f32_wgrad<16>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
+                else HIP_TRY((launch_conv_f32_wgrad<32>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
+            } else if (kind == 8 && l == 0) {
+                if (g.S == 1) HIP_TRY(launch_conv_bytes_wgrad<1>(frames, c->dact[l], part, B, g.H, 1.f / 255.f, s, c->rb));
+                else if (g.S == 2) HIP_TRY(launch_conv_bytes_wgrad<2>(frames, c->dact[l], part, B, g.H, 1.f / 255.f, s, c->rb));
+                else HIP_TRY(launch_conv_bytes_wgrad<3>(frames, c->dact[l], part, B, g.H, 1.f / 255.f, s, c->rb));
+            } else if (kind == 8) {
+                if (g.OC == 32) HIP_TRY(launch_conv_band_wgrad<32>((const float *)xin, c->dact[l], part, B, g.H, g.W, s, c->rb));
+                else HIP_TRY(launch_conv_band_wgrad<64>((const float *)xin, c->dact[l], part, B, g.H, g.W, s, c->rb));
             } else if (l == 0) {
                 ConvWgradP<uint8_t> p; p.rb = c->rb;
                 p.M = g.OC; p.N = g.K + 1; p.K = B * g.OHW; p.kchunk = kchunk; p.g = g;
@@ -2833,10 +2843,10 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         // input gradient
         // bytes: dY in, the layer's input (for the ReLU mask) in, dX out
         STAGE(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W));
-        if (c->fast && c->band[l] && is_aligned16(th + c->off[2 * l])) {
-            const float *wl = th + c->off[2 * l];
-            if (g.OC == 32) HIP_TRY(launch_conv_band_f32_dgrad<32>(c->dact[l], wl, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
-            else HIP_TRY(launch_conv_band_f32_dgrad<64>(c->dact[l], wl, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
+        if (c->fast && c->band[l]) {
+            const u32x4 *wf = c->bfrag[cur] + c->bfrag_dgrad[l];
+            if (g.OC == 32) HIP_TRY(launch_conv_band_dgrad<32>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
+            else HIP_TRY(launch_conv_band_dgrad<64>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
             continue;
         }
         if (c->fast && spec_matches<SpecL3>(g, false)) {

@@ -74,3 +74,34 @@ def test_training_activations_are_the_any_shape_kernels_bits(G, shape, n):
         net.close()
     for l, (a, b) in enumerate(zip(*acts)):
         assert float(a.abs().max()) > 0 and torch.equal(a, b), f"layer {l}"
+
+
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("stride,h,N", [(1, 35, 30), (2, 37, 60), (3, 38, 80)])
+def test_gradients_with_several_items_per_block(G, stride, h, N, math):
+    # more bands than blocks: 28x77 / 15x39 / 11x26 pixels of conv1, then 13x37 / 6x18 / 4x12 of the second layer, whose rows are
+    # filled up to octets and whose bands do not divide the map; the last band of a frame is short
+    desc = G.NetDesc(in_c=4, in_h=h, in_w=84, conv=((32, 8, stride), (32 if stride > 1 else 64, 4, 2)), fc_units=16, n_actions=4, math=math)
+    fr = np.tile(frames_of(9401, 25, h), (N // 5, 1, 1, 1))[:5 * N]
+    P.run_train(G, desc, N, 5, 9400, dict(clip_norm=40.0), frames=fr.reshape(N, 5, 4, h, 84))
+
+
+def test_gradients_do_not_meet_what_an_earlier_larger_batch_left(G):
+    # rows end inside a vector, and what lies behind the last frame of a batch is an earlier batch's, here not numbers
+    import torch
+    desc = G.NetDesc(in_c=4, in_h=36, in_w=84, conv=((32, 8, 2), (32, 4, 2)), fc_units=16, n_actions=4)
+    fr = torch.from_numpy(frames_of(9501, 10, 36)).cuda().view(5, 2, 4, 36, 84)
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9502, 5, 2, 4).items()}
+    grads = []
+    for dirty in (False, True):
+        net = G.Ga3c(desc, 5, 10)
+        if dirty:
+            net.params_set(torch.full((net.n_params,), float("nan"), device="cuda"), 0)
+            net.train_step(fr, tr["actions"], tr["rewards"], tr["dones"], None, G.HParams())
+        net.params_init(9503)
+        cut = {k: v[:3].contiguous() for k, v in tr.items()}
+        net.train_step(fr[:3].contiguous(), cut["actions"], cut["rewards"], cut["dones"], None, G.HParams())
+        grads.append(net.params_get(2))
+        torch.cuda.synchronize()
+        net.close()
+    assert float(grads[0].abs().max()) > 0 and torch.equal(grads[0], grads[1])
