@@ -53,14 +53,15 @@ constexpr int band_pitch() { return 6 * C + 16; }
 
 // ---------------------------------------------------------------- fragments --
 
-// One tensor's fragments: n threads write three vectors (the terms) each, at dst[(i / 64 * 3 + term) * 64 + i % 64].
-enum { FRAG_CONV = 0, FRAG_BYTES8 = 1, FRAG_DGRAD = 2 };
+// One tensor's fragments: n threads write three vectors (the terms) each, at dst[(i / 64 * 3 + term) * 64 + i % 64]; FRAG_F32:
+// one vector of four weights each, at dst[i].
+enum { FRAG_CONV = 0, FRAG_BYTES8 = 1, FRAG_DGRAD = 2, FRAG_F32 = 3 };
 struct FragJob {
     const float *w;          // [OC][C][KS][KS]
     u32x4 *dst;
     int kind, C, OC, KS, n, first_block;
 };
-constexpr int MAX_FRAG_JOBS = 8;
+constexpr int MAX_FRAG_JOBS = 12;
 struct FragJobs {
     FragJob job[MAX_FRAG_JOBS];
     int n;
@@ -73,6 +74,12 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
     if (i >= j.n) return;
     const int lane = i % 64, l16 = lane & 15, g = lane >> 4;
     int blk = i / 64;
+    if (j.kind == FRAG_F32) {                // [filter tile][group of 16 taps]: row = filter, a lane's k = four taps of the group
+        const int groups = j.C * j.KS * j.KS / 16;
+        const f32x4_dw v = *(const f32x4_dw *)(j.w + ((size_t)(blk / groups * 16 + l16) * groups + blk % groups) * 16 + 4 * g);
+        ((float4 *)j.dst)[i] = make_float4(v.x, v.y, v.z, v.w);
+        return;
+    }
     float f[8];
     if (j.kind == FRAG_CONV) {               // [filter tile][(u, v, 32 channels)]: row = filter, k = channel
         const int cgs = j.C / 32, kbs = j.KS * j.KS * cgs;

@@ -17,9 +17,8 @@
 // What bounds them is the instruction: 146 - 150 TFLOP/s on this chip.  With k
 // in the filter's own order (c, u, v), the four k of a lane are four columns of
 // one filter row: a 16-byte piece of a filter, and four neighbouring values (or
-// bytes) of an input row.  So the input stays in LDS as it is in memory, without
-// any re-laying or conversion, and one read of 16 bytes per lane feeds four
-// instructions per filter tile.
+// bytes) of an input row.  So the input is used as it lies in memory, without
+// any re-laying, and one read per lane feeds four instructions per filter tile.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -32,280 +31,188 @@
 namespace ga3c {
 
 constexpr int BAND_F32_LDS = 80 * 1024;           // two blocks per compute unit: one stages while the other multiplies
-constexpr int BAND_F32_MAXK = 3;                  // values of a channel in flight per thread
 
-// 4x4, stride 2, 32 channels; a block takes the pixel tiles of its item four wavefronts apart, all filters.
+// Forward: 4x4, stride 2, 32 channels of floats, or 8x8, any stride, four planes of bytes.  A step is 16 taps: a channel's
+// filter, or two rows of a plane's.  The weights lie in LDS as fragments; the pixels of all frames are numbered on, sixteen to
+// a tile, and a block takes a run of tiles, wavefront by wavefront: a lane's four columns of a step come straight from memory
+// (the caches see every row several times), DEPTH steps ahead, also across tiles.  No barrier after the weights have come, no
+// tile with fewer pixels but the last, and only input values in the queue of loads.
+// Bound by the instruction: 640 frames, 77x77 map 281 us (379 in bands of rows that were staged in LDS, whose weights were
+// read while the tiles were multiplied and so arrived behind the next band's values), 223 without the loads, 195 the products
+// alone; 84x84 bytes with stride 1 555 (605), 484 without loads and conversions; 100 frames with stride 3 16 (24).
 // RB: both operands rounded to bfloat16.
-template <int C, int OC, bool RB>
-__global__ __launch_bounds__(256, 2) void conv_band_f32_fwd_kernel(const float *__restrict__ x, const float *__restrict__ w,
-                                                                   const float *__restrict__ bias, float *__restrict__ y, int nframes,
-                                                                   const BandGeom b) {
-    constexpr int OT = OC / 16, K = 16 * C, MAXK = BAND_F32_MAXK;
+struct F32FwdGeom {
+    int nframes, H, W, S, OH, OW;
+    float scale;             // of the sums
+    int tiles;               // of 16 pixels
+    FastDiv dNPIX, dOW;
+};
+template <class TIn> constexpr int f32_fwd_steps() { return sizeof(TIn) == 1 ? 16 : 32; }
+
+template <class TIn, int OC, int MT, bool LDSW, bool RB>
+__global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kernel(const TIn *__restrict__ x, const float4 *__restrict__ w,
+                                                              const float *__restrict__ bias, float *__restrict__ y, const F32FwdGeom b) {
+    constexpr bool BYTE = sizeof(TIn) == 1;
+    constexpr int C = f32_fwd_steps<TIn>(), OT = OC / 16, DEPTH = BYTE ? 8 : 16;
+    typedef typename std::conditional<BYTE, uint2, float4>::type Vec;
+    constexpr int NW = LDSW ? 8 * MT / OT : 1, N = LDSW ? 2 : 1;      // tiles of a round, and how many of them a wavefront has in turn
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
-    float *xs = (float *)band_smem;                   // [c][frame][row][W]
+    float4 *ws = (float4 *)band_smem;                 // [filter tile][c][lane], as in memory
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    const int HW = b.H * b.W, NPIX = b.OH * b.OW, RI = (b.R - 1) * 2 + 4;
-    const int chunk = RI * b.W, plane = b.F * chunk;      // a frame's band of a channel is contiguous in memory
-    const size_t total = (size_t)nframes * C * HW;
+    const int ot = wave % (OT / MT) * MT, slot = wave / (OT / MT);      // my first filter tile
+    const int HW = b.H * b.W, CHW = (BYTE ? 4 : C) * HW, NPIX = b.OH * b.OW, npix = b.nframes * NPIX;
+    const int first = (int)((long)blockIdx.x * b.tiles / gridDim.x), end = (int)((long)(blockIdx.x + 1) * b.tiles / gridDim.x);
 
-    // value k of a thread and channel: number tid + 256 k of the channel's part of the item
-    uint32_t src[MAXK];
-#pragma unroll
-    for (int k = 0; k < MAXK; ++k) {
-        const int e = min(tid + 256 * k, plane - 1);
-        src[k] = (uint32_t)(e / chunk * C * HW + e % chunk);
-    }
-    float pre[C][MAXK];
-    auto fetch = [&](int item) {
-        const size_t base = (size_t)(item / b.nb) * b.F * C * HW + (size_t)(item % b.nb) * b.R * 2 * b.W;
-        const size_t left = total - base - (size_t)(C - 1) * HW - 1;
-        const uint32_t lim = left > 0x3fffffff ? 0x3fffffffu : (uint32_t)left;
-#pragma unroll
-        for (int k = 0; k < MAXK; ++k)
-            if (256 * k < plane) {
-                const uint32_t off = 4u * min(src[k], lim);          // rows past the map feed no output
-#pragma unroll
-                for (int c = 0; c < C; ++c) pre[c][k] = *(const float *)((const char *)(x + base + (size_t)c * HW) + off);
-            }
+    // Where a tile's values of step 0 lie: bytes from `base`, its first frame's, lane by lane.  Bytes come with the dword that
+    // they begin in and the next one, or the frame's last two; `sel` picks mine.
+    auto locate = [&](int t, const TIn *&base, uint32_t &off, uint32_t &sel) {
+        const int p0 = min(t * 16, npix - 1);
+        const uint32_t f0 = __builtin_amdgcn_readfirstlane(b.dNPIX.div((uint32_t)p0));
+        uint32_t f, rem, i, j;
+        b.dNPIX.divmod((uint32_t)min(t * 16 + l16, npix - 1), f, rem);
+        b.dOW.divmod(rem, i, j);
+        base = x + (size_t)f0 * CHW;
+        if (BYTE) {
+            const uint32_t at = (i * b.S + (g >> 1)) * b.W + j * b.S + 4 * (g & 1);
+            off = min(at & ~3u, (uint32_t)((b.H - 6) * b.W - 8));      // the last step's rows are six further down
+            sel = 0x03020100u + 0x01010101u * (at - off);
+            off += (f - f0) * (uint32_t)CHW;
+        } else off = 4u * ((f - f0) * (uint32_t)CHW + (2 * i + g) * b.W + 2 * j);
     };
-    int item = blockIdx.x;
-    fetch(min(item, b.items - 1));
-    float bv[OT];
-#pragma unroll
-    for (int m = 0; m < OT; ++m) bv[m] = bias[m * 16 + l16];
-    const float *wl = w + (size_t)l16 * K + 4 * g;    // my four taps of channel 0 in filter l16
-
-    int turn = 0;
-    for (; item < b.items; item += gridDim.x, ++turn) {
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < MAXK; ++k)
-            if (tid + 256 * k < plane) {
-#pragma unroll
-                for (int c = 0; c < C; ++c) xs[c * plane + tid + 256 * k] = RB ? bf16_rne(pre[c][k]) : pre[c][k];
-            }
-        __syncthreads();
-        fetch(min(item + (int)gridDim.x, b.items - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        const int f0 = (item / b.nb) * b.F, i0 = (item % b.nb) * b.R;
-        const int cnt = b.F * b.R * b.OW, vpix = min(b.R, b.OH - i0) * b.OW, ntile = (cnt + 15) / 16;
-        auto pass = [&](auto nc, int t0) {
-            constexpr int N = decltype(nc)::value;
-            const float *base[N];
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                uint32_t p = (uint32_t)((t0 + 4 * n) * 16 + l16), f, rem, i, j;
-                if ((int)p >= cnt) p = 0;
-                b.dFR.divmod(p, f, rem);
-                b.dC.divmod(rem, i, j);
-                base[n] = xs + (int)f * chunk + (2 * (int)i + g) * b.W + 2 * (int)j;
-            }
-            floatx4 acc[N][OT];
-#pragma unroll
-            for (int n = 0; n < N; ++n)
-#pragma unroll
-                for (int m = 0; m < OT; ++m) acc[n][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-            float4 wv[2][OT];
-            auto read_w = [&](int c, float4 (&d)[OT]) {
-#pragma unroll
-                for (int m = 0; m < OT; ++m) {
-                    d[m] = *(const float4 *)(wl + (size_t)m * 16 * K + 16 * c);
-                    if (RB) d[m] = bf16_rne(d[m]);
-                }
-            };
-            float xv[2][N][4];
-            auto read_x = [&](int c, float (&d)[N][4]) {
-#pragma unroll
-                for (int n = 0; n < N; ++n)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) d[n][e] = base[n][c * plane + e];
-            };
-            read_w(0, wv[0]);
-            read_x(0, xv[0]);
-#pragma unroll 2
-            for (int c = 0; c < C; ++c) {
-                const int cn = min(c + 1, C - 1);
-                read_w(cn, wv[(c + 1) & 1]);
-                read_x(cn, xv[(c + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int m = 0; m < OT; ++m) {
-                        const float4 q = wv[c & 1][m];
-                        const float we = e == 0 ? q.x : e == 1 ? q.y : e == 2 ? q.z : q.w;
-#pragma unroll
-                        for (int n = 0; n < N; ++n) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[c & 1][n][e], we, acc[n][m], 0, 0, 0);
-                    }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int n = 0; n < N; ++n) {
-                const uint32_t p0 = (uint32_t)((t0 + 4 * n) * 16 + 4 * g);
-                uint32_t f, rem;
-                b.dFR.divmod(p0, f, rem);
-                const bool whole = (int)p0 < cnt && f0 + (int)f < nframes && (int)rem + 3 < vpix;
-#pragma unroll
-                for (int m = 0; m < OT; ++m) {
-                    float v[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        v[r] = acc[n][m][r] + bv[m];
-                        v[r] = v[r] > 0.f ? v[r] : 0.f;
-                    }
-                    if (whole) {
-                        *(f32x4_dw *)(y + ((size_t)(f0 + (int)f) * OC + m * 16 + l16) * NPIX + i0 * b.OW + rem) = f32x4_dw{v[0], v[1], v[2], v[3]};
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            uint32_t fe, re;
-                            b.dFR.divmod(p0 + r, fe, re);
-                            if ((int)p0 + r < cnt && f0 + (int)fe < nframes && (int)re < vpix)
-                                y[((size_t)(f0 + (int)fe) * OC + m * 16 + l16) * NPIX + i0 * b.OW + re] = v[r];
-                        }
-                    }
-                }
-            }
-        };
-        constexpr int NMAX = OC == 32 ? 4 : 2;        // accumulators of a pass: NMAX x OC / 16
-        const int wt = (wave + turn) & 3;             // who gets an odd tile more changes from item to item: the SIMDs share it
-        int t = wt, left = (ntile - wt + 3) / 4;      // (640 frames of 77x77 402 -> 397 us)
-        for (; left >= NMAX; left -= NMAX, t += 4 * NMAX) pass(std::integral_constant<int, NMAX>{}, t);
-        if (NMAX > 2 && left == 3) pass(std::integral_constant<int, 3>{}, t);
-        else if (NMAX > 2 && left == 2) pass(std::integral_constant<int, 2>{}, t);
-        else if (left == 1) pass(std::integral_constant<int, 1>{}, t);
-    }
-}
-
-// The byte layer: 8x8 filters over four planes of width 84.  A wavefront keeps all filters in registers (64 x OC / 16) and
-// takes every fourth pixel tile; a lane's four bytes of a filter row come out of the two dwords they lie in.
-template <int OC, bool RB>
-__global__ __launch_bounds__(256, 2) void conv_bytes_f32_fwd_kernel(const uint8_t *__restrict__ x, const float *__restrict__ w,
-                                                                    const float *__restrict__ bias, float *__restrict__ y, int nframes,
-                                                                    float scale, const BytesGeom b) {
-    constexpr int OT = OC / 16, KB = 16, MAXU = 7;
-    extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];      // [plane][row][84] bytes, and a dword more
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, g = lane >> 4;
-    const int RI = (b.R - 1) * b.S + 8, NU = RI * BYTES_Q, PLANE = b.H * BYTES_W, NPIX = b.OH * b.OW;
-
-    uint32_t pre[MAXU][4];
-    auto fetch = [&](int item) {
-        const int r0 = (item % b.nb) * b.R * b.S;
-        const uint8_t *src = x + (size_t)(item / b.nb) * 4 * PLANE + (size_t)r0 * BYTES_W;
-        const int last = (b.H - r0) * BYTES_Q - 1;            // rows past the frame feed no output
-#pragma unroll
-        for (int i = 0; i < MAXU; ++i)
-            if (256 * i < NU) {
-                const uint32_t off = 4u * (uint32_t)min(min(tid + 256 * i, NU - 1), last);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) pre[i][c] = *(const uint32_t *)(src + (size_t)c * PLANE + off);
-            }
-    };
-    int item = blockIdx.x;
-    fetch(min(item, b.items - 1));
-    // group kb of 16 taps: plane kb / 4, filter rows 2 (kb % 4) and the next; my four taps: row + g / 2, columns 4 (g % 2) ..
-    float4 wq[KB][OT];
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int m = 0; m < OT; ++m) {
-            wq[kb][m] = *(const float4 *)(w + (size_t)(m * 16 + l16) * 256 + 16 * kb + 4 * g);
-            if (RB) wq[kb][m] = bf16_rne(wq[kb][m]);
+    Vec xv[DEPTH][N];
+    auto load = [&](const TIn *base, uint32_t off, int c, Vec &d) {
+        if constexpr (BYTE) {
+            const uint32_t *p = (const uint32_t *)(base + ((c >> 2) * HW + 2 * (c & 3) * b.W) + off);
+            d = make_uint2(p[0], p[1]);
+        } else {
+            const f32x4_dw v = *(const f32x4_dw *)((const char *)(base + (size_t)c * HW) + off);
+            d = make_float4(v.x, v.y, v.z, v.w);
         }
-    float bv[OT];
+    };
+    auto values = [&](const Vec &d, uint32_t sel, float (&v)[4]) {
+        if constexpr (BYTE) {
+            const uint32_t q = __builtin_amdgcn_perm(d.y, d.x, sel);
+            v[0] = (float)(q & 0xff); v[1] = (float)((q >> 8) & 0xff); v[2] = (float)((q >> 16) & 0xff); v[3] = (float)(q >> 24);
+        } else {
+            const float4 q = RB ? bf16_rne(d) : d;
+            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        }
+    };
+    const TIn *base[N], *next[N];
+    uint32_t off[N], noff[N], sel[N], nsel[N];
+    float4 wq[LDSW ? 1 : DEPTH][MT];                  // weights that do not lie in LDS come as the values do
+    auto load_w = [&](int c, float4 (&d)[MT]) {
 #pragma unroll
-    for (int m = 0; m < OT; ++m) bv[m] = bias[m * 16 + l16];
-    for (; item < b.items; item += gridDim.x) {
-        __syncthreads();
+        for (int m = 0; m < MT; ++m) d[m] = w[((ot + m) * C + c % C) * 64 + lane];
+    };
+    int t = first + slot;
 #pragma unroll
-        for (int i = 0; i < MAXU; ++i)
-            if (tid + 256 * i < NU) {
+    for (int n = 0; n < N; ++n) {
+        locate(t + NW * n, base[n], off[n], sel[n]);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) ((uint32_t *)band_smem)[c * NU + tid + 256 * i] = pre[i][c];
-            }
-        __syncthreads();
-        fetch(min(item + (int)gridDim.x, b.items - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        const int i0 = (item % b.nb) * b.R, cnt = min(b.R, b.OH - i0) * b.OW, ntile = (cnt + 15) / 16;
-        float *yb = y + ((size_t)(item / b.nb) * OC + l16) * NPIX + i0 * b.OW;
-        auto pass = [&](auto nc, int t0) {
-            constexpr int N = decltype(nc)::value;
-            const uint32_t *base[N];
-            uint32_t sh[N];
+        for (int c = 0; c < DEPTH - 1; ++c) load(base[n], off[n], c, xv[c][n]);
+    }
+    if constexpr (!LDSW) {
 #pragma unroll
-            for (int n = 0; n < N; ++n) {
-                uint32_t p = (uint32_t)((t0 + 4 * n) * 16 + l16), i, j;
-                if ((int)p >= cnt) p = 0;
-                b.dC.divmod(p, i, j);
-                const int at = ((int)i * b.S + (g >> 1)) * BYTES_W + (int)j * b.S + 4 * (g & 1);
-                base[n] = (const uint32_t *)band_smem + (at >> 2);
-                sh[n] = (uint32_t)at & 3u;
-            }
-            floatx4 acc[N][OT];
+        for (int c = 0; c < DEPTH - 1; ++c) load_w(c, wq[c]);
+    } else {
 #pragma unroll
-            for (int n = 0; n < N; ++n)
+        for (int e = 0; e < C * OT / 8; ++e) {
+            const float4 v = w[512 * e + tid];
+            ws[512 * e + tid] = RB ? bf16_rne(v) : v;
+        }
+    }
+    float bv[MT];
 #pragma unroll
-                for (int m = 0; m < OT; ++m) acc[n][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-            uint32_t lo[2][N], hi[2][N];
-            auto read = [&](int kb, uint32_t (&a)[N], uint32_t (&c)[N]) {
-                const int off = (kb / 4) * NU + 2 * (kb % 4) * BYTES_Q;
+    for (int m = 0; m < MT; ++m) bv[m] = bias[(ot + m) * 16 + l16];
+    if (LDSW) __syncthreads();
+
+    // tiles t, t + NW, ..: NT of them; behind the last channels of these come the first ones of the next
+    auto pass = [&](auto ntc) {
+        constexpr int NT = decltype(ntc)::value;
+        const bool more = t + NW * N < end;
 #pragma unroll
-                for (int n = 0; n < N; ++n) { a[n] = base[n][off]; c[n] = base[n][off + 1]; }
-            };
-            read(0, lo[0], hi[0]);
+        for (int n = 0; n < N; ++n) locate(min(t + NW * (N + n), end - 1), next[n], noff[n], nsel[n]);
+        floatx4 acc[NT][MT];
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                if (kb + 1 < KB) read(kb + 1, lo[(kb + 1) & 1], hi[(kb + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-                float xv[N][4];
+        for (int n = 0; n < NT; ++n)
 #pragma unroll
-                for (int n = 0; n < N; ++n) {
-                    const uint32_t v = __builtin_amdgcn_alignbyte(hi[kb & 1][n], lo[kb & 1][n], sh[n]);
-                    xv[n][0] = (float)(v & 0xff); xv[n][1] = (float)((v >> 8) & 0xff);
-                    xv[n][2] = (float)((v >> 16) & 0xff); xv[n][3] = (float)(v >> 24);
+            for (int m = 0; m < MT; ++m) acc[n][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        float4 wv[2][MT];
+        auto read_w = [&](int c, float4 (&d)[MT]) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m) d[m] = ws[((ot + m) * C + c) * 64 + lane];
+        };
+        if (LDSW) read_w(0, wv[0]);
+        auto chunk = [&](int c0, auto lastc) {
+            constexpr bool LAST = decltype(lastc)::value;
+#pragma unroll
+            for (int k = 0; k < DEPTH; ++k) {
+                constexpr int A = DEPTH - 1;
+                if (!LAST || k == 0) {
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) load(base[n], off[n], c0 + k + A, xv[(k + A) % DEPTH][n]);
+                } else if (more) {
+#pragma unroll
+                    for (int n = 0; n < N; ++n) load(next[n], noff[n], k - 1, xv[(k + A) % DEPTH][n]);
                 }
+                if constexpr (!LDSW) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) wv[k & 1][m] = RB ? bf16_rne(wq[k][m]) : wq[k][m];
+                    load_w(c0 + k + A, wq[(k + A) % DEPTH]);
+                } else if (!LAST || k + 1 < DEPTH) read_w(c0 + k + 1, wv[(k + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                float v[NT][4];
+#pragma unroll
+                for (int n = 0; n < NT; ++n) values(xv[k][n], sel[n], v[n]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
-                    for (int m = 0; m < OT; ++m) {
-                        const float4 q = wq[kb][m];
+                    for (int m = 0; m < MT; ++m) {
+                        const float4 q = wv[k & 1][m];
                         const float we = e == 0 ? q.x : e == 1 ? q.y : e == 2 ? q.z : q.w;
 #pragma unroll
-                        for (int n = 0; n < N; ++n) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv[n][e], we, acc[n][m], 0, 0, 0);
+                        for (int n = 0; n < NT; ++n) acc[n][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[n][e], we, acc[n][m], 0, 0, 0);
                     }
                 __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        for (int c0 = 0; c0 < C - DEPTH; c0 += DEPTH) chunk(c0, std::false_type{});
+        chunk(C - DEPTH, std::true_type{});
 #pragma unroll
-            for (int n = 0; n < N; ++n) {
-                const int p0 = (t0 + 4 * n) * 16 + 4 * g;
+        for (int n = 0; n < NT; ++n) {
+            const int p0 = (t + NW * n) * 16 + 4 * g;
+            if (t + NW * n >= end) continue;
+            uint32_t f, rem;
+            b.dNPIX.divmod((uint32_t)min(p0, npix - 1), f, rem);
 #pragma unroll
-                for (int m = 0; m < OT; ++m) {
-                    float v[4];
+            for (int m = 0; m < MT; ++m) {
+                float v[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    v[r] = BYTE ? acc[n][m][r] * b.scale + bv[m] : acc[n][m][r] + bv[m];
+                    v[r] = v[r] > 0.f ? v[r] : 0.f;
+                }
+                if ((int)rem + 3 < NPIX && p0 + 3 < npix) {
+                    *(f32x4_dw *)(y + ((size_t)f * OC + (ot + m) * 16 + l16) * NPIX + rem) = f32x4_dw{v[0], v[1], v[2], v[3]};
+                } else {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        v[r] = acc[n][m][r] * scale + bv[m];
-                        v[r] = v[r] > 0.f ? v[r] : 0.f;
-                    }
-                    float *o = yb + (size_t)m * 16 * NPIX + p0;
-                    if (p0 + 3 < cnt) *(f32x4_dw *)o = f32x4_dw{v[0], v[1], v[2], v[3]};
-                    else {
-#pragma unroll
-                        for (int r = 0; r < 3; ++r)
-                            if (p0 + r < cnt) o[r] = v[r];
+                        uint32_t fe, re;
+                        b.dNPIX.divmod((uint32_t)(p0 + r), fe, re);
+                        if (p0 + r < npix) y[((size_t)fe * OC + (ot + m) * 16 + l16) * NPIX + re] = v[r];
                     }
                 }
             }
-        };
-        int t = wave, left = (ntile - wave + 3) / 4;
-        for (; left >= 4; left -= 4, t += 16) pass(std::integral_constant<int, 4>{}, t);
-        if (left == 3) pass(std::integral_constant<int, 3>{}, t);
-        else if (left == 2) pass(std::integral_constant<int, 2>{}, t);
-        else if (left == 1) pass(std::integral_constant<int, 1>{}, t);
-    }
+        }
+#pragma unroll
+        for (int n = 0; n < N; ++n) { base[n] = next[n]; off[n] = noff[n]; sel[n] = nsel[n]; }
+    };
+    // a last round that has one tile at most for every wavefront takes half the time
+    for (; end - (t - slot) > NW * (N - 1); t += NW * N) pass(std::integral_constant<int, N>{});
+    if (N > 1 && t < end) pass(std::integral_constant<int, 1>{});
 }
 
 // ---------------------------------------------------------- weight gradient --
@@ -481,54 +388,41 @@ __global__ __launch_bounds__(64 * F32_WGRAD_WAVES, 5) void conv_f32_wgrad_kernel
     if (by == 0 && wave == (z & (NW - 1)) && lane < OC) pb[(size_t)lane * K1 + K1 - 1] = bsum;
 }
 
-template <int C>
-inline bool band_f32_geom(BandGeom &b, int nframes) {
-    auto px = [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W; };
-    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return px(F, R) * C * 4 <= BAND_F32_LDS ? 0 : 2 * BAND_LDS; },
-                      [&](int F, int R) { return px(F, R) <= 256 * BAND_F32_MAXK ? 0 : 1 << 30; }, BAND_MAXU, 2 * BAND_CUS);
-}
-
-template <int C, int OC, bool RB>
-inline hipError_t launch_conv_band_f32_fwd1(const float *x, const float *w, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
-    BandGeom b = band_geom(H, W);
-    if (!band_f32_geom<C>(b, n)) return hipErrorInvalidValue;
+template <class TIn, int OC, int MT, bool LDSW, bool RB>
+inline hipError_t launch_conv_f32_fwd1(const TIn *x, const float4 *w, const float *bias, float *y, const F32FwdGeom &b, hipStream_t s) {
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_f32_fwd_kernel<C, OC, RB>, attr);
+    const hipError_t e = LDSW ? band_allow_lds(conv_f32_fwd_kernel<TIn, OC, MT, LDSW, RB>, attr) : hipSuccess;
     if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_f32_fwd_kernel<C, OC, RB>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256),
-                 b.F * ((b.R - 1) * 2 + 4) * b.W * C * 4, s, x, w, bias, y, n, b);
+    constexpr int NW = 128 * MT / OC;
+    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW, RB>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, BAND_CUS) : b.tiles),
+                 dim3(LDSW ? 512 : 4 * OC / MT), LDSW ? f32_fwd_steps<TIn>() * OC * 64 : 0, s, x, w, bias, y, b);
     return hipGetLastError();
 }
-// x [n][32][H][W] -> y [n][OC][OH][OW]; w [OC][32][4][4], 16-byte aligned.
-template <int C, int OC>
-inline hipError_t launch_conv_band_f32_fwd(const float *x, const float *w, const float *bias, float *y, int n, int H, int W, hipStream_t s, int rb) {
+template <class TIn, int OC, bool RB>
+inline hipError_t launch_conv_f32_fwd2(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s) {
+    constexpr int KS = sizeof(TIn) == 1 ? 8 : 4;
+    F32FwdGeom b{};
+    b.nframes = n; b.H = H; b.W = W; b.S = S; b.OH = (H - KS) / S + 1; b.OW = (W - KS) / S + 1; b.scale = scale;
+    const int npix = b.OH * b.OW;
+    b.tiles = (int)(((long long)n * npix + 15) / 16);
+    b.dNPIX = FastDiv((uint32_t)npix); b.dOW = FastDiv((uint32_t)b.OW);
+    // Few tiles: a block each, a wavefront per filter tile.  Otherwise two filter tiles per wavefront, or one where the last
+    // round of blocks would be half empty with two.  640 .. 20 frames of the family's maps, us, a block per tile / one filter
+    // tile / two: 32 filters, 203 tiles 5.1 / 7.8 / 11.3, 451 7.5 / 7.6 / 11.0, 902 9.2 / 8.2 / 11.6, 1440 12.7 / 13.4 / 12.2,
+    // 2278 20.3 / 16.3 / 22.7, 3240 26 / 23.3 / 23.2, 54760 418 / 305 / 281; 64 filters, 250 tiles 6.4 / 8.9 / 12.5, 500
+    // 10.4 / 9.6 / 13.0, 640 12.6 / 13.6 / 12.5, 1280 20 / 16.8 / 22.6, 2560 37 / 29.5 / 28.7.  (In bands of rows staged in
+    // LDS: 9.4, 9.5, 15.8, 17.5, 24.9, 34.9, 384; 13.3, 21.5, 21.6, 35.9, 52.8.)
+    const int half = BAND_CUS * (128 / OC), rounds = (b.tiles + half - 1) / half;
+    if (b.tiles <= BAND_CUS) return launch_conv_f32_fwd1<TIn, OC, 1, false, RB>(x, w, bias, y, b, s);
+    if (rounds == 1 || rounds == 3) return launch_conv_f32_fwd1<TIn, OC, 1, true, RB>(x, w, bias, y, b, s);
+    return launch_conv_f32_fwd1<TIn, OC, OC == 16 ? 1 : 2, true, RB>(x, w, bias, y, b, s);
+}
+// x [n][32][H][W] floats -> y [n][OC][OH][OW] of the 4x4, stride-2 layer, or [n][4][H][W] bytes of the 8x8 layer of stride S;
+// w: FRAG_F32 of the filters.
+template <class TIn, int OC>
+inline hipError_t launch_conv_f32_fwd(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s, int rb) {
     if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_f32_fwd1<C, OC, true>(x, w, bias, y, n, H, W, s) : launch_conv_band_f32_fwd1<C, OC, false>(x, w, bias, y, n, H, W, s);
-}
-
-template <int OC, bool RB>
-inline hipError_t launch_conv_bytes_f32_fwd1(const uint8_t *x, const float *w, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
-    const BytesGeom b = bytes_fwd_geom(H, S, n);
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_bytes_f32_fwd_kernel<OC, RB>, attr);
-    if (e != hipSuccess) return e;
-    const int RI = (b.R - 1) * b.S + 8;
-    ga3c::launch((conv_bytes_f32_fwd_kernel<OC, RB>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), RI * BYTES_W * 4 + 16, s, x, w, bias, y, n, scale, b);
-    return hipGetLastError();
-}
-// x [n][4][H][84] bytes -> y [n][OC][OH][OW]; w [OC][4][8][8], 16-byte aligned.
-template <int OC>
-inline hipError_t launch_conv_bytes_f32_fwd(const uint8_t *x, const float *w, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s,
-                                            int rb) {
-    if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_bytes_f32_fwd1<OC, true>(x, w, bias, y, n, H, S, scale, s) : launch_conv_bytes_f32_fwd1<OC, false>(x, w, bias, y, n, H, S, scale, s);
-}
-
-// Whether the forward pass can run maps of H x W.
-template <int C>
-inline bool band_f32_ok(int H, int W) {
-    BandGeom b = band_geom(H, W);
-    return band_f32_geom<C>(b, 1);
+    return rb ? launch_conv_f32_fwd2<TIn, OC, true>(x, w, bias, y, n, H, W, S, scale, s) : launch_conv_f32_fwd2<TIn, OC, false>(x, w, bias, y, n, H, W, S, scale, s);
 }
 
 // b.rows: rows of input that a step can touch; it covers up to R output rows and d frame boundaries.

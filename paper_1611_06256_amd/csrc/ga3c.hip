@@ -165,7 +165,7 @@ struct ga3c_ctx {
     // layers on the any-size kernels of conv_band.hpp and conv_bytes.hpp: which ones, where their fragments sit in the
     // buffer of each parameter copy (in vectors), and the buffers (nullptr where no layer needs one)
     bool band[GA3C_MAX_CONV];
-    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_dgrad[GA3C_MAX_CONV], bfrag_vecs;
+    size_t bfrag_fwd[GA3C_MAX_CONV], bfrag_f32[GA3C_MAX_CONV], bfrag_dgrad[GA3C_MAX_CONV], bfrag_vecs;
     u32x4 *bfrag[2];
     ga3c::FcPlanes fcw[2];        // fc weights of each parameter copy as operands of the forward product (w == nullptr: none); kept
                                   // current by whoever writes the copy
@@ -2034,6 +2034,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
             if (!c->band[l]) continue;
             const ConvGeom &g = c->geom[l];
             if (!c->rb) add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
+            if (c->rb || c->max_train > 0) add(l, FRAG_F32, c->bfrag[i] + c->bfrag_f32[l], g.OC * g.K / 4);
             if (l > 0 && c->max_train > 0) add(l, FRAG_DGRAD, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
         }
         ga3c::launch_stop(stop, band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
@@ -2048,7 +2049,7 @@ bool on_band_kernels(const ConvGeom &g, int l) {
     if (g.OC != 32 && !(l == 0 && g.OC == 16) && !(l > 0 && g.OC == 64)) return false;
     if (l == 0) return g.C == 4 && g.KS == 8 && bytes_ok(g.H, g.W, g.S) && !spec_matches<SpecS1>(g, true) && !spec_matches<SpecL1>(g, true);
     if (g.C != 32 || g.KS != 4 || g.S != 2 || spec_matches<SpecL2>(g, false)) return false;
-    return band_ok<32>(g.H, g.W) && band_f32_ok<32>(g.H, g.W) && band_grads_ok(g.H, g.W);
+    return band_ok<32>(g.H, g.W) && band_grads_ok(g.H, g.W);
 }
 
 // Forward pass of `B` frames into `w`; heads outputs to the optional pointers.  table (frames is nullptr then): the frames lie
@@ -2128,14 +2129,15 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         // 20.5).
         if (c->fast && c->band[l] && is_aligned16(xin) && is_aligned16(wl)) {
             const u32x4 *wf = c->bfrag[which] + c->bfrag_fwd[l];
+            const float4 *w32 = (const float4 *)(c->bfrag[which] + c->bfrag_f32[l]);
             const bool f32 = c->rb || keep_zv;
             if (l == 0) {
-                if (f32 && g.OC == 16) HIP_TRY(launch_conv_bytes_f32_fwd<16>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
-                else if (f32) HIP_TRY(launch_conv_bytes_f32_fwd<32>(frames, wl, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
+                if (f32 && g.OC == 16) HIP_TRY((launch_conv_f32_fwd<uint8_t, 16>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s, c->rb)));
+                else if (f32) HIP_TRY((launch_conv_f32_fwd<uint8_t, 32>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s, c->rb)));
                 else if (g.OC == 16) HIP_TRY(launch_conv_bytes_fwd<16>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
                 else HIP_TRY(launch_conv_bytes_fwd<32>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s));
-            } else if (f32 && g.OC == 32) HIP_TRY((launch_conv_band_f32_fwd<32, 32>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s, c->rb)));
-            else if (f32) HIP_TRY((launch_conv_band_f32_fwd<32, 64>(w.act[l - 1], wl, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+            } else if (f32 && g.OC == 32) HIP_TRY((launch_conv_f32_fwd<float, 32>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s, c->rb)));
+            else if (f32) HIP_TRY((launch_conv_f32_fwd<float, 64>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s, c->rb)));
             else if (g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
             else HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
             continue;
@@ -2398,7 +2400,8 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         c->band[l] = on_band_kernels(g, l);
         if (!c->band[l]) continue;
         const size_t vecs = (size_t)3 * g.OC * g.K / 8;
-        if (!c->rb) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }      // reduced precision runs forward on the parameters themselves
+        if (!c->rb) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }      // reduced precision runs forward on the fp32 instruction
+        if (c->rb || max_train_frames > 0) { c->bfrag_f32[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)g.OC * g.K / 4; }
         if (l > 0 && max_train_frames > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
     }
     if (c->bfrag_vecs)

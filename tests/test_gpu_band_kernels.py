@@ -105,3 +105,9 @@ def test_gradients_do_not_meet_what_an_earlier_larger_batch_left(G):
         torch.cuda.synchronize()
         net.close()
     assert float(grads[0].abs().max()) > 0 and torch.equal(grads[0], grads[1])
+
+
+@pytest.mark.parametrize("n", [20, 40, 60, 140])
+def test_training_activations_are_the_any_shape_kernels_bits_across_the_launch_rules(G, n):
+    # the second layer's 9 n tiles of 64 filters: a block per tile, one filter tile per wavefront, two, and one again with more rounds
+    test_training_activations_are_the_any_shape_kernels_bits(G, dict(in_h=84, conv=((32, 8, 3), (64, 4, 2))), n)
