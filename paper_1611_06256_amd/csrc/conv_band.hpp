@@ -1,7 +1,8 @@
 // The 4x4, stride-2 convolution layer with 32 input channels and 32 or 64
 // filters on maps of any size (the paper's larger-network family, Sec. 5, whose
 // maps are 9 to 77 pixels wide): forward pass of predictions on the bf16 matrix
-// cores at fp32 accuracy (updates keep one order of sums: conv_band_f32.hpp).
+// cores at fp32 accuracy (updates keep one order of sums: conv_band_f32.hpp), and
+// of both calls with operands rounded to bfloat16 (ONE: one term).
 //
 // A work item is a band of output rows of one frame, as many as a compute unit's LDS holds, or several whole small frames
 // (BandGeom, chosen on the host); a block walks over items and the next item
@@ -32,7 +33,8 @@ namespace ga3c {
 
 constexpr int BAND_LDS = 160 * 1024;          // one block per compute unit
 constexpr int BAND_CUS = 256;
-constexpr int BAND_MAXU = 13;                 // staging units (8 channels of a pixel) per thread: bounds the registers of a band in flight
+// staging units (8 channels of a pixel) per thread: bounds the registers of a band in flight
+template <bool ONE> constexpr int band_maxu() { return ONE ? 10 : 13; }
 
 typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
@@ -48,8 +50,8 @@ struct BandGeom {
 };
 
 // LDS pixel pitch in bytes for C channels.
-template <int C>
-constexpr int band_pitch() { return 6 * C + 16; }
+template <int C, bool ONE>
+constexpr int band_pitch() { return ONE ? 16 * lds_row_units(C / 8) : 6 * C + 16; }
 
 // ---------------------------------------------------------------- fragments --
 
@@ -109,11 +111,12 @@ __device__ __forceinline__ void band_load8(const float *base, uint32_t off, int 
 #pragma unroll
     for (int c = 0; c < 8; ++c) r[c] = *(const float *)((const char *)(base + (size_t)c * plane) + off);
 }
-template <int C>
+template <int C, bool ONE>
 __device__ __forceinline__ void band_store8(unsigned char *dst, const float (&r)[8]) {
     u32x4 h, m, l;
     split3x8(r, h, m, l);
     *(u32x4 *)dst = h;
+    if (ONE) return;
     *(u32x4 *)(dst + 2 * C) = m;
     *(u32x4 *)(dst + 4 * C) = l;
 }
@@ -129,12 +132,12 @@ __device__ __forceinline__ uint32_t band_limit(size_t total, size_t base, int pl
 // filter.  Wavefront w keeps the fragments of filter tile w % (OC / 16) in registers (192 of them: one wavefront per
 // SIMD) and takes every (64 / OC)-th pixel tile, up to four at a time; the operands of the next k-block are read while
 // the current one is multiplied.
-template <int C, int OC>
-__global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__restrict__ x, const u32x4 *__restrict__ wfrag,
+template <int C, int OC, bool ONE>
+__global__ __launch_bounds__(256, ONE ? 2 : 1) void conv_band_fwd_kernel(const float *__restrict__ x, const u32x4 *__restrict__ wfrag,
                                                                const float *__restrict__ bias, float *__restrict__ y,
                                                                int nframes, const BandGeom b) {
-    constexpr int KS = 4, S = 2, KB = KS * KS * C / 32, OT = OC / 16, PG = 4 / OT, NTERM = 3;
-    constexpr int PIT = band_pitch<C>(), MAXU = BAND_MAXU;
+    constexpr int KS = 4, S = 2, KB = KS * KS * C / 32, OT = OC / 16, PG = 4 / OT, NTERM = ONE ? 1 : 3, NPROD = ONE ? 1 : 6;
+    constexpr int PIT = band_pitch<C, ONE>(), MAXU = band_maxu<ONE>();
     static_assert(C == 32 && (OC == 32 || OC == 64), "32 channels in, 32 or 64 filters");
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
 
@@ -182,7 +185,7 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
         __syncthreads();                                     // the last item's planes have been read
 #pragma unroll
         for (int i = 0; i < MAXU; ++i)
-            if (dst[i] >= 0) band_store8<C>(band_smem + dst[i], pre[i]);
+            if (dst[i] >= 0) band_store8<C, ONE>(band_smem + dst[i], pre[i]);
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
         __builtin_amdgcn_sched_barrier(0);
@@ -219,10 +222,10 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
                 __builtin_amdgcn_sched_barrier(0);
                 constexpr int PX[6] = {2, 1, 0, 1, 0, 0}, PW[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
 #pragma unroll
-                for (int q = 0; q < 6; ++q)
+                for (int q = 0; q < NPROD; ++q)
 #pragma unroll
                     for (int n = 0; n < N; ++n)
-                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[kb & 1][n][PX[q]].v, wq[kb][PW[q]].v,
+                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[kb & 1][n][PX[q] % NTERM].v, wq[kb][PW[q] % NTERM].v,
                                                                          acc[n], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -264,8 +267,7 @@ __global__ __launch_bounds__(256, 1) void conv_band_fwd_kernel(const float *__re
 // then as many bands as give every compute unit an item, in equal shares; small maps go several frames to an item
 // while there are items enough.  Returns false if not even one row fits.
 template <class Bytes, class Units>
-inline bool band_split(BandGeom &b, int nframes, int rows, int cols, Bytes bytes, Units units, int maxu = BAND_MAXU,
-                       int want = BAND_CUS) {
+inline bool band_split(BandGeom &b, int nframes, int rows, int cols, Bytes bytes, Units units, int maxu, int want) {
     auto fits = [&](int F, int R) { return bytes(F, R) <= BAND_LDS - 2048 && units(F, R) <= 256 * maxu; };
     int rmax = 0;
     while (rmax < rows && fits(1, rmax + 1)) ++rmax;
@@ -290,12 +292,11 @@ inline BandGeom band_geom(int H, int W) {
 }
 inline int band_in_px(const BandGeom &b, int F, int R) { return F * ((R - 1) * 2 + 4) * 2 * ((b.W + 1) / 2); }
 
-template <int C>
+template <int C, bool ONE>
 inline bool band_fwd_geom(BandGeom &b, int nframes) {
-    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return band_in_px(b, F, R) * band_pitch<C>(); },
-                      [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); });
+    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return (ONE ? 2 : 1) * band_in_px(b, F, R) * band_pitch<C, ONE>(); },
+                      [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); }, band_maxu<ONE>(), (ONE ? 2 : 1) * BAND_CUS);
 }
-inline int band_blocks(const BandGeom &b) { return b.items < BAND_CUS ? b.items : BAND_CUS; }
 
 template <class K>
 inline hipError_t band_allow_lds(K kernel, bool &done) {
@@ -309,20 +310,24 @@ inline hipError_t band_allow_lds(K kernel, bool &done) {
 template <int C>
 inline bool band_ok(int H, int W) {
     BandGeom b = band_geom(H, W);
-    return H >= 4 && W >= 4 && band_fwd_geom<C>(b, 1);
+    return H >= 4 && W >= 4 && band_fwd_geom<C, false>(b, 1);
 }
 
-template <int C, int OC>
-inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
+template <int C, int OC, bool ONE>
+inline hipError_t launch_conv_band_fwd1(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
     BandGeom b = band_geom(H, W);
-    if (!band_fwd_geom<C>(b, n)) return hipErrorInvalidValue;
+    if (!band_fwd_geom<C, ONE>(b, n)) return hipErrorInvalidValue;
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_fwd_kernel<C, OC>, attr);
+    const hipError_t e = band_allow_lds(conv_band_fwd_kernel<C, OC, ONE>, attr);
     if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_fwd_kernel<C, OC>), dim3(band_blocks(b)), dim3(256), band_in_px(b, b.F, b.R) * band_pitch<C>(), s, x, wfrag,
-                 bias, y, n, b);
+    ga3c::launch((conv_band_fwd_kernel<C, OC, ONE>), dim3(std::min(b.items, (ONE ? 2 : 1) * BAND_CUS)), dim3(256),
+                 band_in_px(b, b.F, b.R) * band_pitch<C, ONE>(), s, x, wfrag, bias, y, n, b);
     return hipGetLastError();
+}
+template <int C, int OC>
+inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s, int rb) {
+    if (n <= 0) return hipSuccess;
+    return rb ? launch_conv_band_fwd1<C, OC, true>(x, wfrag, bias, y, n, H, W, s) : launch_conv_band_fwd1<C, OC, false>(x, wfrag, bias, y, n, H, W, s);
 }
 
 }  // namespace ga3c

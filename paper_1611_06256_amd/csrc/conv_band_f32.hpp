@@ -40,7 +40,6 @@ constexpr int BAND_F32_LDS = 80 * 1024;           // two blocks per compute unit
 // Bound by the instruction: 640 frames, 77x77 map 281 us (379 in bands of rows that were staged in LDS, whose weights were
 // read while the tiles were multiplied and so arrived behind the next band's values), 223 without the loads, 195 the products
 // alone; 84x84 bytes with stride 1 555 (605), 484 without loads and conversions; 100 frames with stride 3 16 (24).
-// RB: both operands rounded to bfloat16.
 struct F32FwdGeom {
     int nframes, H, W, S, OH, OW;
     float scale;             // of the sums
@@ -49,7 +48,7 @@ struct F32FwdGeom {
 };
 template <class TIn> constexpr int f32_fwd_steps() { return sizeof(TIn) == 1 ? 16 : 32; }
 
-template <class TIn, int OC, int MT, bool LDSW, bool RB>
+template <class TIn, int OC, int MT, bool LDSW>
 __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kernel(const TIn *__restrict__ x, const float4 *__restrict__ w,
                                                               const float *__restrict__ bias, float *__restrict__ y, const F32FwdGeom b) {
     constexpr bool BYTE = sizeof(TIn) == 1;
@@ -96,8 +95,7 @@ __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kern
             const uint32_t q = __builtin_amdgcn_perm(d.y, d.x, sel);
             v[0] = (float)(q & 0xff); v[1] = (float)((q >> 8) & 0xff); v[2] = (float)((q >> 16) & 0xff); v[3] = (float)(q >> 24);
         } else {
-            const float4 q = RB ? bf16_rne(d) : d;
-            v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+            v[0] = d.x; v[1] = d.y; v[2] = d.z; v[3] = d.w;
         }
     };
     const TIn *base[N], *next[N];
@@ -120,8 +118,7 @@ __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kern
     } else {
 #pragma unroll
         for (int e = 0; e < C * OT / 8; ++e) {
-            const float4 v = w[512 * e + tid];
-            ws[512 * e + tid] = RB ? bf16_rne(v) : v;
+            ws[512 * e + tid] = w[512 * e + tid];
         }
     }
     float bv[MT];
@@ -160,7 +157,7 @@ __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kern
                 }
                 if constexpr (!LDSW) {
 #pragma unroll
-                    for (int m = 0; m < MT; ++m) wv[k & 1][m] = RB ? bf16_rne(wq[k][m]) : wq[k][m];
+                    for (int m = 0; m < MT; ++m) wv[k & 1][m] = wq[k][m];
                     load_w(c0 + k + A, wq[(k + A) % DEPTH]);
                 } else if (!LAST || k + 1 < DEPTH) read_w(c0 + k + 1, wv[(k + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -388,18 +385,21 @@ __global__ __launch_bounds__(64 * F32_WGRAD_WAVES, 5) void conv_f32_wgrad_kernel
     if (by == 0 && wave == (z & (NW - 1)) && lane < OC) pb[(size_t)lane * K1 + K1 - 1] = bsum;
 }
 
-template <class TIn, int OC, int MT, bool LDSW, bool RB>
+template <class TIn, int OC, int MT, bool LDSW>
 inline hipError_t launch_conv_f32_fwd1(const TIn *x, const float4 *w, const float *bias, float *y, const F32FwdGeom &b, hipStream_t s) {
     static bool attr = false;
-    const hipError_t e = LDSW ? band_allow_lds(conv_f32_fwd_kernel<TIn, OC, MT, LDSW, RB>, attr) : hipSuccess;
+    const hipError_t e = LDSW ? band_allow_lds(conv_f32_fwd_kernel<TIn, OC, MT, LDSW>, attr) : hipSuccess;
     if (e != hipSuccess) return e;
     constexpr int NW = 128 * MT / OC;
-    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW, RB>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, BAND_CUS) : b.tiles),
+    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, BAND_CUS) : b.tiles),
                  dim3(LDSW ? 512 : 4 * OC / MT), LDSW ? f32_fwd_steps<TIn>() * OC * 64 : 0, s, x, w, bias, y, b);
     return hipGetLastError();
 }
-template <class TIn, int OC, bool RB>
-inline hipError_t launch_conv_f32_fwd2(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s) {
+// x [n][32][H][W] floats -> y [n][OC][OH][OW] of the 4x4, stride-2 layer, or [n][4][H][W] bytes of the 8x8 layer of stride S;
+// w: FRAG_F32 of the filters.
+template <class TIn, int OC>
+inline hipError_t launch_conv_f32_fwd(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
     constexpr int KS = sizeof(TIn) == 1 ? 8 : 4;
     F32FwdGeom b{};
     b.nframes = n; b.H = H; b.W = W; b.S = S; b.OH = (H - KS) / S + 1; b.OW = (W - KS) / S + 1; b.scale = scale;
@@ -413,16 +413,9 @@ inline hipError_t launch_conv_f32_fwd2(const TIn *x, const float4 *w, const floa
     // 10.4 / 9.6 / 13.0, 640 12.6 / 13.6 / 12.5, 1280 20 / 16.8 / 22.6, 2560 37 / 29.5 / 28.7.  (In bands of rows staged in
     // LDS: 9.4, 9.5, 15.8, 17.5, 24.9, 34.9, 384; 13.3, 21.5, 21.6, 35.9, 52.8.)
     const int half = BAND_CUS * (128 / OC), rounds = (b.tiles + half - 1) / half;
-    if (b.tiles <= BAND_CUS) return launch_conv_f32_fwd1<TIn, OC, 1, false, RB>(x, w, bias, y, b, s);
-    if (rounds == 1 || rounds == 3) return launch_conv_f32_fwd1<TIn, OC, 1, true, RB>(x, w, bias, y, b, s);
-    return launch_conv_f32_fwd1<TIn, OC, OC == 16 ? 1 : 2, true, RB>(x, w, bias, y, b, s);
-}
-// x [n][32][H][W] floats -> y [n][OC][OH][OW] of the 4x4, stride-2 layer, or [n][4][H][W] bytes of the 8x8 layer of stride S;
-// w: FRAG_F32 of the filters.
-template <class TIn, int OC>
-inline hipError_t launch_conv_f32_fwd(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s, int rb) {
-    if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_f32_fwd2<TIn, OC, true>(x, w, bias, y, n, H, W, S, scale, s) : launch_conv_f32_fwd2<TIn, OC, false>(x, w, bias, y, n, H, W, S, scale, s);
+    if (b.tiles <= BAND_CUS) return launch_conv_f32_fwd1<TIn, OC, 1, false>(x, w, bias, y, b, s);
+    if (rounds == 1 || rounds == 3) return launch_conv_f32_fwd1<TIn, OC, 1, true>(x, w, bias, y, b, s);
+    return launch_conv_f32_fwd1<TIn, OC, OC == 16 ? 1 : 2, true>(x, w, bias, y, b, s);
 }
 
 // b.rows: rows of input that a step can touch; it covers up to R output rows and d frame boundaries.

@@ -1,6 +1,7 @@
 // First convolution layer (8x8 filters over four planes of bytes, any stride;
 // the paper's larger-network family, Sec. 5, uses 4, 3, 2 and 1): forward
-// pass of predictions on the bf16 matrix cores at fp32 accuracy.
+// pass of predictions on the bf16 matrix cores at fp32 accuracy, and of both
+// calls with operands rounded to bfloat16 (ONE: one term).
 //
 // A byte is exact in bf16 and an fp32 weight or gradient is the exact sum of
 // three bf16 terms, so a product is three bf16 products that are exact in the
@@ -47,11 +48,11 @@ __device__ __forceinline__ void bytes_store4(unsigned char *dst, const uint32_t 
 // y[oc][i][j] = max(0, scale * sum W[oc][c][u][v] x[c][S i + u][S j + v] + b[oc]).  Wavefront w keeps the fragments of
 // filter tile w % (OC / 16) in registers (96 of them) and takes every (64 / OC)-th pixel tile, four at a time; two blocks
 // share a compute unit.
-template <int OC>
+template <int OC, bool ONE>
 __global__ __launch_bounds__(256, 2) void conv_bytes_fwd_kernel(const uint8_t *__restrict__ x, const u32x4 *__restrict__ wfrag,
                                                                 const float *__restrict__ bias, float *__restrict__ y, int nframes,
                                                                 float scale, const BytesGeom b) {
-    constexpr int OT = OC / 16, PG = 4 / OT, NTERM = 3, KB = 8, MAXU = 7;
+    constexpr int OT = OC / 16, PG = 4 / OT, NTERM = ONE ? 1 : 3, KB = 8, MAXU = 7;
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -177,16 +178,20 @@ inline bool bytes_ok(int H, int W, int S) {
     return W == BYTES_W && H >= 8 && S >= 1 && (BYTES_W - 8) / S + 1 <= 128;
 }
 
-template <int OC>
-inline hipError_t launch_conv_bytes_fwd(const uint8_t *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
+template <int OC, bool ONE>
+inline hipError_t launch_conv_bytes_fwd1(const uint8_t *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s) {
     const BytesGeom b = bytes_fwd_geom(H, S, n);
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_bytes_fwd_kernel<OC>, attr);
+    const hipError_t e = band_allow_lds(conv_bytes_fwd_kernel<OC, ONE>, attr);
     if (e != hipSuccess) return e;
     const int RI = (b.R - 1) * S + 8, units = (RI * BYTES_Q + 255) / 256 * 256;
-    ga3c::launch((conv_bytes_fwd_kernel<OC>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), units * 32, s, x, wfrag, bias, y, n, scale, b);
+    ga3c::launch((conv_bytes_fwd_kernel<OC, ONE>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), units * 32, s, x, wfrag, bias, y, n, scale, b);
     return hipGetLastError();
+}
+template <int OC>
+inline hipError_t launch_conv_bytes_fwd(const uint8_t *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int S, float scale, hipStream_t s, int rb) {
+    if (n <= 0) return hipSuccess;
+    return rb ? launch_conv_bytes_fwd1<OC, true>(x, wfrag, bias, y, n, H, S, scale, s) : launch_conv_bytes_fwd1<OC, false>(x, wfrag, bias, y, n, H, S, scale, s);
 }
 
 }  // namespace ga3c
