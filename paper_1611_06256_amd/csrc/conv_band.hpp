@@ -1,22 +1,18 @@
 // The 4x4, stride-2 convolution layer with 32 input channels and 32 or 64
 // filters on maps of any size (the paper's larger-network family, Sec. 5, whose
-// maps are 9 to 77 pixels wide): forward pass of predictions on the bf16 matrix
-// cores at fp32 accuracy (updates keep one order of sums: conv_band_f32.hpp), and
-// of both calls with operands rounded to bfloat16 (ONE: one term).
+// maps are 9 to 77 pixels wide): what its kernels share, and the forward pass
+// with operands rounded to bfloat16 (at fp32 accuracy: conv_band_f32.hpp).
 //
-// A work item is a band of output rows of one frame, as many as a compute unit's LDS holds, or several whole small frames
+// A work item is a band of output rows of one frame, or several whole small frames
 // (BandGeom, chosen on the host); a block walks over items and the next item
-// travels from memory while the current one is multiplied.  Operands are split
-// into three bf16 terms (x = hi + mid + lo exactly) while they are staged, and a
-// product is evaluated as the six largest of the nine term products
-// (dense_gemm_bf16x6.hpp has the error argument).  LDS holds [pixel][term]
-// [channel], so one staging unit (8 channels of a pixel: eight loads along
-// planes, coalesced over pixels) leaves as one 16-byte store per term, and the 8
-// consecutive channels a lane feeds to an MFMA are one 16-byte read.  The pixel
-// pitch is 6 C + 16 bytes (one of lds_row_units' was level here); with stride 2
-// the even and the odd columns of an input row are stored apart, so that
-// consecutive output pixels read consecutive LDS pixels.  Filters come as
-// ready-made fragments (band_filter_fragments_kernel, once per parameter copy).
+// travels from memory while the current one is multiplied.  Operands are rounded
+// while they are staged.  LDS holds [pixel][channel], so one staging unit (8
+// channels of a pixel: eight loads along planes, coalesced over pixels) leaves as
+// one 16-byte store, and the 8 consecutive channels a lane feeds to an MFMA are
+// one 16-byte read; with stride 2 the even and the odd columns of an input row
+// are stored apart, so that consecutive output pixels read consecutive LDS
+// pixels.  Filters come as ready-made fragments (band_filter_fragments_kernel,
+// once per parameter copy).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -31,10 +27,11 @@
 
 namespace ga3c {
 
-constexpr int BAND_LDS = 160 * 1024;          // one block per compute unit
+constexpr int BAND_LDS = 160 * 1024;          // of a compute unit
+constexpr int BAND_HALF_LDS = BAND_LDS / 2;   // two blocks per compute unit: one stages while the other multiplies
 constexpr int BAND_CUS = 256;
 // staging units (8 channels of a pixel) per thread: bounds the registers of a band in flight
-template <bool ONE> constexpr int band_maxu() { return ONE ? 10 : 13; }
+constexpr int BAND_MAXU = 10;
 
 typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
@@ -50,8 +47,8 @@ struct BandGeom {
 };
 
 // LDS pixel pitch in bytes for C channels.
-template <int C, bool ONE>
-constexpr int band_pitch() { return ONE ? 16 * lds_row_units(C / 8) : 6 * C + 16; }
+template <int C>
+constexpr int band_pitch() { return 16 * lds_row_units(C / 8); }
 
 // ---------------------------------------------------------------- fragments --
 
@@ -111,14 +108,8 @@ __device__ __forceinline__ void band_load8(const float *base, uint32_t off, int 
 #pragma unroll
     for (int c = 0; c < 8; ++c) r[c] = *(const float *)((const char *)(base + (size_t)c * plane) + off);
 }
-template <int C, bool ONE>
-__device__ __forceinline__ void band_store8(unsigned char *dst, const float (&r)[8]) {
-    u32x4 h, m, l;
-    split3x8(r, h, m, l);
-    *(u32x4 *)dst = h;
-    if (ONE) return;
-    *(u32x4 *)(dst + 2 * C) = m;
-    *(u32x4 *)(dst + 4 * C) = l;
+__device__ __forceinline__ u32x4 band_round8(const float (&r)[8]) {
+    return u32x4{pack_bf16_rne(r[0], r[1]), pack_bf16_rne(r[2], r[3]), pack_bf16_rne(r[4], r[5]), pack_bf16_rne(r[6], r[7])};
 }
 // Floats left in a tensor of `total` behind `base`, less the eight planes a unit reads: the largest offset a unit may use.
 __device__ __forceinline__ uint32_t band_limit(size_t total, size_t base, int plane) {
@@ -129,15 +120,15 @@ __device__ __forceinline__ uint32_t band_limit(size_t total, size_t base, int pl
 // ------------------------------------------------------------------ forward --
 // y[oc][oy][ox] = max(0, b[oc] + sum W[oc][c][u][v] x[c][2 oy + u][2 ox + v]).
 // Pixels are the rows of the products and filters the columns, so a lane ends up with four consecutive pixels of one
-// filter.  Wavefront w keeps the fragments of filter tile w % (OC / 16) in registers (192 of them: one wavefront per
-// SIMD) and takes every (64 / OC)-th pixel tile, up to four at a time; the operands of the next k-block are read while
-// the current one is multiplied.
-template <int C, int OC, bool ONE>
-__global__ __launch_bounds__(256, ONE ? 2 : 1) void conv_band_fwd_kernel(const float *__restrict__ x, const u32x4 *__restrict__ wfrag,
+// filter.  Wavefront w keeps the fragments of filter tile w % (OC / 16) in registers (64 of them) and takes every
+// (64 / OC)-th pixel tile, up to four at a time; the operands of the next k-block are read while the current one is
+// multiplied.  640 frames of 26x26 19 us, of 77x77 181 (for 600 MB).
+template <int C, int OC>
+__global__ __launch_bounds__(256, 2) void conv_band_fwd_kernel(const float *__restrict__ x, const u32x4 *__restrict__ wfrag,
                                                                const float *__restrict__ bias, float *__restrict__ y,
                                                                int nframes, const BandGeom b) {
-    constexpr int KS = 4, S = 2, KB = KS * KS * C / 32, OT = OC / 16, PG = 4 / OT, NTERM = ONE ? 1 : 3, NPROD = ONE ? 1 : 6;
-    constexpr int PIT = band_pitch<C, ONE>(), MAXU = band_maxu<ONE>();
+    constexpr int KS = 4, S = 2, KB = KS * KS * C / 32, OT = OC / 16, PG = 4 / OT;
+    constexpr int PIT = band_pitch<C>(), MAXU = BAND_MAXU;
     static_assert(C == 32 && (OC == 32 || OC == 64), "32 channels in, 32 or 64 filters");
     extern __shared__ __attribute__((aligned(16))) unsigned char band_smem[];
 
@@ -171,21 +162,16 @@ __global__ __launch_bounds__(256, ONE ? 2 : 1) void conv_band_fwd_kernel(const f
     int item = blockIdx.x;
     fetch(min(item, b.items - 1));
 
-    Bf16x8Bits wq[KB][NTERM];
-    {
-        const u32x4 *ws = wfrag + (size_t)(ot * KB) * 3 * 64 + lane;
+    Bf16x8Bits wq[KB];                                       // the first of three terms
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-            for (int t = 0; t < NTERM; ++t) wq[kb][t].u = ws[(kb * 3 + t) * 64];
-    }
+    for (int kb = 0; kb < KB; ++kb) wq[kb].u = wfrag[(size_t)(ot * KB + kb) * 3 * 64 + lane];
     const float bv = bias[ot * 16 + l16];
 
     for (; item < b.items; item += gridDim.x) {
         __syncthreads();                                     // the last item's planes have been read
 #pragma unroll
         for (int i = 0; i < MAXU; ++i)
-            if (dst[i] >= 0) band_store8<C, ONE>(band_smem + dst[i], pre[i]);
+            if (dst[i] >= 0) *(u32x4 *)(band_smem + dst[i]) = band_round8(pre[i]);
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
         __builtin_amdgcn_sched_barrier(0);
@@ -206,27 +192,20 @@ __global__ __launch_bounds__(256, ONE ? 2 : 1) void conv_band_fwd_kernel(const f
             floatx4 acc[N];
 #pragma unroll
             for (int n = 0; n < N; ++n) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
-            Bf16x8Bits xv[2][N][NTERM];
-            auto read = [&](int kb, Bf16x8Bits (&d)[N][NTERM]) {
+            Bf16x8Bits xv[2][N];
+            auto read = [&](int kb, Bf16x8Bits (&d)[N]) {
                 const int tap = kb / (C / 32), cg = kb % (C / 32), u = tap / KS, v = tap % KS;
                 const int koff = (u * WP + (v & 1) * WH + (v >> 1)) * PIT + cg * 64;
 #pragma unroll
-                for (int n = 0; n < N; ++n)
-#pragma unroll
-                    for (int t = 0; t < NTERM; ++t) d[n][t].u = *(const u32x4 *)(band_smem + base[n] + koff + t * 2 * C);
+                for (int n = 0; n < N; ++n) d[n].u = *(const u32x4 *)(band_smem + base[n] + koff);
             };
             read(0, xv[0]);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 if (kb + 1 < KB) read(kb + 1, xv[(kb + 1) & 1]);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int PX[6] = {2, 1, 0, 1, 0, 0}, PW[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
 #pragma unroll
-                for (int q = 0; q < NPROD; ++q)
-#pragma unroll
-                    for (int n = 0; n < N; ++n)
-                        acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[kb & 1][n][PX[q] % NTERM].v, wq[kb][PW[q] % NTERM].v,
-                                                                         acc[n], 0, 0, 0);
+                for (int n = 0; n < N; ++n) acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[kb & 1][n].v, wq[kb].v, acc[n], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -292,10 +271,10 @@ inline BandGeom band_geom(int H, int W) {
 }
 inline int band_in_px(const BandGeom &b, int F, int R) { return F * ((R - 1) * 2 + 4) * 2 * ((b.W + 1) / 2); }
 
-template <int C, bool ONE>
+template <int C>
 inline bool band_fwd_geom(BandGeom &b, int nframes) {
-    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return (ONE ? 2 : 1) * band_in_px(b, F, R) * band_pitch<C, ONE>(); },
-                      [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); }, band_maxu<ONE>(), (ONE ? 2 : 1) * BAND_CUS);
+    return band_split(b, nframes, b.OH, b.OW, [&](int F, int R) { return 2 * band_in_px(b, F, R) * band_pitch<C>(); },
+                      [&](int F, int R) { return F * ((R - 1) * 2 + 4) * b.W * (C / 8); }, BAND_MAXU, 2 * BAND_CUS);
 }
 
 template <class K>
@@ -310,24 +289,21 @@ inline hipError_t band_allow_lds(K kernel, bool &done) {
 template <int C>
 inline bool band_ok(int H, int W) {
     BandGeom b = band_geom(H, W);
-    return H >= 4 && W >= 4 && band_fwd_geom<C, false>(b, 1);
+    return H >= 4 && W >= 4 && band_fwd_geom<C>(b, 1);
 }
 
-template <int C, int OC, bool ONE>
-inline hipError_t launch_conv_band_fwd1(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
-    BandGeom b = band_geom(H, W);
-    if (!band_fwd_geom<C, ONE>(b, n)) return hipErrorInvalidValue;
-    static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_fwd_kernel<C, OC, ONE>, attr);
-    if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_fwd_kernel<C, OC, ONE>), dim3(std::min(b.items, (ONE ? 2 : 1) * BAND_CUS)), dim3(256),
-                 band_in_px(b, b.F, b.R) * band_pitch<C, ONE>(), s, x, wfrag, bias, y, n, b);
-    return hipGetLastError();
-}
+// x [n][32][H][W] -> y [n][OC][OH][OW]; wfrag: FRAG_CONV of the filters.
 template <int C, int OC>
-inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s, int rb) {
+inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
     if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_fwd1<C, OC, true>(x, wfrag, bias, y, n, H, W, s) : launch_conv_band_fwd1<C, OC, false>(x, wfrag, bias, y, n, H, W, s);
+    BandGeom b = band_geom(H, W);
+    if (!band_fwd_geom<C>(b, n)) return hipErrorInvalidValue;
+    static bool attr = false;
+    const hipError_t e = band_allow_lds(conv_band_fwd_kernel<C, OC>, attr);
+    if (e != hipSuccess) return e;
+    ga3c::launch((conv_band_fwd_kernel<C, OC>), dim3(std::min(b.items, 2 * BAND_CUS)), dim3(256), band_in_px(b, b.F, b.R) * band_pitch<C>(), s, x, wfrag,
+                 bias, y, n, b);
+    return hipGetLastError();
 }
 
 }  // namespace ga3c

@@ -7,7 +7,8 @@
 // gemm_mfma.hpp (v_mfma_f32_16x16x4_f32, product t of a group of 16 k sums
 // k = 16 kb + 4 g + t over g, groups and t ascending), so activations and
 // gradients are the same bits as those of the any-shape kernels.  In the forward
-// pass of an update that matters: where a pre-activation lies within rounding of
+// pass of an update that matters (predictions run the 4x4 layers here too, the byte
+// layer on the bf16 instruction, conv_bytes.hpp): where a pre-activation lies within rounding of
 // zero, another order of the sum can put it on the other side of the rectifier,
 // and a map of millions of pixels has enough of those to move the gradient of a
 // filter by 1e-4 of itself.  The gradients decide nothing: an input gradient's
@@ -29,8 +30,6 @@
 #include "conv_bytes.hpp"
 
 namespace ga3c {
-
-constexpr int BAND_F32_LDS = 80 * 1024;           // two blocks per compute unit: one stages while the other multiplies
 
 // Forward: 4x4, stride 2, 32 channels of floats, or 8x8, any stride, four planes of bytes.  A step is 16 taps: a channel's
 // filter, or two rows of a plane's.  The weights lie in LDS as fragments; the pixels of all frames are numbered on, sixteen to
@@ -437,7 +436,7 @@ inline int f32_wgrad_stage(const F32WgradGeom &b, int OC) {      // the input's 
 // Whether a step fits the threads and half of a compute unit's LDS.
 inline bool f32_wgrad_ok(int C, int H, int W, int S, int OC) {
     const F32WgradGeom b = f32_wgrad_geom(C, H, W, S, 1, F32_WGRAD_KT, 1.f);
-    return b.rows * W <= 64 * F32_WGRAD_WAVES * F32_WGRAD_MAXX && 2 * f32_wgrad_stage(b, OC) <= BAND_F32_LDS;
+    return b.rows * W <= 64 * F32_WGRAD_WAVES * F32_WGRAD_MAXX && 2 * f32_wgrad_stage(b, OC) <= BAND_HALF_LDS;
 }
 // part [nz][OC][K + 1], nz chunks of kchunk pixels (a multiple of 16).
 template <int OC>

@@ -23,7 +23,6 @@
 
 namespace ga3c {
 
-constexpr int BAND_HALF_LDS = 80 * 1024;          // two blocks per compute unit
 constexpr int BAND_SLACK = 16;                    // floats that a row's last vector may reach past a tensor
 
 // ----------------------------------------------------------- input gradient --

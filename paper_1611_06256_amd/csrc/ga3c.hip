@@ -2033,8 +2033,8 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
         for (int l = 0; l < c->nconv; ++l) {
             if (!c->band[l]) continue;
             const ConvGeom &g = c->geom[l];
-            add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
-            if (!c->rb && c->max_train > 0) add(l, FRAG_F32, c->bfrag[i] + c->bfrag_f32[l], g.OC * g.K / 4);
+            if (l == 0 || c->rb) add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
+            if (!c->rb && (l > 0 || c->max_train > 0)) add(l, FRAG_F32, c->bfrag[i] + c->bfrag_f32[l], g.OC * g.K / 4);
             if (l > 0 && c->max_train > 0) add(l, FRAG_DGRAD, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
         }
         ga3c::launch_stop(stop, band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
@@ -2122,24 +2122,26 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
                 continue;
             }
         }
-        // Updates at fp32 accuracy run these layers on the fp32 instruction, in the any-shape kernels' order of sums
-        // (conv_band_f32.hpp says why).  Predictions take the bf16 terms: they round differently from the same frames' forward
-        // pass in an update (both within 1e-6 of the exact sums) and are faster.  With operands rounded to bfloat16 both calls take
-        // one term (640 frames of the stride-3 member, on the fp32 instruction / with one term: conv1 70 / 22, conv2
-        // 35 / 19, conv3 16 / 10 us).
+        // At fp32 accuracy the 4x4 layers run on the fp32 instruction, straight from memory, in both calls: faster than bands
+        // staged as three bf16 terms up to 256 frames (128 frames: 77x77 map 65 / 73 us, 26x26 11.8 / 12.7, 12x12 with 64 filters 6.1 /
+        // 10.2, the only loss 37x37 with 64 filters 27.9 / 24.8; one frame 4.6 / 9.8) and nearer to the exact sums (2.9e-7 /
+        // 3.3e-7).  The byte layer does so in updates only, whose activations keep the any-shape kernels' order of sums
+        // (conv_band_f32.hpp); predictions take three bf16 terms of its weights (128 frames, stride 3: 9.5 us, on the fp32
+        // instruction 19.4).  With operands rounded to bfloat16 everything takes one term (640 frames of the stride-3 member, on
+        // the fp32 instruction / with one term: conv1 70 / 22, conv2 35 / 19, conv3 16 / 10 us).
         if (c->fast && c->band[l] && is_aligned16(xin) && is_aligned16(wl)) {
             const u32x4 *wf = c->bfrag[which] + c->bfrag_fwd[l];
             const float4 *w32 = (const float4 *)(c->bfrag[which] + c->bfrag_f32[l]);
-            const bool f32 = !c->rb && keep_zv;
             if (l == 0) {
+                const bool f32 = !c->rb && keep_zv;
                 if (f32 && g.OC == 16) HIP_TRY((launch_conv_f32_fwd<uint8_t, 16>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s)));
                 else if (f32) HIP_TRY((launch_conv_f32_fwd<uint8_t, 32>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s)));
                 else if (g.OC == 16) HIP_TRY(launch_conv_bytes_fwd<16>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
                 else HIP_TRY(launch_conv_bytes_fwd<32>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
-            } else if (f32 && g.OC == 32) HIP_TRY((launch_conv_f32_fwd<float, 32>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s)));
-            else if (f32) HIP_TRY((launch_conv_f32_fwd<float, 64>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s)));
-            else if (g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s, c->rb)));
-            else HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s, c->rb)));
+            } else if (c->rb && g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
+            else if (c->rb) HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
+            else if (g.OC == 32) HIP_TRY((launch_conv_f32_fwd<float, 32>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s)));
+            else HIP_TRY((launch_conv_f32_fwd<float, 64>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s)));
             continue;
         }
         if (l == 0) {
@@ -2400,8 +2402,8 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         c->band[l] = on_band_kernels(g, l);
         if (!c->band[l]) continue;
         const size_t vecs = (size_t)3 * g.OC * g.K / 8;
-        c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs;
-        if (!c->rb && max_train_frames > 0) { c->bfrag_f32[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)g.OC * g.K / 4; }
+        if (l == 0 || c->rb) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
+        if (!c->rb && (l > 0 || max_train_frames > 0)) { c->bfrag_f32[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)g.OC * g.K / 4; }
         if (l > 0 && max_train_frames > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
     }
     if (c->bfrag_vecs)
