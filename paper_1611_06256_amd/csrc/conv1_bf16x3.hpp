@@ -130,7 +130,9 @@ __device__ __forceinline__ void bytes_to_bf16(const u32x4 b, u32x4 &lo8, u32x4 &
 // k = 8g..8g+7 share of a 16x16x32 MFMA.  The split filters stay in registers.
 // ONE: operands rounded to bfloat16 (the reduced-precision variant): one term, one product (1280 frames of 32 filters 27.9 -> 24.2 us
 // against two more terms that were zero).
-template <int OC, bool TABLE, bool ONE>
+// PARTS: blocks per frame (blockIdx.y), each with every PARTS-th group of four (pixel tile, filter tile) pairs, so that a few
+// frames keep the chip busy.
+template <int OC, bool TABLE, bool ONE, int PARTS>
 __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t *__restrict__ x,
                                                                   const uint8_t *const *__restrict__ table,
                                                                   const float *__restrict__ w,
@@ -139,8 +141,8 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
     constexpr int NTERM = ONE ? 1 : 3;
     constexpr int C = 4, H = 84, W = 84, S = 4, OW = 20, NPIX = 400, K = 256, CHW = C * H * W;
     constexpr int NV = CHW / 16, VPT = (NV + 255) / 256;           // 16-byte vectors of the byte frame
-    constexpr int OT = OC / 16, JOBS = 25 * OT, TPW = (JOBS + 3) / 4;
-    constexpr int FULL = JOBS % 4 == 0 ? TPW : TPW - 1, NLAST = JOBS - 4 * FULL;
+    constexpr int OT = OC / 16, JOBS = 25 * OT, SLOTS = 4 * PARTS, TPW = (JOBS + SLOTS - 1) / SLOTS;
+    constexpr int FULL = JOBS % SLOTS == 0 ? TPW : TPW - 1, NLAST = JOBS - SLOTS * FULL;
     static_assert(OC == 16 || OC == 32, "16 or 32 filters");
     __shared__ __attribute__((aligned(16))) __bf16 xs[VPT * 256 * 16];
 
@@ -149,7 +151,7 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
     // blocks sharing a compute unit do not load the same SIMD
     const int wave = __builtin_amdgcn_readfirstlane(((tid >> 6) + (OT == 1 ? blockIdx.x : 2 * (blockIdx.x & 1))) & 3);
     const int l16 = lane & 15, g = lane >> 4;
-    const int ot = wave % OT;
+    const int ot = wave % OT, slot = wave + (PARTS == 1 ? 0 : 4 * blockIdx.y);
 
     // my filter (row l16 of tile ot), split into three bf16 terms, 8 taps per 32-tap block
     bf16x8 wq[NTERM][8];
@@ -173,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
     int pixbase[TPW], pixidx[TPW];
 #pragma unroll
     for (int i = 0; i < TPW; ++i) {
-        const int job = wave + 4 * i;
+        const int job = slot + SLOTS * i;
         int p = (job / OT) * 16 + l16;
         pixidx[i] = (job < JOBS && p < NPIX) ? (job / OT) * 16 + 4 * g : -1;       // first of my four output pixels
         if (p >= NPIX) p = 0;
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(256, 2) void conv1_bf16x3_fwd_kernel(const uint8_t 
         for (int kb = 0; kb < 8; ++kb)
 #pragma unroll
             for (int i = 0; i < FULL; ++i) tile_step(i, kb);
-        if (NLAST > 0 && wave < NLAST) {
+        if (NLAST > 0 && slot < NLAST) {
 #pragma unroll
             for (int kb = 0; kb < 8; ++kb) tile_step(TPW - 1, kb);
         }
@@ -251,9 +253,15 @@ inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const uint8_t *const
                                           float scale, hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
     const int grid = nframes < 512 ? nframes : 512;
-    auto go = [&](auto kernel) { ga3c::launch(kernel, dim3(grid), dim3(256), 0, s, x, table, w, bias, y, nframes, scale); };
-    if (table) rb ? go(conv1_bf16x3_fwd_kernel<OC, true, true>) : go(conv1_bf16x3_fwd_kernel<OC, true, false>);
-    else rb ? go(conv1_bf16x3_fwd_kernel<OC, false, true>) : go(conv1_bf16x3_fwd_kernel<OC, false, false>);
+    auto go = [&](auto kernel, int parts) { ga3c::launch(kernel, dim3(grid, parts), dim3(256), 0, s, x, table, w, bias, y, nframes, scale); };
+    auto pick = [&](auto parts) {
+        constexpr int P = decltype(parts)::value;
+        if (table) rb ? go(conv1_bf16x3_fwd_kernel<OC, true, true, P>, P) : go(conv1_bf16x3_fwd_kernel<OC, true, false, P>, P);
+        else rb ? go(conv1_bf16x3_fwd_kernel<OC, false, true, P>, P) : go(conv1_bf16x3_fwd_kernel<OC, false, false, P>, P);
+    };
+    // four blocks per frame while one per compute unit has room (32 filters: 1 frame 8.0 -> 5.4 us, 64 frames 9.7 -> 6.8)
+    if (OC == 32 && 4 * nframes <= 256) pick(std::integral_constant<int, OC == 32 ? 4 : 1>{});
+    else pick(std::integral_constant<int, 1>{});
     return hipGetLastError();
 }
 

@@ -103,10 +103,12 @@ __global__ __launch_bounds__(256) void conv_fwd_filter_fragments_kernel(const fl
     conv_fwd_filter_fragments_thread<SP, DGRAD>(w, wfrag, blockIdx.x * 256 + threadIdx.x);
 }
 
-// NW wavefronts per block (4 or 8).  ONE: operands rounded to bfloat16 (the reduced-precision variant): one term,
+// NW wavefronts per block (4 or 8).  OTB: filter tiles per block; blockIdx.y takes the others, so that a few frames keep the
+// chip busy (conv2 and conv3 on average, four / two / one: 16 frames 10.0 / - / 6.3 us, 64 10.6 / - / 6.7, 128 11.1 / 8.6; the
+// same sums).  ONE: operands rounded to bfloat16 (the reduced-precision variant): one term,
 // one product.  DGRAD: x = dY [SP::C][SP::H - 2 PAD][SP::W - 2 PAD], w = the layer's filters [SP::C][SP::OC][KS][KS],
 // aux = the layer's input (ReLU mask), y = dX; otherwise aux = bias.
-template <class SP, int NW, bool ONE, bool DGRAD>
+template <class SP, int NW, bool ONE, bool DGRAD, int OTB>
 __global__ __launch_bounds__(64 * NW, ONE ? 2 : 1) void conv_fwd_bf16x6_kernel(const float *__restrict__ x, const float *__restrict__ w,
                                                                      const float *__restrict__ aux, float *__restrict__ y,
                                                                      int nframes, const u32x4 *__restrict__ wfrag) {
@@ -116,7 +118,7 @@ __global__ __launch_bounds__(64 * NW, ONE ? 2 : 1) void conv_fwd_bf16x6_kernel(c
     constexpr int C = SP::C, HW = SP::H * SP::W, KS = SP::KS, S = SP::S, OW = SP::OW, NPIX = SP::NPIX;
     constexpr int CG = G::CG, KB = G::KB, NT = G::NT, PIT = G::PIT, PLANE = G::PLANE;
     constexpr int NTERM = ONE ? 1 : 3, NTHR = 64 * NW;
-    constexpr int PG = NW / 4, TPW = (NT + PG - 1) / PG;           // pixel groups; pixel tiles per wavefront
+    constexpr int PG = NW / OTB, TPW = (NT + PG - 1) / PG;         // pixel groups; pixel tiles per wavefront
     static_assert(!DGRAD || S == 1, "input gradient: stride 1 only");
     constexpr int PAD = DGRAD ? KS - 1 : 0;
     constexpr int SH = SP::H - 2 * PAD, SW = SP::W - 2 * PAD, SHW = SH * SW;  // the frame as it sits in memory
@@ -126,7 +128,7 @@ __global__ __launch_bounds__(64 * NW, ONE ? 2 : 1) void conv_fwd_bf16x6_kernel(c
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, g = lane >> 4;
-    const int ot = wave % 4, pg = wave / 4;
+    const int ot = (OTB == 4 ? 0 : blockIdx.y * OTB) + wave % OTB, pg = wave / OTB;
 
     // the first frame is asked for before the filters are prepared
     int src_off[DPT], dst_off[DPT];
@@ -279,20 +281,25 @@ inline hipError_t launch_conv_bf16x6_impl(const float *x, const float *w, const 
     const int grid = nframes < blocks ? nframes : blocks;
     static bool attr_set = false;          // once per layer shape: let the kernels use more than 64 KB of LDS
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(false));
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_fwd_bf16x6_kernel<SP, NW, true, DGRAD>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(true));
+        hipError_t e = hipSuccess;
+        auto allow = [&](auto kernel, bool one) {
+            if (e == hipSuccess) e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(one));
+        };
+        allow(conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD, 4>, false);
+        allow(conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD, 2>, false);
+        allow(conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD, 1>, false);
+        allow(conv_fwd_bf16x6_kernel<SP, NW, true, DGRAD, 4>, true);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    if (rb)
-        ga3c::launch((conv_fwd_bf16x6_kernel<SP, NW, true, DGRAD>), dim3(grid), dim3(64 * NW), G::lds_bytes(true), s, x, w,
-                           aux, y, nframes, wfrag);
-    else
-        ga3c::launch((conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD>), dim3(grid), dim3(64 * NW), G::lds_bytes(false), s, x,
-                           w, aux, y, nframes, wfrag);
+    auto go = [&](auto kernel, int slices, bool one) {
+        ga3c::launch(kernel, dim3(grid, slices), dim3(64 * NW), G::lds_bytes(one), s, x, w, aux, y, nframes, wfrag);
+    };
+    // Few frames: as many blocks per frame as the chip has room for.
+    if (rb) go(conv_fwd_bf16x6_kernel<SP, NW, true, DGRAD, 4>, 1, true);
+    else if (4 * nframes <= blocks) go(conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD, 1>, 4, false);
+    else if (2 * nframes <= blocks) go(conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD, 2>, 2, false);
+    else go(conv_fwd_bf16x6_kernel<SP, NW, false, DGRAD, 4>, 1, false);
     return hipGetLastError();
 }
 
