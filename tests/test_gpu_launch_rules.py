@@ -268,3 +268,52 @@ def test_updates_in_place_give_the_same_parameters(G, which):
     for other in got[1:]:
         for x, y in zip(got[0], other):
             np.testing.assert_array_equal(x, y)
+
+
+# four, two blocks per frame and one in the larger net's convolutions (up to 64 and 128 frames), four and one in its first layer (up to 64)
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 129])
+def test_larger_net_convolutions_have_the_same_bits_with_several_blocks_per_frame(G, n):
+    import torch
+    A, B = 6, 260
+    desc = G.LARGE_NET(A)
+    net = G.Ga3c(desc, B, B)
+    net.params_init(7821)
+    frames = torch.from_numpy(synth.uniform_frames(7822, (B, 1, 4, 84, 84))).cuda()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(7823, B, 1, A).items()}
+
+    def convolutions(k):
+        print(f"train {k} frames", flush=True)
+        net.train_step(frames[:k], tr["actions"][:k], tr["rewards"][:k], tr["dones"][:k], None, G.HParams(lr=0.0))
+        acts = [net.train_debug_get(4 + l, torch.empty(k * m, device="cuda")).clone() for l, m in enumerate((32 * 400, 64 * 81, 64 * 49))]
+        return acts, [net.train_debug_get(10 + l, torch.empty(k * m, device="cuda")).clone() for l, m in enumerate((32 * 400, 64 * 81, 64 * 49))]
+
+    (whole, dwhole), (part, dpart) = convolutions(B), convolutions(n)
+    torch.cuda.synchronize()
+    for l in range(3):
+        assert float(part[l].abs().max()) > 0 and torch.equal(whole[l][:part[l].numel()], part[l]), f"layer {l + 1}"
+    for l in (2, 1):       # what the fc layer sends back, and the last layer's input gradient
+        assert float(dpart[l].abs().max()) > 0 and torch.equal(dwhole[l][:dpart[l].numel()], dpart[l]), f"input gradient of layer {l + 2}"
+    net.close()
+
+
+# heads with a block per frame (up to 256 frames) and four frames per block
+@pytest.mark.parametrize("F,A", [(256, 18), (256, 3), (512, 15), (512, 16), (512, 63), (1024, 6)])
+def test_predictions_have_the_same_heads_with_one_and_four_frames_per_block(G, F, A):
+    import torch
+    B = 264
+    net = G.Ga3c(G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=A), B, 0)
+    net.params_init(7831)
+    # 256 frames take one block each; of 264 the same chunks of the fc product are added up
+    frames = torch.from_numpy(synth.uniform_frames(7832, (B, 4, 84, 84))).cuda()
+    out = [[torch.full((B, A), float("nan"), device="cuda"), torch.full((B,), float("nan"), device="cuda")] for _ in range(2)]
+    u = torch.from_numpy(synth.uniforms(7833, B)).cuda()
+    acts = [torch.full((B,), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+    print(f"predict F={F} A={A}", flush=True)
+    net.predict(frames, logits=out[0][0], values=out[0][1], uniforms=u, actions=acts[0])
+    for lo, hi in ((0, 132), (132, 264)):
+        net.predict(frames[lo:hi], logits=out[1][0][lo:hi], values=out[1][1][lo:hi], uniforms=u[lo:hi], actions=acts[1][lo:hi])
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.isfinite(a).all() and float((a - b).abs().max() / a.abs().max()) <= 2e-6       # other chunks of k: rounding of fp32 sums
+    assert float((acts[0] != acts[1]).float().mean()) <= 0.01
+    net.close()
