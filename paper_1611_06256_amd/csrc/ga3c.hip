@@ -306,11 +306,13 @@ inline int heads_loads(int F, int nz, const void *ws, const void *fcb, const voi
     if (F % 4 != 0 || !ws || (((uintptr_t)ws | (uintptr_t)fcb | (uintptr_t)h | (uintptr_t)Wp) & 15) != 0) return LOADS_SCALAR;
     return nz <= 8 ? LOADS_VEC8 : LOADS_VEC16;
 }
-template <int NT, int NF, int CH, int IP>
+// meanwhile(): called once by every thread, also where it has no output, between the first requests and their use.
+template <int NT, int NF, int CH, int IP, class Meanwhile>
 __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int tid, const int b0, const int nf,
                                                 const float *__restrict__ ws, int nz, const float *__restrict__ fcb,
                                                 float *__restrict__ h, int B, int F, int F4, int WP, int A,
-                                                const float *__restrict__ Wp, const float *__restrict__ Wv, int rb, const FastDiv dFQ) {
+                                                const float *__restrict__ Wp, const float *__restrict__ Wv, int rb, const FastDiv dFQ,
+                                                Meanwhile meanwhile) {
     constexpr int WQ = 8, WVQ = 2;
     const int FQ = F >> 2, nwq = A * FQ, nit = NF * FQ;
     const size_t stride4 = (size_t)B * FQ;
@@ -320,7 +322,7 @@ __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int
     for (int j = 0; j < WQ; ++j) wv4[j] = ((const float4 *)Wp)[min(j * NT + tid, nwq - 1)];
 #pragma unroll
     for (int j = 0; j < WVQ; ++j) wv[j] = Wv[min(j * NT + tid, F - 1)];
-    for (int it0 = tid; it0 < nit; it0 += IP * NT) {
+    for (int it0 = tid; it0 == tid || it0 < nit; it0 += IP * NT) {
         // output it of the block is vector b0 * FQ + it of a chunk's sums
         const float4 *src = (const float4 *)ws + (size_t)b0 * FQ;
         float4 bias[IP], acc[IP];
@@ -344,6 +346,7 @@ __device__ __forceinline__ void heads_load_vec4(float *hs, float *wsh, const int
                         for (int j = i; j < i + 4; ++j) v[p][j] = (src + (size_t)min(z + j, nz - 1) * stride4)[off[p]];
                 }
             __builtin_amdgcn_sched_barrier(0);
+            if (z == 0 && it0 == tid) meanwhile();
 #pragma unroll
             for (int i = 0; i < CH; i += 4)
                 if (z + i < nz) {
@@ -410,7 +413,7 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict_
     heads_zero_padding<NT>(wsh, tid, F, WP, A + 1);
     const int nw = (A + 1) * F;                 // Wp [A][F] and Wv [F] are adjacent in LDS, not in global memory
     constexpr bool vec4 = LOADS != LOADS_SCALAR;
-    if (vec4) heads_load_vec4<NT, 4, LOADS == LOADS_VEC8 ? 8 : 16, LOADS == LOADS_VEC8 ? 2 : 1>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+    if (vec4) heads_load_vec4<NT, 4, LOADS == LOADS_VEC8 ? 8 : 16, LOADS == LOADS_VEC8 ? 2 : 1>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ, [] {});
     for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * NT) {
         float wv[24];
 #pragma unroll
@@ -1259,21 +1262,21 @@ __global__ __launch_bounds__(256) void heads_dgrad_kernel(const float *__restric
 // kernel, for HD_FRAMES frames per block.  (1) last step of the split-k fc layer:
 // h = max(0, bias + sum_z ws[z]); (2) heads: z = W h + b; (3) n-step returns
 // (text after Eq. 1), loss and its gradient w.r.t. the head outputs (Eq. 1, 2,
-// 5), one thread per (frame, action), sums taken in action order so that they
-// do not depend on the thread layout; (4) heads backward: dh = [h > 0] dz W,
+// 5), a wavefront per frame with an output per lane, sums taken in action order;
+// (4) heads backward: dh = [h > 0] dz W,
 // and the block's shares of the heads' weight and bias gradients (wpart
 // [block][A+1][F+1]) and of the fc bias gradient (colpart [block][F]): a
 // thread takes VK consecutive k and every fourth output, so that weights,
 // activations and gradients move as vectors; the four partial sums of dh meet in
 // LDS.
 // What it takes is one block's chain of steps (us since its start, 40 frames of 256
-// units, 27 chunks of partial sums: operands in LDS 6.2, dots 7.3, returns and loss
-// 10.5, end 13.5), and in the long ones of them the block's instructions and its
-// requests to memory, each of which occupies a wavefront for a hundred cycles.  So a
-// block has eight wavefronts where the launch leaves compute units idle: 14.9 -> 12.9 us
-// (40 frames), 512 units 26.6 -> 19.5 (40 frames), 21.3 -> 17.8 (1280).  With more than
-// 1024 frames of 256 units four of them with vectors of four are as good (update of
-// 1280 frames 157.6 us against 158.9, 2560: 258.0 / 260.2).
+// units, 27 chunks of partial sums: operands in LDS 5.0, dots 5.9, returns and loss
+// 8.3, end 11.0; with four barriers and a thread per (frame, action) the loss ended at
+// 9.4), and in the long ones of them the block's instructions and its requests to
+// memory, each of which occupies a wavefront for a hundred cycles; hence eight
+// wavefronts.  Launches, with loss by threads of four or eight wavefronts / now: 40 frames
+// 13.9 / 13.4, 640 in segments of unequal length 13.9 / 12.1, 1050 13.6 / 12.0, 2560
+// 17.9 / 18.1, in unequal segments 19.1 / 17.8, 1280 frames of 512 units 18.7 / 17.2.
 // Writes h, zv, R, dzv (kept for inspection), dh, colpart, wpart and three loss
 // sums per block.  rb: operands of every product rounded to bfloat16.
 // Dynamic LDS: heads_train_lds_floats(F, A) floats.
@@ -1281,18 +1284,15 @@ __host__ __device__ inline int heads_train_kparts(int F, int A) {
     const int kp = 256 / (A + 1), nk = heads_f4(F) / 4;
     return kp < nk ? kp : nk;
 }
-// Threads of a block, and k per thread in the backward part (a pass over 256 or 512 units); see there for the line.
-struct HeadsTrainShape { int threads, vk; };
-inline HeadsTrainShape heads_train_shape(int F, int B) {
-    return HeadsTrainShape{F > 256 || B <= 1024 ? 512 : 256, F > 256 ? 4 : B <= 1024 ? 2 : 4};
-}
+constexpr int HEADS_TRAIN_THREADS = 64 * HD_FRAMES;
+inline int heads_train_vk(int F) { return F > 256 ? 4 : 2; }      // k per thread in the backward part: a pass over 256 or 512 units
 __host__ __device__ inline int heads_train_lds_floats(int F, int A) {
     return HD_FRAMES * heads_f4(F) + (A + 1) * (heads_f4(F) + 4) + HD_FRAMES * (F > 256 ? 2048 : 1024) + (A + 1) * HD_FRAMES +
-           3 * HD_FRAMES * heads_f4(A + 1) + HD_FRAMES * (A + 1) * heads_train_kparts(F, A) + 512;
+           4 * HD_FRAMES + HD_FRAMES * (A + 1) * heads_train_kparts(F, A) + 512;
 }
 
-template <int LOADS, int NT, int VK>
-__global__ __launch_bounds__(NT) void heads_train_kernel(
+template <int LOADS, int VK>
+__global__ __launch_bounds__(HEADS_TRAIN_THREADS) void heads_train_kernel(
     const float *__restrict__ ws, int nz, const float *__restrict__ fcb, int B, int F, int A,
     const float *__restrict__ Wp, const float *__restrict__ bp, const float *__restrict__ Wv, const float *__restrict__ bv,
     const int32_t *__restrict__ actions, const float *__restrict__ rewards, const uint8_t *__restrict__ dones,
@@ -1301,20 +1301,18 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
     float *__restrict__ dh, float *__restrict__ colpart, float *__restrict__ wpart, float *__restrict__ losspart, int rb,
     const FastDiv dFQ, const FastDiv dA1, const FastDiv dKP, const FastDiv dT, const ga3c::FcDhPlanes dhp) {
     extern __shared__ __attribute__((aligned(16))) float sm[];
-    constexpr int NF = HD_FRAMES, KPASS = NT / 4 * VK;      // k of a pass of the backward part
+    constexpr int NT = HEADS_TRAIN_THREADS, NF = HD_FRAMES, KPASS = NT / 4 * VK;      // k of a pass of the backward part
     const int F4 = heads_f4(F), WP = F4 + 4, A1 = A + 1, KP = (int)dKP.d;
-    const int ZR = heads_f4(A1);             // row pitch of the per-(frame, output) arrays: rows start on 16 bytes
     float *hs = sm;                          // [NF][F4]   fc output of my frames (rounded if rb)
     float *wsh = hs + NF * F4;               // [A1][WP]   head weights (rounded if rb)
     float *red = wsh + A1 * WP;              // [4][NF][KPASS] partial sums of dh, one set per quarter of the outputs
     float *zt = red + 4 * NF * KPASS;          // [A1][NF]   gradients of the head outputs, transposed
-    float *zs = zt + A1 * NF;                // [NF][ZR]   head outputs, later their gradients
-    float *ex = zs + NF * ZR;                // [NF][ZR]   exp / per-action terms
-    float *tm = ex + NF * ZR;                // [NF][ZR]   per-action terms
-    float *zp = tm + NF * ZR;                // [NF][A1][KP] partial dots
+    float *ls = zt + A1 * NF;                // [3][NF]    loss terms of my frames
+    float *zp = ls + 4 * NF;                 // [NF][A1][KP] partial dots
     float *rw = zp + NF * A1 * KP;           // [256]      rewards of the agents my frames belong to
     float *dn = rw + 256;                    // [256]      1 - done
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b0 = blockIdx.x * NF;
     const int nf = min(NF, B - b0);
 
@@ -1325,14 +1323,28 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
     const size_t at_rw = rw_lds ? (size_t)n0 * T + min(tid, nrw - 1) : 0;
     const float my_rw = rewards[at_rw];
     const uint32_t my_done = dones[at_rw];
-    uint32_t tq, tr;
-    dA1.divmod((uint32_t)tid, tq, tr);
-    const int ofb = min((int)tq, nf - 1), oa = (int)tr;     // thread tid < nf*A1 owns output oa of frame ofb
-    const bool mine = tid < nf * A1;
-    const int ob = b0 + ofb;
-    const float obias = oa < A ? bp[oa] : bv[0];
+    // the loss of a frame is one wavefront's, lane a has output a
+    const int ob = b0 + min(wave, nf - 1);
+    const float obias = lane < A ? bp[lane] : bv[0];
     const int oact = actions[ob];
-    const float oboot = bootstrap && !seg_start ? bootstrap[dT.div((uint32_t)ob)] : 0.f;
+    float oboot = bootstrap && !seg_start ? bootstrap[dT.div((uint32_t)ob)] : 0.f;
+    // Segments of unequal length: a frame's own (ragged_return says how), and its rewards from there on, a step per lane.  The
+    // search goes through the scalar cache while the partial sums are on their way.
+    int send = 0;
+    float srw = 0.f, sdn = 0.f;
+    auto segments = [&]() __attribute__((always_inline)) {
+        if (!seg_start) return;
+        int lo = 0, hi = N - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (seg_start[mid] <= ob) lo = mid; else hi = mid - 1;
+        }
+        send = min(seg_start[lo + 1], B);
+        oboot = bootstrap ? bootstrap[lo] : 0.f;
+        const int at = min(ob + lane, B - 1);
+        srw = rewards[at];
+        sdn = dones[at] ? 0.f : 1.f;
+    };
     for (int e = tid; e < NF * (F4 - F); e += NT) hs[(e / (F4 - F)) * F4 + F + e % (F4 - F)] = 0.f;
     heads_zero_padding<NT>(wsh, tid, F, WP, A1);
     const int nw = A1 * F;
@@ -1341,7 +1353,7 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
     // output as many as the 27 that the small net's updates of at most 320 frames leave, in whole fours; with two outputs 28 would be
     // 224 registers of the 256 that eight wavefronts leave each, 20 are 160.
     constexpr int IP = VK == 2 ? 1 : 2, CH = LOADS == LOADS_VEC8 ? 8 : VK == 2 ? 28 : 20;
-    if (vec4) heads_load_vec4<NT, NF, CH, IP>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ);
+    if constexpr (vec4) heads_load_vec4<NT, NF, CH, IP>(hs, wsh, tid, b0, nf, ws, nz, fcb, h, B, F, F4, WP, A, Wp, Wv, rb, dFQ, segments);
     for (int e0 = 0; !vec4 && (e0 < nw || e0 == 0); e0 += 24 * NT) {
         float wv[24];
 #pragma unroll
@@ -1384,6 +1396,7 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
             if (e < nw) wsh[(e / F) * WP + e % F] = rb ? bf16_rne(wv[j]) : wv[j];
         }
     }
+    if constexpr (!vec4) segments();
     if (rw_lds && tid < nrw) { rw[tid] = my_rw; dn[tid] = my_done ? 0.f : 1.f; }
     __syncthreads();
 
@@ -1413,107 +1426,62 @@ __global__ __launch_bounds__(NT) void heads_train_kernel(
         }
     }
     __syncthreads();
-    float z = 0.f;
-    if (mine) {
-        const float *q = zp + (ofb * A1 + oa) * KP;
-        for (int kp = 0; kp < KP; ++kp) z += q[kp];
+    // ---- loss and dL/dz.  Sums over the parts and over the actions run in index order; no barrier until they are done (five, with
+    // a thread per (frame, output) of the block: 3.5 us of an update of 40 frames, 2.4 now).
+    float dzo = 0.f;
+    if (wave < nf) {
+        float z = 0.f;
+        const float *part = zp + (wave * A1 + min(lane, A)) * KP;
+        for (int kp = 0; kp < KP; ++kp) z += part[kp];
         z += obias;
-        zv[(size_t)ob * A1 + oa] = z;
-        zs[ofb * ZR + oa] = z;
-    }
-    // ---- n-step return of my frame (threads with oa == A: one per frame)
-    float Rt = 0.f;
-    if (mine && oa == A) {
-        const int n = (int)dT.div((uint32_t)ob), t = ob - n * T;
-        float next = oboot;
+        // n-step return
+        float Rt = oboot;
         if (seg_start) {
-            next = ragged_return(rewards, dones, seg_start, bootstrap, N, B, ob, gamma);
-        } else if (rw_lds) {
-            for (int tt = T - 1; tt >= t; --tt) { const int j = (n - n0) * T + tt; next = rw[j] + gamma * dn[j] * next; }
+            for (int j = send - 1; j >= ob + 64; --j) Rt = rewards[j] + gamma * (dones[j] ? 0.f : 1.f) * Rt;
+            for (int j = min(send - ob, 64) - 1; j >= 0; --j) Rt = lane_f32(srw, j) + gamma * lane_f32(sdn, j) * Rt;
         } else {
-            for (int tt = T - 1; tt >= t; --tt) {
-                const size_t j = (size_t)n * T + tt;
-                next = rewards[j] + gamma * (dones[j] ? 0.f : 1.f) * next;
-            }
+            const int n = (int)dT.div((uint32_t)ob), t = ob - n * T;
+            if (rw_lds)
+                for (int tt = T - 1; tt >= t; --tt) { const int j = (n - n0) * T + tt; Rt = rw[j] + gamma * dn[j] * Rt; }
+            else
+                for (int tt = T - 1; tt >= t; --tt) {
+                    const size_t j = (size_t)n * T + tt;
+                    Rt = rewards[j] + gamma * (dones[j] ? 0.f : 1.f) * Rt;
+                }
         }
-        Rt = next;
-        R[ob] = next;
-        tm[ofb * ZR + A] = next;             // the policy threads of the frame read it from here
-    }
-    __syncthreads();
-    // ---- loss and dL/dz, thread (frame, action); sums over the actions run in index order
-    const bool pol = mine && oa < A;
-    // rows are read four values at a time; sums still add one value after the other, in index order
-    const float *zr = zs + ofb * ZR;
-    float zmax = 0.f, e = 0.f;
-    if (pol) {
-        zmax = zr[0];
-        for (int j = 0; j < A; j += 4) {
-            const float4 q = *(const float4 *)(zr + j);
-            zmax = fmaxf(zmax, q.x);
-            if (j + 1 < A) zmax = fmaxf(zmax, q.y);
-            if (j + 2 < A) zmax = fmaxf(zmax, q.z);
-            if (j + 3 < A) zmax = fmaxf(zmax, q.w);
-        }
-        e = expf(z - zmax);
-        ex[ofb * ZR + oa] = e;
-    }
-    __syncthreads();
-    float p = 0.f, lg = 0.f, r = 1.f, adv = 0.f;
-    if (mine) {
-        const float V = zr[A];
-        adv = tm[ofb * ZR + A] - V;
-    }
-    if (pol) {
+        const bool pol = lane < A;
+        const float adv = Rt - lane_f32(z, A), zmax = wave_max(pol ? z : lane_f32(z, 0));
+        const float e = expf(z - zmax);
         float S = 0.f;
-        for (int j = 0; j < A; j += 4) {
-            const float4 q = *(const float4 *)(ex + ofb * ZR + j);
-            S += q.x;
-            if (j + 1 < A) S += q.y;
-            if (j + 2 < A) S += q.z;
-            if (j + 3 < A) S += q.w;
-        }
+        for (int j = 0; j < A; ++j) S += lane_f32(e, j);
         const float logS = logf(S), invS = 1.f / S;
-        p = e * invS;
+        const float p = e * invS;
+        float lg, r;
         if (eps == 0.f) { lg = z - zmax - logS; r = 1.f; }
         else { lg = logf(p + eps); r = p / (p + eps); }
-    }
-    __syncthreads();                                  // every exp has been read
-    if (pol) {
-        ex[ofb * ZR + oa] = p * lg;                   // -H terms
-        tm[ofb * ZR + oa] = p * beta * (lg + r);      // dot terms
-    }
-    __syncthreads();
-    float dzo = 0.f, s_pl = 0.f, s_vl = 0.f, s_en = 0.f;
-    // the thread of the action taken publishes its lg and r
-    if (pol && oa == oact) { dn[ofb * 2] = lg; dn[ofb * 2 + 1] = r; }      // (rw, dn are free again by now)
-    __syncthreads();
-    if (mine) {
+        const float ent = p * lg, trm = p * beta * (lg + r);
         float H = 0.f, dot = 0.f;
-        for (int j = 0; j < A; j += 4) {
-            const float4 q = *(const float4 *)(ex + ofb * ZR + j), u = *(const float4 *)(tm + ofb * ZR + j);
-            H -= q.x; dot += u.x;
-            if (j + 1 < A) { H -= q.y; dot += u.y; }
-            if (j + 2 < A) { H -= q.z; dot += u.z; }
-            if (j + 3 < A) { H -= q.w; dot += u.w; }
-        }
+        for (int j = 0; j < A; ++j) { H -= lane_f32(ent, j); dot += lane_f32(trm, j); }
         const bool known = (unsigned)oact < (unsigned)A;
-        const float lga = known ? dn[ofb * 2] : 0.f, ra = known ? dn[ofb * 2 + 1] : 1.f;
+        const int taken = __builtin_amdgcn_readfirstlane(known ? oact : 0);
+        const float lga = known ? lane_f32(lg, taken) : 0.f, ra = known ? lane_f32(r, taken) : 1.f;
         dot -= adv * ra;
-        if (oa < A) dzo = p * (beta * (lg + r) - dot) - (oa == oact ? adv * ra : 0.f);
-        else {
-            dzo = -2.f * cv * adv;
-            s_pl = -lga * adv; s_vl = adv * adv; s_en = H;
+        if (pol) dzo = p * (beta * (lg + r) - dot) - (lane == oact ? adv * ra : 0.f);
+        else dzo = -2.f * cv * adv;
+        if (lane < A1) {
+            zv[(size_t)ob * A1 + lane] = z;
+            dzv[(size_t)ob * A1 + lane] = dzo;
         }
-        dzv[(size_t)ob * A1 + oa] = dzo;
+        if (lane == 0) {
+            R[ob] = Rt;
+            ls[wave] = -lga * adv; ls[NF + wave] = adv * adv; ls[2 * NF + wave] = H;
+        }
     }
-    // the gradients go to zt[output][frame] (zero for frames the block does not have) for the backward pass
-    if (tid < NF * A1) zt[oa * NF + (int)tq] = mine ? (rb ? bf16_rne(dzo) : dzo) : 0.f;
-    // loss sums of the block, frames in order (threads oa == A hold them)
-    if (mine && oa == A) { rw[ofb] = s_pl; rw[NF + ofb] = s_vl; rw[2 * NF + ofb] = s_en; }
+    // zt[output][frame] for the backward pass, zero for frames the block does not have
+    if (lane < A1) zt[lane * NF + wave] = rb ? bf16_rne(dzo) : dzo;
     __syncthreads();
     if (tid < 3) {
-        const float *src = rw + tid * NF;
+        const float *src = ls + tid * NF;
         float sum = 0.f;
         for (int fb = 0; fb < nf; ++fb) sum += src[fb];
         losspart[3 * blockIdx.x + tid] = sum;
@@ -2737,17 +2705,15 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         const int nblk = cdiv(B, HD_FRAMES);
         float *part = region((size_t)nblk * (A + 1) * (F + 1));
         if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (heads)");
-        typedef decltype(&heads_train_kernel<LOADS_SCALAR, 256, 4>) HeadsTrain;
-        static const HeadsTrain ht_kernels[9] = {
-            heads_train_kernel<LOADS_SCALAR, 256, 4>, heads_train_kernel<LOADS_VEC8, 256, 4>, heads_train_kernel<LOADS_VEC16, 256, 4>,
-            heads_train_kernel<LOADS_SCALAR, 512, 2>, heads_train_kernel<LOADS_VEC8, 512, 2>, heads_train_kernel<LOADS_VEC16, 512, 2>,
-            heads_train_kernel<LOADS_SCALAR, 512, 4>, heads_train_kernel<LOADS_VEC8, 512, 4>, heads_train_kernel<LOADS_VEC16, 512, 4>};
-        static size_t ht_lds_set[9] = {};
-        const HeadsTrainShape shape = heads_train_shape(F, B);
-        const int ht = heads_loads(F, w.fc_nz, w.fc_ws, th + c->off[nb + 1], w.h, Wp) + (shape.threads == 256 ? 0 : shape.vk == 2 ? 3 : 6);
+        typedef decltype(&heads_train_kernel<LOADS_SCALAR, 2>) HeadsTrain;
+        static const HeadsTrain ht_kernels[6] = {heads_train_kernel<LOADS_SCALAR, 2>, heads_train_kernel<LOADS_VEC8, 2>, heads_train_kernel<LOADS_VEC16, 2>,
+                                                 heads_train_kernel<LOADS_SCALAR, 4>, heads_train_kernel<LOADS_VEC8, 4>, heads_train_kernel<LOADS_VEC16, 4>};
+        static size_t ht_lds_set[6] = {0, 0, 0, 0, 0, 0};
+        const int vk = heads_train_vk(F);
+        const int ht = heads_loads(F, w.fc_nz, w.fc_ws, th + c->off[nb + 1], w.h, Wp) + (vk == 2 ? 0 : 3);
         HIP_TRY(allow_dynamic_lds((const void *)ht_kernels[ht], ht_lds, ht_lds_set[ht]));
         STAGE("heads_train", 6.0 * B * (A + 1) * F, 4.0 * (w.fc_nz + 1) * B * F);
-        ga3c::launch(ht_kernels[ht], dim3(nblk), dim3(shape.threads), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
+        ga3c::launch(ht_kernels[ht], dim3(nblk), dim3(HEADS_TRAIN_THREADS), ht_lds, s, w.fc_ws, w.fc_nz, th + c->off[nb + 1], B, F, A, Wp,
                            th + c->off[nb + 3], Wv, th + c->off[nb + 5], actions, rewards, dones, bootstrap, seg_start, N, T, hp->gamma, hp->beta,
                            hp->value_coef, hp->log_eps, w.h, w.zv, c->R, c->dzv, c->dh, c->colpart, part, losspart, c->rb,
                            FastDiv(std::max(1, F / 4)), FastDiv(A + 1), FastDiv(heads_train_kparts(F, A)), FastDiv(T), c->dhp);

@@ -320,3 +320,33 @@ def test_predictions_have_the_same_heads_with_one_and_four_frames_per_block(G, F
         assert torch.isfinite(a).all() and float((a - b).abs().max() / a.abs().max()) <= 2e-6       # other chunks of k: rounding of fp32 sums
     assert float((acts[0] != acts[1]).float().mean()) <= 0.01
     net.close()
+
+
+# segments longer than a wavefront's lanes hold the rewards of (64), as long, and shorter; units in fours and not, several
+# frames of a block beyond the last, one output and the most that the fused kernel has
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 150])
+@pytest.mark.parametrize("F,A", [(12, 6), (13, 1), (260, 31)])
+def test_ragged_update_of_equal_segments_is_the_rectangular_one(G, T, F, A):
+    import torch
+    N = 3
+    desc = G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=A)
+    frames = torch.from_numpy(synth.uniform_frames(7841, (N, T, 4, 84, 84))).cuda()
+    tr = synth.trajectories(7842, N, T, A)
+    ac, rw, dn = (torch.from_numpy(tr[k]).cuda() for k in ("actions", "rewards", "dones"))
+    boot = torch.from_numpy(synth.rng(7843).standard_normal(N).astype(np.float32)).cuda()
+    print(f"train T={T} F={F} A={A}", flush=True)
+    out = []
+    for ragged in (False, True):
+        net = G.Ga3c(desc, 4, N * T)
+        net.params_init(7844)
+        if ragged:
+            start = torch.from_numpy(np.arange(N + 1, dtype=np.int32) * T).cuda()
+            net.train_step_ragged(frames.reshape(N * T, 4, 84, 84), ac.reshape(-1), rw.reshape(-1), dn.reshape(-1), start, boot, G.HParams())
+        else:
+            net.train_step(frames, ac, rw, dn, boot, G.HParams())
+        torch.cuda.synchronize()
+        out.append((net.params_get(0).cpu().numpy(), net.params_get(2).cpu().numpy(), net.train_debug_get(0, torch.empty(N * T, device="cuda")).cpu().numpy()))
+        net.close()
+    for x, y in zip(*out):
+        assert np.isfinite(x).all()
+        np.testing.assert_array_equal(x, y)
