@@ -288,6 +288,41 @@ def test_batches_of_any_size_match_direct_calls(G, which, math):
     sched.close(); ns.close(); nd.close()
 
 
+@pytest.mark.parametrize("nan", [False, True])
+def test_polled_results_are_this_batch_s_and_complete(G, nan):
+    # results are taken from host memory as they arrive, in slots that are used again and again: one launch for the whole
+    # network, heads with a block per frame and with four frames per block, more than one batch in flight; values that are no numbers
+    import time
+    import torch
+    N, cap = 300, 300
+    (ns, nd), frames, _, u = setup(G, 60, 5, 2070, max_pred=cap, max_train=10)
+    frames = frames.view(N, 4, 84, 84); u = u.reshape(N)
+    if nan:
+        theta = torch.full((ns.n_params,), float("nan"), device="cuda")
+        for n in (ns, nd):
+            n.params_set(theta, 0)
+    sched = G.Scheduler(ns, G.HParams(), t_max=5, predict_cap=100, train_min=5, train_cap=10)
+    rng = np.random.default_rng(2071)
+    for n in (1, 64, 100, 65, 300, 2, 101, 40, 200, 3):
+        who = rng.permutation(N)[:n].astype(np.int32)
+        sched.submit_predict_many(who, np.uint64(frames.data_ptr()) + who.astype(np.uint64) * np.uint64(4 * 84 * 84), u[who])
+        got, until = {}, time.monotonic() + 20
+        while len(got) < n:
+            assert time.monotonic() < until, f"{len(got)} of {n} results"
+            sched.tick()
+            a, act, val = sched.poll_arrays()
+            got.update(zip(a.tolist(), zip(act.tolist(), val.tolist())))
+        print(f"n={n} done", flush=True)
+        for lo in range(0, n, 100):                  # the batches that the cap makes of them
+            part = who[lo:lo + 100]
+            v, _, act = direct_predict(nd, frames[torch.from_numpy(part.astype(np.int64)).cuda()], u[part])
+            np.testing.assert_array_equal([got[i][0] for i in part], act)
+            np.testing.assert_array_equal(np.float32([got[i][1] for i in part]), v)
+    sched.close()
+    for n in (ns, nd):
+        n.close()
+
+
 def test_scheduler_host_code_is_clean_under_the_address_and_undefined_behaviour_sanitizers():
     # paper_1611_06256_amd/sched_sanitized (built beforehand by build.py / the entry point's build()) is the whole
     # library with its HOST code under ASan and UBSan plus tests/sched_sanitizer_driver.cpp: a closed loop of agents with
