@@ -33,6 +33,17 @@ constexpr int BAND_CUS = 256;
 // staging units (8 channels of a pixel) per thread: bounds the registers of a band in flight
 constexpr int BAND_MAXU = 10;
 
+// Which outputs of a layer of 32 filters are positive: a byte for four pixels of a filter, four filters to a plane: the byte of
+// pixels 4 q .. 4 q + 3, counted through all frames, and filter o lies at `at` + o / 4 * `plane` + 4 q + o % 4, bit i for pixel
+// 4 q + i.  That is how a lane of the forward pass has them, and what a lane of the input gradient wants, a pixel and its right
+// neighbour of four filters, are eight bytes in one place.  at == nullptr: none.
+struct PositiveBits {
+    uint8_t *at = nullptr;
+    size_t plane = 0;
+    static size_t plane_of(size_t pixels) { return (pixels + 15) / 16 * 16 + 16; }      // whole tiles, and the last pixels' neighbours
+    static constexpr int PLANES = 8;
+};
+
 typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
 

@@ -47,9 +47,10 @@ struct F32FwdGeom {
 };
 template <class TIn> constexpr int f32_fwd_steps() { return sizeof(TIn) == 1 ? 16 : 32; }
 
-template <class TIn, int OC, int MT, bool LDSW>
+template <class TIn, int OC, int MT, bool LDSW, bool BITS>
 __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kernel(const TIn *__restrict__ x, const float4 *__restrict__ w,
-                                                              const float *__restrict__ bias, float *__restrict__ y, const F32FwdGeom b) {
+                                                              const float *__restrict__ bias, float *__restrict__ y, const F32FwdGeom b,
+                                                              const PositiveBits bits) {
     constexpr bool BYTE = sizeof(TIn) == 1;
     constexpr int C = f32_fwd_steps<TIn>(), OT = OC / 16, DEPTH = BYTE ? 8 : 16;
     typedef typename std::conditional<BYTE, uint2, float4>::type Vec;
@@ -120,6 +121,7 @@ __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kern
             ws[512 * e + tid] = w[512 * e + tid];
         }
     }
+    const uint32_t bit_off = BITS ? (uint32_t)(l16 >> 2) * (uint32_t)bits.plane + 4 * g + (l16 & 3) : 0u;
     float bv[MT];
 #pragma unroll
     for (int m = 0; m < MT; ++m) bv[m] = bias[(ot + m) * 16 + l16];
@@ -190,6 +192,12 @@ __global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kern
                 for (int r = 0; r < 4; ++r) {
                     v[r] = BYTE ? acc[n][m][r] * b.scale + bv[m] : acc[n][m][r] + bv[m];
                     v[r] = v[r] > 0.f ? v[r] : 0.f;
+                }
+                if constexpr (BITS) {                 // behind the rectifier a value is positive if its bits are not all zero
+                    uint32_t q = 0;
+#pragma unroll
+                    for (int r = 3; r >= 0; --r) q = 2 * q + min(__float_as_uint(v[r]), 1u);
+                    (bits.at + (size_t)(ot + m) * 4 * bits.plane + (size_t)(t + NW * n) * 16)[bit_off] = (uint8_t)q;
                 }
                 if ((int)rem + 3 < NPIX && p0 + 3 < npix) {
                     *(f32x4_dw *)(y + ((size_t)f * OC + (ot + m) * 16 + l16) * NPIX + rem) = f32x4_dw{v[0], v[1], v[2], v[3]};
@@ -384,20 +392,27 @@ __global__ __launch_bounds__(64 * F32_WGRAD_WAVES, 5) void conv_f32_wgrad_kernel
     if (by == 0 && wave == (z & (NW - 1)) && lane < OC) pb[(size_t)lane * K1 + K1 - 1] = bsum;
 }
 
-template <class TIn, int OC, int MT, bool LDSW>
-inline hipError_t launch_conv_f32_fwd1(const TIn *x, const float4 *w, const float *bias, float *y, const F32FwdGeom &b, hipStream_t s) {
+template <class TIn, int OC, int MT, bool LDSW, bool BITS>
+inline hipError_t launch_conv_f32_fwd2(const TIn *x, const float4 *w, const float *bias, float *y, const PositiveBits &bits, const F32FwdGeom &b, hipStream_t s) {
     static bool attr = false;
-    const hipError_t e = LDSW ? band_allow_lds(conv_f32_fwd_kernel<TIn, OC, MT, LDSW>, attr) : hipSuccess;
+    const hipError_t e = LDSW ? band_allow_lds(conv_f32_fwd_kernel<TIn, OC, MT, LDSW, BITS>, attr) : hipSuccess;
     if (e != hipSuccess) return e;
     constexpr int NW = 128 * MT / OC;
-    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, BAND_CUS) : b.tiles),
-                 dim3(LDSW ? 512 : 4 * OC / MT), LDSW ? f32_fwd_steps<TIn>() * OC * 64 : 0, s, x, w, bias, y, b);
+    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW, BITS>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, BAND_CUS) : b.tiles),
+                 dim3(LDSW ? 512 : 4 * OC / MT), LDSW ? f32_fwd_steps<TIn>() * OC * 64 : 0, s, x, w, bias, y, b, bits);
     return hipGetLastError();
 }
+template <class TIn, int OC, int MT, bool LDSW>
+inline hipError_t launch_conv_f32_fwd1(const TIn *x, const float4 *w, const float *bias, float *y, const PositiveBits &bits, const F32FwdGeom &b, hipStream_t s) {
+    if constexpr (OC == 32)
+        if (bits.at) return launch_conv_f32_fwd2<TIn, OC, MT, LDSW, true>(x, w, bias, y, bits, b, s);
+    return launch_conv_f32_fwd2<TIn, OC, MT, LDSW, false>(x, w, bias, y, bits, b, s);
+}
 // x [n][32][H][W] floats -> y [n][OC][OH][OW] of the 4x4, stride-2 layer, or [n][4][H][W] bytes of the 8x8 layer of stride S;
-// w: FRAG_F32 of the filters.
+// w: FRAG_F32 of the filters; bits (OC == 32): also written, if given.
 template <class TIn, int OC>
-inline hipError_t launch_conv_f32_fwd(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s) {
+inline hipError_t launch_conv_f32_fwd(const TIn *x, const float4 *w, const float *bias, float *y, int n, int H, int W, int S, float scale, hipStream_t s,
+                                      const PositiveBits &bits = {}) {
     if (n <= 0) return hipSuccess;
     constexpr int KS = sizeof(TIn) == 1 ? 8 : 4;
     F32FwdGeom b{};
@@ -412,9 +427,9 @@ inline hipError_t launch_conv_f32_fwd(const TIn *x, const float4 *w, const float
     // 10.4 / 9.6 / 13.0, 640 12.6 / 13.6 / 12.5, 1280 20 / 16.8 / 22.6, 2560 37 / 29.5 / 28.7.  (In bands of rows staged in
     // LDS: 9.4, 9.5, 15.8, 17.5, 24.9, 34.9, 384; 13.3, 21.5, 21.6, 35.9, 52.8.)
     const int half = BAND_CUS * (128 / OC), rounds = (b.tiles + half - 1) / half;
-    if (b.tiles <= BAND_CUS) return launch_conv_f32_fwd1<TIn, OC, 1, false>(x, w, bias, y, b, s);
-    if (rounds == 1 || rounds == 3) return launch_conv_f32_fwd1<TIn, OC, 1, true>(x, w, bias, y, b, s);
-    return launch_conv_f32_fwd1<TIn, OC, OC == 16 ? 1 : 2, true>(x, w, bias, y, b, s);
+    if (b.tiles <= BAND_CUS) return launch_conv_f32_fwd1<TIn, OC, 1, false>(x, w, bias, y, bits, b, s);
+    if (rounds == 1 || rounds == 3) return launch_conv_f32_fwd1<TIn, OC, 1, true>(x, w, bias, y, bits, b, s);
+    return launch_conv_f32_fwd1<TIn, OC, OC == 16 ? 1 : 2, true>(x, w, bias, y, bits, b, s);
 }
 
 // b.rows: rows of input that a step can touch; it covers up to R output rows and d frame boundaries.

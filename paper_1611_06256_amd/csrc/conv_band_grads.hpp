@@ -23,6 +23,7 @@
 
 namespace ga3c {
 
+typedef uint32_t u32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
 constexpr int BAND_SLACK = 16;                    // floats that a row's last vector may reach past a tensor
 
 // ----------------------------------------------------------- input gradient --
@@ -30,7 +31,9 @@ constexpr int BAND_SLACK = 16;                    // floats that a row's last ve
 // x = 2 ix + rx: a contraction over (a, e, oc) on the stride-phase grid.  LDS holds the zero-padded dY as
 // [pixel][term][oc]; wavefront = (channel tile, ry) and keeps the fragments of both rx, so the two products of a pixel
 // share its operands and a lane ends up with two neighbouring columns of four channels: mask and result move as pairs.
-// The mask of a tile is on its way while the tile is multiplied.  The five smaller products of all k-blocks come first: their
+// The mask of a tile is on its way while the tile is multiplied.  BITS: it comes as the bits that the forward pass of an update has
+// left (PositiveBits) instead of the floats, which on a 77x77 map were 486 of the 1084 MB that 640 frames move: 304 -> 211 us,
+// 37x37 with 64 filters 116 -> 110; what the forward pass pays for them: 84x84 bytes 543 -> 560, 77x77 map 245 -> 250.  The five smaller products of all k-blocks come first: their
 // sum is rounded 2^-8 finer than the result, so only the largest products' additions round it (relative error against 64
 // bits 5e-8; 1.4e-7 with the six products of a k-block in turn, as with the fp32 instruction).
 // 640 frames, 77x77 map: 303 us for 1.08 GB of dY, mask and dX (498 with the fp32 instruction); 37x37 and 64 filters 115
@@ -43,9 +46,9 @@ constexpr int band_dgrad_maxu() { return OC == 32 ? 6 : 13; }
 struct BandDgradDivs {
     FastDiv px, ow, rl;      // by the pixels of dY that an item stages, by OW, by R + 1
 };
-template <int OC, bool ONE>
+template <int OC, bool ONE, bool BITS>
 __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(const float *__restrict__ dy, const u32x4 *__restrict__ wfrag,
-                                                                                const float *__restrict__ xin, float *__restrict__ dx,
+                                                                                const float *__restrict__ xin, const PositiveBits bits, float *__restrict__ dx,
                                                                                 int nframes, const BandGeom b, const BandDgradDivs d) {
     constexpr int C = 32, CGS = OC / 32, KB = 4 * CGS, MAXU = band_dgrad_maxu<OC>(), PIT = band_dgrad_pitch<OC, ONE>();
     constexpr int NTERM = ONE ? 1 : 3, NMAX = 2, YB = OC == 32 && !ONE ? 1 : 2;
@@ -110,13 +113,17 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
         __builtin_amdgcn_sched_barrier(0);
         const int cnt = b.F * b.R * GW, ntile = (cnt + 15) / 16;
         const float *mb = xin + ((size_t)f0 * C + ct * 16 + 4 * g) * HW;
+        const size_t pixel0 = (size_t)f0 * HW;
+        const uint8_t *pb = bits.at + (size_t)(ct * 4 + g) * bits.plane + pixel0 / 4 * 4;
+        const uint32_t first = pixel0 & 3;
         float *db = dx + ((size_t)f0 * C + ct * 16 + 4 * g) * HW;
         auto pass = [&](auto nc, int t0) {
             constexpr int N = decltype(nc)::value;
             int base[N];
             uint32_t out[N];
             bool in[N], two[N];
-            f32x2_dw mk[N][4];
+            f32x2_dw mk[BITS ? 1 : N][4];
+            uint32_t pos[BITS ? N : 1][2];                   // of four filters: bit 8 r for my pixel, and for its neighbour
 #pragma unroll
             for (int n = 0; n < N; ++n) {
                 uint32_t p = (uint32_t)((t0 + n) * 16 + l16), f, rem, i, j;
@@ -129,7 +136,12 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
                 in[n] = ok && f0 + (int)f < nframes && yr < b.H;
                 two[n] = 2 * (int)j + 1 < b.W;
                 out[n] = in[n] ? f * (uint32_t)(C * HW) + (uint32_t)(yr * b.W + 2 * (int)j) : 0u;
-                // the last column of an odd map is the second of the pair in front of it
+                if constexpr (BITS) {
+                    const uint32_t at = first + (in[n] ? f * (uint32_t)HW + (uint32_t)(yr * b.W + 2 * (int)j) : 0u), i4 = at & 3;
+                    const u32x2_dw q = *(const u32x2_dw *)(pb + (at & ~3u));
+                    pos[n][0] = q.x >> i4;
+                    pos[n][1] = i4 == 3 ? q.y : q.x >> (i4 + 1);
+                } else                                       // the last column of an odd map is the second of the pair in front of it
 #pragma unroll
                 for (int r = 0; r < 4; ++r) mk[n][r] = *(const f32x2_dw *)(mb + (size_t)r * HW + out[n] - (in[n] && !two[n] ? 1 : 0));
             }
@@ -178,9 +190,11 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         float *o = db + (size_t)r * HW + out[n];
-                        const f32x2_dw m = mk[n][r];
-                        if (two[n]) *(f32x2_dw *)o = f32x2_dw{m.x > 0.f ? acc[n][0][r] : 0.f, m.y > 0.f ? acc[n][1][r] : 0.f};
-                        else o[0] = m.y > 0.f ? acc[n][0][r] : 0.f;
+                        bool m0, m1;
+                        if constexpr (BITS) { m0 = pos[n][0] >> 8 * r & 1; m1 = pos[n][1] >> 8 * r & 1; }
+                        else { m0 = (two[n] ? mk[n][r].x : mk[n][r].y) > 0.f; m1 = mk[n][r].y > 0.f; }
+                        if (two[n]) *(f32x2_dw *)o = f32x2_dw{m0 ? acc[n][0][r] : 0.f, m1 ? acc[n][1][r] : 0.f};
+                        else o[0] = m0 ? acc[n][0][r] : 0.f;
                     }
                 }
         };
@@ -197,23 +211,27 @@ inline bool band_dgrad_geom(BandGeom &b, int nframes) {
                       [&](int F, int R) { return F * (R + 1) * (GW + 1) * band_dgrad_pitch<OC, ONE>() <= lds ? 0 : 2 * BAND_LDS; },
                       [&](int F, int R) { return F * (R + 1) * b.OW * (OC / 8); }, band_dgrad_maxu<OC>(), (OC == 32 ? 2 : 1) * BAND_CUS);
 }
-template <int OC, bool ONE>
-inline hipError_t launch_conv_band_dgrad1(const float *dy, const u32x4 *wfrag, const float *xin, float *dx, int n, int H, int W, hipStream_t s) {
+template <int OC, bool ONE, bool BITS>
+inline hipError_t launch_conv_band_dgrad1(const float *dy, const u32x4 *wfrag, const float *xin, const PositiveBits &bits, float *dx, int n, int H, int W, hipStream_t s) {
     BandGeom b = band_geom(H, W);
     if (!band_dgrad_geom<OC, ONE>(b, n)) return hipErrorInvalidValue;
     static bool attr = false;
-    const hipError_t e = band_allow_lds(conv_band_dgrad_kernel<OC, ONE>, attr);
+    const hipError_t e = band_allow_lds(conv_band_dgrad_kernel<OC, ONE, BITS>, attr);
     if (e != hipSuccess) return e;
-    ga3c::launch((conv_band_dgrad_kernel<OC, ONE>), dim3(std::min(b.items, (OC == 32 ? 2 : 1) * BAND_CUS)), dim3(256),
-                 b.F * (b.R + 1) * (b.cols + 1) * band_dgrad_pitch<OC, ONE>(), s, dy, wfrag, xin, dx, n, b,
+    ga3c::launch((conv_band_dgrad_kernel<OC, ONE, BITS>), dim3(std::min(b.items, (OC == 32 ? 2 : 1) * BAND_CUS)), dim3(256),
+                 b.F * (b.R + 1) * (b.cols + 1) * band_dgrad_pitch<OC, ONE>(), s, dy, wfrag, xin, bits, dx, n, b,
                  BandDgradDivs{FastDiv((uint32_t)(b.F * (b.R + 1) * b.OW)), FastDiv((uint32_t)b.OW), FastDiv((uint32_t)(b.R + 1))});
     return hipGetLastError();
 }
-// dy [n][OC][OH][OW] -> dx [n][32][H][W], masked by xin > 0; wfrag: FRAG_DGRAD of w [OC][32][4][4].
+// dy [n][OC][OH][OW] -> dx [n][32][H][W], masked by xin > 0, or by its bits where the forward pass has left them; wfrag: FRAG_DGRAD
+// of w [OC][32][4][4].
 template <int OC>
-inline hipError_t launch_conv_band_dgrad(const float *dy, const u32x4 *wfrag, const float *xin, float *dx, int n, int H, int W, hipStream_t s, int rb) {
+inline hipError_t launch_conv_band_dgrad(const float *dy, const u32x4 *wfrag, const float *xin, const PositiveBits &bits, float *dx, int n, int H, int W,
+                                         hipStream_t s, int rb) {
     if (n <= 0) return hipSuccess;
-    return rb ? launch_conv_band_dgrad1<OC, true>(dy, wfrag, xin, dx, n, H, W, s) : launch_conv_band_dgrad1<OC, false>(dy, wfrag, xin, dx, n, H, W, s);
+    return rb        ? launch_conv_band_dgrad1<OC, true, false>(dy, wfrag, xin, bits, dx, n, H, W, s)
+           : bits.at ? launch_conv_band_dgrad1<OC, false, true>(dy, wfrag, xin, bits, dx, n, H, W, s)
+                     : launch_conv_band_dgrad1<OC, false, false>(dy, wfrag, xin, bits, dx, n, H, W, s);
 }
 
 // --------------------------------------------------------- weight gradients --

@@ -106,6 +106,9 @@ struct Work {            // activations of one call; predict and train own one e
     size_t ws_floats = 0;
     const float *fc_ws = nullptr;   // where the last forward left the fc partial sums, and how many
     int fc_nz = 1;
+    // which conv outputs are positive, where the next layer's input gradient wants bits, and whether this forward pass has left them
+    PositiveBits bits[GA3C_MAX_CONV];
+    bool bits_set[GA3C_MAX_CONV] = {false, false, false, false};
 };
 
 }  // namespace
@@ -1999,11 +2002,17 @@ inline void pick_split_xcd(int tiles, int K, int &nz, int &kchunk, int target = 
     nz = (K + kchunk - 1) / kchunk;
 }
 
-int alloc_work(Work &w, const ga3c_ctx *c, int cap) {
+int alloc_work(Work &w, const ga3c_ctx *c, int cap, bool training) {
     w.cap = cap;
     if (cap <= 0) return GA3C_OK;
     for (int l = 0; l < c->nconv; ++l)
         HIP_TRY(hipMalloc(&w.act[l], sizeof(float) * ((size_t)cap * c->geom[l].OC * c->geom[l].OHW + BAND_SLACK)));
+    // layers of 32 filters whose forward pass in updates is conv_f32_fwd_kernel and whose gradient comes from conv_band_dgrad_kernel
+    for (int l = 0; training && !c->rb && l + 1 < c->nconv; ++l)
+        if (c->band[l] && c->band[l + 1]) {
+            w.bits[l].plane = PositiveBits::plane_of((size_t)cap * c->geom[l].OHW);
+            HIP_TRY(hipMalloc(&w.bits[l].at, PositiveBits::PLANES * w.bits[l].plane));
+        }
     HIP_TRY(hipMalloc(&w.h, sizeof(float) * (size_t)cap * c->F));
     HIP_TRY(hipMalloc(&w.zv, sizeof(float) * (size_t)cap * (c->A + 1)));
     return GA3C_OK;
@@ -2011,7 +2020,7 @@ int alloc_work(Work &w, const ga3c_ctx *c, int cap) {
 
 void free_work(Work &w) {
     (void)hipFree(w.ws);
-    for (int l = 0; l < GA3C_MAX_CONV; ++l) (void)hipFree(w.act[l]);
+    for (int l = 0; l < GA3C_MAX_CONV; ++l) { (void)hipFree(w.act[l]); (void)hipFree(w.bits[l].at); }
     (void)hipFree(w.h);
     (void)hipFree(w.zv);
 }
@@ -2104,6 +2113,7 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     const float *th = c->theta2[which];
     const int nb = 2 * c->nconv;
     int first = 0;
+    std::fill(w.bits_set, w.bits_set + GA3C_MAX_CONV, false);
     if (c->fast && c->small_predict && c->ticket && c->cfrag[which] && is_aligned16(frames) && !keep_zv && with_heads && B <= SP_MAX_FRAMES &&
         c->nconv == 2 && c->F == SP_FC && c->flat == SP_FLAT && is_aligned16(th + c->off[nb + 1]) && is_aligned16(th + c->off[nb + 2])) {
         // a handful of frames: one launch for the whole network, in about as many blocks as there are compute units
@@ -2177,15 +2187,16 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         if (c->fast && c->band[l] && is_aligned16(xin) && is_aligned16(wl)) {
             const u32x4 *wf = c->bfrag[which] + c->bfrag_fwd[l];
             const float4 *w32 = (const float4 *)(c->bfrag[which] + c->bfrag_f32[l]);
+            w.bits_set[l] = w.bits[l].at != nullptr;
             if (l == 0) {
                 const bool f32 = !c->rb && keep_zv;
                 if (f32 && g.OC == 16) HIP_TRY((launch_conv_f32_fwd<uint8_t, 16>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s)));
-                else if (f32) HIP_TRY((launch_conv_f32_fwd<uint8_t, 32>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s)));
+                else if (f32) HIP_TRY((launch_conv_f32_fwd<uint8_t, 32>(frames, w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f / 255.f, s, w.bits[l])));
                 else if (g.OC == 16) HIP_TRY(launch_conv_bytes_fwd<16>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
                 else HIP_TRY(launch_conv_bytes_fwd<32>(frames, wf, bl, w.act[l], B, g.H, g.S, 1.f / 255.f, s, c->rb));
             } else if (c->rb && g.OC == 32) HIP_TRY((launch_conv_band_fwd<32, 32>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
             else if (c->rb) HIP_TRY((launch_conv_band_fwd<32, 64>(w.act[l - 1], wf, bl, w.act[l], B, g.H, g.W, s)));
-            else if (g.OC == 32) HIP_TRY((launch_conv_f32_fwd<float, 32>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s)));
+            else if (g.OC == 32) HIP_TRY((launch_conv_f32_fwd<float, 32>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s, w.bits[l])));
             else HIP_TRY((launch_conv_f32_fwd<float, 64>(w.act[l - 1], w32, bl, w.act[l], B, g.H, g.W, g.S, 1.f, s)));
             continue;
         }
@@ -2481,8 +2492,8 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
             if (e != hipSuccess) guard(fail(GA3C_EHIP, "hipMemset: %s", hipGetErrorString(e)));
         }
     }
-    if (rc == GA3C_OK) guard(alloc_work(c->pred, c, max_predict_batch));
-    if (rc == GA3C_OK) guard(alloc_work(c->train, c, max_train_frames));
+    if (rc == GA3C_OK) guard(alloc_work(c->pred, c, max_predict_batch, false));
+    if (rc == GA3C_OK) guard(alloc_work(c->train, c, max_train_frames, true));
     if (rc == GA3C_OK && max_train_frames > 0) {
         const size_t B = (size_t)max_train_frames;
         for (int l = 0; l < c->nconv && rc == GA3C_OK; ++l)
@@ -2900,8 +2911,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         STAGE(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W));
         if (c->fast && c->band[l]) {
             const u32x4 *wf = c->bfrag[cur] + c->bfrag_dgrad[l];
-            if (g.OC == 32) HIP_TRY(launch_conv_band_dgrad<32>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
-            else HIP_TRY(launch_conv_band_dgrad<64>(c->dact[l], wf, w.act[l - 1], c->dact[l - 1], B, g.H, g.W, s, c->rb));
+            const PositiveBits bits = w.bits_set[l - 1] ? w.bits[l - 1] : PositiveBits{};
+            if (g.OC == 32) HIP_TRY(launch_conv_band_dgrad<32>(c->dact[l], wf, w.act[l - 1], bits, c->dact[l - 1], B, g.H, g.W, s, c->rb));
+            else HIP_TRY(launch_conv_band_dgrad<64>(c->dact[l], wf, w.act[l - 1], bits, c->dact[l - 1], B, g.H, g.W, s, c->rb));
             continue;
         }
         if (c->fast && spec_matches<SpecL3>(g, false)) {

@@ -111,3 +111,30 @@ def test_gradients_do_not_meet_what_an_earlier_larger_batch_left(G):
 def test_training_activations_are_the_any_shape_kernels_bits_across_the_launch_rules(G, n):
     # the second layer's 9 n tiles of 64 filters: a block per tile, one filter tile per wavefront, two, and one again with more rounds
     test_training_activations_are_the_any_shape_kernels_bits(G, dict(in_h=84, conv=((32, 8, 3), (64, 4, 2))), n)
+
+
+@pytest.mark.parametrize("shape,n", [(SHAPES[0], 7), (SHAPES[0], 1), (dict(in_h=84, conv=((32, 8, 3), (32, 4, 2), (64, 4, 2))), 5),
+                                     (dict(in_h=36, conv=((32, 8, 9), (64, 4, 2))), 300)])
+def test_masks_as_bits_are_the_masks_as_values(G, shape, n):
+    # frames that are not 16-byte aligned go through the any-shape kernel of the first layer, which has the same sums and leaves no
+    # bits: the input gradient of the second layer then takes its mask from the activations
+    import torch
+    desc = G.NetDesc(in_c=4, in_w=84, fc_units=32, n_actions=4, **shape)
+    fr = np.tile(frames_of(9401, min(n, 20), desc.in_h), (-(-n // min(n, 20)), 1, 1, 1))[:n]
+    room = torch.empty(fr.size + 4, dtype=torch.uint8, device="cuda")
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9402, n, 1, 4).items()}
+    h, w = (desc.in_h - desc.conv[0][1]) // desc.conv[0][2] + 1, (84 - desc.conv[0][1]) // desc.conv[0][2] + 1
+    got = []
+    for shift in (0, 4):
+        x = room[shift:shift + fr.size].view(n, 1, 4, desc.in_h, 84)
+        x.copy_(torch.from_numpy(fr).view(n, 1, 4, desc.in_h, 84))
+        net = G.Ga3c(desc, n, n)
+        net.params_init(9403)
+        print(f"n={n} shift={shift}", flush=True)
+        net.train_step(x, tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.0))
+        got.append([net.train_debug_get(which, torch.empty(n * 32 * h * w, device="cuda")) for which in (4, 10)])
+        torch.cuda.synchronize()
+        net.close()
+    for a, b in zip(*got):
+        assert float(a.abs().max()) > 0 and torch.equal(a, b)
+    assert bool(((got[0][0] > 0) | (got[0][1] == 0)).all()) and bool((got[0][0] == 0).any())
