@@ -36,7 +36,7 @@ struct FcForwardArgs {
     int kchunk, nz;                           // k is cut into nz chunks of kchunk; K and kchunk are multiples of 32
     FastDiv tiles, cols;                      // row x column tiles of a chunk; column tiles
     const float *x;                           // [M][K]
-    const u32x4 *w;                           // [N / 16][K / 32][16 rows][terms][32 k] bf16
+    const u32x4 *w;                           // [N / 16][K / 32][terms][16 rows][32 k] bf16
     float *part;                              // [nz][M][N]
 };
 
@@ -48,16 +48,18 @@ struct FcPlanes {
     FastDiv row;                              // by K / 4
 };
 // Vector i of the tensor.  A row's 32 k of a block lie together (64 bytes a term), so the threads that update them, eight in a
-// row, write whole memory sectors; the order in which a lane takes them would scatter them by 16 bytes.
+// row, write whole memory sectors; the order in which a lane takes them would scatter them by 16 bytes.  The sixteen rows of a
+// term follow each other, so that a load of a wavefront is 1 KB without gaps (640 x 1024 x 18496: 159 -> 149 us; with a row's
+// three terms together it was sixteen pieces of 64 bytes).
 __device__ __forceinline__ void fc_planes_store4(const FcPlanes &p, unsigned i, const float4 v) {
     const unsigned o = p.row.div(i), q = i - o * p.row.d;
-    unsigned char *dst = (unsigned char *)p.w + ((((size_t)(o >> 4) * p.kblocks + (q >> 3)) * 16 + (o & 15)) * p.terms * 64 + (q & 7) * 8);
+    unsigned char *dst = (unsigned char *)p.w + (size_t)(((o >> 4) * p.kblocks + (q >> 3)) * p.terms) * 1024 + ((o & 15) * 64 + (q & 7) * 8);
     uint2 t[3];
     split3_pair(v.x, v.y, t[0].x, t[1].x, t[2].x);
     split3_pair(v.z, v.w, t[0].y, t[1].y, t[2].y);
 #pragma unroll
     for (int k = 0; k < 3; ++k)
-        if (k < p.terms) *(uint2 *)(dst + 64 * k) = t[k];
+        if (k < p.terms) *(uint2 *)(dst + 1024 * k) = t[k];
 }
 __global__ __launch_bounds__(256) void fc_planes_kernel(const float4 *__restrict__ theta, const FcPlanes p) {
     const unsigned i = blockIdx.x * 256 + threadIdx.x;
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void fc_forward_kernel(const FcForwardArgs 
     }
     const unsigned char *xk = (const unsigned char *)(p.x + kbeg);
     const unsigned char *wk = (const unsigned char *)(p.w + ((size_t)(n0 / 16 + wave) * (p.K / 32) + kbeg / 32) * (NTERM * 64));
-    const uint32_t woff = l16 * (NTERM * 64) + g * 16;
+    const uint32_t woff = l16 * 64 + g * 16;
     const uint32_t lds = lds_address(fc_smem);
     auto issue = [&](int kb, int slot) {
         const uint32_t at = lds + slot * (XB + WB);
@@ -102,7 +104,7 @@ __global__ __launch_bounds__(256, 2) void fc_forward_kernel(const FcForwardArgs 
         for (int i = 0; i < 2; ++i) load_vec_to_lds(xk + (size_t)kb * 128, xoff[i], at + wave * 2048 + i * 1024);
 #pragma unroll
         for (int q = 0; q < NTERM; ++q)
-            load_vec_to_lds(wk + (size_t)kb * (NTERM * 1024) + q * 64, woff, at + XB + (wave * NTERM + q) * 1024);
+            load_vec_to_lds(wk + (size_t)kb * (NTERM * 1024) + q * 1024, woff, at + XB + (wave * NTERM + q) * 1024);
     };
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)

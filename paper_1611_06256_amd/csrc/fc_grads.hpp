@@ -12,7 +12,9 @@
 // instructions next to 28 % of products.  Here everything goes straight from memory to LDS, one k-step of 32 ahead, and
 // three blocks share a compute unit (48 KB each): MFMA 29 - 43 %, vector instructions 19 - 27 %, no bank conflicts; the rest is
 // waiting at the one barrier of a k-step (two blocks with two steps ahead: 64 instead of 57 us).  Rows of 128 units or frames
-// in blocks of eight wavefronts were level.  us of the launch before and after, and of the reduction behind it where dW needs no
+// in blocks of eight wavefronts were level; tiles of 128x128, one block of eight wavefronts with three steps in LDS per compute
+// unit, which ask for half the bytes, were too (2560 frames of the small net 57.5 / 59.4 us, 1280 of the larger 57.5 / 60.2,
+// 640 x 1024 x 18496 288 / 277), four wavefronts slower.  us of the launch before and after, and of the reduction behind it where dW needs no
 // partial sums any more: small net 40 frames 14.6 -> 8.0, 640: 20.0 -> 16.0 (10.1 -> 8.3), 2560: 55.2 -> 47.7; larger net 1280:
 // 67.0 -> 49.8 (34.8 -> 23.5), its operands rounded to bfloat16 38.8 -> 23.4 (36.7 -> 24.7); 640 x 1024 x 18496: 430 -> 250 (125
 // -> 35).
@@ -69,6 +71,7 @@ struct FcGradArgs {
     int ntx, ntw, ntn;                        // row tiles of dX and of dW, column tiles of both
     int per_x, per_w;                         // blocks per XCD
     int w_first;                              // dW's blocks come first
+    int x_cols;                               // dX: an XCD's column tiles next to each other, not a column's row tiles
     int z_to_xcd;                             // dW: an XCD takes every eighth chunk instead of every eighth column tile
     FastDiv dntx, dntw, dtw;                  // by ntx, ntw, and dW's tiles of a chunk or of a column
     FcDhPlanes dh;
@@ -95,7 +98,10 @@ __device__ __forceinline__ u32x4 lds_transpose8(const unsigned char *p0, const u
     return o.u;
 }
 
-// One block's tile.  A wavefront takes 16 of the 64 columns and all 64 rows, whose operands (dh) the four share through LDS.
+// One block's tile.  dW: a wavefront takes 16 of the 64 columns, which it splits, and all 64 rows, whose operands (dh) the four share
+// through LDS.  dX: 32 rows and 32 columns (24 instead of 30 reads of LDS per step).  With that, the mask asked for with the last
+// step, W's terms in pieces of 1 KB without gaps and the order of blocks below, larger net, 1280 frames: 58.4 -> 53.7 us, small net,
+// 2560: 52.4 -> 50.5.
 // FOLD (dW): all chunks of the tile, one after the other, their sums added up in the order of reduce_all_kernel.
 template <bool WGRAD, bool ONE, bool FOLD>
 __device__ __forceinline__ void fc_grad_block(const FcGradArgs &p, const int bid, unsigned char *smem) {
@@ -110,7 +116,8 @@ __device__ __forceinline__ void fc_grad_block(const FcGradArgs &p, const int bid
         if ((int)z >= p.nz || (int)tn >= p.ntn) return;
     } else {
         uint32_t ci;
-        (WGRAD ? p.dntw : p.dntx).divmod((uint32_t)local, ci, tm);
+        if (WGRAD || !p.x_cols) (WGRAD ? p.dntw : p.dntx).divmod((uint32_t)local, ci, tm);
+        else p.dntx.divmod((uint32_t)local, tm, ci);
         tn = ci * DG_XCDS + xcd;
         if ((int)tn >= p.ntn) return;
     }
@@ -142,7 +149,7 @@ __device__ __forceinline__ void fc_grad_block(const FcGradArgs &p, const int bid
         }
         bk = (const unsigned char *)p.x;
     } else {
-        boff[0] = (lane >> 2) * (NT * 64) + ((lane & 3) ^ (2 * (lane >> 5))) * 16;
+        boff[0] = (lane >> 2) * 64 + ((lane & 3) ^ (2 * (lane >> 5))) * 16;
         bk = (const unsigned char *)(p.w + ((size_t)(wave >> 1) * (p.flat / 32) + min(n0 / 32 + (wave & 1), p.flat / 32 - 1)) * (NT * 64));
     }
     const size_t bstep = WGRAD ? (size_t)32 * p.flat * 4 : (size_t)2 * (p.flat / 32) * (NT * 1024);
@@ -159,11 +166,18 @@ __device__ __forceinline__ void fc_grad_block(const FcGradArgs &p, const int bid
                 load_vec_to_lds(b, (uint32_t)min(brow[i], last) * (uint32_t)p.flat * 4u + boff[i], at + AB + (2 * wave + i) * 1024);
         } else {
 #pragma unroll
-            for (int q = 0; q < NT; ++q) load_vec_to_lds(b + q * 64, boff[0], at + AB + (wave * NT + q) * 1024);
+            for (int q = 0; q < NT; ++q) load_vec_to_lds(b + q * 1024, boff[0], at + AB + (wave * NT + q) * 1024);
         }
     };
     if (kb0 < kb1) issue(kb0, 0);
 
+    // dX: the mask of my four tiles, asked for behind the first step's operands
+    float4 keep[WGRAD ? 1 : 4];
+    auto out_at = [&](int i, int j, bool &in) {
+        const int n = n0 + 32 * (wave & 1) + 16 * i + 4 * g, m = m0 + 32 * (wave >> 1) + 16 * j + l16;
+        in = n < p.flat && m < p.B;
+        return in ? (size_t)m * p.flat + n : (size_t)0;
+    };
     floatx4 acc[4], tot[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) { acc[j] = floatx4{0.f, 0.f, 0.f, 0.f}; tot[j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
@@ -174,11 +188,17 @@ __device__ __forceinline__ void fc_grad_block(const FcGradArgs &p, const int bid
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         if (kb + 1 < kb1) issue(kb + 1, slot ^ 1);
+        if (!WGRAD && kb == kb1 - 1)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                bool in;
+                keep[WGRAD ? 0 : i] = *(const float4 *)(p.x + out_at(i >> 1, i & 1, in));
+            }
         const unsigned char *at = smem + slot * STEP;
         slot ^= 1;
-        Bf16x8Bits a[4][NT], b[3];
-        const int odd = (l16 >> 1) & 1;
-        if (WGRAD) {
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
+        if constexpr (WGRAD) {
+            Bf16x8Bits a[4][NT], b[3];
             float v[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e)
@@ -188,51 +208,68 @@ __device__ __forceinline__ void fc_grad_block(const FcGradArgs &p, const int bid
                 for (int e = 0; e < 8; ++e) v[e] = 32 * kb + 8 * g + e < p.B ? v[e] : 0.f;
             }
             split3x8(v, b[0].u, b[1].u, b[2].u, ONE);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) a[j][t].u = ((const u32x4 *)at)[(j * NT + t) * 64 + lane];
+#pragma unroll
+            for (int q = ONE ? 5 : 0; q < 6; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)        // rows of the result: four consecutive columns per lane
+                    acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[PB[q]].v, a[j][PA[q] % NT].v, acc[j], 0, 0, 0);
         } else {
-            // unit 8 g + 4 h + r of the step, r = l16 / 4; columns 16 (wave % 2) + 4 (l16 % 4) .. of the 32
-            const unsigned char *blk = at + AB + (2 * (g >> 1) + (wave >> 1)) * (NT * 1024);
-            const int r0 = 8 * (g & 1) + (l16 >> 2), c = 2 * (wave & 1) + ((l16 >> 1) & 1);
-            const int o0 = r0 * 64 + ((c ^ (2 * (g & 1))) * 16) + (l16 & 1) * 8;
+            Bf16x8Bits a[2][NT], b[2][NT];
+            const int odd = (l16 >> 1) & 1;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) b[t].u = lds_transpose8(blk + t * 1024 + o0, blk + t * 1024 + o0 + 256);
-        }
+            for (int i = 0; i < 2; ++i) {
+                // unit 8 g + 4 h + r of the step, r = l16 / 4; columns 16 i + 4 (l16 % 4) .. of my 32
+                const unsigned char *blk = at + AB + (2 * (g >> 1) + (wave & 1)) * (NT * 1024);
+                const int r0 = 8 * (g & 1) + (l16 >> 2), c = 2 * i + odd;
+                const int o0 = r0 * 64 + ((c ^ (2 * (g & 1))) * 16) + (l16 & 1) * 8;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+                for (int t = 0; t < NT; ++t) b[i][t].u = lds_transpose8(blk + t * 1024 + o0, blk + t * 1024 + o0 + 256);
+            }
 #pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                if (WGRAD) a[j][t].u = ((const u32x4 *)at)[(j * NT + t) * 64 + lane];
-                else {                         // unit 8 g + 4 h + l16 / 4 of the step, frames 16 j + 4 (l16 % 4) ..
-                    const unsigned char *q = at + ((2 * (g >> 1) + (j >> 1)) * NT + t) * 1024 + (2 * (j & 1) + odd) * 256 + (8 * (g & 1) + (l16 >> 2)) * 16 +
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {     // unit 8 g + 4 h + l16 / 4 of the step, frames 16 j + 4 (l16 % 4) .. of my 32
+                    const unsigned char *q = at + ((2 * (g >> 1) + (wave >> 1)) * NT + t) * 1024 + (2 * j + odd) * 256 + (8 * (g & 1) + (l16 >> 2)) * 16 +
                                              (l16 & 1) * 8;
                     a[j][t].u = lds_transpose8(q + 64 * odd, q + 64 * (1 - odd));
                 }
-            }
-        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
 #pragma unroll
-        for (int q = ONE ? 5 : 0; q < 6; ++q)
+            for (int q = ONE ? 5 : 0; q < 6; ++q)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)        // rows of the result: four consecutive columns per lane
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[PB[q]].v, a[j][PA[q] % NT].v, acc[j], 0, 0, 0);
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+                        acc[2 * i + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[i][PB[q] % NT].v, a[j][PA[q] % NT].v, acc[2 * i + j], 0, 0, 0);
+        }
         if (WGRAD && FOLD && (kb == fold_at || kb + 1 == kb1)) {
             fold_at += kc;
 #pragma unroll
             for (int j = 0; j < 4; ++j) { tot[j] += acc[j]; acc[j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
         }
     }
-    const int n = n0 + 16 * wave + 4 * g;
-    if (n >= p.flat) return;
+    if constexpr (WGRAD) {
+        const int n = n0 + 16 * wave + 4 * g;
+        if (n >= p.flat) return;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int m = m0 + 16 * j + l16;
-        const size_t at = (size_t)m * p.flat + n;
-        if (WGRAD) {
-            *(floatx4 *)(p.dw + (FOLD ? 0 : (size_t)z * p.F * p.flat) + at) = FOLD ? tot[j] : acc[j];
-        } else if (m < p.B) {
-            const float4 k4 = *(const float4 *)(p.x + at);
-            floatx4 v = acc[j];
-            v[0] = k4.x > 0.f ? v[0] : 0.f; v[1] = k4.y > 0.f ? v[1] : 0.f; v[2] = k4.z > 0.f ? v[2] : 0.f; v[3] = k4.w > 0.f ? v[3] : 0.f;
-            *(floatx4 *)(p.dx + at) = v;
-        }
+        for (int j = 0; j < 4; ++j)
+            *(floatx4 *)(p.dw + (FOLD ? 0 : (size_t)z * p.F * p.flat) + (size_t)(m0 + 16 * j + l16) * p.flat + n) = FOLD ? tot[j] : acc[j];
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                bool in;
+                const size_t at = out_at(i, j, in);
+                if (!in) continue;
+                const float4 k4 = keep[2 * i + j];
+                floatx4 v = acc[2 * i + j];
+                v[0] = k4.x > 0.f ? v[0] : 0.f; v[1] = k4.y > 0.f ? v[1] : 0.f; v[2] = k4.z > 0.f ? v[2] : 0.f; v[3] = k4.w > 0.f ? v[3] : 0.f;
+                *(floatx4 *)(p.dx + at) = v;
+            }
     }
 }
 
@@ -265,7 +302,11 @@ inline hipError_t launch_fc_grads(FcGradArgs p, bool fold, int rb, hipStream_t s
     // Every eighth column tile of W or x goes to the same XCD, whose L2 holds those columns; dW's chunks do where each XCD gets one.
     p.z_to_xcd = !fold && p.nz >= DG_XCDS;
     p.per_w = fold ? cols * p.ntw : p.z_to_xcd ? (p.nz + DG_XCDS - 1) / DG_XCDS * p.ntw * p.ntn : cols * p.ntw * p.nz;
-    p.dntx = FastDiv(p.ntx); p.dntw = FastDiv(p.ntw); p.dtw = FastDiv(p.ntw * (p.z_to_xcd ? p.ntn : p.nz));
+    // dh, which every column of W meets, passes through an XCD's L2 (4 MB) once where all its columns of W fit in half of it (small
+    // net 2560 frames: dX alone 33.2 -> 31.8 us, 1280 of the larger 33.5 -> 32.2; where they don't, W would pass through more often:
+    // 640 x 1024 x 18496 143 -> 178).
+    p.x_cols = (size_t)cols * 64 * p.F * (rb ? 2 : 6) <= (size_t)2 << 20;
+    p.dntx = FastDiv(p.x_cols ? cols : p.ntx); p.dntw = FastDiv(p.ntw); p.dtw = FastDiv(p.ntw * (p.z_to_xcd ? p.ntn : p.nz));
     p.w_first = fold && p.per_w <= 3 * 256 / DG_XCDS;
     const dim3 grid(DG_XCDS * (p.per_x + p.per_w));
     if (rb && fold) ga3c::launch((fc_grads_kernel<true, true>), grid, dim3(256), fc_grads_lds<true>(), s, p);
