@@ -48,7 +48,7 @@ struct F32FwdGeom {
 template <class TIn> constexpr int f32_fwd_steps() { return sizeof(TIn) == 1 ? 16 : 32; }
 
 template <class TIn, int OC, int MT, bool LDSW, bool BITS>
-__global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, 1) void conv_f32_fwd_kernel(const TIn *__restrict__ x, const float4 *__restrict__ w,
+__global__ __launch_bounds__(LDSW ? 512 : 4 * OC / MT, LDSW && sizeof(TIn) == 1 ? 4 : 1) void conv_f32_fwd_kernel(const TIn *__restrict__ x, const float4 *__restrict__ w,
                                                               const float *__restrict__ bias, float *__restrict__ y, const F32FwdGeom b,
                                                               const PositiveBits bits) {
     constexpr bool BYTE = sizeof(TIn) == 1;
@@ -398,7 +398,15 @@ inline hipError_t launch_conv_f32_fwd2(const TIn *x, const float4 *w, const floa
     const hipError_t e = LDSW ? band_allow_lds(conv_f32_fwd_kernel<TIn, OC, MT, LDSW, BITS>, attr) : hipSuccess;
     if (e != hipSuccess) return e;
     constexpr int NW = 128 * MT / OC;
-    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW, BITS>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, BAND_CUS) : b.tiles),
+    // Bytes: two blocks fit a compute unit, and hide each other's conversions (640 frames of 84x84 with stride 1 551 -> 526 us), if
+    // their rounds of 2 NW tiles, of which the last may be one of NW, are no more than one block's by 3 %: 320 frames with stride 3
+    // 42.2 us with one, 44.7 with two, 150 with stride 2 42.7 and 45.1.
+    auto turns = [&](int blocks) {
+        const int per = (b.tiles + blocks - 1) / blocks, rest = per % (2 * NW);
+        return per / (2 * NW) * 2 + (rest > NW ? 2 : rest > 0 ? 1 : 0);
+    };
+    const int blocks = sizeof(TIn) == 1 && LDSW && 64 * turns(2 * BAND_CUS) <= 33 * turns(BAND_CUS) ? 2 * BAND_CUS : BAND_CUS;
+    ga3c::launch((conv_f32_fwd_kernel<TIn, OC, MT, LDSW, BITS>), dim3(LDSW ? std::min((b.tiles + NW - 1) / NW, blocks) : b.tiles),
                  dim3(LDSW ? 512 : 4 * OC / MT), LDSW ? f32_fwd_steps<TIn>() * OC * 64 : 0, s, x, w, bias, y, b, bits);
     return hipGetLastError();
 }

@@ -138,3 +138,9 @@ def test_masks_as_bits_are_the_masks_as_values(G, shape, n):
     for a, b in zip(*got):
         assert float(a.abs().max()) > 0 and torch.equal(a, b)
     assert bool(((got[0][0] > 0) | (got[0][1] == 0)).all()) and bool((got[0][0] == 0).any())
+
+
+@pytest.mark.parametrize("in_h", [49, 50])
+def test_byte_layer_with_two_blocks_per_compute_unit_has_the_any_shape_kernels_bits(G, in_h):
+    # 40 frames: 42x77 maps are 8085 tiles, whole rounds for two blocks per compute unit; 43x77 are a tile a block more, and take one
+    test_training_activations_are_the_any_shape_kernels_bits(G, dict(in_h=in_h, conv=((32, 8, 1), (32, 4, 2))), 40)
