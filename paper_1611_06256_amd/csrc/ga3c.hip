@@ -1198,51 +1198,63 @@ __global__ __launch_bounds__(LOSS_THREADS) void returns_loss_kernel(
 }
 
 // dL/d(pre-activation of fc)[b][k] = [h > 0] * (sum_a dz[b][a] Wp[a][k] + dv[b] Wv[k]).
-// A block takes HD_FRAMES frames; both weight matrices and the frames' dz rows
-// are first copied to LDS.  colpart[block][k] receives the block's sum over
-// its frames, which a reduction turns into the fc bias gradient.  Dynamic LDS: (A + 1) * (F + HD_FRAMES) floats.
-constexpr int HD_FRAMES = 8;
-__global__ __launch_bounds__(256) void heads_dgrad_kernel(const float *__restrict__ dzv, const float *__restrict__ h,
-                                                          const float *__restrict__ Wp, const float *__restrict__ Wv,
-                                                          int B, int F, int A, float *__restrict__ dh,
-                                                          float *__restrict__ colpart, float *__restrict__ wpart, int rb) {
+// A block takes HD_FRAMES frames and 256 columns, a thread one of them, whose weights it alone reads: straight from memory, eight
+// outputs ahead.  A block that took all columns copied the weights to LDS first and ran as many passes as there are 256 columns.
+// 640 frames, 1024 units, 18 actions: 28.2 -> 9.2 us, and an update of 5 frames of the stride-1 member 429 -> 410.
+// colpart[block][k] receives the block's sum over its frames, which a reduction turns into the fc bias gradient.
+// Dynamic LDS: (A + 1) * HD_FRAMES floats.
+constexpr int HD_FRAMES = 8, HD_COLS = 256, HD_AHEAD = 8;
+__global__ __launch_bounds__(HD_COLS) void heads_dgrad_kernel(const float *__restrict__ dzv, const float *__restrict__ h,
+                                                              const float *__restrict__ Wp, const float *__restrict__ Wv,
+                                                              int B, int F, int A, float *__restrict__ dh,
+                                                              float *__restrict__ colpart, float *__restrict__ wpart, int rb) {
     // rb: every product takes its operands rounded to bfloat16, and the sums that are products with ones
     // (the bias gradients) take rounded terms; dh is stored as computed
-    extern __shared__ float sm[];
-    float *wsh = sm;                        // [A+1][F]
-    float *dzs = sm + (A + 1) * F;          // [HD_FRAMES][A+1]
+    extern __shared__ float4 hd_dz[];       // [A+1][HD_FRAMES]
+    float *dzs = (float *)hd_dz;
     const int tid = threadIdx.x;
     const int b0 = blockIdx.x * HD_FRAMES;
     const int nf = min(HD_FRAMES, B - b0);
-    copy_to_lds<8>(wsh, Wp, A * F, tid, 256);
-    copy_to_lds<2>(wsh + A * F, Wv, F, tid, 256);
-    copy_to_lds<1>(dzs, dzv + (size_t)b0 * (A + 1), nf * (A + 1), tid, 256);
-    __syncthreads();
-    if (rb) {
-        for (int e = tid; e < (A + 1) * F; e += 256) wsh[e] = bf16_rne(wsh[e]);
-        for (int e = tid; e < nf * (A + 1); e += 256) dzs[e] = bf16_rne(dzs[e]);
-        __syncthreads();
-    }
-    for (int k = tid; k < F; k += 256) {
-        float hv[HD_FRAMES];
+    const int k = blockIdx.y * HD_COLS + tid, kc = min(k, F - 1);
+    float wv[HD_AHEAD], hv[HD_FRAMES];
+    auto weights = [&](int a0) {
 #pragma unroll
-        for (int fb = 0; fb < HD_FRAMES; ++fb) hv[fb] = h[(size_t)(b0 + min(fb, nf - 1)) * F + k];
+        for (int i = 0; i < HD_AHEAD; ++i) wv[i] = (a0 + i < A ? Wp + (size_t)(a0 + i) * F : Wv)[kc];
+    };
+    weights(0);
+#pragma unroll
+    for (int fb = 0; fb < HD_FRAMES; ++fb) hv[fb] = h[(size_t)(b0 + min(fb, nf - 1)) * F + kc];
+    for (int e = tid; e < (A + 1) * HD_FRAMES; e += HD_COLS) {
+        const int fb = e % HD_FRAMES;
+        const float d = fb < nf ? dzv[(size_t)(b0 + fb) * (A + 1) + e / HD_FRAMES] : 0.f;
+        dzs[e] = rb ? bf16_rne(d) : d;
+    }
+    __syncthreads();
+    if (k < F) {
         float s[HD_FRAMES];
 #pragma unroll
         for (int fb = 0; fb < HD_FRAMES; ++fb) s[fb] = 0.f;
         // wpart (optional): this block's share of the heads' weight gradient,
         // [block][A+1][F+1] with the bias gradient in the last column
         float *wp = wpart ? wpart + (size_t)blockIdx.x * (A + 1) * (F + 1) + k : nullptr;
-        for (int a = 0; a <= A; ++a) {
-            const float wv = wsh[a * F + k];
-            float gw = 0.f;
+        for (int a0 = 0; a0 <= A; a0 += HD_AHEAD) {
+            float w[HD_AHEAD];
 #pragma unroll
-            for (int fb = 0; fb < HD_FRAMES; ++fb) {
-                const float d = dzs[min(fb, nf - 1) * (A + 1) + a];
-                s[fb] += d * wv;
-                gw += fb < nf ? d * (rb ? bf16_rne(hv[fb]) : hv[fb]) : 0.f;
-            }
-            if (wp) wp[(size_t)a * (F + 1)] = gw;
+            for (int i = 0; i < HD_AHEAD; ++i) w[i] = rb ? bf16_rne(wv[i]) : wv[i];
+            if (a0 + HD_AHEAD <= A) weights(a0 + HD_AHEAD);
+#pragma unroll
+            for (int i = 0; i < HD_AHEAD; ++i)
+                if (a0 + i <= A) {
+                    const float4 lo = hd_dz[2 * (a0 + i)], hi = hd_dz[2 * (a0 + i) + 1];
+                    const float d[HD_FRAMES] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                    float gw = 0.f;
+#pragma unroll
+                    for (int fb = 0; fb < HD_FRAMES; ++fb) {
+                        s[fb] += d[fb] * w[i];
+                        gw += fb < nf ? d[fb] * (rb ? bf16_rne(hv[fb]) : hv[fb]) : 0.f;
+                    }
+                    if (wp) wp[(size_t)(a0 + i) * (F + 1)] = gw;
+                }
         }
         float col = 0.f;
 #pragma unroll
@@ -1254,9 +1266,9 @@ __global__ __launch_bounds__(256) void heads_dgrad_kernel(const float *__restric
             }
         colpart[(size_t)blockIdx.x * F + k] = col;      // this block's share of the fc bias gradient
     }
-    if (wpart && tid <= A) {
+    if (wpart && blockIdx.y == 0 && tid <= A) {
         float gb = 0.f;
-        for (int fb = 0; fb < nf; ++fb) gb += dzs[fb * (A + 1) + tid];
+        for (int fb = 0; fb < nf; ++fb) gb += dzs[tid * HD_FRAMES + fb];
         wpart[((size_t)blockIdx.x * (A + 1) + tid) * (F + 1) + F] = gb;
     }
 }
@@ -2710,7 +2722,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         red_blocks += 8 * g.per_xcd;
         red_bytes += 4.0 * (nz_ + 1) * rows * Ncols;
     };
-    const size_t hd_lds = sizeof(float) * (A + 1) * (F + HD_FRAMES);      // heads_dgrad_kernel's LDS
+    const size_t hd_lds = sizeof(float) * (A + 1) * HD_FRAMES;      // heads_dgrad_kernel's LDS
     static size_t hd_lds_set = 0;
     if (fused_heads) {
         const int nblk = cdiv(B, HD_FRAMES);
@@ -2737,7 +2749,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (heads)");
         STAGE("heads_bwd", 4.0 * B * (A + 1) * F, 0);
         HIP_TRY(allow_dynamic_lds((const void *)heads_dgrad_kernel, hd_lds, hd_lds_set));
-        ga3c::launch(heads_dgrad_kernel, dim3(nblk), dim3(256), hd_lds, s, c->dzv, w.h, Wp, Wv, B,
+        ga3c::launch(heads_dgrad_kernel, dim3(nblk, cdiv(F, HD_COLS)), dim3(HD_COLS), hd_lds, s, c->dzv, w.h, Wp, Wv, B,
                            F, A, c->dh, c->colpart, part, c->rb);
         HIP_TRY(hipGetLastError());
         add_seg(part, nblk, A + 1, F + 1, 0, A, c->grad + c->off[nb + 2], c->grad + c->off[nb + 3], 1);
@@ -2759,7 +2771,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         add_seg(p.C, nz, A + 1, F + 1, A, 1, c->grad + c->off[nb + 4], c->grad + c->off[nb + 5], 1);
         STAGE("heads_dgrad", 2.0 * B * (A + 1) * F, 0);
         HIP_TRY(allow_dynamic_lds((const void *)heads_dgrad_kernel, hd_lds, hd_lds_set));
-        ga3c::launch(heads_dgrad_kernel, dim3(cdiv(B, HD_FRAMES)), dim3(256), hd_lds, s, c->dzv, w.h, Wp, Wv, B,
+        ga3c::launch(heads_dgrad_kernel, dim3(cdiv(B, HD_FRAMES), cdiv(F, HD_COLS)), dim3(HD_COLS), hd_lds, s, c->dzv, w.h, Wp, Wv, B,
                            F, A, c->dh, c->colpart, (float *)nullptr, c->rb);
         HIP_TRY(hipGetLastError());
     }

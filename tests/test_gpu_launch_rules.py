@@ -88,6 +88,14 @@ def test_fused_heads_of_1024_units(G, A, math):
     P.run_train(G, G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=1024, n_actions=A, math=math), 77, 1, 7280 + A, dict(clip_norm=40.0))
 
 
+# heads too large for the fused kernel: blocks of 256 columns of the fc layer (one, one and a rest, four), a last block of five
+# frames; outputs around the eight that are read ahead
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("F,A", [(256, 32), (300, 39), (1024, 15), (1024, 18)])
+def test_separate_heads_backward(G, F, A, math):
+    P.run_train(G, G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=A, math=math), 13, 1, 7290 + A, dict(clip_norm=40.0))
+
+
 # Layer by layer only: both sides then round the same numbers and P.STAGE_TOL_BF16 holds at every size.  End to end a single operand
 # that rounds differently on the two sides reaches every gradient behind it, so a median over 32 biases (observed 1.3e-3 at 641 frames)
 # is a matter of how many such operands there are, and not of the kernels.
