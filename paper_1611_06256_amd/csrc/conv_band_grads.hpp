@@ -43,6 +43,18 @@ constexpr int band_dgrad_pitch() { return 16 * lds_row_units((ONE ? 2 : 6) * OC 
 template <int OC>
 constexpr int band_dgrad_maxu() { return OC == 32 ? 6 : 13; }
 
+// Where a staging unit goes, in one register: its byte in LDS (at most 18 bits) and its row of the item, 0 .. R.  Narrow, tall maps
+// would fit more rows than the eight bits hold (one term, 4 columns: R = 336), so band_dgrad_geom stops at the last that they do.
+constexpr int BAND_DGRAD_MAXR = 255;
+struct BandDgradUnit {
+    int v;                                                // negative: none
+    __host__ __device__ static BandDgradUnit none() { return {-1}; }
+    __host__ __device__ static BandDgradUnit at(uint32_t byte, uint32_t row) { return {(int)(byte * 256 + row)}; }
+    __host__ __device__ bool any() const { return v >= 0; }
+    __host__ __device__ int byte() const { return v >> 8; }
+    __host__ __device__ int row() const { return v & 255; }
+};
+
 struct BandDgradDivs {
     FastDiv px, ow, rl;      // by the pixels of dY that an item stages, by OW, by R + 1
 };
@@ -60,7 +72,8 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
     const int HW = b.H * b.W, NPIX = b.OH * b.OW, GW = b.cols, PW = GW + 1, RL = b.R + 1;
     const int npx = b.F * RL * b.OW, NU = npx * (OC / 8);
 
-    int src[MAXU], dst[MAXU];                             // dst: byte, in units of 256, and row of the item
+    int src[MAXU];
+    BandDgradUnit dst[MAXU];
 #pragma unroll
     for (int i = 0; i < MAXU; ++i) {
         uint32_t cg, px, row, xc, f, r;
@@ -68,7 +81,7 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
         d.ow.divmod(px, row, xc);
         d.rl.divmod(row, f, r);
         src[i] = (f * OC + cg * 8) * NPIX + xc;
-        dst[i] = tid + 256 * i < NU ? ((row * PW + xc + 1) * PIT + 16 * cg) * 256 + r : -1;
+        dst[i] = tid + 256 * i < NU ? BandDgradUnit::at((row * PW + xc + 1) * PIT + 16 * cg, r) : BandDgradUnit::none();
     }
     const size_t total = (size_t)nframes * OC * NPIX;
     float pre[MAXU][8];
@@ -79,7 +92,7 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
 #pragma unroll
         for (int i = 0; i < MAXU; ++i)
             if (256 * i < NU) {
-                const int yr = min(max(g0 + (dst[i] & 255) - 1, 0), b.OH - 1);
+                const int yr = min(max(g0 + dst[i].row() - 1, 0), b.OH - 1);
                 band_load8(dy + base, 4u * min((uint32_t)(src[i] + yr * b.OW), lim), NPIX, pre[i]);
             }
     };
@@ -101,12 +114,12 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
         __syncthreads();                                     // the last item's planes have been read
 #pragma unroll
         for (int i = 0; i < MAXU; ++i)
-            if (dst[i] >= 0) {
-                const bool in = (unsigned)(g0 + (dst[i] & 255) - 1) < (unsigned)b.OH;      // else a row above or below dY
+            if (dst[i].any()) {
+                const bool in = (unsigned)(g0 + dst[i].row() - 1) < (unsigned)b.OH;      // else a row above or below dY
                 u32x4 t[3];
                 split3x8(pre[i], t[0], t[1], t[2]);
 #pragma unroll
-                for (int k = 0; k < NTERM; ++k) *(u32x4 *)(band_smem + (dst[i] >> 8) + 2 * OC * k) = in ? t[k] : u32x4{0u, 0u, 0u, 0u};
+                for (int k = 0; k < NTERM; ++k) *(u32x4 *)(band_smem + dst[i].byte() + 2 * OC * k) = in ? t[k] : u32x4{0u, 0u, 0u, 0u};
             }
         __syncthreads();
         fetch(min(item + (int)gridDim.x, b.items - 1));
@@ -208,7 +221,7 @@ template <int OC, bool ONE>
 inline bool band_dgrad_geom(BandGeom &b, int nframes) {
     const int GW = (b.W + 1) / 2, lds = OC == 32 ? BAND_HALF_LDS : BAND_LDS - 2048;
     return band_split(b, nframes, (b.H + 1) / 2, GW,
-                      [&](int F, int R) { return F * (R + 1) * (GW + 1) * band_dgrad_pitch<OC, ONE>() <= lds ? 0 : 2 * BAND_LDS; },
+                      [&](int F, int R) { return R <= BAND_DGRAD_MAXR && F * (R + 1) * (GW + 1) * band_dgrad_pitch<OC, ONE>() <= lds ? 0 : 2 * BAND_LDS; },
                       [&](int F, int R) { return F * (R + 1) * b.OW * (OC / 8); }, band_dgrad_maxu<OC>(), (OC == 32 ? 2 : 1) * BAND_CUS);
 }
 template <int OC, bool ONE, bool BITS>

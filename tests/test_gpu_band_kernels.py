@@ -144,3 +144,28 @@ def test_masks_as_bits_are_the_masks_as_values(G, shape, n):
 def test_byte_layer_with_two_blocks_per_compute_unit_has_the_any_shape_kernels_bits(G, in_h):
     # 40 frames: 42x77 maps are 8085 tiles, whole rounds for two blocks per compute unit; 43x77 are a tile a block more, and take one
     test_training_activations_are_the_any_shape_kernels_bits(G, dict(in_h=in_h, conv=((32, 8, 1), (32, 4, 2))), 40)
+
+
+@pytest.mark.parametrize("oc,n", [(64, 256), (32, 512)])
+def test_input_gradient_of_a_tall_narrow_map(G, oc, n):
+    # 514x4 with one term: LDS and registers would hold all 257 rows of the phase grid in one item, more than a staging unit can name
+    import torch
+    import torch.nn.functional as F
+    desc = G.NetDesc(in_c=4, in_h=521, in_w=11, conv=((32, 8, 1), (oc, 4, 2)), fc_units=16, n_actions=4, math=1)
+    net = G.Ga3c(desc, 1, n)
+    net.params_init(9601)
+    fr = torch.from_numpy(synth.uniform_frames(9602, (n, 1, 4, 521, 11))).cuda()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9603, n, 1, 4).items()}
+    print(f"train {n} frames, {oc} filters", flush=True)
+    net.train_step(fr, tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.0))
+    at = net.offsets()["conv2.W"][0]
+    w = net.params_get(0)[at:at + oc * 32 * 16].cpu().view(oc, 32, 4, 4)
+    act, dact, dy = (net.train_debug_get(which, torch.empty((n, *shape), device="cuda"))[::51].cpu()
+                     for which, shape in ((4, (32, 514, 4)), (10, (32, 514, 4)), (11, (oc, 256, 1))))
+    torch.cuda.synchronize()
+    net.close()
+    assert bool((dy[:, :, -2:] != 0).any())
+    ref = F.conv_transpose2d(dy.bfloat16().double(), w.bfloat16().double(), stride=2) * (act > 0)
+    # products of bfloat16 are exact; at most 2 x 2 x oc of them are added in fp32
+    bound = 4 * oc * 2.0 ** -24 * F.conv_transpose2d(dy.bfloat16().double().abs(), w.bfloat16().double().abs(), stride=2)
+    assert bool(((dact - ref).abs() <= bound).all())

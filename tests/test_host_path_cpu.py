@@ -1,5 +1,6 @@
 """What the library's host code asks of the HIP runtime, call by call, on a stand-in that keeps account (no GPU):
-tests/host_path_model.cpp, linked with the host side of the library's own sources."""
+tests/host_path_model.cpp, linked with the host side of the library's own sources.  And the work items that it cuts
+maps into: tests/band_geometry_model.cpp with the host side of the headers."""
 import os
 import subprocess
 
@@ -35,4 +36,14 @@ def model(tmp_path_factory):
 ])
 def test_host_path(model, check):
     r = subprocess.run([model, check], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and " 0 problems" in r.stdout, r.stdout[-3000:] + r.stderr[-1000:]
+
+
+def test_work_items_of_maps_of_any_proportion(tmp_path):
+    # rows that a staging unit's packed place cannot hold would be another row's, at a byte that is no vector's
+    hipcc, obj, exe = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), str(tmp_path / "model.o"), str(tmp_path / "model")
+    subprocess.check_call([hipcc, "-x", "hip", "--cuda-host-only", "--offload-arch=gfx950", "-O1", "-w", "-std=c++17", "-c",
+                           os.path.join(ROOT, "tests", "band_geometry_model.cpp"), "-o", obj])
+    subprocess.check_call(["g++", "-no-pie", "-o", exe, obj, "-Wl,--unresolved-symbols=ignore-all"])
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and " 0 problems" in r.stdout, r.stdout[-3000:] + r.stderr[-1000:]
