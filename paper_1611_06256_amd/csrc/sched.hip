@@ -263,6 +263,27 @@ int harvest(ga3c_sched *s, bool wait) {
     return GA3C_OK;
 }
 
+// What a batch that could not be enqueued whole has left on its stream reads the slot's lists and writes its results: it has to be
+// over before the slot is filled again.  Returns the batch's code.
+int abandon(hipStream_t stream, int rc) {
+    (void)hipStreamSynchronize(stream);
+    return rc;
+}
+
+int enqueue_predict(ga3c_sched *s, PredSlot &p, int n) {
+    int rc;
+    if (ga3c::takes_frame_table(s->ctx))
+        rc = ga3c::predict_from_table(s->ctx, (const uint8_t *const *)p.ptrs_h, n, p.unif_h, p.val_h, p.act_h, s->sp);
+    else {
+        hipLaunchKernelGGL(gather_frames_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, (uint4 *)s->pred_frames, (int)(s->frame_bytes / 16));
+        SHIP(hipGetLastError());
+        rc = ga3c_predict(s->ctx, s->pred_frames, n, p.unif_h, nullptr, p.val_h, nullptr, p.act_h, s->sp);
+    }
+    if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_predict: %s", ga3c_last_error());
+    SHIP(hipEventRecord(p.done, s->sp));
+    return GA3C_OK;
+}
+
 int issue_predict(ga3c_sched *s, int *count) {
     *count = 0;
     if (s->pq.empty()) return GA3C_OK;
@@ -288,22 +309,35 @@ int issue_predict(ga3c_sched *s, int *count) {
         p.agents[i] = r.agent; p.ptrs_h[i] = (const uint4 *)r.frame; p.unif_h[i] = r.uniform;
     }
     await_results(p, n);
-    int rc;
-    if (ga3c::takes_frame_table(s->ctx))
-        rc = ga3c::predict_from_table(s->ctx, (const uint8_t *const *)p.ptrs_h, n, p.unif_h, p.val_h, p.act_h, s->sp);
-    else {
-        hipLaunchKernelGGL(gather_frames_kernel, dim3(n), dim3(256), 0, s->sp, p.ptrs_h, (uint4 *)s->pred_frames, (int)(s->frame_bytes / 16));
-        SHIP(hipGetLastError());
-        rc = ga3c_predict(s->ctx, s->pred_frames, n, p.unif_h, nullptr, p.val_h, nullptr, p.act_h, s->sp);
-    }
-    if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_predict: %s", ga3c_last_error());
-    SHIP(hipEventRecord(p.done, s->sp));
+    if (const int rc = enqueue_predict(s, p, n); rc != GA3C_OK) return abandon(s->sp, rc);
     s->pq.pop(n);
     p.busy = true; p.n = n;
     p.version = s->stats.train_batches;      // the call above reads the parameters that this many updates produced
     s->ps_next = (s->ps_next + 1) % RING;
     s->stats.predictions += n; s->stats.predict_batches += 1;
     *count = n;
+    return GA3C_OK;
+}
+
+// n segments of B frames in all, the lists of which lie in the slot.
+int enqueue_train(ga3c_sched *s, TrainSlot &t, int n, int B, bool equal) {
+    const int T = s->cfg.t_max;
+    const bool table = ga3c::takes_frame_table(s->ctx);
+    int rc;
+    if (table && equal) {        // every list is read where the host wrote it
+        rc = ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_h, t.rew_h, t.done_h, t.boot_h, nullptr, n, T, B, &s->cfg.hp, s->st);
+    } else {
+        const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, table ? nullptr : (uint4 *)s->train_frames, t.act_d, t.seg_d,
+                             t.rew_d, t.boot_d, t.done_d, (int)(s->frame_bytes / 16), n};
+        hipLaunchKernelGGL(gather_experiences_kernel, dim3(B), dim3(256), 0, s->st, ga);
+        SHIP(hipGetLastError());
+        rc = table   ? ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_d, t.rew_d, t.done_d, t.boot_d, t.seg_d, n, 1, B,
+                                              &s->cfg.hp, s->st)
+             : equal ? ga3c_train_step(s->ctx, s->train_frames, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp, nullptr, s->st)
+                     : ga3c_train_step_ragged(s->ctx, s->train_frames, t.act_d, t.rew_d, t.done_d, t.seg_d, t.boot_d, n, B, &s->cfg.hp, nullptr, s->st);
+    }
+    if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_train_step: %s", ga3c_last_error());
+    SHIP(hipEventRecord(t.done, s->st));
     return GA3C_OK;
 }
 
@@ -337,22 +371,7 @@ int issue_train(ga3c_sched *s, int *count) {
     memcpy(t.act_h, s->tq_act.data(), sizeof(int32_t) * B);
     memcpy(t.rew_h, s->tq_rew.data(), sizeof(float) * B);
     memcpy(t.done_h, s->tq_done.data(), B);
-    const bool table = ga3c::takes_frame_table(s->ctx);
-    int rc;
-    if (table && equal) {        // every list is read where the host wrote it
-        rc = ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_h, t.rew_h, t.done_h, t.boot_h, nullptr, n, T, B, &s->cfg.hp, s->st);
-    } else {
-        const GatherTrain ga{t.ptrs_h, t.act_h, t.seg_h, t.rew_h, t.boot_h, t.done_h, table ? nullptr : (uint4 *)s->train_frames, t.act_d, t.seg_d,
-                             t.rew_d, t.boot_d, t.done_d, (int)(s->frame_bytes / 16), n};
-        hipLaunchKernelGGL(gather_experiences_kernel, dim3(B), dim3(256), 0, s->st, ga);
-        SHIP(hipGetLastError());
-        rc = table   ? ga3c::train_from_table(s->ctx, (const uint8_t *const *)t.ptrs_h, t.act_d, t.rew_d, t.done_d, t.boot_d, t.seg_d, n, 1, B,
-                                              &s->cfg.hp, s->st)
-             : equal ? ga3c_train_step(s->ctx, s->train_frames, t.act_d, t.rew_d, t.done_d, t.boot_d, n, T, &s->cfg.hp, nullptr, s->st)
-                     : ga3c_train_step_ragged(s->ctx, s->train_frames, t.act_d, t.rew_d, t.done_d, t.seg_d, t.boot_d, n, B, &s->cfg.hp, nullptr, s->st);
-    }
-    if (rc != GA3C_OK) return sfail(GA3C_EHIP, "ga3c_train_step: %s", ga3c_last_error());
-    SHIP(hipEventRecord(t.done, s->st));
+    if (const int rc = enqueue_train(s, t, n, B, equal); rc != GA3C_OK) return abandon(s->st, rc);
     const int64_t now = s->stats.train_batches;       // updates issued before this one = the version it starts from
     for (int i = 0; i < n; ++i) {
         const Traj &tr = s->tq[i];

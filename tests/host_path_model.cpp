@@ -19,6 +19,9 @@ static int problems = 0;
 #define PROBLEM(...) do { if (++problems <= 20) { printf("problem: " __VA_ARGS__); printf("\n"); } } while (0)
 
 static int memory_left = -1;                          // allocations until one fails; -1: none does
+static int launches_left = -1, records_left = -1;     // launches, and event records, until one fails
+static bool launch_failed = false;
+static bool fails(int &left) { return left >= 0 && left-- == 0; }
 void *operator new(size_t n) {
     if (memory_left >= 0 && memory_left-- == 0) throw std::bad_alloc();
     if (void *p = malloc(n ? n : 1)) return p;
@@ -85,7 +88,11 @@ static void launched(const void *f, void **args, hipStream_t s) {
     const void *a = rms || fill || copy ? *(void **)args[0] : nullptr, *b = rms || copy ? *(void **)args[1] : nullptr;
     put(s, name, rms ? b : a, rms ? a : b);
 }
-hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t s) { launched(f, args, s); return hipSuccess; }
+hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t s) {
+    if (fails(launches_left)) { launch_failed = true; return hipErrorUnknown; }
+    launched(f, args, s);
+    return hipSuccess;
+}
 hipError_t hipExtLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t s, hipEvent_t, hipEvent_t stop, int) {
     launched(f, args, s);
     if (streams[s].capturing) PROBLEM("a launch with events of its own on a stream that is being captured");
@@ -102,7 +109,12 @@ static hipError_t new_event(hipEvent_t *e) { *e = (hipEvent_t)new Fake(); events
 hipError_t hipEventCreate(hipEvent_t *e) { return new_event(e); }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return new_event(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { events[e].alive = false; return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { ++records; events[e].seen = use(s, "hipEventRecord")->seen; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    if (fails(records_left)) return hipErrorUnknown;
+    ++records;
+    events[e].seen = use(s, "hipEventRecord")->seen;
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { join(use(s, "hipStreamWaitEvent")->seen, events[e].seen); return hipSuccess; }
 hipError_t hipEventQuery(hipEvent_t e) { join(host, events[e].seen); return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t e) { join(host, events[e].seen); return hipSuccess; }
@@ -126,7 +138,7 @@ hipError_t hipMalloc(void **p, size_t n) { take(p, n); device_memory[*p] = n; de
 hipError_t hipFree(void *p) { if (p) { device_bytes -= device_memory[p]; device_memory.erase(p); free(p); } return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { ++allocations; if (in_call) PROBLEM("hipHostMalloc inside a call that only enqueues"); *p = calloc(1, n); return hipSuccess; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) { const hipError_t e = launch_failed ? hipErrorUnknown : hipSuccess; launch_failed = false; return e; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
@@ -391,6 +403,50 @@ static void memory_check() {
     ga3c_sched_destroy(s);
 }
 
+// A tick that fails half way has launched kernels that read the slot's lists and write into its results: the next tick, which
+// takes the same slot, must find them over.
+static void failures_check() {
+    for (const char *net : {"small", "large", "paper3"})
+        for (const bool training : {false, true})
+            for (int what = 0; what < 12; ++what) {        // the event, or the first, second, .. launch
+                Program p(net);
+                p.init(nullptr);
+                ga3c_sched_config cfg;
+                memset(&cfg, 0, sizeof(cfg));
+                cfg.t_max = 5; cfg.predict_cap = 16; cfg.train_min = 10; cfg.train_cap = 40; cfg.hp = p.hp;
+                ga3c_sched *s = nullptr;
+                if (ga3c_sched_create(p.ctx, &cfg, &s) != GA3C_OK) { PROBLEM("sched_create: %s", ga3c_sched_last_error()); return; }
+                const int32_t actions[5] = {0, 1, 2, 3, 4};
+                const float rewards[5] = {0, 0, 1, 0, 0};
+                const uint8_t dones[5] = {0, 0, 0, 0, 1};
+                auto submit = [&] {
+                    for (int a = 0; a < 4; ++a)
+                        if ((training ? ga3c_sched_submit_segment(s, a, address(a), 5, actions, rewards, dones, 0.f, 0)
+                                      : ga3c_sched_submit_predict(s, a, address(a), 0.5f)) != GA3C_OK) PROBLEM("submit");
+                };
+                auto ticked = [&] { int predicted = 0, trained = 0; return ga3c_sched_tick(s, &predicted, &trained) == GA3C_OK ? predicted + trained : -1; };
+                // predictions of new parameters and the first update record events of the context's own
+                submit();
+                if (ticked() < 0 || ga3c_sched_drain(s) != GA3C_OK) PROBLEM("a first tick: %s", ga3c_sched_last_error());
+                ga3c_prediction out[16];
+                if (ga3c_sched_poll(s, out, 16) != (training ? 0 : 4)) PROBLEM("results of the first tick");
+                submit();
+                const size_t first = ops.size();
+                (what ? launches_left : records_left) = what ? what - 1 : 0;
+                const int got = ticked();
+                const bool failed = (what ? launches_left : records_left) < 0;
+                launches_left = records_left = -1;
+                if ((got < 0) != failed) PROBLEM("%s network, %s: a call failed and the tick says %d", net, training ? "update" : "prediction", got);
+                if (got < 0) {
+                    for (size_t i = first; i < ops.size(); ++i)
+                        if (!(i < host.size() && host[i])) { PROBLEM("%s network, a failed %s: %s may still run", net, training ? "update" : "prediction", ops[i].name.c_str()); break; }
+                    if (ticked() < 0) PROBLEM("the tick behind a failed one: %s", ga3c_sched_last_error());
+                    if (ga3c_sched_drain(s) != GA3C_OK || ga3c_sched_poll(s, out, 16) != (training ? 0 : 4)) PROBLEM("%s network: a failed call lost requests", net);
+                }
+                ga3c_sched_destroy(s);
+            }
+}
+
 int main(int argc, char **argv) {
     streams[nullptr] = Stream();
     const std::string what = argc > 1 ? argv[1] : "";
@@ -399,6 +455,7 @@ int main(int argc, char **argv) {
     else if (what == "packets") packets_check();
     else if (what == "ticks") ticks_check();
     else if (what == "memory") memory_check();
+    else if (what == "failures") failures_check();
     else PROBLEM("no such check");
     printf("%zu launches, %d problems\n", ops.size(), problems);
     return problems ? 1 : 0;

@@ -33,6 +33,7 @@ def model(tmp_path_factory):
     "packets",      # what predictions and updates leave in the queues besides their launches
     "ticks",        # a scheduler's tick allocates nothing and waits for nothing
     "memory",       # host memory that runs out in the scheduler's queues
+    "failures",     # launches and event records that fail in a scheduler's tick
 ])
 def test_host_path(model, check):
     r = subprocess.run([model, check], capture_output=True, text=True, timeout=120)
