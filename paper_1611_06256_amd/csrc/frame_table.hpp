@@ -1,6 +1,7 @@
 // Predictions and updates on frames that lie wherever a table of pointers says (the scheduler's agents keep their own
 // frames): the first layer's kernels fetch each frame from its place, so the batch is not put together in memory first.
-// The table is host memory the GPU can read (pinned) and must stay as it is until the call's GPU work has finished.
+// The table is host memory the GPU can read (pinned) and must stay as it is until the call's GPU work has finished; behind a
+// prediction whose values and actions go to coherent host memory, until the last of them has arrived there (each is stored once).
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -542,7 +542,9 @@ __global__ __launch_bounds__(256) void heads_fwd_kernel(const float *__restrict_
 
 // The end of a prediction, by one wavefront: lane a < A holds logit a of frame b, lane A the value.  Softmax and the draw stay
 // in registers; the running sums of the draw go left to right in fp32 exactly as a single thread would form them, so the
-// sampled action is a pure function of the probabilities written out.
+// sampled action is a pure function of the probabilities written out.  A frame's value and action are stored once each, behind
+// the reads of its pixels, its pointer and its uniform number (here and in heads_fwd_kernel): whoever has seen them all may use
+// that memory for something else while the kernel still runs.
 __device__ __forceinline__ void heads_finish_frame(const int lane, const float z, const int A, const int b, const float u, float *logits,
                                                    float *values, float *probs, int32_t *actions) {
     const bool pol = lane < A;

@@ -148,7 +148,9 @@ void await_results(PredSlot &p, int n) {
 }
 // Whether all results of the batch lie in the host's memory, which the kernels write.  They do before the event behind the
 // batch has completed: that takes the release at the end of the last kernel and a packet of its own (closed loop of 256 agents,
-// five predictions and an update: 420 -> 380 us).  A frame's result is the last thing that a batch does for it.
+// five predictions and an update: 440 -> 404 us).  The slot is filled again, and the agents' frames are theirs again, from then on:
+// the kernels that end a prediction (heads_finish_frame, heads_fwd_kernel) store a frame's value and action once each, behind
+// every read of a frame, the table or a uniform number that anything still depends on.
 bool results_arrived(PredSlot &p) {
     for (; p.seen < p.n; ++p.seen)
         if (__atomic_load_n(p.act_h + p.seen, __ATOMIC_ACQUIRE) == NO_ACTION ||
@@ -199,9 +201,11 @@ struct ga3c_sched {
 
 namespace {
 
+// Coherent: the host reads results while the kernels that store them run (results_arrived), and kernels read lists that the
+// host has just written; what the default is can be changed from outside (HIP_HOST_COHERENT).
 template <class T>
 int pinned(T **p, size_t n) {
-    SHIP(hipHostMalloc((void **)p, sizeof(T) * std::max<size_t>(n, 1), hipHostMallocDefault));
+    SHIP(hipHostMalloc((void **)p, sizeof(T) * std::max<size_t>(n, 1), hipHostMallocCoherent));
     return GA3C_OK;
 }
 template <class T>

@@ -136,7 +136,13 @@ static hipError_t take(void **p, size_t n) {
 }
 hipError_t hipMalloc(void **p, size_t n) { take(p, n); device_memory[*p] = n; device_bytes += n; return hipSuccess; }
 hipError_t hipFree(void *p) { if (p) { device_bytes -= device_memory[p]; device_memory.erase(p); free(p); } return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned) { ++allocations; if (in_call) PROBLEM("hipHostMalloc inside a call that only enqueues"); *p = calloc(1, n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned flags) {
+    ++allocations;
+    if (in_call) PROBLEM("hipHostMalloc inside a call that only enqueues");
+    if (!(flags & hipHostMallocCoherent)) PROBLEM("host memory that is not asked for as coherent");      // results are read while kernels run
+    *p = calloc(1, n);
+    return hipSuccess;
+}
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipGetLastError(void) { const hipError_t e = launch_failed ? hipErrorUnknown : hipSuccess; launch_failed = false; return e; }
 const char *hipGetErrorString(hipError_t) { return "error"; }
