@@ -681,16 +681,17 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_wgrad_kernel(const uint8_t 
 
 // ------------------------------------------------------------------- launch --
 
-// Rows per item: the most that fit, then items in equal shares, at least `want` of them where the batch has the rows (128:
-// 20 frames of the stride-3 member 10 / 12 / 10 us in the three layers, with 512 of fewer rows 13 / 13 / 10 and 2 us more
+// Rows per item: the most that fit, then items in equal shares, at least BAND_WGRAD_ITEMS of them where the batch has the rows
+// (20 frames of the stride-3 member 10 / 12 / 10 us in the three layers, with 512 of fewer rows 13 / 13 / 10 and 2 us more
 // of partial sums to add up).
+constexpr int BAND_WGRAD_ITEMS = 128;
 template <class Fits>
-inline bool band_wgrad_split(BandWgradGeom &b, int most, int want, Fits fits) {
+inline bool band_wgrad_split(BandWgradGeom &b, int most, Fits fits) {
     int rmax = 0;
     while (rmax < b.OH && fits(rmax + 1)) ++rmax;
     if (rmax < 1) return false;
     int nb = (b.OH + rmax - 1) / rmax;
-    if (b.nframes * nb < want) nb = std::max(nb, std::min(b.OH, want / b.nframes));
+    if (b.nframes * nb < BAND_WGRAD_ITEMS) nb = std::max(nb, std::min(b.OH, BAND_WGRAD_ITEMS / b.nframes));
     b.R = (b.OH + nb - 1) / nb;
     b.nb = (b.OH + b.R - 1) / b.R;
     b.items = b.nframes * b.nb;
@@ -717,9 +718,9 @@ inline bool band_wgrad_geom(BandWgradGeom &b, int n, int H, int W) {
     auto fits = [&](int R, int lds) {
         return band_wgrad_lds(b, R, ONE) <= lds && (2 * R + 2) * 16 * b.nx <= 256 * BAND_WGRAD_MAXX && 32 * R * b.NO <= 256 * BAND_WGRAD_MAXD;
     };
-    const int most = 8192 / OC, want = 128;
-    return band_wgrad_split(b, most, want, [&](int R) { return fits(R, BAND_HALF_LDS); }) ||
-           band_wgrad_split(b, most, want, [&](int R) { return fits(R, BAND_LDS - 2048); });
+    const int most = 8192 / OC;
+    return band_wgrad_split(b, most, [&](int R) { return fits(R, BAND_HALF_LDS); }) ||
+           band_wgrad_split(b, most, [&](int R) { return fits(R, BAND_LDS - 2048); });
 }
 // Partial gradients that an update of n frames leaves; 0: the layer's maps do not fit.
 template <int OC>
@@ -761,7 +762,7 @@ inline bool bytes_wgrad_geom(BandWgradGeom &b, int n, int H, bool one) {
     b.nframes = n; b.H = H; b.W = BYTES_W; b.OH = (H - 8) / S + 1; b.OW = (BYTES_W - 8) / S + 1;
     b.NO = (b.OW + 7) / 8;
     b.dNO = FastDiv((uint32_t)b.NO);
-    return band_wgrad_split(b, 512, 128, [&](int R) {
+    return band_wgrad_split(b, 512, [&](int R) {
         return bytes_wgrad_lds<S>(b, R, one) <= BAND_HALF_LDS && ((R - 1) * S + 8) * BYTES_Q <= 256 * BYTES_WGRAD_MAXX &&
                32 * R * b.NO <= 256 * BYTES_WGRAD_MAXD;
     });

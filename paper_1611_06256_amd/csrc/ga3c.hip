@@ -2312,6 +2312,14 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     return GA3C_OK;
 }
 
+// Partial weight gradients that an update of B frames leaves for a layer on conv_band_grads.hpp's kernels; 0 for every other layer.
+int band_grad_parts(const ga3c_ctx *c, int l, int B) {
+    const ConvGeom &g = c->geom[l];
+    if (!c->band[l]) return 0;
+    if (l == 0) return bytes_wgrad_ok(g.S, g.OC) ? bytes_wgrad_parts(B, g.H, g.S, c->rb) : 0;
+    return g.OC == 32 ? band_wgrad_parts<32>(B, g.H, g.W, c->rb) : band_wgrad_parts<64>(B, g.H, g.W, c->rb);
+}
+
 // Floats of split-k workspace a call on up to `cap` frames can need.
 size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
     size_t need = 0;
@@ -2330,7 +2338,11 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
         for (int l = 0; l < c->nconv; ++l) {
             const ConvGeom &g = c->geom[l];
             pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kc);
-            nz = std::max(nz, c->band[l] ? 512 : std::min(B, 512));              // any-shape kernel, or one partial per block
+            // any-shape kernel; one partial per block; or bands: as many as fit from BAND_WGRAD_ITEMS frames on, before that also more
+            // of fewer rows (five frames of the stride-3 member 12 MB, with the 512 of the largest updates 120)
+            if (!c->band[l]) nz = std::max(nz, std::min(B, 512));
+            for (int b = 1; c->band[l] && b <= std::min(B, BAND_WGRAD_ITEMS); ++b) nz = std::max(nz, band_grad_parts(c, l, b));
+            nz = std::max(nz, band_grad_parts(c, l, B));
             add((size_t)nz * g.OC * (g.K + 1));
         }
         int nz2;
@@ -2846,6 +2858,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         {
             const void *xin = l == 0 ? (const void *)frames : (const void *)w.act[l - 1];
             const bool ok = c->fast && is_aligned16(xin);
+            const int band_nz = band_grad_parts(c, l, B);
             const int kind = !ok || !is_aligned16(c->dact[l]) ? 0
                                      : spec_matches<SpecS1>(g, l == 0) ? 1
                                      : spec_matches<SpecL1>(g, l == 0) ? 2
@@ -2853,7 +2866,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                                      : spec_matches<SpecL2>(g, l == 0) ? 4
                                      : spec_matches<SpecL3>(g, l == 0) ? 5
                                      : spec_matches<SpecP2>(g, l == 0) ? 6
-                                     : c->band[l] && (l > 0 || bytes_wgrad_ok(g.S, g.OC)) ? 8
+                                     : band_nz > 0 ? 8
                                      : c->band[l] && f32_wgrad_ok(g.C, g.H, g.W, g.S, g.OC) ? 7 : 0;
             if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
             else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
@@ -2861,8 +2874,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             else if (kind == 4) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
             else if (kind == 5) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
             else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
-            else if (kind == 8) nz = l == 0 ? bytes_wgrad_parts(B, g.H, g.S, c->rb)
-                                   : g.OC == 32 ? band_wgrad_parts<32>(B, g.H, g.W, c->rb) : band_wgrad_parts<64>(B, g.H, g.W, c->rb);
+            else if (kind == 8) nz = band_nz;
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");

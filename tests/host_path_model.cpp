@@ -49,7 +49,7 @@ static std::set<hipStream_t> given;                   // handles that the runnin
 static Seen host;                                     // launches known to be over
 static bool in_call = false;                          // inside a call that only enqueues
 static int allocations = 0, records = 0;
-static size_t device_bytes = 0;
+static size_t device_bytes = 0, last_bytes = 0;      // device memory held, and asked for last
 
 static Stream *use(hipStream_t s, const char *what) {
     if (in_call && !given.count(s)) PROBLEM("%s on a stream that the call was not given", what);
@@ -134,7 +134,7 @@ static hipError_t take(void **p, size_t n) {
     *p = malloc(n < 4096 ? n : 4096);                 // device memory is never touched here
     return hipSuccess;
 }
-hipError_t hipMalloc(void **p, size_t n) { take(p, n); device_memory[*p] = n; device_bytes += n; return hipSuccess; }
+hipError_t hipMalloc(void **p, size_t n) { take(p, n); device_memory[*p] = n; device_bytes += n; last_bytes = n; return hipSuccess; }
 hipError_t hipFree(void *p) { if (p) { device_bytes -= device_memory[p]; device_memory.erase(p); free(p); } return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned flags) {
     ++allocations;
@@ -453,6 +453,34 @@ static void failures_check() {
             }
 }
 
+// The workspace of partial sums, which a context allocates last: enough for an update of every size up to the capacity, on both
+// kinds of kernels, and for a few frames of the any-size layers no more than the bands that they are cut into.
+static void workspace_check() {
+    for (const char *net : {"small", "large", "paper1", "paper2", "paper3", "paper4"})
+        for (int math : {0, 1})
+            for (int cap : {1, 5, 40, 140}) {
+                ga3c_net_desc d = net_desc(net);
+                d.math = math;
+                ga3c_ctx *ctx = nullptr;
+                if (ga3c_create(&d, 0, cap, &ctx) != GA3C_OK) { PROBLEM("create: %s", ga3c_last_error()); continue; }
+                // 128 bands, a few more where they don't come out even, of three layers; any other sum takes no more than the parameters
+                const size_t most = 4 * (160 * (32 * 257 + 32 * 513 + 64 * 513) + 2 * ga3c_params_count(ctx));
+                if (!strncmp(net, "paper", 5) && cap <= 5 && last_bytes > most) PROBLEM("%s, %d frames: %zu bytes of workspace", net, cap, last_bytes);
+                const ga3c_hparams hp = {0.99f, 0.01f, 1.f, 0.f, 1e-4f, 0.99f, 0.1f, 40.f};
+                for (int generic : {0, 1}) {
+                    ga3c_use_generic_kernels(ctx, generic);
+                    for (int B = 1; B <= cap; ++B)
+                        if (ga3c_train_step(ctx, address(0), (const int32_t *)address(1), (const float *)address(2), address(3), nullptr, B, 1, &hp, nullptr, nullptr) != GA3C_OK) {
+                            PROBLEM("%s, math %d, capacity %d: an update of %d frames: %s", net, math, cap, B, ga3c_last_error());
+                            break;
+                        }
+                    ops.clear(); host.clear(); streams[nullptr] = Stream();      // what comes next is another program
+                    for (auto &e : events) e.second.seen.clear();
+                }
+                ga3c_destroy(ctx);
+            }
+}
+
 int main(int argc, char **argv) {
     streams[nullptr] = Stream();
     const std::string what = argc > 1 ? argv[1] : "";
@@ -462,6 +490,7 @@ int main(int argc, char **argv) {
     else if (what == "ticks") ticks_check();
     else if (what == "memory") memory_check();
     else if (what == "failures") failures_check();
+    else if (what == "workspace") workspace_check();
     else PROBLEM("no such check");
     printf("%zu launches, %d problems\n", ops.size(), problems);
     return problems ? 1 : 0;
