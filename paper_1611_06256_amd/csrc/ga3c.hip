@@ -1993,28 +1993,28 @@ inline unsigned blocks_for(size_t n, int per = 256) { return (unsigned)((n + per
 // Number of k-chunks for a split-k product with `tiles` output tiles and a
 // reduction of length K: enough blocks to fill 256 compute units a few times
 // over, chunks a multiple of the k-tile and at least two k-tiles long.
-inline void pick_split(int tiles, int K, int &nz, int &kchunk) {
-    int want = (512 + tiles - 1) / tiles;
-    int maxz = std::max(1, K / (2 * GEMM_BK));
-    want = std::max(1, std::min(want, maxz));
+// split_want: what is asked for, never fewer with a larger K (a workspace is sized by it); rounding the chunks up may leave fewer.
+inline int split_want(int tiles, int K) {
+    const int maxz = std::max(1, K / (2 * GEMM_BK));
+    return std::max(1, std::min((512 + tiles - 1) / tiles, maxz));
+}
+inline void split_into(int want, int K, int &nz, int &kchunk) {
     kchunk = (K + want - 1) / want;
     kchunk = (kchunk + GEMM_BK - 1) / GEMM_BK * GEMM_BK;
     nz = (K + kchunk - 1) / kchunk;
 }
+inline void pick_split(int tiles, int K, int &nz, int &kchunk) { split_into(split_want(tiles, K), K, nz, kchunk); }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 // k-chunks for the XCD-partitioned dense product: a multiple of 8 chunks (one
 // or more per XCD) when the reduction is long enough, about `target` blocks in
 // all (fewer chunks mean fewer partial sums to write and add up again).
-inline void pick_split_xcd(int tiles, int K, int &nz, int &kchunk, int target = 512) {
-    int want = 8 * std::max(1, (target + 8 * tiles - 1) / (8 * tiles));
-    const int maxz = std::max(1, K / (2 * GEMM_BK));
-    if (want > maxz) want = maxz >= 8 ? maxz / 8 * 8 : maxz;
-    kchunk = (K + want - 1) / want;
-    kchunk = (kchunk + GEMM_BK - 1) / GEMM_BK * GEMM_BK;
-    nz = (K + kchunk - 1) / kchunk;
+inline int split_want_xcd(int tiles, int K, int target) {
+    const int want = 8 * std::max(1, (target + 8 * tiles - 1) / (8 * tiles)), maxz = std::max(1, K / (2 * GEMM_BK));
+    return want <= maxz ? want : maxz >= 8 ? maxz / 8 * 8 : maxz;
 }
+inline void pick_split_xcd(int tiles, int K, int &nz, int &kchunk, int target = 512) { split_into(split_want_xcd(tiles, K, target), K, nz, kchunk); }
 
 int alloc_work(Work &w, const ga3c_ctx *c, int cap, bool training) {
     w.cap = cap;
@@ -2334,10 +2334,9 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
     if (training && B > 0) {       // every weight gradient has a region of its own (rounded up to 64 floats)
         size_t sum = 0;
         auto add = [&](size_t floats) { sum += (floats + 63) / 64 * 64; };
-        int nz, kc;
         for (int l = 0; l < c->nconv; ++l) {
             const ConvGeom &g = c->geom[l];
-            pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kc);
+            int nz = split_want(conv_like_tiles(g.OC, g.K + 1), B * g.OHW);
             // any-shape kernel; one partial per block; or bands: as many as fit from BAND_WGRAD_ITEMS frames on, before that also more
             // of fewer rows (five frames of the stride-3 member 12 MB, with the 512 of the largest updates 120)
             if (!c->band[l]) nz = std::max(nz, std::min(B, 512));
@@ -2345,13 +2344,10 @@ size_t workspace_floats(const ga3c_ctx *c, int cap, bool training) {
             nz = std::max(nz, band_grad_parts(c, l, B));
             add((size_t)nz * g.OC * (g.K + 1));
         }
-        int nz2;
-        pick_split(cdiv(c->F, 64) * cdiv(c->flat + 1, 64), B, nz, kc);
-        pick_split_xcd(cdiv(c->F, 64) * cdiv(c->flat, 64), B, nz2, kc, 256);
-        if (c->fold_ok && fc_grads_fold(c->F, c->flat, 1 << 30, c->dhp.terms)) nz2 = 0;
-        add((size_t)std::max(nz, nz2) * c->F * (c->flat + 1));
-        pick_split(conv_like_tiles(c->A + 1, c->F + 1), B, nz, kc);
-        add((size_t)std::max(nz, cdiv(B, HD_FRAMES)) * (c->A + 1) * (c->F + 1));
+        const bool fold = c->fold_ok && fc_grads_fold(c->F, c->flat, 1 << 30, c->dhp.terms);
+        const int dense = fold ? 0 : split_want_xcd(cdiv(c->F, 64) * cdiv(c->flat, 64), B, 256);
+        add((size_t)std::max(split_want(cdiv(c->F, 64) * cdiv(c->flat + 1, 64), B), dense) * c->F * (c->flat + 1));
+        add((size_t)std::max(split_want(conv_like_tiles(c->A + 1, c->F + 1), B), cdiv(B, HD_FRAMES)) * (c->A + 1) * (c->F + 1));
         need = (need + 63) / 64 * 64 + sum;      // the regions follow the fc partial sums
     }
     return need;

@@ -458,7 +458,7 @@ static void failures_check() {
 static void workspace_check() {
     for (const char *net : {"small", "large", "paper1", "paper2", "paper3", "paper4"})
         for (int math : {0, 1})
-            for (int cap : {1, 5, 40, 140}) {
+            for (int cap : {1, 5, 40, 140, 600, 1280}) {
                 ga3c_net_desc d = net_desc(net);
                 d.math = math;
                 ga3c_ctx *ctx = nullptr;
@@ -469,13 +469,16 @@ static void workspace_check() {
                 const ga3c_hparams hp = {0.99f, 0.01f, 1.f, 0.f, 1e-4f, 0.99f, 0.1f, 40.f};
                 for (int generic : {0, 1}) {
                     ga3c_use_generic_kernels(ctx, generic);
-                    for (int B = 1; B <= cap; ++B)
+                    for (int B = 1; B <= cap; ++B) {
                         if (ga3c_train_step(ctx, address(0), (const int32_t *)address(1), (const float *)address(2), address(3), nullptr, B, 1, &hp, nullptr, nullptr) != GA3C_OK) {
                             PROBLEM("%s, math %d, capacity %d: an update of %d frames: %s", net, math, cap, B, ga3c_last_error());
                             break;
                         }
-                    ops.clear(); host.clear(); streams[nullptr] = Stream();      // what comes next is another program
-                    for (auto &e : events) e.second.seen.clear();
+                        if (B % 20 == 0 || B == cap) {             // the order of these launches is not what is looked at
+                            ops.clear(); host.clear(); streams[nullptr] = Stream();
+                            for (auto &e : events) e.second.seen.clear();
+                        }
+                    }
                 }
                 ga3c_destroy(ctx);
             }
