@@ -63,13 +63,13 @@ constexpr int band_pitch() { return 16 * lds_row_units(C / 8); }
 
 // ---------------------------------------------------------------- fragments --
 
-// One tensor's fragments: n threads write three vectors (the terms) each, at dst[(i / 64 * 3 + term) * 64 + i % 64]; FRAG_F32:
-// one vector of four weights each, at dst[i].
+// One tensor's fragments: n threads write a vector for each term (three, or one where operands are rounded to bfloat16), at
+// dst[(i / 64 * terms + term) * 64 + i % 64]; FRAG_F32: one vector of four weights each, at dst[i].
 enum { FRAG_CONV = 0, FRAG_BYTES8 = 1, FRAG_DGRAD = 2, FRAG_F32 = 3 };
 struct FragJob {
     const float *w;          // [OC][C][KS][KS]
     u32x4 *dst;
-    int kind, C, OC, KS, n, first_block;
+    int kind, terms, C, OC, KS, n, first_block;
 };
 constexpr int MAX_FRAG_JOBS = 12;
 struct FragJobs {
@@ -108,8 +108,9 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
     }
     u32x4 h, m, l;
     split3x8(f, h, m, l);
-    u32x4 *dst = j.dst + (size_t)(i / 64) * 3 * 64 + lane;
-    dst[0] = h; dst[64] = m; dst[128] = l;
+    u32x4 *dst = j.dst + (size_t)(i / 64) * j.terms * 64 + lane;
+    dst[0] = h;
+    if (j.terms == 3) { dst[64] = m; dst[128] = l; }
 }
 
 // ------------------------------------------------------------------ staging --
@@ -173,9 +174,9 @@ __global__ __launch_bounds__(256, 2) void conv_band_fwd_kernel(const float *__re
     int item = blockIdx.x;
     fetch(min(item, b.items - 1));
 
-    Bf16x8Bits wq[KB];                                       // the first of three terms
+    Bf16x8Bits wq[KB];
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb) wq[kb].u = wfrag[(size_t)(ot * KB + kb) * 3 * 64 + lane];
+    for (int kb = 0; kb < KB; ++kb) wq[kb].u = wfrag[(size_t)(ot * KB + kb) * 64 + lane];
     const float bv = bias[ot * 16 + l16];
 
     for (; item < b.items; item += gridDim.x) {
@@ -303,7 +304,7 @@ inline bool band_ok(int H, int W) {
     return H >= 4 && W >= 4 && band_fwd_geom<C>(b, 1);
 }
 
-// x [n][32][H][W] -> y [n][OC][OH][OW]; wfrag: FRAG_CONV of the filters.
+// x [n][32][H][W] -> y [n][OC][OH][OW]; wfrag: FRAG_CONV of the filters, one term.
 template <int C, int OC>
 inline hipError_t launch_conv_band_fwd(const float *x, const u32x4 *wfrag, const float *bias, float *y, int n, int H, int W, hipStream_t s) {
     if (n <= 0) return hipSuccess;

@@ -102,11 +102,11 @@ __global__ __launch_bounds__(256, OC == 32 ? 2 : 1) void conv_band_dgrad_kernel(
 
     Bf16x8Bits wq[2][KB][NTERM];
     {
-        const u32x4 *ws = wfrag + (size_t)((ct * 2 + ry) * 2 * KB) * 3 * 64 + lane;
+        const u32x4 *ws = wfrag + (size_t)((ct * 2 + ry) * 2 * KB) * NTERM * 64 + lane;
 #pragma unroll
         for (int q = 0; q < 2 * KB; ++q)
 #pragma unroll
-            for (int t = 0; t < NTERM; ++t) wq[q / KB][q % KB][t].u = ws[(q * 3 + t) * 64];
+            for (int t = 0; t < NTERM; ++t) wq[q / KB][q % KB][t].u = ws[(q * NTERM + t) * 64];
     }
 
     for (; item < b.items; item += gridDim.x) {
@@ -237,7 +237,7 @@ inline hipError_t launch_conv_band_dgrad1(const float *dy, const u32x4 *wfrag, c
     return hipGetLastError();
 }
 // dy [n][OC][OH][OW] -> dx [n][32][H][W], masked by xin > 0, or by its bits where the forward pass has left them; wfrag: FRAG_DGRAD
-// of w [OC][32][4][4].
+// of w [OC][32][4][4], three terms or one (rb).
 template <int OC>
 inline hipError_t launch_conv_band_dgrad(const float *dy, const u32x4 *wfrag, const float *xin, const PositiveBits &bits, float *dx, int n, int H, int W,
                                          hipStream_t s, int rb) {

@@ -77,11 +77,11 @@ __global__ __launch_bounds__(256, 2) void conv_bytes_fwd_kernel(const uint8_t *_
     fetch(min(item, b.items - 1));
     Bf16x8Bits wq[KB][NTERM];
     {
-        const u32x4 *ws = wfrag + (size_t)(ot * KB) * 3 * 64 + lane;
+        const u32x4 *ws = wfrag + (size_t)(ot * KB) * NTERM * 64 + lane;
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int t = 0; t < NTERM; ++t) wq[kb][t].u = ws[(kb * 3 + t) * 64];
+            for (int t = 0; t < NTERM; ++t) wq[kb][t].u = ws[(kb * NTERM + t) * 64];
     }
     const float bv = bias[ot * 16 + l16];
     for (; item < b.items; item += gridDim.x) {

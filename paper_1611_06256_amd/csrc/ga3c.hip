@@ -2095,7 +2095,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
         jobs.n = 0;
         int blocks = 0;
         auto add = [&](int l, int kind, u32x4 *dst, int n) {
-            jobs.job[jobs.n++] = FragJob{c->theta2[i] + c->off[2 * l], dst, kind, c->geom[l].C, c->geom[l].OC, c->geom[l].KS, n, blocks};
+            jobs.job[jobs.n++] = FragJob{c->theta2[i] + c->off[2 * l], dst, kind, c->rb ? 1 : 3, c->geom[l].C, c->geom[l].OC, c->geom[l].KS, n, blocks};
             blocks += cdiv(n, 256);
         };
         for (int l = 0; l < c->nconv; ++l) {
@@ -2486,7 +2486,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         const ConvGeom &g = c->geom[l];
         c->band[l] = on_band_kernels(g, l);
         if (!c->band[l]) continue;
-        const size_t vecs = (size_t)3 * g.OC * g.K / 8;
+        const size_t vecs = (size_t)(c->rb ? 1 : 3) * g.OC * g.K / 8;
         if (l == 0 || c->rb) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
         if (!c->rb && (l > 0 || max_train_frames > 0)) { c->bfrag_f32[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)g.OC * g.K / 4; }
         if (l > 0 && max_train_frames > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }

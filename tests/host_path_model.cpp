@@ -484,6 +484,29 @@ static void workspace_check() {
             }
 }
 
+// What a context keeps of the any-size layers' filters: with operands rounded to bfloat16 one term of two bytes per weight and
+// purpose, which is less than the terms, or the floats in another order, of the exact variant.
+static void fragments_check() {
+    for (int train : {0, 5}) {
+        size_t bytes[2];
+        for (int math : {0, 1}) {
+            ga3c_net_desc d = net_desc("paper3");
+            d.math = math;
+            d.fc_units = 16;                              // too few for the fc layer's operands to be kept
+            const size_t before = device_bytes;
+            ga3c_ctx *ctx = nullptr;
+            if (ga3c_create(&d, 1, train, &ctx) != GA3C_OK) { PROBLEM("create: %s", ga3c_last_error()); return; }
+            bytes[math] = device_bytes - before;
+            ga3c_destroy(ctx);
+            if (device_bytes != before) PROBLEM("%zu bytes of device memory left behind", device_bytes - before);
+        }
+        const size_t weights = 32 * 256 + 32 * 512 + 64 * 512;
+        // two copies: the byte layer's terms (6 bytes a weight) and the others' floats against one term of each
+        if (train == 0 && bytes[0] - bytes[1] < 2 * (6 * 8192 + 4 * (weights - 8192) - 2 * weights)) PROBLEM("%zu bytes exact, %zu rounded", bytes[0], bytes[1]);
+        if (bytes[1] >= bytes[0]) PROBLEM("%d frames: %zu bytes exact, %zu rounded", train, bytes[0], bytes[1]);
+    }
+}
+
 int main(int argc, char **argv) {
     streams[nullptr] = Stream();
     const std::string what = argc > 1 ? argv[1] : "";
@@ -494,6 +517,7 @@ int main(int argc, char **argv) {
     else if (what == "memory") memory_check();
     else if (what == "failures") failures_check();
     else if (what == "workspace") workspace_check();
+    else if (what == "fragments") fragments_check();
     else PROBLEM("no such check");
     printf("%zu launches, %d problems\n", ops.size(), problems);
     return problems ? 1 : 0;
