@@ -401,12 +401,12 @@ __global__ __launch_bounds__(256, 2) void conv_band_wgrad_kernel(const float *__
     for (; item < end; ++item) {
         const int rows = rows_of(item);
         __syncthreads();                                      // the last item's operands have been read
-        // what a vector holds behind its row's end meets zeros of dY; behind the last frame it need not be a number
-        if (item / b.nb == b.nframes - 1)
+        // what a vector holds behind its row's end meets zeros of dY, but it is another row's, another channel's or nobody's, and if it
+        // is not finite its products with zero are not numbers
 #pragma unroll
-            for (int i = 0; i < MAXX; ++i)
+        for (int i = 0; i < MAXX; ++i)
 #pragma unroll
-                for (int e = 1; e < 8; ++e) xpre[i][e] = e < xcol[i] ? xpre[i][e] : 0.f;
+            for (int e = 1; e < 8; ++e) xpre[i][e] = e < xcol[i] ? xpre[i][e] : 0.f;
 #pragma unroll
         for (int i = 0; i < MAXX; ++i)
             if (xdst[i] >= 0) {

@@ -169,3 +169,25 @@ def test_input_gradient_of_a_tall_narrow_map(G, oc, n):
     # products of bfloat16 are exact; at most 2 x 2 x oc of them are added in fp32
     bound = 4 * oc * 2.0 ** -24 * F.conv_transpose2d(dy.bfloat16().double().abs(), w.bfloat16().double().abs(), stride=2)
     assert bool(((dact - ref).abs() <= bound).all())
+
+
+def test_an_infinite_activation_stays_in_its_channel(G):
+    # a vector of eight columns ends in the next row, in the next channel or behind the last frame: what lies there meets zeros of dY,
+    # and infinity times zero is no number.  11x38 -> 4x18 with dY all zero (the fc layer's sums are no numbers, its rectifier makes them 0)
+    import torch
+    desc = G.NetDesc(in_c=4, in_h=30, in_w=84, conv=((32, 8, 2), (32, 4, 2)), fc_units=32, n_actions=4)
+    n, c = 5, 3
+    net = G.Ga3c(desc, n, n)
+    net.params_init(9801)
+    theta, at = net.params_get(0), net.offsets()
+    theta[at["conv1.b"][0] + c] = float("inf")
+    net.params_set(theta, 0)
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9802, n, 1, 4).items()}
+    net.train_step(torch.from_numpy(frames_of(9803, n, 30)).cuda().view(n, 1, 4, 30, 84), tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.0))
+    o = at["conv2.W"][0]
+    dw = net.params_get(2)[o:o + 32 * 32 * 16].view(32, 32, 16)
+    torch.cuda.synchronize()
+    net.close()
+    assert bool(dw[:, c].isnan().all())
+    dw[:, c] = 0
+    assert bool((dw == 0).all())
