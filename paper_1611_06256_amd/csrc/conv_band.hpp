@@ -63,6 +63,16 @@ constexpr int band_pitch() { return 16 * lds_row_units(C / 8); }
 
 // ---------------------------------------------------------------- fragments --
 
+__device__ __forceinline__ u32x4 band_round8(const float (&r)[8]) {
+    return u32x4{pack_bf16_rne(r[0], r[1]), pack_bf16_rne(r[2], r[3]), pack_bf16_rne(r[4], r[5]), pack_bf16_rne(r[6], r[7])};
+}
+// The largest bfloat16 for what would round to infinity and is none (the last 0.4 % of what an fp32 holds): the first term of such a
+// weight.  Infinity would leave minus infinity for the second, and every product of the filter would be no number.
+__device__ __forceinline__ float within_bf16(float x) {
+    const float most = __uint_as_float(0x7f7f0000u);
+    return fabsf(x) > most && fabsf(x) < __uint_as_float(0x7f800000u) ? copysignf(most, x) : x;
+}
+
 // One tensor's fragments: n threads write a vector for each term (three, or one where operands are rounded to bfloat16), at
 // dst[(i / 64 * terms + term) * 64 + i % 64]; FRAG_F32: one vector of four weights each, at dst[i].
 enum { FRAG_CONV = 0, FRAG_BYTES8 = 1, FRAG_DGRAD = 2, FRAG_F32 = 3 };
@@ -106,11 +116,15 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = j.w[((size_t)(ot * 16 + l16) * 4 + e % 4) * 64 + u * 8 + 2 * g + e / 4];
     }
-    u32x4 h, m, l;
-    split3x8(f, h, m, l);
     u32x4 *dst = j.dst + (size_t)(i / 64) * j.terms * 64 + lane;
-    dst[0] = h;
-    if (j.terms == 3) { dst[64] = m; dst[128] = l; }
+    for (int t = 0; t < j.terms; ++t) {
+        float near[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) near[e] = j.terms > 1 ? within_bf16(f[e]) : f[e];
+        dst[64 * t] = band_round8(near);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] -= bf16_rne(near[e]);
+    }
 }
 
 // ------------------------------------------------------------------ staging --
@@ -119,9 +133,6 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
 __device__ __forceinline__ void band_load8(const float *base, uint32_t off, int plane, float (&r)[8]) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) r[c] = *(const float *)((const char *)(base + (size_t)c * plane) + off);
-}
-__device__ __forceinline__ u32x4 band_round8(const float (&r)[8]) {
-    return u32x4{pack_bf16_rne(r[0], r[1]), pack_bf16_rne(r[2], r[3]), pack_bf16_rne(r[4], r[5]), pack_bf16_rne(r[6], r[7])};
 }
 // Floats left in a tensor of `total` behind `base`, less the eight planes a unit reads: the largest offset a unit may use.
 __device__ __forceinline__ uint32_t band_limit(size_t total, size_t base, int plane) {

@@ -191,3 +191,31 @@ def test_an_infinite_activation_stays_in_its_channel(G):
     assert bool(dw[:, c].isnan().all())
     dw[:, c] = 0
     assert bool((dw == 0).all())
+
+
+@pytest.mark.parametrize("shape", [SHAPES[0], dict(in_h=84, conv=((32, 8, 3), (32, 4, 2), (64, 4, 2)))])
+def test_weights_beyond_the_largest_bfloat16(G, shape):
+    # -3.4e38 is a number, though its first term would round to minus infinity: outputs with it are cut off, gradients of the rest stay
+    import torch
+    n = 4
+    desc = G.NetDesc(in_c=4, in_w=84, fc_units=32, n_actions=4, **shape)
+    fr = torch.from_numpy(frames_of(9901, n, desc.in_h)).cuda()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9902, n, 1, 4).items()}
+    got = []
+    for generic in (False, True):
+        net = G.Ga3c(desc, n, n)
+        net.params_init(9903)
+        theta, at = net.params_get(0), net.offsets()
+        for layer, k in (("conv1.W", 500), ("conv2.W", 5000), ("conv3.W", 9000)):
+            theta[at[layer][0] + k] = -3.4e38
+        net.params_set(theta, 0)
+        net.use_generic_kernels(generic)
+        print(f"generic={generic}", flush=True)
+        logits, values = torch.empty((n, 4), device="cuda"), torch.empty(n, device="cuda")
+        net.predict(fr, logits=logits, values=values)
+        net.train_step(fr.view(n, 1, 4, desc.in_h, 84), tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.0))
+        got.append([logits, values, net.params_get(2)])
+        torch.cuda.synchronize()
+        net.close()
+    for a, b in zip(*got):
+        assert bool(torch.isfinite(a).all()) and float((a - b).norm() / b.norm()) <= 5e-5      # sums of fp32 products through the layers
