@@ -171,6 +171,45 @@ def test_input_gradient_of_a_tall_narrow_map(G, oc, n):
     assert bool(((dact - ref).abs() <= bound).all())
 
 
+@pytest.mark.parametrize("shape", [SHAPES[0], dict(in_h=50, conv=((32, 8, 1), (32, 4, 2), (64, 4, 2))), dict(in_h=84, conv=((32, 8, 3), (32, 4, 2), (64, 4, 2)))])
+def test_gradients_are_as_near_to_the_exact_sums_as_those_of_the_fp32_instruction(G, shape):
+    # every layer's gradients from the library's own activations and dY, against products and sums in 64 bits: three bf16 terms an
+    # operand (csrc/conv_band_grads.hpp), and the any-shape kernels' chains of the fp32 instruction
+    import torch
+    import torch.nn.functional as F
+    n = 6
+    desc = G.NetDesc(in_c=4, in_w=84, fc_units=32, n_actions=4, **shape)
+    fr = torch.from_numpy(frames_of(9701, n, desc.in_h))
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9702, n, 1, 4).items()}
+    off = {}
+    for generic in (False, True):
+        net = G.Ga3c(desc, n, n)
+        net.params_init(9703)
+        net.use_generic_kernels(generic)
+        print(f"train generic={generic}", flush=True)
+        net.train_step(fr.cuda().view(n, 1, 4, desc.in_h, 84), tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.0))
+        theta, grad, at = net.params_get(0).cpu(), net.params_get(2).cpu(), net.offsets()
+        x, h, w = fr.double() / 255, desc.in_h, 84
+        for l, (oc, k, s) in enumerate(desc.conv):
+            oh, ow = (h - k) // s + 1, (w - k) // s + 1
+            act, dy = (net.train_debug_get(which + l, torch.empty((n, oc, oh, ow), device="cuda")).cpu().double() for which in (4, 10))
+            o, sh = at[f"conv{l + 1}.W"]
+            W, dW = (v[o:o + oc * sh[1] * k * k].view(*sh).double() for v in (theta, grad))
+            off[f"dW{l + 1}", generic] = float((dW - torch.nn.grad.conv2d_weight(x, W.shape, dy, stride=s)).norm() / dW.norm())
+            o = at[f"conv{l + 1}.b"][0]
+            db = grad[o:o + oc].double()
+            off[f"db{l + 1}", generic] = float((db - dy.sum((0, 2, 3))).norm() / db.norm())
+            if l:
+                dx = F.conv_transpose2d(dy, W, stride=s, output_padding=((h - k) % s, (w - k) % s)) * (x > 0)
+                off[f"dX{l + 1}", generic] = float((below - dx).norm() / dx.norm())
+            x, below, h, w = act, dy, oh, ow
+        net.close()
+    print({k[0]: (f"{v:.1e}", f"{off[k[0], True]:.1e}") for k, v in off.items() if not k[1]}, flush=True)
+    for (what, generic), v in off.items():
+        if not generic:
+            assert 0 < v <= off[what, True] and (what[:2] != "dX" or v <= 8e-8), (what, v, off[what, True])
+
+
 def test_an_infinite_activation_stays_in_its_channel(G):
     # a vector of eight columns ends in the next row, in the next channel or behind the last frame: what lies there meets zeros of dY,
     # and infinity times zero is no number.  11x38 -> 4x18 with dY all zero (the fc layer's sums are no numbers, its rectifier makes them 0)

@@ -492,7 +492,6 @@ def test_predict_and_train_paper_family_net(G, stride, B, N, T):
 
 def test_predict_and_train_forty_actions(G):
     # more than 31 actions: the heads, the loss and the heads' backward pass run as separate kernels in training
-    # (the fused kernel gives a thread to every (frame, output) pair of 8 frames)
     desc = G.SMALL_NET(40)
     check_predict(G, desc, 9, 7500, frames=synth.rectangle_frames(7501, 9))
     run_train(G, desc, 5, 5, 7510, dict(clip_norm=40.0), frames=synth.rectangle_frames(7511, 25).reshape(5, 5, 4, 84, 84))
