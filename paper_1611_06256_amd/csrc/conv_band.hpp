@@ -74,18 +74,19 @@ __device__ __forceinline__ float within_bf16(float x) {
 }
 
 // One tensor's fragments: n threads write a vector for each term (three, or one where operands are rounded to bfloat16), at
-// dst[(i / 64 * terms + term) * 64 + i % 64]; FRAG_F32: one vector of four weights each, at dst[i].
+// dst[(i / 64 * TERMS + term) * 64 + i % 64]; FRAG_F32: one vector of four weights each, at dst[i].
 enum { FRAG_CONV = 0, FRAG_BYTES8 = 1, FRAG_DGRAD = 2, FRAG_F32 = 3 };
 struct FragJob {
     const float *w;          // [OC][C][KS][KS]
     u32x4 *dst;
-    int kind, terms, C, OC, KS, n, first_block;
+    int kind, C, OC, KS, n, first_block;
 };
 constexpr int MAX_FRAG_JOBS = 12;
 struct FragJobs {
     FragJob job[MAX_FRAG_JOBS];
     int n;
 };
+template <int TERMS>
 __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJobs jobs) {
     int q = 0;
     while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.job[q + 1].first_block) ++q;
@@ -116,14 +117,19 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] = j.w[((size_t)(ot * 16 + l16) * 4 + e % 4) * 64 + u * 8 + 2 * g + e / 4];
     }
-    u32x4 *dst = j.dst + (size_t)(i / 64) * j.terms * 64 + lane;
-    for (int t = 0; t < j.terms; ++t) {
+    u32x4 *dst = j.dst + (size_t)(i / 64) * TERMS * 64 + lane;
+    if constexpr (TERMS == 1) dst[0] = band_round8(f);
+    else {
         float near[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) near[e] = j.terms > 1 ? within_bf16(f[e]) : f[e];
-        dst[64 * t] = band_round8(near);
+        for (int e = 0; e < 8; ++e) near[e] = within_bf16(f[e]);
+        dst[0] = band_round8(near);
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[e] -= bf16_rne(near[e]);
+        dst[64] = band_round8(f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] -= bf16_rne(f[e]);
+        dst[128] = band_round8(f);
     }
 }
 

@@ -2095,7 +2095,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
         jobs.n = 0;
         int blocks = 0;
         auto add = [&](int l, int kind, u32x4 *dst, int n) {
-            jobs.job[jobs.n++] = FragJob{c->theta2[i] + c->off[2 * l], dst, kind, c->rb ? 1 : 3, c->geom[l].C, c->geom[l].OC, c->geom[l].KS, n, blocks};
+            jobs.job[jobs.n++] = FragJob{c->theta2[i] + c->off[2 * l], dst, kind, c->geom[l].C, c->geom[l].OC, c->geom[l].KS, n, blocks};
             blocks += cdiv(n, 256);
         };
         for (int l = 0; l < c->nconv; ++l) {
@@ -2105,7 +2105,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
             if (!c->rb && (l > 0 || c->max_train > 0)) add(l, FRAG_F32, c->bfrag[i] + c->bfrag_f32[l], g.OC * g.K / 4);
             if (l > 0 && c->max_train > 0) add(l, FRAG_DGRAD, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
         }
-        ga3c::launch_stop(stop, band_filter_fragments_kernel, dim3(blocks), dim3(256), 0, s, jobs);
+        ga3c::launch_stop(stop, c->rb ? band_filter_fragments_kernel<1> : band_filter_fragments_kernel<3>, dim3(blocks), dim3(256), 0, s, jobs);
         HIP_TRY(hipGetLastError());
     }
     return GA3C_OK;
