@@ -48,7 +48,7 @@ typedef float f32x4_dw __attribute__((ext_vector_type(4), aligned(4)));
 typedef float f32x2_dw __attribute__((ext_vector_type(2), aligned(4)));
 
 // Where the items of a launch lie.  "Rows" are output rows for the forward pass, rows of the stride-phase grid
-// (ceil(H / 2)) for the input gradient (conv_band_f32.hpp).
+// (ceil(H / 2)) for the input gradient (conv_band_grads.hpp).
 struct BandGeom {
     int H, W, OH, OW;
     int F, R;                // an item: R rows of each of F consecutive frames (F > 1 only with all rows)

@@ -2194,7 +2194,8 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         // At fp32 accuracy the 4x4 layers run on the fp32 instruction, straight from memory, in both calls: faster than bands
         // staged as three bf16 terms up to 256 frames (128 frames: 77x77 map 65 / 73 us, 26x26 11.8 / 12.7, 12x12 with 64 filters 6.1 /
         // 10.2, the only loss 37x37 with 64 filters 27.9 / 24.8; one frame 4.6 / 9.8) and nearer to the exact sums (2.9e-7 /
-        // 3.3e-7).  The byte layer does so in updates only, whose activations keep the any-shape kernels' order of sums
+        // 3.3e-7); with 512 frames a call is still ahead (stride-1 member 545 -> 504 us, stride 3 76.1 -> 70.5, stride 4 56.8 -> 50.9).
+        // The byte layer does so in updates only, whose activations keep the any-shape kernels' order of sums
         // (conv_band_f32.hpp); predictions take three bf16 terms of its weights (128 frames, stride 3: 9.5 us, on the fp32
         // instruction 19.4).  With operands rounded to bfloat16 everything takes one term (640 frames of the stride-3 member, on
         // the fp32 instruction / with one term: conv1 70 / 22, conv2 35 / 19, conv3 16 / 10 us).
@@ -2286,7 +2287,9 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         const size_t lds = sizeof(float) * (c->A + 1) * (c->F + 4);
         HIP_TRY(allow_dynamic_lds((const void *)hp_kernels[k], lds, hp_lds_set[k]));
         STAGE("heads_fwd", 2.0 * B * c->F * (c->A + 1), 4.0 * fc_nz * B * c->F);
-        if (B <= 256 && hf == LOADS_VEC16) {      // a block per compute unit at most
+        // A block per compute unit at most.  With eight chunks or fewer (1024 units from 193 frames on) there is little to share out:
+        // calls of 193 / 224 / 256 frames of the stride-1 member 237 / 253 / 271 us with four frames a block, 233 / 250 / 269 with one.
+        if (B <= 256 && hf == LOADS_VEC16) {
             static const HeadsPredict few[3] = {heads_predict_few_kernel<1>, heads_predict_few_kernel<2>, heads_predict_few_kernel<4>};
             ga3c::launch(few[nj / 2], dim3(B), dim3(256), 0, s, fc_ws, fc_nz, th + c->off[nb + 1], B, c->A, th + c->off[nb + 2],
                          th + c->off[nb + 3], th + c->off[nb + 4], th + c->off[nb + 5], logits, values, probs, uniforms, actions, c->rb);
@@ -2684,9 +2687,12 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     const int cur = c->cur;
     const float *th = c->theta2[cur];
     TRY(wait_ready(c, s));
-    // One kernel finishes the fc layer, runs the heads, the loss and the heads' backward pass, if its LDS fits.
+    // One kernel finishes the fc layer, runs the heads, the loss and the heads' backward pass, if its LDS fits, for at most the 31
+    // actions that it is tested with.  Its layout would do for 63 (the loss has an output per lane), and it would be ahead there: us an
+    // update, separate kernels / this one, small net with 32 actions 40 frames 85.7 / 68.0, 2560 frames 304.7 / 292.7, with 63 actions
+    // 104.0 / 72.1 and 330.1 / 302.1; larger net with 32 actions 640 frames 357.6 / 336.3.
     const size_t ht_lds = sizeof(float) * (size_t)heads_train_lds_floats(F, A);
-    const bool fused_heads = c->fast && ht_lds <= HEADS_TRAIN_MAX_LDS && HD_FRAMES * (A + 1) <= 256;      // a thread per (frame, output)
+    const bool fused_heads = c->fast && ht_lds <= HEADS_TRAIN_MAX_LDS && A <= 31;
     int rc = forward(c, cur, w, frames, table, B, true, nullptr, nullptr, nullptr, nullptr, nullptr, s, !fused_heads);
     if (rc != GA3C_OK) return rc;
 
@@ -2732,8 +2738,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         red_blocks += 8 * g.per_xcd;
         red_bytes += 4.0 * (nz_ + 1) * rows * Ncols;
     };
-    const size_t hd_lds = sizeof(float) * (A + 1) * HD_FRAMES;      // heads_dgrad_kernel's LDS
-    static size_t hd_lds_set = 0;
+    const size_t hd_lds = sizeof(float) * (A + 1) * HD_FRAMES;      // heads_dgrad_kernel's LDS, 2 KB at most
     if (fused_heads) {
         const int nblk = cdiv(B, HD_FRAMES);
         float *part = region((size_t)nblk * (A + 1) * (F + 1));
@@ -2758,7 +2763,6 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         float *part = region((size_t)nblk * (A + 1) * (F + 1));
         if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (heads)");
         STAGE("heads_bwd", 4.0 * B * (A + 1) * F, 0);
-        HIP_TRY(allow_dynamic_lds((const void *)heads_dgrad_kernel, hd_lds, hd_lds_set));
         ga3c::launch(heads_dgrad_kernel, dim3(nblk, cdiv(F, HD_COLS)), dim3(HD_COLS), hd_lds, s, c->dzv, w.h, Wp, Wv, B,
                            F, A, c->dh, c->colpart, part, c->rb);
         HIP_TRY(hipGetLastError());
@@ -2780,7 +2784,6 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
         add_seg(p.C, nz, A + 1, F + 1, 0, A, c->grad + c->off[nb + 2], c->grad + c->off[nb + 3], 1);
         add_seg(p.C, nz, A + 1, F + 1, A, 1, c->grad + c->off[nb + 4], c->grad + c->off[nb + 5], 1);
         STAGE("heads_dgrad", 2.0 * B * (A + 1) * F, 0);
-        HIP_TRY(allow_dynamic_lds((const void *)heads_dgrad_kernel, hd_lds, hd_lds_set));
         ga3c::launch(heads_dgrad_kernel, dim3(cdiv(B, HD_FRAMES), cdiv(F, HD_COLS)), dim3(HD_COLS), hd_lds, s, c->dzv, w.h, Wp, Wv, B,
                            F, A, c->dh, c->colpart, (float *)nullptr, c->rb);
         HIP_TRY(hipGetLastError());
