@@ -249,7 +249,7 @@ int harvest(ga3c_sched *s, bool wait) {
         if (wait) SHIP(hipEventSynchronize(p.done));
         else if (!results_arrived(p)) {
             const hipError_t q = hipEventQuery(p.done);
-            if (q == hipErrorNotReady) continue;
+            if (q == hipErrorNotReady) break;                // a later one that is over by now waits for this one
             if (q != hipSuccess) return sfail(GA3C_EHIP, "hipEventQuery: %s", hipGetErrorString(q));
         }
         try { s->ready.room(p.n); } NO_MEMORY("ga3c_sched: results")

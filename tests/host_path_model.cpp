@@ -116,7 +116,12 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) { join(use(s, "hipStreamWaitEvent")->seen, events[e].seen); return hipSuccess; }
-hipError_t hipEventQuery(hipEvent_t e) { join(host, events[e].seen); return hipSuccess; }
+static int queries_left = -1;                         // event queries until one finds its event not completed
+hipError_t hipEventQuery(hipEvent_t e) {
+    if (fails(queries_left)) return hipErrorNotReady;
+    join(host, events[e].seen);
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t e) { join(host, events[e].seen); return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 
@@ -507,6 +512,39 @@ static void fragments_check() {
     }
 }
 
+// Two batches in flight, of which the second is over by the time that it is looked at and the first was not yet: results come
+// oldest first all the same.
+static void order_check() {
+    Program p("small");
+    p.init(nullptr);
+    ga3c_sched_config cfg;
+    memset(&cfg, 0, sizeof(cfg));
+    cfg.t_max = 5; cfg.predict_cap = 4; cfg.train_min = 10; cfg.train_cap = 40; cfg.hp = p.hp;
+    ga3c_sched *s = nullptr;
+    if (ga3c_sched_create(p.ctx, &cfg, &s) != GA3C_OK) { PROBLEM("sched_create: %s", ga3c_sched_last_error()); return; }
+    for (int round = 0; round < 6; ++round) {              // every slot comes first once
+        int predicted = 0;
+        for (int a = 0; a < 8; ++a)
+            if (ga3c_sched_submit_predict(s, a, address(a), 0.5f) != GA3C_OK) PROBLEM("submit_predict");
+        for (int k = 0; k < 2; ++k) {
+            queries_left = 0;                              // the tick's own look at the first batch
+            if (ga3c_sched_tick(s, &predicted, nullptr) != GA3C_OK || predicted != 4) PROBLEM("tick: %d", predicted);
+        }
+        ga3c_prediction out[16];
+        queries_left = 0;
+        int got = ga3c_sched_poll(s, out, 16);
+        queries_left = -1;
+        while (got < 8) {
+            const int more = ga3c_sched_poll(s, out + got, 16 - got);
+            if (more <= 0) { PROBLEM("%d of 8 results", got); break; }
+            got += more;
+        }
+        for (int a = 0; a < got; ++a)
+            if (out[a].agent != a) { PROBLEM("result %d is agent %d's", a, out[a].agent); break; }
+    }
+    ga3c_sched_destroy(s);
+}
+
 int main(int argc, char **argv) {
     streams[nullptr] = Stream();
     const std::string what = argc > 1 ? argv[1] : "";
@@ -516,6 +554,7 @@ int main(int argc, char **argv) {
     else if (what == "ticks") ticks_check();
     else if (what == "memory") memory_check();
     else if (what == "failures") failures_check();
+    else if (what == "order") order_check();
     else if (what == "workspace") workspace_check();
     else if (what == "fragments") fragments_check();
     else PROBLEM("no such check");

@@ -35,6 +35,7 @@ def model(tmp_path_factory):
     "memory",       # host memory that runs out in the scheduler's queues
     "workspace",    # partial sums of updates of any size, and no more memory for them than those need
     "fragments",    # the any-size layers' filters, as terms or rounded
+    "order",        # results of several batches, oldest first
     "failures",     # launches and event records that fail in a scheduler's tick
 ])
 def test_host_path(model, check):
