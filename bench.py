@@ -87,11 +87,12 @@ KERNELS = {"conv12_fwd": "conv12_fused_fwd_kernel", "fc_fwd": "fc_forward_kernel
            "heads_train": "heads_train_kernel", "conv1_wgrad": "conv1_bf16x3_wgrad_kernel",
            "conv2_wgrad": "conv_grads_bf16x6_kernel", "conv3_wgrad": "conv_wgrad_s1_bf16x6_kernel",
            "conv2_dgrad": "conv_grads_bf16x6_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
-           "conv1_fwd": "conv1_bf16x3_fwd_kernel", "conv2_fwd": "conv_fwd_bf16x6_kernel", "conv3_fwd": "conv_fwd_bf16x6_kernel",
+           "conv123_fwd": "conv123_f16_kernel", "conv1_fwd": "conv1_bf16x3_fwd_kernel", "conv2_fwd": "conv_fwd_bf16x6_kernel", "conv3_fwd": "conv_fwd_bf16x6_kernel",
            "wgrad_reduce": "reduce_all_kernel", "rmsprop": "rmsprop_kernel", "predict_small": "predict_small_kernel"}
 # bf16 MFMAs executed per nominal one with fp32-grade accuracy (operand split into three bf16 terms); "f32" = the
-# stage runs on the fp32 matrix cores
-TERMS = {"conv1_fwd": 3, "conv2_fwd": 6, "conv3_fwd": 6, "fc_fwd": 6, "fc_wgrad": 6, "fc_dgrad": 6, "conv1_wgrad": 3,
+# stage runs on the fp32 matrix cores.  conv123_fwd has two float16 terms of every number but the bytes, 2 products in
+# its first layer and 3 in the others.
+TERMS = {"conv123_fwd": 2.58, "conv1_fwd": 3, "conv2_fwd": 6, "conv3_fwd": 6, "fc_fwd": 6, "fc_wgrad": 6, "fc_dgrad": 6, "conv1_wgrad": 3,
          "conv2_dgrad": 6, "conv3_dgrad": 6, "conv2_wgrad": 6, "conv3_wgrad": 6}
 HBM_STAGES = {"rmsprop", "wgrad_reduce"}
 

@@ -28,6 +28,7 @@
 #include "conv2_bf16x6.hpp"
 #include "conv12_fused.hpp"
 #include "conv_fwd_bf16x6.hpp"
+#include "conv123_f16.hpp"
 #include "conv_dgrad_bf16x6.hpp"
 #include "conv_grads_bf16x6.hpp"
 #include "conv_wgrad_bf16x6.hpp"
@@ -49,24 +50,26 @@ typedef ConvSpec<float, 32, 20, 20, 32, 4, 2> SpecP2;     // the paper's larger-
 // 16-byte vectors of a small-net fragment buffer: the filters of conv1 / conv2 for the fused forward kernel, then
 // those of conv2 for its input-gradient kernel
 constexpr int CFRAG_FWD_VECS = 3 * C12_FRAG_SET, CFRAG_VECS = CFRAG_FWD_VECS + ConvDgradBf16Geom<SpecS2>::FRAG_VECS;
-// parts of a larger-net fragment buffer: conv2 forward, conv2 input gradient, conv3 forward, conv3 input gradient
+// parts of a larger-net fragment buffer: conv2 forward, conv2 input gradient, conv3 forward, conv3 input gradient; then (at
+// LFRAG_VECS) all three layers for predictions, in a context that predicts at fp32 accuracy
 constexpr int LFRAG_FWD2 = 0, LFRAG_DGRAD2 = LFRAG_FWD2 + ConvFwdBf16Geom<SpecL2>::FRAG_VECS,
               LFRAG_FWD3 = LFRAG_DGRAD2 + ConvDgradBf16Geom<SpecL2>::FRAG_VECS, LFRAG_DGRAD3 = LFRAG_FWD3 + ConvFwdBf16Geom<SpecL3>::FRAG_VECS,
               LFRAG_VECS = LFRAG_DGRAD3 + conv_dgrad_s1_frag_vecs<SpecL3>();
 
-// All four parts in one launch (w2, w3: the filter tensors of conv2 and conv3).
+// All parts in one launch (w1, w2, w3: the filter tensors); the last in LFRAG_B3 .. LFRAG_B3 + Conv123Frags::BLOCKS.
 typedef ConvSpec<float, SpecL3::OC, SpecL3::OH + 2 * (SpecL3::KS - 1), SpecL3::OW + 2 * (SpecL3::KS - 1), SpecL3::C, SpecL3::KS, 1> SpecL3Dgrad;
 constexpr int LFRAG_B0 = ConvFwdBf16Geom<SpecL2>::KB, LFRAG_B1 = LFRAG_B0 + (SpecL2::OC * SpecL2::C * 4 + 255) / 256,
               LFRAG_B2 = LFRAG_B1 + ConvFwdBf16Geom<SpecL3>::KB, LFRAG_B3 = LFRAG_B2 + ConvFwdBf16Geom<SpecL3Dgrad>::KB;
-__global__ __launch_bounds__(256) void large_filter_fragments_kernel(const float *__restrict__ w2, const float *__restrict__ w3,
-                                                                     u32x4 *__restrict__ lfrag) {
+__global__ __launch_bounds__(256) void large_filter_fragments_kernel(const float *__restrict__ w1, const float *__restrict__ w2,
+                                                                     const float *__restrict__ w3, u32x4 *__restrict__ lfrag) {
     const int b = blockIdx.x, t = threadIdx.x;
     if (b < LFRAG_B0) conv_fwd_filter_fragments_thread<SpecL2, false>(w2, lfrag + LFRAG_FWD2, b * 256 + t);
     else if (b < LFRAG_B1) {
         const int i = (b - LFRAG_B0) * 256 + t;
         if (i < SpecL2::OC * SpecL2::C * 4) conv_dgrad_store_fragment4<SpecL2>(lfrag + LFRAG_DGRAD2, 4 * i, ((const float4 *)w2)[i]);
     } else if (b < LFRAG_B2) conv_fwd_filter_fragments_thread<SpecL3, false>(w3, lfrag + LFRAG_FWD3, (b - LFRAG_B1) * 256 + t);
-    else conv_fwd_filter_fragments_thread<SpecL3Dgrad, true>(w3, lfrag + LFRAG_DGRAD3, (b - LFRAG_B2) * 256 + t);
+    else if (b < LFRAG_B3) conv_fwd_filter_fragments_thread<SpecL3Dgrad, true>(w3, lfrag + LFRAG_DGRAD3, (b - LFRAG_B2) * 256 + t);
+    else conv123_fragments_block(w1, w2, w3, lfrag + LFRAG_VECS, b - LFRAG_B3);
 }
 
 // ---------------------------------------------------------------- errors ----
@@ -165,6 +168,7 @@ struct ga3c_ctx {
     // larger net: the filters of conv2 and conv3 of each parameter copy as ready-made fragments for the forward and the
     // input-gradient kernels (LFRAG_* give the parts); rebuilt by whoever writes the copy
     u32x4 *lfrag[2];
+    bool conv123;                 // predictions run the larger net's three convolutions in one kernel; the buffers hold its part too
     // layers on the any-size kernels of conv_band.hpp and conv_bytes.hpp: which ones, where their fragments sit in the
     // buffer of each parameter copy (in vectors), and the buffers (nullptr where no layer needs one)
     bool band[GA3C_MAX_CONV];
@@ -2086,8 +2090,9 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
             HIP_TRY(launch_conv_dgrad_filter_fragments<SpecS2>(c->theta2[i] + c->off[2], c->cfrag[i] + CFRAG_FWD_VECS, s));
     }
     if (c->lfrag[i]) {
-        const float *w2 = c->theta2[i] + c->off[2], *w3 = c->theta2[i] + c->off[4];
-        ga3c::launch_stop(c->bfrag[i] ? nullptr : stop, large_filter_fragments_kernel, dim3(LFRAG_B3), dim3(256), 0, s, w2, w3, c->lfrag[i]);
+        const float *th = c->theta2[i];
+        ga3c::launch_stop(c->bfrag[i] ? nullptr : stop, large_filter_fragments_kernel, dim3(LFRAG_B3 + (c->conv123 ? Conv123Frags::BLOCKS : 0)),
+                          dim3(256), 0, s, th + c->off[0], th + c->off[2], th + c->off[4], c->lfrag[i]);
         HIP_TRY(hipGetLastError());
     }
     if (c->bfrag[i]) {
@@ -2161,6 +2166,15 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         HIP_TRY(launch_conv12_fused_fwd(frames, table, c->cfrag[which], th + c->off[1], th + c->off[3],
                                         keep_zv ? w.act[0] : nullptr, w.act[1], B, 1.f / 255.f, s, c->rb));
         first = 2;
+    }
+    if (c->fast && c->conv123 && !keep_zv && is_aligned16(frames)) {
+        // larger net, predictions: all three layers in one kernel
+        const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1], &g2 = c->geom[2];
+        STAGE("conv123_fwd", 2.0 * B * (g0.OHW * g0.OC * g0.K + g1.OHW * g1.OC * g1.K + g2.OHW * g2.OC * g2.K),
+              (double)B * (g0.CHW + 4.0 * g2.OC * g2.OHW));
+        HIP_TRY((launch_conv123_f16<SpecL2, SpecL3>(frames, table, c->lfrag[which] + LFRAG_VECS, th + c->off[1], th + c->off[3], th + c->off[5],
+                                                    w.act[2], B, 1.f / 255.f, s)));
+        first = 3;
     }
     for (int l = first; l < c->nconv; ++l) {
         const ConvGeom &g = c->geom[l];
@@ -2480,8 +2494,9 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     }
     if (rc == GA3C_OK && c->nconv == 3 && spec_matches<SpecL2>(c->geom[1], false) && spec_matches<SpecL3>(c->geom[2], false) &&
         c->off[2] % 4 == 0 && c->off[4] % 4 == 0) {
+        c->conv123 = spec_matches<SpecL1>(c->geom[0], true) && !c->rb && max_predict_batch > 0;
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
-            guard(dmalloc((void **)&c->lfrag[i], sizeof(u32x4) * LFRAG_VECS));
+            guard(dmalloc((void **)&c->lfrag[i], sizeof(u32x4) * (LFRAG_VECS + (c->conv123 ? Conv123Frags::VECS : 0))));
             if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
         }
     }

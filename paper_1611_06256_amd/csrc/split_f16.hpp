@@ -1,0 +1,63 @@
+// fp32 numbers as two float16 terms, and what scales them.
+//
+// Scaled by a power of two, x = hi + lo with hi = x rounded to float16 (11 bits) and lo = the rest rounded to float16: 22
+// bits and the sign of lo, so that what is left is 2^-23 of x at most, and nothing in three of four numbers of 24 bits.  A
+// product of two such numbers is evaluated as lo hi' + hi lo' + hi hi' in the fp32 accumulator of
+// v_mfma_f32_16x16x32_f16: three instructions where three bfloat16 terms take six, with two thirds of the operands.  The
+// fp32 accumulator rounds half as often, which is what the error of a sum of some hundred products consists of.
+//
+// The scale brings the largest magnitude of a row or a tensor to [2^14, 2^15).  Numbers far below it keep an absolute error
+// of 2^-40 of that largest one (float16 has no smaller steps than 2^-24, and the instruction takes them as they are).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "conv1_bf16x3.hpp"
+
+namespace ga3c {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+union F16x8Bits {
+    f16x8 v;
+    u32x4 u;
+};
+
+// The power of two by which numbers of magnitude `most` at most are multiplied, and its reciprocal.  Both are normal
+// numbers; a tensor of less than 2^-112 stays below 2^14.
+__device__ __forceinline__ void f16_scale(const float most, float &scale, float &inverse) {
+    const int e = (int)(__float_as_uint(most) >> 23) & 0xff, s = min(268 - e, 253);
+    scale = __uint_as_float((uint32_t)s << 23);
+    inverse = __uint_as_float((uint32_t)(254 - s) << 23);
+}
+
+// Two numbers times `scale` as terms, x in the low halves and y in the high ones: four instructions.
+__device__ __forceinline__ void split2_pair(const float x, const float y, const float scale, uint32_t &hi, uint32_t &lo) {
+    uint32_t h, l;
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(x), "v"(scale));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(h) : "v"(y), "v"(scale));
+    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(l) : "v"(x), "v"(scale), "v"(h));
+    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(l) : "v"(y), "v"(scale), "v"(h));
+    hi = h;
+    lo = l;
+}
+
+// 16 bytes -> 16 float16 (two 16-byte vectors), exactly: 1024 + b is the number whose bits are 0x6400 + b.
+__device__ __forceinline__ void bytes_to_f16(const u32x4 b, u32x4 &lo8, u32x4 &hi8) {
+    union { uint32_t u; f16x2 h; } c;
+    uint32_t o[8];
+    const f16x2 k = {(_Float16)1024.f, (_Float16)1024.f};
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        c.u = __builtin_amdgcn_perm(0x64646464u, b[d], 0x04010400u);
+        c.h -= k;
+        o[2 * d] = c.u;
+        c.u = __builtin_amdgcn_perm(0x64646464u, b[d], 0x04030402u);
+        c.h -= k;
+        o[2 * d + 1] = c.u;
+    }
+    lo8 = u32x4{o[0], o[1], o[2], o[3]};
+    hi8 = u32x4{o[4], o[5], o[6], o[7]};
+}
+
+}  // namespace ga3c
