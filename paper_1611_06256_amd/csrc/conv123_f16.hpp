@@ -1,22 +1,26 @@
-// The three convolution layers of the larger network (32 8x8 stride 4 on the 4x84x84 byte frame, 64 4x4 stride 2, 64 3x3
-// stride 1, each with its rectifier) in one kernel, for predictions: a block of eight wavefronts takes a frame from its
-// bytes to the fc layer's input, and nothing in between leaves the compute unit.
+// The three convolution layers of a network in one kernel, for predictions: a block of eight wavefronts takes a frame from
+// its bytes to the fc layer's input, and nothing in between leaves the compute unit.  Networks are the larger one (32 8x8
+// stride 4 on the 4x84x84 byte frame, 64 4x4 stride 2, 64 3x3 stride 1) and those of the larger-network family whose first map
+// fits (32 8x8 stride 4 or 3, 32 4x4 stride 2, 64 4x4 stride 2), each layer with its rectifier.
 //
 // Operands are two float16 terms each (split_f16.hpp), bytes one.  Filters come scaled and split, in the order in which the
 // lanes take them, from a buffer per parameter copy; an activation map is scaled by its own largest value, which the eight
 // wavefronts find between a layer's products and its way to LDS (one barrier more than without).
 //
-//   layer 1  both filter tiles from one read of a pixel tile's bytes: wavefront w has tiles w, w + 8, w + 16 of the 25, and the last
-//            one is shared by wavefronts 0 and 1, a filter tile each
-//   layer 2  wavefront w has filter tile w % 4 and every other of the six pixel tiles; layer 3 likewise, of four
+//   layer 1  both filter tiles from one read of a pixel tile's bytes: wavefront w has tiles w, w + 8, ..; of the tiles that are left
+//            over wavefronts 2 i and 2 i + 1 have the i-th, a filter tile each
+//   layers 2, 3  wavefront w has filter tile w % (filters / 16) and every so many pixel tiles
 //
-// LDS holds the frame as float16 (later layer 2's output) and layer 1's output in the layouts of conv_fwd_bf16x6.hpp.  Every
-// wavefront keeps a layer's filters in registers, 64 to 144 of them; those of the next layer take the place of the ones that have been
-// multiplied, k-block by k-block, so that no layer waits for its filters.
+// LDS holds the frame as [row][column][plane] float16, so that a lane's eight values of a filter row are 16 bytes in one place
+// whatever the stride; later layer 2's output takes its place.  Every wavefront keeps a layer's filters in registers, 128 or 144 of
+// them; those of the next layer take the place of the ones that have been multiplied, k-block by k-block, so that no layer waits
+// for its filters.
 //
 // Bound by one frame's chain through a compute unit: bytes in, three layers and six barriers.  us a call (with the fc layer and the heads
-// behind it) against a kernel per layer on three bfloat16 terms: 1 frame 26.2 -> 21.6, 64: 28.8 -> 23.2, 128: 36.9 -> 25.6, 256: 47.4 ->
-// 29.0, 512: 71.5 -> 45.5, 1024: 116 -> 80.  Error of the logits against 64 bits (2-norm, 256 frames) 5.1e-7 -> 4.3e-7.
+// behind it) against a kernel per layer on three bfloat16 terms or the fp32 instruction: larger net 1 frame 26.4 -> 21.8, 64: 28.8 ->
+// 23.2, 128: 36.9 -> 25.6, 256: 47.1 -> 29.4, 512: 71.4 -> 44.8, 1024: 116 -> 80; stride-4 member 1: 23.1 -> 18.3, 128: 34.4 -> 19.8, 256:
+// 41.0 -> 20.7; stride-3 member 1: 23.4 -> 21.0, 64: 30.6 -> 22.6, 128: 37.9 -> 22.9, 256: 47.1 -> 25.6, 512: 69.1 -> 40.0.  Error of the
+// logits against 64 bits (2-norm, 256 frames) 5.1e-7 -> 4.4e-7, 5.4e-7 -> 5.1e-7, 4.9e-7 -> 4.6e-7.
 //
 // Updates keep the layers' own kernels: another rounding of a sum puts a pre-activation next to zero on the other side of the
 // rectifier now and then, and a map's gradients with it.
@@ -26,30 +30,67 @@
 #include "launch.hpp"
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "conv_fwd_bf16x6.hpp"
 #include "split_f16.hpp"
 
 namespace ga3c {
 
-// Filters of the three layers: [filter tile][k-block][term][lane] vectors of eight float16 each; then the reciprocals of
-// the filters' scales, 32 + 64 + 64 floats.
-struct Conv123Frags {
-    static constexpr int KB1 = 8, KB2 = 16, KB3 = 18;
-    static constexpr int F1 = 0, F2 = F1 + 2 * KB1 * 128, F3 = F2 + 4 * KB2 * 128, INV = F3 + 4 * KB3 * 128, VECS = INV + (32 + 64 + 64) / 4;
-    static constexpr int BLOCKS = 2 * 2 + 4 * 4 + 4 * 5;       // of the kernel that writes them: four k-blocks of a filter tile each
+// A map in LDS, as the input of layer SP: [term], eight channels of a pixel in 16 bytes.  Sixteen neighbouring output pixels read
+// without bank conflicts: with stride 2 the even and the odd columns of a row lie apart, and rows are as long as makes pixel OW of
+// a row fall where pixel 0 of the next one does.  PLANAR: the groups of eight channels apart from each other, which takes no
+// padding behind a pixel but needs an even OW.
+template <class SP, bool PLANAR>
+struct F16Map {
+    static constexpr int UNITS = SP::C / 8, PIT = PLANAR ? 1 : lds_row_units(UNITS), EVEN = (SP::W + 1) / 2;
+    static constexpr int row_units() {
+        int r = SP::W * PIT;
+        while ((SP::S * r - PIT * SP::OW) % 16 != 0) ++r;
+        return r;
+    }
+    static constexpr int ROW = 16 * row_units(), GROUP = PLANAR ? (SP::H * ROW + 255) / 256 * 256 : 16;
+    static constexpr int TERM = PLANAR ? UNITS * GROUP : SP::H * ROW;
+    // where a pixel's first eight channels lie; output pixel p's first one
+    __host__ __device__ static constexpr int pixel(int row, int col) {
+        return row * ROW + (SP::S == 2 ? (col & 1) * EVEN + (col >> 1) : col) * (16 * PIT);
+    }
+    __host__ __device__ static constexpr int origin(int p) { return p / SP::OW * SP::S * ROW + p % SP::OW * (16 * PIT); }
 };
 
-// Block b of BLOCKS, 256 threads.  w1 [32][4][8][8], w2 [64][32][4][4], w3 [64][64][3][3], 16-byte aligned.
+// A network: stride of layer 1 (32 filters), layers 2 and 3, whether layer 1's map is planar.
+template <int S1_, class SP2_, class SP3_, bool PLANAR_>
+struct Conv123Net {
+    typedef SP2_ SP2;
+    typedef SP3_ SP3;
+    typedef F16Map<SP2, PLANAR_> M2;
+    typedef F16Map<SP3, false> M3;
+    static constexpr int S1 = S1_, OW1 = (84 - 8) / S1 + 1, NPIX1 = OW1 * OW1, NT1 = (NPIX1 + 15) / 16;
+    static constexpr int NT2 = (SP2::NPIX + 15) / 16, NT3 = (SP3::NPIX + 15) / 16, OT2 = SP2::OC / 16;
+    static_assert(SP2::H == OW1 && SP2::W == OW1 && SP2::C == 32 && SP2::K == 512 && SP2::S == 2 && (SP2::OC == 32 || SP2::OC == 64), "layer 2: 4x4, stride 2");
+    static_assert(SP3::H == SP2::OH && SP3::C == SP2::OC && SP3::K % 32 == 0 && SP3::OC == 64, "layer 3");
+    // Filters: [filter tile][k-block][term][lane] vectors of eight float16 each; then the reciprocals of the filters' scales.
+    static constexpr int KB1 = 8, KB2 = 16, KB3 = SP3::K / 32, CG3 = SP3::C / 32;
+    static constexpr int F1 = 0, F2 = F1 + 2 * KB1 * 128, F3 = F2 + OT2 * KB2 * 128, INV = F3 + 4 * KB3 * 128;
+    static constexpr int FILTERS = 32 + SP2::OC + 64, VECS = INV + FILTERS / 4;
+    // the kernel that writes them: four k-blocks of a filter tile each block
+    static constexpr int B1 = 2 * KB1 / 4, B2 = B1 + OT2 * KB2 / 4, PER3 = (KB3 + 3) / 4, BLOCKS = B2 + 4 * PER3;
+    static constexpr int XS = 0, Y2 = 0, Y1 = 84 * 84 * 8, LDS = Y1 + 2 * M2::TERM;        // layer 2's output takes the frame's place
+    static_assert(Y2 + 2 * M3::TERM <= Y1 && LDS + 2048 <= 160 * 1024, "LDS");
+};
+
+// Block b of N::BLOCKS, 256 threads.  w1, w2, w3: the filter tensors, 16-byte aligned.
+template <class N>
 __device__ __forceinline__ void conv123_fragments_block(const float *__restrict__ w1, const float *__restrict__ w2, const float *__restrict__ w3,
                                                         u32x4 *__restrict__ frag, int b) {
-    typedef Conv123Frags G;
     __shared__ float scales[16];
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
-    int layer, ot, kb0, K, KB, at;
+    constexpr int K3 = N::SP3::K, TAPS3 = K3 / N::SP3::C, KMOST = K3 > 512 ? K3 : 512;
+    int layer, ot, kb0, K, KB, at, first;
     const float *w;
-    if (b < 4) { layer = 1; ot = b / 2; kb0 = b % 2 * 4; K = 256; KB = G::KB1; w = w1; at = G::F1; }
-    else if (b < 20) { layer = 2; ot = (b - 4) / 4; kb0 = (b - 4) % 4 * 4; K = 512; KB = G::KB2; w = w2; at = G::F2; }
-    else { layer = 3; ot = (b - 20) / 5; kb0 = (b - 20) % 5 * 4; K = 576; KB = G::KB3; w = w3; at = G::F3; }
+    if (b < N::B1) { layer = 1; ot = b / 2; kb0 = b % 2 * 4; K = 256; KB = N::KB1; w = w1; at = N::F1; first = 0; }
+    else if (b < N::B2) { layer = 2; ot = (b - N::B1) / 4; kb0 = (b - N::B1) % 4 * 4; K = 512; KB = N::KB2; w = w2; at = N::F2; first = 32; }
+    else { layer = 3; ot = (b - N::B2) / N::PER3; kb0 = (b - N::B2) % N::PER3 * 4; K = K3; KB = N::KB3; w = w3; at = N::F3; first = 32 + N::SP2::OC; }
     w += (size_t)ot * 16 * K;
     // everything is asked for at once: my eight values, and sixteen threads, which are a row of lanes, find a filter's largest one
     const int kb = kb0 + (tid >> 6);
@@ -57,23 +98,23 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         int k;                                             // of the filter as it lies in memory: (channel, row, column)
-        if (layer == 1) k = 32 * kb + 8 * g + j;
+        if (layer == 1) k = j % 4 * 64 + kb * 8 + 2 * g + j / 4;
         else if (layer == 2) k = (8 * g + j) * 16 + kb;
-        else k = (kb % 2 * 32 + 8 * g + j) * 9 + kb / 2;
+        else k = (kb % N::CG3 * 32 + 8 * g + j) * TAPS3 + kb / N::CG3;
         v[j] = w[(size_t)l16 * K + min(k, K - 1)];
     }
-    float4 all[9];
+    float4 all[KMOST / 64];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) all[i] = *(const float4 *)(w + (size_t)(tid >> 4) * K + min(4 * (tid & 15) + 64 * i, K - 4));
+    for (int i = 0; i < KMOST / 64; ++i) all[i] = *(const float4 *)(w + (size_t)(tid >> 4) * K + min(4 * (tid & 15) + 64 * i, K - 4));
 #pragma unroll
-    for (int i = 0; i < 9; ++i) m = fmaxf(fmaxf(fmaxf(m, fabsf(all[i].x)), fmaxf(fabsf(all[i].y), fabsf(all[i].z))), fabsf(all[i].w));
+    for (int i = 0; i < KMOST / 64; ++i) m = fmaxf(fmaxf(fmaxf(m, fabsf(all[i].x)), fmaxf(fabsf(all[i].y), fabsf(all[i].z))), fabsf(all[i].w));
     m = fmaxf(m, dpp_row_f32<0xB1>(m)); m = fmaxf(m, dpp_row_f32<0x4E>(m));
     m = fmaxf(m, dpp_row_f32<0x141>(m)); m = fmaxf(m, dpp_row_f32<0x140>(m));
     if ((tid & 15) == 0) {
         float s, inv;
         f16_scale(m, s, inv);
         scales[tid >> 4] = s;
-        if (kb0 == 0) ((float *)(frag + G::INV))[(layer == 1 ? 0 : layer == 2 ? 32 : 96) + ot * 16 + (tid >> 4)] = inv;
+        if (kb0 == 0) ((float *)(frag + N::INV))[first + ot * 16 + (tid >> 4)] = inv;
     }
     __syncthreads();
     if (kb >= KB) return;
@@ -90,70 +131,65 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
     dst[64] = lo;
 }
 
-template <class SP2, class SP3>
-struct Conv123Geom {
-    typedef ConvFwdBf16Geom<SP2> G2;
-    typedef ConvFwdBf16Geom<SP3> G3;
-    static constexpr int NV = 4 * 84 * 84 / 16;                                        // 16-byte vectors of a frame
-    static constexpr int XS = 0, Y1 = NV * 32, Y2 = 0, LDS = Y1 + 2 * G2::PLANE;        // layer 2's output takes the frame's place
-    static_assert(Y2 + 2 * G3::PLANE <= Y1 && LDS <= 160 * 1024 - 64, "LDS");
-};
-
-// x: [n][4][84][84] bytes, or table: where each frame lies; frag: Conv123Frags; b1 [32], b2, b3 [64]; y: [n][64][49].
-template <class SP2, class SP3, bool TABLE>
+// x: [n][4][84][84] bytes, or table: where each frame lies; frag: N's filters; b1 [32], b2, b3: biases; y: [n][64][layer 3's pixels].
+template <class N, bool TABLE>
 __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table,
                                                              const u32x4 *__restrict__ frag, const float *__restrict__ b1,
                                                              const float *__restrict__ b2, const float *__restrict__ b3, float *__restrict__ y,
                                                              int nframes, float scale) {
-    typedef Conv123Geom<SP2, SP3> G;
-    typedef typename G::G2 G2;
-    typedef typename G::G3 G3;
-    typedef Conv123Frags R;
-    constexpr int CHW = 4 * 84 * 84, NV = G::NV, VPT = (NV + 511) / 512;
+    typedef typename N::SP2 SP2;
+    typedef typename N::SP3 SP3;
+    typedef typename N::M2 M2;
+    typedef typename N::M3 M3;
+    constexpr int CHW = 4 * 84 * 84, HW4 = 84 * 84 / 4, VPT = (HW4 + 511) / 512, KB1 = N::KB1, KB2 = N::KB2, KB3 = N::KB3;
+    constexpr int FULL1 = N::NT1 / 8, REST1 = N::NT1 % 8, PG2 = 8 / N::OT2;      // tiles per wavefront, tiles left over; groups of wavefronts
+    static_assert(2 * REST1 <= 8, "half a tile each");
     extern __shared__ __attribute__((aligned(16))) unsigned char c123_smem[];
     __shared__ float most[2][8];                           // largest values of layers 1 and 2, by wavefront
-    __shared__ __attribute__((aligned(16))) float consts[2][160];       // by filter: reciprocal of its scale, bias
-    _Float16 *xs = (_Float16 *)(c123_smem + G::XS);
+    __shared__ __attribute__((aligned(16))) float consts[2][N::FILTERS];       // by filter: reciprocal of its scale, bias
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    u32x4 pre[VPT];
+    // a unit is four pixels: a dword of each plane
+    uint32_t pre[VPT][4];
     int f = blockIdx.x;
     FramePointer<TABLE> next;
     auto fetch = [&]() {
-        const u32x4 *src = (const u32x4 *)next.get();
+        const uint8_t *src = next.get();
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) pre[i] = src[min(tid + 512 * i, NV - 1)];
+        for (int i = 0; i < VPT; ++i)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) pre[i][c] = *(const uint32_t *)(src + c * (84 * 84) + 4u * (uint32_t)min(tid + 512 * i, HW4 - 1));
     };
     next.ask(x, table, min(f, nframes - 1), CHW);
     fetch();
     if (TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
 
     // layer 1: w1[0] is filter tile `own`, w1[1] the other one
-    const int own = wave & 1, ot = wave & 3, pg = wave >> 2;
-    F16x8Bits w1[2][R::KB1][2], w2[R::KB2][2], w3[R::KB3][2];
+    const int own = wave & 1, ot2 = wave % N::OT2, pg2 = wave / N::OT2, ot3 = wave & 3, pg3 = wave >> 2;
+    F16x8Bits w1[2][KB1][2], w2[KB2][2], w3[KB3][2];
     // A wavefront's place is added to the scalar address, a lane's is the same for all vectors.
-    uint32_t again = 0;
+    uint32_t again;
     const uint32_t mine = 16 * lane;
     auto vec = [&](int at) { return *(const u32x4 *)((const char *)(frag + again + at) + mine); };
     auto load1 = [&](int kb) {
 #pragma unroll
         for (int o = 0; o < 2; ++o)
 #pragma unroll
-            for (int t = 0; t < 2; ++t) w1[o][kb][t].u = vec(R::F1 + (((own ^ o) * R::KB1 + kb) * 2 + t) * 64);
+            for (int t = 0; t < 2; ++t) w1[o][kb][t].u = vec(N::F1 + (((own ^ o) * KB1 + kb) * 2 + t) * 64);
     };
     auto load2 = [&](int kb) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) w2[kb][t].u = vec(R::F2 + ((ot * R::KB2 + kb) * 2 + t) * 64);
+        for (int t = 0; t < 2; ++t) w2[kb][t].u = vec(N::F2 + ((ot2 * KB2 + kb) * 2 + t) * 64);
     };
     auto load3 = [&](int kb) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) w3[kb][t].u = vec(R::F3 + ((ot * R::KB3 + kb) * 2 + t) * 64);
+        for (int t = 0; t < 2; ++t) w3[kb][t].u = vec(N::F3 + ((ot3 * KB3 + kb) * 2 + t) * 64);
     };
-    if (tid < 160) {
-        consts[0][tid] = ((const float *)(frag + R::INV))[tid] * (tid < 32 ? scale : 1.f);
-        consts[1][tid] = tid < 32 ? b1[tid] : tid < 96 ? b2[tid - 32] : b3[tid - 96];
+    if (tid < N::FILTERS) {
+        consts[0][tid] = ((const float *)(frag + N::INV))[tid] * (tid < 32 ? scale * F16_BYTE_UNIT : 1.f);
+        consts[1][tid] = tid < 32 ? b1[tid] : tid < 32 + SP2::OC ? b2[tid - 32] : b3[tid - 32 - SP2::OC];
     }
 
     // Largest value of all wavefronts, as a scale (behind a barrier).
@@ -168,100 +204,115 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
         return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 0)), __int_as_float(__builtin_amdgcn_readlane(u, 16))),
                      fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 32)), __int_as_float(__builtin_amdgcn_readlane(u, 48))));
     };
+    constexpr int WT[3] = {1, 0, 0}, XT[3] = {0, 1, 0};    // smallest products first
+
     for (; f < nframes; f += gridDim.x) {
         // what a frame does not change is read and worked out anew for each: there are no registers to keep it in
         int own_lane = lane;
-        asm volatile("" : "+s"(again), "+v"(own_lane));
+        asm volatile("s_mov_b32 %0, 0" : "=s"(again), "+v"(own_lane));
         const int l16 = own_lane & 15, g = own_lane >> 4;
         const float4 *inv = (const float4 *)consts[0] + g, *bias = (const float4 *)consts[1] + g;      // my four filters of tile t: [4 t]
+        // sums of those for a pixel -> rectified values, and the largest of them
+        auto rectify = [&](floatx4 &a, const float4 iv, const float4 bv, const float si, bool in, float &m) {
+            const float v[4] = {a[0] * iv.x * si + bv.x, a[1] * iv.y * si + bv.y, a[2] * iv.z * si + bv.z, a[3] * iv.w * si + bv.w};
 #pragma unroll
-        for (int kb = 0; kb < R::KB1; ++kb) load1(kb);
+            for (int r = 0; r < 4; ++r) {
+                a[r] = v[r] > 0.f ? v[r] : 0.f;
+                m = in ? fmaxf(m, a[r]) : m;
+            }
+        };
+        // values of filters 16 t + 4 g .. as terms, to the pixel that lies at `at`
+        auto store4 = [&](unsigned char *map, int term, int group, int at, int t, const floatx4 v, float s) {
+            uint2 hi, lo;
+            split2_pair(v[0], v[1], s, hi.x, lo.x);
+            split2_pair(v[2], v[3], s, hi.y, lo.y);
+            unsigned char *dst = map + at + (2 * t + (g >> 1)) * group + 8 * (g & 1);
+            *(uint2 *)dst = hi;
+            *(uint2 *)(dst + term) = lo;
+        };
+#pragma unroll
+        for (int kb = 0; kb < KB1; ++kb) load1(kb);
         __syncthreads();                                   // the last frame's layer-2 output has been read
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
-            const int v = tid + 512 * i;
-            u32x4 a, b;
-            bytes_to_f16(pre[i], a, b);
-            if (v < NV) {
-                u32x4 *dst = (u32x4 *)(xs + (size_t)v * 16);
-                dst[0] = a; dst[1] = b;
+            u32x4 o[2];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                o[t / 2][t % 2 * 2] = f16_of_bytes(pre[i][0], pre[i][1], t);
+                o[t / 2][t % 2 * 2 + 1] = f16_of_bytes(pre[i][2], pre[i][3], t);
+            }
+            if (tid + 512 * i < HW4) {
+                u32x4 *dst = (u32x4 *)(c123_smem + N::XS) + 2 * (tid + 512 * i);
+                dst[0] = o[0]; dst[1] = o[1];
             }
         }
         __syncthreads();
         if (!TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
         fetch();
         if (TABLE) next.ask(x, table, min(f + 2 * (int)gridDim.x, nframes - 1), CHW);
-        // four filters' values of a pixel (4 g .. of filter tile t), as terms
-        auto store4 = [&](unsigned char *plane, int plane_bytes, int at, int t, const float (&v)[4], float s) {
-            uint2 hi, lo;
-            split2_pair(v[0], v[1], s, hi.x, lo.x);
-            split2_pair(v[2], v[3], s, hi.y, lo.y);
-            *(uint2 *)(plane + at + t * 32 + 8 * g) = hi;
-            *(uint2 *)(plane + plane_bytes + at + t * 32 + 8 * g) = lo;
-        };
-        // ---- layer 1
+        // ---- layer 1: a k-block is a filter row, a lane's eight k two pixels of four planes
         {
             auto base_of = [&](int t) {
-                const int p = t * 16 + l16;
-                return (p / 20 * 4 + g) * 84 + p % 20 * 4;
+                const int p = min(t * 16 + l16, N::NPIX1 - 1);
+                return N::XS + ((p / N::OW1 * 84 + p % N::OW1) * N::S1 + 2 * g) * 8;
             };
             auto operand = [&](int base, int kb) {
-                const _Float16 *src = xs + base + (kb / 2) * (84 * 84) + 4 * (kb % 2) * 84;      // 8-byte aligned
-                const uint2 lo = *(const uint2 *)src, hi = *(const uint2 *)(src + 4);
+                const unsigned char *src = c123_smem + base + kb * (84 * 8);       // 8-byte aligned
                 F16x8Bits v;
-                v.u = u32x4{lo.x, lo.y, hi.x, hi.y};
+                if (N::S1 % 2 == 0) v.u = *(const u32x4 *)src;
+                else {
+                    const uint2 lo = *(const uint2 *)src, hi = *(const uint2 *)(src + 8);
+                    v.u = u32x4{lo.x, lo.y, hi.x, hi.y};
+                }
                 return v.v;
             };
-            int base[3];
-            floatx4 acc[3][2], accx = floatx4{0.f, 0.f, 0.f, 0.f};
+            const int left = 8 * FULL1 + (wave >> 1);
+            int base[FULL1];
+            floatx4 acc[FULL1][2], accx = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < FULL1; ++i) {
                 base[i] = base_of(wave + 8 * i);
                 acc[i][0] = acc[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-            if (wave < 2) {                                // before the filters go
-                const int b24 = base_of(24);
+            if (wave < 2 * REST1) {                        // before the filters go
+                const int b = base_of(left);
 #pragma unroll
-                for (int kb = 0; kb < R::KB1; ++kb) {
-                    const f16x8 v = operand(b24, kb);
+                for (int kb = 0; kb < KB1; ++kb) {
+                    const f16x8 v = operand(b, kb);
 #pragma unroll
                     for (int t = 1; t >= 0; --t) accx = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[0][kb][t].v, v, accx, 0, 0, 0);
                 }
             }
-            f16x8 xv[2][3];
+            constexpr bool AHEAD = FULL1 <= 3;             // registers for the next k-block's operands
+            f16x8 xv[AHEAD ? 2 : 1][FULL1];
+            auto read = [&](int kb) {
 #pragma unroll
-            for (int i = 0; i < 3; ++i) xv[0][i] = operand(base[i], 0);
+                for (int i = 0; i < FULL1; ++i) xv[AHEAD ? kb & 1 : 0][i] = operand(base[i], kb);
+            };
+            if (AHEAD) read(0);
 #pragma unroll
-            for (int kb = 0; kb < R::KB1; ++kb) {
-                if (kb + 1 < R::KB1) {
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) xv[(kb + 1) & 1][i] = operand(base[i], kb + 1);
-                }
+            for (int kb = 0; kb < KB1; ++kb) {
+                if (!AHEAD) read(kb);
+                else if (kb + 1 < KB1) read(kb + 1);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int t = 1; t >= 0; --t)
 #pragma unroll
-                    for (int i = 0; i < 3; ++i)
+                    for (int i = 0; i < FULL1; ++i)
 #pragma unroll
                         for (int o = 0; o < 2; ++o)
-                            acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[o][kb][t].v, xv[kb & 1][i], acc[i][o], 0, 0, 0);
+                            acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[o][kb][t].v, xv[AHEAD ? kb & 1 : 0][i], acc[i][o], 0, 0, 0);
                 load2(2 * kb);
                 load2(2 * kb + 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
             float m = 0.f;
             const float4 iv[2] = {inv[4 * own], inv[4 * (own ^ 1)]}, bv[2] = {bias[4 * own], bias[4 * (own ^ 1)]};
-            auto finish = [&](floatx4 &a, int o) {
-                const float v[4] = {a[0] * iv[o].x + bv[o].x, a[1] * iv[o].y + bv[o].y, a[2] * iv[o].z + bv[o].z, a[3] * iv[o].w + bv[o].w};
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    a[r] = v[r] > 0.f ? v[r] : 0.f;
-                    m = fmaxf(m, a[r]);
-                }
-            };
+            for (int i = 0; i < FULL1; ++i)
 #pragma unroll
-            for (int i = 0; i < 3; ++i) { finish(acc[i][0], 0); finish(acc[i][1], 1); }
-            if (wave < 2) finish(accx, 0);
+                for (int o = 0; o < 2; ++o) rectify(acc[i][o], iv[o], bv[o], 1.f, true, m);
+            if (wave < 2 * REST1) rectify(accx, iv[0], bv[0], 1.f, true, m);       // pixels behind the last are copies of it
             m = wave_most(m);
             if (lane == 0) most[0][wave] = m;
             __syncthreads();
@@ -269,138 +320,123 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
             scale_of(most[0], s, si);
             auto put = [&](const floatx4 a, int t, int o) {
                 const int p = t * 16 + l16;
-                const float v[4] = {a[0], a[1], a[2], a[3]};
-                store4(c123_smem + G::Y1, G2::PLANE, G2::pixel(p / 20, p % 20), own ^ o, v, s);
+                if (N::NPIX1 % 16 == 0 || p < N::NPIX1) store4(c123_smem + N::Y1, M2::TERM, M2::GROUP, M2::pixel(p / N::OW1, p % N::OW1), own ^ o, a, s);
             };
 #pragma unroll
-            for (int i = 0; i < 3; ++i) { put(acc[i][0], wave + 8 * i, 0); put(acc[i][1], wave + 8 * i, 1); }
-            if (wave < 2) put(accx, 24, 0);
+            for (int i = 0; i < FULL1; ++i) { put(acc[i][0], wave + 8 * i, 0); put(acc[i][1], wave + 8 * i, 1); }
+            if (wave < 2 * REST1) put(accx, left, 0);
         }
         __syncthreads();
-        // ---- layer 2
+        // ---- layer 2: a k-block is a tap, 32 channels
         {
+            float m = 0.f;
+            constexpr int NT = (N::NT2 + PG2 - 1) / PG2;      // the last of some wavefronts is not there
             float s, si;
             scale_of(most[0], s, si);
-            floatx4 acc[3];
-            int pb[3], px[3];
+            floatx4 acc[NT];
+            int pb[NT], px[NT];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int p = (pg + 2 * i) * 16 + l16, q = p < SP2::NPIX ? p : 0;
+            for (int i = 0; i < NT; ++i) {
+                const int p = (pg2 + PG2 * i) * 16 + l16;
                 px[i] = p < SP2::NPIX ? p : -1;
-                pb[i] = G::Y1 + (q / SP2::OW) * 2 * G2::ROW + (q % SP2::OW) * G2::PIT + 16 * g;
+                pb[i] = N::Y1 + M2::origin(p < SP2::NPIX ? p : 0) + g * M2::GROUP;
                 acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-            F16x8Bits xv[2][3][2];
+            F16x8Bits xv[2][NT][2];
             auto read = [&](int kb) {
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+                for (int i = 0; i < NT; ++i)
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
-                        xv[kb & 1][i][t].u = *(const u32x4 *)(c123_smem + t * G2::PLANE + pb[i] + G2::pixel(kb / 4, kb % 4));
+                        xv[kb & 1][i][t].u = *(const u32x4 *)(c123_smem + t * M2::TERM + pb[i] + M2::pixel(kb / 4, kb % 4));
             };
             read(0);
 #pragma unroll
-            for (int kb = 0; kb < R::KB2; ++kb) {
-                if (kb + 1 < R::KB2) read(kb + 1);
+            for (int kb = 0; kb < KB2; ++kb) {
+                if (kb + 1 < KB2) read(kb + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int WT[3] = {1, 0, 0}, XT[3] = {0, 1, 0};      // smallest products first
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int i = 0; i < 3; ++i)
+                    for (int i = 0; i < NT; ++i)
                         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[kb][WT[q]].v, xv[kb & 1][i][XT[q]].v, acc[i], 0, 0, 0);
                 load3(kb);
-                if (kb >= R::KB2 - 2) load3(kb + 2);
+                if (kb + KB3 - KB2 >= KB2) load3(kb + KB3 - KB2);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            float m = 0.f;
-            const float4 iv = inv[4 * (2 + ot)], bv = bias[4 * (2 + ot)];
+            const float4 iv = inv[4 * (2 + ot2)], bv = bias[4 * (2 + ot2)];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const float v[4] = {acc[i][0] * iv.x * si + bv.x, acc[i][1] * iv.y * si + bv.y, acc[i][2] * iv.z * si + bv.z, acc[i][3] * iv.w * si + bv.w};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    acc[i][r] = v[r] > 0.f ? v[r] : 0.f;
-                    m = px[i] >= 0 ? fmaxf(m, acc[i][r]) : m;
-                }
-            }
+            for (int i = 0; i < NT; ++i) rectify(acc[i], iv, bv, si, px[i] >= 0, m);
             m = wave_most(m);
             if (lane == 0) most[1][wave] = m;
             __syncthreads();
             scale_of(most[1], s, si);
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
-                if (px[i] >= 0) {
-                    const float v[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-                    store4(c123_smem + G::Y2, G3::PLANE, G3::pixel(px[i] / SP3::W, px[i] % SP3::W), ot, v, s);
-                }
+            for (int i = 0; i < NT; ++i)
+                if (px[i] >= 0) store4(c123_smem + N::Y2, M3::TERM, M3::GROUP, M3::pixel(px[i] / SP3::W, px[i] % SP3::W), ot2, acc[i], s);
         }
         __syncthreads();
-        // ---- layer 3
-        {
+        // ---- layer 3: a k-block is 32 channels of a tap
+        if (N::NT3 > 1 || pg3 == 0) {
+            constexpr int NT = (N::NT3 + 1) / 2;
             float s, si;
             scale_of(most[1], s, si);
-            floatx4 acc[2];
-            int pb[2], px[2];
+            floatx4 acc[NT];
+            int pb[NT], px[NT];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int p = (pg + 2 * i) * 16 + l16, q = p < SP3::NPIX ? p : 0;
+            for (int i = 0; i < NT; ++i) {
+                const int p = (pg3 + 2 * i) * 16 + l16;
                 px[i] = p < SP3::NPIX ? p : -1;
-                pb[i] = G::Y2 + (q / SP3::OW) * G3::ROW + (q % SP3::OW) * G3::PIT + 16 * g;
+                pb[i] = N::Y2 + M3::origin(p < SP3::NPIX ? p : 0) + g * M3::GROUP;
                 acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-            F16x8Bits xv[2][2][2];
+            F16x8Bits xv[2][NT][2];
             auto read = [&](int kb) {
-                const int tap = kb / 2;
+                const int tap = kb / N::CG3;
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int i = 0; i < NT; ++i)
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
-                        xv[kb & 1][i][t].u = *(const u32x4 *)(c123_smem + t * G3::PLANE + pb[i] + G3::pixel(tap / 3, tap % 3) + kb % 2 * 64);
+                        xv[kb & 1][i][t].u = *(const u32x4 *)(c123_smem + t * M3::TERM + pb[i] + M3::pixel(tap / SP3::KS, tap % SP3::KS) +
+                                                              kb % N::CG3 * 4 * M3::GROUP);
             };
             read(0);
 #pragma unroll
-            for (int kb = 0; kb < R::KB3; ++kb) {
-                if (kb + 1 < R::KB3) read(kb + 1);
+            for (int kb = 0; kb < KB3; ++kb) {
+                if (kb + 1 < KB3) read(kb + 1);
                 __builtin_amdgcn_sched_barrier(0);
-                constexpr int WT[3] = {1, 0, 0}, XT[3] = {0, 1, 0};
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < NT; ++i)
                         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[kb][WT[q]].v, xv[kb & 1][i][XT[q]].v, acc[i], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            float *yb = y + (size_t)f * SP3::OC * SP3::NPIX;
-            const float4 iv = inv[4 * (6 + ot)], bv = bias[4 * (6 + ot)];
+            float *yb = y + (size_t)f * SP3::OC * SP3::NPIX, m = 0.f;
+            const float4 iv = inv[4 * (2 + N::OT2 + ot3)], bv = bias[4 * (2 + N::OT2 + ot3)];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float v[4] = {acc[i][0] * iv.x * si + bv.x, acc[i][1] * iv.y * si + bv.y, acc[i][2] * iv.z * si + bv.z, acc[i][3] * iv.w * si + bv.w};
+            for (int i = 0; i < NT; ++i) {
+                rectify(acc[i], iv, bv, si, false, m);
                 if (px[i] >= 0) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) yb[(ot * 16 + 4 * g + r) * SP3::NPIX + px[i]] = v[r] > 0.f ? v[r] : 0.f;
+                    for (int r = 0; r < 4; ++r) yb[(ot3 * 16 + 4 * g + r) * SP3::NPIX + px[i]] = acc[i][r];
                 }
             }
         }
     }
 }
 
-template <class SP2, class SP3>
+template <class N, bool TABLE>
 inline hipError_t launch_conv123_f16(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2,
                                      const float *b3, float *y, int nframes, float scale, hipStream_t s) {
     if (nframes <= 0) return hipSuccess;
-    constexpr int LDS = Conv123Geom<SP2, SP3>::LDS;
     static bool attr_set = false;
     if (!attr_set) {
-        for (const void *k : {(const void *)conv123_f16_kernel<SP2, SP3, false>, (const void *)conv123_f16_kernel<SP2, SP3, true>}) {
-            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
-            if (e != hipSuccess) return e;
-        }
+        const hipError_t e = hipFuncSetAttribute((const void *)conv123_f16_kernel<N, TABLE>, hipFuncAttributeMaxDynamicSharedMemorySize, N::LDS);
+        if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const int grid = nframes < 256 ? nframes : 256;
-    if (table) ga3c::launch((conv123_f16_kernel<SP2, SP3, true>), dim3(grid), dim3(512), LDS, s, x, table, frag, b1, b2, b3, y, nframes, scale);
-    else ga3c::launch((conv123_f16_kernel<SP2, SP3, false>), dim3(grid), dim3(512), LDS, s, x, table, frag, b1, b2, b3, y, nframes, scale);
+    ga3c::launch((conv123_f16_kernel<N, TABLE>), dim3(nframes < 256 ? nframes : 256), dim3(512), N::LDS, s, x, table, frag, b1, b2, b3, y, nframes, scale);
     return hipGetLastError();
 }
 

@@ -87,11 +87,11 @@ struct FragJobs {
     int n;
 };
 template <int TERMS>
-__global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJobs jobs) {
+__device__ __forceinline__ void band_filter_fragments_block(const FragJobs &jobs, const int block) {
     int q = 0;
-    while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.job[q + 1].first_block) ++q;
+    while (q + 1 < jobs.n && block >= jobs.job[q + 1].first_block) ++q;
     const FragJob &j = jobs.job[q];
-    const int i = (blockIdx.x - j.first_block) * 256 + threadIdx.x;
+    const int i = (block - j.first_block) * 256 + threadIdx.x;
     if (i >= j.n) return;
     const int lane = i % 64, l16 = lane & 15, g = lane >> 4;
     int blk = i / 64;
@@ -131,6 +131,11 @@ __global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJo
         for (int e = 0; e < 8; ++e) f[e] -= bf16_rne(f[e]);
         dst[128] = band_round8(f);
     }
+}
+
+template <int TERMS>
+__global__ __launch_bounds__(256) void band_filter_fragments_kernel(const FragJobs jobs) {
+    band_filter_fragments_block<TERMS>(jobs, blockIdx.x);
 }
 
 // ------------------------------------------------------------------ staging --

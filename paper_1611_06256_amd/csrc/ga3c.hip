@@ -56,7 +56,17 @@ constexpr int LFRAG_FWD2 = 0, LFRAG_DGRAD2 = LFRAG_FWD2 + ConvFwdBf16Geom<SpecL2
               LFRAG_FWD3 = LFRAG_DGRAD2 + ConvDgradBf16Geom<SpecL2>::FRAG_VECS, LFRAG_DGRAD3 = LFRAG_FWD3 + ConvFwdBf16Geom<SpecL3>::FRAG_VECS,
               LFRAG_VECS = LFRAG_DGRAD3 + conv_dgrad_s1_frag_vecs<SpecL3>();
 
-// All parts in one launch (w1, w2, w3: the filter tensors); the last in LFRAG_B3 .. LFRAG_B3 + Conv123Frags::BLOCKS.
+// Networks whose predictions run their three convolutions in one kernel: the larger one, the family's members of stride 4 and 3
+// (the other members' first maps do not fit a compute unit's LDS).
+typedef ConvSpec<float, 32, 9, 9, 64, 4, 2> SpecP43;
+typedef ConvSpec<float, 32, 26, 26, 32, 4, 2> SpecP32;
+typedef ConvSpec<float, 32, 12, 12, 64, 4, 2> SpecP33;
+typedef Conv123Net<4, SpecL2, SpecL3, false> Conv123Large;
+typedef Conv123Net<4, SpecP2, SpecP43, false> Conv123Paper4;
+typedef Conv123Net<3, SpecP32, SpecP33, true> Conv123Paper3;
+enum { CONV123_NONE = 0, CONV123_LARGE, CONV123_PAPER4, CONV123_PAPER3 };
+
+// All parts in one launch (w1, w2, w3: the filter tensors); the last in LFRAG_B3 .. LFRAG_B3 + Conv123Large::BLOCKS.
 typedef ConvSpec<float, SpecL3::OC, SpecL3::OH + 2 * (SpecL3::KS - 1), SpecL3::OW + 2 * (SpecL3::KS - 1), SpecL3::C, SpecL3::KS, 1> SpecL3Dgrad;
 constexpr int LFRAG_B0 = ConvFwdBf16Geom<SpecL2>::KB, LFRAG_B1 = LFRAG_B0 + (SpecL2::OC * SpecL2::C * 4 + 255) / 256,
               LFRAG_B2 = LFRAG_B1 + ConvFwdBf16Geom<SpecL3>::KB, LFRAG_B3 = LFRAG_B2 + ConvFwdBf16Geom<SpecL3Dgrad>::KB;
@@ -69,7 +79,14 @@ __global__ __launch_bounds__(256) void large_filter_fragments_kernel(const float
         if (i < SpecL2::OC * SpecL2::C * 4) conv_dgrad_store_fragment4<SpecL2>(lfrag + LFRAG_DGRAD2, 4 * i, ((const float4 *)w2)[i]);
     } else if (b < LFRAG_B2) conv_fwd_filter_fragments_thread<SpecL3, false>(w3, lfrag + LFRAG_FWD3, (b - LFRAG_B1) * 256 + t);
     else if (b < LFRAG_B3) conv_fwd_filter_fragments_thread<SpecL3Dgrad, true>(w3, lfrag + LFRAG_DGRAD3, (b - LFRAG_B2) * 256 + t);
-    else conv123_fragments_block(w1, w2, w3, lfrag + LFRAG_VECS, b - LFRAG_B3);
+    else conv123_fragments_block<Conv123Large>(w1, w2, w3, lfrag + LFRAG_VECS, b - LFRAG_B3);
+}
+// The family's fragments (jobs) and, in front of them, N's.
+template <class N>
+__global__ __launch_bounds__(256) void family_filter_fragments_kernel(const float *__restrict__ w1, const float *__restrict__ w2,
+                                                                      const float *__restrict__ w3, u32x4 *__restrict__ frag, const FragJobs jobs) {
+    if (blockIdx.x < N::BLOCKS) conv123_fragments_block<N>(w1, w2, w3, frag, blockIdx.x);
+    else band_filter_fragments_block<3>(jobs, blockIdx.x - N::BLOCKS);
 }
 
 // ---------------------------------------------------------------- errors ----
@@ -168,7 +185,10 @@ struct ga3c_ctx {
     // larger net: the filters of conv2 and conv3 of each parameter copy as ready-made fragments for the forward and the
     // input-gradient kernels (LFRAG_* give the parts); rebuilt by whoever writes the copy
     u32x4 *lfrag[2];
-    bool conv123;                 // predictions run the larger net's three convolutions in one kernel; the buffers hold its part too
+    // predictions run the network's three convolutions in one kernel (CONV123_..), whose filters lie in lfrag at LFRAG_VECS or in bfrag
+    // at bfrag_123
+    int conv123;
+    size_t bfrag_123;
     // layers on the any-size kernels of conv_band.hpp and conv_bytes.hpp: which ones, where their fragments sit in the
     // buffer of each parameter copy (in vectors), and the buffers (nullptr where no layer needs one)
     bool band[GA3C_MAX_CONV];
@@ -2077,6 +2097,10 @@ inline bool spec_matches(const ConvGeom &g, bool byte_input) {
 }
 inline bool is_aligned16(const void *p) { return (((uintptr_t)p) & 15) == 0; }
 
+// Whether the forward kernels of an any-size layer take its filters as terms: with rounded operands, and the byte layer of predictions
+// that run a kernel per layer.
+bool takes_terms(const ga3c_ctx *c, int l) { return c->rb || (l == 0 && !c->conv123); }
+
 // Things derived from parameter copy i, rebuilt on s after that copy was written there.  fc: the fc weights' too (an update
 // writes those itself).  stop: the event for the last launch, if the larger nets' fragments are among them.
 int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::StopEvent *stop = nullptr) {
@@ -2091,7 +2115,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
     }
     if (c->lfrag[i]) {
         const float *th = c->theta2[i];
-        ga3c::launch_stop(c->bfrag[i] ? nullptr : stop, large_filter_fragments_kernel, dim3(LFRAG_B3 + (c->conv123 ? Conv123Frags::BLOCKS : 0)),
+        ga3c::launch_stop(c->bfrag[i] ? nullptr : stop, large_filter_fragments_kernel, dim3(LFRAG_B3 + (c->conv123 ? Conv123Large::BLOCKS : 0)),
                           dim3(256), 0, s, th + c->off[0], th + c->off[2], th + c->off[4], c->lfrag[i]);
         HIP_TRY(hipGetLastError());
     }
@@ -2106,11 +2130,17 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
         for (int l = 0; l < c->nconv; ++l) {
             if (!c->band[l]) continue;
             const ConvGeom &g = c->geom[l];
-            if (l == 0 || c->rb) add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
+            if (takes_terms(c, l)) add(l, l == 0 ? FRAG_BYTES8 : FRAG_CONV, c->bfrag[i] + c->bfrag_fwd[l], g.OC * g.K / 8);
             if (!c->rb && (l > 0 || c->max_train > 0)) add(l, FRAG_F32, c->bfrag[i] + c->bfrag_f32[l], g.OC * g.K / 4);
             if (l > 0 && c->max_train > 0) add(l, FRAG_DGRAD, c->bfrag[i] + c->bfrag_dgrad[l], g.OC * g.K / 8);
         }
-        ga3c::launch_stop(stop, c->rb ? band_filter_fragments_kernel<1> : band_filter_fragments_kernel<3>, dim3(blocks), dim3(256), 0, s, jobs);
+        const float *th = c->theta2[i];
+        auto both = [&](auto kernel, int more) {
+            ga3c::launch_stop(stop, kernel, dim3(blocks + more), dim3(256), 0, s, th + c->off[0], th + c->off[2], th + c->off[4], c->bfrag[i] + c->bfrag_123, jobs);
+        };
+        if (c->conv123 == CONV123_PAPER4) both(family_filter_fragments_kernel<Conv123Paper4>, Conv123Paper4::BLOCKS);
+        else if (c->conv123 == CONV123_PAPER3) both(family_filter_fragments_kernel<Conv123Paper3>, Conv123Paper3::BLOCKS);
+        else ga3c::launch_stop(stop, c->rb ? band_filter_fragments_kernel<1> : band_filter_fragments_kernel<3>, dim3(blocks), dim3(256), 0, s, jobs);
         HIP_TRY(hipGetLastError());
     }
     return GA3C_OK;
@@ -2168,12 +2198,18 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         first = 2;
     }
     if (c->fast && c->conv123 && !keep_zv && is_aligned16(frames)) {
-        // larger net, predictions: all three layers in one kernel
+        // predictions: all three layers in one kernel
         const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1], &g2 = c->geom[2];
         STAGE("conv123_fwd", 2.0 * B * (g0.OHW * g0.OC * g0.K + g1.OHW * g1.OC * g1.K + g2.OHW * g2.OC * g2.K),
               (double)B * (g0.CHW + 4.0 * g2.OC * g2.OHW));
-        HIP_TRY((launch_conv123_f16<SpecL2, SpecL3>(frames, table, c->lfrag[which] + LFRAG_VECS, th + c->off[1], th + c->off[3], th + c->off[5],
-                                                    w.act[2], B, 1.f / 255.f, s)));
+        auto go = [&](auto launch, const u32x4 *frag) {
+            return launch(frames, table, frag, th + c->off[1], th + c->off[3], th + c->off[5], w.act[2], B, 1.f / 255.f, s);
+        };
+        if (c->conv123 == CONV123_LARGE)
+            HIP_TRY(go(table ? launch_conv123_f16<Conv123Large, true> : launch_conv123_f16<Conv123Large, false>, c->lfrag[which] + LFRAG_VECS));
+        else if (c->conv123 == CONV123_PAPER4)
+            HIP_TRY(go(table ? launch_conv123_f16<Conv123Paper4, true> : launch_conv123_f16<Conv123Paper4, false>, c->bfrag[which] + c->bfrag_123));
+        else HIP_TRY(go(launch_conv123_f16<Conv123Paper3, false>, c->bfrag[which] + c->bfrag_123));      // its frames never come in a table
         first = 3;
     }
     for (int l = first; l < c->nconv; ++l) {
@@ -2205,6 +2241,7 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
                 continue;
             }
         }
+        // (Predictions whose maps fit a compute unit's LDS are done already, in one kernel.)
         // At fp32 accuracy the 4x4 layers run on the fp32 instruction, straight from memory, in both calls: faster than bands
         // staged as three bf16 terms up to 256 frames (128 frames: 77x77 map 65 / 73 us, 26x26 11.8 / 12.7, 12x12 with 64 filters 6.1 /
         // 10.2, the only loss 37x37 with 64 filters 27.9 / 24.8; one frame 4.6 / 9.8) and nearer to the exact sums (2.9e-7 /
@@ -2494,21 +2531,29 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     }
     if (rc == GA3C_OK && c->nconv == 3 && spec_matches<SpecL2>(c->geom[1], false) && spec_matches<SpecL3>(c->geom[2], false) &&
         c->off[2] % 4 == 0 && c->off[4] % 4 == 0) {
-        c->conv123 = spec_matches<SpecL1>(c->geom[0], true) && !c->rb && max_predict_batch > 0;
+        if (spec_matches<SpecL1>(c->geom[0], true) && !c->rb && max_predict_batch > 0) c->conv123 = CONV123_LARGE;
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
-            guard(dmalloc((void **)&c->lfrag[i], sizeof(u32x4) * (LFRAG_VECS + (c->conv123 ? Conv123Frags::VECS : 0))));
+            guard(dmalloc((void **)&c->lfrag[i], sizeof(u32x4) * (LFRAG_VECS + (c->conv123 ? Conv123Large::VECS : 0))));
             if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
         }
     }
+    for (int l = 0; l < c->nconv; ++l) c->band[l] = on_band_kernels(c->geom[l], l);
+    if (c->nconv == 3 && !c->rb && max_predict_batch > 0 && c->band[2] && c->off[2] % 4 == 0 && c->off[4] % 4 == 0) {
+        const ConvGeom &g = c->geom[0];
+        const bool frames = g.C == 4 && g.H == 84 && g.W == 84 && g.OC == 32 && g.KS == 8;
+        if (frames && g.S == 4 && spec_matches<SpecP2>(c->geom[1], false) && spec_matches<SpecP43>(c->geom[2], false)) c->conv123 = CONV123_PAPER4;
+        if (frames && g.S == 3 && spec_matches<SpecP32>(c->geom[1], false) && spec_matches<SpecP33>(c->geom[2], false)) c->conv123 = CONV123_PAPER3;
+    }
     for (int l = 0; l < c->nconv; ++l) {
         const ConvGeom &g = c->geom[l];
-        c->band[l] = on_band_kernels(g, l);
         if (!c->band[l]) continue;
         const size_t vecs = (size_t)(c->rb ? 1 : 3) * g.OC * g.K / 8;
-        if (l == 0 || c->rb) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
+        if (takes_terms(c, l)) { c->bfrag_fwd[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
         if (!c->rb && (l > 0 || max_train_frames > 0)) { c->bfrag_f32[l] = c->bfrag_vecs; c->bfrag_vecs += (size_t)g.OC * g.K / 4; }
         if (l > 0 && max_train_frames > 0) { c->bfrag_dgrad[l] = c->bfrag_vecs; c->bfrag_vecs += vecs; }
     }
+    c->bfrag_123 = c->bfrag_vecs;
+    c->bfrag_vecs += c->conv123 == CONV123_PAPER4 ? Conv123Paper4::VECS : c->conv123 == CONV123_PAPER3 ? Conv123Paper3::VECS : 0;
     if (c->bfrag_vecs)
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
             guard(dmalloc((void **)&c->bfrag[i], sizeof(u32x4) * c->bfrag_vecs));

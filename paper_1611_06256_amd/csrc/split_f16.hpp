@@ -17,7 +17,6 @@
 namespace ga3c {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 union F16x8Bits {
     f16x8 v;
     u32x4 u;
@@ -42,22 +41,10 @@ __device__ __forceinline__ void split2_pair(const float x, const float y, const 
     lo = l;
 }
 
-// 16 bytes -> 16 float16 (two 16-byte vectors), exactly: 1024 + b is the number whose bits are 0x6400 + b.
-__device__ __forceinline__ void bytes_to_f16(const u32x4 b, u32x4 &lo8, u32x4 &hi8) {
-    union { uint32_t u; f16x2 h; } c;
-    uint32_t o[8];
-    const f16x2 k = {(_Float16)1024.f, (_Float16)1024.f};
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        c.u = __builtin_amdgcn_perm(0x64646464u, b[d], 0x04010400u);
-        c.h -= k;
-        o[2 * d] = c.u;
-        c.u = __builtin_amdgcn_perm(0x64646464u, b[d], 0x04030402u);
-        c.h -= k;
-        o[2 * d + 1] = c.u;
-    }
-    lo8 = u32x4{o[0], o[1], o[2], o[3]};
-    hi8 = u32x4{o[4], o[5], o[6], o[7]};
+// Byte t of a, then of b, as float16: a byte's bits are those of the subnormal number b 2^-24, which the matrix instruction takes as it is.
+__device__ __forceinline__ uint32_t f16_of_bytes(const uint32_t a, const uint32_t b, int t) {
+    return __builtin_amdgcn_perm(b, a, 0x0c040c00u + 0x00010001u * t);
 }
+constexpr float F16_BYTE_UNIT = 16777216.f;       // what products with such numbers are multiplied by
 
 }  // namespace ga3c

@@ -36,11 +36,16 @@ def scaled(net, theta, layer, power):
     return theta
 
 
+def network(G, which, A):
+    return G.LARGE_NET(A) if which == "large" else G.NetDesc(conv=((32, 8, int(which[-1])), (32, 4, 2), (64, 4, 2)), fc_units=256, n_actions=A)
+
+
 # one, two and three frames a block; activations beyond float16's largest number and below its smallest; a filter of zeros
+@pytest.mark.parametrize("which", ["large", "paper4", "paper3"])
 @pytest.mark.parametrize("B,layer,power", [(1, 1, 0), (256, 1, 0), (257, 1, 0), (513, 1, 0), (3, 1, 30), (3, 1, -30), (3, 2, 30), (3, 2, -30), (3, 3, 30), (3, 3, -40)])
-def test_larger_net_predictions_in_one_kernel(G, B, layer, power):
+def test_predictions_with_three_convolutions_in_one_kernel(G, which, B, layer, power):
     import torch
-    net, onet, theta = P.make(G, G.LARGE_NET(6), B, 0, 9100 + B)
+    net, onet, theta = P.make(G, network(G, which, 6), B, 0, 9100 + B)
     theta = scaled(net, theta, layer, power)
     at, shape = net.offsets()[f"conv{layer}.W"]
     theta[at:at + int(np.prod(shape[1:]))] = 0
