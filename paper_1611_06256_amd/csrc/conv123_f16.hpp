@@ -4,17 +4,18 @@
 // fits (32 8x8 stride 4 or 3, 32 4x4 stride 2, 64 4x4 stride 2), each layer with its rectifier.
 //
 // Operands are two float16 terms each (split_f16.hpp), bytes one.  Filters come scaled and split, in the order in which the
-// lanes take them, from a buffer per parameter copy; an activation map is scaled by its own largest value, which the eight
-// wavefronts find between a layer's products and its way to LDS (one barrier more than without).
+// lanes take them, from a buffer per parameter copy.  Layer 1's map is scaled by the largest value that it can have with these filters
+// (sum of a filter's magnitudes and its bias; a byte is 1 at most), layer 2's by its own largest value, which the eight wavefronts
+// find between the layer's products and its way to LDS.
 //
 //   layer 1  both filter tiles from one read of a pixel tile's bytes: wavefront w has tiles w, w + 8, ..; of the tiles that are left
 //            over wavefronts 2 i and 2 i + 1 have the i-th, a filter tile each
 //   layers 2, 3  wavefront w has filter tile w % (filters / 16) and every so many pixel tiles
 //
-// LDS holds the frame as [row][column][plane] float16, so that a lane's eight values of a filter row are 16 bytes in one place
-// whatever the stride; later layer 2's output takes its place.  Every wavefront keeps a layer's filters in registers, 128 or 144 of
-// them; those of the next layer take the place of the ones that have been multiplied, k-block by k-block, so that no layer waits
-// for its filters.
+// Frames come to LDS as the bytes they are, the next one while this one is worked on; a lane's eight columns of a filter row are two
+// dwords, or cut from three where the stride is odd.  Layer 2's map takes the place of layer 1's.  Every wavefront keeps a layer's
+// filters in registers, 128 or 144 of them; those of the next layer take the place of the ones that have been multiplied, k-block by
+// k-block, so that no layer waits for its filters.
 //
 // Bound by one frame's chain through a compute unit: bytes in, three layers and six barriers.  us a call (with the fc layer and the heads
 // behind it) against a kernel per layer on three bfloat16 terms or the fp32 instruction: larger net 1 frame 26.4 -> 21.8, 64: 28.8 ->
@@ -69,14 +70,15 @@ struct Conv123Net {
     static constexpr int NT2 = (SP2::NPIX + 15) / 16, NT3 = (SP3::NPIX + 15) / 16, OT2 = SP2::OC / 16;
     static_assert(SP2::H == OW1 && SP2::W == OW1 && SP2::C == 32 && SP2::K == 512 && SP2::S == 2 && (SP2::OC == 32 || SP2::OC == 64), "layer 2: 4x4, stride 2");
     static_assert(SP3::H == SP2::OH && SP3::C == SP2::OC && SP3::K % 32 == 0 && SP3::OC == 64, "layer 3");
-    // Filters: [filter tile][k-block][term][lane] vectors of eight float16 each; then the reciprocals of the filters' scales.
+    // Filters: [filter tile][k-block][term][lane] vectors of eight float16 each; then the reciprocals of the filters' scales, and sums of the
+    // magnitudes of layer 1's.
     static constexpr int KB1 = 8, KB2 = 16, KB3 = SP3::K / 32, CG3 = SP3::C / 32;
     static constexpr int F1 = 0, F2 = F1 + 2 * KB1 * 128, F3 = F2 + OT2 * KB2 * 128, INV = F3 + 4 * KB3 * 128;
-    static constexpr int FILTERS = 32 + SP2::OC + 64, VECS = INV + FILTERS / 4;
+    static constexpr int FILTERS = 32 + SP2::OC + 64, SUM = INV + FILTERS / 4, VECS = SUM + 32 / 4;
     // the kernel that writes them: four k-blocks of a filter tile each block
     static constexpr int B1 = 2 * KB1 / 4, B2 = B1 + OT2 * KB2 / 4, PER3 = (KB3 + 3) / 4, BLOCKS = B2 + 4 * PER3;
-    static constexpr int XS = 0, Y2 = 0, Y1 = 84 * 84 * 8, LDS = Y1 + 2 * M2::TERM;        // layer 2's output takes the frame's place
-    static_assert(Y2 + 2 * M3::TERM <= Y1 && LDS + 2048 <= 160 * 1024, "LDS");
+    static constexpr int Y = 2 * F16_FRAME, LDS = Y + 2 * (M2::TERM > M3::TERM ? M2::TERM : M3::TERM);
+    static_assert(LDS + 2048 <= 160 * 1024, "LDS");
 };
 
 // Block b of N::BLOCKS, 256 threads.  w1, w2, w3: the filter tensors, 16-byte aligned.
@@ -94,11 +96,11 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
     w += (size_t)ot * 16 * K;
     // everything is asked for at once: my eight values, and sixteen threads, which are a row of lanes, find a filter's largest one
     const int kb = kb0 + (tid >> 6);
-    float v[8], m = 0.f;
+    float v[8], m = 0.f, sum = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         int k;                                             // of the filter as it lies in memory: (channel, row, column)
-        if (layer == 1) k = j % 4 * 64 + kb * 8 + 2 * g + j / 4;
+        if (layer == 1) k = 32 * kb + 8 * g + j;
         else if (layer == 2) k = (8 * g + j) * 16 + kb;
         else k = (kb % N::CG3 * 32 + 8 * g + j) * TAPS3 + kb / N::CG3;
         v[j] = w[(size_t)l16 * K + min(k, K - 1)];
@@ -110,6 +112,12 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
     for (int i = 0; i < KMOST / 64; ++i) m = fmaxf(fmaxf(fmaxf(m, fabsf(all[i].x)), fmaxf(fabsf(all[i].y), fabsf(all[i].z))), fabsf(all[i].w));
     m = fmaxf(m, dpp_row_f32<0xB1>(m)); m = fmaxf(m, dpp_row_f32<0x4E>(m));
     m = fmaxf(m, dpp_row_f32<0x141>(m)); m = fmaxf(m, dpp_row_f32<0x140>(m));
+    if (layer == 1) {                                      // K = 256: four vectors a thread
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum += (fabsf(all[i].x) + fabsf(all[i].y)) + (fabsf(all[i].z) + fabsf(all[i].w));
+        sum += dpp_row_f32<0xB1>(sum); sum += dpp_row_f32<0x4E>(sum); sum += dpp_row_f32<0x141>(sum); sum += dpp_row_f32<0x140>(sum);
+        if (kb0 == 0 && (tid & 15) == 0) ((float *)(frag + N::SUM))[ot * 16 + (tid >> 4)] = sum;
+    }
     if ((tid & 15) == 0) {
         float s, inv;
         f16_scale(m, s, inv);
@@ -141,30 +149,24 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
     typedef typename N::SP3 SP3;
     typedef typename N::M2 M2;
     typedef typename N::M3 M3;
-    constexpr int CHW = 4 * 84 * 84, HW4 = 84 * 84 / 4, VPT = (HW4 + 511) / 512, KB1 = N::KB1, KB2 = N::KB2, KB3 = N::KB3;
+    constexpr int CHW = 4 * 84 * 84, KB1 = N::KB1, KB2 = N::KB2, KB3 = N::KB3;
     constexpr int FULL1 = N::NT1 / 8, REST1 = N::NT1 % 8, PG2 = 8 / N::OT2;      // tiles per wavefront, tiles left over; groups of wavefronts
+    constexpr int T2 = (N::NT2 + PG2 - 1) / PG2, T3 = (N::NT3 + 1) / 2;          // the last of some wavefronts is not there
     static_assert(2 * REST1 <= 8, "half a tile each");
     extern __shared__ __attribute__((aligned(16))) unsigned char c123_smem[];
-    __shared__ float most[2][8];                           // largest values of layers 1 and 2, by wavefront
+    __shared__ float most[8];                              // largest values of layer 2, by wavefront
     __shared__ __attribute__((aligned(16))) float consts[2][N::FILTERS];       // by filter: reciprocal of its scale, bias
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int grid = (int)gridDim.x;
+    const uint32_t lds = lds_address(c123_smem);
 
-    // a unit is four pixels: a dword of each plane
-    uint32_t pre[VPT][4];
     int f = blockIdx.x;
     FramePointer<TABLE> next;
-    auto fetch = [&]() {
-        const uint8_t *src = next.get();
-#pragma unroll
-        for (int i = 0; i < VPT; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) pre[i][c] = *(const uint32_t *)(src + c * (84 * 84) + 4u * (uint32_t)min(tid + 512 * i, HW4 - 1));
-    };
     next.ask(x, table, min(f, nframes - 1), CHW);
-    fetch();
-    if (TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
+    f16_frame_to_lds<8>(next.get(), lds, wave, lane);
+    if (TABLE) next.ask(x, table, min(f + grid, nframes - 1), CHW);
 
     // layer 1: w1[0] is filter tile `own`, w1[1] the other one
     const int own = wave & 1, ot2 = wave % N::OT2, pg2 = wave / N::OT2, ot3 = wave & 3, pg3 = wave >> 2;
@@ -187,165 +189,152 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
 #pragma unroll
         for (int t = 0; t < 2; ++t) w3[kb][t].u = vec(N::F3 + ((ot3 * KB3 + kb) * 2 + t) * 64);
     };
+    float bound = ((const float *)(frag + N::SUM))[lane & 31];
+    const float bb = b1[lane & 31];
     if (tid < N::FILTERS) {
         consts[0][tid] = ((const float *)(frag + N::INV))[tid] * (tid < 32 ? scale * F16_BYTE_UNIT : 1.f);
         consts[1][tid] = tid < 32 ? b1[tid] : tid < 32 + SP2::OC ? b2[tid - 32] : b3[tid - 32 - SP2::OC];
     }
+    bound = 1.0001f * (255.f * scale * bound + fabsf(bb));
+    float s1, si1;
+    f16_scale(f16_wave_most(bound), s1, si1);
+    s1 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s1)));
+    si1 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(si1)));
 
-    // Largest value of all wavefronts, as a scale (behind a barrier).
-    auto scale_of = [&](const float (&m)[8], float &s, float &si) {
-        const float a = fmaxf(fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])), fmaxf(fmaxf(m[4], m[5]), fmaxf(m[6], m[7])));
-        f16_scale(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(a))), s, si);
-    };
-    auto wave_most = [&](float m) {
-        m = fmaxf(m, dpp_row_f32<0xB1>(m)); m = fmaxf(m, dpp_row_f32<0x4E>(m));
-        m = fmaxf(m, dpp_row_f32<0x141>(m)); m = fmaxf(m, dpp_row_f32<0x140>(m));
-        const int u = __float_as_int(m);
-        return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 0)), __int_as_float(__builtin_amdgcn_readlane(u, 16))),
-                     fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 32)), __int_as_float(__builtin_amdgcn_readlane(u, 48))));
-    };
     constexpr int WT[3] = {1, 0, 0}, XT[3] = {0, 1, 0};    // smallest products first
-
-    for (; f < nframes; f += gridDim.x) {
+    floatx4 out[T3];
+    // layer 3's results leave when the next frame has arrived: a wait for that would be one for the stores
+    auto store = [&](int fr) {
+        if (N::NT3 == 1 && pg3 != 0) return;
+        float *yb = y + (size_t)fr * SP3::OC * SP3::NPIX;
+#pragma unroll
+        for (int i = 0; i < T3; ++i) {
+            const int p = (pg3 + 2 * i) * 16 + (lane & 15);
+            if (p < SP3::NPIX) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) yb[(ot3 * 16 + 4 * (lane >> 4) + r) * SP3::NPIX + p] = out[i][r];
+            }
+        }
+    };
+    int place = 0;
+    for (bool first = true; f < nframes; f += grid, place ^= F16_FRAME, first = false) {
         // what a frame does not change is read and worked out anew for each: there are no registers to keep it in
         int own_lane = lane;
         asm volatile("s_mov_b32 %0, 0" : "=s"(again), "+v"(own_lane));
         const int l16 = own_lane & 15, g = own_lane >> 4;
         const float4 *inv = (const float4 *)consts[0] + g, *bias = (const float4 *)consts[1] + g;      // my four filters of tile t: [4 t]
-        // sums of those for a pixel -> rectified values, and the largest of them
-        auto rectify = [&](floatx4 &a, const float4 iv, const float4 bv, const float si, bool in, float &m) {
-            const float v[4] = {a[0] * iv.x * si + bv.x, a[1] * iv.y * si + bv.y, a[2] * iv.z * si + bv.z, a[3] * iv.w * si + bv.w};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                a[r] = v[r] > 0.f ? v[r] : 0.f;
-                m = in ? fmaxf(m, a[r]) : m;
-            }
+        // sums of those for a pixel -> rectified values
+        auto rectify = [&](const floatx4 a, const float4 iv, const float4 bv, const float si) {
+            return floatx4{fmaxf(a[0] * iv.x * si + bv.x, 0.f), fmaxf(a[1] * iv.y * si + bv.y, 0.f), fmaxf(a[2] * iv.z * si + bv.z, 0.f),
+                           fmaxf(a[3] * iv.w * si + bv.w, 0.f)};
         };
         // values of filters 16 t + 4 g .. as terms, to the pixel that lies at `at`
-        auto store4 = [&](unsigned char *map, int term, int group, int at, int t, const floatx4 v, float s) {
+        auto store4 = [&](int term, int group, int at, int t, const floatx4 v, float s) {
             uint2 hi, lo;
             split2_pair(v[0], v[1], s, hi.x, lo.x);
             split2_pair(v[2], v[3], s, hi.y, lo.y);
-            unsigned char *dst = map + at + (2 * t + (g >> 1)) * group + 8 * (g & 1);
+            unsigned char *dst = c123_smem + N::Y + at + (2 * t + (g >> 1)) * group + 8 * (g & 1);
             *(uint2 *)dst = hi;
             *(uint2 *)(dst + term) = lo;
         };
 #pragma unroll
         for (int kb = 0; kb < KB1; ++kb) load1(kb);
-        __syncthreads();                                   // the last frame's layer-2 output has been read
-#pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-            u32x4 o[2];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                o[t / 2][t % 2 * 2] = f16_of_bytes(pre[i][0], pre[i][1], t);
-                o[t / 2][t % 2 * 2 + 1] = f16_of_bytes(pre[i][2], pre[i][3], t);
-            }
-            if (tid + 512 * i < HW4) {
-                u32x4 *dst = (u32x4 *)(c123_smem + N::XS) + 2 * (tid + 512 * i);
-                dst[0] = o[0]; dst[1] = o[1];
-            }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // my pieces of the frame are there
+        __syncthreads();                                   // everybody's are; the last layer-2 map has been read
+        if (!first) store(f - grid);
+        if (f + grid < nframes) {
+            if (!TABLE) next.ask(x, table, f + grid, CHW);
+            f16_frame_to_lds<8>(next.get(), lds + (place ^ F16_FRAME), wave, lane);
+            if (TABLE) next.ask(x, table, min(f + 2 * grid, nframes - 1), CHW);
         }
-        __syncthreads();
-        if (!TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
-        fetch();
-        if (TABLE) next.ask(x, table, min(f + 2 * (int)gridDim.x, nframes - 1), CHW);
-        // ---- layer 1: a k-block is a filter row, a lane's eight k two pixels of four planes
+        // ---- layer 1: a k-block is four filter rows of a plane
         {
+            constexpr bool ODD = N::S1 % 2 != 0;
+            constexpr int DW = ODD ? 3 : 2;
+            struct Raw { uint32_t d[DW]; };
             auto base_of = [&](int t) {
                 const int p = min(t * 16 + l16, N::NPIX1 - 1);
-                return N::XS + ((p / N::OW1 * 84 + p % N::OW1) * N::S1 + 2 * g) * 8;
+                return (p / N::OW1 * N::S1 + g) * 84 + p % N::OW1 * N::S1;
             };
-            auto operand = [&](int base, int kb) {
-                const unsigned char *src = c123_smem + base + kb * (84 * 8);       // 8-byte aligned
-                F16x8Bits v;
-                if (N::S1 % 2 == 0) v.u = *(const u32x4 *)src;
-                else {
-                    const uint2 lo = *(const uint2 *)src, hi = *(const uint2 *)(src + 8);
-                    v.u = u32x4{lo.x, lo.y, hi.x, hi.y};
-                }
-                return v.v;
+            auto raw = [&](int base, int kb) {
+                const uint32_t *src = (const uint32_t *)(c123_smem + place + (ODD ? base & ~3 : base) + (kb >> 1) * (84 * 84) + (kb & 1) * (4 * 84));
+                Raw r;
+#pragma unroll
+                for (int d = 0; d < DW; ++d) r.d[d] = src[d];
+                return r;
+            };
+            auto operand = [&](const Raw &r, int base) {
+                if constexpr (ODD) return f16_of_bytes(__builtin_amdgcn_alignbyte(r.d[1], r.d[0], base & 3), __builtin_amdgcn_alignbyte(r.d[2], r.d[1], base & 3));
+                else return f16_of_bytes(r.d[0], r.d[1]);
             };
             const int left = 8 * FULL1 + (wave >> 1);
             int base[FULL1];
-            floatx4 acc[FULL1][2], accx = floatx4{0.f, 0.f, 0.f, 0.f};
+            floatx4 acc[FULL1][2], accx[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+            if (wave < 2 * REST1) {                        // before the filters go
+                const int b = base_of(left);
+                Raw r[KB1];
+#pragma unroll
+                for (int kb = 0; kb < KB1; ++kb) r[kb] = raw(b, kb);
+#pragma unroll
+                for (int kb = 0; kb < KB1; ++kb) {
+                    const f16x8 v = operand(r[kb], b);
+#pragma unroll
+                    for (int t = 1; t >= 0; --t) accx[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[0][kb][t].v, v, accx[t], 0, 0, 0);
+                }
+                accx[0] += accx[1];
+            }
+            Raw r[2][FULL1];
 #pragma unroll
             for (int i = 0; i < FULL1; ++i) {
                 base[i] = base_of(wave + 8 * i);
                 acc[i][0] = acc[i][1] = floatx4{0.f, 0.f, 0.f, 0.f};
+                r[0][i] = raw(base[i], 0);
             }
-            if (wave < 2 * REST1) {                        // before the filters go
-                const int b = base_of(left);
-#pragma unroll
-                for (int kb = 0; kb < KB1; ++kb) {
-                    const f16x8 v = operand(b, kb);
-#pragma unroll
-                    for (int t = 1; t >= 0; --t) accx = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[0][kb][t].v, v, accx, 0, 0, 0);
-                }
-            }
-            constexpr bool AHEAD = FULL1 <= 3;             // registers for the next k-block's operands
-            f16x8 xv[AHEAD ? 2 : 1][FULL1];
-            auto read = [&](int kb) {
-#pragma unroll
-                for (int i = 0; i < FULL1; ++i) xv[AHEAD ? kb & 1 : 0][i] = operand(base[i], kb);
-            };
-            if (AHEAD) read(0);
 #pragma unroll
             for (int kb = 0; kb < KB1; ++kb) {
-                if (!AHEAD) read(kb);
-                else if (kb + 1 < KB1) read(kb + 1);
+                if (kb + 1 < KB1) {
+#pragma unroll
+                    for (int i = 0; i < FULL1; ++i) r[(kb + 1) & 1][i] = raw(base[i], kb + 1);
+                }
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int t = 1; t >= 0; --t)
+                for (int i = 0; i < FULL1; ++i) {
+                    const f16x8 v = operand(r[kb & 1][i], base[i]);
 #pragma unroll
-                    for (int i = 0; i < FULL1; ++i)
+                    for (int t = 1; t >= 0; --t)
 #pragma unroll
-                        for (int o = 0; o < 2; ++o)
-                            acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[o][kb][t].v, xv[AHEAD ? kb & 1 : 0][i], acc[i][o], 0, 0, 0);
+                        for (int o = 0; o < 2; ++o) acc[i][o] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w1[o][kb][t].v, v, acc[i][o], 0, 0, 0);
+                }
                 load2(2 * kb);
                 load2(2 * kb + 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            float m = 0.f;
             const float4 iv[2] = {inv[4 * own], inv[4 * (own ^ 1)]}, bv[2] = {bias[4 * own], bias[4 * (own ^ 1)]};
-#pragma unroll
-            for (int i = 0; i < FULL1; ++i)
-#pragma unroll
-                for (int o = 0; o < 2; ++o) rectify(acc[i][o], iv[o], bv[o], 1.f, true, m);
-            if (wave < 2 * REST1) rectify(accx, iv[0], bv[0], 1.f, true, m);       // pixels behind the last are copies of it
-            m = wave_most(m);
-            if (lane == 0) most[0][wave] = m;
-            __syncthreads();
-            float s, si;
-            scale_of(most[0], s, si);
             auto put = [&](const floatx4 a, int t, int o) {
                 const int p = t * 16 + l16;
-                if (N::NPIX1 % 16 == 0 || p < N::NPIX1) store4(c123_smem + N::Y1, M2::TERM, M2::GROUP, M2::pixel(p / N::OW1, p % N::OW1), own ^ o, a, s);
+                if (N::NPIX1 % 16 == 0 || p < N::NPIX1)
+                    store4(M2::TERM, M2::GROUP, M2::pixel(p / N::OW1, p % N::OW1), own ^ o, rectify(a, iv[o], bv[o], 1.f), s1);
             };
 #pragma unroll
             for (int i = 0; i < FULL1; ++i) { put(acc[i][0], wave + 8 * i, 0); put(acc[i][1], wave + 8 * i, 1); }
-            if (wave < 2 * REST1) put(accx, left, 0);
+            if (wave < 2 * REST1) put(accx[0], left, 0);
         }
         __syncthreads();
         // ---- layer 2: a k-block is a tap, 32 channels
         {
-            float m = 0.f;
-            constexpr int NT = (N::NT2 + PG2 - 1) / PG2;      // the last of some wavefronts is not there
-            float s, si;
-            scale_of(most[0], s, si);
-            floatx4 acc[NT];
-            int pb[NT], px[NT];
+            floatx4 acc[T2];
+            int pb[T2], px[T2];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) {
+            for (int i = 0; i < T2; ++i) {
                 const int p = (pg2 + PG2 * i) * 16 + l16;
                 px[i] = p < SP2::NPIX ? p : -1;
-                pb[i] = N::Y1 + M2::origin(p < SP2::NPIX ? p : 0) + g * M2::GROUP;
+                pb[i] = N::Y + M2::origin(p < SP2::NPIX ? p : 0) + g * M2::GROUP;
                 acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-            F16x8Bits xv[2][NT][2];
+            F16x8Bits xv[2][T2][2];
             auto read = [&](int kb) {
 #pragma unroll
-                for (int i = 0; i < NT; ++i)
+                for (int i = 0; i < T2; ++i)
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
                         xv[kb & 1][i][t].u = *(const u32x4 *)(c123_smem + t * M2::TERM + pb[i] + M2::pixel(kb / 4, kb % 4));
@@ -358,43 +347,46 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int i = 0; i < NT; ++i)
+                    for (int i = 0; i < T2; ++i)
                         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w2[kb][WT[q]].v, xv[kb & 1][i][XT[q]].v, acc[i], 0, 0, 0);
                 load3(kb);
                 if (kb + KB3 - KB2 >= KB2) load3(kb + KB3 - KB2);
                 __builtin_amdgcn_sched_barrier(0);
             }
             const float4 iv = inv[4 * (2 + ot2)], bv = bias[4 * (2 + ot2)];
+            float m = 0.f;
 #pragma unroll
-            for (int i = 0; i < NT; ++i) rectify(acc[i], iv, bv, si, px[i] >= 0, m);
-            m = wave_most(m);
-            if (lane == 0) most[1][wave] = m;
-            __syncthreads();
-            scale_of(most[1], s, si);
+            for (int i = 0; i < T2; ++i) {
+                acc[i] = rectify(acc[i], iv, bv, si1);
+                const float mi = fmaxf(fmaxf(acc[i][0], acc[i][1]), fmaxf(acc[i][2], acc[i][3]));
+                m = px[i] >= 0 ? fmaxf(m, mi) : m;
+            }
+            m = f16_wave_most(m);
+            if (lane == 0) most[wave] = m;
+            __syncthreads();                               // everybody's largest value; layer 1's map has been read
+            float s, si;
+            f16_scale_of(most, s, si);
 #pragma unroll
-            for (int i = 0; i < NT; ++i)
-                if (px[i] >= 0) store4(c123_smem + N::Y2, M3::TERM, M3::GROUP, M3::pixel(px[i] / SP3::W, px[i] % SP3::W), ot2, acc[i], s);
+            for (int i = 0; i < T2; ++i)
+                if (px[i] >= 0) store4(M3::TERM, M3::GROUP, M3::pixel(px[i] / SP3::W, px[i] % SP3::W), ot2, acc[i], s);
         }
         __syncthreads();
         // ---- layer 3: a k-block is 32 channels of a tap
         if (N::NT3 > 1 || pg3 == 0) {
-            constexpr int NT = (N::NT3 + 1) / 2;
             float s, si;
-            scale_of(most[1], s, si);
-            floatx4 acc[NT];
-            int pb[NT], px[NT];
+            f16_scale_of(most, s, si);
+            floatx4 acc[T3];
+            int pb[T3];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                const int p = (pg3 + 2 * i) * 16 + l16;
-                px[i] = p < SP3::NPIX ? p : -1;
-                pb[i] = N::Y2 + M3::origin(p < SP3::NPIX ? p : 0) + g * M3::GROUP;
+            for (int i = 0; i < T3; ++i) {
+                pb[i] = N::Y + M3::origin(min((pg3 + 2 * i) * 16 + l16, SP3::NPIX - 1)) + g * M3::GROUP;
                 acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
             }
-            F16x8Bits xv[2][NT][2];
+            F16x8Bits xv[2][T3][2];
             auto read = [&](int kb) {
                 const int tap = kb / N::CG3;
 #pragma unroll
-                for (int i = 0; i < NT; ++i)
+                for (int i = 0; i < T3; ++i)
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
                         xv[kb & 1][i][t].u = *(const u32x4 *)(c123_smem + t * M3::TERM + pb[i] + M3::pixel(tap / SP3::KS, tap % SP3::KS) +
@@ -408,22 +400,16 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
 #pragma unroll
                 for (int q = 0; q < 3; ++q)
 #pragma unroll
-                    for (int i = 0; i < NT; ++i)
+                    for (int i = 0; i < T3; ++i)
                         acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(w3[kb][WT[q]].v, xv[kb & 1][i][XT[q]].v, acc[i], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            float *yb = y + (size_t)f * SP3::OC * SP3::NPIX, m = 0.f;
             const float4 iv = inv[4 * (2 + N::OT2 + ot3)], bv = bias[4 * (2 + N::OT2 + ot3)];
 #pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                rectify(acc[i], iv, bv, si, false, m);
-                if (px[i] >= 0) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) yb[(ot3 * 16 + 4 * g + r) * SP3::NPIX + px[i]] = acc[i][r];
-                }
-            }
+            for (int i = 0; i < T3; ++i) out[i] = rectify(acc[i], iv, bv, si);
         }
     }
+    store(f - grid);
 }
 
 template <class N, bool TABLE>

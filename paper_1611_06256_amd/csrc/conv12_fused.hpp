@@ -108,9 +108,9 @@ inline hipError_t launch_conv12_filter_fragments(const float *w1, const float *w
     return hipGetLastError();
 }
 
-// The next frame of a block is staged between two barriers of the block, or early: between the layer-1 wavefronts' own waits, while
-// layer 2 goes on; or either, as the block's number of frames says (the wait is there in any case).
-enum Conv12Stage { C12_BARRIERS, C12_EARLY, C12_EITHER };
+// The next frame of a block is staged between two barriers of the block, or early, between the layer-1 wavefronts' own waits, while
+// layer 2 goes on, as the block's number of frames says (the wait is there in any case).
+enum Conv12Stage { C12_BARRIERS, C12_EITHER };
 
 // x: [n][4][84][84] bytes, or table: where each frame lies (FramePointer); frag: the three fragment sets; b1 [16], b2 [32];
 // y1: [n][16][400] or nullptr; y2: [n][32][81].  Frames blockIdx.x, + gridDim.x, ...
@@ -182,7 +182,7 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
 
     const int n = (nframes - first + grid - 1) / grid;             // frames of this block (>= 1)
 
-    const bool early = STAGE == C12_EITHER ? n > (ONE ? 5 : 2) : WAIT;
+    const bool early = WAIT && n > (ONE ? 5 : 2);
 
     floatx4 keep[3];                                               // layer 2: my filter tile's sums of the previous frame
 #pragma unroll
@@ -408,12 +408,10 @@ __global__ __launch_bounds__(512, 1) void conv12_fused_fwd_kernel(const uint8_t 
 
 inline int conv12_fused_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
 
+// For updates, and predictions with operands rounded to bfloat16 (the others: conv12_f16.hpp).
 // When the next frame is staged (barriers / early, us of the launch, medians of three runs).
-// Predictions at fp32 accuracy: early where a block has more than two frames, 512 frames 14.95 / 14.98, 600: 18.4 / 17.9, 768: 18.6 /
-// 18.4, 1024: 22.8 / 22.6.  One frame a block has nothing to stage, and the wait and the count cost it 0.3 us (128 frames 8.35 / 8.6,
-// 256: 9.4 / 9.7), so the two are kernels of their own.  Frames from a table need two registers more than there are to stage early, and
-// a launch with scratch memory starts about a microsecond later; with rounded operands there is a sixth of the products for the wait to
-// hide behind (1024: 15.1 / 15.5, 2048: 23.5 / 24.2): barriers.
+// Predictions: between barriers, a sixth of the products is not enough for the wait to hide behind (1024 frames 15.1 / 15.5, 2048: 23.5 /
+// 24.2).
 // Updates: early in blocks of three frames and more, with rounded operands of six and more, one kernel for both; 1025 frames 25.7 /
 // 25.1, 2560: 50.1 / 48.8; rounded 640: 14.7 / 14.7, 1025: 18.6 / 19.1, 1280: 20.2 / 20.3, 1750: 25.3 / 24.7, 2560: 39.2 / 36.2.
 // (Kernels of their own took 0.3 us less for 40 frames and 0.8 for 640 rounded ones, but the 50 KB of them moved the other kernels
@@ -421,13 +419,12 @@ inline int conv12_fused_blocks(int nframes) { return nframes < 256 ? nframes : 2
 inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2, float *y1,
                                           float *y2, int nframes, float scale, hipStream_t s, int rb) {
     if (nframes <= 0) return hipSuccess;
-    typedef decltype(&conv12_fused_fwd_kernel<false, false, false, C12_BARRIERS>) Kernel;
-    static const Kernel kernels[9] = {                     // ONE, KEEP, TABLE; the last: predictions staged early
-        conv12_fused_fwd_kernel<false, false, false, C12_BARRIERS>, conv12_fused_fwd_kernel<false, false, true, C12_BARRIERS>,
+    if (!y1 && !rb) return hipErrorInvalidValue;       // conv12_f16.hpp's
+    typedef decltype(&conv12_fused_fwd_kernel<true, false, false, C12_BARRIERS>) Kernel;
+    static const Kernel kernels[6] = {                     // table; updates (exact, rounded), rounded predictions
         conv12_fused_fwd_kernel<false, true, false, C12_EITHER>, conv12_fused_fwd_kernel<false, true, true, C12_EITHER>,
-        conv12_fused_fwd_kernel<true, false, false, C12_BARRIERS>, conv12_fused_fwd_kernel<true, false, true, C12_BARRIERS>,
         conv12_fused_fwd_kernel<true, true, false, C12_EITHER>, conv12_fused_fwd_kernel<true, true, true, C12_EITHER>,
-        conv12_fused_fwd_kernel<false, false, false, C12_EARLY>};
+        conv12_fused_fwd_kernel<true, false, false, C12_BARRIERS>, conv12_fused_fwd_kernel<true, false, true, C12_BARRIERS>};
     static bool attr_set = false;     // the kernels need more LDS than the default limit
     if (!attr_set) {
         for (const Kernel k : kernels) {
@@ -436,8 +433,7 @@ inline hipError_t launch_conv12_fused_fwd(const uint8_t *x, const uint8_t *const
         }
         attr_set = true;
     }
-    const bool early = !rb && !y1 && !table && nframes > 2 * conv12_fused_blocks(nframes);
-    const Kernel kernel = kernels[early ? 8 : 4 * (rb != 0) + 2 * (y1 != nullptr) + (table != nullptr)];
+    const Kernel kernel = kernels[(y1 ? (rb ? 2 : 0) : 4) + (table != nullptr)];
     ga3c::launch(kernel, dim3(conv12_fused_blocks(nframes)), dim3(512), C12_LDS_BYTES, s, x, table, frag, b1, b2, y1, y2, nframes, scale, rb);
     return hipGetLastError();
 }

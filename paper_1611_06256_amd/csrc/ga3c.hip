@@ -27,6 +27,7 @@
 #include "fc_grads.hpp"
 #include "conv2_bf16x6.hpp"
 #include "conv12_fused.hpp"
+#include "conv12_f16.hpp"
 #include "conv_fwd_bf16x6.hpp"
 #include "conv123_f16.hpp"
 #include "conv_dgrad_bf16x6.hpp"
@@ -181,6 +182,7 @@ struct ga3c_ctx {
     // small net: conv1/conv2 filters of each parameter copy as split MFMA fragments (nullptr for other nets), forward
     // kernel's first, then (at CFRAG_FWD_VECS) the input-gradient kernel's; refreshed by whoever writes the copy
     u32x4 *cfrag[2];
+    u32x4 *hfrag[2];              // the same filters for predictions at fp32 accuracy (conv12_f16.hpp), kept current likewise
     bool cfrag_dgrad;             // the buffers hold the second part too (a context that can train)
     // larger net: the filters of conv2 and conv3 of each parameter copy as ready-made fragments for the forward and the
     // input-gradient kernels (LFRAG_* give the parts); rebuilt by whoever writes the copy
@@ -1767,12 +1769,11 @@ template <int VARIANT, int VPT>
 __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, float *theta_out, float *__restrict__ g,
                                                       const float *__restrict__ grad, size_t n,
                                                       const float *__restrict__ scale_dev, float scale_host, float lr,
-                                                      float alpha, float eps, u32x4 *__restrict__ frag, unsigned w1_off,
-                                                      unsigned w2_off, int frag_rb, const ga3c::FcPlanes fcw,
-                                                      const RmsClip clipargs) {
-    // frag (optional): split MFMA fragments of the small net's conv filters, kept current with theta_out;
-    // w1_off / w2_off: where the two filter tensors start in the flat buffer (multiples of 4).  fcw (optional): the fc weights
-    // as operands of the forward product, likewise
+                                                      float alpha, float eps, u32x4 *__restrict__ frag, u32x4 *__restrict__ hfrag,
+                                                      int frag_rb, const ga3c::FcPlanes fcw, const RmsClip clipargs) {
+    // frag (optional): split MFMA fragments of the small net's conv filters, kept current with theta_out; hfrag (optional, VPT == 1): the
+    // same for predictions (conv12_f16.hpp).  fcw (optional): the fc weights as operands of the forward product, likewise
+    constexpr unsigned W1 = 0, W2 = 16u * 256u + 16u;      // where the filter tensors start in the flat buffer then
     float s = scale_dev ? scale_dev[0] : scale_host;
     if (clipargs.normpart) {
         __shared__ float sh[4][4];
@@ -1816,11 +1817,21 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, flo
     float4 *o4 = (float4 *)theta_out;
     float4 *g4 = (float4 *)g;
     const float4 *d4 = (const float4 *)grad;
+    // hfrag takes filters whole, from the 64 lanes of a wavefront: the second tensor begins four vectors (the first one's biases) behind a
+    // multiple of 64, and these four come behind it
+    auto vector_of = [&](const size_t i) {
+        if (VPT != 1 || !hfrag) return i;
+        constexpr size_t A = W1 + 16 * 64, B = A + 32 * 64;
+        return i < A || i >= B + 4 ? i : i < B ? i + 4 : i - (B - A);
+    };
+    auto store_filter = [&](const size_t i, const float4 t) {
+        if (VPT == 1 && hfrag && i < 48 * 64) conv12_f16_store_filter(hfrag, __builtin_amdgcn_readfirstlane((int)i >> 6), threadIdx.x & 63, t);
+    };
     // a block works on tiles of 256 * VPT consecutive vectors (16 KB of each array for VPT = 4): thread t takes vectors
     // t, t + 256, ... of the tile, all requested before the first is used
     const size_t ntile = n4 / (256 * VPT);
     for (size_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-        const size_t i = tile * (256 * VPT) + threadIdx.x;
+        const size_t first = tile * (256 * VPT) + threadIdx.x, i = vector_of(first);
         float4 t[VPT], gg[VPT], d[VPT];
 #pragma unroll
         for (int j = 0; j < VPT; ++j) {
@@ -1834,12 +1845,13 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, flo
             if (VARIANT & 2) { nt_store(gg[j], g4 + i + 256 * j); nt_store(t[j], o4 + i + 256 * j); }
             else { g4[i + 256 * j] = gg[j]; o4[i + 256 * j] = t[j]; }
             if (frag) {
-                const unsigned r1 = (unsigned)(4 * (i + 256 * j)) - w1_off, r2 = (unsigned)(4 * (i + 256 * j)) - w2_off;
+                const unsigned r1 = (unsigned)(4 * (i + 256 * j)) - W1, r2 = (unsigned)(4 * (i + 256 * j)) - W2;
                 if (r1 < 16u * 256u) conv12_store_fragment4(frag, 0, (int)r1, t[j], frag_rb);
                 else if (r2 < 32u * 256u) {
                     conv12_store_fragment4(frag, 1, (int)r2, t[j], frag_rb);
                     conv_dgrad_store_fragment4<SpecS2>(frag + CFRAG_FWD_VECS, (int)r2, t[j]);
                 }
+                store_filter(first + 256 * j, t[j]);
             }
             if (fcw.w) {
                 const unsigned r = (unsigned)(i + 256 * j) - fcw.first;
@@ -1847,17 +1859,19 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(const float *theta_in, flo
             }
         }
     }
-    for (size_t i = ntile * (256 * VPT) + (size_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
+    for (size_t at = ntile * (256 * VPT) + (size_t)blockIdx.x * 256 + threadIdx.x; at < n4; at += stride) {
+        const size_t i = vector_of(at);
         float4 t = t4[i], gg = g4[i];
         rmsprop4(t, gg, d4[i], s, lr, alpha, oma, eps);
         g4[i] = gg; o4[i] = t;
         if (frag) {
-            const unsigned r1 = (unsigned)(4 * i) - w1_off, r2 = (unsigned)(4 * i) - w2_off;
+            const unsigned r1 = (unsigned)(4 * i) - W1, r2 = (unsigned)(4 * i) - W2;
             if (r1 < 16u * 256u) conv12_store_fragment4(frag, 0, (int)r1, t, frag_rb);
             else if (r2 < 32u * 256u) {
                 conv12_store_fragment4(frag, 1, (int)r2, t, frag_rb);
                 conv_dgrad_store_fragment4<SpecS2>(frag + CFRAG_FWD_VECS, (int)r2, t);
             }
+            store_filter(at, t);
         }
         if (fcw.w) {
             const unsigned r = (unsigned)i - fcw.first;
@@ -2112,6 +2126,7 @@ int refresh_derived(ga3c_ctx *c, int i, hipStream_t s, bool fc = true, ga3c::Sto
         HIP_TRY(launch_conv12_filter_fragments(c->theta2[i] + c->off[0], c->theta2[i] + c->off[2], c->cfrag[i], s, c->rb));
         if (c->cfrag_dgrad)
             HIP_TRY(launch_conv_dgrad_filter_fragments<SpecS2>(c->theta2[i] + c->off[2], c->cfrag[i] + CFRAG_FWD_VECS, s));
+        if (c->hfrag[i]) HIP_TRY(launch_conv12_f16_filters(c->theta2[i] + c->off[0], c->theta2[i] + c->off[2], c->hfrag[i], s));
     }
     if (c->lfrag[i]) {
         const float *th = c->theta2[i];
@@ -2188,13 +2203,17 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         HIP_TRY(hipGetLastError());
         return GA3C_OK;
     }
-    if (c->fast && c->cfrag[which] && is_aligned16(frames)) {
+    if (c->fast && (keep_zv || c->rb ? c->cfrag[which] : c->hfrag[which]) && is_aligned16(frames)) {
         // small net: both convolution layers in one kernel; layer-1 activations go to HBM only when training
         const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1];
         STAGE("conv12_fwd", 2.0 * B * (g0.OHW * g0.OC * g0.K + g1.OHW * g1.OC * g1.K),
               (double)B * (g0.CHW + (keep_zv ? 4.0 * g0.OC * g0.OHW : 0.0) + 4.0 * g1.OC * g1.OHW));
-        HIP_TRY(launch_conv12_fused_fwd(frames, table, c->cfrag[which], th + c->off[1], th + c->off[3],
-                                        keep_zv ? w.act[0] : nullptr, w.act[1], B, 1.f / 255.f, s, c->rb));
+        // predictions at fp32 accuracy: two float16 terms; updates keep the rounding of their sums (conv123_f16.hpp says why)
+        if (!keep_zv && !c->rb)
+            HIP_TRY(launch_conv12_f16(frames, table, c->hfrag[which], th + c->off[1], th + c->off[3], w.act[1], B, 1.f / 255.f, s));
+        else
+            HIP_TRY(launch_conv12_fused_fwd(frames, table, c->cfrag[which], th + c->off[1], th + c->off[3],
+                                            keep_zv ? w.act[0] : nullptr, w.act[1], B, 1.f / 255.f, s, c->rb));
         first = 2;
     }
     if (c->fast && c->conv123 && !keep_zv && is_aligned16(frames)) {
@@ -2521,6 +2540,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         c->cfrag_dgrad = true;
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
             guard(dmalloc((void **)&c->cfrag[i], sizeof(u32x4) * CFRAG_VECS));
+            if (rc == GA3C_OK && !c->rb && max_predict_batch > 0) guard(dmalloc((void **)&c->hfrag[i], sizeof(u32x4) * Conv12F16::VECS));
             if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
         }
         if (rc == GA3C_OK) guard(dmalloc((void **)&c->ticket, sizeof(int) * SP_MAX_FRAMES * SP_TICKET_PITCH));
@@ -2628,7 +2648,7 @@ extern "C" int ga3c_destroy(ga3c_ctx *c) {
         if (m->ev) (void)hipEventDestroy(m->ev);
     (void)hipFree(c->theta2[0]); (void)hipFree(c->theta2[1]);
     (void)hipFree(c->g); (void)hipFree(c->grad);
-    (void)hipFree(c->cfrag[0]); (void)hipFree(c->cfrag[1]); (void)hipFree(c->ticket); (void)hipFree(c->lfrag[0]); (void)hipFree(c->lfrag[1]);
+    (void)hipFree(c->cfrag[0]); (void)hipFree(c->cfrag[1]); (void)hipFree(c->hfrag[0]); (void)hipFree(c->hfrag[1]); (void)hipFree(c->ticket); (void)hipFree(c->lfrag[0]); (void)hipFree(c->lfrag[1]);
     (void)hipFree(c->bfrag[0]); (void)hipFree(c->bfrag[1]); (void)hipFree(c->fcw[0].w);      // both copies' in one piece
     free_work(c->pred); free_work(c->train);
     (void)hipFree(c->dhp.w); (void)hipFree(c->dh); (void)hipFree(c->dzv); (void)hipFree(c->R);
@@ -3041,7 +3061,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
     const bool fragments = c->lfrag[to] || c->bfrag[to];      // they follow the new parameters, in launches of their own
     ga3c::StopEvent stop = stop_for(c->ready[to], s);
     ga3c::launch_stop(fragments ? nullptr : &stop, (rmsprop_kernel<0, 1>), dim3(rb), dim3(256), 0, s, th, c->theta2[to], c->g, c->grad, c->P,
-                      (const float *)nullptr, 1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[to], (unsigned)c->off[0], (unsigned)c->off[2], c->rb,
+                      (const float *)nullptr, 1.f, hp->lr, hp->rms_decay, hp->rms_eps, c->cfrag[to], c->hfrag[to], c->rb,
                       c->fcw[to], ca);
     HIP_TRY(hipGetLastError());
     if (fragments) TRY(refresh_derived(c, to, s, false, &stop));
@@ -3131,7 +3151,7 @@ extern "C" int ga3c_rmsprop_flat(float *theta, float *g, const float *grad, size
     memset(&none, 0, sizeof(none));
 #define GA3C_RMS_LAUNCH(V)                                                                                               \
     ga3c::launch((rmsprop_kernel<V, 4>), dim3(rb), dim3(256), 0, (hipStream_t)stream, theta, theta, g, grad, n,         \
-                       (const float *)nullptr, scale, lr, rms_decay, rms_eps, (u32x4 *)nullptr, 0u, 0u, 0, FcPlanes(), none)
+                       (const float *)nullptr, scale, lr, rms_decay, rms_eps, (u32x4 *)nullptr, (u32x4 *)nullptr, 0, FcPlanes(), none)
     if (stream_past_caches) GA3C_RMS_LAUNCH(3); else GA3C_RMS_LAUNCH(0);
 #undef GA3C_RMS_LAUNCH
     HIP_TRY(hipGetLastError());
@@ -3196,7 +3216,8 @@ constexpr int STATIC_MAX_FRAMES = GA3C_STATIC_MAX_FRAMES;
 constexpr int STATIC_MAX_SPLITS = 40;                                    // k-chunks of the fc product: 2592 / 64
 constexpr size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 constexpr size_t ST_FRAG_OFF = 0;
-constexpr size_t ST_TICKET_OFF = ST_FRAG_OFF + up256(sizeof(u32x4) * 3 * C12_FRAG_SET);
+constexpr size_t ST_HFRAG_OFF = ST_FRAG_OFF + up256(sizeof(u32x4) * 3 * C12_FRAG_SET);
+constexpr size_t ST_TICKET_OFF = ST_HFRAG_OFF + up256(sizeof(u32x4) * Conv12F16::VECS);
 constexpr size_t ST_H_OFF = ST_TICKET_OFF + up256(sizeof(int) * SP_MAX_FRAMES * SP_TICKET_PITCH);
 constexpr size_t ST_Y2_OFF = ST_H_OFF + up256(sizeof(float) * STATIC_MAX_FRAMES * SP_FC);
 constexpr size_t ST_WS_OFF = ST_Y2_OFF + up256(sizeof(float) * STATIC_MAX_FRAMES * SP_FLAT);
@@ -3266,7 +3287,10 @@ extern "C" int ga3c_predict_static(int n_actions, int math, const float *theta, 
     c.pred.ws = (float *)(base + ST_WS_OFF);
     c.pred.ws_floats = ST_WS_FLOATS;
     hipStream_t s = (hipStream_t)stream;
-    // the filters as split MFMA fragments, from the caller's parameters (a context does this when they change)
-    TRY(refresh_derived(&c, 0, s));
+    // the filters as split MFMA fragments, from the caller's parameters (a context does this when they change): those that this call reads
+    if (B > SP_MAX_FRAMES && !math) {
+        c.hfrag[0] = (u32x4 *)(base + ST_HFRAG_OFF);
+        HIP_TRY(launch_conv12_f16_filters(theta + c.off[0], theta + c.off[2], c.hfrag[0], s));
+    } else TRY(refresh_derived(&c, 0, s));
     return forward(&c, 0, c.pred, frames, nullptr, B, false, logits, values, probs, uniforms, actions, s);
 }

@@ -41,10 +41,41 @@ __device__ __forceinline__ void split2_pair(const float x, const float y, const 
     lo = l;
 }
 
-// Byte t of a, then of b, as float16: a byte's bits are those of the subnormal number b 2^-24, which the matrix instruction takes as it is.
-__device__ __forceinline__ uint32_t f16_of_bytes(const uint32_t a, const uint32_t b, int t) {
-    return __builtin_amdgcn_perm(b, a, 0x0c040c00u + 0x00010001u * t);
+// The largest of a wavefront's values (none is negative).
+__device__ __forceinline__ float f16_wave_most(float m) {
+    m = fmaxf(m, dpp_row_f32<0xB1>(m)); m = fmaxf(m, dpp_row_f32<0x4E>(m));
+    m = fmaxf(m, dpp_row_f32<0x141>(m)); m = fmaxf(m, dpp_row_f32<0x140>(m));
+    const int u = __float_as_int(m);
+    return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 0)), __int_as_float(__builtin_amdgcn_readlane(u, 16))),
+                 fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 32)), __int_as_float(__builtin_amdgcn_readlane(u, 48))));
+}
+// The scale of a map whose largest values the eight wavefronts of a block have left in LDS.
+__device__ __forceinline__ void f16_scale_of(const float (&m)[8], float &scale, float &inverse) {
+    const float a = fmaxf(fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])), fmaxf(fmaxf(m[4], m[5]), fmaxf(m[6], m[7])));
+    f16_scale(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(a))), scale, inverse);
+}
+
+// Eight bytes as float16: a byte's bits are those of the subnormal number b 2^-24, which the matrix instruction takes as it is.
+__device__ __forceinline__ f16x8 f16_of_bytes(const uint32_t lo, const uint32_t hi) {
+    F16x8Bits v;
+    v.u = u32x4{__builtin_amdgcn_perm(0u, lo, 0x0c010c00u), __builtin_amdgcn_perm(0u, lo, 0x0c030c02u), __builtin_amdgcn_perm(0u, hi, 0x0c010c00u),
+                __builtin_amdgcn_perm(0u, hi, 0x0c030c02u)};
+    return v.v;
 }
 constexpr float F16_BYTE_UNIT = 16777216.f;       // what products with such numbers are multiplied by
+
+// A frame of 4 x 84 x 84 bytes in LDS, as it lies in memory, where it comes without passing through registers; NW wavefronts, 16
+// bytes per lane and load.  The last load's lanes behind the frame's end fill the place up with its last bytes.
+constexpr int F16_FRAME = 28 * 1024;
+template <int NW>
+__device__ __forceinline__ void f16_frame_to_lds(const uint8_t *src, const uint32_t lds, const int wave, const int lane) {
+    constexpr int LAST = 4 * 84 * 84 / 1024, REST = (4 * 84 * 84 % 1024) / 16;
+#pragma unroll
+    for (int i = 0; i < (LAST + NW) / NW; ++i) {
+        const int p = wave + NW * i;
+        if (p < LAST) load_vec_to_lds(src + 1024 * p, 16u * lane, lds + 1024 * p);
+        else if (p == LAST) load_vec_to_lds(src + 1024 * p, 16u * min(lane, REST - 1), lds + 1024 * p);
+    }
+}
 
 }  // namespace ga3c

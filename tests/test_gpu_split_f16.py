@@ -37,13 +37,17 @@ def scaled(net, theta, layer, power):
 
 
 def network(G, which, A):
+    if which == "small":
+        return G.SMALL_NET(A)
     return G.LARGE_NET(A) if which == "large" else G.NetDesc(conv=((32, 8, int(which[-1])), (32, 4, 2), (64, 4, 2)), fc_units=256, n_actions=A)
 
 
 # one, two and three frames a block; activations beyond float16's largest number and below its smallest; a filter of zeros
-@pytest.mark.parametrize("which", ["large", "paper4", "paper3"])
-@pytest.mark.parametrize("B,layer,power", [(1, 1, 0), (256, 1, 0), (257, 1, 0), (513, 1, 0), (3, 1, 30), (3, 1, -30), (3, 2, 30), (3, 2, -30), (3, 3, 30), (3, 3, -40)])
-def test_predictions_with_three_convolutions_in_one_kernel(G, which, B, layer, power):
+@pytest.mark.parametrize("which,B,layer,power",
+                         [(which, *c) for which in ("large", "paper4", "paper3") for c in
+                          [(1, 1, 0), (256, 1, 0), (257, 1, 0), (513, 1, 0), (3, 1, 30), (3, 1, -30), (3, 2, 30), (3, 2, -30), (3, 3, 30), (3, 3, -40)]] +
+                         [("small", *c) for c in [(65, 1, 0), (256, 1, 0), (257, 1, 0), (515, 1, 0), (1025, 1, 0), (67, 1, 30), (67, 1, -30), (67, 2, 30), (67, 2, -40)]])
+def test_predictions_with_the_convolutions_in_one_kernel(G, which, B, layer, power):
     import torch
     net, onet, theta = P.make(G, network(G, which, 6), B, 0, 9100 + B)
     theta = scaled(net, theta, layer, power)
@@ -51,9 +55,39 @@ def test_predictions_with_three_convolutions_in_one_kernel(G, which, B, layer, p
     theta[at:at + int(np.prod(shape[1:]))] = 0
     net.params_set(torch.from_numpy(theta).cuda(), 0)
     frames = synth.rectangle_frames(9101 + B, B)
-    if B == 3:
+    if power:
         frames[0] = 0
     lg, vl, _, _ = P.run_predict(G, net, frames)
     ref = orc.forward(onet, theta, frames)
     assert P.rel_err(lg, ref["logits"]) <= TOL and P.rel_err(vl, ref["values"]) <= TOL
     net.close()
+
+
+# The small net's filters for predictions follow every update, a filter per wavefront of the kernel that updates the parameters: the
+# same bits as in a context that was given those parameters.  The second network ends soon behind the filters (3113 vectors of four).
+@pytest.mark.parametrize("conv,F", [(((16, 8, 4), (32, 4, 2)), 256), (((16, 8, 4), (32, 4, 2), (1, 1, 1)), 1)])
+def test_predictions_read_the_filters_that_an_update_leaves(G, conv, F):
+    import torch
+    A, B, N = 3, 70, 6
+    desc = G.NetDesc(conv=conv, fc_units=F, n_actions=A)
+    net, other = G.Ga3c(desc, B, 5 * N), G.Ga3c(desc, B, 0)
+    net.params_init(9201)
+    frames = torch.from_numpy(synth.uniform_frames(9202, (B, 4, 84, 84))).cuda()
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9203, N, 5, A).items()}
+    u = torch.from_numpy(synth.uniforms(9204, B)).cuda()
+
+    def told(n):
+        o = dict(logits=torch.full((B, A), float("nan"), device="cuda"), values=torch.full((B,), float("nan"), device="cuda"))
+        n.predict(frames, uniforms=u, **o)
+        return o
+
+    before = told(net)
+    for step in range(2):
+        net.train_step(frames[:5 * N].view(N, 5, 4, 84, 84), tr["actions"], tr["rewards"], tr["dones"], None, G.HParams(lr=0.05))
+        theta = net.params_get(0).clone()
+        other.params_set(theta, 0)
+        got, want = told(net), told(other)
+        torch.cuda.synchronize()
+        for k in want:
+            assert torch.isfinite(want[k]).all() and not torch.equal(want[k], before[k]) and torch.equal(got[k], want[k]), (step, k)
+    net.close(); other.close()
