@@ -5,7 +5,7 @@
 //
 // Operands are two float16 terms each (split_f16.hpp), bytes one.  Filters come scaled and split, in the order in which the
 // lanes take them, from a buffer per parameter copy.  Layer 1's map is scaled by the largest value that it can have with these filters
-// (sum of a filter's magnitudes and its bias; a byte is 1 at most), layer 2's by its own largest value, which the eight wavefronts
+// (sum of a filter's positive weights and its bias; a byte is 1 at most), layer 2's by its own largest value, which the eight wavefronts
 // find between the layer's products and its way to LDS.
 //
 //   layer 1  both filter tiles from one read of a pixel tile's bytes: wavefront w has tiles w, w + 8, ..; of the tiles that are left
@@ -34,6 +34,7 @@
 #include <type_traits>
 
 #include "conv_fwd_bf16x6.hpp"
+#include "conv_plain.hpp"
 #include "split_f16.hpp"
 
 namespace ga3c {
@@ -70,8 +71,8 @@ struct Conv123Net {
     static constexpr int NT2 = (SP2::NPIX + 15) / 16, NT3 = (SP3::NPIX + 15) / 16, OT2 = SP2::OC / 16;
     static_assert(SP2::H == OW1 && SP2::W == OW1 && SP2::C == 32 && SP2::K == 512 && SP2::S == 2 && (SP2::OC == 32 || SP2::OC == 64), "layer 2: 4x4, stride 2");
     static_assert(SP3::H == SP2::OH && SP3::C == SP2::OC && SP3::K % 32 == 0 && SP3::OC == 64, "layer 3");
-    // Filters: [filter tile][k-block][term][lane] vectors of eight float16 each; then the reciprocals of the filters' scales, and sums of the
-    // magnitudes of layer 1's.
+    // Filters: [filter tile][k-block][term][lane] vectors of eight float16 each; then the reciprocals of the filters' scales (negative:
+    // F16_WIDE), and sums of the positive weights of layer 1's.
     static constexpr int KB1 = 8, KB2 = 16, KB3 = SP3::K / 32, CG3 = SP3::C / 32;
     static constexpr int F1 = 0, F2 = F1 + 2 * KB1 * 128, F3 = F2 + OT2 * KB2 * 128, INV = F3 + 4 * KB3 * 128;
     static constexpr int FILTERS = 32 + SP2::OC + 64, SUM = INV + FILTERS / 4, VECS = SUM + 32 / 4;
@@ -79,6 +80,7 @@ struct Conv123Net {
     static constexpr int B1 = 2 * KB1 / 4, B2 = B1 + OT2 * KB2 / 4, PER3 = (KB3 + 3) / 4, BLOCKS = B2 + 4 * PER3;
     static constexpr int Y = 2 * F16_FRAME, LDS = Y + 2 * (M2::TERM > M3::TERM ? M2::TERM : M3::TERM);
     static_assert(LDS + 2048 <= 160 * 1024, "LDS");
+    static_assert((32 * NPIX1 + SP2::OC * SP2::NPIX) * 4 <= LDS, "the maps of plain sums");
 };
 
 // Block b of N::BLOCKS, 256 threads.  w1, w2, w3: the filter tensors, 16-byte aligned.
@@ -114,15 +116,21 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
     m = fmaxf(m, dpp_row_f32<0x141>(m)); m = fmaxf(m, dpp_row_f32<0x140>(m));
     if (layer == 1) {                                      // K = 256: four vectors a thread
 #pragma unroll
-        for (int i = 0; i < 4; ++i) sum += (fabsf(all[i].x) + fabsf(all[i].y)) + (fabsf(all[i].z) + fabsf(all[i].w));
+        for (int i = 0; i < 4; ++i) sum += (fmaxf(all[i].x, 0.f) + fmaxf(all[i].y, 0.f)) + (fmaxf(all[i].z, 0.f) + fmaxf(all[i].w, 0.f));
         sum += dpp_row_f32<0xB1>(sum); sum += dpp_row_f32<0x4E>(sum); sum += dpp_row_f32<0x141>(sum); sum += dpp_row_f32<0x140>(sum);
         if (kb0 == 0 && (tid & 15) == 0) ((float *)(frag + N::SUM))[ot * 16 + (tid >> 4)] = sum;
     }
+    float small = 0.f;
+#pragma unroll
+    for (int i = 0; i < KMOST / 64; ++i)
+        if (4 * (tid & 15) + 64 * i < K)
+            small += (float)(f16_is_small(all[i].x, m) + f16_is_small(all[i].y, m) + f16_is_small(all[i].z, m) + f16_is_small(all[i].w, m));
+    small += dpp_row_f32<0xB1>(small); small += dpp_row_f32<0x4E>(small); small += dpp_row_f32<0x141>(small); small += dpp_row_f32<0x140>(small);
     if ((tid & 15) == 0) {
         float s, inv;
         f16_scale(m, s, inv);
         scales[tid >> 4] = s;
-        if (kb0 == 0) ((float *)(frag + N::INV))[first + ot * 16 + (tid >> 4)] = inv;
+        if (kb0 == 0) ((float *)(frag + N::INV))[first + ot * 16 + (tid >> 4)] = small > (float)F16_WIDE || !(m < __builtin_inff()) ? -inv : inv;
     }
     __syncthreads();
     if (kb >= KB) return;
@@ -139,12 +147,14 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
     dst[64] = lo;
 }
 
-// x: [n][4][84][84] bytes, or table: where each frame lies; frag: N's filters; b1 [32], b2, b3: biases; y: [n][64][layer 3's pixels].
+// x: [n][4][84][84] bytes, or table: where each frame lies; frag: N's filters; b1 [32], b2, b3: biases; y: [n][64][layer 3's pixels]; f1, f2,
+// f3: the filter tensors, for plain sums.
 template <class N, bool TABLE>
 __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table,
                                                              const u32x4 *__restrict__ frag, const float *__restrict__ b1,
-                                                             const float *__restrict__ b2, const float *__restrict__ b3, float *__restrict__ y,
-                                                             int nframes, float scale) {
+                                                             const float *__restrict__ b2, const float *__restrict__ b3, float *y, int nframes,
+                                                             float scale, const float *__restrict__ f1, const float *__restrict__ f2,
+                                                             const float *__restrict__ f3) {
     typedef typename N::SP2 SP2;
     typedef typename N::SP3 SP3;
     typedef typename N::M2 M2;
@@ -154,6 +164,7 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
     constexpr int T2 = (N::NT2 + PG2 - 1) / PG2, T3 = (N::NT3 + 1) / 2;          // the last of some wavefronts is not there
     static_assert(2 * REST1 <= 8, "half a tile each");
     extern __shared__ __attribute__((aligned(16))) unsigned char c123_smem[];
+    __shared__ int wide[3];                                // layers that need plain sums
     __shared__ float most[8];                              // largest values of layer 2, by wavefront
     __shared__ __attribute__((aligned(16))) float consts[2][N::FILTERS];       // by filter: reciprocal of its scale, bias
 
@@ -191,11 +202,15 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
     };
     float bound = ((const float *)(frag + N::SUM))[lane & 31];
     const float bb = b1[lane & 31];
+    if (wave < 3) {
+        const float v = ((const float *)(frag + N::INV))[wave == 0 ? lane & 31 : wave == 1 ? 32 + lane % SP2::OC : 32 + SP2::OC + lane];
+        wide[wave] = wave < 2 ? f16_wide_layer(v) : __any(v < 0.f);
+    }
     if (tid < N::FILTERS) {
-        consts[0][tid] = ((const float *)(frag + N::INV))[tid] * (tid < 32 ? scale * F16_BYTE_UNIT : 1.f);
+        consts[0][tid] = fabsf(((const float *)(frag + N::INV))[tid]) * (tid < 32 ? scale * F16_BYTE_UNIT : 1.f);
         consts[1][tid] = tid < 32 ? b1[tid] : tid < 32 + SP2::OC ? b2[tid - 32] : b3[tid - 32 - SP2::OC];
     }
-    bound = 1.0001f * (255.f * scale * bound + fabsf(bb));
+    bound = 1.0001f * (255.f * scale * bound + fmaxf(bb, 0.f));
     float s1, si1;
     f16_scale(f16_wave_most(bound), s1, si1);
     s1 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s1)));
@@ -410,11 +425,23 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
         }
     }
     store(f - grid);
+    if (wide[0] | wide[1] | wide[2]) {                     // my frames once more
+        __syncthreads();
+        float *y1 = (float *)c123_smem, *y2 = y1 + 32 * N::NPIX1;
+        for (f = blockIdx.x; f < nframes; f += grid) {
+            plain_conv_layer(TABLE ? table[f] : x + (size_t)f * CHW, scale, f1, b1, y1, 4, 84, 84, 32, 8, N::S1, tid, 512);
+            __syncthreads();
+            plain_conv_layer(y1, 1.f, f2, b2, y2, 32, SP2::H, SP2::W, SP2::OC, 4, 2, tid, 512);
+            __syncthreads();
+            plain_conv_layer(y2, 1.f, f3, b3, y + (size_t)f * SP3::OC * SP3::NPIX, SP3::C, SP3::H, SP3::W, SP3::OC, SP3::KS, SP3::S, tid, 512);
+            __syncthreads();
+        }
+    }
 }
 
 template <class N, bool TABLE>
 inline hipError_t launch_conv123_f16(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2,
-                                     const float *b3, float *y, int nframes, float scale, hipStream_t s) {
+                                     const float *b3, float *y, int nframes, float scale, const float *f1, const float *f2, const float *f3, hipStream_t s) {
     if (nframes <= 0) return hipSuccess;
     static bool attr_set = false;
     if (!attr_set) {
@@ -422,7 +449,8 @@ inline hipError_t launch_conv123_f16(const uint8_t *x, const uint8_t *const *tab
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    ga3c::launch((conv123_f16_kernel<N, TABLE>), dim3(nframes < 256 ? nframes : 256), dim3(512), N::LDS, s, x, table, frag, b1, b2, b3, y, nframes, scale);
+    ga3c::launch((conv123_f16_kernel<N, TABLE>), dim3(nframes < 256 ? nframes : 256), dim3(512), N::LDS, s, x, table, frag, b1, b2, b3, y, nframes, scale,
+                 f1, f2, f3);
     return hipGetLastError();
 }
 

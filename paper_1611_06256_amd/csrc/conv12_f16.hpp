@@ -4,7 +4,7 @@
 // Operands are two float16 terms each (split_f16.hpp), bytes one, as in conv123_f16.hpp; sums of small and of large terms have
 // accumulators of their own.  A block takes a frame at a time, first layer 1, then layer 2, with its filters of both in registers for
 // the whole launch.  Frames come to LDS as the bytes they are, the next one while this one is worked on.  Layer 1's map is scaled by
-// the largest value that it can have with these filters (sum of a filter's magnitudes and its bias; a byte is 1 at most), so nobody
+// the largest value that it can have with these filters (sum of a filter's positive weights and its bias; a byte is 1 at most), so nobody
 // has to look for the one that it has: some bits of the scale are lost, of forty to spare.
 //
 // The map: [term][pixel][16 channels], even and odd columns of a row apart; a k-block of layer 2 is two neighbouring taps of a
@@ -23,6 +23,7 @@
 #include <stdint.h>
 
 #include "conv1_bf16x3.hpp"
+#include "conv_plain.hpp"
 #include "gemm_mfma.hpp"
 #include "split_f16.hpp"
 
@@ -33,24 +34,28 @@ struct Conv12F16 {
     static constexpr int MAP = 2 * F16_FRAME, LDS = MAP + 2 * TERM;
     __host__ __device__ static constexpr int pixel(int row, int col) { return row * ROW + (col & 1) * ODD + (col >> 1) * PIT; }
     // Filters of a parameter copy: layer 1 [k-block][term][lane], layer 2 [filter tile][k-block][term][lane], vectors of eight float16;
-    // then floats by filter: reciprocals of the scales (48), sums of layer 1's magnitudes (16).
+    // then floats by filter: reciprocals of the scales (48; negative: F16_WIDE), sums of layer 1's positive weights (16).
     static constexpr int F1 = 0, F2 = F1 + 8 * 128, INV = F2 + 2 * 8 * 128, SUM = INV + 12, VECS = SUM + 4;
 };
 
 // Filter q of both layers (0 .. 15, then 16 .. 47), whose 256 weights a wavefront has, four per lane.
 __device__ __forceinline__ void conv12_f16_store_filter(u32x4 *__restrict__ frag, const int q, const int lane, const float4 v) {
     typedef Conv12F16 G;
+    const float most = f16_wave_most(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
     float s, si;
-    f16_scale(f16_wave_most(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w)))), s, si);
+    f16_scale(most, s, si);
+    const int small = __popcll(__ballot(f16_is_small(v.x, most))) + __popcll(__ballot(f16_is_small(v.y, most))) +
+                      __popcll(__ballot(f16_is_small(v.z, most))) + __popcll(__ballot(f16_is_small(v.w, most)));
+    const float stored = small > F16_WIDE || !(most < __builtin_inff()) ? -si : si;
     uint32_t h[2], l[2];
     split2_pair(v.x, v.y, s, h[0], l[0]);
     split2_pair(v.z, v.w, s, h[1], l[1]);
-    if (lane == 0) ((float *)(frag + G::INV))[q] = si;
+    if (lane == 0) ((float *)(frag + G::INV))[q] = stored;
     if (q < 16) {                                          // plane lane / 16, row lane / 2 % 8, columns 4 (lane % 2) ..
         uint2 *dst = (uint2 *)(frag + G::F1 + (lane >> 3) * 128 + (lane >> 1 & 3) * 16 + q) + (lane & 1);
         dst[0] = uint2{h[0], h[1]};
         dst[128] = uint2{l[0], l[1]};
-        float sum = (fabsf(v.x) + fabsf(v.y)) + (fabsf(v.z) + fabsf(v.w));
+        float sum = (fmaxf(v.x, 0.f) + fmaxf(v.y, 0.f)) + (fmaxf(v.z, 0.f) + fmaxf(v.w, 0.f));
         sum += dpp_row_f32<0xB1>(sum); sum += dpp_row_f32<0x4E>(sum); sum += dpp_row_f32<0x141>(sum); sum += dpp_row_f32<0x140>(sum);
         const int u = __float_as_int(sum);
         if (lane == 0)
@@ -77,16 +82,18 @@ inline hipError_t launch_conv12_f16_filters(const float *w1, const float *w2, u3
     return hipGetLastError();
 }
 
-// x: [n][4][84][84] bytes, or table: where each frame lies; frag: the filters; y2: [n][32][81].  Frames blockIdx.x, + gridDim.x, ..
+// x: [n][4][84][84] bytes, or table: where each frame lies; frag: the filters; y2: [n][32][81]; w1, w2: the filter tensors, for plain sums.  Frames blockIdx.x, + gridDim.x, ..
 // Wavefront w has pixel tiles w, w + 8, w + 16 of layer 1, the 25th goes to another one with every frame; of layer 2 filter tile w % 2 and
 // pixel tile w / 2, the first four also w / 2 + 4: three for every SIMD.
 template <bool TABLE>
 __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__restrict__ x, const uint8_t *const *__restrict__ table,
                                                             const u32x4 *__restrict__ frag, const float *__restrict__ b1,
-                                                            const float *__restrict__ b2, float *__restrict__ y2, int nframes, float scale) {
+                                                            const float *__restrict__ b2, float *y2, int nframes, float scale,
+                                                            const float *__restrict__ w1, const float *__restrict__ w2) {
     typedef Conv12F16 G;
     constexpr int CHW = 4 * 84 * 84, NPIX2 = 81, NW = 8, T1 = 3, PG = 4, T2 = 2;
     extern __shared__ __attribute__((aligned(16))) unsigned char c12h_smem[];        // two frames, a map
+    __shared__ int wide;                                                             // filters need plain sums
     __shared__ __attribute__((aligned(16))) float consts[2][48];                     // by filter: reciprocal of its scale, bias
 
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, g = lane >> 4;
@@ -109,8 +116,9 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
     const float *inv = (const float *)(frag + G::INV);
     float bound = ((const float *)(frag + G::SUM))[l16];
     const float bb = b1[l16];
+    if (wave == 0) wide = f16_wide_layer(inv[l16]) || __any(inv[min(lane, 47)] < 0.f);
     if (tid < 48) {
-        consts[0][tid] = inv[tid] * (tid < 16 ? scale * F16_BYTE_UNIT : 1.f);
+        consts[0][tid] = fabsf(inv[tid]) * (tid < 16 ? scale * F16_BYTE_UNIT : 1.f);
         consts[1][tid] = tid < 16 ? b1[tid] : b2[tid - 16];
     }
 #pragma unroll
@@ -118,7 +126,7 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
 #pragma unroll
         for (int t = 0; t < 2; ++t) q2[kb][t].u = (frag + G::F2 + ((ot * 8 + kb) * 2 + t) * 64)[lane];
     // layer 1's values are 255 scale = 1 times this at most
-    bound = 1.0001f * (255.f * scale * bound + fabsf(bb));
+    bound = 1.0001f * (255.f * scale * bound + fmaxf(bb, 0.f));
     float s, si;
     f16_scale(f16_wave_most(bound), s, si);
     s = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s)));
@@ -248,10 +256,20 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
         else tiles(std::integral_constant<int, 1>{});
     }
     store(f - grid);
+    if (wide) {                                            // my frames once more
+        __syncthreads();
+        float *y1 = (float *)c12h_smem;
+        for (f = blockIdx.x; f < nframes; f += grid) {
+            plain_conv_layer(TABLE ? table[f] : x + (size_t)f * CHW, scale, w1, b1, y1, 4, 84, 84, 16, 8, 4, tid, 512);
+            __syncthreads();
+            plain_conv_layer(y1, 1.f, w2, b2, y2 + (size_t)f * 32 * NPIX2, 16, 20, 20, 32, 4, 2, tid, 512);
+            __syncthreads();
+        }
+    }
 }
 
 inline hipError_t launch_conv12_f16(const uint8_t *x, const uint8_t *const *table, const u32x4 *frag, const float *b1, const float *b2, float *y2,
-                                    int nframes, float scale, hipStream_t s) {
+                                    int nframes, float scale, const float *w1, const float *w2, hipStream_t s) {
     if (nframes <= 0) return hipSuccess;
     static bool attr_set = false;
     if (!attr_set) {
@@ -262,7 +280,7 @@ inline hipError_t launch_conv12_f16(const uint8_t *x, const uint8_t *const *tabl
         attr_set = true;
     }
     ga3c::launch(table ? conv12_f16_kernel<true> : conv12_f16_kernel<false>, dim3(nframes < 256 ? nframes : 256), dim3(512), Conv12F16::LDS, s, x,
-                 table, frag, b1, b2, y2, nframes, scale);
+                 table, frag, b1, b2, y2, nframes, scale, w1, w2);
     return hipGetLastError();
 }
 

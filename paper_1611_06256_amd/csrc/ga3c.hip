@@ -2210,7 +2210,8 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
               (double)B * (g0.CHW + (keep_zv ? 4.0 * g0.OC * g0.OHW : 0.0) + 4.0 * g1.OC * g1.OHW));
         // predictions at fp32 accuracy: two float16 terms; updates keep the rounding of their sums (conv123_f16.hpp says why)
         if (!keep_zv && !c->rb)
-            HIP_TRY(launch_conv12_f16(frames, table, c->hfrag[which], th + c->off[1], th + c->off[3], w.act[1], B, 1.f / 255.f, s));
+            HIP_TRY(launch_conv12_f16(frames, table, c->hfrag[which], th + c->off[1], th + c->off[3], w.act[1], B, 1.f / 255.f, th + c->off[0],
+                                      th + c->off[2], s));
         else
             HIP_TRY(launch_conv12_fused_fwd(frames, table, c->cfrag[which], th + c->off[1], th + c->off[3],
                                             keep_zv ? w.act[0] : nullptr, w.act[1], B, 1.f / 255.f, s, c->rb));
@@ -2222,7 +2223,8 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         STAGE("conv123_fwd", 2.0 * B * (g0.OHW * g0.OC * g0.K + g1.OHW * g1.OC * g1.K + g2.OHW * g2.OC * g2.K),
               (double)B * (g0.CHW + 4.0 * g2.OC * g2.OHW));
         auto go = [&](auto launch, const u32x4 *frag) {
-            return launch(frames, table, frag, th + c->off[1], th + c->off[3], th + c->off[5], w.act[2], B, 1.f / 255.f, s);
+            return launch(frames, table, frag, th + c->off[1], th + c->off[3], th + c->off[5], w.act[2], B, 1.f / 255.f, th + c->off[0],
+                          th + c->off[2], th + c->off[4], s);
         };
         if (c->conv123 == CONV123_LARGE)
             HIP_TRY(go(table ? launch_conv123_f16<Conv123Large, true> : launch_conv123_f16<Conv123Large, false>, c->lfrag[which] + LFRAG_VECS));

@@ -22,6 +22,13 @@ union F16x8Bits {
     u32x4 u;
 };
 
+// Weights too far apart for that: more than eight of a filter are not zero and below 2^-18 of its largest, or that one is no number.  Such a
+// filter's reciprocal of the scale is stored as a negative number, and kernels that read it take plain sums instead (conv_plain.hpp).
+// (Of normally distributed weights, one in a million is that small.)
+constexpr float F16_SMALL = 3.814697265625e-6f;
+constexpr int F16_WIDE = 8;
+__device__ __forceinline__ int f16_is_small(const float w, const float most) { return w != 0.f && fabsf(w) < most * F16_SMALL; }
+
 // The power of two by which numbers of magnitude `most` at most are multiplied, and its reciprocal.  Both are normal
 // numbers; a tensor of less than 2^-112 stays below 2^14.
 __device__ __forceinline__ void f16_scale(const float most, float &scale, float &inverse) {
@@ -48,6 +55,14 @@ __device__ __forceinline__ float f16_wave_most(float m) {
     const int u = __float_as_int(m);
     return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 0)), __int_as_float(__builtin_amdgcn_readlane(u, 16))),
                  fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 32)), __int_as_float(__builtin_amdgcn_readlane(u, 48))));
+}
+// Whether a layer's filters, one per lane of a wavefront (some may be there twice), need plain sums: one of them does, or they are of such
+// different sizes that the values of their map would be too far apart.  Filters of zeros don't count.
+__device__ __forceinline__ bool f16_wide_layer(const float inverse) {
+    const float a = fabsf(inverse);
+    const bool none = a <= 1.1754943508222875e-38f;        // 2^-126: zeros
+    const float most = f16_wave_most(a), least = f16_wave_most(none ? 0.f : 1.f / a);
+    return __any(inverse < 0.f) || most * least > 16384.f;
 }
 // The scale of a map whose largest values the eight wavefronts of a block have left in LDS.
 __device__ __forceinline__ void f16_scale_of(const float (&m)[8], float &scale, float &inverse) {

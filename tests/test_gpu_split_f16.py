@@ -63,6 +63,33 @@ def test_predictions_with_the_convolutions_in_one_kernel(G, which, B, layer, pow
     net.close()
 
 
+# Weights that two terms of one scale do not hold: a single huge one per layer, whose output the rectifier cuts off where the input is not
+# zero; a channel of other sizes, which the next layer's weights undo
+@pytest.mark.parametrize("which,B,what", [(n, b, w) for n, b in (("large", 2), ("paper4", 2), ("paper3", 258), ("small", 67))
+                                          for w in ("huge", "channel 1", "channel 2") if n != "small" or w != "channel 2"])
+def test_predictions_with_weights_far_apart(G, which, B, what):
+    import torch
+    net, onet, theta = P.make(G, network(G, which, 6), B, 0, 9150 + B)
+    if what == "huge":
+        for name, (at, shape) in net.offsets().items():
+            if name.startswith("conv") and name.endswith(".W"):
+                theta[at + int(np.prod(shape)) // 3] = -3.4e38
+    else:
+        l = int(what[-1])
+        v = orc.views(onet, theta)
+        for name, part, p in ((f"conv{l}.W", np.s_[3], 24), (f"conv{l}.b", np.s_[3], 24), (f"conv{l + 1}.W", np.s_[:, 3], -24)):
+            w = v[name].copy()
+            w[part] *= np.float32(2.0 ** p)
+            at = net.offsets()[name][0]
+            theta[at:at + w.size] = w.ravel()
+    net.params_set(torch.from_numpy(theta).cuda(), 0)
+    frames = synth.rectangle_frames(9151 + B, B)
+    lg, vl, _, _ = P.run_predict(G, net, frames)
+    ref = orc.forward(onet, theta, frames)
+    assert np.isfinite(ref["logits"]).all() and P.rel_err(lg, ref["logits"]) <= TOL and P.rel_err(vl, ref["values"]) <= TOL
+    net.close()
+
+
 # The small net's filters for predictions follow every update, a filter per wavefront of the kernel that updates the parameters: the
 # same bits as in a context that was given those parameters.  The second network ends soon behind the filters (3113 vectors of four).
 @pytest.mark.parametrize("conv,F", [(((16, 8, 4), (32, 4, 2)), 256), (((16, 8, 4), (32, 4, 2), (1, 1, 1)), 1)])
