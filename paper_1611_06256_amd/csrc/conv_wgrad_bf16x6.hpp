@@ -19,10 +19,16 @@
 // The bias gradient is one more product, dY times a column of ones, which the
 // wavefronts of channel slice 0 share by groups of 32 k.
 //
-// Both operands are split into three bf16 terms (x = hi + mid + lo exactly)
-// while they are staged, and a product is evaluated as the six largest of the
-// nine term products (dense_gemm_bf16x6.hpp): 6 x 16 cycles per 32 pixels
-// instead of 8 x 32 on the fp32 instruction.
+// Both operands are split into two float16 terms while they are staged, three
+// products a sum (split_f16.hpp); the two small ones have accumulators of their
+// own.  The scales are those of the largest values that the block has met so far
+// (its 16 channels, its filters' dY); where a frame brings larger ones, the sums
+// so far are brought to the new scale.  So a value of 2^-17 of the largest one
+// that goes into the same sums still has its 22 bits, and what is smaller an
+// error of 2^-40 of that one.  Three bfloat16 terms, six products, operands of
+// the next group read ahead, against this, error of dW in the 2-norm: small net 40
+// frames 1.45e-7 -> 1.34e-7, 2560: 1.8e-7 -> 1.1e-7, larger net 1280: 1.8e-7 -> 1.1e-7
+// (with one accumulator 1.6e-7, 1.6e-7 and 1.9e-7).
 //
 // A block takes 16 input channels, 16 by .. (C / 16 slices), and
 // OCB filters, OCB bz .. (all of them, or 32 where two blocks then fit
@@ -37,7 +43,7 @@
 #include "launch.hpp"
 #include <stdint.h>
 
-#include "conv1_bf16x3.hpp"
+#include "split_f16.hpp"
 
 namespace ga3c {
 
@@ -55,7 +61,7 @@ struct ConvWgradBf16Geom {
     static constexpr int DTERM = OCB * DROW, PTERM = 4 * CS * PROW;         // elements per term
     static constexpr int OTP = CS * 16 + 4;                        // floats per filter row of the block's result in LDS
     __host__ __device__ static constexpr int lds_bytes(bool one) {
-        const int stage = (one ? 1 : 3) * (DTERM + PTERM) * 2, out = OCB * OTP * 4;
+        const int stage = (one ? 1 : 2) * (DTERM + PTERM) * 2, out = OCB * OTP * 4;
         return stage > out ? stage : out;
     }
     static constexpr int PER_CU = 2 * lds_bytes(false) <= 160 * 1024 ? 2 : 1;
@@ -75,7 +81,7 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
     static_assert((OCB * SP::NPIX) % 4 == 0 && (G::DTERM % 8) == 0 && (G::PTERM % 8) == 0, "16-byte steps");
     constexpr int CS = G::CS, GW = G::GW, NKB = G::NKB, DROW = G::DROW, PROW = G::PROW, MT = G::MT;
     constexpr int DTERM = G::DTERM, PTERM = G::PTERM, OTP = G::OTP;
-    constexpr int NTERM = ONE ? 1 : 3;
+    constexpr int NTERM = ONE ? 1 : 2;
     constexpr int W4 = SP::W / 4, XV = CS * SP::H * W4, XPT = (XV + 255) / 256;       // float4 of the input slice
     constexpr int NDV = OCB * SP::NPIX / 4, DPT = (NDV + 255) / 256;                   // float4 of my filters' dY
     constexpr int K1 = SP::K + 1;
@@ -110,16 +116,19 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
             ddst[i][j] = oc * DROW + (pix / SP::OW) * GW + pix % SP::OW;
         }
 
-    floatx4 acc[4][MT];
+    constexpr bool LOW = !ONE;                         // small products have sums of their own
+    floatx4 acc[4][MT], low[4][LOW ? MT : 1];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int m = 0; m < MT; ++m) acc[s][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < MT; ++m) acc[s][m] = low[s][LOW ? m : 0] = floatx4{0.f, 0.f, 0.f, 0.f};
     floatx4 bacc[MT];                                  // dY times ones: every column holds the row sums
 #pragma unroll
     for (int m = 0; m < MT; ++m) bacc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-    Bf16x8Bits ones;
-    ones.u = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    constexpr uint32_t ONES = ONE ? 0x3F803F80u : 0x3C003C00u;
+    const u32x4 ones{ONES, ONES, ONES, ONES};
+    __shared__ __attribute__((aligned(16))) float most[2][4];
+    int scales[2] = {F16_NO_SCALE, F16_NO_SCALE};      // exponents: of the input, of dY
 
     float4 xpre[XPT], dpre[DPT];
     auto fetch = [&](int f) {
@@ -133,13 +142,44 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
     int f = bx;
     fetch(min(f, nframes - 1));
     for (; f < nframes; f += nbx) {
-        __syncthreads();                      // the last frame's operands have been read
+        if constexpr (ONE) __syncthreads();   // the last frame's operands have been read
+        else {
+            int e[2];
+            f16_block_exponents(most, wave, lane, [&](int n, auto fold) {
+                auto four = [&](const float4 v) { fold(v.x); fold(v.y); fold(v.z); fold(v.w); };
+                if (n == 0) {
+#pragma unroll
+                    for (int i = 0; i < XPT; ++i) four(xpre[i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < DPT; ++i) four(dpre[i]);
+                }
+            }, e);
+            // the sums so far come to the scale of the largest values so far
+            const int ex = min(e[0], scales[0]), ed = min(e[1], scales[1]);
+            if (ex + ed != scales[0] + scales[1]) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        bacc[m][r] = ldexpf(bacc[m][r], ed - scales[1]);
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            acc[s][m][r] = ldexpf(acc[s][m][r], ex + ed - scales[0] - scales[1]);
+                            if (LOW) low[s][m][r] = ldexpf(low[s][m][r], ex + ed - scales[0] - scales[1]);
+                        }
+                    }
+                scales[0] = ex;
+                scales[1] = ed;
+            }
+        }
+        const float xscale = f16_power(scales[0]), dscale = f16_power(scales[1]);
 #pragma unroll
         for (int i = 0; i < XPT; ++i)
             if (tid + 256 * i < XV) {
-                uint32_t t0[3], t1[3];
-                split3_pair(xpre[i].x, xpre[i].z, t0[0], t0[1], t0[2]);
-                split3_pair(xpre[i].y, xpre[i].w, t1[0], t1[1], t1[2]);
+                uint32_t t0[2], t1[2];
+                split_terms<ONE>(xpre[i].x, xpre[i].z, xscale, t0);
+                split_terms<ONE>(xpre[i].y, xpre[i].w, xscale, t1);
 #pragma unroll
                 for (int t = 0; t < NTERM; ++t) {
                     *(uint32_t *)(psm + t * PTERM + xdst[i]) = t0[t];
@@ -149,9 +189,9 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
             if (tid + 256 * i < NDV) {
-                uint32_t t0[3], t1[3];
-                split3_pair(dpre[i].x, dpre[i].y, t0[0], t0[1], t0[2]);
-                split3_pair(dpre[i].z, dpre[i].w, t1[0], t1[1], t1[2]);
+                uint32_t t0[2], t1[2];
+                split_terms<ONE>(dpre[i].x, dpre[i].y, dscale, t0);
+                split_terms<ONE>(dpre[i].z, dpre[i].w, dscale, t1);
                 uint16_t *dst = (uint16_t *)dsm;
 #pragma unroll
                 for (int t = 0; t < NTERM; ++t) {
@@ -165,61 +205,61 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
         fetch(min(f + nbx, nframes - 1));
         // the loads above go out before the products start (the compiler would otherwise sink them below the MFMAs)
         __builtin_amdgcn_sched_barrier(0);
-        constexpr int NPROD = ONE ? 1 : 6;
-        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
-        // the operand reads of the next group of 32 k are issued before the products of this one
-        Bf16x8Bits a[2][MT][NTERM];
-        u32x4 win[2][NTERM][3];
-        auto read_operands = [&](int kb, Bf16x8Bits (&ad)[MT][NTERM], u32x4 (&wd)[NTERM][3]) {
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int t = 0; t < NTERM; ++t)
-                    ad[m][t].u = *(const u32x4 *)(dsm + t * DTERM + (m * 16 + l16) * DROW + 32 * kb + 8 * g);
-#pragma unroll
-            for (int t = 0; t < NTERM; ++t) {
-                const u32x4 *src = (const u32x4 *)(psm + t * PTERM + (wave * CS + l16) * PROW + 32 * kb + 8 * g);
-                wd[t][0] = src[0]; wd[t][1] = src[1]; wd[t][2] = src[2];
-            }
-        };
-        read_operands(0, a[0], win[0]);
+        u32x4 a[MT][NTERM], win[NTERM][3];
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-            if (kb + 1 < NKB) read_operands(kb + 1, a[(kb + 1) & 1], win[(kb + 1) & 1]);
-            __builtin_amdgcn_sched_barrier(0);
-            Bf16x8Bits b[4][NTERM];
+#pragma unroll
+            for (int m = 0; m < MT; ++m)
+#pragma unroll
+                for (int t = 0; t < NTERM; ++t) a[m][t] = *(const u32x4 *)(dsm + t * DTERM + (m * 16 + l16) * DROW + 32 * kb + 8 * g);
 #pragma unroll
             for (int t = 0; t < NTERM; ++t) {
-                const u32x4 w0 = win[kb & 1][t][0], w1 = win[kb & 1][t][1], w2 = win[kb & 1][t][2];
+                const u32x4 *src = (const u32x4 *)(psm + t * PTERM + (wave * CS + l16) * PROW + 32 * kb + 8 * g);
+                win[t][0] = src[0]; win[t][1] = src[1]; win[t][2] = src[2];
+            }
+            u32x4 b[4][NTERM];
+#pragma unroll
+            for (int t = 0; t < NTERM; ++t) {
+                const u32x4 w0 = win[t][0], w1 = win[t][1], w2 = win[t][2];
                 const uint32_t dw[12] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3], w2[0], w2[1], w2[2], w2[3]};
 #pragma unroll
                 for (int av = 0; av < 2; ++av) {
                     const int o = av * (GW / 2);          // a shift of a rows of the phase grid is GW / 2 dwords
-                    b[2 * av][t].u = u32x4{dw[o], dw[o + 1], dw[o + 2], dw[o + 3]};
-                    b[2 * av + 1][t].u = u32x4{__builtin_amdgcn_alignbit(dw[o + 1], dw[o], 16), __builtin_amdgcn_alignbit(dw[o + 2], dw[o + 1], 16),
-                                               __builtin_amdgcn_alignbit(dw[o + 3], dw[o + 2], 16), __builtin_amdgcn_alignbit(dw[o + 4], dw[o + 3], 16)};
+                    b[2 * av][t] = u32x4{dw[o], dw[o + 1], dw[o + 2], dw[o + 3]};
+                    b[2 * av + 1][t] = u32x4{__builtin_amdgcn_alignbit(dw[o + 1], dw[o], 16), __builtin_amdgcn_alignbit(dw[o + 2], dw[o + 1], 16),
+                                             __builtin_amdgcn_alignbit(dw[o + 3], dw[o + 2], 16), __builtin_amdgcn_alignbit(dw[o + 4], dw[o + 3], 16)};
                 }
             }
-            if (by == 0 && kb % 4 == wave) {      // bias: the terms add up to dY exactly, smallest first
+            if (by == 0 && kb % 4 == wave) {      // bias, smallest first
 #pragma unroll
                 for (int t = NTERM - 1; t >= 0; --t)
 #pragma unroll
                     for (int m = 0; m < MT; ++m)
-                        bacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kb & 1][m][t].v, ones.v, bacc[m], 0, 0, 0);
+                        bacc[m] = mfma_terms<ONE>(a[m][t], ones, bacc[m]);
             }
 #pragma unroll
-            for (int q = 0; q < NPROD; ++q) {
-                const int ai = ONE ? 0 : PA[q], bi = ONE ? 0 : PB[q];
+            for (int q = 0; q < F16_PRODUCTS<ONE>; ++q)
 #pragma unroll
                 for (int s = 0; s < 4; ++s)
 #pragma unroll
-                    for (int m = 0; m < MT; ++m)
-                        acc[s][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kb & 1][m][ai % NTERM].v, b[s][bi % NTERM].v, acc[s][m], 0, 0, 0);
-            }
+                    for (int m = 0; m < MT; ++m) {
+                        floatx4 &sum = LOW && q < 2 ? low[s][LOW ? m : 0] : acc[s][m];
+                        sum = mfma_terms<ONE>(a[m][f16_a_term<ONE>(q)], b[s][f16_b_term<ONE>(q)], sum);
+                    }
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
+    }
+    if constexpr (!ONE) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                bacc[m][r] = ldexpf(bacc[m][r], 127 - scales[1]);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc[s][m][r] = ldexpf(LOW ? acc[s][m][r] + low[s][LOW ? m : 0][r] : acc[s][m][r], 254 - scales[0] - scales[1]);
+            }
     }
     // lane (l16, g), register r of acc[s = 2a + e][m]: filter 16 m + 4 g + r, channel c0 + l16, tap (ry + 2a, rx + 2e).
     // The block's result is put together in LDS and leaves in rows.
@@ -259,10 +299,11 @@ __global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void con
     conv_wgrad_bf16x6_block<SP, ONE, OCB>(x, dy, part, nframes, scale, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
 }
 
-// One partial dW per block: fewer blocks where a partial is large.
+// One partial dW per block.  They are written, read and added up again, so there are no more of them than it takes to fill the
+// chip beside the input gradient's blocks (conv_grads_bf16x6.hpp).
 template <class SP>
 inline int conv_wgrad_bf16x6_blocks(int nframes) {
-    constexpr int LIMIT = SP::OC * (SP::K + 1) > 16384 ? 256 : 512;
+    constexpr int LIMIT = SP::C == 16 ? 256 : 128;
     return nframes < LIMIT ? nframes : LIMIT;
 }
 

@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "conv1_bf16x3.hpp"
 
 namespace ga3c {
@@ -68,6 +70,79 @@ __device__ __forceinline__ bool f16_wide_layer(const float inverse) {
 __device__ __forceinline__ void f16_scale_of(const float (&m)[8], float &scale, float &inverse) {
     const float a = fmaxf(fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3])), fmaxf(fmaxf(m[4], m[5]), fmaxf(m[6], m[7])));
     f16_scale(__uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(a))), scale, inverse);
+}
+
+// ---- Gradients: operands whose magnitude nobody knows before they are there, and sums over several frames.
+//
+// A scale is its biased exponent here, so that it can be undone in one step (v_ldexp_f32), whatever the two operands' scales are.
+constexpr int F16_NO_SCALE = 253;
+__device__ __forceinline__ int f16_exponent(const float most) { return min(268 - (int)(__float_as_uint(most) >> 23 & 0xff), F16_NO_SCALE); }
+__device__ __forceinline__ float f16_power(const int exponent) { return __uint_as_float((uint32_t)exponent << 23); }
+
+// Scale exponents of N sets of values that a block of four wavefronts is about to split: at(n, fold) folds the calling thread's values
+// of set n.  `most` lies in LDS; a barrier of the block comes in front of its next use.  Infinities don't count (in a second look, which
+// only they cost), NaN never do.
+template <int N, class At>
+__device__ __forceinline__ void f16_block_exponents(float (&most)[N][4], const int wave, const int lane, const At &at, int (&e)[N]) {
+    auto look = [&](auto finite) {
+        float m[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            m[n] = 0.f;
+            at(n, [&](const float v) {
+                const float a = fabsf(v);
+                m[n] = fmaxf(m[n], !decltype(finite)::value || a < __builtin_inff() ? a : 0.f);
+            });
+            m[n] = f16_wave_most(m[n]);
+        }
+        if (lane == 0)
+#pragma unroll
+            for (int n = 0; n < N; ++n) most[n][wave] = m[n];
+        __syncthreads();
+        bool again = false;
+#pragma unroll
+        for (int n = 0; n < N; ++n) {
+            const float a = fmaxf(fmaxf(most[n][0], most[n][1]), fmaxf(most[n][2], most[n][3]));
+            const uint32_t u = __builtin_amdgcn_readfirstlane(__float_as_uint(a));
+            again |= u == 0x7f800000u;
+            e[n] = f16_exponent(__uint_as_float(u));
+        }
+        return again;
+    };
+    if (look(std::false_type{})) {
+        __syncthreads();
+        look(std::true_type{});
+    }
+}
+
+// One of the operands' terms times the other's: bfloat16 (one term) or float16.
+template <bool BF16>
+__device__ __forceinline__ floatx4 mfma_terms(const u32x4 a, const u32x4 b, const floatx4 c) {
+    if constexpr (BF16) {
+        Bf16x8Bits x, y;
+        x.u = a; y.u = b;
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v, y.v, c, 0, 0, 0);
+    } else {
+        F16x8Bits x, y;
+        x.u = a; y.u = b;
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(x.v, y.v, c, 0, 0, 0);
+    }
+}
+// Three products a sum, smallest first, or the one of rounded operands.
+template <bool ONE> constexpr int F16_PRODUCTS = ONE ? 1 : 3;
+template <bool ONE> constexpr int f16_a_term(int q) { return ONE ? 0 : q == 0; }
+template <bool ONE> constexpr int f16_b_term(int q) { return ONE ? 0 : q == 1; }
+
+// Two values as terms: bfloat16, rounded (the others are not used), or two of float16.
+template <bool ONE>
+__device__ __forceinline__ void split_terms(const float x, const float y, const float scale, uint32_t (&t)[2]) {
+    if constexpr (ONE) {
+        uint32_t mid, lo;
+        split3_pair(x, y, t[0], mid, lo);
+        t[1] = 0;
+    } else {
+        split2_pair(x, y, scale, t[0], t[1]);
+    }
 }
 
 // Eight bytes as float16: a byte's bits are those of the subnormal number b 2^-24, which the matrix instruction takes as it is.

@@ -118,3 +118,47 @@ def test_predictions_read_the_filters_that_an_update_leaves(G, conv, F):
         for k in want:
             assert torch.isfinite(want[k]).all() and not torch.equal(want[k], before[k]) and torch.equal(got[k], want[k]), (step, k)
     net.close(); other.close()
+
+
+# Gradients, whose operands are scaled by what a block has met so far: one frame a block and several, rewards (and with them gradients) of
+# very different sizes in one block, a layer whose map is zero.  Each layer on its own, from the tensors that the update has left, in 64
+# bits: sums of n products carry sqrt(n / 32) roundings of 2^-24 of the running sum, observed 3e-7 of the result at most.
+@pytest.mark.parametrize("which,N,spread,dead", [(w, *c) for w in ("small", "large", "paper4") for c in [(1, 0, 0), (157, 0, 0), (160, 6, 0), (40, 0, 1)]])
+def test_gradients_of_the_convolutions(G, which, N, spread, dead):
+    import torch
+    A, T = 6, 5
+    B = N * T
+    net, onet, theta = P.make(G, network(G, which, A), 1, B, 9300 + N)
+    off = net.offsets()
+    if dead:
+        at, shape = off["conv1.b"]
+        theta[at:at + int(np.prod(shape))] = -50
+    net.params_set(torch.from_numpy(theta).cuda(), 0)
+    frames = synth.rectangle_frames(9301 + N, B).reshape(B, 4, 84, 84)
+    tr = synth.trajectories(9302 + N, N, T, A)
+    sizes = np.float32(10.0) ** np.random.default_rng(9303).uniform(-spread, spread, N).astype(np.float32)
+    rewards = (tr["rewards"] + np.float32(0.5)) * sizes[:, None]
+    net.train_step(torch.from_numpy(frames).cuda().view(N, T, 4, 84, 84), torch.from_numpy(tr["actions"]).cuda(), torch.from_numpy(rewards).cuda(),
+                   torch.from_numpy(tr["dones"]).cuda(), None, G.HParams())
+
+    def get(which, *shape):
+        return net.train_debug_get(which, torch.empty(int(np.prod(shape)), device="cuda")).cpu().double().view(shape)
+
+    def close(got, want, what):
+        assert torch.isfinite(got).all() and float((got - want).norm()) <= 1e-6 * float(want.norm()), what
+
+    x, grad = torch.from_numpy(frames).double() / 255, net.params_get(2).cpu().double()
+    conv = onet.conv
+    for l, (oc, k, s) in enumerate(conv):
+        oh = (x.shape[-1] - k) // s + 1
+        y, dy = get(4 + l, B, oc, oh, oh), get(10 + l, B, oc, oh, oh)
+        at, shape = off[f"conv{l + 1}.W"]
+        n = int(np.prod(shape))
+        close(grad[at:at + n].view(*shape), torch.nn.grad.conv2d_weight(x, tuple(shape), dy, stride=s), f"conv{l + 1}.W")
+        at_b = off[f"conv{l + 1}.b"][0]
+        close(grad[at_b:at_b + oc], dy.sum((0, 2, 3)), f"conv{l + 1}.b")
+        if l:
+            w = torch.from_numpy(theta[at:at + n]).double().view(*shape)
+            close(get(10 + l - 1, *x.shape), torch.nn.grad.conv2d_input(x.shape, w, dy, stride=s) * (x > 0), f"input of conv{l + 1}")
+        x = y
+    net.close()
