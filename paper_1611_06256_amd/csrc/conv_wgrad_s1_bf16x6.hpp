@@ -14,13 +14,15 @@
 // dwords for even shifts, a 16-bit funnel shift for odd ones.  Wavefront w owns
 // the channels 16 w .. 16 w + 15: KS x KS taps x 2 filter tiles of accumulators
 // [16 filters] x [16 channels], kept over all frames of its block.  The bias
-// gradient is one more product, dY times a column of ones.  (Rows at the pitch of
+// gradient is one more product, dY times a column of ones.  (With three bfloat16 terms, rows at the pitch of
 // lds_row_units, and staging in 8-byte instead of 2-byte stores with one unaligned
-// 16-byte load each, gained nothing: 1280 frames 30.5 us, 31.1 with the latter.)
+// 16-byte load each gained nothing: 1280 frames 30.5 us, 31.1 with the latter.)
 //
-// Both operands are split into three bf16 terms (x = hi + mid + lo exactly)
-// while they are staged, and a product is evaluated as the six largest of the
-// nine term products (dense_gemm_bf16x6.hpp).
+// Both operands are split into two float16 terms while they are staged, three
+// products a sum, under the scales of the largest values that the block has met
+// so far (split_f16.hpp, conv_wgrad_bf16x6.hpp).  With three bfloat16 terms, six
+// products, 1280 frames took 37.5 us instead of 29.7; error of dW in the 2-norm
+// 1.27e-7 both (320 frames 1.42e-7 -> 1.40e-7).  There is no room for accumulators of the small products.
 //
 // A block takes 32 filters, 32 blockIdx.y .. (gridDim.y = OC / 32), of frames
 // blockIdx.x, + gridDim.x, .. and writes its rows of one partial gradient,
@@ -33,7 +35,7 @@
 #include "launch.hpp"
 #include <stdint.h>
 
-#include "conv1_bf16x3.hpp"
+#include "split_f16.hpp"
 
 namespace ga3c {
 
@@ -49,7 +51,7 @@ struct ConvWgradS1Bf16Geom {
     static constexpr int DTERM = MS * 16 * DROW, PTERM = SP::C * PROW;      // elements per term
     static constexpr int OTP = SP::K + 4;                          // floats per filter row of a tile's result in LDS
     __host__ __device__ static constexpr int lds_bytes(bool one) {
-        const int stage = (one ? 1 : 3) * (DTERM + PTERM) * 2, out = 16 * OTP * 4;
+        const int stage = (one ? 1 : 2) * (DTERM + PTERM) * 2, out = 16 * OTP * 4;
         return stage > out ? stage : out;
     }
 };
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     static_assert((G::PROW / 2) % 8 == 4 && (G::DROW / 2) % 8 == 4, "rows of an odd number of 16-byte units");
     constexpr int MS = G::MS, NKB = G::NKB, DROW = G::DROW, PROW = G::PROW, KS = SP::KS, NTAP = KS * KS;
     constexpr int DTERM = G::DTERM, PTERM = G::PTERM, OTP = G::OTP, HW = SP::H * SP::W;
-    constexpr int NTERM = ONE ? 1 : 3;
+    constexpr int NTERM = ONE ? 1 : 2;
     constexpr int XV = SP::CHW / 4, XPT = (XV + 255) / 256;                // float4 of the input frame
     constexpr int NDV = MS * 16 * SP::NPIX / 4, DPT = (NDV + 255) / 256;    // float4 of my filters' dY
     constexpr int K1 = SP::K + 1;
@@ -106,8 +108,10 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
 #pragma unroll
         for (int s = 0; s < NTAP; ++s) acc[s][m] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    Bf16x8Bits ones;
-    ones.u = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    constexpr uint32_t ONES = ONE ? 0x3F803F80u : 0x3C003C00u;
+    const u32x4 ones{ONES, ONES, ONES, ONES};
+    __shared__ __attribute__((aligned(16))) float most[2][4];
+    int scales[2] = {F16_NO_SCALE, F16_NO_SCALE};      // exponents: of the input, of dY
 
     float4 xpre[XPT], dpre[DPT];
     auto fetch = [&](int f) {
@@ -118,10 +122,10 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
 #pragma unroll
         for (int i = 0; i < DPT; ++i) dpre[i] = ds[min(tid + 256 * i, NDV - 1)];
     };
-    auto stash4 = [&](const float4 v, __bf16 *base, int tstride, const int (&dst)[4]) {
-        uint32_t t0[3], t1[3];
-        split3_pair(v.x, v.y, t0[0], t0[1], t0[2]);
-        split3_pair(v.z, v.w, t1[0], t1[1], t1[2]);
+    auto stash4 = [&](const float4 v, float scale, __bf16 *base, int tstride, const int (&dst)[4]) {
+        uint32_t t0[2], t1[2];
+        split_terms<ONE>(v.x, v.y, scale, t0);
+        split_terms<ONE>(v.z, v.w, scale, t1);
         uint16_t *o = (uint16_t *)base;
 #pragma unroll
         for (int t = 0; t < NTERM; ++t) {
@@ -134,29 +138,55 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     int f = blockIdx.x;
     fetch(min(f, nframes - 1));
     for (; f < nframes; f += gridDim.x) {
-        __syncthreads();                      // the last frame's operands have been read
+        if constexpr (ONE) __syncthreads();   // the last frame's operands have been read
+        else {
+            int e[2];
+            f16_block_exponents(most, wave, lane, [&](int n, auto fold) {
+                auto four = [&](const float4 v) { fold(v.x); fold(v.y); fold(v.z); fold(v.w); };
+                if (n == 0) {
+#pragma unroll
+                    for (int i = 0; i < XPT; ++i) four(xpre[i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < DPT; ++i) four(dpre[i]);
+                }
+            }, e);
+            // the sums so far come to the scale of the largest values so far
+            const int ex = min(e[0], scales[0]), ed = min(e[1], scales[1]);
+            if (ex + ed != scales[0] + scales[1]) {
+#pragma unroll
+                for (int m = 0; m < MS; ++m)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        bacc[m][r] = ldexpf(bacc[m][r], ed - scales[1]);
+#pragma unroll
+                        for (int s = 0; s < NTAP; ++s) acc[s][m][r] = ldexpf(acc[s][m][r], ex + ed - scales[0] - scales[1]);
+                    }
+                scales[0] = ex;
+                scales[1] = ed;
+            }
+        }
+        const float xscale = f16_power(scales[0]), dscale = f16_power(scales[1]);
 #pragma unroll
         for (int i = 0; i < XPT; ++i)
-            if (tid + 256 * i < XV) stash4(xpre[i], psm, PTERM, xdst[i]);
+            if (tid + 256 * i < XV) stash4(xpre[i], xscale, psm, PTERM, xdst[i]);
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
-            if (tid + 256 * i < NDV) stash4(dpre[i], dsm, DTERM, ddst[i]);
+            if (tid + 256 * i < NDV) stash4(dpre[i], dscale, dsm, DTERM, ddst[i]);
         __syncthreads();
         fetch(min(f + (int)gridDim.x, nframes - 1));
         // the loads above go out before the products start (the compiler would otherwise sink them below the MFMAs)
         __builtin_amdgcn_sched_barrier(0);
-        constexpr int NPROD = ONE ? 1 : 6;
-        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-            Bf16x8Bits a[MS][NTERM];
+            u32x4 a[MS][NTERM];
             uint32_t dw[NTERM][16];
 #pragma unroll
             for (int m = 0; m < MS; ++m)
 #pragma unroll
                 for (int t = 0; t < NTERM; ++t)
-                    a[m][t].u = *(const u32x4 *)(dsm + t * DTERM + (m * 16 + l16) * DROW + 32 * kb + 8 * g);
+                    a[m][t] = *(const u32x4 *)(dsm + t * DTERM + (m * 16 + l16) * DROW + 32 * kb + 8 * g);
 #pragma unroll
             for (int t = 0; t < NTERM; ++t) {
                 const u32x4 *src = (const u32x4 *)(psm + t * PTERM + (wave * 16 + l16) * PROW + 32 * kb + 8 * g);
@@ -166,42 +196,49 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
                     dw[t][4 * q] = w[0]; dw[t][4 * q + 1] = w[1]; dw[t][4 * q + 2] = w[2]; dw[t][4 * q + 3] = w[3];
                 }
             }
-            if (kb % 4 == wave) {             // bias: the terms add up to dY exactly, smallest first
+            if (kb % 4 == wave) {             // bias, smallest first
 #pragma unroll
                 for (int t = NTERM - 1; t >= 0; --t)
 #pragma unroll
                     for (int m = 0; m < MS; ++m)
-                        bacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][t].v, ones.v, bacc[m], 0, 0, 0);
+                        bacc[m] = mfma_terms<ONE>(a[m][t], ones, bacc[m]);
             }
             // one row of taps at a time: KS shifts x MS filter tiles of independent accumulators
 #pragma unroll
             for (int u = 0; u < KS; ++u) {
-                Bf16x8Bits b[KS][NTERM];
+                u32x4 b[KS][NTERM];
 #pragma unroll
                 for (int v = 0; v < KS; ++v) {
                     const int sh = u * SP::W + v, o = sh / 2;
 #pragma unroll
                     for (int t = 0; t < NTERM; ++t) {
                         if (sh % 2 == 0)
-                            b[v][t].u = u32x4{dw[t][o], dw[t][o + 1], dw[t][o + 2], dw[t][o + 3]};
+                            b[v][t] = u32x4{dw[t][o], dw[t][o + 1], dw[t][o + 2], dw[t][o + 3]};
                         else
-                            b[v][t].u = u32x4{__builtin_amdgcn_alignbit(dw[t][o + 1], dw[t][o], 16), __builtin_amdgcn_alignbit(dw[t][o + 2], dw[t][o + 1], 16),
+                            b[v][t] = u32x4{__builtin_amdgcn_alignbit(dw[t][o + 1], dw[t][o], 16), __builtin_amdgcn_alignbit(dw[t][o + 2], dw[t][o + 1], 16),
                                               __builtin_amdgcn_alignbit(dw[t][o + 3], dw[t][o + 2], 16), __builtin_amdgcn_alignbit(dw[t][o + 4], dw[t][o + 3], 16)};
                     }
                 }
 #pragma unroll
-                for (int q = 0; q < NPROD; ++q) {
-                    const int ai = ONE ? 0 : PA[q], bi = ONE ? 0 : PB[q];
+                for (int q = 0; q < F16_PRODUCTS<ONE>; ++q)
 #pragma unroll
                     for (int v = 0; v < KS; ++v)
 #pragma unroll
                         for (int m = 0; m < MS; ++m)
-                            acc[u * KS + v][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m][ai % NTERM].v, b[v][bi % NTERM].v,
-                                                                                         acc[u * KS + v][m], 0, 0, 0);
-                }
+                            acc[u * KS + v][m] = mfma_terms<ONE>(a[m][f16_a_term<ONE>(q)], b[v][f16_b_term<ONE>(q)], acc[u * KS + v][m]);
             }
         }
         __builtin_amdgcn_s_setprio(0);
+    }
+    if constexpr (!ONE) {
+#pragma unroll
+        for (int m = 0; m < MS; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                bacc[m][r] = ldexpf(bacc[m][r], 127 - scales[1]);
+#pragma unroll
+                for (int s = 0; s < NTAP; ++s) acc[s][m][r] = ldexpf(acc[s][m][r], 254 - scales[0] - scales[1]);
+            }
     }
     // lane (l16, g), register r of acc[tap][m]: filter oc0 + 16 m + 4 g + r, channel 16 wave + l16.  One filter tile at a
     // time is put together in LDS and leaves in rows.

@@ -79,11 +79,11 @@ constexpr int F16_NO_SCALE = 253;
 __device__ __forceinline__ int f16_exponent(const float most) { return min(268 - (int)(__float_as_uint(most) >> 23 & 0xff), F16_NO_SCALE); }
 __device__ __forceinline__ float f16_power(const int exponent) { return __uint_as_float((uint32_t)exponent << 23); }
 
-// Scale exponents of N sets of values that a block of four wavefronts is about to split: at(n, fold) folds the calling thread's values
+// Scale exponents of N sets of values that a block of NW wavefronts is about to split: at(n, fold) folds the calling thread's values
 // of set n.  `most` lies in LDS; a barrier of the block comes in front of its next use.  Infinities don't count (in a second look, which
 // only they cost), NaN never do.
-template <int N, class At>
-__device__ __forceinline__ void f16_block_exponents(float (&most)[N][4], const int wave, const int lane, const At &at, int (&e)[N]) {
+template <int N, int NW, class At>
+__device__ __forceinline__ void f16_block_exponents(float (&most)[N][NW], const int wave, const int lane, const At &at, int (&e)[N]) {
     auto look = [&](auto finite) {
         float m[N];
 #pragma unroll
@@ -102,7 +102,9 @@ __device__ __forceinline__ void f16_block_exponents(float (&most)[N][4], const i
         bool again = false;
 #pragma unroll
         for (int n = 0; n < N; ++n) {
-            const float a = fmaxf(fmaxf(most[n][0], most[n][1]), fmaxf(most[n][2], most[n][3]));
+            float a = most[n][0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) a = fmaxf(a, most[n][w]);
             const uint32_t u = __builtin_amdgcn_readfirstlane(__float_as_uint(a));
             again |= u == 0x7f800000u;
             e[n] = f16_exponent(__uint_as_float(u));
