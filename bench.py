@@ -84,7 +84,7 @@ COUNTER_KIB = {   # stage: {frames per launch: (FETCH_SIZE, WRITE_SIZE)}; two st
 # HIP kernel behind each stage of the small net's fast path, and the larger net's
 KERNELS = {"conv12_fwd": "conv12_f16_kernel (predictions), conv12_fused_fwd_kernel (updates)", "fc_fwd": "fc_forward_kernel",
            "fc_wgrad": "fc_grads_kernel", "fc_dgrad": "fc_grads_kernel", "heads_fwd": "heads_predict_kernel",
-           "heads_train": "heads_train_kernel", "conv1_wgrad": "conv1_bf16x3_wgrad_kernel",
+           "heads_train": "heads_train_kernel", "conv1_wgrad": "conv1_wgrad_kernel",
            "conv2_wgrad": "conv_grads_bf16x6_kernel", "conv3_wgrad": "conv_wgrad_s1_bf16x6_kernel",
            "conv2_dgrad": "conv_grads_bf16x6_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
            "conv123_fwd": "conv123_f16_kernel", "conv1_fwd": "conv1_bf16x3_fwd_kernel", "conv2_fwd": "conv_fwd_bf16x6_kernel", "conv3_fwd": "conv_fwd_bf16x6_kernel",

@@ -265,231 +265,4 @@ inline hipError_t launch_conv1_bf16x3_fwd(const uint8_t *x, const uint8_t *const
     return hipGetLastError();
 }
 
-
-// Weight and bias gradient of the same layer, same arithmetic: the frame is
-// exact in bf16 and dY is split into three bf16 terms.
-//   dW[oc][c][u][v] = sum_{i,j} dY[oc][i][j] x[c][4i+u][4j+v],   db[oc] = sum dY[oc][i][j]
-// The contraction runs over output pixels, 8 consecutive pixels of a row per
-// lane, so the frame is re-laid in LDS "space to depth": with u = 4a + u',
-// v = 4b + v' the pixel x[c][4i+u][4j+v] is X[(c,u',v')][i+a][j+b], and 8
-// consecutive j are 8 consecutive elements of a row of plane (c,u',v').  Plane
-// index q = (c,u',v') is the column of the MFMA tile (wave w owns channel w and
-// its 16 planes), the filters are the rows, and the four (a,b) are four
-// accumulators.  Shift b = 1 is made from the b = 0 vector and one more dword.
-// Rows of 20 pixels are padded to 24 = 3 blocks of 8 with zero dY.
-// part: [gridDim.x][OCT][257]; the last column is the bias gradient.  A layer
-// with OCT = 32 filters is done in two slices of 16 (blockIdx.y).
-// Matrix and vector instructions (28 % and 36 % of the SIMDs' cycles: bytes to bf16, the split of dY) and the phases of
-// the one block per compute unit bound it; half of the cycles of the LDS were bank conflicts while rows of the planes
-// were 32 pixels and planes and filters at odd pitches: 2560 frames of 16 filters 36.4 -> 34.5 us, 1280 of 32 40.9 ->
-// 38.1; with one term of dY (ONE) instead of two more that were zero 36.6 -> 30.1 and 41.3 -> 32.5.
-template <int OCT, int NPART, bool TABLE, bool ONE>
-__global__ __launch_bounds__(256 * NPART) void conv1_bf16x3_wgrad_kernel(const uint8_t *__restrict__ x,
-                                                                 const uint8_t *const *__restrict__ table,
-                                                                 const float *__restrict__ dy,
-                                                                 float *__restrict__ part, int nframes, float scale) {
-    // ONE: dY enters the products (and the bias sums) rounded to bfloat16
-    constexpr int C = 4, H = 84, W = 84, OC = 16, OH = 20, NPIX = 400, K = 256, CHW = C * H * W;
-    // bf16 elements.  Blocks of 8 pixels are consecutive units of 16 bytes, in the planes as in dY; dY's filters lie at a pitch
-    // of lds_row_units.  A plane (c, u', v') lies 4 u' + {0, 2, 8, 10}[v'] (mod 16) units behind a multiple of 256 bytes: even
-    // places that differ within {0-3, 12-15} and within {4-11}, as lds_row_units wants them, and the four u' that a store
-    // instruction meets are 64 bytes apart.
-    constexpr int XROW = 24, XPLANE = 80 * 8;
-    constexpr int DROW = 24, DOC = 8 * lds_row_units(OH * 3);
-    constexpr int NTERM = ONE ? 1 : 3;
-    constexpr int NTHR = 256 * NPART;                      // NPART wavefronts per SIMD, so that one's LDS and
-                                                           // conversion work fills another's MFMA waits
-    constexpr int NITEM = 336 * 6, IPT = (NITEM + NTHR - 1) / NTHR;    // (frame row, group of 4 dwords)
-    constexpr int NDV = OC * NPIX / 4, DPT = (NDV + NTHR - 1) / NTHR;  // float4 of dY per frame
-    constexpr int NSTEP = OH * 3 / 4;                      // 60 blocks of 8 pixels, 4 per MFMA
-    __shared__ __attribute__((aligned(16))) __bf16 xp[64 * XPLANE + 16 * 8];
-    __shared__ __attribute__((aligned(16))) __bf16 dp[NTERM * OC * DOC];
-    __shared__ float bsh[NDV];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, g = lane >> 4;
-    const int oc0 = blockIdx.y * OC;                       // my slice of the filters
-    static_assert(OCT % OC == 0, "whole slices of 16 filters");
-
-    for (int e = tid; e < (64 * XPLANE + 16 * 8) / 2; e += NTHR) ((uint32_t *)xp)[e] = 0u;     // padding stays zero
-    for (int e = tid; e < NTERM * OC * DOC / 2; e += NTHR) ((uint32_t *)dp)[e] = 0u;
-
-    // staging descriptors: where my dwords come from and where they go.  A row of 21 dwords is five groups of four
-    // and a last group of one; that one is fetched as the last of the row's dwords 17..20, so that every fetch is one
-    // 16-byte load (4-byte aligned) that stays inside the frame.
-    int xsrc[IPT], xdst[IPT], xup[IPT], xcnt[IPT];       // xup: where v' = 2 lies, from v' = 0
-#pragma unroll
-    for (int i = 0; i < IPT; ++i) {
-        const int it = min(tid + NTHR * i, NITEM - 1);
-        const int row = it / 6, gq = it % 6;               // row = c*84 + r
-        const int c = row / H, r = row % H;
-        xsrc[i] = row * (W / 4) + (gq == 5 ? 17 : 4 * gq); // dword index in the frame
-        xcnt[i] = (tid + NTHR * i < NITEM) ? (gq == 5 ? 1 : 4) : 0;
-        xdst[i] = ((c * 4 + r % 4) * 4) * XPLANE + 4 * (r % 4) * 8 + (r / 4) * XROW + 4 * gq;   // plane (c, u'=r%4, v'=0)
-        xup[i] = 2 * XPLANE + (r % 4 < 2 ? 64 : -64);
-    }
-    int dsrc[DPT], ddst[DPT];
-#pragma unroll
-    for (int i = 0; i < DPT; ++i) {
-        const int e = min(tid + NTHR * i, NDV - 1);
-        dsrc[i] = e;
-        const int oc = e / (NPIX / 4), pq = e % (NPIX / 4);           // 5 float4 per row of 20
-        ddst[i] = oc * DOC + (pq / 5) * DROW + 4 * (pq % 5);
-    }
-
-    floatx4 acc[2][2];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-
-    typedef uint32_t u32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
-    u32x4 xpre[IPT];
-    float4 dpre[DPT];
-    auto fetch = [&](const uint8_t *at, int ff) {
-        const uint32_t *xs = (const uint32_t *)at;
-#pragma unroll
-        for (int i = 0; i < IPT; ++i) xpre[i] = *(const u32x4_dword_aligned *)(xs + xsrc[i]);
-        const float4 *ds = (const float4 *)(dy + ((size_t)ff * OCT + oc0) * NPIX);
-#pragma unroll
-        for (int i = 0; i < DPT; ++i) dpre[i] = ds[dsrc[i]];
-    };
-    int f = blockIdx.x;
-    FramePointer<TABLE> next;
-    next.ask(x, table, min(f, nframes - 1), CHW);
-    fetch(next.get(), min(f, nframes - 1));
-    if (TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
-    const int ch = wave & 3, prt = wave >> 2;        // wavefronts w, w + 4, ... share channel w and divide the pixel blocks
-    const __bf16 *xq = xp + (ch * 16 + l16) * XPLANE + 8 * ((4 * (l16 >> 2) + (l16 & 1) * 2 + (l16 & 2) * 4) & 15);      // my plane
-    for (; f < nframes; f += gridDim.x) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < IPT; ++i) {
-            if (xcnt[i] > 0) {
-                // a last group holds its dword in the fourth place; the other three places become zero padding
-                const u32x4 xv = xcnt[i] == 4 ? xpre[i] : u32x4{xpre[i][3], 0u, 0u, 0u};
-#pragma unroll
-                for (int vq = 0; vq < 4; ++vq) {             // plane v' = vq gets byte vq of each dword
-                    union { __bf16 h[4]; uint2 u; } o;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) o.h[t] = (__bf16)(float)((xv[t] >> (8 * vq)) & 0xff);
-                    *(uint2 *)(xp + xdst[i] + (vq / 2) * xup[i] + (vq % 2) * (XPLANE + 16)) = o.u;
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < DPT; ++i) {
-            if (tid + NTHR * i < NDV) {
-                const float v[4] = {dpre[i].x, dpre[i].y, dpre[i].z, dpre[i].w};
-                union { __bf16 h[4]; uint2 u; } o[3];
-                split3_pair(v[0], v[1], o[0].u.x, o[1].u.x, o[2].u.x);
-                split3_pair(v[2], v[3], o[0].u.y, o[1].u.y, o[2].u.y);
-#pragma unroll
-                for (int term = 0; term < NTERM; ++term) *(uint2 *)(dp + term * OC * DOC + ddst[i]) = o[term].u;
-                bsh[tid + NTHR * i] = ONE ? ((float)o[0].h[0] + (float)o[0].h[1]) + ((float)o[0].h[2] + (float)o[0].h[3])
-                                        : (v[0] + v[1]) + (v[2] + v[3]);
-            }
-        }
-        __syncthreads();
-        if (!TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
-        fetch(next.get(), min(f + (int)gridDim.x, nframes - 1));
-        if (TABLE) next.ask(x, table, min(f + 2 * (int)gridDim.x, nframes - 1), CHW);
-        if (tid < 256) {   // bias: 16 lanes share a filter, 100 partial sums each
-            const int oc = tid / 16, pt = tid % 16;
-            float sum = 0.f;
-            for (int m = pt; m < NPIX / 4; m += 16) sum += bsh[oc * (NPIX / 4) + m];
-            sum += dpp_row_f32<0xB1>(sum); sum += dpp_row_f32<0x4E>(sum);
-            sum += dpp_row_f32<0x141>(sum); sum += dpp_row_f32<0x140>(sum);
-            bsum += sum;
-        }
-        auto steps = [&](auto first, auto last) {
-#pragma unroll
-            for (int st = decltype(first)::value; st < decltype(last)::value; ++st) {
-                const int blk = 4 * st + g;               // row blk / 3 of 24 pixels, block blk % 3 of it
-                Bf16x8Bits d[3];
-#pragma unroll
-                for (int term = 0; term < NTERM; ++term)
-                    d[term].u = *(const u32x4 *)(dp + term * OC * DOC + l16 * DOC + 8 * blk);
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const __bf16 *src = xq + 8 * blk + a * XROW;
-                    const u32x4 c0 = *(const u32x4 *)src;
-                    const uint32_t c4 = *(const uint32_t *)(src + 8);
-                    Bf16x8Bits x0, x1;
-                    x0.u = c0;
-                    x1.u = u32x4{__builtin_amdgcn_alignbit(c0[1], c0[0], 16), __builtin_amdgcn_alignbit(c0[2], c0[1], 16),
-                                 __builtin_amdgcn_alignbit(c0[3], c0[2], 16), __builtin_amdgcn_alignbit(c4, c0[3], 16)};
-#pragma unroll
-                    for (int term = NTERM - 1; term >= 0; --term) {
-                        acc[a][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[term].v, x0.v, acc[a][0], 0, 0, 0);
-                        acc[a][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[term].v, x1.v, acc[a][1], 0, 0, 0);
-                    }
-                }
-            }
-        };
-        static_assert(NPART == 1 || NPART == 2 || NPART == 4, "one, two or four wavefronts per SIMD");
-        constexpr int Q1 = NSTEP / NPART, Q2 = 2 * NSTEP / NPART, Q3 = 3 * NSTEP / NPART;
-        typedef std::integral_constant<int, 0> I0;
-        typedef std::integral_constant<int, NSTEP> IN;
-        if (NPART == 1) steps(I0{}, IN{});
-        else if (NPART == 2) {
-            if (prt == 0) steps(I0{}, std::integral_constant<int, Q1>{});
-            else steps(std::integral_constant<int, Q1>{}, IN{});
-        } else {
-            if (prt == 0) steps(I0{}, std::integral_constant<int, Q1>{});
-            else if (prt == 1) steps(std::integral_constant<int, Q1>{}, std::integral_constant<int, Q2>{});
-            else if (prt == 2) steps(std::integral_constant<int, Q2>{}, std::integral_constant<int, Q3>{});
-            else steps(std::integral_constant<int, Q3>{}, IN{});
-        }
-    }
-    if (NPART > 1) {   // the parts of a channel's pixel blocks are added through LDS (the frame planes are no longer needed)
-        __syncthreads();
-        float *xch = (float *)xp;
-        if (prt > 0) {
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        xch[(((prt - 1) * 4 + ch) * 16 + (a * 2 + b) * 4 + r) * 64 + lane] = acc[a][b][r];
-        }
-        __syncthreads();
-        if (prt > 0) return;
-#pragma unroll
-        for (int q = 0; q < NPART - 1; ++q)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[a][b][r] += xch[((q * 4 + ch) * 16 + (a * 2 + b) * 4 + r) * 64 + lane];
-    }
-    // lane (l16, g), register r of acc[a][b]: filter 4g + r, tap (c = wave, u = 4a + l16/4, v = 4b + l16%4)
-    float *pb = part + ((size_t)blockIdx.x * OCT + oc0) * (K + 1);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                pb[(4 * g + r) * (K + 1) + ch * 64 + (4 * a + l16 / 4) * 8 + 4 * b + l16 % 4] = acc[a][b][r] * scale;
-    if (tid % 16 == 0) pb[(tid / 16) * (K + 1) + K] = bsum;      // tid < 256 here
-}
-
-inline int conv1_bf16x3_wgrad_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
-
-template <int OCT = 16, int NPART = 4>
-inline hipError_t launch_conv1_bf16x3_wgrad(const uint8_t *x, const uint8_t *const *table, const float *dy, float *part, int nframes, float scale,
-                                            hipStream_t s, int rb = 0) {
-    if (nframes <= 0) return hipSuccess;
-    const dim3 grid(conv1_bf16x3_wgrad_blocks(nframes), OCT / 16), block(256 * NPART);
-    auto go = [&](auto kernel) { ga3c::launch(kernel, grid, block, 0, s, x, table, dy, part, nframes, scale); };
-    if (table) rb ? go(conv1_bf16x3_wgrad_kernel<OCT, NPART, true, true>) : go(conv1_bf16x3_wgrad_kernel<OCT, NPART, true, false>);
-    else rb ? go(conv1_bf16x3_wgrad_kernel<OCT, NPART, false, true>) : go(conv1_bf16x3_wgrad_kernel<OCT, NPART, false, false>);
-    return hipGetLastError();
-}
-
 }  // namespace ga3c

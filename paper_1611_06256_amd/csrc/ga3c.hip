@@ -22,6 +22,7 @@
 #include "conv_frame.hpp"
 #include "dense_gemm.hpp"
 #include "conv1_bf16x3.hpp"
+#include "conv1_wgrad_f16.hpp"
 #include "dense_gemm_bf16x6.hpp"
 #include "fc_forward.hpp"
 #include "fc_grads.hpp"
@@ -2949,8 +2950,7 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                                      : spec_matches<SpecP2>(g, l == 0) ? 6
                                      : band_nz > 0 ? 8
                                      : c->band[l] && f32_wgrad_ok(g.C, g.H, g.W, g.S, g.OC) ? 7 : 0;
-            if (kind == 1) nz = conv1_bf16x3_wgrad_blocks(B);
-            else if (kind == 2) nz = conv1_bf16x3_wgrad_blocks(B);
+            if (kind == 1 || kind == 2) nz = conv1_wgrad_blocks(B);
             else if (kind == 3) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
             else if (kind == 4) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
             else if (kind == 5) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
@@ -2978,9 +2978,9 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             }
             STAGE(CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * ((l == 0 ? 1.0 : 4.0) * g.CHW + 4.0 * g.OC * g.OHW));
             if (kind == 1) {
-                HIP_TRY(launch_conv1_bf16x3_wgrad((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
+                HIP_TRY(launch_conv1_wgrad<16>((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
             } else if (kind == 2) {
-                HIP_TRY(launch_conv1_bf16x3_wgrad<32>((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
+                HIP_TRY(launch_conv1_wgrad<32>((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
             } else if (kind == 3) {
                 HIP_TRY(launch_conv_wgrad_bf16x6<SpecS2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 4) {

@@ -154,6 +154,14 @@ __device__ __forceinline__ f16x8 f16_of_bytes(const uint32_t lo, const uint32_t 
                 __builtin_amdgcn_perm(0u, hi, 0x0c030c02u)};
     return v.v;
 }
+// Two bytes, in the low halves of a register's halves, as normal numbers: 1024 + b is 0x6400 | b.
+__device__ __forceinline__ uint32_t f16_pair_of_bytes(const uint32_t b) {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    union { uint32_t u; f16x2 v; } c;
+    c.u = b | 0x64006400u;
+    c.v -= f16x2{1024.f, 1024.f};
+    return c.u;
+}
 constexpr float F16_BYTE_UNIT = 16777216.f;       // what products with such numbers are multiplied by
 
 // A frame of 4 x 84 x 84 bytes in LDS, as it lies in memory, where it comes without passing through registers; NW wavefronts, 16
