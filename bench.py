@@ -89,11 +89,11 @@ KERNELS = {"conv12_fwd": "conv12_f16_kernel (predictions), conv12_fused_fwd_kern
            "conv2_dgrad": "conv_grads_bf16x6_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
            "conv123_fwd": "conv123_f16_kernel", "conv1_fwd": "conv1_bf16x3_fwd_kernel", "conv2_fwd": "conv_fwd_bf16x6_kernel", "conv3_fwd": "conv_fwd_bf16x6_kernel",
            "wgrad_reduce": "reduce_all_kernel", "rmsprop": "rmsprop_kernel", "predict_small": "predict_small_kernel"}
-# bf16 MFMAs executed per nominal one with fp32-grade accuracy (operand split into three bf16 terms); "f32" = the
-# stage runs on the fp32 matrix cores.  conv123_fwd has two float16 terms of every number but the bytes, 2 products in
+# 16-bit MFMAs executed per nominal one with fp32-grade accuracy: 3 or 6 with operands in three bf16 terms, 2 or 3 with two float16
+# terms (the lower figure where one operand is bytes); "f32" = the stage runs on the fp32 matrix cores.  conv123_fwd has 2 products in
 # its first layer and 3 in the others.
-TERMS = {"conv123_fwd": 2.58, "conv1_fwd": 3, "conv2_fwd": 6, "conv3_fwd": 6, "fc_fwd": 6, "fc_wgrad": 6, "fc_dgrad": 6, "conv1_wgrad": 3,
-         "conv2_dgrad": 6, "conv3_dgrad": 6, "conv2_wgrad": 6, "conv3_wgrad": 6}
+TERMS = {"conv123_fwd": 2.58, "conv1_fwd": 3, "conv2_fwd": 6, "conv3_fwd": 6, "fc_fwd": 6, "fc_wgrad": 6, "fc_dgrad": 6, "conv1_wgrad": 2,
+         "conv2_dgrad": 3, "conv3_dgrad": 6, "conv2_wgrad": 3, "conv3_wgrad": 3}
 HBM_STAGES = {"rmsprop", "wgrad_reduce"}
 
 

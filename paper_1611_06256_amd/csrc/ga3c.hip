@@ -2311,12 +2311,12 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
         int nz, kchunk;
         if (c->fast && dense_operand_ok(x, c->flat, c->flat) && dense_operand_ok(wfc, c->flat, c->flat)) {
             // Up to 16 tiles a prediction's fc product takes one block per compute unit: a second one would double the partial
-            // sums that the heads add up one after the other.  One block against two, us a call: larger net 16 frames 42.2 / 44.2,
-            // 128: 45.8 / 48.1; small net 192: 21.3 / 21.7, 256: 21.0 / 22.8.  With more tiles one block would be level or ahead too
-            // (small net 512 frames 27.9 / 28.5, 768: 33.5 / 36.5, 1024: 37.1 / 37.2; larger net 192: 48.7 / 53.3, 256: 50.8 / 51.7,
-            // 512: 73.8 / 73.8); the line stays because a prediction's value enters its segment's update as the bootstrap, and another
-            // rounding of it can move a pre-activation across zero a few updates later (512 agents: gradient 2.5e-4 off in one of 24
-            // updates).  Updates keep one order of sums.
+            // sums that the heads add up one after the other.  One block against two, us a call (the convolutions took longer then): larger
+            // net 16 frames 42.2 / 44.2, 128: 45.8 / 48.1; small net 192: 21.3 / 21.7, 256: 21.0 / 22.8.  With more tiles it depends (small
+            // net 300 frames 22.4 / 23.1, 400: 23.0 / 24.2, 512: 23.9 / 23.6, 768: 28.1 / 28.9; larger net 140: 25.8 / 25.6, 192: 26.5 / 26.7, 256:
+            // 30.2 / 27.6, 300: 41.1 / 42.8); the line stays because of the larger net's 256, and because a prediction's value enters its
+            // segment's update as the bootstrap, and another rounding of it can move a pre-activation across zero a few updates later.
+            // Updates keep one order of sums.
             const int tiles = cdiv(B, 64) * cdiv(c->F, 64);
             pick_split_xcd(tiles, c->flat, nz, kchunk, !keep_zv && tiles <= 16 ? 256 : 512);
             if ((size_t)nz * B * c->F > w.ws_floats) return fail(GA3C_EINVAL, "internal: split-k workspace too small (fc)");

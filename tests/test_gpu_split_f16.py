@@ -162,3 +162,27 @@ def test_gradients_of_the_convolutions(G, which, N, spread, dead):
             close(get(10 + l - 1, *x.shape), torch.nn.grad.conv2d_input(x.shape, w, dy, stride=s) * (x > 0), f"input of conv{l + 1}")
         x = y
     net.close()
+
+
+# The first layer's weight gradient where a block takes all 32 filters of a frame (more than 128 frames) and where it takes 16, in both
+# arithmetics; with rounded operands its sums are of bytes times dY rounded to bfloat16, products that are exact in fp32.  Bound as above.
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("which,N", [("large", 128), ("large", 129), ("large", 515), ("small", 257)])
+def test_first_layers_weight_gradient(G, which, N, math):
+    import torch
+    A = 4
+    desc = network(G, which, A)
+    desc.math = math
+    net = G.Ga3c(desc, 1, N)
+    net.params_init(9400)
+    frames = torch.from_numpy(synth.rectangle_frames(9401, N))
+    tr = {k: torch.from_numpy(v).cuda() for k, v in synth.trajectories(9402, N, 1, A).items()}
+    net.train_step(frames.cuda().view(N, 1, 4, 84, 84), tr["actions"], tr["rewards"] + 0.5, tr["dones"], None, G.HParams())
+    oc = desc.conv[0][0]
+    dy = net.train_debug_get(10, torch.empty((N, oc, 20, 20), device="cuda")).cpu()
+    dy = (dy.bfloat16() if math else dy).double()
+    grad, off = net.params_get(2).cpu().double(), net.offsets()
+    for name, want in (("conv1.W", torch.nn.grad.conv2d_weight(frames.double(), (oc, 4, 8, 8), dy, stride=4) / 255), ("conv1.b", dy.sum((0, 2, 3)))):
+        got = grad[off[name][0]:off[name][0] + want.numel()].view(want.shape)
+        assert float((got - want).norm()) <= 1e-6 * float(want.norm()), name
+    net.close()
