@@ -341,8 +341,8 @@ def main() -> int:
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "timed_blocks": TIMED_BLOCKS,
         "ms_per_step": round(sec * 1e3, 4), "spread_ms_per_step": spread([s * 1e3 for s in secs]),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32" if args.math == 0 else "bf16", "data": "synthetic",
-        "arithmetic": ("fp32 accuracy with fp32 accumulation: fp32 operands split exactly into three bf16 terms on the bf16 "
-                       "MFMA (bytes are exact in bf16)") if args.math == 0 else
+        "arithmetic": ("fp32 accuracy with fp32 accumulation: fp32 operands as three bf16 terms (exact) or two scaled float16 terms "
+                       "(22 bits and a sign) on the 16-bit MFMA; bytes are exact in both") if args.math == 0 else
                       "operands of every contraction rounded to bfloat16, exact products, fp32 accumulation, fp32 parameters",
         "config": {"workload": f"{args.net} net, 18 actions; per step {T}x predict B={N} "
                                f"and 1 train_step {N} agents x t_max={T} = {N * T} frames, "
