@@ -207,7 +207,7 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
         wide[wave] = wave < 2 ? f16_wide_layer(v) : __any(v < 0.f);
     }
     if (tid < N::FILTERS) {
-        consts[0][tid] = fabsf(((const float *)(frag + N::INV))[tid]) * (tid < 32 ? scale * F16_BYTE_UNIT : 1.f);
+        consts[0][tid] = fabsf(((const float *)(frag + N::INV))[tid]) * (tid < 32 ? scale : 1.f);
         consts[1][tid] = tid < 32 ? b1[tid] : tid < 32 + SP2::OC ? b2[tid - 32] : b3[tid - 32 - SP2::OC];
     }
     bound = 1.0001f * (255.f * scale * bound + fmaxf(bb, 0.f));

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
     const float bb = b1[l16];
     if (wave == 0) wide = f16_wide_layer(inv[l16]) || __any(inv[min(lane, 47)] < 0.f);
     if (tid < 48) {
-        consts[0][tid] = fabsf(inv[tid]) * (tid < 16 ? scale * F16_BYTE_UNIT : 1.f);
+        consts[0][tid] = fabsf(inv[tid]) * (tid < 16 ? scale : 1.f);
         consts[1][tid] = tid < 16 ? b1[tid] : b2[tid - 16];
     }
 #pragma unroll

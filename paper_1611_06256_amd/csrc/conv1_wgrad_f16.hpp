@@ -3,9 +3,7 @@
 //   dW[oc][c][u][v] = sum_{i,j} dY[oc][i][j] x[c][4i+u][4j+v],   db[oc] = sum dY[oc][i][j]
 // A byte is exact in float16, and dY is split into two float16 terms under the scale of the largest values that the block has
 // met so far (split_f16.hpp, conv_wgrad_bf16x6.hpp): two products a sum.  Rounded operands (ONE) are one bfloat16 term, and the
-// bytes bfloat16 as well.  (Bytes as subnormal numbers, which cost no conversion, are not good enough here: the instruction drops
-// bits of the running sum that are small against a product of such a number taken as if it were 2^-14, and sums of gradients
-// cancel; dW was 1.2e-6 from 64 bits at 785 frames.)
+// bytes bfloat16 as well.
 //
 // The contraction runs over output pixels, 8 consecutive pixels of a row per
 // lane, so the frame is re-laid in LDS "space to depth": with u = 4a + u',
@@ -148,7 +146,7 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
                         o = uint2{pack_bf16_rne(byte(0), byte(1)), pack_bf16_rne(byte(2), byte(3))};
                     } else {
                         const uint32_t sel = 0x0c040c00u + 0x00010001u * vq;
-                        o = uint2{f16_pair_of_bytes(__builtin_amdgcn_perm(xv[1], xv[0], sel)), f16_pair_of_bytes(__builtin_amdgcn_perm(xv[3], xv[2], sel))};
+                        o = uint2{f16_pair_of_bytes(__builtin_amdgcn_perm(xv[1], xv[0], sel) | 0x64006400u), f16_pair_of_bytes(__builtin_amdgcn_perm(xv[3], xv[2], sel) | 0x64006400u)};
                     }
                     *(uint2 *)(xp + xdst[i] + (vq / 2) * xup[i] + (vq % 2) * (XPLANE + 16)) = o;
                 }

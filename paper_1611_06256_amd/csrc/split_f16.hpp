@@ -147,22 +147,24 @@ __device__ __forceinline__ void split_terms(const float x, const float y, const 
     }
 }
 
-// Eight bytes as float16: a byte's bits are those of the subnormal number b 2^-24, which the matrix instruction takes as it is.
-__device__ __forceinline__ f16x8 f16_of_bytes(const uint32_t lo, const uint32_t hi) {
-    F16x8Bits v;
-    v.u = u32x4{__builtin_amdgcn_perm(0u, lo, 0x0c010c00u), __builtin_amdgcn_perm(0u, lo, 0x0c030c02u), __builtin_amdgcn_perm(0u, hi, 0x0c010c00u),
-                __builtin_amdgcn_perm(0u, hi, 0x0c030c02u)};
-    return v.v;
-}
-// Two bytes, in the low halves of a register's halves, as normal numbers: 1024 + b is 0x6400 | b.
+// Two bytes, in the low halves of a register's halves under 0x64, as float16: 1024 + b is 0x6400 | b.  (A byte's bits alone are those of the
+// subnormal number b 2^-24, which the matrix instruction takes as if it were 2^-14: bits of the running sum that are small against
+// that are dropped, and sums of dark frames were 3e-5 off.)
 __device__ __forceinline__ uint32_t f16_pair_of_bytes(const uint32_t b) {
     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     union { uint32_t u; f16x2 v; } c;
-    c.u = b | 0x64006400u;
+    c.u = b;
     c.v -= f16x2{1024.f, 1024.f};
     return c.u;
 }
-constexpr float F16_BYTE_UNIT = 16777216.f;       // what products with such numbers are multiplied by
+// Eight bytes.
+__device__ __forceinline__ f16x8 f16_of_bytes(const uint32_t lo, const uint32_t hi) {
+    constexpr uint32_t UP = 0x64646464u;
+    F16x8Bits v;
+    v.u = u32x4{f16_pair_of_bytes(__builtin_amdgcn_perm(UP, lo, 0x04010400u)), f16_pair_of_bytes(__builtin_amdgcn_perm(UP, lo, 0x04030402u)),
+                f16_pair_of_bytes(__builtin_amdgcn_perm(UP, hi, 0x04010400u)), f16_pair_of_bytes(__builtin_amdgcn_perm(UP, hi, 0x04030402u))};
+    return v.v;
+}
 
 // A frame of 4 x 84 x 84 bytes in LDS, as it lies in memory, where it comes without passing through registers; NW wavefronts, 16
 // bytes per lane and load.  The last load's lanes behind the frame's end fill the place up with its last bytes.

@@ -186,3 +186,33 @@ def test_first_layers_weight_gradient(G, which, N, math):
         got = grad[off[name][0]:off[name][0] + want.numel()].view(want.shape)
         assert float((got - want).norm()) <= 1e-6 * float(want.norm()), name
     net.close()
+
+
+def err2(x, y):
+    return float(np.linalg.norm(np.asarray(x, np.float64) - y) / np.linalg.norm(y))
+
+
+# Frames of which little is lit, and no bias that would cover it: a byte of 1 counts as much as one of 255.  Bound: five layers of 1e-6 each (TOL above), as norms add up.
+@pytest.mark.parametrize("which,B", [("small", 67), ("large", 3), ("paper4", 3), ("paper3", 3)])
+@pytest.mark.parametrize("what", [1, 3, 15, "dots"])
+def test_predictions_of_dark_frames(G, which, B, what):
+    import torch
+    net, onet, theta = P.make(G, network(G, which, 6), B, 0, 9120)
+    for name, (at, shape) in net.offsets().items():
+        if name.endswith(".b"):
+            theta[at:at + int(np.prod(shape))] = 0
+    net.params_set(torch.from_numpy(theta).cuda(), 0)
+    r = synth.rng(9121)
+    if what == "dots":                 # six pixels of 1 or 2
+        frames = np.zeros((B, 4 * 84 * 84), np.uint8)
+        for b in range(B):
+            frames[b, r.integers(0, 4 * 84 * 84, 6)] = r.integers(1, 3, 6)
+        frames = frames.reshape(B, 4, 84, 84)
+    else:
+        frames = r.integers(0, what + 1, (B, 4, 84, 84)).astype(np.uint8)
+    lg, vl, _, _ = P.run_predict(G, net, frames)
+    ref = orc.forward(onet, theta, frames)
+    e = err2(lg, ref["logits"]), err2(vl, ref["values"])
+    print(f"dark {which} {what}: {e[0]:.2e} {e[1]:.2e}", flush=True)
+    assert max(e) <= 2.5e-6
+    net.close()
