@@ -202,17 +202,21 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
     };
     float bound = ((const float *)(frag + N::SUM))[lane & 31];
     const float bb = b1[lane & 31];
-    if (wave < 3) {
-        const float v = ((const float *)(frag + N::INV))[wave == 0 ? lane & 31 : wave == 1 ? 32 + lane % SP2::OC : 32 + SP2::OC + lane];
-        wide[wave] = wave < 2 ? f16_wide_layer(v) : __any(v < 0.f);
-    }
+    const float v = ((const float *)(frag + N::INV))[wave == 0 ? lane & 31 : wave == 1 ? 32 + lane % SP2::OC : 32 + SP2::OC + lane];
+    const float b2v = b2[lane % SP2::OC];
     if (tid < N::FILTERS) {
         consts[0][tid] = fabsf(((const float *)(frag + N::INV))[tid]) * (tid < 32 ? scale : 1.f);
         consts[1][tid] = tid < 32 ? b1[tid] : tid < 32 + SP2::OC ? b2[tid - 32] : b3[tid - 32 - SP2::OC];
     }
     bound = 1.0001f * (255.f * scale * bound + fmaxf(bb, 0.f));
+    const float top = f16_wave_most(bound);
     float s1, si1;
-    f16_scale(f16_wave_most(bound), s1, si1);
+    f16_scale(top, s1, si1);
+    if (wave < 3) {
+        // of layer 2's channels: the filter's largest weight (2^15 times the reciprocal of its scale; 0: 2^-126) times the largest value it can meet
+        const float size = wave == 0 ? bound : (fabsf(v) <= 1.1754943508222875e-38f ? 0.f : fabsf(v) * 32768.f * top) + fmaxf(b2v, 0.f);
+        wide[wave] = __any(v < 0.f) || (wave < 2 && f16_apart(size));
+    }
     s1 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s1)));
     si1 = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(si1)));
 

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
     const float *inv = (const float *)(frag + G::INV);
     float bound = ((const float *)(frag + G::SUM))[l16];
     const float bb = b1[l16];
-    if (wave == 0) wide = f16_wide_layer(inv[l16]) || __any(inv[min(lane, 47)] < 0.f);
+    const bool marked = __any(inv[min(lane, 47)] < 0.f);
     if (tid < 48) {
         consts[0][tid] = fabsf(inv[tid]) * (tid < 16 ? scale : 1.f);
         consts[1][tid] = tid < 16 ? b1[tid] : b2[tid - 16];
@@ -127,6 +127,7 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
         for (int t = 0; t < 2; ++t) q2[kb][t].u = (frag + G::F2 + ((ot * 8 + kb) * 2 + t) * 64)[lane];
     // layer 1's values are 255 scale = 1 times this at most
     bound = 1.0001f * (255.f * scale * bound + fmaxf(bb, 0.f));
+    if (wave == 0) wide = f16_apart(bound) || marked;
     float s, si;
     f16_scale(f16_wave_most(bound), s, si);
     s = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(s)));

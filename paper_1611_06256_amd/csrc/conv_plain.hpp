@@ -1,5 +1,5 @@
 // A convolution layer as plain sums of fp32 products: what a kernel on two float16 terms (split_f16.hpp) turns to when filters hold weights
-// that the terms do not (F16_WIDE).  A thread per output, hundreds of times slower; nothing that initialisation or training makes of a filter
+// that the terms do not (F16_WIDE), or channels of a map, by their filters and biases, are too far apart for one scale (F16_APART).  A thread per output, hundreds of times slower; nothing that initialisation or training makes of a filter
 // comes here.
 #pragma once
 #include <hip/hip_runtime.h>

@@ -58,13 +58,14 @@ __device__ __forceinline__ float f16_wave_most(float m) {
     return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 0)), __int_as_float(__builtin_amdgcn_readlane(u, 16))),
                  fmaxf(__int_as_float(__builtin_amdgcn_readlane(u, 32)), __int_as_float(__builtin_amdgcn_readlane(u, 48))));
 }
-// Whether a layer's filters, one per lane of a wavefront (some may be there twice), need plain sums: one of them does, or they are of such
-// different sizes that the values of their map would be too far apart.  Filters of zeros don't count.
-__device__ __forceinline__ bool f16_wide_layer(const float inverse) {
-    const float a = fabsf(inverse);
-    const bool none = a <= 1.1754943508222875e-38f;        // 2^-126: zeros
-    const float most = f16_wave_most(a), least = f16_wave_most(none ? 0.f : 1.f / a);
-    return __any(inverse < 0.f) || most * least > 16384.f;
+// Whether channels of a map, one per lane of a wavefront (some may be there twice), are too far apart for one scale: `size` is what a
+// channel's values are of the order of, or at most, the bias of its filter included.  1024: a channel's values are then 2^-10 of the
+// largest ones, 2^-18 in a frame of which little is lit, and still good to 2^-21.  (Filters as they are initialised differ by 1.5 at most.)
+// Channels of zeros don't count.
+constexpr float F16_APART = 1024.f;
+__device__ __forceinline__ bool f16_apart(const float size) {
+    const bool none = size <= 1.1754943508222875e-38f;        // 2^-126: zeros
+    return !(f16_wave_most(size) * f16_wave_most(none ? 0.f : 1.f / size) <= F16_APART);        // infinities are apart
 }
 // The scale of a map whose largest values the eight wavefronts of a block have left in LDS.
 __device__ __forceinline__ void f16_scale_of(const float (&m)[8], float &scale, float &inverse) {

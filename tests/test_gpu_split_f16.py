@@ -216,3 +216,26 @@ def test_predictions_of_dark_frames(G, which, B, what):
     print(f"dark {which} {what}: {e[0]:.2e} {e[1]:.2e}", flush=True)
     assert max(e) <= 2.5e-6
     net.close()
+
+
+# A channel that the next layer does not look at, whose values lie far above all others: their scale is not its.  The first layer's bias, the
+# second one's (the small net's second map stays fp32).  2^9: still one scale, in frames of zeros and ones too.
+@pytest.mark.parametrize("which,B,layer", [("large", 2, 1), ("large", 2, 2), ("paper4", 2, 1), ("paper4", 2, 2), ("paper3", 258, 1), ("paper3", 2, 2),
+                                           ("small", 67, 1)])
+@pytest.mark.parametrize("power", [9, 14, 27])
+def test_predictions_with_a_bias_that_nothing_reads(G, which, B, layer, power):
+    import torch
+    net, onet, theta = P.make(G, network(G, which, 6), B, 0, 9130)
+    at, _ = net.offsets()[f"conv{layer}.b"]
+    theta[at + 5] = 2.0 ** power
+    at, shape = net.offsets()[f"conv{layer + 1}.W"]
+    w = theta[at:at + int(np.prod(shape))].reshape(shape)
+    w[:, 5] = 0
+    net.params_set(torch.from_numpy(theta).cuda(), 0)
+    frames = synth.rectangle_frames(9131, B) >> (7 if power == 9 else 0)
+    lg, vl, _, _ = P.run_predict(G, net, frames)
+    ref = orc.forward(onet, theta, frames)
+    e = err2(lg, ref["logits"]), err2(vl, ref["values"])
+    print(f"bias {which} {layer} {power}: {e[0]:.2e} {e[1]:.2e}", flush=True)
+    assert max(e) <= 2.5e-6
+    net.close()
