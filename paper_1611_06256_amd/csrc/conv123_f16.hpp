@@ -120,17 +120,21 @@ __device__ __forceinline__ void conv123_fragments_block(const float *__restrict_
         sum += dpp_row_f32<0xB1>(sum); sum += dpp_row_f32<0x4E>(sum); sum += dpp_row_f32<0x141>(sum); sum += dpp_row_f32<0x140>(sum);
         if (kb0 == 0 && (tid & 15) == 0) ((float *)(frag + N::SUM))[ot * 16 + (tid >> 4)] = sum;
     }
-    float small = 0.f;
+    // small weights and those that are not zero, counted in one number: 1024 for each of the former
+    float count = 0.f;
 #pragma unroll
     for (int i = 0; i < KMOST / 64; ++i)
-        if (4 * (tid & 15) + 64 * i < K)
-            small += (float)(f16_is_small(all[i].x, m) + f16_is_small(all[i].y, m) + f16_is_small(all[i].z, m) + f16_is_small(all[i].w, m));
-    small += dpp_row_f32<0xB1>(small); small += dpp_row_f32<0x4E>(small); small += dpp_row_f32<0x141>(small); small += dpp_row_f32<0x140>(small);
+        if (4 * (tid & 15) + 64 * i < K) {
+            auto weigh = [&](const float w) { return (float)(1024 * f16_is_small(w, m) + (w != 0.f)); };
+            count += (weigh(all[i].x) + weigh(all[i].y)) + (weigh(all[i].z) + weigh(all[i].w));
+        }
+    count += dpp_row_f32<0xB1>(count); count += dpp_row_f32<0x4E>(count); count += dpp_row_f32<0x141>(count); count += dpp_row_f32<0x140>(count);
+    static_assert(KMOST < 1024, "the count of weights");
     if ((tid & 15) == 0) {
         float s, inv;
         f16_scale(m, s, inv);
         scales[tid >> 4] = s;
-        if (kb0 == 0) ((float *)(frag + N::INV))[first + ot * 16 + (tid >> 4)] = small > (float)F16_WIDE || !(m < __builtin_inff()) ? -inv : inv;
+        if (kb0 == 0) ((float *)(frag + N::INV))[first + ot * 16 + (tid >> 4)] = f16_wide((int)count >> 10, (int)count & 1023) || !(m < __builtin_inff()) ? -inv : inv;
     }
     __syncthreads();
     if (kb >= KB) return;

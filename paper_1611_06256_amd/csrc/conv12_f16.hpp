@@ -46,7 +46,8 @@ __device__ __forceinline__ void conv12_f16_store_filter(u32x4 *__restrict__ frag
     f16_scale(most, s, si);
     const int small = __popcll(__ballot(f16_is_small(v.x, most))) + __popcll(__ballot(f16_is_small(v.y, most))) +
                       __popcll(__ballot(f16_is_small(v.z, most))) + __popcll(__ballot(f16_is_small(v.w, most)));
-    const float stored = small > F16_WIDE || !(most < __builtin_inff()) ? -si : si;
+    const int there = __popcll(__ballot(v.x != 0.f)) + __popcll(__ballot(v.y != 0.f)) + __popcll(__ballot(v.z != 0.f)) + __popcll(__ballot(v.w != 0.f));
+    const float stored = f16_wide(small, there) || !(most < __builtin_inff()) ? -si : si;
     uint32_t h[2], l[2];
     split2_pair(v.x, v.y, s, h[0], l[0]);
     split2_pair(v.z, v.w, s, h[1], l[1]);

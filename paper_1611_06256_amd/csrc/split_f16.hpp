@@ -24,11 +24,13 @@ union F16x8Bits {
     u32x4 u;
 };
 
-// Weights too far apart for that: more than eight of a filter are not zero and below 2^-18 of its largest, or that one is no number.  Such a
-// filter's reciprocal of the scale is stored as a negative number, and kernels that read it take plain sums instead (conv_plain.hpp).
-// (Of normally distributed weights, one in a million is that small.)
+// Weights too far apart for that: of a filter's weights that are not zero, more than eight or more than one in 32 are below 2^-18 of its
+// largest, or that one is no number.  (Where there are few, nothing but small ones may meet an input that is not zero.)  Such a filter's
+// reciprocal of the scale is stored as a negative number, and kernels that read it take plain sums instead (conv_plain.hpp).  Of normally
+// distributed weights, one in a hundred thousand is that small: nine of a filter's 576, once in 10^26 filters.
 constexpr float F16_SMALL = 3.814697265625e-6f;
 constexpr int F16_WIDE = 8;
+__device__ __forceinline__ bool f16_wide(const int small, const int there) { return small > F16_WIDE || 32 * small > there; }
 __device__ __forceinline__ int f16_is_small(const float w, const float most) { return w != 0.f && fabsf(w) < most * F16_SMALL; }
 
 // The power of two by which numbers of magnitude `most` at most are multiplied, and its reciprocal.  Both are normal

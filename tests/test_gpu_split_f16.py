@@ -239,3 +239,35 @@ def test_predictions_with_a_bias_that_nothing_reads(G, which, B, layer, power):
     print(f"bias {which} {layer} {power}: {e[0]:.2e} {e[1]:.2e}", flush=True)
     assert max(e) <= 2.5e-6
     net.close()
+
+
+# Filters of few weights, of which the large ones meet nothing but zeros: what is left is as exact as any.
+@pytest.mark.parametrize("which,B", [("large", 2), ("paper4", 2), ("paper3", 2), ("small", 67)])
+@pytest.mark.parametrize("layer", [1, 2])
+def test_predictions_with_few_weights_in_a_filter(G, which, B, layer):
+    import torch
+    net, onet, theta = P.make(G, network(G, which, 6), B, 0, 9140)
+    off = net.offsets()
+
+    def tensor(name):
+        at, shape = off[name]
+        return theta[at:at + int(np.prod(shape))].reshape(shape)
+
+    w = tensor(f"conv{layer}.W")
+    if layer == 2:                     # channel 0 of the first map stays zero
+        tensor("conv1.W")[0] = 0
+        tensor("conv1.b")[0] = 0
+    keep = w[:, 1, :2, :4].copy()
+    w[:] = 0
+    w[:, 1, :2, :4] = keep
+    w[:, 0, 0, 0] = 2.0 ** 24
+    tensor(f"conv{layer}.b")[:] = 0
+    net.params_set(torch.from_numpy(theta).cuda(), 0)
+    frames = synth.rectangle_frames(9141, B)
+    frames[:, 0] = 0
+    lg, vl, _, _ = P.run_predict(G, net, frames)
+    ref = orc.forward(onet, theta, frames)
+    e = err2(lg, ref["logits"]), err2(vl, ref["values"])
+    print(f"few {which} {layer}: {e[0]:.2e} {e[1]:.2e}", flush=True)
+    assert max(e) <= 2.5e-6
+    net.close()
