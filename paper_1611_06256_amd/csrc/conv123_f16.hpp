@@ -80,7 +80,7 @@ struct Conv123Net {
     static constexpr int B1 = 2 * KB1 / 4, B2 = B1 + OT2 * KB2 / 4, PER3 = (KB3 + 3) / 4, BLOCKS = B2 + 4 * PER3;
     static constexpr int Y = 2 * F16_FRAME, LDS = Y + 2 * (M2::TERM > M3::TERM ? M2::TERM : M3::TERM);
     static_assert(LDS + 2048 <= 160 * 1024, "LDS");
-    static_assert((32 * NPIX1 + SP2::OC * SP2::NPIX) * 4 <= LDS, "the maps of plain sums");
+    static_assert(32 * NPIX1 * 4 + F16_FRAME <= LDS && (32 * NPIX1 + SP2::OC * SP2::NPIX) * 4 <= LDS, "plain sums: the first map, then a frame or the second");
 };
 
 // Block b of N::BLOCKS, 256 threads.  w1, w2, w3: the filter tensors, 16-byte aligned.
@@ -434,15 +434,18 @@ __global__ __launch_bounds__(512, 1) void conv123_f16_kernel(const uint8_t *__re
     }
     store(f - grid);
     if (wide[0] | wide[1] | wide[2]) {                     // my frames once more
-        __syncthreads();
-        float *y1 = (float *)c123_smem, *y2 = y1 + 32 * N::NPIX1;
+        float *y1 = (float *)c123_smem, *y2 = y1 + 32 * N::NPIX1;      // the frame lies in the second map's place first
+        const unsigned char *frame = (const unsigned char *)y2;
         for (f = blockIdx.x; f < nframes; f += grid) {
-            plain_conv_layer(TABLE ? table[f] : x + (size_t)f * CHW, scale, f1, b1, y1, 4, 84, 84, 32, 8, N::S1, tid, 512);
             __syncthreads();
-            plain_conv_layer(y1, 1.f, f2, b2, y2, 32, SP2::H, SP2::W, SP2::OC, 4, 2, tid, 512);
+            f16_frame_to_lds<8>(TABLE ? table[f] : x + (size_t)f * CHW, lds + 32 * N::NPIX1 * 4, wave, lane);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            plain_conv_layer(y2, 1.f, f3, b3, y + (size_t)f * SP3::OC * SP3::NPIX, SP3::C, SP3::H, SP3::W, SP3::OC, SP3::KS, SP3::S, tid, 512);
+            plain_conv_layer<uint8_t, 4, 84, 32, 8, N::S1, 8>(frame, scale, f1, b1, y1, wave, lane);
             __syncthreads();
+            plain_conv_layer<float, 32, SP2::H, SP2::OC, 4, 2, 8>(y1, 1.f, f2, b2, y2, wave, lane);
+            __syncthreads();
+            plain_conv_layer<float, SP3::C, SP3::H, SP3::OC, SP3::KS, SP3::S, 8>(y2, 1.f, f3, b3, y + (size_t)f * SP3::OC * SP3::NPIX, wave, lane);
         }
     }
 }

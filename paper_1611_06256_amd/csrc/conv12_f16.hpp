@@ -259,13 +259,17 @@ __global__ __launch_bounds__(512, 2) void conv12_f16_kernel(const uint8_t *__res
     }
     store(f - grid);
     if (wide) {                                            // my frames once more
-        __syncthreads();
         float *y1 = (float *)c12h_smem;
+        constexpr int AT = 16 * 400 * 4;                   // the frame, behind the first map
+        static_assert(AT + F16_FRAME <= G::LDS, "LDS");
         for (f = blockIdx.x; f < nframes; f += grid) {
-            plain_conv_layer(TABLE ? table[f] : x + (size_t)f * CHW, scale, w1, b1, y1, 4, 84, 84, 16, 8, 4, tid, 512);
             __syncthreads();
-            plain_conv_layer(y1, 1.f, w2, b2, y2 + (size_t)f * 32 * NPIX2, 16, 20, 20, 32, 4, 2, tid, 512);
+            f16_frame_to_lds<NW>(TABLE ? table[f] : x + (size_t)f * CHW, lds + AT, wave, lane);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
+            plain_conv_layer<uint8_t, 4, 84, 16, 8, 4, NW>(c12h_smem + AT, scale, w1, b1, y1, wave, lane);
+            __syncthreads();
+            plain_conv_layer<float, 16, 20, 32, 4, 2, NW>(y1, 1.f, w2, b2, y2 + (size_t)f * 32 * NPIX2, wave, lane);
         }
     }
 }
