@@ -21,11 +21,12 @@
 //
 // Both operands are split into two float16 terms while they are staged, three
 // products a sum (split_f16.hpp); the two small ones have accumulators of their
-// own.  The scales are those of the largest values that the block has met so far
-// (its 16 channels, its filters' dY); where a frame brings larger ones, the sums
-// so far are brought to the new scale.  So a value of 2^-17 of the largest one
-// that goes into the same sums still has its 22 bits, and what is smaller an
-// error of 2^-40 of that one.  Three bfloat16 terms, six products, operands of
+// own.  Every channel and every filter has a scale, by the largest values that
+// the block has met in it so far; where a frame brings larger ones, the sums so
+// far are brought to the new scale.  So a value of 2^-15 of the largest one that
+// goes into the same sums still has its 22 bits, and what is smaller an error of
+// 2^-37 of that one.  The lanes that stage a channel or a filter are neighbours
+// and find its largest value between themselves.  Three bfloat16 terms, six products, operands of
 // the next group read ahead, against this, error of dW in the 2-norm: small net 40
 // frames 1.45e-7 -> 1.34e-7, 2560: 1.8e-7 -> 1.1e-7, larger net 1280: 1.8e-7 -> 1.1e-7
 // (with one accumulator 1.6e-7, 1.6e-7 and 1.9e-7).
@@ -78,12 +79,13 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
     static_assert(SP::H % 2 == 0 && SP::W % 4 == 0 && G::GW % 2 == 0, "rows are read four values at a time; shifts are whole dwords");
     static_assert(G::GW + 9 <= G::WIN, "the window must hold the largest shift plus eight elements");
     static_assert(SP::OW + 1 <= G::GW && SP::OH + 1 <= G::GH, "shifted pixels must stay on the phase grid");
-    static_assert((OCB * SP::NPIX) % 4 == 0 && (G::DTERM % 8) == 0 && (G::PTERM % 8) == 0, "16-byte steps");
+    static_assert((G::DTERM % 8) == 0 && (G::PTERM % 8) == 0, "16-byte steps");
     constexpr int CS = G::CS, GW = G::GW, NKB = G::NKB, DROW = G::DROW, PROW = G::PROW, MT = G::MT;
     constexpr int DTERM = G::DTERM, PTERM = G::PTERM, OTP = G::OTP;
     constexpr int NTERM = ONE ? 1 : 2;
-    constexpr int W4 = SP::W / 4, XV = CS * SP::H * W4, XPT = (XV + 255) / 256;       // float4 of the input slice
-    constexpr int NDV = OCB * SP::NPIX / 4, DPT = (NDV + 255) / 256;                   // float4 of my filters' dY
+    typedef F16Rows<SP::H * SP::W, CS, 256> RX;        // staging: channels of the input slice, my filters' dY
+    typedef F16Rows<SP::NPIX, OCB, 256> RD;
+    constexpr int W4 = SP::W / 4, XPT = RX::PER, DPT = RD::PER;
     constexpr int K1 = SP::K + 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __bf16 *dsm = (__bf16 *)smem;                      // [term][oc][DROW]
@@ -99,21 +101,20 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
 
     // staging descriptors.  Input: float4 item -> (c, y, x = 4q..4q+3): x, x+2 are neighbours in phase column 0 and
     // x+1, x+3 in phase column 1 of phase row y % 2.
+    const int xrow = RX::row(tid), drow = RD::row(tid);
     int xdst[XPT];
 #pragma unroll
     for (int i = 0; i < XPT; ++i) {
-        const int e = min(tid + 256 * i, XV - 1);
-        const int c = e / (SP::H * W4), rem = e % (SP::H * W4), y = rem / W4, q = rem % W4;
-        xdst[i] = ((y % 2) * 2 * CS + c) * PROW + (y / 2) * GW + 2 * q;
+        const int y = RX::at(tid, i) / SP::W, q = RX::at(tid, i) % SP::W / 4;
+        xdst[i] = ((y % 2) * 2 * CS + xrow) * PROW + (y / 2) * GW + 2 * q;
     }
     int ddst[DPT][4];
 #pragma unroll
     for (int i = 0; i < DPT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int el = min(4 * (tid + 256 * i) + j, OCB * SP::NPIX - 1);
-            const int oc = el / SP::NPIX, pix = el % SP::NPIX;
-            ddst[i][j] = oc * DROW + (pix / SP::OW) * GW + pix % SP::OW;
+            const int pix = RD::at(tid, i) + j;
+            ddst[i][j] = drow * DROW + (pix / SP::OW) * GW + pix % SP::OW;
         }
 
     constexpr bool LOW = !ONE;                         // small products have sums of their own
@@ -127,56 +128,43 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
     for (int m = 0; m < MT; ++m) bacc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
     constexpr uint32_t ONES = ONE ? 0x3F803F80u : 0x3C003C00u;
     const u32x4 ones{ONES, ONES, ONES, ONES};
-    __shared__ __attribute__((aligned(16))) float most[2][4];
-    int scales[2] = {F16_NO_SCALE, F16_NO_SCALE};      // exponents: of the input, of dY
+    // exponents of the scales (channels, then filters), and how they have changed with this frame
+    __shared__ __attribute__((aligned(16))) int scales[CS + OCB], steps[CS + OCB];
+    int xe = F16_NO_SCALE, de = F16_NO_SCALE;          // of the channel and the filter that I stage
 
-    float4 xpre[XPT], dpre[DPT];
+    typedef float f32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
+    f32x4_dword_aligned xpre[XPT], dpre[DPT];
     auto fetch = [&](int f) {
-        const float4 *xs = (const float4 *)(x + (size_t)f * SP::CHW + (size_t)c0 * (SP::H * SP::W));
+        const float *xs = x + (size_t)f * SP::CHW + (size_t)(c0 + xrow) * (SP::H * SP::W);
 #pragma unroll
-        for (int i = 0; i < XPT; ++i) xpre[i] = xs[min(tid + 256 * i, XV - 1)];
-        const float4 *ds = (const float4 *)(dy + ((size_t)f * SP::OC + oc0) * SP::NPIX);
+        for (int i = 0; i < XPT; ++i) xpre[i] = *(const f32x4_dword_aligned *)(xs + RX::at(tid, i));
+        const float *ds = dy + ((size_t)f * SP::OC + oc0 + drow) * SP::NPIX;
 #pragma unroll
-        for (int i = 0; i < DPT; ++i) dpre[i] = ds[min(tid + 256 * i, NDV - 1)];
+        for (int i = 0; i < DPT; ++i) dpre[i] = *(const f32x4_dword_aligned *)(ds + RD::at(tid, i));
     };
     int f = bx;
     fetch(min(f, nframes - 1));
     for (; f < nframes; f += nbx) {
-        if constexpr (ONE) __syncthreads();   // the last frame's operands have been read
-        else {
-            int e[2];
-            f16_block_exponents(most, wave, lane, [&](int n, auto fold) {
-                auto four = [&](const float4 v) { fold(v.x); fold(v.y); fold(v.z); fold(v.w); };
-                if (n == 0) {
+        __syncthreads();                      // the last frame's operands have been read
+        if constexpr (!ONE) {
+            auto four = [](const f32x4_dword_aligned v, const auto &fold) { fold(v.x); fold(v.y); fold(v.z); fold(v.w); };
+            const int nx = f16_row_exponent<RX::LANES>(xe, [&](const auto &fold) {
 #pragma unroll
-                    for (int i = 0; i < XPT; ++i) four(xpre[i]);
-                } else {
+                for (int i = 0; i < XPT; ++i) four(xpre[i], fold);
+            });
+            const int nd = f16_row_exponent<RD::LANES>(de, [&](const auto &fold) {
 #pragma unroll
-                    for (int i = 0; i < DPT; ++i) four(dpre[i]);
-                }
-            }, e);
-            // the sums so far come to the scale of the largest values so far
-            const int ex = min(e[0], scales[0]), ed = min(e[1], scales[1]);
-            if (ex + ed != scales[0] + scales[1]) {
-#pragma unroll
-                for (int m = 0; m < MT; ++m)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        bacc[m][r] = ldexpf(bacc[m][r], ed - scales[1]);
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) {
-                            acc[s][m][r] = ldexpf(acc[s][m][r], ex + ed - scales[0] - scales[1]);
-                            if (LOW) low[s][m][r] = ldexpf(low[s][m][r], ex + ed - scales[0] - scales[1]);
-                        }
-                    }
-                scales[0] = ex;
-                scales[1] = ed;
-            }
+                for (int i = 0; i < DPT; ++i) four(dpre[i], fold);
+            });
+            if (tid % RX::LANES == 0) { scales[xrow] = nx; steps[xrow] = nx - xe; }
+            if (tid % RD::LANES == 0) { scales[CS + drow] = nd; steps[CS + drow] = nd - de; }
+            xe = nx;
+            de = nd;
         }
-        const float xscale = f16_power(scales[0]), dscale = f16_power(scales[1]);
+        const float xscale = f16_power(xe), dscale = f16_power(de);
 #pragma unroll
         for (int i = 0; i < XPT; ++i)
-            if (tid + 256 * i < XV) {
+            if (RX::there(tid, i)) {
                 uint32_t t0[2], t1[2];
                 split_terms<ONE>(xpre[i].x, xpre[i].z, xscale, t0);
                 split_terms<ONE>(xpre[i].y, xpre[i].w, xscale, t1);
@@ -188,7 +176,7 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
             }
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
-            if (tid + 256 * i < NDV) {
+            if (RD::there(tid, i)) {
                 uint32_t t0[2], t1[2];
                 split_terms<ONE>(dpre[i].x, dpre[i].y, dscale, t0);
                 split_terms<ONE>(dpre[i].z, dpre[i].w, dscale, t1);
@@ -205,6 +193,27 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
         fetch(min(f + nbx, nframes - 1));
         // the loads above go out before the products start (the compiler would otherwise sink them below the MFMAs)
         __builtin_amdgcn_sched_barrier(0);
+        if (!ONE && f != bx) {                // the sums so far come to the scales of the largest values so far
+            int4 sd[MT];
+            const int sx = steps[l16];
+            int any = sx;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                sd[m] = *(const int4 *)(steps + CS + 16 * m + 4 * g);
+                any |= sd[m].x | sd[m].y | sd[m].z | sd[m].w;
+            }
+            if (__any(any != 0)) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    f16_ldexp4(bacc[m], sd[m], 0);
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) {
+                        f16_ldexp4(acc[s][m], sd[m], sx);
+                        if (LOW) f16_ldexp4(low[s][LOW ? m : 0], sd[m], sx);
+                    }
+                }
+            }
+        }
         u32x4 a[MT][NTERM], win[NTERM][3];
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
@@ -252,14 +261,17 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
         __builtin_amdgcn_s_setprio(0);
     }
     if constexpr (!ONE) {
+        const int sx = 127 - scales[l16];
 #pragma unroll
-        for (int m = 0; m < MT; ++m)
+        for (int m = 0; m < MT; ++m) {
+            const int4 e = *(const int4 *)(scales + CS + 16 * m + 4 * g), back{127 - e.x, 127 - e.y, 127 - e.z, 127 - e.w};
+            f16_ldexp4(bacc[m], back, 0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                bacc[m][r] = ldexpf(bacc[m][r], 127 - scales[1]);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) acc[s][m][r] = ldexpf(LOW ? acc[s][m][r] + low[s][LOW ? m : 0][r] : acc[s][m][r], 254 - scales[0] - scales[1]);
+            for (int s = 0; s < 4; ++s) {
+                if (LOW) acc[s][m] += low[s][LOW ? m : 0];
+                f16_ldexp4(acc[s][m], back, sx);
             }
+        }
     }
     // lane (l16, g), register r of acc[s = 2a + e][m]: filter 16 m + 4 g + r, channel c0 + l16, tap (ry + 2a, rx + 2e).
     // The block's result is put together in LDS and leaves in rows.
@@ -281,7 +293,6 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
             for (int r = 0; r < 4; ++r) ot[(m * 16 + 4 * g + r) * OTP + l16 * 16 + u * 4 + v] = acc[s][m][r];
     }
     __syncthreads();
-    typedef float f32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
     float *pb = part + ((size_t)bx * SP::OC + oc0) * K1 + c0 * 16;
     for (int it = tid; it < OCB * CS * 4; it += 256) {
         const int oc = it / (CS * 4), kq = it % (CS * 4);

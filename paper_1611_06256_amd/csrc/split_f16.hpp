@@ -77,10 +77,52 @@ __device__ __forceinline__ void f16_scale_of(const float (&m)[8], float &scale, 
 
 // ---- Gradients: operands whose magnitude nobody knows before they are there, and sums over several frames.
 //
-// A scale is its biased exponent here, so that it can be undone in one step (v_ldexp_f32), whatever the two operands' scales are.
-constexpr int F16_NO_SCALE = 253;
+// A scale is its biased exponent here, so that it can be undone in one step (v_ldexp_f32), whatever the two operands' scales are.  What is
+// contracted over pixels and frames has one for each row and each column of the product: a filter's dY, a channel's values, so that
+// what is far smaller in one filter or channel than in another loses nothing by it.
+constexpr int F16_NO_SCALE = 253, F16_ROOM = 2;
 __device__ __forceinline__ int f16_exponent(const float most) { return min(268 - (int)(__float_as_uint(most) >> 23 & 0xff), F16_NO_SCALE); }
 __device__ __forceinline__ float f16_power(const int exponent) { return __uint_as_float((uint32_t)exponent << 23); }
+__device__ __forceinline__ void f16_ldexp4(floatx4 &a, const int4 e, const int more) {
+    a[0] = ldexpf(a[0], e.x + more); a[1] = ldexpf(a[1], e.y + more); a[2] = ldexpf(a[2], e.z + more); a[3] = ldexpf(a[3], e.w + more);
+}
+
+// ROWS rows of R numbers, one behind the other, that NTHR threads stage: so many neighbouring lanes have a row, four numbers at a time.  The
+// last four of a row whose length is no multiple of four overlap the ones before them.
+template <int R, int ROWS, int NTHR>
+struct F16Rows {
+    static constexpr int LANES = NTHR / ROWS, UNITS = (R + 3) / 4, PER = (UNITS + LANES - 1) / LANES;
+    static_assert(LANES * ROWS == NTHR && 64 % LANES == 0 && R >= 4, "whole wavefronts of whole rows");
+    __device__ static int row(int tid) { return tid / LANES; }
+    __device__ static bool there(int tid, int i) { return UNITS % LANES == 0 || tid % LANES + LANES * i < UNITS; }
+    __device__ static int at(int tid, int i) { return min(4 * (tid % LANES + LANES * i), R - 4); }           // the first of my numbers in the row
+};
+// The largest of a row's lanes.
+template <int LANES>
+__device__ __forceinline__ float f16_row_most(float m) {
+    if constexpr (LANES == 64) return f16_wave_most(m);
+    if constexpr (LANES >= 2) m = fmaxf(m, dpp_row_f32<0xB1>(m));
+    if constexpr (LANES >= 4) m = fmaxf(m, dpp_row_f32<0x4E>(m));
+    if constexpr (LANES >= 8) m = fmaxf(m, dpp_row_f32<0x141>(m));
+    if constexpr (LANES >= 16) m = fmaxf(m, dpp_row_f32<0x140>(m));
+    if constexpr (LANES >= 32) m = fmaxf(m, __shfl_xor(m, 16));
+    return m;
+}
+// The exponent of my row's scale, which has been `e`: where that is too large for what all(fold) folds, one that leaves room for four
+// times as much, so that few frames change it.  Infinities don't count (in a second look, which only they cost), NaN never do.
+template <int LANES, class All>
+__device__ __forceinline__ int f16_row_exponent(const int e, const All &all) {
+    float m = 0.f;
+    all([&](const float v) { m = fmaxf(m, fabsf(v)); });
+    m = f16_row_most<LANES>(m);
+    if (__any(m == __builtin_inff())) {
+        m = 0.f;
+        all([&](const float v) { const float a = fabsf(v); m = fmaxf(m, a < __builtin_inff() ? a : 0.f); });
+        m = f16_row_most<LANES>(m);
+    }
+    const int need = f16_exponent(m);
+    return need < e ? need - F16_ROOM : e;
+}
 
 // Scale exponents of N sets of values that a block of NW wavefronts is about to split: at(n, fold) folds the calling thread's values
 // of set n.  `most` lies in LDS; a barrier of the block comes in front of its next use.  Infinities don't count (in a second look, which

@@ -271,3 +271,65 @@ def test_predictions_with_few_weights_in_a_filter(G, which, B, layer):
     print(f"few {which} {layer}: {e[0]:.2e} {e[1]:.2e}", flush=True)
     assert max(e) <= 2.5e-6
     net.close()
+
+
+# Gradients of a network one of whose channels is 2^`power` times the others, which the next layer undoes: every filter's and every input
+# channel's part has the error of a sum of fp32 products, not that of the largest.  Each layer from what the update left, in 64 bits; bound
+# as in test_gradients_of_the_convolutions, for parts.
+@pytest.mark.parametrize("which,N,layer", [(w, n, l) for w in ("small", "large", "paper4") for n in (1, 157) for l in (1, 2, 3) if w != "small" or l < 3])
+@pytest.mark.parametrize("power", [24, -24])
+def test_gradients_with_a_channel_of_another_size(G, which, N, layer, power):
+    import torch
+    A, T = 6, 5
+    B = N * T
+    net, onet, theta = P.make(G, network(G, which, A), 1, B, 9350 + N)
+    off = net.offsets()
+
+    def tensor(name, *shape):
+        at, sh = off[name]
+        return theta[at:at + int(np.prod(sh))].reshape(shape or sh)
+
+    def times(part, p):
+        part *= np.float32(2.0 ** p)
+
+    times(tensor(f"conv{layer}.W")[3], power)
+    times(tensor(f"conv{layer}.b")[3:4], power)
+    if f"conv{layer + 1}.W" in off:
+        times(tensor(f"conv{layer + 1}.W")[:, 3], -power)
+    else:
+        oc = onet.conv[layer - 1][0]
+        times(tensor("fc.W", off["fc.W"][1][0], oc, -1)[:, 3], -power)
+    net.params_set(torch.from_numpy(theta).cuda(), 0)
+    frames = synth.rectangle_frames(9351 + N, B).reshape(B, 4, 84, 84)
+    tr = synth.trajectories(9352 + N, N, T, A)
+    print(f"gradients {which} N={N} layer={layer} power={power}", flush=True)
+    net.train_step(torch.from_numpy(frames).cuda().view(N, T, 4, 84, 84), torch.from_numpy(tr["actions"]).cuda(),
+                   torch.from_numpy(tr["rewards"] + np.float32(0.5)).cuda(), torch.from_numpy(tr["dones"]).cuda(), None, G.HParams())
+
+    def get(which, *shape):
+        return net.train_debug_get(which, torch.empty(int(np.prod(shape)), device="cuda")).cpu().double().view(shape)
+
+    def worst(got, want, dim):
+        other = [d for d in range(want.dim()) if d != dim]
+        d, n = (got - want).pow(2).sum(other).sqrt(), want.pow(2).sum(other).sqrt()
+        assert torch.isfinite(got).all()
+        return float((d[n > 0] / n[n > 0]).max())
+
+    x, grad, errors = torch.from_numpy(frames).double() / 255, net.params_get(2).cpu().double(), {}
+    for l, (oc, k, s) in enumerate(onet.conv):
+        oh = (x.shape[-1] - k) // s + 1
+        y, dy = get(4 + l, B, oc, oh, oh), get(10 + l, B, oc, oh, oh)
+        at, shape = off[f"conv{l + 1}.W"]
+        n = int(np.prod(shape))
+        got, want = grad[at:at + n].view(*shape), torch.nn.grad.conv2d_weight(x, tuple(shape), dy, stride=s)
+        errors[f"conv{l + 1}.W filter"], errors[f"conv{l + 1}.W channel"] = worst(got, want, 0), worst(got, want, 1)
+        at_b = off[f"conv{l + 1}.b"][0]
+        errors[f"conv{l + 1}.b"] = worst(grad[at_b:at_b + oc][:, None], dy.sum((0, 2, 3))[:, None], 1)
+        if l:
+            w = torch.from_numpy(theta[at:at + n]).double().view(*shape)
+            errors[f"input of conv{l + 1}"] = worst(get(10 + l - 1, *x.shape), torch.nn.grad.conv2d_input(x.shape, w, dy, stride=s) * (x > 0), 1)
+        x = y
+    print("  " + ", ".join(f"{k} {v:.1e}" for k, v in errors.items()), flush=True)
+    off_by = {k: v for k, v in errors.items() if v > 2e-6 and k.startswith("conv2")}
+    assert not off_by, off_by
+    net.close()
