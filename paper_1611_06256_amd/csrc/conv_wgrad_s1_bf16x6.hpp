@@ -19,8 +19,8 @@
 // 16-byte load each gained nothing: 1280 frames 30.5 us, 31.1 with the latter.)
 //
 // Both operands are split into two float16 terms while they are staged, three
-// products a sum, under the scales of the largest values that the block has met
-// so far (split_f16.hpp, conv_wgrad_bf16x6.hpp).  With three bfloat16 terms, six
+// products a sum, under scales for every channel and every filter, by the largest
+// values that the block has met so far (split_f16.hpp, conv_wgrad_bf16x6.hpp).  With three bfloat16 terms, six
 // products, 1280 frames took 37.5 us instead of 29.7; error of dW in the 2-norm
 // 1.27e-7 both (320 frames 1.42e-7 -> 1.40e-7).  There is no room for accumulators of the small products.
 //
@@ -64,13 +64,14 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     static_assert(SP::S == 1 && SP::C == 64 && SP::OC % 32 == 0, "stride 1, 64 channels in (16 per wavefront), filters in groups of 32");
     static_assert(G::SHIFT + 8 <= G::WIN && G::NKB * 32 - 8 + G::WIN <= G::PROW, "the window holds every shift and stays in its row");
     static_assert(SP::H * SP::W <= G::PROW, "a plane fits its row");
-    static_assert((SP::CHW % 4) == 0 && (32 * SP::NPIX) % 4 == 0 && (G::DTERM % 8) == 0 && (G::PTERM % 8) == 0, "16-byte steps");
+    static_assert((G::DTERM % 8) == 0 && (G::PTERM % 8) == 0, "16-byte steps");
     static_assert((G::PROW / 2) % 8 == 4 && (G::DROW / 2) % 8 == 4, "rows of an odd number of 16-byte units");
     constexpr int MS = G::MS, NKB = G::NKB, DROW = G::DROW, PROW = G::PROW, KS = SP::KS, NTAP = KS * KS;
     constexpr int DTERM = G::DTERM, PTERM = G::PTERM, OTP = G::OTP, HW = SP::H * SP::W;
     constexpr int NTERM = ONE ? 1 : 2;
-    constexpr int XV = SP::CHW / 4, XPT = (XV + 255) / 256;                // float4 of the input frame
-    constexpr int NDV = MS * 16 * SP::NPIX / 4, DPT = (NDV + 255) / 256;    // float4 of my filters' dY
+    typedef F16Rows<HW, SP::C, 256> RX;                                    // staging: channels of the input frame, my filters' dY
+    typedef F16Rows<SP::NPIX, MS * 16, 256> RD;
+    constexpr int XPT = RX::PER, DPT = RD::PER;
     constexpr int K1 = SP::K + 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __bf16 *dsm = (__bf16 *)smem;                      // [term][oc][DROW]
@@ -84,21 +85,14 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     for (int e = tid; e < NTERM * (DTERM + PTERM) / 8; e += 256) ((u32x4 *)smem)[e] = u32x4{0u, 0u, 0u, 0u};   // padding stays zero
 
     // staging descriptors: element -> its place in LDS (term 0)
-    int xdst[XPT][4], ddst[DPT][4];
-#pragma unroll
-    for (int i = 0; i < XPT; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int el = min(4 * (tid + 256 * i) + j, SP::CHW - 1);
-            xdst[i][j] = (el / HW) * PROW + el % HW;
-        }
+    const int xrow = RX::row(tid), drow = RD::row(tid);
+    int ddst[DPT][4];
 #pragma unroll
     for (int i = 0; i < DPT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int el = min(4 * (tid + 256 * i) + j, MS * 16 * SP::NPIX - 1);
-            const int oc = el / SP::NPIX, pix = el % SP::NPIX;
-            ddst[i][j] = oc * DROW + (pix / SP::OW) * SP::W + pix % SP::OW;
+            const int pix = RD::at(tid, i) + j;
+            ddst[i][j] = drow * DROW + (pix / SP::OW) * SP::W + pix % SP::OW;
         }
 
     floatx4 acc[NTAP][MS], bacc[MS];
@@ -110,19 +104,21 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     }
     constexpr uint32_t ONES = ONE ? 0x3F803F80u : 0x3C003C00u;
     const u32x4 ones{ONES, ONES, ONES, ONES};
-    __shared__ __attribute__((aligned(16))) float most[2][4];
-    int scales[2] = {F16_NO_SCALE, F16_NO_SCALE};      // exponents: of the input, of dY
+    // exponents of the scales (channels, then filters), and how they have changed with this frame
+    __shared__ __attribute__((aligned(16))) int scales[SP::C + MS * 16], steps[SP::C + MS * 16];
+    int xe = F16_NO_SCALE, de = F16_NO_SCALE;          // of the channel and the filter that I stage
 
-    float4 xpre[XPT], dpre[DPT];
+    typedef float f32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
+    f32x4_dword_aligned xpre[XPT], dpre[DPT];
     auto fetch = [&](int f) {
-        const float4 *xs = (const float4 *)(x + (size_t)f * SP::CHW);
+        const float *xs = x + (size_t)f * SP::CHW + xrow * HW;
 #pragma unroll
-        for (int i = 0; i < XPT; ++i) xpre[i] = xs[min(tid + 256 * i, XV - 1)];
-        const float4 *ds = (const float4 *)(dy + ((size_t)f * SP::OC + oc0) * SP::NPIX);
+        for (int i = 0; i < XPT; ++i) xpre[i] = *(const f32x4_dword_aligned *)(xs + RX::at(tid, i));
+        const float *ds = dy + ((size_t)f * SP::OC + oc0 + drow) * SP::NPIX;
 #pragma unroll
-        for (int i = 0; i < DPT; ++i) dpre[i] = ds[min(tid + 256 * i, NDV - 1)];
+        for (int i = 0; i < DPT; ++i) dpre[i] = *(const f32x4_dword_aligned *)(ds + RD::at(tid, i));
     };
-    auto stash4 = [&](const float4 v, float scale, __bf16 *base, int tstride, const int (&dst)[4]) {
+    auto stash4 = [&](const f32x4_dword_aligned v, float scale, __bf16 *base, int tstride, const int (&dst)[4]) {
         uint32_t t0[2], t1[2];
         split_terms<ONE>(v.x, v.y, scale, t0);
         split_terms<ONE>(v.z, v.w, scale, t1);
@@ -138,45 +134,55 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     int f = blockIdx.x;
     fetch(min(f, nframes - 1));
     for (; f < nframes; f += gridDim.x) {
-        if constexpr (ONE) __syncthreads();   // the last frame's operands have been read
-        else {
-            int e[2];
-            f16_block_exponents(most, wave, lane, [&](int n, auto fold) {
-                auto four = [&](const float4 v) { fold(v.x); fold(v.y); fold(v.z); fold(v.w); };
-                if (n == 0) {
+        __syncthreads();                      // the last frame's operands have been read
+        if constexpr (!ONE) {
+            auto four = [](const f32x4_dword_aligned v, const auto &fold) { fold(v.x); fold(v.y); fold(v.z); fold(v.w); };
+            const int nx = f16_row_exponent<RX::LANES>(xe, [&](const auto &fold) {
 #pragma unroll
-                    for (int i = 0; i < XPT; ++i) four(xpre[i]);
-                } else {
+                for (int i = 0; i < XPT; ++i) four(xpre[i], fold);
+            });
+            const int nd = f16_row_exponent<RD::LANES>(de, [&](const auto &fold) {
 #pragma unroll
-                    for (int i = 0; i < DPT; ++i) four(dpre[i]);
-                }
-            }, e);
-            // the sums so far come to the scale of the largest values so far
-            const int ex = min(e[0], scales[0]), ed = min(e[1], scales[1]);
-            if (ex + ed != scales[0] + scales[1]) {
-#pragma unroll
-                for (int m = 0; m < MS; ++m)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        bacc[m][r] = ldexpf(bacc[m][r], ed - scales[1]);
-#pragma unroll
-                        for (int s = 0; s < NTAP; ++s) acc[s][m][r] = ldexpf(acc[s][m][r], ex + ed - scales[0] - scales[1]);
-                    }
-                scales[0] = ex;
-                scales[1] = ed;
-            }
+                for (int i = 0; i < DPT; ++i) four(dpre[i], fold);
+            });
+            if (tid % RX::LANES == 0) { scales[xrow] = nx; steps[xrow] = nx - xe; }
+            if (tid % RD::LANES == 0) { scales[SP::C + drow] = nd; steps[SP::C + drow] = nd - de; }
+            xe = nx;
+            de = nd;
         }
-        const float xscale = f16_power(scales[0]), dscale = f16_power(scales[1]);
+        const float xscale = f16_power(xe), dscale = f16_power(de);
 #pragma unroll
         for (int i = 0; i < XPT; ++i)
-            if (tid + 256 * i < XV) stash4(xpre[i], xscale, psm, PTERM, xdst[i]);
+            if (RX::there(tid, i)) {
+                const int to = xrow * PROW + RX::at(tid, i);
+                const int at[4] = {to, to + 1, to + 2, to + 3};
+                stash4(xpre[i], xscale, psm, PTERM, at);
+            }
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
-            if (tid + 256 * i < NDV) stash4(dpre[i], dscale, dsm, DTERM, ddst[i]);
+            if (RD::there(tid, i)) stash4(dpre[i], dscale, dsm, DTERM, ddst[i]);
         __syncthreads();
         fetch(min(f + (int)gridDim.x, nframes - 1));
         // the loads above go out before the products start (the compiler would otherwise sink them below the MFMAs)
         __builtin_amdgcn_sched_barrier(0);
+        if (!ONE && f != (int)blockIdx.x) {   // the sums so far come to the scales of the largest values so far
+            int4 sd[MS];
+            const int sx = steps[16 * wave + l16];
+            int any = sx;
+#pragma unroll
+            for (int m = 0; m < MS; ++m) {
+                sd[m] = *(const int4 *)(steps + SP::C + 16 * m + 4 * g);
+                any |= sd[m].x | sd[m].y | sd[m].z | sd[m].w;
+            }
+            if (__any(any != 0)) {
+#pragma unroll
+                for (int m = 0; m < MS; ++m) {
+                    f16_ldexp4(bacc[m], sd[m], 0);
+#pragma unroll
+                    for (int s = 0; s < NTAP; ++s) f16_ldexp4(acc[s][m], sd[m], sx);
+                }
+            }
+        }
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
@@ -231,20 +237,19 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
         __builtin_amdgcn_s_setprio(0);
     }
     if constexpr (!ONE) {
+        const int sx = 127 - scales[16 * wave + l16];
 #pragma unroll
-        for (int m = 0; m < MS; ++m)
+        for (int m = 0; m < MS; ++m) {
+            const int4 e = *(const int4 *)(scales + SP::C + 16 * m + 4 * g), back{127 - e.x, 127 - e.y, 127 - e.z, 127 - e.w};
+            f16_ldexp4(bacc[m], back, 0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                bacc[m][r] = ldexpf(bacc[m][r], 127 - scales[1]);
-#pragma unroll
-                for (int s = 0; s < NTAP; ++s) acc[s][m][r] = ldexpf(acc[s][m][r], 254 - scales[0] - scales[1]);
-            }
+            for (int s = 0; s < NTAP; ++s) f16_ldexp4(acc[s][m], back, sx);
+        }
     }
     // lane (l16, g), register r of acc[tap][m]: filter oc0 + 16 m + 4 g + r, channel 16 wave + l16.  One filter tile at a
     // time is put together in LDS and leaves in rows.
     __shared__ float bsh[4][MS * 16];                  // bias sums of the four wavefronts
     float *ot = (float *)smem;                         // [16 filters][OTP]
-    typedef float f32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
     for (int m = 0; m < MS; ++m) {
         __syncthreads();
