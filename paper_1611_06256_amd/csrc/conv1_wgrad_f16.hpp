@@ -1,8 +1,8 @@
 // Weight and bias gradient of the first convolution layer (8x8 filters, stride 4, on 4x84x84 byte frames) on the 16-bit
 // matrix cores at fp32 accuracy:
 //   dW[oc][c][u][v] = sum_{i,j} dY[oc][i][j] x[c][4i+u][4j+v],   db[oc] = sum dY[oc][i][j]
-// A byte is exact in float16, and dY is split into two float16 terms under the scale of the largest values that the block has
-// met so far (split_f16.hpp, conv_wgrad_bf16x6.hpp): two products a sum.  Rounded operands (ONE) are one bfloat16 term, and the
+// A byte is exact in float16, and dY is split into two float16 terms, every filter's under the scale of the largest values that the block
+// has met in it so far (split_f16.hpp, conv_wgrad_bf16x6.hpp): two products a sum.  Rounded operands (ONE) are one bfloat16 term, and the
 // bytes bfloat16 as well.
 //
 // The contraction runs over output pixels, 8 consecutive pixels of a row per
@@ -45,14 +45,16 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
     constexpr int NPART = 4, NTHR = 256 * NPART;           // NPART wavefronts per SIMD, so that one's LDS and
                                                            // staging work fills another's MFMA waits
     constexpr int NITEM = 336 * 6, IPT = (NITEM + NTHR - 1) / NTHR;    // (frame row, group of 4 dwords)
-    constexpr int NDV = OC * NPIX / 4, DPT = (NDV + NTHR - 1) / NTHR;  // float4 of dY per frame
+    typedef F16Rows<NPIX, OC, NTHR> RD;                    // staging: my filters' dY
+    constexpr int NDV = OC * NPIX / 4, DPT = RD::PER;      // float4 of dY per frame
     constexpr int NSTEP = OH * 3 / 4;                      // 60 blocks of 8 pixels, 4 per MFMA
     constexpr int XCH = (NPART - 1) * 4 * MT * 16 * 64;    // floats: sums that three of the four parts hand over
     static_assert(OCT % OC == 0 && OC % 16 == 0 && 16 * OC <= NTHR, "whole tiles of 16 filters, 16 lanes for each one's bias");
     constexpr int STAGE_BYTES = (XALL + NTERM * OC * DOC) * 2, SMEM = STAGE_BYTES > 4 * XCH ? STAGE_BYTES : 4 * XCH;
     __shared__ __attribute__((aligned(16))) uint16_t xp[SMEM / 2];
     __shared__ float bsh[NDV];
-    __shared__ __attribute__((aligned(16))) float most[1][NTHR / 64];
+    // exponents of the filters' scales, and how they have changed with this frame
+    __shared__ __attribute__((aligned(16))) int scales[OC], steps[OC];
     uint16_t *dp = xp + XALL;                              // [term][filter][DOC]
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -76,13 +78,10 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
         xdst[i] = ((c * 4 + r % 4) * 4) * XPLANE + 4 * (r % 4) * 8 + (r / 4) * XROW + 4 * gq;   // plane (c, u'=r%4, v'=0)
         xup[i] = 2 * XPLANE + (r % 4 < 2 ? 64 : -64);
     }
+    const int drow = RD::row(tid);
     int ddst[DPT];
 #pragma unroll
-    for (int i = 0; i < DPT; ++i) {
-        const int e = min(tid + NTHR * i, NDV - 1);
-        const int oc = e / (NPIX / 4), pq = e % (NPIX / 4);           // 5 float4 per row of 20
-        ddst[i] = oc * DOC + (pq / 5) * DROW + 4 * (pq % 5);
-    }
+    for (int i = 0; i < DPT; ++i) ddst[i] = drow * DOC + RD::at(tid, i) / OH * DROW + RD::at(tid, i) % OH;       // 5 float4 per row of 20
 
     floatx4 acc[MT][2][2];
 #pragma unroll
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
 #pragma unroll
             for (int b = 0; b < 2; ++b) acc[m][a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
     float bsum = 0.f;
-    int exponent = F16_NO_SCALE;                           // of dY's scale
+    int exponent = F16_NO_SCALE;                           // of the filter that I stage
 
     typedef uint32_t u32x4_dword_aligned __attribute__((ext_vector_type(4), aligned(4)));
     u32x4 xpre[IPT];
@@ -101,9 +100,9 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
         const uint32_t *xs = (const uint32_t *)at;
 #pragma unroll
         for (int i = 0; i < IPT; ++i) xpre[i] = *(const u32x4_dword_aligned *)(xs + xsrc[i]);
-        const float4 *ds = (const float4 *)(dy + ((size_t)ff * OCT + oc0) * NPIX);
+        const float *ds = dy + ((size_t)ff * OCT + oc0 + drow) * NPIX;
 #pragma unroll
-        for (int i = 0; i < DPT; ++i) dpre[i] = ds[min(tid + NTHR * i, NDV - 1)];
+        for (int i = 0; i < DPT; ++i) dpre[i] = *(const float4 *)(ds + RD::at(tid, i));
     };
     int f = blockIdx.x;
     FramePointer<TABLE> next;
@@ -113,24 +112,14 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
     const int ch = wave & 3, prt = wave >> 2;        // wavefronts w, w + 4, ... share channel w and divide the pixel blocks
     const uint16_t *xq = xp + (ch * 16 + l16) * XPLANE + 8 * ((4 * (l16 >> 2) + (l16 & 1) * 2 + (l16 & 2) * 4) & 15);      // my plane
     for (; f < nframes; f += gridDim.x) {
-        if constexpr (ONE) __syncthreads();          // the last frame's operands have been read
-        else {
-            int e[1];
-            f16_block_exponents(most, wave, lane, [&](int, auto fold) {
+        __syncthreads();                             // the last frame's operands have been read
+        if constexpr (!ONE) {
+            const int need = f16_row_exponent<RD::LANES>(exponent, [&](const auto &fold) {
 #pragma unroll
                 for (int i = 0; i < DPT; ++i) { fold(dpre[i].x); fold(dpre[i].y); fold(dpre[i].z); fold(dpre[i].w); }
-            }, e);
-            if (e[0] < exponent) {                   // the sums so far come to the scale of the largest values so far
-#pragma unroll
-                for (int m = 0; m < MT; ++m)
-#pragma unroll
-                    for (int a = 0; a < 2; ++a)
-#pragma unroll
-                        for (int b = 0; b < 2; ++b)
-#pragma unroll
-                            for (int r = 0; r < 4; ++r) acc[m][a][b][r] = ldexpf(acc[m][a][b][r], e[0] - exponent);
-                exponent = e[0];
-            }
+            });
+            if (tid % RD::LANES == 0) { scales[drow] = need; steps[drow] = need - exponent; }
+            exponent = need;
         }
         const float dscale = f16_power(exponent);
 #pragma unroll
@@ -154,7 +143,7 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
         }
 #pragma unroll
         for (int i = 0; i < DPT; ++i) {
-            if (tid + NTHR * i < NDV) {
+            if (RD::there(tid, i)) {
                 const float4 v = dpre[i];
                 uint32_t t0[2], t1[2];
                 split_terms<ONE>(v.x, v.y, dscale, t0);
@@ -163,13 +152,30 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
                 for (int term = 0; term < NTERM; ++term) *(uint2 *)(dp + term * OC * DOC + ddst[i]) = uint2{t0[term], t1[term]};
                 auto low = [](uint32_t u) { return __uint_as_float(u << 16); };
                 auto high = [](uint32_t u) { return __uint_as_float(u & 0xffff0000u); };
-                bsh[tid + NTHR * i] = ONE ? (low(t0[0]) + high(t0[0])) + (low(t1[0]) + high(t1[0])) : (v.x + v.y) + (v.z + v.w);
+                bsh[drow * (NPIX / 4) + RD::at(tid, i) / 4] = ONE ? (low(t0[0]) + high(t0[0])) + (low(t1[0]) + high(t1[0])) : (v.x + v.y) + (v.z + v.w);
             }
         }
         __syncthreads();
         if (!TABLE) next.ask(x, table, min(f + (int)gridDim.x, nframes - 1), CHW);
         fetch(next.get(), min(f + (int)gridDim.x, nframes - 1));
         if (TABLE) next.ask(x, table, min(f + 2 * (int)gridDim.x, nframes - 1), CHW);
+        if (!ONE && f != (int)blockIdx.x) {          // the sums so far come to the scales of the largest values so far
+            int4 sd[MT];
+            int any = 0;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                sd[m] = *(const int4 *)(steps + 16 * m + 4 * g);
+                any |= sd[m].x | sd[m].y | sd[m].z | sd[m].w;
+            }
+            if (__any(any != 0)) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int a = 0; a < 2; ++a)
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) f16_ldexp4(acc[m][a][b], sd[m], 0);
+            }
+        }
         if (tid < 16 * OC) {   // bias: 16 lanes share a filter, 100 partial sums each
             const int oc = tid / 16, pt = tid % 16;
             float sum = 0.f;
@@ -236,17 +242,18 @@ __global__ __launch_bounds__(1024) void conv1_wgrad_kernel(const uint8_t *__rest
                     for (int r = 0; r < 4; ++r) acc[m][a][b][r] += xch[at(q, m, a, b, r)];
     // lane (l16, g), register r of acc[m][a][b]: filter 16 m + 4g + r, tap (c = wave, u = 4a + l16/4, v = 4b + l16%4)
 #pragma unroll
-    for (int m = 0; m < MT; ++m)
+    for (int m = 0; m < MT; ++m) {
+        const int4 e = ONE ? int4{127, 127, 127, 127} : *(const int4 *)(scales + 16 * m + 4 * g), back{127 - e.x, 127 - e.y, 127 - e.z, 127 - e.w};
 #pragma unroll
         for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < 2; ++b) {
+                if constexpr (!ONE) f16_ldexp4(acc[m][a][b], back, 0);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float v = acc[m][a][b][r];
-                    pb[(16 * m + 4 * g + r) * (K + 1) + ch * 64 + (4 * a + l16 / 4) * 8 + 4 * b + l16 % 4] =
-                        (ONE ? v : ldexpf(v, 127 - exponent)) * scale;
-                }
+                for (int r = 0; r < 4; ++r)
+                    pb[(16 * m + 4 * g + r) * (K + 1) + ch * 64 + (4 * a + l16 / 4) * 8 + 4 * b + l16 % 4] = acc[m][a][b][r] * scale;
+            }
+    }
 }
 
 inline int conv1_wgrad_blocks(int nframes) { return nframes < 256 ? nframes : 256; }
