@@ -13,8 +13,14 @@
 // stored with full-width writes.  A block computes 16 input channels,
 // 16 by .. (C / 16 slices), of frames bx, + nbx, ...
 //
-// Both operands are split into two float16 terms, three products a sum (split_f16.hpp): dY under a scale of its own for each frame,
-// the filters for each input channel.  The contraction index is ordered (tap, oc), and dY sits in
+// Both operands are split into
+// three bf16 terms (x = hi + mid + lo exactly) and a product is evaluated as the
+// six largest of the nine term products (dense_gemm_bf16x6.hpp), on
+// v_mfma_f32_16x16x32_bf16: 6 x 16 cycles per 32 k instead of 8 x 32 on the
+// fp32 instruction.  (Two float16 terms, three products, took 1.5 % less of the larger
+// net's update, but the contraction runs over filters here: one whose gradients are 2^24
+// times another's takes the other's bits, although their filters may make the two count
+// alike.  No scale of a row or a column of the product can help there.)  The contraction index is ordered (tap, oc), and dY sits in
 // LDS as [padded pixel][oc] per term, so the 8 consecutive k a lane feeds to an
 // MFMA are 8 consecutive filters of one pixel: one 16-byte LDS read per term.
 // The pixel pitch (lds_row_units) and a padded grid as wide as the phase grid spread
@@ -32,7 +38,7 @@
 #include "launch.hpp"
 #include <stdint.h>
 
-#include "split_f16.hpp"
+#include "conv1_bf16x3.hpp"
 
 namespace ga3c {
 
@@ -64,7 +70,7 @@ struct ConvDgradBf16Geom {
     static constexpr int PIT = 16 * lds_row_units(SP::OC / 8);     // bytes per padded pixel and term
     static constexpr int PLANE = PPIX * PIT;
     static constexpr int NX = CS * SP::H * SP::W;
-    __host__ __device__ static constexpr int lds_bytes(bool one) { return (one ? 1 : 2) * PLANE + NX * 4; }
+    __host__ __device__ static constexpr int lds_bytes(bool one) { return (one ? 1 : 3) * PLANE + NX * 4; }
     // ready-made filter fragments: [channel slice][wavefront = phase][k-block][term][lane] vectors of 8 bf16
     static constexpr int FRAG_VECS = (SP::C / CS) * 4 * KB * 3 * 64;
 };
@@ -116,7 +122,7 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
     static_assert(G::GH <= SP::OH + 1 && G::GW <= SP::OW + 1, "phase grid must fit the padded dY");
     constexpr int CS = G::CS, S = G::S, GW = G::GW, GP = G::GP, NT = G::NT, PW = G::PW;
     constexpr int OCB = G::OCB, KB = G::KB, PIT = G::PIT, PLANE = G::PLANE, NX = G::NX;
-    constexpr int NTERM = ONE ? 1 : 2;
+    constexpr int NTERM = ONE ? 1 : 3;
     constexpr int NITEM = (SP::OC / 8) * SP::NPIX, DPT = (NITEM + 255) / 256;      // items: 8 filters of one pixel
     constexpr int XV = NX / 4, XPT = (XV + 255) / 256;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -166,90 +172,46 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
     int f = bx;
     fetch_dy(min(f, nframes - 1));       // on its way while the filters arrive
     // sub-filter fragments of my phase: row = channel l16, k = (tap, filter 8g..8g+7 of the block's 32)
-    u32x4 af[KB][NTERM];
-    int wexp[4] = {0, 0, 0, 0};          // what undoes the scales of my output rows
-    if (ONE && wfrag) {
+    Bf16x8Bits af[KB][NTERM];
+    if (wfrag) {
         const u32x4 *src = wfrag + (size_t)((by * 4 + wave) * KB) * 3 * 64 + lane;
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) af[kb][0] = src[kb * 3 * 64];
-    } else {
-        float wv[KB][8];
-        if (wfrag) {                     // the three terms add up to the weight
-            const u32x4 *src = wfrag + (size_t)((by * 4 + wave) * KB) * 3 * 64 + lane;
-            u32x4 t[KB][3];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int x = 0; x < 3; ++x) t[kb][x] = src[(kb * 3 + x) * 64];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    auto part = [&](int x) { return __uint_as_float(j % 2 ? t[kb][x][j / 2] & 0xffff0000u : t[kb][x][j / 2] << 16); };
-                    wv[kb][j] = (part(2) + part(1)) + part(0);
-                }
-        } else {
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                const int tap = kb / OCB, a = tap / 2, e = tap % 2;
-                const int u = ry + S * a, v = rx + S * e;
-                const int oc0 = (kb % OCB) * 32 + 8 * g;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) wv[kb][j] = w[((size_t)((oc0 + j) * SP::C + c0 + l16) * SP::KS + u) * SP::KS + v];
-            }
-        }
-        float scale = 1.f;
-        if constexpr (!ONE) {            // a scale for each row; what is no number does not count
-            float m = 0.f;
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float a = fabsf(wv[kb][j]);
-                    m = fmaxf(m, a < __builtin_inff() ? a : 0.f);
-                }
-            m = fmaxf(m, __shfl_xor(m, 16));
-            m = fmaxf(m, __shfl_xor(m, 32));
-            const int e = f16_exponent(m);
-            scale = f16_power(e);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) wexp[r] = 127 - __shfl(e, 4 * g + r);
-        }
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                uint32_t t[2];
-                split_terms<ONE>(wv[kb][2 * j], wv[kb][2 * j + 1], scale, t);
+            for (int x = 0; x < NTERM; ++x) af[kb][x].u = src[(kb * 3 + x) * 64];
+    } else {
 #pragma unroll
-                for (int x = 0; x < NTERM; ++x) af[kb][x][j] = t[x];
+        for (int kb = 0; kb < KB; ++kb) {
+            const int tap = kb / OCB, a = tap / 2, e = tap % 2;
+            const int u = ry + S * a, v = rx + S * e;
+            const int oc0 = (kb % OCB) * 32 + 8 * g;
+            Bf16x8Bits t[3];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float f = w[((size_t)((oc0 + j) * SP::C + c0 + l16) * SP::KS + u) * SP::KS + v];
+                __bf16 h, m, l;
+                split3(f, h, m, l);
+                t[0].v[j] = h; t[1].v[j] = m; t[2].v[j] = l;
             }
+#pragma unroll
+            for (int x = 0; x < NTERM; ++x) af[kb][x] = t[x];
+        }
     }
-    __shared__ __attribute__((aligned(16))) float most[1][4];
     CONV_DGRAD_STAMP(1);
     for (; f < nframes; f += nbx) {
-        int de[1] = {127};
-        if constexpr (ONE) __syncthreads();   // the border is zero; the last frame's dY and outs have been read
-        else
-            f16_block_exponents(most, wave, lane, [&](int, auto fold) {
-#pragma unroll
-                for (int i = 0; i < DPT; ++i)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) fold(dpre[i][j]);
-            }, de);
-        const float dscale = f16_power(de[0]);
+        __syncthreads();                      // the border is zero; the last frame's dY and outs have been read
 #pragma unroll
         for (int i = 0; i < DPT; ++i)
             if (tid + 256 * i < NITEM) {
-                u32x4 o[2];
+                u32x4 o3[3];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    uint32_t t[2];
-                    split_terms<ONE>(dpre[i][2 * j], dpre[i][2 * j + 1], dscale, t);
-                    o[0][j] = t[0]; o[1][j] = t[1];
+                    uint32_t t[3];
+                    split3_pair(dpre[i][2 * j], dpre[i][2 * j + 1], t[0], t[1], t[2]);
+                    o3[0][j] = t[0]; o3[1][j] = t[1]; o3[2][j] = t[2];
                 }
 #pragma unroll
-                for (int x = 0; x < NTERM; ++x) *(u32x4 *)(dp + x * PLANE + dlds[i]) = o[x];
+                for (int x = 0; x < NTERM; ++x) *(u32x4 *)(dp + x * PLANE + dlds[i]) = o3[x];
             }
         __syncthreads();
         fetch_dy(min(f + nbx, nframes - 1));
@@ -269,9 +231,11 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
         // one k-block of one group; where the registers allow (32 filters), the operand reads of the next step are
         // issued before the products of this one, so that no product waits for LDS.
         constexpr int IG = 4, NSTEP = ((NT + IG - 1) / IG) * KB;
-        constexpr bool AHEAD = KB * NTERM > 8 || (ONE && KB > 4);
-        u32x4 b[AHEAD ? 2 : 1][IG][NTERM];
-        auto read_b = [&](int step, u32x4 (&dst)[IG][NTERM]) {
+        constexpr bool AHEAD = KB * NTERM <= 12;
+        constexpr int NPROD = ONE ? 1 : 6;
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};      // smallest products first
+        Bf16x8Bits b[AHEAD ? 2 : 1][IG][NTERM];
+        auto read_b = [&](int step, Bf16x8Bits (&dst)[IG][NTERM]) {
             const int i0 = (step / KB) * IG, kb = step % KB;
             const int tap = kb / OCB, a = tap / 2, e = tap % 2;
             const int koff = ((1 - a) * PW + (1 - e)) * PIT + (kb % OCB) * 64;
@@ -279,7 +243,7 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
             for (int ii = 0; ii < IG; ++ii)
                 if (i0 + ii < NT) {
 #pragma unroll
-                    for (int x = 0; x < NTERM; ++x) dst[ii][x] = *(const u32x4 *)(dp + x * PLANE + pbyte[i0 + ii] + koff);
+                    for (int x = 0; x < NTERM; ++x) dst[ii][x].u = *(const u32x4 *)(dp + x * PLANE + pbyte[i0 + ii] + koff);
                 }
         };
         __builtin_amdgcn_s_setprio(1);         // the products first: measured 2 % over equal priorities
@@ -291,11 +255,14 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);
             const int i0 = (step / KB) * IG, kb = step % KB;
 #pragma unroll
-            for (int q = 0; q < F16_PRODUCTS<ONE>; ++q)
+            for (int q = 0; q < NPROD; ++q) {
+                const int ai = ONE ? 0 : PA[q], bi = ONE ? 0 : PB[q];
 #pragma unroll
                 for (int ii = 0; ii < IG; ++ii)
                     if (i0 + ii < NT)
-                        acc[i0 + ii] = mfma_terms<ONE>(af[kb][f16_a_term<ONE>(q)], b[AHEAD ? step & 1 : 0][ii][f16_b_term<ONE>(q)], acc[i0 + ii]);
+                        acc[i0 + ii] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[kb][ai % NTERM].v, b[AHEAD ? step & 1 : 0][ii][bi % NTERM].v,
+                                                                               acc[i0 + ii], 0, 0, 0);
+            }
             if (AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
@@ -303,8 +270,7 @@ __device__ __forceinline__ void conv_dgrad_bf16x6_block(const float *__restrict_
         for (int i = 0; i < NT; ++i)
             if (obase[i] >= 0) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    outs[(4 * g + r) * (SP::H * SP::W) + obase[i]] = ONE ? acc[i][r] : ldexpf(acc[i][r], wexp[r] + 127 - de[0]);
+                for (int r = 0; r < 4; ++r) outs[(4 * g + r) * (SP::H * SP::W) + obase[i]] = acc[i][r];
             }
         __syncthreads();
         float4 *dst = (float4 *)(dx + (size_t)f * SP::CHW + (size_t)c0 * (SP::H * SP::W));

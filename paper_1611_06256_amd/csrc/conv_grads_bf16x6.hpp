@@ -43,9 +43,8 @@ inline hipError_t launch_conv_grads_bf16x6(const float *x, const float *dy, cons
     constexpr int SLICES = SP::C / 16;
     // As few blocks as take the same number of frames each at most: the weight gradient's start the earlier.  16 channels: half of the 512
     // places each, so that all blocks start at once; 32: the weight gradient's blocks (four to a partial sum) follow the input gradient's.
-    // us an update by places / partial sums, small net 2560 frames 512 / 512: 260.6, 512 / 256: 264.8, 384 / 256: 260.6, 256 / 256: 246.9; 640:
-    // 112.3, 111.7, 111.7, 107.0; larger net 1280 frames 512 / 256: 449, 512 / 192: 442, 512 / 128: 435, 512 / 96: 440, 512 / 64: 453, 384 / 128:
-    // 439; stride-4 member 640: 512 / 256: 192.9, 512 / 128: 192.7.
+    // us an update by places / partial sums, small net 2560 frames 512 / 512: 235, 512 / 256: 238, 384 / 256: 236, 256 / 256: 220; 640: 103, 102,
+    // 102, 98; larger net 1280 frames 512 / 256: 413, 512 / 128: 402, 384 / 128: 406; stride-4 member 640: 512 / 256: 189.9, 512 / 128: 188.8.
     constexpr int PLACES = SP::C == 16 ? 256 : 512;
     const int per = (nframes * SLICES + PLACES - 1) / PLACES, nbd = (nframes + per - 1) / per, nbw = conv_wgrad_bf16x6_blocks<SP>(nframes);
     auto lds = [](bool one) { return std::max(ConvDgradBf16Geom<SP>::lds_bytes(one), ConvWgradBf16Geom<SP, OCB>::lds_bytes(one)); };

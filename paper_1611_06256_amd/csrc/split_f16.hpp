@@ -124,44 +124,6 @@ __device__ __forceinline__ int f16_row_exponent(const int e, const All &all) {
     return need < e ? need - F16_ROOM : e;
 }
 
-// Scale exponents of N sets of values that a block of NW wavefronts is about to split: at(n, fold) folds the calling thread's values
-// of set n.  `most` lies in LDS; a barrier of the block comes in front of its next use.  Infinities don't count (in a second look, which
-// only they cost), NaN never do.
-template <int N, int NW, class At>
-__device__ __forceinline__ void f16_block_exponents(float (&most)[N][NW], const int wave, const int lane, const At &at, int (&e)[N]) {
-    auto look = [&](auto finite) {
-        float m[N];
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            m[n] = 0.f;
-            at(n, [&](const float v) {
-                const float a = fabsf(v);
-                m[n] = fmaxf(m[n], !decltype(finite)::value || a < __builtin_inff() ? a : 0.f);
-            });
-            m[n] = f16_wave_most(m[n]);
-        }
-        if (lane == 0)
-#pragma unroll
-            for (int n = 0; n < N; ++n) most[n][wave] = m[n];
-        __syncthreads();
-        bool again = false;
-#pragma unroll
-        for (int n = 0; n < N; ++n) {
-            float a = most[n][0];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) a = fmaxf(a, most[n][w]);
-            const uint32_t u = __builtin_amdgcn_readfirstlane(__float_as_uint(a));
-            again |= u == 0x7f800000u;
-            e[n] = f16_exponent(__uint_as_float(u));
-        }
-        return again;
-    };
-    if (look(std::false_type{})) {
-        __syncthreads();
-        look(std::true_type{});
-    }
-}
-
 // One of the operands' terms times the other's: bfloat16 (one term) or float16.
 template <bool BF16>
 __device__ __forceinline__ floatx4 mfma_terms(const u32x4 a, const u32x4 b, const floatx4 c) {
