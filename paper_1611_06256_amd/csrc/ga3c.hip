@@ -161,7 +161,7 @@ enum Reads { READS_NONE, READS_OPEN, READS_MARKED };
 struct ga3c_ctx {
     Profiler *prof;
     bool fast;                    // use the fixed-geometry kernels where they apply
-    bool small_predict;           // predictions of a handful of frames go out as one launch
+    int small_frames;             // predictions of up to so many frames go out as one launch (small_launch_frames)
     int rb;                       // desc.math == 1: operands of every contraction are rounded to bfloat16
     ga3c_net_desc desc;
     int nconv, F, A, flat;
@@ -801,7 +801,7 @@ __global__ __launch_bounds__(256) void heads_predict_few_kernel(const float *__r
 // Blocks in order of (row group, slice): an XCD reads few parts of the fc weights.
 // Latency: nothing is large.  One frame 15.9 -> 12.8 us a call, 37 frames 23.9 -> 18.6 us against a kernel whose blocks each ran
 // both layers of a whole frame, with an event recorded behind every call (9.6 and 14.9 us without one).
-constexpr int SP_FC = 256, SP_FLAT = 2592, SP_MAX_FRAMES = 64;
+constexpr int SP_FC = 256, SP_FLAT = 2592, SP_MAX_FRAMES = 42, SP_ONE_FRAME = 21;      // up to so many: a frame a block
 constexpr int SP_TICKET_PITCH = 32;                        // ints between two groups' counters: a cache line each
 constexpr int SP_ROWS1 = 8, SP_PIX1 = SP_ROWS1 * 20, SP_PIX2 = 27, SP_XROWS = 36;      // of a row group: layer 1, layer 2, input
 constexpr int SP_XVEC = 4 * SP_XROWS * 84 / 16;            // 16-byte vectors of a frame's part
@@ -2171,6 +2171,17 @@ bool on_band_kernels(const ConvGeom &g, int l) {
     return band_ok<32>(g.H, g.W) && band_grads_ok(g.H, g.W);
 }
 
+// Predictions of up to how many frames go out as one launch (predict_small_kernel); 0: not this network's.  42: the most that 256 blocks hold, two
+// frames and four slices of the fc layer each; beyond, slices are halves and the kernel takes as long as the three launches do and more
+// (us a call, one launch / three: 42 frames 15.2 / 15.5, 43: 16.9 / 15.4, 64: 17.8 / 15.9; rounded 14.1 / 15.7, 16.8 / 15.8, 17.1 / 15.8;
+// ga3c_predict_static 19.8 / 19.1 to 20.6, 21.6 / 19.0 to 20.4, 22.5 / 19.4 to 20.8).  Where the heads of many actions leave no room for
+// two frames in LDS, 21 (63 actions, 21 frames 15.0 / 16.5, 22: 16.6 / 16.5, 42: 19.0 / 16.9; rounded 15.0 / 14.4, 17.0 / 14.4, 18.9 / 14.8).
+int small_launch_frames(const ga3c_ctx *c) {
+    const int nb = 2 * c->nconv;
+    if (c->nconv != 2 || c->F != SP_FC || c->flat != SP_FLAT || c->off[nb + 1] % 4 != 0 || c->off[nb + 2] % 4 != 0) return 0;
+    return SpLds<2>::bytes(c->A) <= HEADS_FWD_MAX_LDS ? SP_MAX_FRAMES : SP_ONE_FRAME;
+}
+
 // Forward pass of `B` frames into `w`; heads outputs to the optional pointers.  table (frames is nullptr then): the frames lie
 // where its entries point; only where takes_frame_table says so.
 int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_t *const *table, int B, bool keep_zv, float *logits, float *values,
@@ -2179,11 +2190,10 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
     const int nb = 2 * c->nconv;
     int first = 0;
     std::fill(w.bits_set, w.bits_set + GA3C_MAX_CONV, false);
-    if (c->fast && c->small_predict && c->ticket && c->cfrag[which] && is_aligned16(frames) && !keep_zv && with_heads && B <= SP_MAX_FRAMES &&
-        c->nconv == 2 && c->F == SP_FC && c->flat == SP_FLAT && is_aligned16(th + c->off[nb + 1]) && is_aligned16(th + c->off[nb + 2])) {
+    if (c->fast && c->ticket && c->cfrag[which] && is_aligned16(frames) && !keep_zv && with_heads && B <= c->small_frames) {
         // a handful of frames: one launch for the whole network, in about as many blocks as there are compute units
-        const bool two = B > 21 && SpLds<2>::bytes(c->A) <= HEADS_FWD_MAX_LDS;
-        const int NS = two ? (B <= 42 ? 4 : 2) : B <= 5 ? 16 : B <= 10 ? 8 : B <= 21 ? 4 : B <= 42 ? 2 : 1;
+        const bool two = B > SP_ONE_FRAME;
+        const int NS = B <= 5 ? 16 : B <= 10 ? 8 : 4;
         const int groups = two ? (B + 1) / 2 : B;
         if ((size_t)B * 3 * SP_FC > w.ws_floats) return fail(GA3C_EINVAL, "internal: workspace too small (small predictions)");
         const ConvGeom &g0 = c->geom[0], &g1 = c->geom[1];
@@ -2483,7 +2493,6 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     memset((void *)c, 0, sizeof(*c));
     c->prof = new (std::nothrow) Profiler();
     c->fast = true;
-    c->small_predict = true;
     c->max_pred = max_predict_batch; c->max_train = max_train_frames;
 
     if (init_shape(c, d) != GA3C_OK) {
@@ -2541,6 +2550,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
     if (rc == GA3C_OK && c->nconv >= 2 && spec_matches<SpecS1>(c->geom[0], true) && spec_matches<SpecS2>(c->geom[1], false) &&
         c->off[0] % 4 == 0 && c->off[2] % 4 == 0) {
         c->cfrag_dgrad = true;
+        c->small_frames = small_launch_frames(c);
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
             guard(dmalloc((void **)&c->cfrag[i], sizeof(u32x4) * CFRAG_VECS));
             if (rc == GA3C_OK && !c->rb && max_predict_batch > 0) guard(dmalloc((void **)&c->hfrag[i], sizeof(u32x4) * Conv12F16::VECS));
@@ -2584,7 +2594,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         }
     // a small net whose calls all fit one launch has no use for them
     if (rc == GA3C_OK && fc_forward_ok(c->flat, c->F) && c->off[2 * c->nconv] % 4 == 0 && c->P < (size_t)1 << 31 &&
-        !(c->ticket && max_train_frames == 0 && max_predict_batch <= SP_MAX_FRAMES)) {
+        !(c->ticket && max_train_frames == 0 && max_predict_batch <= c->small_frames)) {
         const int terms = c->rb ? 1 : 3;
         const size_t bytes = (size_t)c->flat * c->F * 2 * terms;
         unsigned char *w = nullptr;
@@ -3279,7 +3289,7 @@ extern "C" int ga3c_predict_static(int n_actions, int math, const float *theta, 
         return fail(GA3C_EINVAL, "ga3c_predict_static: internal: unexpected layout");
     unsigned char *base = nullptr;
     TRY(static_scratch(&base));
-    c.fast = true; c.small_predict = true; c.max_pred = STATIC_MAX_FRAMES;
+    c.fast = true; c.small_frames = small_launch_frames(&c); c.max_pred = STATIC_MAX_FRAMES;
     c.theta2[0] = const_cast<float *>(theta);
     c.cfrag[0] = (u32x4 *)(base + ST_FRAG_OFF);
     c.ticket = (int *)(base + ST_TICKET_OFF);
@@ -3290,7 +3300,7 @@ extern "C" int ga3c_predict_static(int n_actions, int math, const float *theta, 
     c.pred.ws_floats = ST_WS_FLOATS;
     hipStream_t s = (hipStream_t)stream;
     // the filters as split MFMA fragments, from the caller's parameters (a context does this when they change): those that this call reads
-    if (B > SP_MAX_FRAMES && !math) {
+    if (B > c.small_frames && !math) {
         c.hfrag[0] = (u32x4 *)(base + ST_HFRAG_OFF);
         HIP_TRY(launch_conv12_f16_filters(theta + c.off[0], theta + c.off[2], c.hfrag[0], s));
     } else TRY(refresh_derived(&c, 0, s));

@@ -25,6 +25,28 @@ def test_small_net_predictions_across_the_splits_of_a_frame(G, A, batches):
         P.check_predict(G, G.SMALL_NET(A), B, 7000 + B)
 
 
+# The last batch of one launch and the first of three: 42 and 43 frames, 21 and 22 where two frames do not fit a block; from the caller's own
+# parameters too.
+@pytest.mark.parametrize("math", [0, 1])
+@pytest.mark.parametrize("A,B", [(18, 42), (18, 43), (63, 21), (63, 22)])
+def test_where_the_one_launch_of_a_prediction_ends(G, A, B, math):
+    import dataclasses
+    import torch
+    desc = dataclasses.replace(G.SMALL_NET(A), math=math)
+    # (a seed at which no uniform is within 1e-5 of an edge of the distribution: 63 actions of 21 frames, one draw in forty sets has one there)
+    P.check_predict(G, desc, B, 7080 + B)
+    net, onet, theta = P.make(G, desc, B, 0, 7060 + B)
+    frames = synth.rectangle_frames(7061, B)
+    lg, vl, _, _ = P.run_predict(G, net, frames)
+    got = {k: torch.full(s, float("nan"), device="cuda") for k, s in (("logits", (B, A)), ("values", (B,)))}
+    G.predict_static(A, math, torch.from_numpy(theta).cuda(), torch.from_numpy(frames).cuda(), **got)
+    torch.cuda.synchronize()
+    # the same kernels on the same filters; three launches take the fc weights from another buffer, with the same sums
+    np.testing.assert_array_equal(got["logits"].cpu().numpy(), lg)
+    np.testing.assert_array_equal(got["values"].cpu().numpy(), vl)
+    net.close()
+
+
 @pytest.mark.parametrize("F,B", [(256, 3), (256, 66), (512, 1), (512, 5), (512, 130), (1024, 2), (1024, 65)])
 def test_heads_after_few_and_many_partial_sums(G, F, B):
     desc = G.NetDesc(conv=((16, 8, 4), (32, 4, 2)), fc_units=F, n_actions=18)
