@@ -183,7 +183,8 @@ struct ga3c_ctx {
     // small net: conv1/conv2 filters of each parameter copy as split MFMA fragments (nullptr for other nets), forward
     // kernel's first, then (at CFRAG_FWD_VECS) the input-gradient kernel's; refreshed by whoever writes the copy
     u32x4 *cfrag[2];
-    u32x4 *hfrag[2];              // the same filters for predictions at fp32 accuracy (conv12_f16.hpp), kept current likewise
+    u32x4 *hfrag[2];              // the same filters for predictions at fp32 accuracy of more frames than one launch takes (conv12_f16.hpp), kept
+                                  // current likewise; nullptr in a context that makes none
     bool cfrag_dgrad;             // the buffers hold the second part too (a context that can train)
     // larger net: the filters of conv2 and conv3 of each parameter copy as ready-made fragments for the forward and the
     // input-gradient kernels (LFRAG_* give the parts); rebuilt by whoever writes the copy
@@ -2553,7 +2554,7 @@ extern "C" int ga3c_create(const ga3c_net_desc *d, int max_predict_batch, int ma
         c->small_frames = small_launch_frames(c);
         for (int i = 0; i < 2 && rc == GA3C_OK; ++i) {
             guard(dmalloc((void **)&c->cfrag[i], sizeof(u32x4) * CFRAG_VECS));
-            if (rc == GA3C_OK && !c->rb && max_predict_batch > 0) guard(dmalloc((void **)&c->hfrag[i], sizeof(u32x4) * Conv12F16::VECS));
+            if (rc == GA3C_OK && !c->rb && max_predict_batch > c->small_frames) guard(dmalloc((void **)&c->hfrag[i], sizeof(u32x4) * Conv12F16::VECS));
             if (rc == GA3C_OK) guard(refresh_derived(c, i, nullptr));
         }
         if (rc == GA3C_OK) guard(dmalloc((void **)&c->ticket, sizeof(int) * SP_MAX_FRAMES * SP_TICKET_PITCH));
