@@ -2335,8 +2335,8 @@ int forward(ga3c_ctx *c, int which, Work &w, const uint8_t *frames, const uint8_
                 FcForwardArgs p;
                 p.M = B; p.N = c->F; p.K = c->flat; p.kchunk = kchunk; p.nz = nz;
                 p.x = x; p.w = c->fcw[which].w; p.part = w.ws;
-                size_t pass_bytes = 0;
-                for (int l = 0; l < c->nconv; ++l) pass_bytes += sizeof(float) * (size_t)B * c->geom[l].OC * c->geom[l].OHW;
+                size_t pass_bytes = 0;           // (of layers in one kernel a prediction writes the last one's only)
+                for (int l = first > 0 && !keep_zv ? first - 1 : 0; l < c->nconv; ++l) pass_bytes += sizeof(float) * (size_t)B * c->geom[l].OC * c->geom[l].OHW;
                 HIP_TRY(launch_fc_forward(p, pass_bytes, c->rb, s));
             } else {
                 DenseGemmArgs p{}; p.rb = c->rb;
