@@ -85,8 +85,8 @@ COUNTER_KIB = {   # stage: {frames per launch: (FETCH_SIZE, WRITE_SIZE)}; two st
 KERNELS = {"conv12_fwd": "conv12_f16_kernel (predictions), conv12_fused_fwd_kernel (updates)", "fc_fwd": "fc_forward_kernel",
            "fc_wgrad": "fc_grads_kernel", "fc_dgrad": "fc_grads_kernel", "heads_fwd": "heads_predict_kernel",
            "heads_train": "heads_train_kernel", "conv1_wgrad": "conv1_wgrad_kernel",
-           "conv2_wgrad": "conv_grads_bf16x6_kernel", "conv3_wgrad": "conv_wgrad_s1_bf16x6_kernel",
-           "conv2_dgrad": "conv_grads_bf16x6_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
+           "conv2_wgrad": "conv_grads_kernel", "conv3_wgrad": "conv_wgrad_s1_f16_kernel",
+           "conv2_dgrad": "conv_grads_kernel", "conv3_dgrad": "conv_fwd_bf16x6_kernel<dgrad>",
            "conv123_fwd": "conv123_f16_kernel", "conv1_fwd": "conv1_bf16x3_fwd_kernel", "conv2_fwd": "conv_fwd_bf16x6_kernel", "conv3_fwd": "conv_fwd_bf16x6_kernel",
            "wgrad_reduce": "reduce_all_kernel", "rmsprop": "rmsprop_kernel", "predict_small": "predict_small_kernel"}
 # 16-bit MFMAs executed per nominal one with fp32-grade accuracy: 3 or 6 with operands in three bf16 terms, 2 or 3 with two float16

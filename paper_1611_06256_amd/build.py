@@ -8,9 +8,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(HERE, "libga3c.so")
 SOURCES = [os.path.join(HERE, "csrc", "ga3c.hip"), os.path.join(HERE, "csrc", "sched.hip"),
            os.path.join(HERE, "csrc", "tuner.cpp")]
-HEADERS = [os.path.join(HERE, "csrc", f) for f in ("conv_grads_bf16x6.hpp", "conv_plain.hpp", "fc_forward.hpp", "fc_grads.hpp", "frame_table.hpp", "gemm_mfma.hpp", "problems.hpp", "conv_frame.hpp", "dense_gemm.hpp",
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("conv_grads.hpp", "conv_plain.hpp", "fc_forward.hpp", "fc_grads.hpp", "frame_table.hpp", "gemm_mfma.hpp", "problems.hpp", "conv_frame.hpp", "dense_gemm.hpp",
                                                   "conv1_bf16x3.hpp", "conv1_wgrad_f16.hpp", "dense_gemm_bf16x6.hpp", "conv2_bf16x6.hpp", "conv12_fused.hpp", "conv_fwd_bf16x6.hpp", "conv123_f16.hpp", "conv12_f16.hpp", "split_f16.hpp",
-                                                  "conv_dgrad_bf16x6.hpp", "conv_wgrad_bf16x6.hpp", "conv_wgrad_s1_bf16x6.hpp", "conv_band.hpp", "conv_bytes.hpp", "conv_band_f32.hpp", "conv_band_grads.hpp", "sched_error.hpp", "launch.hpp")] + [
+                                                  "conv_dgrad_bf16x6.hpp", "conv_wgrad_f16.hpp", "conv_wgrad_s1_f16.hpp", "conv_band.hpp", "conv_bytes.hpp", "conv_band_f32.hpp", "conv_band_grads.hpp", "sched_error.hpp", "launch.hpp")] + [
     os.path.join(os.path.dirname(HERE), "include", "ga3c.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
          # packed fp32 instructions stay off: the compiler must not form them

@@ -22,6 +22,8 @@
 #include "launch.hpp"
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "conv1_bf16x3.hpp"
 #include "conv_plain.hpp"
 #include "gemm_mfma.hpp"

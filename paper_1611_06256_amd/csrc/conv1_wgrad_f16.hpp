@@ -2,7 +2,7 @@
 // matrix cores at fp32 accuracy:
 //   dW[oc][c][u][v] = sum_{i,j} dY[oc][i][j] x[c][4i+u][4j+v],   db[oc] = sum dY[oc][i][j]
 // A byte is exact in float16, and dY is split into two float16 terms, every filter's under the scale of the largest values that the block
-// has met in it so far (split_f16.hpp, conv_wgrad_bf16x6.hpp): two products a sum.  Rounded operands (ONE) are one bfloat16 term, and the
+// has met in it so far (split_f16.hpp, conv_wgrad_f16.hpp): two products a sum.  Rounded operands (ONE) are one bfloat16 term, and the
 // bytes bfloat16 as well.
 //
 // The contraction runs over output pixels, 8 consecutive pixels of a row per
@@ -25,6 +25,8 @@
 
 #include "launch.hpp"
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "split_f16.hpp"
 

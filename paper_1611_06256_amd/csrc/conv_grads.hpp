@@ -14,12 +14,12 @@
 #include <algorithm>
 
 #include "conv_dgrad_bf16x6.hpp"
-#include "conv_wgrad_bf16x6.hpp"
+#include "conv_wgrad_f16.hpp"
 
 namespace ga3c {
 
 template <class SP, bool ONE, int OCB>
-__global__ __launch_bounds__(256, 2) void conv_grads_bf16x6_kernel(const float *__restrict__ x, const float *__restrict__ dy,
+__global__ __launch_bounds__(256, 2) void conv_grads_kernel(const float *__restrict__ x, const float *__restrict__ dy,
                                                                    const float *__restrict__ w, const u32x4 *__restrict__ wfrag,
                                                                    float *__restrict__ dx, float *__restrict__ part, int nframes,
                                                                    int nbd, int nbw) {
@@ -31,13 +31,13 @@ __global__ __launch_bounds__(256, 2) void conv_grads_bf16x6_kernel(const float *
         return;
     }
     for (b -= nbd * SLICES; b >= nbw; b -= nbw) ++slice;
-    conv_wgrad_bf16x6_block<SP, ONE, OCB>(x, dy, part, nframes, 1.f, b, slice % SLICES, slice / SLICES, nbw);
+    conv_wgrad_f16_block<SP, ONE, OCB>(x, dy, part, nframes, 1.f, b, slice % SLICES, slice / SLICES, nbw);
 }
 
 // x [n][C][H][W] (the layer's input, and the ReLU mask of dx), dy [n][OC][OH][OW], w the filters, wfrag their fragments for the
-// input gradient or nullptr; all 16-byte aligned.  part: [conv_wgrad_bf16x6_blocks(n)][OC][K + 1].
+// input gradient or nullptr; all 16-byte aligned.  part: [conv_wgrad_f16_blocks(n)][OC][K + 1].
 template <class SP, int OCB = SP::OC>
-inline hipError_t launch_conv_grads_bf16x6(const float *x, const float *dy, const float *w, const u32x4 *wfrag, float *dx, float *part,
+inline hipError_t launch_conv_grads(const float *x, const float *dy, const float *w, const u32x4 *wfrag, float *dx, float *part,
                                            int nframes, hipStream_t s, int rb) {
     if (nframes <= 0) return hipSuccess;
     constexpr int SLICES = SP::C / 16;
@@ -46,21 +46,21 @@ inline hipError_t launch_conv_grads_bf16x6(const float *x, const float *dy, cons
     // us an update by places / partial sums, small net 2560 frames 512 / 512: 235, 512 / 256: 238, 384 / 256: 236, 256 / 256: 220; 640: 103, 102,
     // 102, 98; larger net 1280 frames 512 / 256: 413, 512 / 128: 402, 384 / 128: 406; stride-4 member 640: 512 / 256: 189.9, 512 / 128: 188.8.
     constexpr int PLACES = SP::C == 16 ? 256 : 512;
-    const int per = (nframes * SLICES + PLACES - 1) / PLACES, nbd = (nframes + per - 1) / per, nbw = conv_wgrad_bf16x6_blocks<SP>(nframes);
-    auto lds = [](bool one) { return std::max(ConvDgradBf16Geom<SP>::lds_bytes(one), ConvWgradBf16Geom<SP, OCB>::lds_bytes(one)); };
+    const int per = (nframes * SLICES + PLACES - 1) / PLACES, nbd = (nframes + per - 1) / per, nbw = conv_wgrad_f16_blocks<SP>(nframes);
+    auto lds = [](bool one) { return std::max(ConvDgradBf16Geom<SP>::lds_bytes(one), ConvWgradGeom<SP, OCB>::lds_bytes(one)); };
     static bool attr_set = false;          // once per layer shape: let the kernels use more than 64 KB of LDS
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)conv_grads_bf16x6_kernel<SP, false, OCB>,
+        hipError_t e = hipFuncSetAttribute((const void *)conv_grads_kernel<SP, false, OCB>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds(false));
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_grads_bf16x6_kernel<SP, true, OCB>,
+            e = hipFuncSetAttribute((const void *)conv_grads_kernel<SP, true, OCB>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds(true));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
     const dim3 grid(nbd * SLICES + nbw * SLICES * (SP::OC / OCB));
-    if (rb) ga3c::launch((conv_grads_bf16x6_kernel<SP, true, OCB>), grid, dim3(256), lds(true), s, x, dy, w, wfrag, dx, part, nframes, nbd, nbw);
-    else ga3c::launch((conv_grads_bf16x6_kernel<SP, false, OCB>), grid, dim3(256), lds(false), s, x, dy, w, wfrag, dx, part, nframes, nbd, nbw);
+    if (rb) ga3c::launch((conv_grads_kernel<SP, true, OCB>), grid, dim3(256), lds(true), s, x, dy, w, wfrag, dx, part, nframes, nbd, nbw);
+    else ga3c::launch((conv_grads_kernel<SP, false, OCB>), grid, dim3(256), lds(false), s, x, dy, w, wfrag, dx, part, nframes, nbd, nbw);
     return hipGetLastError();
 }
 

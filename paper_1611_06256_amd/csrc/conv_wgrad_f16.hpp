@@ -1,4 +1,4 @@
-// Weight and bias gradient of a 4x4, stride-2 convolution layer on the bf16
+// Weight and bias gradient of a 4x4, stride-2 convolution layer on the 16-bit
 // matrix cores at fp32 accuracy (backward pass of the network of Sec. 3.2; the
 // layer is the second convolution of both networks):
 //
@@ -26,8 +26,10 @@
 // far are brought to the new scale.  So a value of 2^-15 of the largest one that
 // goes into the same sums still has its 22 bits, and what is smaller an error of
 // 2^-37 of that one.  The lanes that stage a channel or a filter are neighbours
-// and find its largest value between themselves.  Three bfloat16 terms, six products, operands of
-// the next group read ahead, against this, error of dW in the 2-norm: small net 40
+// and find its largest value between themselves.  (One scale for all channels and
+// one for all filters took the bits of those far smaller than another, and cost
+// an exchange between the wavefronts: the same time.)  Three bfloat16 terms, six
+// products, operands of the next group read ahead, against two, error of dW in the 2-norm: small net 40
 // frames 1.45e-7 -> 1.34e-7, 2560: 1.8e-7 -> 1.1e-7, larger net 1280: 1.8e-7 -> 1.1e-7
 // (with one accumulator 1.6e-7, 1.6e-7 and 1.9e-7).
 //
@@ -50,14 +52,14 @@ namespace ga3c {
 
 // OCB: filters per block (a multiple of 16; bz takes the slices of OCB filters)
 template <class SP, int OCB = SP::OC>
-struct ConvWgradBf16Geom {
+struct ConvWgradGeom {
     static constexpr int CS = 16;
     static constexpr int GH = SP::H / 2, GW = SP::W / 2;
     static constexpr int KTOT = SP::OH * GW;                       // k = i * GW + j
     static constexpr int NKB = (KTOT + 31) / 32;                   // groups of 32 k
-    static constexpr int DROW = 8 * lds_row_units(NKB * 4);        // bf16 per filter row of dY
+    static constexpr int DROW = 8 * lds_row_units(NKB * 4);        // elements per filter row of dY
     static constexpr int WIN = 24;                                 // elements of a plane row a lane reads per group and term
-    static constexpr int PROW = 8 * lds_row_units((NKB * 32 - 8 + WIN) / 8);      // bf16 per channel row of a phase plane
+    static constexpr int PROW = 8 * lds_row_units((NKB * 32 - 8 + WIN) / 8);      // and per channel row of a phase plane
     static constexpr int MT = OCB / 16;
     static constexpr int DTERM = OCB * DROW, PTERM = 4 * CS * PROW;         // elements per term
     static constexpr int OTP = CS * 16 + 4;                        // floats per filter row of the block's result in LDS
@@ -70,9 +72,9 @@ struct ConvWgradBf16Geom {
 
 // ONE: operands rounded to bfloat16 (the reduced-precision variant): one term, one product.
 template <class SP, bool ONE, int OCB = SP::OC>
-__device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part,
+__device__ __forceinline__ void conv_wgrad_f16_block(const float *__restrict__ x, const float *__restrict__ dy, float *__restrict__ part,
                                                         int nframes, float scale, const int bx, const int by, const int bz, const int nbx) {
-    typedef ConvWgradBf16Geom<SP, OCB> G;
+    typedef ConvWgradGeom<SP, OCB> G;
     static_assert(SP::OC % OCB == 0 && OCB % 16 == 0, "whole slices of filters");
     static_assert(SP::KS == 4 && SP::S == 2, "kernel must be 4x4 with stride 2");
     static_assert(SP::C % 16 == 0 && SP::OC % 16 == 0 && SP::OC <= 256, "channels and filters in groups of 16");
@@ -88,8 +90,8 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
     constexpr int W4 = SP::W / 4, XPT = RX::PER, DPT = RD::PER;
     constexpr int K1 = SP::K + 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __bf16 *dsm = (__bf16 *)smem;                      // [term][oc][DROW]
-    __bf16 *psm = dsm + NTERM * DTERM;                 // [term][phase][c][PROW]
+    uint16_t *dsm = (uint16_t *)smem;                  // [term][oc][DROW]
+    uint16_t *psm = dsm + NTERM * DTERM;                 // [term][phase][c][PROW]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -303,42 +305,42 @@ __device__ __forceinline__ void conv_wgrad_bf16x6_block(const float *__restrict_
         part[((size_t)bx * SP::OC + oc0 + tid) * K1 + SP::K] = (bsh[0][tid] + bsh[1][tid]) + (bsh[2][tid] + bsh[3][tid]);
 }
 template <class SP, bool ONE, int OCB = SP::OC>
-__global__ __launch_bounds__(256, (ConvWgradBf16Geom<SP, OCB>::PER_CU)) void conv_wgrad_bf16x6_kernel(const float *__restrict__ x,
+__global__ __launch_bounds__(256, (ConvWgradGeom<SP, OCB>::PER_CU)) void conv_wgrad_f16_kernel(const float *__restrict__ x,
                                                                                               const float *__restrict__ dy,
                                                                                               float *__restrict__ part,
                                                                                               int nframes, float scale) {
-    conv_wgrad_bf16x6_block<SP, ONE, OCB>(x, dy, part, nframes, scale, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
+    conv_wgrad_f16_block<SP, ONE, OCB>(x, dy, part, nframes, scale, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.x);
 }
 
 // One partial dW per block.  They are written, read and added up again, so there are no more of them than it takes to fill the
-// chip beside the input gradient's blocks (conv_grads_bf16x6.hpp).
+// chip beside the input gradient's blocks (conv_grads.hpp).
 template <class SP>
-inline int conv_wgrad_bf16x6_blocks(int nframes) {
+inline int conv_wgrad_f16_blocks(int nframes) {
     constexpr int LIMIT = SP::C == 16 ? 256 : 128;
     return nframes < LIMIT ? nframes : LIMIT;
 }
 
-// x: [n][C][H][W] and dy: [n][OC][OH][OW], both 16-byte aligned; part: [conv_wgrad_bf16x6_blocks(n)][OC][K + 1].
+// x: [n][C][H][W] and dy: [n][OC][OH][OW], both 16-byte aligned; part: [conv_wgrad_f16_blocks(n)][OC][K + 1].
 template <class SP, int OCB = SP::OC>
-inline hipError_t launch_conv_wgrad_bf16x6(const float *x, const float *dy, float *part, int nframes, float scale,
+inline hipError_t launch_conv_wgrad_f16(const float *x, const float *dy, float *part, int nframes, float scale,
                                            hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
-    typedef ConvWgradBf16Geom<SP, OCB> G;
+    typedef ConvWgradGeom<SP, OCB> G;
     static bool attr_set = false;          // once per layer shape: let the kernels use more than 64 KB of LDS
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)conv_wgrad_bf16x6_kernel<SP, false, OCB>,
+        hipError_t e = hipFuncSetAttribute((const void *)conv_wgrad_f16_kernel<SP, false, OCB>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(false));
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_wgrad_bf16x6_kernel<SP, true, OCB>,
+            e = hipFuncSetAttribute((const void *)conv_wgrad_f16_kernel<SP, true, OCB>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(true));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const dim3 grid(conv_wgrad_bf16x6_blocks<SP>(nframes), SP::C / 16, SP::OC / OCB);
+    const dim3 grid(conv_wgrad_f16_blocks<SP>(nframes), SP::C / 16, SP::OC / OCB);
     if (rb)
-        ga3c::launch((conv_wgrad_bf16x6_kernel<SP, true, OCB>), grid, dim3(256), G::lds_bytes(true), s, x, dy, part, nframes, scale);
+        ga3c::launch((conv_wgrad_f16_kernel<SP, true, OCB>), grid, dim3(256), G::lds_bytes(true), s, x, dy, part, nframes, scale);
     else
-        ga3c::launch((conv_wgrad_bf16x6_kernel<SP, false, OCB>), grid, dim3(256), G::lds_bytes(false), s, x, dy, part, nframes, scale);
+        ga3c::launch((conv_wgrad_f16_kernel<SP, false, OCB>), grid, dim3(256), G::lds_bytes(false), s, x, dy, part, nframes, scale);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 // Weight and bias gradient of a stride-1 convolution layer with 64 input
-// channels (the third layer of the larger network) on the bf16 matrix cores at
+// channels (the third layer of the larger network) on the 16-bit matrix cores at
 // fp32 accuracy:
 //
 //   dW[oc][c][u][v] = sum over frames and output pixels (i, j) of dY[oc][i][j] x[c][i+u][j+v]
@@ -20,7 +20,7 @@
 //
 // Both operands are split into two float16 terms while they are staged, three
 // products a sum, under scales for every channel and every filter, by the largest
-// values that the block has met so far (split_f16.hpp, conv_wgrad_bf16x6.hpp).  With three bfloat16 terms, six
+// values that the block has met so far (split_f16.hpp, conv_wgrad_f16.hpp).  With three bfloat16 terms, six
 // products, 1280 frames took 37.5 us instead of 29.7; error of dW in the 2-norm
 // 1.27e-7 both (320 frames 1.42e-7 -> 1.40e-7).  There is no room for accumulators of the small products.
 //
@@ -40,14 +40,14 @@
 namespace ga3c {
 
 template <class SP>
-struct ConvWgradS1Bf16Geom {
+struct ConvWgradS1Geom {
     static constexpr int MS = 2;                                   // filter tiles of 16 per block
     static constexpr int KTOT = (SP::OH - 1) * SP::W + SP::OW;     // k = i * W + j
     static constexpr int NKB = (KTOT + 31) / 32;                   // groups of 32 k
-    static constexpr int DROW = NKB * 32 + 8;                      // bf16 per filter row of dY
+    static constexpr int DROW = NKB * 32 + 8;                      // elements per filter row of dY
     static constexpr int WIN = 32;                                 // elements of a plane row a lane reads per group and term
     static constexpr int SHIFT = (SP::KS - 1) * SP::W + SP::KS - 1;         // the largest shift
-    static constexpr int PROW = ((NKB * 32 + WIN - 8) / 8) * 8 + 16;        // bf16 per channel row of the input (52 dwords)
+    static constexpr int PROW = ((NKB * 32 + WIN - 8) / 8) * 8 + 16;        // and per channel row of the input (52 dwords)
     static constexpr int DTERM = MS * 16 * DROW, PTERM = SP::C * PROW;      // elements per term
     static constexpr int OTP = SP::K + 4;                          // floats per filter row of a tile's result in LDS
     __host__ __device__ static constexpr int lds_bytes(bool one) {
@@ -58,9 +58,9 @@ struct ConvWgradS1Bf16Geom {
 
 // ONE: operands rounded to bfloat16 (the reduced-precision variant): one term, one product.
 template <class SP, bool ONE>
-__global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const float *__restrict__ x, const float *__restrict__ dy,
+__global__ __launch_bounds__(256, 2) void conv_wgrad_s1_f16_kernel(const float *__restrict__ x, const float *__restrict__ dy,
                                                                       float *__restrict__ part, int nframes, float scale) {
-    typedef ConvWgradS1Bf16Geom<SP> G;
+    typedef ConvWgradS1Geom<SP> G;
     static_assert(SP::S == 1 && SP::C == 64 && SP::OC % 32 == 0, "stride 1, 64 channels in (16 per wavefront), filters in groups of 32");
     static_assert(G::SHIFT + 8 <= G::WIN && G::NKB * 32 - 8 + G::WIN <= G::PROW, "the window holds every shift and stays in its row");
     static_assert(SP::H * SP::W <= G::PROW, "a plane fits its row");
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
     constexpr int XPT = RX::PER, DPT = RD::PER;
     constexpr int K1 = SP::K + 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __bf16 *dsm = (__bf16 *)smem;                      // [term][oc][DROW]
-    __bf16 *psm = dsm + NTERM * DTERM;                 // [term][c][PROW]
+    uint16_t *dsm = (uint16_t *)smem;                  // [term][oc][DROW]
+    uint16_t *psm = dsm + NTERM * DTERM;                 // [term][c][PROW]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,17 +118,16 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
 #pragma unroll
         for (int i = 0; i < DPT; ++i) dpre[i] = *(const f32x4_dword_aligned *)(ds + RD::at(tid, i));
     };
-    auto stash4 = [&](const f32x4_dword_aligned v, float scale, __bf16 *base, int tstride, const int (&dst)[4]) {
+    auto stash4 = [&](const f32x4_dword_aligned v, float scale, uint16_t *base, int tstride, const int (&dst)[4]) {
         uint32_t t0[2], t1[2];
         split_terms<ONE>(v.x, v.y, scale, t0);
         split_terms<ONE>(v.z, v.w, scale, t1);
-        uint16_t *o = (uint16_t *)base;
 #pragma unroll
         for (int t = 0; t < NTERM; ++t) {
-            o[t * tstride + dst[0]] = (uint16_t)(t0[t] & 0xffffu);
-            o[t * tstride + dst[1]] = (uint16_t)(t0[t] >> 16);
-            o[t * tstride + dst[2]] = (uint16_t)(t1[t] & 0xffffu);
-            o[t * tstride + dst[3]] = (uint16_t)(t1[t] >> 16);
+            base[t * tstride + dst[0]] = (uint16_t)(t0[t] & 0xffffu);
+            base[t * tstride + dst[1]] = (uint16_t)(t0[t] >> 16);
+            base[t * tstride + dst[2]] = (uint16_t)(t1[t] & 0xffffu);
+            base[t * tstride + dst[3]] = (uint16_t)(t1[t] >> 16);
         }
     };
     int f = blockIdx.x;
@@ -275,32 +274,32 @@ __global__ __launch_bounds__(256, 2) void conv_wgrad_s1_bf16x6_kernel(const floa
 
 // One partial dW per block: fewer blocks where a partial is large.
 template <class SP>
-inline int conv_wgrad_s1_bf16x6_blocks(int nframes) {
+inline int conv_wgrad_s1_f16_blocks(int nframes) {
     constexpr int LIMIT = SP::OC * (SP::K + 1) > 16384 ? 256 : 512;
     return nframes < LIMIT ? nframes : LIMIT;
 }
 
-// x: [n][C][H][W] and dy: [n][OC][OH][OW], both 16-byte aligned; part: [conv_wgrad_s1_bf16x6_blocks(n)][OC][K + 1].
+// x: [n][C][H][W] and dy: [n][OC][OH][OW], both 16-byte aligned; part: [conv_wgrad_s1_f16_blocks(n)][OC][K + 1].
 template <class SP>
-inline hipError_t launch_conv_wgrad_s1_bf16x6(const float *x, const float *dy, float *part, int nframes, float scale,
+inline hipError_t launch_conv_wgrad_s1_f16(const float *x, const float *dy, float *part, int nframes, float scale,
                                               hipStream_t s, int rb = 0) {
     if (nframes <= 0) return hipSuccess;
-    typedef ConvWgradS1Bf16Geom<SP> G;
+    typedef ConvWgradS1Geom<SP> G;
     static bool attr_set = false;          // once per layer shape: let the kernels use more than 64 KB of LDS
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)conv_wgrad_s1_bf16x6_kernel<SP, false>,
+        hipError_t e = hipFuncSetAttribute((const void *)conv_wgrad_s1_f16_kernel<SP, false>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(false));
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)conv_wgrad_s1_bf16x6_kernel<SP, true>,
+            e = hipFuncSetAttribute((const void *)conv_wgrad_s1_f16_kernel<SP, true>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, G::lds_bytes(true));
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const dim3 grid(conv_wgrad_s1_bf16x6_blocks<SP>(nframes), SP::OC / 32);
+    const dim3 grid(conv_wgrad_s1_f16_blocks<SP>(nframes), SP::OC / 32);
     if (rb)
-        ga3c::launch((conv_wgrad_s1_bf16x6_kernel<SP, true>), grid, dim3(256), G::lds_bytes(true), s, x, dy, part, nframes, scale);
+        ga3c::launch((conv_wgrad_s1_f16_kernel<SP, true>), grid, dim3(256), G::lds_bytes(true), s, x, dy, part, nframes, scale);
     else
-        ga3c::launch((conv_wgrad_s1_bf16x6_kernel<SP, false>), grid, dim3(256), G::lds_bytes(false), s, x, dy, part, nframes, scale);
+        ga3c::launch((conv_wgrad_s1_f16_kernel<SP, false>), grid, dim3(256), G::lds_bytes(false), s, x, dy, part, nframes, scale);
     return hipGetLastError();
 }
 

@@ -32,9 +32,9 @@
 #include "conv_fwd_bf16x6.hpp"
 #include "conv123_f16.hpp"
 #include "conv_dgrad_bf16x6.hpp"
-#include "conv_grads_bf16x6.hpp"
-#include "conv_wgrad_bf16x6.hpp"
-#include "conv_wgrad_s1_bf16x6.hpp"
+#include "conv_grads.hpp"
+#include "conv_wgrad_f16.hpp"
+#include "conv_wgrad_s1_f16.hpp"
 #include "conv_band.hpp"
 #include "conv_bytes.hpp"
 #include "conv_band_f32.hpp"
@@ -2962,28 +2962,28 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
                                      : band_nz > 0 ? 8
                                      : c->band[l] && f32_wgrad_ok(g.C, g.H, g.W, g.S, g.OC) ? 7 : 0;
             if (kind == 1 || kind == 2) nz = conv1_wgrad_blocks(B);
-            else if (kind == 3) nz = conv_wgrad_bf16x6_blocks<SpecS2>(B);
-            else if (kind == 4) nz = conv_wgrad_bf16x6_blocks<SpecL2>(B);
-            else if (kind == 5) nz = conv_wgrad_s1_bf16x6_blocks<SpecL3>(B);
-            else if (kind == 6) nz = conv_wgrad_bf16x6_blocks<SpecP2>(B);
+            else if (kind == 3) nz = conv_wgrad_f16_blocks<SpecS2>(B);
+            else if (kind == 4) nz = conv_wgrad_f16_blocks<SpecL2>(B);
+            else if (kind == 5) nz = conv_wgrad_s1_f16_blocks<SpecL3>(B);
+            else if (kind == 6) nz = conv_wgrad_f16_blocks<SpecP2>(B);
             else if (kind == 8) nz = band_nz;
             else pick_split(conv_like_tiles(g.OC, g.K + 1), B * g.OHW, nz, kchunk);
             float *part = region((size_t)nz * g.OC * (g.K + 1));
             if (!part) return fail(GA3C_EINVAL, "internal: split-k workspace too small (conv)");
-            // the 4x4 stride-2 layers' two gradients share a launch (conv_grads_bf16x6.hpp)
+            // the 4x4 stride-2 layers' two gradients share a launch (conv_grads.hpp)
             if ((kind == 3 || kind == 4 || kind == 6) && is_aligned16(th + c->off[2 * l])) {
                 STAGE2(CONV_DGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, 4.0 * B * (g.OC * g.OHW + 2.0 * g.C * g.H * g.W),
                        CONV_WGRAD[l], 2.0 * B * g.OHW * g.OC * g.K, (double)B * (4.0 * g.CHW + 4.0 * g.OC * g.OHW));
                 const float *x = (const float *)xin, *dy = c->dact[l], *wl = th + c->off[2 * l];
                 // the fragments of the copy being trained on, when the context keeps them
                 if (kind == 3)
-                    HIP_TRY(launch_conv_grads_bf16x6<SpecS2>(x, dy, wl, c->cfrag[cur] && c->cfrag_dgrad ? c->cfrag[cur] + CFRAG_FWD_VECS : nullptr,
+                    HIP_TRY(launch_conv_grads<SpecS2>(x, dy, wl, c->cfrag[cur] && c->cfrag_dgrad ? c->cfrag[cur] + CFRAG_FWD_VECS : nullptr,
                                                              c->dact[l - 1], part, B, s, c->rb));
                 else if (kind == 4)
-                    HIP_TRY((launch_conv_grads_bf16x6<SpecL2, 32>(x, dy, wl, c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr,
+                    HIP_TRY((launch_conv_grads<SpecL2, 32>(x, dy, wl, c->lfrag[cur] && l == 1 ? c->lfrag[cur] + LFRAG_DGRAD2 : nullptr,
                                                                   c->dact[l - 1], part, B, s, c->rb)));
                 else
-                    HIP_TRY(launch_conv_grads_bf16x6<SpecP2>(x, dy, wl, nullptr, c->dact[l - 1], part, B, s, c->rb));
+                    HIP_TRY(launch_conv_grads<SpecP2>(x, dy, wl, nullptr, c->dact[l - 1], part, B, s, c->rb));
                 add_seg(part, nz, g.OC, g.K + 1, 0, g.OC, c->grad + c->off[2 * l], c->grad + c->off[2 * l + 1], 1);
                 continue;
             }
@@ -2993,13 +2993,13 @@ static int train_step_impl(ga3c_ctx *c, const uint8_t *frames, const uint8_t *co
             } else if (kind == 2) {
                 HIP_TRY(launch_conv1_wgrad<32>((const uint8_t *)xin, table, c->dact[l], part, B, 1.f / 255.f, s, c->rb));
             } else if (kind == 3) {
-                HIP_TRY(launch_conv_wgrad_bf16x6<SpecS2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
+                HIP_TRY(launch_conv_wgrad_f16<SpecS2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 4) {
-                HIP_TRY((launch_conv_wgrad_bf16x6<SpecL2, 32>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb)));
+                HIP_TRY((launch_conv_wgrad_f16<SpecL2, 32>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb)));
             } else if (kind == 5) {
-                HIP_TRY(launch_conv_wgrad_s1_bf16x6<SpecL3>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
+                HIP_TRY(launch_conv_wgrad_s1_f16<SpecL3>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 6) {
-                HIP_TRY(launch_conv_wgrad_bf16x6<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
+                HIP_TRY(launch_conv_wgrad_f16<SpecP2>((const float *)xin, c->dact[l], part, B, 1.f, s, c->rb));
             } else if (kind == 7) {
                 if (g.OC == 16) HIP_TRY((launch_conv_f32_wgrad<16>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));
                 else HIP_TRY((launch_conv_f32_wgrad<32>(frames, c->dact[l], part, B, g.C, g.H, g.W, g.S, nz, kchunk, 1.f / 255.f, s, c->rb)));

@@ -6,13 +6,13 @@
 // v_mfma_f32_16x16x32_f16: three instructions where three bfloat16 terms take six, with two thirds of the operands.  The
 // fp32 accumulator rounds half as often, which is what the error of a sum of some hundred products consists of.
 //
-// The scale brings the largest magnitude of a row or a tensor to [2^14, 2^15).  Numbers far below it keep an absolute error
-// of 2^-40 of that largest one (float16 has no smaller steps than 2^-24, and the instruction takes them as they are).
+// The scale brings the largest magnitude of a row or a tensor to [2^14, 2^15).  Numbers below 2^-17 of it are held to 2^-39 of it
+// (float16's steps are 2^-24 at least, and the instruction takes such terms as they are).  So a scale is for numbers that go into the same
+// sums, and what is contracted against it must not undo its size: filters have one each, a map one as long as its channels are not
+// far apart (F16_APART), the operands of weight gradients one for each filter and each channel.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-
-#include <type_traits>
 
 #include "conv1_bf16x3.hpp"
 
