@@ -72,13 +72,13 @@ TIMED_BLOCKS = 10
 # 0.5000 and 1.0000 of the known bytes, hence the scale factors.  The summary is kept under profiles/.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 COUNTER_KIB = {   # stage: {frames per launch: (FETCH_SIZE, WRITE_SIZE)}; two stages of one launch have no figure of their own
-    "conv12_fwd": {512: (7567.0, 5184.0), 1024: (14640.0, 10370.0), 2560: (35850.0, 89930.0)},   # 2560: training, keeps y1
-    "fc_fwd": {512: (4553.0, 7168.0), 1024: (7145.0, 8192.0), 2560: (14940.0, 20480.0)},
-    "heads_fwd": {512: (3733.0, 80.0), 1024: (4228.0, 80.0)},
-    "heads_train": {2560: (10520.0, 15840.0)},
-    "conv1_wgrad": {2560: (67610.0, 4112.0)},
-    "wgrad_reduce": {2560: (24280.0, 2715.0)},
-    "rmsprop": {2560: (4076.0, 9385.0)},
+    "conv12_fwd": {512: (7360.0, 5184.0), 1024: (14432.0, 10368.0), 2560: (35857.0, 89926.0)},   # 2560: training, keeps y1
+    "fc_fwd": {512: (4559.0, 7168.0), 1024: (7150.0, 8192.0), 2560: (15056.0, 20480.0)},
+    "heads_fwd": {512: (3733.0, 80.0), 1024: (4222.0, 80.0)},
+    "heads_train": {2560: (10496.0, 15810.0)},
+    "conv1_wgrad": {2560: (67586.0, 4112.0)},
+    "wgrad_reduce": {2560: (20162.0, 2710.0)},
+    "rmsprop": {2560: (4077.0, 9426.0)},
 }
 
 # HIP kernel behind each stage of the small net's fast path, and the larger net's
@@ -93,7 +93,7 @@ KERNELS = {"conv12_fwd": "conv12_f16_kernel (predictions), conv12_fused_fwd_kern
 # terms (the lower figure where one operand is bytes); "f32" = the stage runs on the fp32 matrix cores.  conv123_fwd has 2 products in
 # its first layer and 3 in the others.
 TERMS = {"conv123_fwd": 2.58, "conv1_fwd": 3, "conv2_fwd": 6, "conv3_fwd": 6, "fc_fwd": 6, "fc_wgrad": 6, "fc_dgrad": 6, "conv1_wgrad": 2,
-         "conv2_dgrad": 3, "conv3_dgrad": 6, "conv2_wgrad": 3, "conv3_wgrad": 3}
+         "conv2_dgrad": 6, "conv3_dgrad": 6, "conv2_wgrad": 3, "conv3_wgrad": 3}
 HBM_STAGES = {"rmsprop", "wgrad_reduce"}
 
 

@@ -76,7 +76,19 @@ typedef struct ga3c_ctx ga3c_ctx;   /* opaque: parameters, RMSProp state, gradie
  * after each hidden layer, a softmax policy output and a linear value
  * output.  Convolutions are VALID cross-correlations.  Limits: n_conv in
  * [1,4]; n_actions in [1,63]; (n_actions + 5) * (fc_units + 16) <= 40960 (the
- * heads keep their weights in LDS); every spatial size must stay >= 1. */
+ * heads keep their weights in LDS); every spatial size must stay >= 1.
+ * Arithmetic, math = 0: sums are fp32's; an operand of a contraction is held
+ * to its 24 bits (three bfloat16 terms, or the fp32 instruction) or to 22 bits
+ * and a sign (two float16 terms under a common power of two: convolutions of
+ * predictions, weight gradients of the layers that have kernels of their own),
+ * the latter where results are no further from exact sums for it.  Two terms
+ * lose bits of values below 2^-15 of the largest one under the same scale, so
+ * a filter, and in gradients a channel, has its own.  Parameters that do not
+ * suit them are found by the library: a filter of whose weights more than
+ * eight, or one in 32, are below 2^-18 of its largest, and channels whose
+ * sizes, by their filters and biases, lie further apart than 2^10.
+ * Predictions with such parameters run their convolutions on the fp32
+ * instruction, in two to three times the time. */
 typedef struct {
     int in_c, in_h, in_w;                 /* input planes / height / width (4, 84, 84) */
     int n_conv;

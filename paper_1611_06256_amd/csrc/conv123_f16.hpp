@@ -18,10 +18,10 @@
 // k-block, so that no layer waits for its filters.
 //
 // Bound by one frame's chain through a compute unit: bytes in, three layers and six barriers.  us a call (with the fc layer and the heads
-// behind it) against a kernel per layer on three bfloat16 terms or the fp32 instruction: larger net 1 frame 26.4 -> 21.8, 64: 28.8 ->
-// 23.2, 128: 36.9 -> 25.6, 256: 47.1 -> 29.4, 512: 71.4 -> 44.8, 1024: 116 -> 80; stride-4 member 1: 23.1 -> 18.3, 128: 34.4 -> 19.8, 256:
-// 41.0 -> 20.7; stride-3 member 1: 23.4 -> 21.0, 64: 30.6 -> 22.6, 128: 37.9 -> 22.9, 256: 47.1 -> 25.6, 512: 69.1 -> 40.0.  Error of the
-// logits against 64 bits (2-norm, 256 frames) 5.1e-7 -> 4.4e-7, 5.4e-7 -> 5.1e-7, 4.9e-7 -> 4.6e-7.
+// behind it) against a kernel per layer on three bfloat16 terms or the fp32 instruction: larger net 1 frame 27.6 -> 21.9, 64: 29.8 ->
+// 23.5, 128: 37.3 -> 25.7, 256: 47.1 -> 29.0, 512: 69.9 -> 44.8, 1024: 113 -> 78; stride-4 member 1: 24.4 -> 18.7, 128: 35.0 -> 20.4, 256:
+// 41.1 -> 21.2; stride-3 member 1: 23.5 -> 22.0, 64: 31.9 -> 23.9, 128: 38.3 -> 25.2, 256: 47.3 -> 26.0, 512: 69.1 -> 41.6.  Error of the
+// logits against 64 bits (2-norm, 130 frames) 5.3e-7 -> 4.4e-7, 4.4e-7 -> 3.9e-7, 4.9e-7 -> 4.4e-7.
 //
 // Updates keep the layers' own kernels: another rounding of a sum puts a pre-activation next to zero on the other side of the
 // rectifier now and then, and a map's gradients with it.

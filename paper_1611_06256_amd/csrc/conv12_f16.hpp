@@ -5,15 +5,16 @@
 // accumulators of their own.  A block takes a frame at a time, first layer 1, then layer 2, with its filters of both in registers for
 // the whole launch.  Frames come to LDS as the bytes they are, the next one while this one is worked on.  Layer 1's map is scaled by
 // the largest value that it can have with these filters (sum of a filter's positive weights and its bias; a byte is 1 at most), so nobody
-// has to look for the one that it has: some bits of the scale are lost, of forty to spare.
+// has to look for the one that it has: some bits of the scale are lost, of those to spare (F16_APART).
 //
 // The map: [term][pixel][16 channels], even and odd columns of a row apart; a k-block of layer 2 is two neighbouring taps of a
 // filter row, one of layer 1 four rows of a plane.
 //
-// Bound by vector instructions next to the products (bytes to float16, splitting, rectifiers: the two add up on a SIMD) and, with one
-// frame a block, by its chain of latencies.  us a call, with the fc layer and the heads behind it, against conv12_fused.hpp's pipeline on
-// three bfloat16 terms: 65 frames 16.7 -> 15.8, 128: 18.0 -> 16.8, 256: 20.3 -> 19.4, 512: 28.2 -> 25.5, 1024: 37.9 -> 32.1, 2048: 62.8 ->
-// 53.4.  Error of the logits against 64 bits (2-norm, 256 frames) 2.9e-7 -> 2.7e-7; with one accumulator 3.2e-7.  Built and taken out:
+// Bound by vector instructions next to the products (bytes to float16, splitting, rectifiers: 25 % and 18 % of the SIMD cycles at
+// 1024 frames, and the two add up) and, with one frame a block, by its chain of latencies.  us a call, with the fc layer and the heads behind
+// it, against conv12_fused.hpp's pipeline on three bfloat16 terms: 65 frames 17.2 -> 16.9, 128: 18.6 -> 18.2, 256: 20.5 -> 20.4, 512: 28.0 ->
+// 26.5, 1024: 36.5 -> 33.2, 2048: 62.4 -> 56.6 (bytes as subnormal numbers, 1024 frames 31.5, are not exact enough: split_f16.hpp).  Error of
+// the logits against 64 bits (2-norm, 130 frames) 3.1e-7 -> 2.8e-7; with one accumulator a tenth more.  Built and taken out:
 // blocks of four wavefronts, two to a compute unit (1024 frames 35.1); one barrier per frame, layer 2 of the last frame beside layer 1 of
 // this one (33.5); frames as float16 in LDS (34.8).
 #pragma once

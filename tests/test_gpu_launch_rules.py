@@ -19,7 +19,7 @@ def G():
 
 @pytest.mark.parametrize("A,batches", [(18, (1, 2, 5, 6, 10, 11, 21, 22, 42, 43, 64, 65)), (63, (4, 9, 20, 41, 64))])
 def test_small_net_predictions_across_the_splits_of_a_frame(G, A, batches):
-    # up to 64 frames one launch; the slices of the fc layer per frame and the frames per block change with the batch,
+    # up to 42 frames one launch, 21 with 63 actions; the slices of the fc layer per frame and the frames per block change with the batch,
     # and many actions leave no room in LDS for two frames
     for B in batches:
         P.check_predict(G, G.SMALL_NET(A), B, 7000 + B)

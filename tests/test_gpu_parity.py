@@ -633,8 +633,8 @@ def test_ragged_argument_errors(G):
 
 @pytest.mark.parametrize("math", [0, 1])
 def test_handful_of_frames_in_one_launch(G, math):
-    # up to 64 frames of the small net go out as one kernel (convolutions, fc, heads, draw; 32 blocks per frame up to
-    # 8 frames, 16 up to 16, 8 up to 32, 4 up to 64); more frames take the three-kernel path.  Both compute the same
+    # up to 42 frames of the small net go out as one kernel (convolutions, fc, heads, draw; three row groups of a frame and
+    # 16, 8 or 4 slices of the fc layer up to 5, 10 and 42 frames); more take the three-kernel path.  Both compute the same
     # numbers up to summation order, call after call (the kernel's ticket counters must be back at zero after every
     # launch), in any order of batch sizes.
     import torch
@@ -673,7 +673,7 @@ def test_handful_of_frames_in_one_launch(G, math):
 @pytest.mark.parametrize("math", [0, 1])
 @pytest.mark.parametrize("B", [17, 32, 33, 64])
 def test_one_launch_prediction_17_to_64_frames_against_the_oracle(G, B, math):
-    # the batch sizes that used to take three launches, element by element against the oracle
+    # batches in the upper half of one launch and beyond it, element by element against the oracle
     import dataclasses
     check_predict(G, dataclasses.replace(G.SMALL_NET(18), math=math), B, 8400 + B, frames=synth.rectangle_frames(8400 + B, B))
 
